@@ -342,6 +342,150 @@ __global__ __launch_bounds__(256) void k_gen_dct(const double* __restrict__ Cm, 
       }
 }
 
+// DCT-II / its inverse of a power-of-two length N in O(N log N), fp64, one channel independent of every other.
+// Forward (a real DCT through a complex FFT of half the length): v = (x[0], x[2], .., x[3], x[1]); t[n] = v[2n] +
+// i v[2n+1]; T = FFT of M = N / 2 points; V[k] = Fe + e^{-2 pi i k / N} Fo with Fe, Fo the even and odd parts that T
+// packs; C[k] = sqrt(2/N) Re(e^{-i pi k / 2N} V[k]), C[N-k] = -sqrt(2/N) Im(same).  The inverse runs these steps
+// backwards.  The FFT is in place in LDS, decimation in time (the load puts every point at its bit-reversed place),
+// two radix-2 stages per pass.
+// What bounds it: LDS, 16 N bytes per channel and pass; the dense fp64 product it replaces runs 2 N^2 operations per
+// channel on the fp64 matrix pipe (N = 2048, 4096 channels: 992 us per transform, this kernel 41 and 39).
+// A workgroup holds 2^chlog neighbouring channels, as many as 128 KB of LDS take (8 N bytes each), at most 32.
+// tab: e^{-2 pi i k / M}, k < M, then e^{-i pi k / 2N}, k <= M, then e^{-2 pi i k / N}, k <= M.
+struct cd {
+  double re, im;
+};
+__device__ __forceinline__ cd c_add(cd a, cd b) { return {a.re + b.re, a.im + b.im}; }
+__device__ __forceinline__ cd c_sub(cd a, cd b) { return {a.re - b.re, a.im - b.im}; }
+__device__ __forceinline__ cd c_mul(cd a, cd b) {
+  return {__builtin_fma(a.re, b.re, -(a.im * b.im)), __builtin_fma(a.re, b.im, a.im * b.re)};
+}
+__device__ __forceinline__ cd c_conj(cd a) { return {a.re, -a.im}; }
+
+template <bool INV>
+__device__ __forceinline__ void lds_fft(cd* s, const cd* __restrict__ tw, int m, int chlog, int tid, int nthr) {
+  const int M = 1 << m, CH = 1 << chlog;
+  int lg = 0;  // the sub-transforms have 2^lg points
+  if (m & 1) {
+    for (int u = tid; u < (M >> 1) * CH; u += nthr) {
+      const int ch = u & (CH - 1), j = u >> chlog;
+      cd* a = s + ((2 * j) << chlog) + ch;
+      const cd x = a[0], y = a[CH];
+      a[0] = c_add(x, y);
+      a[CH] = c_sub(x, y);
+    }
+    lg = 1;
+    __syncthreads();
+  }
+  for (; lg < m; lg += 2) {
+    const int L = 1 << lg;
+    for (int u = tid; u < (M >> 2) * CH; u += nthr) {
+      const int ch = u & (CH - 1), q = u >> chlog;
+      const int j = q & (L - 1), base = ((q >> lg) << (lg + 2)) + j;
+      cd* a = s + (base << chlog) + ch;
+      const int st = L << chlog;
+      cd w = tw[j << (m - lg - 1)], v = tw[j << (m - lg - 2)];
+      if constexpr (INV) {
+        w.im = -w.im;
+        v.im = -v.im;
+      }
+      const cd a0 = a[0], a1 = c_mul(w, a[st]), a2 = a[2 * st], a3 = c_mul(w, a[3 * st]);
+      const cd b0 = c_add(a0, a1), b1 = c_sub(a0, a1), b2 = c_mul(v, c_add(a2, a3)), t3 = c_mul(v, c_sub(a2, a3));
+      const cd b3 = INV ? cd{-t3.im, t3.re} : cd{t3.im, -t3.re};  // +- i v
+      a[0] = c_add(b0, b2);
+      a[2 * st] = c_sub(b0, b2);
+      a[st] = c_add(b1, b3);
+      a[3 * st] = c_sub(b1, b3);
+    }
+    __syncthreads();
+  }
+}
+
+template <bool INV>
+__global__ __launch_bounds__(1024) void k_gen_dct_fft(const cd* __restrict__ tab, const void* __restrict__ src, int in_kind,
+                                                      float* __restrict__ T, void* __restrict__ Y,
+                                                      const float* __restrict__ bias, int y_bf16, int lgn, int ld, int chlog) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t dct_smem[];
+  cd* const s = reinterpret_cast<cd*>(dct_smem);  // [M][CH]
+  double* const sd = reinterpret_cast<double*>(dct_smem);
+  const int N = 1 << lgn, m = lgn - 1, M = 1 << m, CH = 1 << chlog;
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  // neighbouring channel groups share cache lines: keep them on one XCD
+  const int ngrp = gridDim.x, xcd = blockIdx.x & 7, tall = ngrp >> 3, rem = ngrp & 7;
+  const int grp = xcd * tall + min(xcd, rem) + (int)(blockIdx.x >> 3);
+  const int c0 = grp << chlog;
+  const size_t bo = (size_t)blockIdx.y * N * ld;
+  const cd *tw = tab, *te = tab + M, *tn = te + M + 1;
+  const double nrm = sqrt(2.0 / N);
+  if constexpr (!INV) {
+    for (int u = tid; u < N * CH; u += nthr) {
+      const int ch = u & (CH - 1), n = u >> chlog, c = c0 + ch;
+      const double x = c < ld ? (double)gen_load(src, in_kind, bo + (size_t)n * ld + c) : 0.0;
+      const int nv = (n & 1) ? N - 1 - (n >> 1) : (n >> 1);
+      const int pos = m > 0 ? (int)(__brev((unsigned)(nv >> 1)) >> (32 - m)) : 0;
+      sd[2 * ((pos << chlog) + ch) + (nv & 1)] = x;
+    }
+    __syncthreads();
+    lds_fft<false>(s, tw, m, chlog, tid, nthr);
+    for (int u = tid; u < ((M >> 1) + 1) * CH; u += nthr) {
+      const int ch = u & (CH - 1), k = u >> chlog, c = c0 + ch;
+      if (c >= ld) continue;
+      float* o = T + bo + c;
+      if (k == 0) {
+        const cd t = s[ch];
+        o[0] = (float)((t.re + t.im) * sqrt(1.0 / N));
+        o[(size_t)M * ld] = (float)((t.re - t.im) * sqrt(0.5) * nrm);
+        continue;
+      }
+      const cd t = s[(k << chlog) + ch], r = c_conj(s[((M - k) << chlog) + ch]);
+      const cd fe = {0.5 * (t.re + r.re), 0.5 * (t.im + r.im)};
+      const cd df = {0.5 * (t.re - r.re), 0.5 * (t.im - r.im)};
+      const cd fo = {df.im, -df.re};  // - i (T[k] - conj T[M-k]) / 2
+      const cd g = c_mul(tn[k], fo);
+      const cd a = c_mul(te[k], c_add(fe, g));                   // e^{-i pi k / 2N} V[k]
+      const cd b = c_mul(te[M - k], c_conj(c_sub(fe, g)));       // the same of V[M-k] = conj(Fe - e^{..} Fo)
+      o[(size_t)k * ld] = (float)(nrm * a.re);
+      o[(size_t)(N - k) * ld] = (float)(-nrm * a.im);
+      o[(size_t)(M - k) * ld] = (float)(nrm * b.re);
+      o[(size_t)(M + k) * ld] = (float)(-nrm * b.im);
+    }
+  } else {
+    const float* S = static_cast<const float*>(src);
+    const double sc = sqrt(0.5 * N) / M;
+    for (int u = tid; u < ((M >> 1) + 1) * CH; u += nthr) {
+      const int ch = u & (CH - 1), k = u >> chlog, c = c0 + ch;
+      cd tk = {0.0, 0.0}, tr = {0.0, 0.0};
+      if (c < ld) {
+        const float* i = S + bo + c;
+        if (k == 0) {
+          const double v0 = (double)i[0] * (sqrt((double)N) / M), vm = (double)i[(size_t)M * ld] * (sc * sqrt(2.0));
+          tk = {0.5 * (v0 + vm), 0.5 * (v0 - vm)};
+        } else {
+          const cd a = {sc * (double)i[(size_t)k * ld], -sc * (double)i[(size_t)(N - k) * ld]};
+          const cd b = {sc * (double)i[(size_t)(M - k) * ld], -sc * (double)i[(size_t)(M + k) * ld]};
+          const cd va = c_mul(c_conj(te[k]), a), vb = c_conj(c_mul(c_conj(te[M - k]), b));  // V[k], conj V[M-k] = V[k+M]
+          const cd fe = {0.5 * (va.re + vb.re), 0.5 * (va.im + vb.im)};
+          const cd fo = c_mul(c_conj(tn[k]), cd{0.5 * (va.re - vb.re), 0.5 * (va.im - vb.im)});
+          tk = {fe.re - fo.im, fe.im + fo.re};   // Fe + i Fo
+          tr = {fe.re + fo.im, fo.re - fe.im};   // conj Fe + i conj Fo
+        }
+      }
+      const int pk = m > 0 ? (int)(__brev((unsigned)k) >> (32 - m)) : 0;
+      s[(pk << chlog) + ch] = tk;
+      if (k != 0 && 2 * k != M) s[((int)(__brev((unsigned)(M - k)) >> (32 - m)) << chlog) + ch] = tr;
+    }
+    __syncthreads();
+    lds_fft<true>(s, tw, m, chlog, tid, nthr);
+    for (int u = tid; u < N * CH; u += nthr) {
+      const int ch = u & (CH - 1), n = u >> chlog, c = c0 + ch;
+      if (c >= ld) continue;
+      const int nv = (n & 1) ? N - 1 - (n >> 1) : (n >> 1);
+      const float v = (float)sd[2 * (((nv >> 1) << chlog) + ch) + (nv & 1)];
+      gen_store_y(Y, y_bf16, bo + (size_t)n * ld + c, v + (bias != nullptr ? bias[c] : 0.0f));
+    }
+  }
+}
+
 __global__ void k_gen_dct_matrix(double* __restrict__ Cm, int s) {
   const int n = blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;
   if (n >= s) return;
@@ -585,6 +729,10 @@ void stamp_gen_plan_free(stamp_plan* p) {
 }
 
 namespace {
+// Lengths whose DCT runs through the FFT: powers of two from 8 on (a channel's N / 2 complex points have to fit LDS:
+// N <= 16384, which is also the longest DCT of the library); other lengths take the dense product.
+bool dct_has_fft(int s) { return s >= 8 && s <= 16384 && (s & (s - 1)) == 0; }
+
 // l = L 1 in fp32, following the forward transform's operation order (host)
 std::vector<float> ell_of(const stamp_plan* p) {
   const StampGen& gn = p->gen;
@@ -671,7 +819,20 @@ hipError_t stamp_gen_plan_tables(stamp_plan* p, const float* W, hipStream_t st) 
     }
     if ((e = upload(&p->perm_dev, inv, st)) != hipSuccess) return e;
   }
-  if (gn.kind == kGenDct) {
+  if (gn.kind == kGenDct && dct_has_fft(s)) {
+    // e^{-2 pi i k / M}, k < M; e^{-i pi k / 2N}, k <= M; e^{-2 pi i k / N}, k <= M (M = N / 2)
+    const int M = s / 2;
+    std::vector<double> tab;
+    auto put = [&](double frac) {  // e^{-2 pi i frac}
+      const long double a = 2.0L * 3.14159265358979323846264338327950288L * (long double)frac;
+      tab.push_back((double)std::cos(a));
+      tab.push_back((double)-std::sin(a));
+    };
+    for (int k = 0; k < M; ++k) put((double)k / M);
+    for (int k = 0; k <= M; ++k) put((double)k / (4.0 * s));
+    for (int k = 0; k <= M; ++k) put((double)k / s);
+    if ((e = upload(&p->dct_dev, tab, st)) != hipSuccess) return e;
+  } else if (gn.kind == kGenDct) {
     if ((e = hipMalloc(reinterpret_cast<void**>(&p->dct_dev), sizeof(double) * (size_t)s * s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_gen_dct_matrix, dim3((s + 255) / 256, s), dim3(256), 0, st, p->dct_dev, s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -721,6 +882,28 @@ template <int NLEV>
 void launch_wht(dim3 grid, hipStream_t st, const void* in, int in_kind, float* out, void* Y, int out_kind, const int* inv_perm, float norm,
                 const float* bias, int y_bf16, int s, int ld, int h_lo) {
   hipLaunchKernelGGL(k_gen_wht<NLEV>, grid, dim3(rows_block(ld, grid.y, grid.z)), 0, st, in, in_kind, out, Y, out_kind, inv_perm, norm, bias, y_bf16, s, ld, h_lo);
+}
+
+// DCT of a power-of-two length; forward (inv = 0): src -> T, inverse: src (fp32) -> Y (+ bias)
+hipError_t launch_dct_fft(const stamp_plan* p, int inv, const void* src, int in_kind, float* T, void* Y, const float* bias, int ld,
+                          hipStream_t st) {
+  const int s = p->geom.s, B = p->geom.B;
+  int lgn = 0, chlog = 5;
+  while ((1 << lgn) < s) ++lgn;
+  while (chlog > 0 && ((size_t)8 * s << chlog) > 128 * 1024) --chlog;
+  // fewer channels per workgroup while the chip is short of workgroups, down to 4 (16-byte runs of a row)
+  while (chlog > 2 && (size_t)((ld + (1 << chlog) - 1) >> chlog) * B < 256) --chlog;
+  const size_t lds = (size_t)8 * s << chlog;
+  const int items = (s / 8) << chlog, nthr = items >= 1024 ? 1024 : items >= 512 ? 512 : 256;
+  const dim3 grid((ld + (1 << chlog) - 1) >> chlog, B);
+  static size_t done[2][kStampMaxDevices] = {};
+  const cd* tab = reinterpret_cast<const cd*>(p->dct_dev);
+  const void* fn = inv ? reinterpret_cast<const void*>(&k_gen_dct_fft<true>) : reinterpret_cast<const void*>(&k_gen_dct_fft<false>);
+  const hipError_t e = stamp_allow_lds(fn, lds, done[inv]);
+  if (e != hipSuccess) return e;
+  if (inv) hipLaunchKernelGGL(k_gen_dct_fft<true>, grid, dim3(nthr), lds, st, tab, src, in_kind, T, Y, bias, p->geom.y_bf16, lgn, ld, chlog);
+  else hipLaunchKernelGGL(k_gen_dct_fft<false>, grid, dim3(nthr), lds, st, tab, src, in_kind, T, Y, bias, 0, lgn, ld, chlog);
+  return hipGetLastError();
 }
 
 // slot of band W of 2-D level l: the final low-low block and the bands of the coarser levels come first
@@ -829,6 +1012,7 @@ hipError_t stamp_gen_forward(const stamp_plan* p, const void* X, float* const (&
     }
     return hipGetLastError();
   }
+  if (gn.kind == kGenDct && dct_has_fft(s)) return launch_dct_fft(p, 0, X, xk, T, nullptr, nullptr, d, st);
   if (gn.kind == kGenDct) {
     hipLaunchKernelGGL(k_gen_cast, rows_grid(d, s, B), dim3(rows_block(d, s, B)), 0, st, X, buf[0], s, d, g.x_bf16);
     hipLaunchKernelGGL(k_gen_dct, dim3((d + 63) / 64, (s + 63) / 64, B), dim3(256), 0, st, p->dct_dev, 0, buf[0], T, s, d);
@@ -926,6 +1110,7 @@ hipError_t stamp_gen_inverse(const stamp_plan* p, float* const (&buf)[3], int nc
     }
     return hipGetLastError();
   }
+  if (gn.kind == kGenDct && dct_has_fft(s)) return launch_dct_fft(p, 1, S, 0, nullptr, Y, bias, ld, st);
   if (gn.kind == kGenDct) {
     hipLaunchKernelGGL(k_gen_dct, dim3((ld + 63) / 64, (s + 63) / 64, B), dim3(256), 0, st, p->dct_dev, 1, S, tmp[0], s, ld);
     hipLaunchKernelGGL(k_gen_store_y, rows_grid(ld, s, B), dim3(rows_block(ld, s, B)), 0, st, tmp[0], bias, Y, s, ld, g.y_bf16);

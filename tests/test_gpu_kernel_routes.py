@@ -1,0 +1,76 @@
+"""Edges of the kernels that serve only part of the plans: each case goes through the C ABI and is compared with the
+oracle (codes and scales bit for bit, outputs to the output bar)."""
+import numpy as np
+import pytest
+
+import stamp_testlib as tl
+from gen.workloads import Workload
+from oracle import stamp_oracle as so
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2510_26771_amd as st
+    st.load_library()
+
+
+def _wl(name, **kw):
+    base = dict(batch=1, seq_len=256, d_in=128, d_out=192, xform="haar1d", levels=3, k_hi=16, x_dtype="f32", rho=0.9,
+                n_outlier_channels=3, outlier_scale=20.0, w_std=0.05, seed=11)
+    base.update(kw)
+    return Workload(name, **base)
+
+
+# ---- DCT of power-of-two lengths (FFT): odd and even numbers of radix-2 stages, one and several channels per
+# workgroup, the shortest length of the route and the longest of the library
+DCT = [_wl("dct_8", batch=2, xform="dct", levels=0, seq_len=8, k_hi=1, seed=201),
+       _wl("dct_16_bf16", xform="dct", levels=0, seq_len=16, k_hi=2, x_dtype="bf16", seed=202),
+       _wl("dct_512", batch=3, xform="dct", levels=0, seq_len=512, d_in=160, d_out=131, seed=203),
+       _wl("dct_1024_asym", xform="dct", levels=0, seq_len=1024, act_quant="asym", mean_shift=0.5, seed=204)]
+
+
+@pytest.mark.parametrize("w", DCT, ids=[w.name for w in DCT])
+def test_dct_of_power_of_two_lengths(w):
+    tl.full_case(w, with_bias=True, check_unfused=False)
+
+
+@pytest.mark.parametrize("s", [8, 64, 2048, 4096, 16384])
+def test_dct_inverse_against_the_dense_product(s):
+    """stamp_inverse of an odd number of columns: fp64 all the way, one rounding at the end.  Both sides are fp64 sums (the
+    dense one carries the rounding of its angles, up to 2^-52 pi s, into the cosines), so they agree to 2^-24 of the
+    column plus that."""
+    import torch
+    import paper_2510_26771_amd as st
+    w = _wl(f"inv_dct_{s}", batch=2 if s <= 64 else 1, seq_len=s, xform="dct", levels=0, k_hi=1, d_in=32, d_out=37)
+    W = torch.zeros((32, 37), dtype=torch.float32, device="cuda")
+    plan = st.StampPlan(tl.plan_desc_for(w, "f32"), W)
+    rng = np.random.default_rng(s)
+    Yt = rng.standard_normal((w.batch, s, 37)).astype(np.float32)
+    Yt[:, :, 5] *= 1e6  # a channel's error stays its own
+    cols = [0, 5, 36]
+    if s <= 4096:
+        ref = np.stack([so.dct_matrix(s).T @ Yt[b][:, cols].astype(np.float64) for b in range(w.batch)])
+    else:
+        n = np.arange(s, dtype=np.float64)
+        k = np.arange(s, dtype=np.int64)
+        ref = np.zeros((w.batch, s, len(cols)))
+        for lo in range(0, s, 1024):  # angles reduced to one turn as integers
+            ang = ((2 * np.arange(lo, lo + 1024, dtype=np.int64)[:, None] + 1) * k[None, :]) % (4 * s)
+            C = np.cos(np.pi * ang / (2.0 * s)) * np.sqrt(2.0 / s)
+            C[:, 0] = np.sqrt(1.0 / s)
+            ref[0, lo:lo + 1024] = C @ Yt[0][:, cols].astype(np.float64)
+        del n
+    one = -(-(w.batch * s * 37 * 4) // 256) * 256
+    ws = torch.empty(2 * one, dtype=torch.uint8, device="cuda")
+    Y = torch.empty((w.batch, s, 37), dtype=torch.float32, device="cuda")
+    plan.inverse(torch.from_numpy(Yt).cuda(), 37, Y, ws)
+    torch.cuda.synchronize()
+    y = Y.cpu().numpy()[:, :, cols].astype(np.float64)
+    bound = 2.0 ** -24 * np.abs(ref) + (s * 2.0 ** -50) * np.abs(ref).max(axis=(0, 1), keepdims=True)
+    assert (np.abs(y - ref) <= bound).all(), float((np.abs(y - ref) / bound).max())
+    plan.destroy()
