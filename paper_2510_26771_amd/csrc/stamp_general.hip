@@ -52,6 +52,21 @@ __global__ __launch_bounds__(256) void k_gen_cast(const void* __restrict__ X, fl
 __device__ __forceinline__ float gen_load(const void* in, int kind, size_t idx) {
   return kind == 2 ? __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(in)[idx] << 16) : reinterpret_cast<const float*>(in)[idx];
 }
+// n elements, `step` apart.  One branch on the type for all of them: a branch per element would make every load wait for
+// the one before it (s = 2048, 4096 channels, 32 rows per thread: WHT 41 -> 25 us).
+template <int n>
+__device__ __forceinline__ void gen_load_rows(const void* in, int kind, size_t idx, size_t step, float (&v)[n]) {
+  if (kind == 2) {
+    uint32_t w[n];
+#pragma unroll
+    for (int j = 0; j < n; ++j) w[j] = reinterpret_cast<const uint16_t*>(in)[idx + j * step];
+#pragma unroll
+    for (int j = 0; j < n; ++j) v[j] = __uint_as_float(w[j] << 16);
+  } else {
+#pragma unroll
+    for (int j = 0; j < n; ++j) v[j] = reinterpret_cast<const float*>(in)[idx + j * step];
+  }
+}
 __device__ __forceinline__ void gen_store_y(void* Y, int y_bf16, size_t idx, float v) {
   if (y_bf16) reinterpret_cast<uint16_t*>(Y)[idx] = f32_to_bf16_rne(v);
   else reinterpret_cast<float*>(Y)[idx] = v;
@@ -286,6 +301,90 @@ __global__ __launch_bounds__(256) void k_gen_wht(const void* __restrict__ in, in
   }
 }
 
+// STaMP slot (sequency) of row r of the Hadamard-ordered WHT of 2^J tokens: r = bit-reverse(gray(slot))
+__host__ __device__ __forceinline__ constexpr int wht_slot(int r, int J) {
+  int q = 0;
+  for (int b = 0; b < J; ++b) q |= ((r >> b) & 1) << (J - 1 - b);
+  for (int sh = 1; sh < J; sh <<= 1) q ^= q >> sh;
+  return q;
+}
+
+// The whole WHT of 2^(N1 + N2) tokens in one pass: a workgroup holds 2^chlog neighbouring channels of a sequence in LDS.
+// The stages with strides 1 .. 2^(N1-1) run in registers on rows read from memory, the others on rows read back from LDS
+// after one exchange: the same butterflies in the same order as the passes of k_gen_wht, which instead read and write
+// every element once per five stages.  Bound by memory: every element is read once and written once (s = 2048, 4096
+// channels: forward 13 us, inverse 16 us, against 51 and 41 us in three passes each).  Rows of LDS are shifted by one
+// row after every 2^N1, so that the writes of neighbouring blocks fall on different banks.
+template <int N1, int N2>
+__global__ __launch_bounds__(512) void k_gen_wht_lds(const void* __restrict__ in, int in_kind, float* __restrict__ out,
+                                                     void* __restrict__ Y, int out_kind, float norm,
+                                                     const float* __restrict__ bias, int y_bf16, int ld, int chlog) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t wht_smem[];
+  float* const s = reinterpret_cast<float*>(wht_smem);
+  constexpr int W1 = 1 << N1, W2 = 1 << N2, seq = W1 * W2;
+  const int CH = 1 << chlog, tid = threadIdx.x;
+  // neighbouring channel groups share cache lines: keep them on one XCD
+  const int ngrp = gridDim.x, xcd = blockIdx.x & 7, tall = ngrp >> 3, rem = ngrp & 7;
+  const int c0 = (xcd * tall + min(xcd, rem) + (int)(blockIdx.x >> 3)) << chlog;
+  const size_t bo = (size_t)blockIdx.y * seq * ld;
+  for (int u = tid; u < W2 * CH; u += 512) {
+    const int ch = u & (CH - 1), blk = u >> chlog, c = min(c0 + ch, ld - 1);
+    float v[W1];
+    gen_load_rows<W1>(in, in_kind, bo + (size_t)(blk * W1) * ld + c, (size_t)ld, v);
+#pragma unroll
+    for (int st = 0; st < N1; ++st) {
+#pragma unroll
+      for (int j = 0; j < W1; ++j) {
+        if ((j & (1 << st)) == 0) {
+          const float x = v[j], y = v[j + (1 << st)];
+          v[j] = __fadd_rn(x, y);
+          v[j + (1 << st)] = __fsub_rn(x, y);
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < W1; ++j) s[((blk * (W1 + 1) + j) << chlog) + ch] = v[j];
+  }
+  __syncthreads();
+  for (int u = tid; u < W1 * CH; u += 512) {
+    const int ch = u & (CH - 1), t = u >> chlog, c = c0 + ch;
+    float v[W2];
+#pragma unroll
+    for (int j = 0; j < W2; ++j) v[j] = s[((j * (W1 + 1) + t) << chlog) + ch];
+#pragma unroll
+    for (int st = 0; st < N2; ++st) {
+#pragma unroll
+      for (int j = 0; j < W2; ++j) {
+        if ((j & (1 << st)) == 0) {
+          const float x = v[j], y = v[j + (1 << st)];
+          v[j] = __fadd_rn(x, y);
+          v[j + (1 << st)] = __fsub_rn(x, y);
+        }
+      }
+    }
+    if (c < ld) {
+      // slot of row r = inverse Gray code of its bit reversal: linear over XOR, so the part of j is a constant
+      const int qt = wht_slot(t, N1 + N2);
+      if (out_kind == 1) {
+#pragma unroll
+        for (int j = 0; j < W2; ++j) out[bo + (size_t)(qt ^ wht_slot(j * W1, N1 + N2)) * ld + c] = __fmul_rn(v[j], norm);
+      } else {
+        const float bv = bias != nullptr ? bias[c] : 0.0f;
+        if (y_bf16) {
+#pragma unroll
+          for (int j = 0; j < W2; ++j)
+            reinterpret_cast<uint16_t*>(Y)[bo + (size_t)(qt ^ wht_slot(j * W1, N1 + N2)) * ld + c] =
+                f32_to_bf16_rne(__fmul_rn(v[j], norm) + bv);
+        } else {
+#pragma unroll
+          for (int j = 0; j < W2; ++j)
+            reinterpret_cast<float*>(Y)[bo + (size_t)(qt ^ wht_slot(j * W1, N1 + N2)) * ld + c] = __fmul_rn(v[j], norm) + bv;
+        }
+      }
+    }
+  }
+}
+
 // dst[k, c] = fl32( sum_n Mx[k, n] * src[n, c] ) in fp64 (Mx = C, or C^T when transposed), per batch, on the fp64
 // matrix pipeline: 64 x 64 outputs per workgroup of 4 waves (2 x 2), a wave 32 x 32 = 2 x 2 blocks of
 // v_mfma_f64_16x16x4_f64, 16 values of n per pass through LDS.  A lane feeds A[row lane % 16][n lane / 16] and
@@ -349,7 +448,7 @@ __global__ __launch_bounds__(256) void k_gen_dct(const double* __restrict__ Cm, 
 // backwards.  The FFT is in place in LDS, decimation in time (the load puts every point at its bit-reversed place),
 // two radix-2 stages per pass.
 // What bounds it: LDS, 16 N bytes per channel and pass; the dense fp64 product it replaces runs 2 N^2 operations per
-// channel on the fp64 matrix pipe (N = 2048, 4096 channels: 992 us per transform, this kernel 41 and 39).
+// channel on the fp64 matrix pipe (N = 2048, 4096 channels: 992 us per transform, this kernel 36 and 38).
 // A workgroup holds 2^chlog neighbouring channels, as many as 128 KB of LDS take (8 N bytes each), at most 32.
 // tab: e^{-2 pi i k / M}, k < M, then e^{-i pi k / 2N}, k <= M, then e^{-2 pi i k / N}, k <= M.
 struct cd {
@@ -363,7 +462,7 @@ __device__ __forceinline__ cd c_mul(cd a, cd b) {
 __device__ __forceinline__ cd c_conj(cd a) { return {a.re, -a.im}; }
 
 template <bool INV>
-__device__ __forceinline__ void lds_fft(cd* s, const cd* __restrict__ tw, int m, int chlog, int tid, int nthr) {
+__device__ __forceinline__ void lds_fft(cd* s, const cd* tw, int m, int chlog, int tid, int nthr) {
   const int M = 1 << m, CH = 1 << chlog;
   int lg = 0;  // the sub-transforms have 2^lg points
   if (m & 1) {
@@ -404,7 +503,8 @@ __device__ __forceinline__ void lds_fft(cd* s, const cd* __restrict__ tw, int m,
 template <bool INV>
 __global__ __launch_bounds__(1024) void k_gen_dct_fft(const cd* __restrict__ tab, const void* __restrict__ src, int in_kind,
                                                       float* __restrict__ T, void* __restrict__ Y,
-                                                      const float* __restrict__ bias, int y_bf16, int lgn, int ld, int chlog) {
+                                                      const float* __restrict__ bias, int y_bf16, int lgn, int ld, int chlog,
+                                                      int tw_lds) {
   extern __shared__ __attribute__((aligned(16))) uint8_t dct_smem[];
   cd* const s = reinterpret_cast<cd*>(dct_smem);  // [M][CH]
   double* const sd = reinterpret_cast<double*>(dct_smem);
@@ -417,24 +517,39 @@ __global__ __launch_bounds__(1024) void k_gen_dct_fft(const cd* __restrict__ tab
   const size_t bo = (size_t)blockIdx.y * N * ld;
   const cd *tw = tab, *te = tab + M, *tn = te + M + 1;
   const double nrm = sqrt(2.0 / N);
+  if (tw_lds) {  // the first M / 2 factors, all that the stages use, behind the points
+    cd* const t = s + ((size_t)M << chlog);
+    for (int u = tid; u < (M >> 1); u += nthr) t[u] = tab[u];
+    tw = t;
+  }
   if constexpr (!INV) {
-    for (int u = tid; u < N * CH; u += nthr) {
-      const int ch = u & (CH - 1), n = u >> chlog, c = c0 + ch;
-      const double x = c < ld ? (double)gen_load(src, in_kind, bo + (size_t)n * ld + c) : 0.0;
-      const int nv = (n & 1) ? N - 1 - (n >> 1) : (n >> 1);
-      const int pos = m > 0 ? (int)(__brev((unsigned)(nv >> 1)) >> (32 - m)) : 0;
-      sd[2 * ((pos << chlog) + ch) + (nv & 1)] = x;
+    // a thread takes 8 rows of one channel per trip, N / 8 rows apart
+    for (int u = tid; u < (N >> 3) * CH; u += nthr) {
+      const int ch = u & (CH - 1), n0 = u >> chlog, c = min(c0 + ch, ld - 1);
+      float x[8];
+      gen_load_rows<8>(src, in_kind, bo + (size_t)n0 * ld + c, (size_t)(N >> 3) * ld, x);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int n = n0 + j * (N >> 3);
+        const int nv = (n & 1) ? N - 1 - (n >> 1) : (n >> 1);
+        const int pos = (int)(__brev((unsigned)(nv >> 1)) >> (32 - m));
+        sd[2 * ((pos << chlog) + ch) + (nv & 1)] = (double)x[j];
+      }
     }
     __syncthreads();
     lds_fft<false>(s, tw, m, chlog, tid, nthr);
-    for (int u = tid; u < ((M >> 1) + 1) * CH; u += nthr) {
+    // k and M - k together, k < M / 2; k = 0 takes M / 2 (V[M/2] = conj T[M/2]) as well
+#pragma unroll 2
+    for (int u = tid; u < (M >> 1) * CH; u += nthr) {
       const int ch = u & (CH - 1), k = u >> chlog, c = c0 + ch;
       if (c >= ld) continue;
       float* o = T + bo + c;
       if (k == 0) {
-        const cd t = s[ch];
+        const cd t = s[ch], h = c_mul(te[M >> 1], c_conj(s[((M >> 1) << chlog) + ch]));
         o[0] = (float)((t.re + t.im) * sqrt(1.0 / N));
         o[(size_t)M * ld] = (float)((t.re - t.im) * sqrt(0.5) * nrm);
+        o[(size_t)(M >> 1) * ld] = (float)(nrm * h.re);
+        o[(size_t)(M + (M >> 1)) * ld] = (float)(-nrm * h.im);
         continue;
       }
       const cd t = s[(k << chlog) + ch], r = c_conj(s[((M - k) << chlog) + ch]);
@@ -452,17 +567,23 @@ __global__ __launch_bounds__(1024) void k_gen_dct_fft(const cd* __restrict__ tab
   } else {
     const float* S = static_cast<const float*>(src);
     const double sc = sqrt(0.5 * N) / M;
-    for (int u = tid; u < ((M >> 1) + 1) * CH; u += nthr) {
-      const int ch = u & (CH - 1), k = u >> chlog, c = c0 + ch;
-      cd tk = {0.0, 0.0}, tr = {0.0, 0.0};
-      if (c < ld) {
+#pragma unroll 2
+    for (int u = tid; u < (M >> 1) * CH; u += nthr) {
+      const int ch = u & (CH - 1), k = u >> chlog, c = min(c0 + ch, ld - 1);
+      cd tk, tr;
+      {
+        // k = 0 reads coefficients 0, M and (for V[M/2]) M / 2, M + M / 2
         const float* i = S + bo + c;
+        const int h = M >> 1;
+        const double x0 = (double)i[(size_t)k * ld], x1 = (double)i[(size_t)(k == 0 ? M : N - k) * ld];
+        const double x2 = (double)i[(size_t)(k == 0 ? h : M - k) * ld], x3 = (double)i[(size_t)(k == 0 ? M + h : M + k) * ld];
         if (k == 0) {
-          const double v0 = (double)i[0] * (sqrt((double)N) / M), vm = (double)i[(size_t)M * ld] * (sc * sqrt(2.0));
+          const double v0 = x0 * (sqrt((double)N) / M), vm = x1 * (sc * sqrt(2.0));
           tk = {0.5 * (v0 + vm), 0.5 * (v0 - vm)};
+          tr = c_mul(te[h], cd{sc * x2, sc * x3});  // T[M/2] = conj V[M/2]
         } else {
-          const cd a = {sc * (double)i[(size_t)k * ld], -sc * (double)i[(size_t)(N - k) * ld]};
-          const cd b = {sc * (double)i[(size_t)(M - k) * ld], -sc * (double)i[(size_t)(M + k) * ld]};
+          const cd a = {sc * x0, -sc * x1};
+          const cd b = {sc * x2, -sc * x3};
           const cd va = c_mul(c_conj(te[k]), a), vb = c_conj(c_mul(c_conj(te[M - k]), b));  // V[k], conj V[M-k] = V[k+M]
           const cd fe = {0.5 * (va.re + vb.re), 0.5 * (va.im + vb.im)};
           const cd fo = c_mul(c_conj(tn[k]), cd{0.5 * (va.re - vb.re), 0.5 * (va.im - vb.im)});
@@ -470,18 +591,25 @@ __global__ __launch_bounds__(1024) void k_gen_dct_fft(const cd* __restrict__ tab
           tr = {fe.re + fo.im, fo.re - fe.im};   // conj Fe + i conj Fo
         }
       }
-      const int pk = m > 0 ? (int)(__brev((unsigned)k) >> (32 - m)) : 0;
+      const int pk = (int)(__brev((unsigned)k) >> (32 - m));
       s[(pk << chlog) + ch] = tk;
-      if (k != 0 && 2 * k != M) s[((int)(__brev((unsigned)(M - k)) >> (32 - m)) << chlog) + ch] = tr;
+      s[((int)(__brev((unsigned)(k == 0 ? M >> 1 : M - k)) >> (32 - m)) << chlog) + ch] = tr;
     }
     __syncthreads();
     lds_fft<true>(s, tw, m, chlog, tid, nthr);
-    for (int u = tid; u < N * CH; u += nthr) {
-      const int ch = u & (CH - 1), n = u >> chlog, c = c0 + ch;
+    for (int u = tid; u < (N >> 3) * CH; u += nthr) {
+      const int ch = u & (CH - 1), n0 = u >> chlog, c = c0 + ch;
       if (c >= ld) continue;
-      const int nv = (n & 1) ? N - 1 - (n >> 1) : (n >> 1);
-      const float v = (float)sd[2 * (((nv >> 1) << chlog) + ch) + (nv & 1)];
-      gen_store_y(Y, y_bf16, bo + (size_t)n * ld + c, v + (bias != nullptr ? bias[c] : 0.0f));
+      const float bv = bias != nullptr ? bias[c] : 0.0f;
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int n = n0 + j * (N >> 3);
+        const int nv = (n & 1) ? N - 1 - (n >> 1) : (n >> 1);
+        v[j] = (float)sd[2 * (((nv >> 1) << chlog) + ch) + (nv & 1)] + bv;
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) gen_store_y(Y, y_bf16, bo + (size_t)(n0 + j * (N >> 3)) * ld + c, v[j]);
     }
   }
 }
@@ -884,6 +1012,40 @@ void launch_wht(dim3 grid, hipStream_t st, const void* in, int in_kind, float* o
   hipLaunchKernelGGL(k_gen_wht<NLEV>, grid, dim3(rows_block(ld, grid.y, grid.z)), 0, st, in, in_kind, out, Y, out_kind, inv_perm, norm, bias, y_bf16, s, ld, h_lo);
 }
 
+// WHT of 2^J tokens, 6 <= J <= 12, in one pass.  Channels per workgroup: what 132 KB of LDS hold (64 at most), fewer
+// while the chip is short of workgroups, down to 16 (whole 64-byte runs of fp32 rows; 4096 tokens: 8).
+bool wht_in_one_pass(int J) { return J >= 6 && J <= 12; }
+template <int N1, int N2>
+hipError_t launch_wht_lds_n(const stamp_plan* p, const void* in, int in_kind, float* out, void* Y, int out_kind, float norm,
+                            const float* bias, int ld, hipStream_t st) {
+  constexpr int s = 1 << (N1 + N2);
+  const int B = p->geom.B;
+  int chlog = 6;
+  while (((size_t)4 * s << chlog) > 128 * 1024) --chlog;
+  while (chlog > 4 && (size_t)((ld + (1 << chlog) - 1) >> chlog) * B < 256) --chlog;
+  const size_t lds = (size_t)4 * ((1 << N2) * ((1 << N1) + 1)) << chlog;
+  static size_t done[kStampMaxDevices] = {};
+  const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gen_wht_lds<N1, N2>), lds, done);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_gen_wht_lds<N1, N2>), dim3((ld + (1 << chlog) - 1) >> chlog, B), dim3(512), lds, st, in, in_kind, out, Y, out_kind,
+                     norm, bias, p->geom.y_bf16, ld, chlog);
+  return hipGetLastError();
+}
+hipError_t launch_wht_lds(const stamp_plan* p, int J, const void* in, int in_kind, float* out, void* Y, int out_kind,
+                          const float* bias, int ld, hipStream_t st) {
+  const float norm = haar_norm_host(J);
+  switch (J) {
+    case 6: return launch_wht_lds_n<5, 1>(p, in, in_kind, out, Y, out_kind, norm, bias, ld, st);
+    case 7: return launch_wht_lds_n<5, 2>(p, in, in_kind, out, Y, out_kind, norm, bias, ld, st);
+    case 8: return launch_wht_lds_n<5, 3>(p, in, in_kind, out, Y, out_kind, norm, bias, ld, st);
+    case 9: return launch_wht_lds_n<5, 4>(p, in, in_kind, out, Y, out_kind, norm, bias, ld, st);
+    case 10: return launch_wht_lds_n<5, 5>(p, in, in_kind, out, Y, out_kind, norm, bias, ld, st);
+    case 11: return launch_wht_lds_n<5, 6>(p, in, in_kind, out, Y, out_kind, norm, bias, ld, st);
+    case 12: return launch_wht_lds_n<6, 6>(p, in, in_kind, out, Y, out_kind, norm, bias, ld, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 // DCT of a power-of-two length; forward (inv = 0): src -> T, inverse: src (fp32) -> Y (+ bias)
 hipError_t launch_dct_fft(const stamp_plan* p, int inv, const void* src, int in_kind, float* T, void* Y, const float* bias, int ld,
                           hipStream_t st) {
@@ -893,7 +1055,9 @@ hipError_t launch_dct_fft(const stamp_plan* p, int inv, const void* src, int in_
   while (chlog > 0 && ((size_t)8 * s << chlog) > 128 * 1024) --chlog;
   // fewer channels per workgroup while the chip is short of workgroups, down to 4 (16-byte runs of a row)
   while (chlog > 2 && (size_t)((ld + (1 << chlog) - 1) >> chlog) * B < 256) --chlog;
-  const size_t lds = (size_t)8 * s << chlog;
+  // the stages' factors (4 N bytes) go to LDS where they fit next to the points
+  const int tw_lds = s <= 4096;
+  const size_t lds = ((size_t)8 * s << chlog) + (tw_lds ? (size_t)4 * s : 0);
   const int items = (s / 8) << chlog, nthr = items >= 1024 ? 1024 : items >= 512 ? 512 : 256;
   const dim3 grid((ld + (1 << chlog) - 1) >> chlog, B);
   static size_t done[2][kStampMaxDevices] = {};
@@ -901,8 +1065,8 @@ hipError_t launch_dct_fft(const stamp_plan* p, int inv, const void* src, int in_
   const void* fn = inv ? reinterpret_cast<const void*>(&k_gen_dct_fft<true>) : reinterpret_cast<const void*>(&k_gen_dct_fft<false>);
   const hipError_t e = stamp_allow_lds(fn, lds, done[inv]);
   if (e != hipSuccess) return e;
-  if (inv) hipLaunchKernelGGL(k_gen_dct_fft<true>, grid, dim3(nthr), lds, st, tab, src, in_kind, T, Y, bias, p->geom.y_bf16, lgn, ld, chlog);
-  else hipLaunchKernelGGL(k_gen_dct_fft<false>, grid, dim3(nthr), lds, st, tab, src, in_kind, T, Y, bias, 0, lgn, ld, chlog);
+  if (inv) hipLaunchKernelGGL(k_gen_dct_fft<true>, grid, dim3(nthr), lds, st, tab, src, in_kind, T, Y, bias, p->geom.y_bf16, lgn, ld, chlog, tw_lds);
+  else hipLaunchKernelGGL(k_gen_dct_fft<false>, grid, dim3(nthr), lds, st, tab, src, in_kind, T, Y, bias, 0, lgn, ld, chlog, tw_lds);
   return hipGetLastError();
 }
 
@@ -990,6 +1154,7 @@ hipError_t stamp_gen_forward(const stamp_plan* p, const void* X, float* const (&
       *T_out = buf[0];
       return hipGetLastError();
     }
+    if (wht_in_one_pass(J)) return launch_wht_lds(p, J, X, xk, T, nullptr, 1, nullptr, d, st);
     const void* in = X;
     int in_kind = xk, flip = 0;
     for (int l = 0; l < J;) {
@@ -1089,6 +1254,7 @@ hipError_t stamp_gen_inverse(const stamp_plan* p, float* const (&buf)[3], int nc
       hipLaunchKernelGGL(k_gen_store_y, rows_grid(ld, s, B), dim3(rows_block(ld, s, B)), 0, st, S, bias, Y, s, ld, g.y_bf16);
       return hipGetLastError();
     }
+    if (wht_in_one_pass(J)) return launch_wht_lds(p, J, S, 0, nullptr, Y, 2, bias, ld, st);
     const float* in = S;
     int flip = 0;
     for (int l = 0; l < J;) {

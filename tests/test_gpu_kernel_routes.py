@@ -74,3 +74,15 @@ def test_dct_inverse_against_the_dense_product(s):
     bound = 2.0 ** -24 * np.abs(ref) + (s * 2.0 ** -50) * np.abs(ref).max(axis=(0, 1), keepdims=True)
     assert (np.abs(y - ref) <= bound).all(), float((np.abs(y - ref) / bound).max())
     plan.destroy()
+
+
+# ---- WHT in one pass (64 .. 4096 tokens): every split of the stages, the lengths on either side of the range, channel
+# counts that leave the last workgroup partly empty
+WHT = [_wl(f"wht_{1 << J}", batch=2 if J < 10 else 1, xform="wht", levels=0, seq_len=1 << J, k_hi=1 << (J // 2), d_in=32 * (J - 3),
+           d_out=101 + J, act_quant="asym" if J % 2 else "sym", x_dtype="bf16" if J % 3 else "f32", seed=220 + J)
+       for J in range(5, 14)]
+
+
+@pytest.mark.parametrize("w", WHT, ids=[w.name for w in WHT])
+def test_wht_lengths(w):
+    tl.full_case(w, with_bias=True, check_unfused=False, engines=("fp6",))
