@@ -170,15 +170,25 @@ struct SplitArgs {
 };
 constexpr int kMaxBlockRows = 128;
 
+// Blocks of a 1-D Haar transform of any length (StampRag): butterflies (x0 +- x1) / sqrt 2, a node without partner carried
+// up unchanged, rows in STaMP order (RowMeta::e is the slot, < 0: no such coefficient).
+struct RagArgs {
+  StampRag q;
+  int j, m;      // block, its tokens
+  int Kpad;
+};
+
 // ASYM: the asymmetric form of the quantizer; zeros_off = distance (in floats) from a row's scale to its offset z.
-template <int NR, bool IS2D, bool ASYM, int PASS, typename MetaFn>
+// RAG: q_lo_blk is the whole buffer, row0 the sequence's first row, scales_blk its first scale, m_kpad the row pitch.
+template <int NR, bool IS2D, bool ASYM, int PASS, bool RAG = false, typename MetaFn>
 __device__ __forceinline__ void flush_rows(float (&rowv)[NR][8], MetaFn meta, int step, uint32_t (*s_max)[kPartWords],
                                            uint8_t* q_lo_blk /* row e=0 of the block, channel 0 (workgroup-uniform) */,
                                            uint32_t q_off /* this thread's byte offset inside a row */,
                                            float* scales_blk, size_t zeros_off, bool active, int tid,
                                            uint32_t* gpart_blk /* PASS 1: this split's partial maxima of the block's row e=0 */,
                                            size_t gpart_neg /* PASS 1: distance to the negative parts */,
-                                           const uint32_t* s_amax /* PASS 2: [2][kMaxBlockRows] */, bool write_scales) {
+                                           const uint32_t* s_amax /* PASS 2: [2][kMaxBlockRows] */, bool write_scales,
+                                           size_t row0 = 0, int Kpad = 0) {
   // Values derived from the thread index are recomputed in every step from an opaque copy: cheap, and it
   // keeps them from being carried (and spilled: a scratch reload waits for ALL outstanding memory
   // operations, the asynchronous loads of the next batches included) across the whole unrolled kernel.
@@ -261,7 +271,7 @@ __device__ __forceinline__ void flush_rows(float (&rowv)[NR][8], MetaFn meta, in
     if constexpr (ASYM) {
       const float hi = __fmul_rn(fkey_inv(reduce_waves(part)), nrm), nlo = __fmul_rn(fkey_inv(reduce_waves(part_neg)), nrm);
       asym_params(hi, nlo, 15.0f, scale, inv, z_lane);
-      if (tid < NR && write_scales) scales_blk[zeros_off + rm.e] = z_lane;
+      if (tid < NR && write_scales && (!RAG || rm.e >= 0)) scales_blk[zeros_off + rm.e] = z_lane;
     } else {
       const float a = __fmul_rn(__uint_as_float(reduce_waves(part)), nrm);
       if (a > 0.0f) {
@@ -272,7 +282,7 @@ __device__ __forceinline__ void flush_rows(float (&rowv)[NR][8], MetaFn meta, in
     // even 1-D levels and all 2-D levels have a power-of-two norm: fold it into the multiplier
     const bool fold = IS2D || ((rm.level & 1) == 0);
     mul_lane = fold ? __fmul_rn(inv, nrm) : inv;
-    if (tid < NR && write_scales) scales_blk[rm.e] = scale;
+    if (tid < NR && write_scales && (!RAG || rm.e >= 0)) scales_blk[rm.e] = scale;
   }
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
@@ -298,7 +308,11 @@ __device__ __forceinline__ void flush_rows(float (&rowv)[NR][8], MetaFn meta, in
     } else {
       w = pack8_int4(p);
     }
-    if (active) *reinterpret_cast<uint32_t*>(q_lo_blk + rm.e * 64 + q_off) = w;  // tiled layout: 64 bytes per row and K step
+    if constexpr (RAG) {
+      if (active && rm.e >= 0) *reinterpret_cast<uint32_t*>(q_lo_blk + stamp_qlo_offset(row0 + rm.e, 0, Kpad) + q_off) = w;
+    } else {
+      if (active) *reinterpret_cast<uint32_t*>(q_lo_blk + rm.e * 64 + q_off) = w;  // tiled layout: 64 bytes per row and K step
+    }
   }
 }
 
@@ -307,7 +321,8 @@ __device__ __forceinline__ void flush_rows(float (&rowv)[NR][8], MetaFn meta, in
 // khi slots, 4-bit codes held as int8 beyond.  Called after the last streaming step (no loads in flight).
 // The 4-bit ones also go, packed like every other 4-bit row, to the block's row 0 of q_lo (q_lo_row: this thread's
 // word of it), which no other coefficient uses: the 4-bit rows' GEMM can then take the block sum from its own rows.
-template <bool IS2D, bool ASYM>
+// RAG: 4-bit rows have no place in q_hi.
+template <bool IS2D, bool ASYM, bool RAG = false>
 __device__ __forceinline__ void finish_top_row(const float (&top)[8], int level, uint32_t* part /* >= 32 words, free */,
                                                int8_t* q_hi_row, uint8_t* q_lo_row, float* scale_out, size_t zeros_off,
                                                bool row8, bool active, int tid) {
@@ -354,7 +369,7 @@ __device__ __forceinline__ void finish_top_row(const float (&top)[8], int level,
     w4 |= ((uint32_t)((int)q) & 0xFu) << (4 * i);
   }
   if (active) {
-    *reinterpret_cast<uint2*>(q_hi_row) = make_uint2(w[0], w[1]);
+    if (!RAG || row8) *reinterpret_cast<uint2*>(q_hi_row) = make_uint2(w[0], w[1]);
     if (!row8) *reinterpret_cast<uint32_t*>(q_lo_row) = w4;
   }
 }
@@ -384,42 +399,46 @@ __device__ __forceinline__ RowMeta meta1d(int r) {
 template <bool BF16>
 __device__ __forceinline__ void request_batch(const uint8_t* X_row /* row 0 of the batch, channel 0 (workgroup-uniform) */,
                                               uint32_t x_off /* byte offset of this thread's 8 channels in a row */,
-                                              size_t row_bytes, uint8_t* half, int nthreads, int wave) {
+                                              size_t row_bytes, uint8_t* half, int nthreads, int wave, int last = 3 /* rows beyond: row `last` again */) {
   constexpr int CPR = BF16 ? 1 : 2;
 #pragma unroll
   for (int t = 0; t < 4; ++t)
 #pragma unroll
     for (int h = 0; h < CPR; ++h)
       __builtin_amdgcn_global_load_lds(
-          (const void __attribute__((address_space(1)))*)(X_row + (size_t)t * row_bytes + 16 * h + x_off),
+          (const void __attribute__((address_space(1)))*)(X_row + (ptrdiff_t)min(t, last) * (ptrdiff_t)row_bytes + 16 * h + x_off),
           (void __attribute__((address_space(3)))*)(half + ((t * CPR + h) * nthreads + wave * 64) * 16), 16, 0, 0);
 }
 
-template <int RLOG, int L, int IDX, int SLOT, int NP, int MAXR>
-__device__ __forceinline__ void chain1d(float (&cur)[8], float (&pend)[NP][8], float (&rowv)[MAXR][8], float (&top)[8]) {
+template <int RLOG, int L, int IDX, int SLOT, bool RAG, int NP, int MAXR>
+__device__ __forceinline__ void chain1d(float (&cur)[8], float (&pend)[NP][8], float (&rowv)[MAXR][8], float (&top)[8], int m) {
   if constexpr (L == RLOG) {
 #pragma unroll
     for (int c = 0; c < 8; ++c) top[c] = cur[c];
   } else if constexpr ((IDX & 1) != 0) {
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-      const float a = __fadd_rn(pend[L - 2][c], cur[c]);
+      float a = __fadd_rn(pend[L - 2][c], cur[c]);
       rowv[SLOT][c] = __fsub_rn(pend[L - 2][c], cur[c]);
+      if constexpr (RAG) {
+        a = (IDX << L) < m ? __fmul_rn(a, kInvSqrt2) : pend[L - 2][c];
+        rowv[SLOT][c] = __fmul_rn(rowv[SLOT][c], kInvSqrt2);
+      }
       cur[c] = a;
     }
-    chain1d<RLOG, L + 1, (IDX >> 1), SLOT + 1, NP, MAXR>(cur, pend, rowv, top);
+    chain1d<RLOG, L + 1, (IDX >> 1), SLOT + 1, RAG, NP, MAXR>(cur, pend, rowv, top, m);
   } else {
 #pragma unroll
     for (int c = 0; c < 8; ++c) pend[L - 2][c] = cur[c];
   }
 }
 
-template <int RLOG, bool BF16, bool ASYM, int PASS, int IT, int NP>
+template <int RLOG, bool BF16, bool ASYM, int PASS, bool RAG, int IT, int NP>
 __device__ __forceinline__ void step1d(const uint8_t* X_blk, uint32_t x_off, size_t row_bytes, uint8_t* stage, int nthreads,
                                        bool active, int tid, float (&pend)[NP][8], float (&top)[8],
                                        uint32_t (*s_max)[kPartWords], uint8_t* q_lo_blk, uint32_t q_off, float* scales_blk,
                                        size_t zeros_off, uint32_t* gpart_blk, size_t gpart_neg, const uint32_t* s_amax,
-                                       bool write_scales) {
+                                       bool write_scales, const RagArgs& rg, size_t row0) {
   constexpr int R = 1 << RLOG;
   constexpr int NIT = R / 4;
   constexpr int CH = cmin(trailing_ones(IT), RLOG - 2);
@@ -445,7 +464,8 @@ __device__ __forceinline__ void step1d(const uint8_t* X_blk, uint32_t x_off, siz
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the half has been read before it is requested again
   asm volatile("" ::: "memory");
   if constexpr (IT + 2 < NIT)
-    request_batch<BF16>(X_blk + (size_t)(4 * (IT + 2)) * row_bytes, x_off, row_bytes, half, nthreads, tid >> 6);
+    request_batch<BF16>(X_blk + (size_t)(4 * (IT + 2)) * row_bytes, x_off, row_bytes, half, nthreads, tid >> 6,
+                        RAG ? rg.m - 1 - 4 * (IT + 2) : 3);
 
   float rowv[NR][8];
   float a1[2][8];
@@ -474,6 +494,10 @@ __device__ __forceinline__ void step1d(const uint8_t* X_blk, uint32_t x_off, siz
     for (int c = 0; c < 8; ++c) {
       a1[u][c] = __fadd_rn(x0[c], x1[c]);
       rowv[u][c] = __fsub_rn(x0[c], x1[c]);
+      if constexpr (RAG) {
+        a1[u][c] = 4 * IT + t + 1 < rg.m ? __fmul_rn(a1[u][c], kInvSqrt2) : x0[c];
+        rowv[u][c] = __fmul_rn(rowv[u][c], kInvSqrt2);
+      }
     }
   }
   float cur[8];
@@ -481,21 +505,33 @@ __device__ __forceinline__ void step1d(const uint8_t* X_blk, uint32_t x_off, siz
   for (int c = 0; c < 8; ++c) {
     cur[c] = __fadd_rn(a1[0][c], a1[1][c]);
     rowv[2][c] = __fsub_rn(a1[0][c], a1[1][c]);
+    if constexpr (RAG) {
+      cur[c] = 4 * IT + 2 < rg.m ? __fmul_rn(cur[c], kInvSqrt2) : a1[0][c];
+      rowv[2][c] = __fmul_rn(rowv[2][c], kInvSqrt2);
+    }
   }
-  chain1d<RLOG, 2, IT, 3, NP, NR>(cur, pend, rowv, top);
-  auto meta = [](int r) -> RowMeta { return meta1d<RLOG, IT>(r); };
-  flush_rows<NR, false, ASYM, PASS>(rowv, meta, IT, s_max, q_lo_blk, q_off, scales_blk, zeros_off, active, tid, gpart_blk,
-                                    gpart_neg, s_amax, write_scales);
+  chain1d<RLOG, 2, IT, 3, RAG, NP, NR>(cur, pend, rowv, top, rg.m);
+  if constexpr (RAG) {
+    auto meta = [&rg](int r) -> RowMeta { return RowMeta{0, stamp_rag_slot(rg.q, rg.j, meta1d<RLOG, IT>(r).e)}; };
+    flush_rows<NR, false, ASYM, PASS, true>(rowv, meta, IT, s_max, q_lo_blk, q_off, scales_blk, zeros_off, active, tid, gpart_blk,
+                                            gpart_neg, s_amax, write_scales, row0, rg.Kpad);
+  } else {
+    auto meta = [](int r) -> RowMeta { return meta1d<RLOG, IT>(r); };
+    flush_rows<NR, false, ASYM, PASS>(rowv, meta, IT, s_max, q_lo_blk, q_off, scales_blk, zeros_off, active, tid, gpart_blk,
+                                      gpart_neg, s_amax, write_scales);
+  }
 }
 
-template <int RLOG, bool BF16, bool ASYM, int PASS, int NP, int... ITS>
+template <int RLOG, bool BF16, bool ASYM, int PASS, bool RAG = false, int NP, int... ITS>
 __device__ __forceinline__ void run1d(std::integer_sequence<int, ITS...>, const uint8_t* X_blk, uint32_t x_off,
                                       size_t row_bytes, uint8_t* stage, int nthreads, bool active, int tid,
                                       float (&pend)[NP][8], float (&top)[8], uint32_t (*s_max)[kPartWords],
                                       uint8_t* q_lo_blk, uint32_t q_off, float* scales_blk, size_t zeros_off,
-                                      uint32_t* gpart_blk, size_t gpart_neg, const uint32_t* s_amax, bool write_scales) {
-  (step1d<RLOG, BF16, ASYM, PASS, ITS, NP>(X_blk, x_off, row_bytes, stage, nthreads, active, tid, pend, top, s_max, q_lo_blk,
-                                           q_off, scales_blk, zeros_off, gpart_blk, gpart_neg, s_amax, write_scales), ...);
+                                      uint32_t* gpart_blk, size_t gpart_neg, const uint32_t* s_amax, bool write_scales,
+                                      const RagArgs& rg = RagArgs{}, size_t seq_row0 = 0) {
+  (step1d<RLOG, BF16, ASYM, PASS, RAG, ITS, NP>(X_blk, x_off, row_bytes, stage, nthreads, active, tid, pend, top, s_max, q_lo_blk,
+                                                q_off, scales_blk, zeros_off, gpart_blk, gpart_neg, s_amax, write_scales, rg,
+                                                seq_row0), ...);
 }
 
 // PASS 2: every row's maximum over the splits -> s_amax[sign][e] (before the first step; ordinary loads)
@@ -545,7 +581,7 @@ __global__ __launch_bounds__(1024) void k_bottom1d(const void* __restrict__ X, u
   float pend[NP][8];
   float top[8];
   uint32_t* gpart_blk = (PASS == 1) ? sp.gpart + (size_t)blockIdx.z * sp.part_rows + row0 : nullptr;
-  run1d<RLOG, BF16, ASYM, PASS, NP>(std::make_integer_sequence<int, R / 4>{}, X_blk, x_off, row_bytes, stage, nthreads, active,
+  run1d<RLOG, BF16, ASYM, PASS>(std::make_integer_sequence<int, R / 4>{}, X_blk, x_off, row_bytes, stage, nthreads, active,
                                     tid, pend, top, s_max, q_lo + stamp_qlo_offset(row0, 0, Kpad), q_off, scales + row0,
                                     zeros_off, gpart_blk, (size_t)sp.nsplit * sp.part_rows, s_amax,
                                     PASS == 0 || blockIdx.z == 0);
@@ -562,6 +598,45 @@ __global__ __launch_bounds__(1024) void k_bottom1d(const void* __restrict__ X, u
     o[0] = make_float4(top[0], top[1], top[2], top[3]);
     o[1] = make_float4(top[4], top[5], top[6], top[7]);
   }
+}
+
+// The same for a 1-D Haar transform of any length, optionally with the first token left out: one workgroup per block
+// (blockIdx.x < nb) of 2^RLOG tokens, one more for the token that was left out.  Codes and scales leave in STaMP order;
+// X is read once and T never leaves the chip (levels as passes over fp32 buffers and a row quantizer, 2048 tokens x 4096
+// channels, 3 levels: 19.5 + 8.6 us; this kernel 10.1).
+template <int RLOG, bool BF16, bool ASYM>
+__global__ __launch_bounds__(1024) void k_bottom1d_rag(const void* __restrict__ X, int8_t* __restrict__ q_hi, uint8_t* __restrict__ q_lo,
+                                                       float* __restrict__ scales, int s, int d, int khi, int Kpad, size_t zeros_off,
+                                                       StampRag q) {
+  constexpr int R = 1 << RLOG;
+  constexpr int NP = RLOG > 2 ? RLOG - 2 : 1;
+  constexpr int CPR = BF16 ? 1 : 2;
+  extern __shared__ __attribute__((aligned(16))) uint8_t stage[];
+  __shared__ __attribute__((aligned(16))) uint32_t s_max[2][kPartWords];
+  const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const int nthreads = blockDim.x;
+  const int c0 = tid * 8;
+  const bool active = c0 < d;
+  const size_t esz = BF16 ? 2 : 4, row_bytes = (size_t)d * esz, seq0 = (size_t)b * s;
+  const uint32_t x_off = (uint32_t)(min(c0, d - 8) * (int)esz);
+  const uint32_t q_off = (uint32_t)(stamp_qlo_offset(0, min(c0, d - 8), Kpad));
+  float top[8];
+  int slot = 0;
+  if (j == q.nb) {
+    load8(X, seq0 * d + min(c0, d - 8), BF16, true, top);
+  } else {
+    const RagArgs rg = {q, j, j == q.nb - 1 ? q.mlast : R, Kpad};
+    const uint8_t* X_blk = reinterpret_cast<const uint8_t*>(X) + (seq0 + q.o + (size_t)j * R) * row_bytes;
+    request_batch<BF16>(X_blk, x_off, row_bytes, stage, nthreads, tid >> 6, rg.m - 1);
+    request_batch<BF16>(X_blk + 4 * row_bytes, x_off, row_bytes, stage + 4 * CPR * nthreads * 16, nthreads, tid >> 6, rg.m - 5);
+    float pend[NP][8];
+    run1d<RLOG, BF16, ASYM, 0, true>(std::make_integer_sequence<int, R / 4>{}, X_blk, x_off, row_bytes, stage, nthreads, active, tid,
+                                     pend, top, s_max, q_lo, q_off, scales + seq0, zeros_off, nullptr, 0, nullptr, true, rg, seq0);
+    slot = q.o + j;
+  }
+  finish_top_row<false, ASYM, true>(top, 0, &s_max[(R / 4) & 1][0], q_hi + ((size_t)b * khi + slot) * d + c0,
+                                    q_lo + stamp_qlo_offset(seq0 + slot, 0, Kpad) + q_off, scales + seq0 + slot, zeros_off, slot < khi,
+                                    active, tid);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -983,6 +1058,42 @@ hipError_t launch_bottom1d(const stamp_plan* p, const void* X, uint8_t* q_lo, fl
 }
 
 }  // namespace
+
+// One workgroup has to hold all channels, 16-byte loads of X need its alignment.
+bool stamp_rag_quantizes(const stamp_plan* p, const void* X) {
+  return p->rag.on && p->geom.d <= (p->geom.x_bf16 ? 8192 : 4096) && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+}
+
+namespace {
+template <int RLOG, bool BF16, bool ASYM>
+hipError_t launch_rag(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st) {
+  const StampGeom& g = p->geom;
+  const int nthreads = (g.d / 8 + 63) / 64 * 64;
+  const size_t lds = (size_t)8 * nthreads * (BF16 ? 16 : 32);
+  static size_t lds_done[kStampMaxDevices] = {};
+  const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_bottom1d_rag<RLOG, BF16, ASYM>), lds, lds_done);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_bottom1d_rag<RLOG, BF16, ASYM>), dim3(p->rag.nb + p->rag.o, g.B), dim3(nthreads), lds, st, X, q_hi, q_lo, scales,
+                     g.s, g.d, g.khi, p->Kpad, (size_t)g.B * g.s, p->rag);
+  return hipGetLastError();
+}
+template <int RLOG>
+hipError_t launch_rag_t(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st) {
+  const StampGeom& g = p->geom;
+  if (g.x_bf16) return g.asym ? launch_rag<RLOG, true, true>(p, X, q_hi, q_lo, scales, st) : launch_rag<RLOG, true, false>(p, X, q_hi, q_lo, scales, st);
+  return g.asym ? launch_rag<RLOG, false, true>(p, X, q_hi, q_lo, scales, st) : launch_rag<RLOG, false, false>(p, X, q_hi, q_lo, scales, st);
+}
+}  // namespace
+
+hipError_t stamp_launch_actquant_rag(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st) {
+  switch (p->rag.r) {
+    case 3: return launch_rag_t<3>(p, X, q_hi, q_lo, scales, st);
+    case 4: return launch_rag_t<4>(p, X, q_hi, q_lo, scales, st);
+    case 5: return launch_rag_t<5>(p, X, q_hi, q_lo, scales, st);
+    case 6: return launch_rag_t<6>(p, X, q_hi, q_lo, scales, st);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 // general path: per-token quantization of the transformed tokens T [B, s, d] fp32 (rows = STaMP slots)
 hipError_t stamp_launch_quant_rows_f32(const stamp_plan* p, const float* T, int8_t* q_hi, uint8_t* q_lo, float* scales,

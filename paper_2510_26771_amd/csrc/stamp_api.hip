@@ -192,6 +192,31 @@ stamp_status_t validate(const stamp_plan_desc_t* d, StampGeom* g, int* fused_ok,
   return STAMP_OK;
 }
 
+// Blocked form of a plan of the general path (1-D Haar of any length): per-token scales, bias after the inverse, 3 to 6
+// levels (blocks of 8 .. 64 tokens: what the GEMM epilogues invert), 8-bit tokens among the approximations (and the
+// token left out, which has to be one of them).  Everything else runs level by level.
+void rag_geometry(stamp_plan* p) {
+  const StampGeom& g = p->geom;
+  const StampGen& gn = p->gen;
+  p->rag = StampRag{};
+  if (gn.kind != kGenHaarRagged || gn.group != 0 || gn.bias_mode != 0 || gn.levels < 3 || gn.levels > 6) return;
+  StampRag r = {};
+  r.o = gn.skip;
+  r.n = g.s - r.o;
+  r.r = gn.levels;
+  r.nb = (r.n + (1 << r.r) - 1) >> r.r;
+  r.mlast = r.n - ((r.nb - 1) << r.r);
+  if (g.khi < 1 || g.khi > r.o + r.nb) return;
+  if (((int64_t)g.B * r.nb << r.r) > (int64_t)1 << 30) return;
+  r.on = 1;
+  p->rag = r;
+  p->bgeom = g;
+  p->bgeom.ident = 0;
+  p->bgeom.J = p->bgeom.r = r.r;
+  p->bgeom.R = 1 << r.r;
+  p->bgeom.k = r.nb;
+}
+
 void layout_workspace(stamp_plan* p) {
   const StampGeom& g = p->geom;
   size_t off = 0;
@@ -211,6 +236,13 @@ void layout_workspace(stamp_plan* p) {
     p->ws_codes8 = take(grouped ? (size_t)g.B * g.s * g.d : 0);
     p->ws_scalesg = take(grouped ? (size_t)g.B * g.s * (g.d / 64) * sizeof(float) : 0);
     p->ws_total = off;
+    // the blocked form uses neither the fp32 copies of the activation nor those of the output: its rows in block order
+    // lie over the former, its block sums over the latter (a plan for which they do not fit keeps the level kernels)
+    p->ws_ba6 = p->ws_T[0];
+    p->ws_bP = p->ws_Yt[0];
+    if (p->rag.on && (stamp_rag_a6_bytes(p) > p->ws_Yt[0] - p->ws_T[0] ||
+                      (size_t)g.B * g.khi * p->Npad * sizeof(float) > p->ws_codes8 - p->ws_Yt[0]))
+      p->rag.on = 0;
     return;
   }
   p->ws_abot = take((size_t)g.B * g.k * g.d * sizeof(float));
@@ -259,12 +291,35 @@ inline hipError_t stamp_launch_block_sums_own(const stamp_plan* p, const int8_t*
   return stamp_launch_sum_parts(ythi, p->hi_ksplit_own, p->geom.B * p->geom.khi, p->geom.N, P, p->Npad, st);
 }
 
+// Blocked form of the 1-D Haar transform of any length (rules: rag_geometry): block sums from the 8-bit rows, then the
+// 4-bit rows' GEMM with the inverse in its epilogue writes Y.  Y has to be aligned for its vector stores.
+inline bool rag_route(const stamp_plan* p, const void* Y) { return p->rag.on && (reinterpret_cast<uintptr_t>(Y) & 15) == 0; }
+
+stamp_status_t rag_forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t* q_lo, const float* scales, void* Y, void* ws,
+                             hipStream_t st) {
+  float* ythi = reinterpret_cast<float*>(at(ws, p->ws_ythi));
+  float* P = reinterpret_cast<float*>(at(ws, p->ws_bP));
+  uint8_t* blk = at(ws, p->ws_ba6);
+  if (stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st) != hipSuccess) return STAMP_ERR_DEVICE;
+  if (stamp_launch_rag_top(p, ythi, p->hi_ksplit, P, Y, st) != hipSuccess) return STAMP_ERR_DEVICE;
+  hipError_t e;
+  if (p->engine == STAMP_GEMM_FP6) {
+    e = stamp_launch_repack6_rag(p, q_lo, blk, st);
+    if (e == hipSuccess) e = stamp_launch_gemm_lo6_rag(p, blk, scales, Y, P, st);
+  } else {
+    e = stamp_launch_gather_lo_rag(p, q_lo, blk, st);
+    if (e == hipSuccess) e = stamp_launch_gemm_lo_rag(p, blk, scales, Y, P, st);
+  }
+  return e == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
+}
+
 // codes_are_ours: q_hi / q_lo were written by this library's quantizer (which also fills the rows of q_lo that
 // own_top reads); buffers a caller packed need not hold them
 stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t* q_lo, const float* scales, void* Y,
                          void* ws, hipStream_t st, bool codes_are_ours) {
   float* ythi = reinterpret_cast<float*>(at(ws, p->ws_ythi));
   float* P = reinterpret_cast<float*>(at(ws, p->ws_P));
+  if (rag_route(p, Y)) return rag_forward_q(p, q_hi, q_lo, scales, Y, ws, st);
   if (p->gen.kind != kGenNone) {
     // general path: dequantized rows in STaMP order -> (transformed bias) -> inverse level by level -> Y
     float* const yt[3] = {reinterpret_cast<float*>(at(ws, p->ws_Yt[0])), reinterpret_cast<float*>(at(ws, p->ws_Yt[1])),
@@ -334,6 +389,8 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
 
 // general path, steps 1-2: forward transform level by level, then the row quantizer
 stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, void* ws, hipStream_t st) {
+  if (stamp_rag_quantizes(p, X))
+    return stamp_launch_actquant_rag(p, X, q_hi, q_lo, scales, st) == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
   float* const tb[3] = {reinterpret_cast<float*>(at(ws, p->ws_T[0])), reinterpret_cast<float*>(at(ws, p->ws_T[1])),
                         reinterpret_cast<float*>(at(ws, p->ws_T[2]))};
   float* T = nullptr;
@@ -385,6 +442,7 @@ stamp_status_t stamp_plan_create(const stamp_plan_desc_t* desc, const void* W_de
   p->Mpad = ((g.B * g.s + 255) / 256) * 256;
   p->hi_ksplit = gen.group ? 1 : stamp_hi_ksplit(p, g.k);
   p->hi_ksplit_own = gen.group ? 1 : stamp_hi_ksplit(p, g.khi);
+  rag_geometry(p);
   layout_workspace(p);
 
   // physical row of every STaMP slot

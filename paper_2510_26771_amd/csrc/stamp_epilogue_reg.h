@@ -76,9 +76,11 @@ __device__ __forceinline__ void put_pair(void* Y, size_t idx, float v0, float v1
 
 // The same pair at a 32-bit byte offset from a wave-uniform base (the tile's first output row): the address is the
 // scalar base plus one 32-bit vector offset, no 64-bit vector arithmetic per store.
-template <bool YBF16>
-__device__ __forceinline__ void put_pair_at(char* base, uint32_t byte_off, float v0, float v1) {
-  if constexpr (YBF16) {
+template <bool YBF16, bool VEC>
+__device__ __forceinline__ void put_pair_at(char* base, uint32_t byte_off, float v0, float v1, int nvalid) {
+  if constexpr (!VEC) {  // odd d_out: a pair may straddle the end of the row
+    put_pair<YBF16, false>(base + byte_off, 0, v0, v1, nvalid);
+  } else if constexpr (YBF16) {
     const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){v0, v1}, bf2));  // v_cvt_pk_bf16_f32, RNE
     __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(base + byte_off));  // Y is not read again here
   } else {
@@ -87,7 +89,7 @@ __device__ __forceinline__ void put_pair_at(char* base, uint32_t byte_off, float
 }
 
 // Operands of the epilogue that come from global memory: requested during the last K step of a tile.
-template <int EPI, int RL>
+template <int EPI, int RL, bool RAG = false>
 struct RegEpiOperands {
   static constexpr int nb = (EPI == 2) ? 64 / (1 << RL) : 1;
   f2 sw, bias, cs;
@@ -107,7 +109,8 @@ struct RegEpiOperands {
         // own, see blocks_reg); blocks beyond read a row that is there and is not used
         const int blk = mrow / R, pk = a.own_top ? a.g.khi : a.g.k;
         const int b = blk / a.g.k, j = blk - b * a.g.k;
-        P[t] = *reinterpret_cast<const f2*>(a.P + (size_t)(b * pk + min(j, pk - 1)) * a.Npad + n);
+        const int prow = RAG ? b * a.g.khi + min(j + a.rag.o, a.g.khi - 1) : b * pk + min(j, pk - 1);
+        P[t] = *reinterpret_cast<const f2*>(a.P + (size_t)prow * a.Npad + n);
       }
     }
   }
@@ -126,10 +129,26 @@ struct RegOut {
   float sw0, sw1;     // weight scales of the two columns
   float off0, off1;   // block sum + bias
   int nvalid;
+  static constexpr bool kShort = false;
   // v = the token's signed sum of detail coefficients, still without the weight scale
-  __device__ __forceinline__ void put(IDX idx, float v0, float v1) const {
-    if constexpr (B32) put_pair_at<YBF16>(reinterpret_cast<char*>(Y), idx, __builtin_fmaf(v0, sw0, off0), __builtin_fmaf(v1, sw1, off1));
+  __device__ __forceinline__ void put(IDX idx, float v0, float v1, int /*token of the block*/) const {
+    if constexpr (B32)
+      put_pair_at<YBF16, VEC>(reinterpret_cast<char*>(Y), idx, __builtin_fmaf(v0, sw0, off0), __builtin_fmaf(v1, sw1, off1), nvalid);
     else put_pair<YBF16, VEC>(Y, idx, __builtin_fmaf(v0, sw0, off0), __builtin_fmaf(v1, sw1, off1), nvalid);
+  }
+};
+
+// The same for the short last block of a sequence of any length (StampRag): the tokens that exist, each with its factor.
+template <bool YBF16, bool VEC>
+struct RegOutShort : RegOut<YBF16, VEC, true> {
+  typedef uint32_t IDX;
+  const float* leaf;  // factor of every token (0: it does not exist)
+  float bsum0, bsum1, bias0, bias1;
+  __device__ __forceinline__ void put(IDX idx, float v0, float v1, int tok) const {
+    const float f = leaf[tok];
+    if (f == 0.0f) return;
+    put_pair_at<YBF16, VEC>(reinterpret_cast<char*>(this->Y), idx, __builtin_fmaf(v0 * f, this->sw0, bsum0 * f + bias0),
+                            __builtin_fmaf(v1 * f, this->sw1, bsum1 * f + bias1), this->nvalid);
   }
 };
 
@@ -140,7 +159,7 @@ template <int RL, int T, int M, int I, typename Out>
 __device__ __forceinline__ void dfs1d_reg(const float (&acc)[4][NI][16], float a0, float a1, const Out& o) {
   using RM = RegMap<RL>;
   if constexpr (M == RL) {
-    o.put(o.base + (typename Out::IDX)I * o.tok_stride, a0, a1);
+    o.put(o.base + (typename Out::IDX)I * o.tok_stride, a0, a1, I);
     if constexpr ((I & 7) == 7) __builtin_amdgcn_sched_barrier(0);  // bounds how far stores and their addresses run ahead
   } else {
     constexpr int e = (1 << M) + I;
@@ -155,7 +174,7 @@ template <int RB, int T, int M, int IY, int IX, typename Out>
 __device__ __forceinline__ void dfs2d_reg(const float (&acc)[4][NI][16], float a0, float a1, const Out& o) {
   using RM = RegMap<2 * RB>;
   if constexpr (M == RB) {
-    o.put(o.base + (typename Out::IDX)IY * o.row_stride + (typename Out::IDX)IX * o.tok_stride, a0, a1);
+    o.put(o.base + (typename Out::IDX)IY * o.row_stride + (typename Out::IDX)IX * o.tok_stride, a0, a1, 0);
     if constexpr ((IY & 1) && (IX & 1)) __builtin_amdgcn_sched_barrier(0);
   } else {
     constexpr int gl = 1 << M, e0 = IY * gl + IX;
@@ -182,7 +201,7 @@ __device__ __forceinline__ void dfs2d_reg(const float (&acc)[4][NI][16], float a
 // rowz0 = that row's entry of the per-row tables.  Per block: c = (acc - rowz * colsum) * rowfac in place, the
 // dequantized coefficient without the weight scale (symmetric plans have rowz = 0 and colsum operand 0: the fma
 // then leaves the sum as it is), then the depth-first inverse.
-template <int RB, bool IS2D, int T, int NB, bool YBF16, bool VEC, bool SYM, int NP>
+template <int RB, bool IS2D, int T, int NB, bool YBF16, bool VEC, bool SYM, bool RAG, int NP>
 __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI][16], const f2 (&P)[NP], f2 bias, f2 cs,
                                            RegOut<YBF16, VEC, !IS2D>& o, const float* rowfac0, const float* rowz0, int mrow0,
                                            int n, int m0) {
@@ -214,12 +233,35 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
       // The block sum comes from the 8-bit rows' GEMM (P), or - plans without top levels, blocks from khi on, marked
       // in the row table - it is the block's own coefficient 0, dequantized above like every other row.
       const bool own = reinterpret_cast<const int*>(rowfac0)[256 + 2 * T * R] == 1;
-      o.off0 = (own ? acc[RM::mi(T, 0)][0][RM::v(T, 0)] * o.sw0 : P[T][0]) + bias[0];
-      o.off1 = (own ? acc[RM::mi(T, 0)][1][RM::v(T, 0)] * o.sw1 : P[T][1]) + bias[1];
+      const float bs0 = own ? acc[RM::mi(T, 0)][0][RM::v(T, 0)] * o.sw0 : P[T][0];
+      const float bs1 = own ? acc[RM::mi(T, 0)][1][RM::v(T, 0)] * o.sw1 : P[T][1];
+      o.off0 = bs0 + bias[0];
+      o.off1 = bs1 + bias[1];
       if constexpr (!IS2D) {
         // token 0 of block j of sequence b is physical row b s + j R; bytes from the tile's first row
-        o.base = ((uint32_t)(mrow - m0) * (uint32_t)a.N + (uint32_t)n) * (uint32_t)(YBF16 ? 2 : 4);
-        dfs1d_reg<RL, T, 0, 0, RegOut<YBF16, VEC, true>>(acc, 0.0f, 0.0f, o);
+        uint32_t drow = (uint32_t)(mrow - m0);
+        bool short_block = false;
+        if constexpr (RAG) {
+          // token 0 of block j of sequence b is row b s + o + j R; o.Y points at that of the tile's first block
+          const int blk = mrow / R, blk0 = m0 / R, b = blk / g.k, b0 = blk0 / g.k;
+          drow += (uint32_t)((b - b0) * (g.s - g.k * R));
+          short_block = blk - b * g.k == a.rag.nb - 1 && a.rag.mlast < R;
+        }
+        o.base = (drow * (uint32_t)a.N + (uint32_t)n) * (uint32_t)(YBF16 ? 2 : 4);
+        if (RAG && short_block) {
+          if constexpr (RAG) {
+            RegOutShort<YBF16, VEC> os;
+            static_cast<RegOut<YBF16, VEC, true>&>(os) = o;
+            os.leaf = rowz0 + 256 - (mrow0 - m0);
+            os.bsum0 = bs0;
+            os.bsum1 = bs1;
+            os.bias0 = bias[0];
+            os.bias1 = bias[1];
+            dfs1d_reg<RL, T, 0, 0, RegOutShort<YBF16, VEC>>(acc, 0.0f, 0.0f, os);
+          }
+        } else {
+          dfs1d_reg<RL, T, 0, 0, RegOut<YBF16, VEC, true>>(acc, 0.0f, 0.0f, o);
+        }
       } else {
         const int b = mrow / g.s, pr = mrow - b * g.s;
         const int j = pr / g.R;
@@ -228,7 +270,7 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
         dfs2d_reg<RB, T, 0, 0, 0, RegOut<YBF16, VEC, false>>(acc, 0.0f, 0.0f, o);
       }
     }
-    blocks_reg<RB, IS2D, T + 1, NB, YBF16, VEC, SYM, NP>(a, acc, P, bias, cs, o, rowfac0, rowz0, mrow0, n, m0);
+    blocks_reg<RB, IS2D, T + 1, NB, YBF16, VEC, SYM, RAG, NP>(a, acc, P, bias, cs, o, rowfac0, rowz0, mrow0, n, m0);
   }
 }
 
@@ -236,9 +278,9 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
 // EPI 3: plans without a sequence transform (rows are tokens).
 // accv: the wave's accumulators, 4 x NIW blocks; this call handles the column pair PAIR (blocks 2 PAIR, 2 PAIR + 1:
 // the 64 columns from nw on).
-template <int EPI, int RB, bool IS2D, bool YBF16, bool VEC, int NIW, int PAIR, bool SYM>
+template <int EPI, int RB, bool IS2D, bool YBF16, bool VEC, int NIW, int PAIR, bool SYM, bool RAG>
 __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const v16f (&accv)[4][NIW], const uint8_t* row_info,
-                                                  const RegEpiOperands<EPI, (IS2D ? 2 * RB : RB)>& eo, int m0, int nw,
+                                                  const RegEpiOperands<EPI, (IS2D ? 2 * RB : RB), RAG>& eo, int m0, int nw,
                                                   int wm, int lane) {
   const StampGeom& g = a.g;
   // single registers from here on (the accumulator tuples are dead after this copy)
@@ -304,7 +346,12 @@ __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const v16f 
     o.nvalid = nvalid;
     if constexpr (!IS2D) {
       constexpr int esize = YBF16 ? 2 : 4;
-      o.Y = reinterpret_cast<char*>(a.out) + (size_t)m0 * a.N * esize;
+      size_t row0 = (size_t)m0;
+      if constexpr (RAG) {
+        const int blk0 = m0 / R, b0 = blk0 / g.k;
+        row0 = (size_t)b0 * g.s + a.rag.o + (size_t)(blk0 - b0 * g.k) * R;
+      }
+      o.Y = reinterpret_cast<char*>(a.out) + row0 * a.N * esize;
       o.tok_stride = (uint32_t)a.N * (uint32_t)esize;
       o.row_stride = 0;
     } else {
@@ -312,19 +359,21 @@ __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const v16f 
       o.tok_stride = (size_t)a.N;
       o.row_stride = (size_t)g.gridW * a.N;
     }
-    blocks_reg<RB, IS2D, 0, nb, YBF16, VEC, SYM>(a, acc, eo.P, eo.bias, eo.cs, o, s_rowfac + wm * 128 + kg * R, s_rowz + wm * 128 + kg * R,
+    blocks_reg<RB, IS2D, 0, nb, YBF16, VEC, SYM, RAG>(a, acc, eo.P, eo.bias, eo.cs, o, s_rowfac + wm * 128 + kg * R, s_rowz + wm * 128 + kg * R,
                                             m0 + wm * 128 + kg * R, n, m0);
   }
 }
 
-template <int EPI, int RB, bool IS2D, bool YBF16, int NIW = NI, int PAIR = 0, bool SYM = false>
+// ODD: a fused-mode kernel for odd d_out.  (A branch between the two forms inside one fused kernel costs 50 to 110 spilled
+// registers: 2048 tokens, 4096 -> 11008, 3 levels, first token left out: 67.8 us against 64.4.)
+template <int EPI, int RB, bool IS2D, bool YBF16, int NIW = NI, int PAIR = 0, bool SYM = false, bool RAG = false, bool ODD = false>
 __device__ __forceinline__ void epilogue_reg(const GemmArgs& a, const v16f (&acc)[4][NIW], const uint8_t* row_info,
-                                             const RegEpiOperands<EPI, (IS2D ? 2 * RB : RB)>& eo, int m0, int nw, int wm,
+                                             const RegEpiOperands<EPI, (IS2D ? 2 * RB : RB), RAG>& eo, int m0, int nw, int wm,
                                              int lane) {
-  // pairs of columns are stored as one word when d_out is even (the pair then never straddles the end); the
-  // fused inverse is only launched on even d_out (odd widths take the separate inverse kernel)
-  if (EPI == 2 || (a.N & 1) == 0) epilogue_reg_impl<EPI, RB, IS2D, YBF16, true, NIW, PAIR, SYM>(a, acc, row_info, eo, m0, nw, wm, lane);
-  else epilogue_reg_impl<EPI, RB, IS2D, YBF16, false, NIW, PAIR, SYM>(a, acc, row_info, eo, m0, nw, wm, lane);
+  // pairs of columns are stored as one word when d_out is even (the pair then never straddles the end)
+  if constexpr (EPI == 2) epilogue_reg_impl<EPI, RB, IS2D, YBF16, !ODD, NIW, PAIR, SYM, RAG>(a, acc, row_info, eo, m0, nw, wm, lane);
+  else if ((a.N & 1) == 0) epilogue_reg_impl<EPI, RB, IS2D, YBF16, true, NIW, PAIR, SYM, RAG>(a, acc, row_info, eo, m0, nw, wm, lane);
+  else epilogue_reg_impl<EPI, RB, IS2D, YBF16, false, NIW, PAIR, SYM, RAG>(a, acc, row_info, eo, m0, nw, wm, lane);
 }
 
 }  // namespace stamp_gemm

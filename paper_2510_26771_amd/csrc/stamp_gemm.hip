@@ -182,7 +182,7 @@ __device__ __forceinline__ int a_row_of(const GemmArgs& a, int m) { return m + (
 // WN = waves along N: 2 -> 4 waves, tile 256 x 128, two workgroups per CU; 4 -> 8 waves, tile 256 x 256,
 // one workgroup per CU (fewer, larger tiles: for the few 8-bit rows, whose whole GEMM is one round of tiles).
 // EPI 4 (8-bit rows): de-quantization + the top levels of the inverse, block sums written directly (epilogue_top_inverse).
-template <bool A_INT4, int EPI, int RB, bool IS2D, bool YBF16, int WN>
+template <bool A_INT4, int EPI, int RB, bool IS2D, bool YBF16, int WN, bool RAG = false>
 __global__ __launch_bounds__(128 * WN, (WN == 2 ? 2 : 1)) void k_gemm(const GemmArgs a_in) {
   GemmArgs a = a_in;
   using Acc = typename std::conditional<A_INT4, AccI8Lo, AccI8Hi>::type;
@@ -315,9 +315,9 @@ __global__ __launch_bounds__(128 * WN, (WN == 2 ? 2 : 1)) void k_gemm(const Gemm
 #define STAMP_REQUEST(KSTEP, STG) request((int)(KSTEP), (int)(STG))
 
   STAMP_REQUEST(kt0, 0);
-  EpiOperands<EPI, RB, IS2D> eo;
+  EpiOperands<EPI, RB, IS2D, RAG> eo;
   eo.request(a, m0, n0, lane, wm, wn);
-  if (NT == 256 || tid < 256) store_row_info<Acc, EPI>(a, m0, tid, smem + kRowInfoOff);
+  if (NT == 256 || tid < 256) store_row_info<Acc, EPI, RAG>(a, m0, tid, smem + kRowInfoOff);
 
   // Step kt: wait for this wave's loads of step kt, then the workgroup barrier (every wave's loads of
   // step kt have landed, and every wave has left step kt-1, whose stage is now free); request step
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(128 * WN, (WN == 2 ? 2 : 1)) void k_gemm(const Gemm
 #undef STAMP_REQUEST
 
   if constexpr (EPI == 4) epilogue_top_inverse<Acc, WN>(a, acc, smem, smem + kRowInfoOff, m0, n0, lane, wm, wn, tid);
-  else epilogue<Acc, EPI, RB, IS2D, YBF16>(a, acc, smem, smem + kRowInfoOff, eo, m0, n0, lane, wave, wm, wn);
+  else epilogue<Acc, EPI, RB, IS2D, YBF16, false, RAG>(a, acc, smem, smem + kRowInfoOff, eo, m0, n0, lane, wave, wm, wn);
 }
 
 // ------------------------------------------------------------------------------------------------------------
@@ -556,18 +556,18 @@ hipError_t launch_hi_few(const GemmArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <bool A_INT4, int EPI, int RB, bool IS2D, bool YBF16, int WN>
+template <bool A_INT4, int EPI, int RB, bool IS2D, bool YBF16, int WN, bool RAG = false>
 hipError_t launch_y(const GemmArgs& a, hipStream_t st) {
   constexpr int BN = 64 * WN;
   constexpr size_t main_lds = 2 * (size_t)(BM * (A_INT4 ? 64 : 128) + BN * 128);
   constexpr size_t epi_lds = (EPI >= 2) ? (size_t)(2 * WN * kWaveTileBytes) : 0;
   constexpr size_t lds = (main_lds > epi_lds ? main_lds : epi_lds) + kRowInfoBytes;  // + per-row factors, destinations, offsets
   static size_t lds_done[kStampMaxDevices] = {};
-  hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gemm<A_INT4, EPI, RB, IS2D, YBF16, WN>), lds, lds_done);
+  hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gemm<A_INT4, EPI, RB, IS2D, YBF16, WN, RAG>), lds, lds_done);
   if (e != hipSuccess) return e;
   const int mt = (a.M + BM - 1) / BM, nt = a.Npad / BN;
   const int split = (!A_INT4 && EPI == 1) ? a.ksplit : 1;
-  hipLaunchKernelGGL((k_gemm<A_INT4, EPI, RB, IS2D, YBF16, WN>), dim3(mt * nt * split), dim3(128 * WN), lds, st, a);
+  hipLaunchKernelGGL((k_gemm<A_INT4, EPI, RB, IS2D, YBF16, WN, RAG>), dim3(mt * nt * split), dim3(128 * WN), lds, st, a);
   return hipGetLastError();
 }
 
@@ -669,6 +669,7 @@ stamp_gemm::GemmArgs stamp_gemm_args(const stamp_plan* p, const float* scales, v
   a.split_stride = 0;
   a.a_seq_rows = a.a_seq_used = 1;
   a.own_top = 0;
+  a.rag = StampRag{};
   return a;
 }
 
@@ -730,6 +731,57 @@ hipError_t stamp_launch_gemm_lo(const stamp_plan* p, const uint8_t* q_lo, const 
   switch (g.r) {
     case 2: return launch<true, 2, 2, true>(a, st);
     case 3: return launch<true, 2, 3, true>(a, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// ---- blocked form of the 1-D Haar transform of any length (StampRag), int8 engine ----
+namespace {
+// packed 4-bit rows, STaMP order -> block order (rows without a coefficient: zeros); thread = 16 bytes of a row
+__global__ __launch_bounds__(256) void k_gather_lo(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ q_blk, StampRag rg, int s,
+                                                   int khi, int KT, int M, int total) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= total) return;
+  const int part = i & 3, row = (i >> 2) & 255, tk = i >> 10, mt = tk / KT, kt = tk - mt * KT;
+  const int m = mt * 256 + row, R = 1 << rg.r;
+  u4 w = {0u, 0u, 0u, 0u};
+  if (m < M) {
+    const int g = m / R, b = g / rg.nb, slot = stamp_rag_slot(rg, g - b * rg.nb, m - g * R);
+    if (slot >= khi) {
+      const size_t ms = (size_t)b * s + slot;
+      w = *reinterpret_cast<const u4*>(q_lo + (((ms >> 8) * KT + kt) * 256 + (ms & 255)) * 64 + part * 16);
+    }
+  }
+  *reinterpret_cast<u4*>(q_blk + (size_t)i * 16) = w;
+}
+
+template <int RB>
+hipError_t launch_rag(const GemmArgs& a, hipStream_t st) {
+  if (a.g.y_bf16) return launch_y<true, 2, RB, false, true, 2, true>(a, st);
+  return launch_y<true, 2, RB, false, false, 2, true>(a, st);
+}
+}  // namespace
+
+hipError_t stamp_launch_gather_lo_rag(const stamp_plan* p, const uint8_t* q_lo, uint8_t* q_blk, hipStream_t st) {
+  const int M = (p->geom.B * p->rag.nb) << p->rag.r, KT = p->Kpad / 128, total = ((M + 255) / 256) * KT * 1024;
+  hipLaunchKernelGGL(k_gather_lo, dim3((total + 255) / 256), dim3(256), 0, st, q_lo, q_blk, p->rag, p->geom.s, p->geom.khi, KT, M, total);
+  return hipGetLastError();
+}
+
+hipError_t stamp_launch_gemm_lo_rag(const stamp_plan* p, const uint8_t* q_blk, const float* scales, void* Y, const float* P, hipStream_t st) {
+  GemmArgs a = stamp_gemm_args(p, scales, Y);
+  a.A = q_blk;
+  a.g = p->bgeom;
+  a.rag = p->rag;
+  a.M = a.g.B * a.g.k * a.g.R;
+  a.a_row_bytes = p->geom.d / 2;
+  a.a_last16 = (size_t)((a.M + 255) / 256 * 256) * (p->Kpad / 2) - 16;
+  a.P = P;
+  switch (a.g.r) {
+    case 3: return launch_rag<3>(a, st);
+    case 4: return launch_rag<4>(a, st);
+    case 5: return launch_rag<5>(a, st);
+    case 6: return launch_rag<6>(a, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -78,6 +78,35 @@ __global__ __launch_bounds__(512) void k_repack6(const uint8_t* __restrict__ q_l
   *reinterpret_cast<ul2*>(dst + 2 * kPart) = ul2{hi[1], hi[2]};
 }
 
+// The same from rows in STaMP order to rows in the block order of StampRag (rows without a coefficient: zeros).
+__global__ __launch_bounds__(512) void k_repack6_rag(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, StampRag rg, int s,
+                                                     int khi, int KT, int M) {
+  const int blk = blockIdx.x, mt = blk / KT, kt = blk - mt * KT;
+  const int row = threadIdx.x & 255, kg = threadIdx.x >> 8;
+  const int m = mt * 256 + row, R = 1 << rg.r;
+  int slot = -1, b = 0;
+  if (m < M) {
+    const int g = m / R;
+    b = g / rg.nb;
+    slot = stamp_rag_slot(rg, g - b * rg.nb, m - g * R);
+  }
+  u4 w0 = {0u, 0u, 0u, 0u}, w1 = w0;
+  if (slot >= khi) {
+    const size_t ms = (size_t)b * s + slot;
+    const uint8_t* src = q_lo + (((ms >> 8) * KT + kt) * 256 + (ms & 255)) * 64 + kg * 16;
+    w0 = *reinterpret_cast<const u4*>(src);
+    w1 = *reinterpret_cast<const u4*>(src + 32);
+  }
+  uint8_t* dst = a6 + (size_t)blk * kStageA6 + (row >> 5) * kBlock6 + kg * 512 + (row & 31) * 16;
+  uint64_t lo[3], hi[3];
+  chunk_to_e2m3(w0, lo);
+  chunk_to_e2m3(w1, hi);
+  typedef uint64_t ul2 __attribute__((ext_vector_type(2)));
+  *reinterpret_cast<ul2*>(dst) = ul2{lo[0], lo[1]};
+  *reinterpret_cast<ul2*>(dst + kPart) = ul2{lo[2], hi[0]};
+  *reinterpret_cast<ul2*>(dst + 2 * kPart) = ul2{hi[1], hi[2]};
+}
+
 // Plan-time weight codes in that layout: per output channel n, code = rne(W_cn * (7 / max)) as in
 // the integer engine (round-to-nearest weights, one scale per output channel), stored as E2M3 c / 8.
 // One thread per (column, 32-channel fragment).
@@ -156,14 +185,16 @@ __device__ __forceinline__ void tile_of_sid(int sid, int mt, int nt, int& tm, in
 }
 
 // SYM: a fused-mode kernel for plans with symmetric activation codes (no offset term in the epilogue)
-template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM = false>
+// RAG: fused mode over the blocks of a 1-D Haar transform of any length (StampRag); ODD: for odd d_out
+template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM = false, bool RAG = false, bool ODD = false>
 __global__ __launch_bounds__(512, 1) void k_gemm6(const GemmArgs a) {
   using Acc = AccF6Lo;
   constexpr int NIW = NI;  // 32-column MFMA blocks per wave along N
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   constexpr int NT = 512;  // threads
   constexpr int kMainBytes = kNumStage6 * kStage6;
-  uint8_t* const row_info = smem + kMainBytes;  // two buffers of kRowInfoBytes, alternating from tile to tile
+  uint8_t* const row_info = smem + kMainBytes;  // two buffers, alternating from tile to tile
+  constexpr int kRowInfo = kRowInfoBytes + (RAG ? 256 : 0);  // RAG: + the token factors of a short block
   constexpr int nA = kStageA6 / (NT * 16), nB = 2 * kStageB6 / (NT * 16);  // 16-byte chunks per thread and step
   constexpr int kLoadsPerStep = nA + nB;
 
@@ -272,7 +303,14 @@ __global__ __launch_bounds__(512, 1) void k_gemm6(const GemmArgs a) {
   {
     int tm0, tn0;
     tile_of_sid(first + local, mt, nt, tm0, tn0);
-    if (tid < 256) store_row_info<Acc, EPI>(a, tm0 * BM, tid, row_info);
+    if (tid < 256) store_row_info<Acc, EPI, RAG>(a, tm0 * BM, tid, row_info);
+    if constexpr (RAG) {
+      if (tid < 64) {
+        const float f = tid < a.rag.mlast ? rag_leaf(a.rag, tid) : 0.0f;
+        reinterpret_cast<float*>(row_info + kRowInfoBytes)[tid] = f;
+        reinterpret_cast<float*>(row_info + kRowInfo + kRowInfoBytes)[tid] = f;
+      }
+    }
   }
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
@@ -482,7 +520,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm6(const GemmArgs a) {
     int lane_e = lane, tid_e = tid;
     asm volatile("" : "+v"(lane_e), "+v"(tid_e));
     // the epilogue's operands from global memory: their latency passes under the lane swaps
-    RegEpiOperands<EPI, (IS2D ? 2 * RB : RB)> eo;
+    RegEpiOperands<EPI, (IS2D ? 2 * RB : RB), RAG> eo;
     if constexpr (EPI >= 2) eo.request(a, m0, nw, wm, lane_e);
     // row factors of the next tile: loaded now, written to the other buffer after the epilogue (a barrier of
     // the next tile's first step publishes them long before its epilogue reads them)
@@ -492,9 +530,9 @@ __global__ __launch_bounds__(512, 1) void k_gemm6(const GemmArgs a) {
     if (has_next && tid_e < 256) {
       int tm1, tn1;
       tile_of_sid(first + pos + wx, mt, nt, tm1, tn1);
-      compute_row_info<Acc, EPI>(a, tm1 * BM, tid_e, nfac, ndst, nrz);
+      compute_row_info<Acc, EPI, RAG>(a, tm1 * BM, tid_e, nfac, ndst, nrz);
     }
-    const uint8_t* ri = row_info + rbuf * kRowInfoBytes;
+    const uint8_t* ri = row_info + rbuf * kRowInfo;
     if constexpr (EPI != 2) {
       // The loads just requested complete here, on every path and in a form the compiler's wait-count bookkeeping
       // sees: a load it believed pending at the end of the tile would make it wait for ALL loads inside the next
@@ -503,13 +541,13 @@ __global__ __launch_bounds__(512, 1) void k_gemm6(const GemmArgs a) {
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     }
     if constexpr (EPI >= 2) {
-      epilogue_reg<EPI, RB, IS2D, YBF16, NI, 0, SYM>(a, acc, ri, eo, m0, nw, wm, lane_e);
+      epilogue_reg<EPI, RB, IS2D, YBF16, NI, 0, SYM, RAG, ODD>(a, acc, ri, eo, m0, nw, wm, lane_e);
     } else {
       EpiOperands<EPI, RB, IS2D> none;
       epilogue<Acc, EPI, RB, IS2D, YBF16, true>(a, acc, smem, ri, none, m0, n0, lane_e, wave, wm, wn);
     }
     rbuf ^= 1;
-    if (has_next && tid_e < 256) write_row_info(row_info + rbuf * kRowInfoBytes, tid_e, nfac, ndst, nrz);
+    if (has_next && tid_e < 256) write_row_info(row_info + rbuf * kRowInfo, tid_e, nfac, ndst, nrz);
   }
 }
 
@@ -524,14 +562,14 @@ int gemm6_workgroups(int tiles) {
   return tiles < cus ? tiles : cus;
 }
 
-template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM>
+template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM, bool RAG = false, bool ODD = false>
 hipError_t launch_k(const GemmArgs& a, hipStream_t st) {
-  constexpr size_t lds = (size_t)kNumStage6 * kStage6 + 2 * kRowInfoBytes;
+  constexpr size_t lds = (size_t)kNumStage6 * kStage6 + 2 * (kRowInfoBytes + (RAG ? 256 : 0));
   static size_t lds_done[kStampMaxDevices] = {};
-  hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gemm6<EPI, RB, IS2D, YBF16, SYM>), lds, lds_done);
+  hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD>), lds, lds_done);
   if (e != hipSuccess) return e;
   const int mt = (a.M + BM - 1) / BM, nt = a.Npad / BN6;
-  hipLaunchKernelGGL((k_gemm6<EPI, RB, IS2D, YBF16, SYM>), dim3(gemm6_workgroups(mt * nt)), dim3(512), lds, st, a);
+  hipLaunchKernelGGL((k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD>), dim3(gemm6_workgroups(mt * nt)), dim3(512), lds, st, a);
   return hipGetLastError();
 }
 
@@ -568,6 +606,46 @@ hipError_t stamp_launch_weight_quant6(const stamp_plan* p, const float* W, const
 hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st) {
   hipLaunchKernelGGL(k_repack6, dim3((p->Mpad / 256) * (p->Kpad / 128)), dim3(512), 0, st, q_lo, a6);
   return hipGetLastError();
+}
+
+size_t stamp_rag_a6_bytes(const stamp_plan* p) {
+  const size_t M = (size_t)p->geom.B * p->rag.nb << p->rag.r;
+  return ((M + 255) / 256) * (p->Kpad / 128) * kStageA6;
+}
+
+hipError_t stamp_launch_repack6_rag(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st) {
+  const int M = (p->geom.B * p->rag.nb) << p->rag.r, KT = p->Kpad / 128;
+  hipLaunchKernelGGL(k_repack6_rag, dim3(((M + 255) / 256) * KT), dim3(512), 0, st, q_lo, a6, p->rag, p->geom.s, p->geom.khi, KT, M);
+  return hipGetLastError();
+}
+
+namespace {
+template <int RB, bool ODD>
+hipError_t launch_rag_n(const GemmArgs& a, hipStream_t st) {
+  if (a.g.y_bf16) return a.g.asym ? launch_k<2, RB, false, true, false, true, ODD>(a, st) : launch_k<2, RB, false, true, true, true, ODD>(a, st);
+  return a.g.asym ? launch_k<2, RB, false, false, false, true, ODD>(a, st) : launch_k<2, RB, false, false, true, true, ODD>(a, st);
+}
+template <int RB>
+hipError_t launch_rag(const GemmArgs& a, hipStream_t st) {
+  return (a.N & 1) ? launch_rag_n<RB, true>(a, st) : launch_rag_n<RB, false>(a, st);
+}
+}  // namespace
+
+hipError_t stamp_launch_gemm_lo6_rag(const stamp_plan* p, const uint8_t* a6, const float* scales, void* Y, const float* P, hipStream_t st) {
+  GemmArgs a = stamp_gemm_args(p, scales, Y);
+  a.A = a6;
+  a.Bq = p->qW6_dev;
+  a.g = p->bgeom;
+  a.rag = p->rag;
+  a.M = a.g.B * a.g.k * a.g.R;
+  a.P = P;
+  switch (a.g.r) {
+    case 3: return launch_rag<3>(a, st);
+    case 4: return launch_rag<4>(a, st);
+    case 5: return launch_rag<5>(a, st);
+    case 6: return launch_rag<6>(a, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t stamp_launch_gemm_lo6(const stamp_plan* p, const uint8_t* a6, const float* scales, int mode, void* out,

@@ -62,7 +62,22 @@ struct GemmArgs {
   int own_top;           // 4-bit rows, fused mode: coefficient 0 of the blocks from g.khi on is a 4-bit row of A (see
                          // compute_row_info); P then holds g.khi rows per sequence
   StampGeom g;
+  StampRag rag;          // RAG kernels: rows in the block order of StampRag (g.k = blocks, g.khi = 8-bit slots), scales in
+                         // STaMP order, P row b * g.khi + slot
 };
+
+// RAG kernels.  An inverse butterfly is (a +- d) / sqrt 2, but a node without partner is its parent unchanged.  The
+// epilogue runs plain a +- d as for whole blocks; a short block is made up for by factors: token i of it by sqrt(2) per
+// carry on its path (rag_leaf), a detail (and the approximation) by 1 / sqrt(2) per carry above it (rag_norm), so that
+// every product along a path comes out right.
+__device__ __forceinline__ float rag_leaf(const StampRag& q, int i) {
+  const int c = stamp_rag_carries(q.mlast, 0, i, q.r);
+  return ldexpf((c & 1) ? 1.41421356237309504880f : 1.0f, c >> 1);
+}
+__device__ __forceinline__ float rag_norm(const StampRag& q, int j, int level, int i) {
+  const int c = level + ((j == q.nb - 1) ? stamp_rag_carries(q.mlast, level, i, q.r) : 0);
+  return haar_norm_dev(c, 0);
+}
 
 // How a kernel's accumulators map to the integer sum acc = sum_c code[m, c] * qW[c, n]:
 //   int8 MFMA, 4-bit rows: both operands are held as code * 16         -> register = 256 acc
@@ -122,7 +137,7 @@ __device__ __forceinline__ void tile_of_block_split(int M, int ksplit, int& tm, 
 // Where one lane stores the tokens of one unit (an aligned part of a block): 8 adjacent output columns
 // per token, written as one 16-byte store (bf16) or two (fp32) when d_out allows it.  The 8 lanes of a
 // unit's group thus cover the wave tile's 64 columns: whole 128-byte lines of a bf16 Y.
-template <bool YBF16, bool VEC>
+template <bool YBF16, bool VEC, bool RAG = false>
 struct OutOct {
   void* Y;
   size_t base;        // element index of token 0 of the block, first of the 8 columns
@@ -131,10 +146,26 @@ struct OutOct {
   f8 scale;           // weight scales of the 8 columns
   f8 offset;          // block sum of the unit's block + bias, per column
   int nvalid;         // how many of the 8 columns exist (d_out tail)
+  // RAG, units of a short block: tokens of the unit that exist (< 0: a whole block), the unit's first token in its block
+  const StampRag* rag;
+  int ntok, tok0;
+  f8 bsum, bias;
   // v = the token's sum of +-detail coefficients, still without the weight scale: one fma per output
-  __device__ __forceinline__ void put(size_t idx, f8 v) const {
+  __device__ __forceinline__ void put(size_t idx, f8 v, int tok = 0) const {
+    bool whole = true;
+    if constexpr (RAG) {
+      whole = ntok < 0;
+      if (!whole) {
+        if (tok >= ntok) return;
+        const float f = rag_leaf(*rag, tok0 + tok);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) v[t] = __builtin_fmaf(v[t], scale[t], offset[t]);
+        for (int t = 0; t < 8; ++t) v[t] = __builtin_fmaf(v[t] * f, scale[t], bsum[t] * f + bias[t]);
+      }
+    }
+    if (whole) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v[t] = __builtin_fmaf(v[t], scale[t], offset[t]);
+    }
     if constexpr (YBF16) {
       // round-to-nearest-even pairs in hardware (v_cvt_pk_bf16_f32)
       u4 w;
@@ -182,7 +213,7 @@ __device__ __forceinline__ f8 tile_row(const float* tile, int e) {
 template <int RLOG, int M0, int M, int I, typename Out>
 __device__ __forceinline__ void dfs1d(const float* tile, int h, f8 a, const Out& o) {
   if constexpr (M == RLOG) {
-    o.put(o.base + (size_t)((h << (RLOG - M0)) + I) * o.tok_stride, a);
+    o.put(o.base + (size_t)((h << (RLOG - M0)) + I) * o.tok_stride, a, I);
   } else {
     const f8 d = tile_row(tile, (1 << M) + (h << (M - M0)) + I);
     dfs1d<RLOG, M0, M + 1, 2 * I, Out>(tile, h, a + d, o);
@@ -226,7 +257,7 @@ struct EpiShape {
 
 // Global operands of the fused epilogue (weight scales, bias, block sums P of this lane's units),
 // requested ahead of the main loop so that their latency is not on the epilogue's path.
-template <int EPI, int RB, bool IS2D>
+template <int EPI, int RB, bool IS2D, bool RAG = false>
 struct EpiOperands {
   using ES = EpiShape<(EPI == 2 ? RB : 3), IS2D>;
   float cs[NI];  // column sums of the weight codes (asymmetric plans)
@@ -254,7 +285,12 @@ struct EpiOperands {
         for (int pass = 0; pass < ES::npass; ++pass) {
           const int blk = (pass * 8 + ug) / ES::U;
           const int mrow = min(m0 + wm * 128 + hf * 64 + blk * ES::R, a.M - 1);
-          const float* src = a.P + (size_t)(mrow / a.g.R) * a.Npad + nw + c8;
+          int prow = mrow / a.g.R;
+          if constexpr (RAG) {
+            const int b = prow / a.g.k;
+            prow = b * a.g.khi + min(prow - b * a.g.k + a.rag.o, max(a.g.khi - 1, 0));
+          }
+          const float* src = a.P + (size_t)prow * a.Npad + nw + c8;
           const f4 p0 = *reinterpret_cast<const f4*>(src), p1 = *reinterpret_cast<const f4*>(src + 4);
           top[hf][pass] = (f8){p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
         }
@@ -268,7 +304,7 @@ struct EpiOperands {
 // format's constant), destination row, and (asymmetric plans) the offset of the stored code in
 // accumulator units, of tile row `tid`, written to LDS at row_info (kRowInfoBytes) before the main
 // loop; the main loop's barriers publish them.
-template <typename Acc, int EPI>
+template <typename Acc, int EPI, bool RAG = false>
 __device__ __forceinline__ void compute_row_info(const GemmArgs& a, int m0, int tid, float& fac, int& dst, float& rz) {
   const StampGeom& g = a.g;
   const int m = m0 + tid;
@@ -276,6 +312,21 @@ __device__ __forceinline__ void compute_row_info(const GemmArgs& a, int m0, int 
   rz = 0.0f;
   dst = -1;
   const size_t zeros_off = (size_t)g.B * g.s;
+  if constexpr (RAG) {
+    // rows that do not exist (short block) and 8-bit approximations: factor 0, their accumulator counts for nothing
+    if (m < a.M) {
+      const int blk = m / g.R, e = m - blk * g.R, b = blk / g.k, j = blk - b * g.k;
+      const int slot = stamp_rag_slot(a.rag, j, e);
+      if (slot >= g.khi) {
+        const int lm = e == 0 ? 0 : 31 - __builtin_clz((unsigned)e);
+        const size_t row = (size_t)b * g.s + slot;
+        fac = a.scales[row] * rag_norm(a.rag, j, g.r - lm, e == 0 ? 0 : e - (1 << lm)) * Acc::kToAcc;
+        if (g.asym) rz = (a.scales[zeros_off + row] - Acc::kZeroShift) * (1.0f / Acc::kToAcc);
+        dst = 1;
+      }
+    }
+    return;
+  }
   if (m < a.M && g.ident) {
     // no sequence transform: row = token, level 0 (norm 1); tokens 0..k-1 of a sequence are the 8-bit rows
     size_t row;
@@ -335,11 +386,11 @@ __device__ __forceinline__ void write_row_info(uint8_t* row_info, int tid, float
   reinterpret_cast<float*>(row_info + 2048)[tid] = rz;  // [256] (z - 2^(b-1)) / kToAcc
 }
 
-template <typename Acc, int EPI>
+template <typename Acc, int EPI, bool RAG = false>
 __device__ __forceinline__ void store_row_info(const GemmArgs& a, int m0, int tid, uint8_t* row_info) {
   float fac, rz;
   int dst;
-  compute_row_info<Acc, EPI>(a, m0, tid, fac, dst, rz);
+  compute_row_info<Acc, EPI, RAG>(a, m0, tid, fac, dst, rz);
   write_row_info(row_info, tid, fac, dst, rz);
 }
 
@@ -352,9 +403,9 @@ __device__ __forceinline__ void store_row_info(const GemmArgs& a, int m0, int ti
 // sequence transform: dequantized rows + bias -> Y through the same staging (4-bit rows only).
 // PAIRCOLS: the weights are stored so that MFMA column l32 of block ni is column 2 l32 + ni of the wave's 64
 // (the FP6 engine's layout) instead of 32 ni + l32.
-template <typename Acc, int EPI, int RB, bool IS2D, bool YBF16, bool PAIRCOLS = false>
+template <typename Acc, int EPI, int RB, bool IS2D, bool YBF16, bool PAIRCOLS = false, bool RAG = false>
 __device__ __forceinline__ void epilogue(const GemmArgs& a, typename Acc::V (&acc)[4][NI], uint8_t* smem,
-                                         const uint8_t* row_info, const EpiOperands<EPI, RB, IS2D>& eo, int m0,
+                                         const uint8_t* row_info, const EpiOperands<EPI, RB, IS2D, RAG>& eo, int m0,
                                          int n0, int lane, int wave, int wm, int wn) {
   const StampGeom& g = a.g;
   const int l32 = lane & 31, kg = lane >> 5;
@@ -429,7 +480,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, typename Acc::V (&ac
     const int n = nw + c8;        // first of this lane's 8 output columns
     auto run_halves = [&](auto vec_tag) __attribute__((always_inline)) {
       constexpr bool VEC = decltype(vec_tag)::value;
-      OutOct<YBF16, VEC> o;
+      OutOct<YBF16, VEC, RAG> o;
       o.Y = a.out;
       o.tok_stride = (size_t)a.N;
       o.row_stride = (size_t)g.gridW * a.N;
@@ -505,11 +556,21 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, typename Acc::V (&ac
           const int blk = unit / U, h = unit % U;
           const int mrow = m0 + wm * 128 + hf * 64 + blk * R;  // physical row of e = 0 of this block
           if (mrow < a.M && n < a.N) {
-            const int b = mrow / g.s, pr = mrow - b * g.s;
-            const int j = pr / g.R;
-            o.offset = eo.top[hf][pass] + eo.bias;
-            f8 top = (f8){0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};  // signed detail sum on the path to the unit
+            const int seq_rows = RAG ? g.k * R : g.s;
+            const int b = mrow / seq_rows, pr = mrow - b * seq_rows;
+            const int j = pr / R;
+            f8 bsum = eo.top[hf][pass];
             const float* tile = s_tile + blk * R * kEpiStride + 4 * (lane & 7);
+            if constexpr (RAG) {
+              // 4-bit approximations are rows like any other (their own coefficient 0)
+              if (s_rowdst[wm * 128 + hf * 64 + blk * R] == 1) {
+                const f8 c0 = tile_row(tile, 0);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) bsum[t] = c0[t] * eo.sw8[t];
+              }
+            }
+            o.offset = bsum + eo.bias;
+            f8 top = (f8){0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};  // signed detail sum on the path to the unit
             if constexpr (IS2D) {
               const int bi = j / g.G, bj = j - bi * g.G;
               o.base = ((size_t)b * g.s + (size_t)(bi << RB) * g.gridW + (size_t)(bj << RB)) * a.N + n;
@@ -527,15 +588,23 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, typename Acc::V (&ac
                 const int qy = (hy >> (M0 - m - 1)) & 1, qx = (hx >> (M0 - m - 1)) & 1;
                 top = qy ? (qx ? (t2 - t3) : (t2 + t3)) : (qx ? (t0 - t1) : (t0 + t1));
               }
-              dfs2d<RB, M0, M0, 0, 0, OutOct<YBF16, VEC>>(tile, hy, hx, top, o);
+              dfs2d<RB, M0, M0, 0, 0, OutOct<YBF16, VEC, RAG>>(tile, hy, hx, top, o);
             } else {
-              o.base = ((size_t)b * g.s + (size_t)j * R) * a.N + n;
+              o.base = ((size_t)b * g.s + (size_t)j * R + (RAG ? a.rag.o : 0)) * a.N + n;
+              if constexpr (RAG) {
+                constexpr int UT = R >> M0;  // tokens per unit
+                o.rag = &a.rag;
+                o.tok0 = h * UT;
+                o.ntok = (j == a.rag.nb - 1 && a.rag.mlast < R) ? max(a.rag.mlast - o.tok0, 0) : -1;
+                o.bsum = bsum;
+                o.bias = eo.bias;
+              }
 #pragma unroll
               for (int m = 0; m < M0; ++m) {
                 const f8 d = tile_row(tile, (1 << m) + (h >> (M0 - m)));
                 top = ((h >> (M0 - m - 1)) & 1) ? (top - d) : (top + d);
               }
-              dfs1d<RB, M0, M0, 0, OutOct<YBF16, VEC>>(tile, h, top, o);
+              dfs1d<RB, M0, M0, 0, OutOct<YBF16, VEC, RAG>>(tile, h, top, o);
             }
           }
         }

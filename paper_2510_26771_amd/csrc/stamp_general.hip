@@ -656,6 +656,24 @@ __global__ __launch_bounds__(256) void k_gen_merge_hi(const float* __restrict__ 
   Yt[bo + (size_t)i * ld + c] = v;
 }
 
+// Blocked form (StampRag): sum of the 8-bit rows' partial rows [nparts][B * khi][N], approximations times the norm of
+// their level -> block sums P [B * khi][Npad]; the token that was left out (slot 0) + bias -> its row of Y.
+__global__ __launch_bounds__(256) void k_rag_top(const float* __restrict__ ythi, int nparts, size_t part_stride, float* __restrict__ P,
+                                                 void* __restrict__ Y, const float* __restrict__ bias, int y_bf16, StampRag rg,
+                                                 float norm, int khi, int s, int N, int Npad) {
+  const int n = blockIdx.x * blockDim.x + threadIdx.x, row = blockIdx.y;
+  if (n >= N) return;
+  const size_t idx = (size_t)row * N + n;
+  float v = ythi[idx];
+  for (int part = 1; part < nparts; ++part) v += ythi[idx + part * part_stride];
+  const int b = row / khi, slot = row - b * khi;
+  if (slot < rg.o) {
+    gen_store_y(Y, y_bf16, (size_t)b * s * N + n, v + (bias != nullptr ? bias[n] : 0.0f));
+  } else {
+    P[(size_t)row * Npad + n] = v * norm;
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Per-block scales
 // ---------------------------------------------------------------------------------------------
@@ -1315,5 +1333,12 @@ hipError_t stamp_launch_merge_hi(const stamp_plan* p, const float* ythi, int npa
 hipError_t stamp_launch_add_ell_bias(const stamp_plan* p, float* Yt, hipStream_t st) {
   const StampGeom& g = p->geom;
   hipLaunchKernelGGL(k_gen_add_ell_bias, rows_grid(g.N, g.s, g.B), dim3(rows_block(g.N, g.s, g.B)), 0, st, Yt, p->ell_dev, p->bias_dev, g.s, g.N);
+  return hipGetLastError();
+}
+
+hipError_t stamp_launch_rag_top(const stamp_plan* p, const float* ythi, int nparts, float* P, void* Y, hipStream_t st) {
+  const StampGeom& g = p->geom;
+  hipLaunchKernelGGL(k_rag_top, rows_grid(g.N, g.B * g.khi, 1), dim3(rows_block(g.N, g.B * g.khi, 1)), 0, st, ythi, nparts,
+                     (size_t)g.B * g.khi * (size_t)g.N, P, Y, p->bias_dev, g.y_bf16, p->rag, haar_norm_host(p->rag.r), g.khi, g.s, g.N, p->Npad);
   return hipGetLastError();
 }

@@ -47,6 +47,33 @@ struct StampGen {
   int32_t gridH, gridW;
 };
 
+// Blocked form of a 1-D Haar transform of any length, optionally with the first token left out (o = 1): the n = s - o
+// transformed tokens are nb blocks of R = 2^r tokens, r = the number of levels, the last one of mlast <= R tokens; a
+// block's coefficients are one approximation and R - 1 details (fewer in a short block), as in the power-of-two case.
+// Block order: row b * nb * R + j * R + e, e = in-block position (0 = the approximation).
+struct StampRag {
+  int32_t on, o, n, nb, mlast, r;
+};
+// STaMP slot of in-block position e of block j, -1 where a short block has no such coefficient.  The details of level l
+// sit from slot o + ceil(n / 2^l) on; one exists where both of its halves do.
+STAMP_HD int stamp_rag_slot(const StampRag& q, int j, int e) {
+  if (e == 0) return q.o + j;
+  const int m = 31 - __builtin_clz((unsigned)e), l = q.r - m, idx = (j << m) + e - (1 << m);
+  if (2 * idx + 1 >= ((q.n + (1 << (l - 1)) - 1) >> (l - 1))) return -1;
+  return q.o + ((q.n + (1 << l) - 1) >> l) + idx;
+}
+// How often a node of level l (index i inside the short last block of m tokens) is carried up unchanged on its way to
+// level r: where a level has an odd number of nodes, the last one has no partner.
+STAMP_HD int stamp_rag_carries(int m, int l, int i, int r) {
+  int cnt = 0;
+  for (int k = l; k < r; ++k) {
+    const int nk = (m + (1 << k) - 1) >> k;
+    cnt += (i == nk - 1 && (nk & 1)) ? 1 : 0;
+    i >>= 1;
+  }
+  return cnt;
+}
+
 // Position inside a block ("e", 0 = the block sum, e >= 1 the in-block detail rows in STaMP
 // order) of the coefficient that the in-place butterfly network leaves at natural position q.
 // 1-D: in-place butterflies at stride 2^l leave the level-l difference of pair i at position
@@ -149,12 +176,15 @@ struct stamp_plan {
   int32_t unfused;          // 1: separate inverse kernel
   int32_t fused_ok;         // shape allows the fused epilogue
   StampGen gen;             // general path (kind != kGenNone)
+  StampRag rag;             // general path, 1-D Haar of any length: blocked form (rag.on), geometry in bgeom
+  StampGeom bgeom;
   int32_t* perm_dev;        // general path, WHT: [s] STaMP slot of every row of the Hadamard-ordered result
   float* ell_dev;           // general path, transformed bias: [s] l = L 1
   double* dct_dev;          // general path, DCT: [s][s] orthonormal DCT-II matrix
   int8_t* qWg_dev;          // per-block scales: weight codes [Npad128][d_in] int8
   float* swg_dev;           // per-block scales: [d_in / 64][Npad128]
   size_t ws_T[3], ws_Yt[3], ws_codes8, ws_scalesg;  // general path workspace (byte offsets)
+  size_t ws_ba6, ws_bP;     // blocked form: the 4-bit rows in block order (over ws_T), the block sums (over ws_Yt)
   // workspace layout (byte offsets, 256-aligned)
   size_t ws_abot, ws_rowmax, ws_gpart, ws_qhi, ws_qlo, ws_scales, ws_ythi, ws_P, ws_a6, ws_ytlo, ws_total;
 };
@@ -211,6 +241,16 @@ size_t stamp_a6_bytes(const stamp_plan* p);
 size_t stamp_b6_bytes(const stamp_plan* p);
 hipError_t stamp_launch_weight_quant6(const stamp_plan* p, const float* W, const uint32_t* colmax, hipStream_t st);
 hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st);
+// blocked form (p->rag.on): the same conversion from rows in STaMP order to block order; packed nibbles in block order
+// for the int8 engine; and the two GEMMs with the inverse transform in their epilogue
+size_t stamp_rag_a6_bytes(const stamp_plan* p);
+hipError_t stamp_launch_repack6_rag(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st);
+hipError_t stamp_launch_gather_lo_rag(const stamp_plan* p, const uint8_t* q_lo, uint8_t* q_blk, hipStream_t st);
+hipError_t stamp_launch_gemm_lo6_rag(const stamp_plan* p, const uint8_t* a6, const float* scales, void* Y, const float* P, hipStream_t st);
+hipError_t stamp_launch_gemm_lo_rag(const stamp_plan* p, const uint8_t* q_blk, const float* scales, void* Y, const float* P, hipStream_t st);
+// 8-bit rows' partial rows [nparts][B*khi][N] -> block sums P [B*khi][Npad] (times the blocks' norm); with the first
+// token left out, its row (+ bias) -> Y
+hipError_t stamp_launch_rag_top(const stamp_plan* p, const float* ythi, int nparts, float* P, void* Y, hipStream_t st);
 // own_top (mode 2, plans without top levels): the blocks from khi on take their sum from their own coefficient 0,
 // a 4-bit row of a6 like any other (the quantizer writes it there as well), and P holds khi rows per sequence
 hipError_t stamp_launch_gemm_lo6(const stamp_plan* p, const uint8_t* a6, const float* scales, int mode, void* out,
@@ -230,6 +270,9 @@ void stamp_gen_plan_free(stamp_plan* p);
 hipError_t stamp_gen_forward(const stamp_plan* p, const void* X, float* const (&buf)[3], float** T_out, hipStream_t st);
 // Yt [B, s, ncols] fp32 in STaMP order (buf[0], only read) -> Y; buf[1], buf[2]: the levels' work buffers
 hipError_t stamp_gen_inverse(const stamp_plan* p, float* const (&buf)[3], int ncols, const float* bias, void* Y, hipStream_t st);
+// blocked form: X -> codes and scales in STaMP order in one pass; false where the kernel does not take the plan or X
+bool stamp_rag_quantizes(const stamp_plan* p, const void* X);
+hipError_t stamp_launch_actquant_rag(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st);
 hipError_t stamp_launch_quant_rows_f32(const stamp_plan* p, const float* T, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st);
 hipError_t stamp_launch_quant_rows_grouped(const stamp_plan* p, const float* T, int8_t* codes, float* scales, hipStream_t st);
 hipError_t stamp_launch_gemm_grouped(const stamp_plan* p, const int8_t* codes, const float* scales, float* Yt, hipStream_t st);

@@ -86,3 +86,26 @@ WHT = [_wl(f"wht_{1 << J}", batch=2 if J < 10 else 1, xform="wht", levels=0, seq
 @pytest.mark.parametrize("w", WHT, ids=[w.name for w in WHT])
 def test_wht_lengths(w):
     tl.full_case(w, with_bias=True, check_unfused=False, engines=("fp6",))
+
+
+# ---- 1-D Haar of any length in its blocked form (3 .. 6 levels): every number of tokens in the short last block, blocks
+# that cross the GEMM's row tiles, 8-bit tokens from one to all approximations, odd d_out
+def _rag(levels, n, skip, **kw):
+    s = n + skip
+    kw.setdefault("k_hi", max(1, min(16, (n >> levels) // 2)))
+    return _wl(f"rag_L{levels}_n{n}_o{skip}_k{kw['k_hi']}_N{kw.get('d_out', 192)}", seq_len=s, levels=levels,
+               skip_first=bool(skip), seed=300 + n, **kw)
+
+
+RAG = ([_rag(3, 40 + m, m & 1, batch=3, d_in=96, d_out=68) for m in range(1, 9)] +
+       [_rag(4, 300 + m, 1, batch=2, d_in=64, act_quant="asym", mean_shift=0.3) for m in (1, 4, 6, 11)] +
+       [_rag(5, 513 + m, 1, d_in=160, d_out=257, x_dtype="bf16") for m in (0, 6, 31)] +
+       [_rag(6, 700 + m, 1, batch=2, d_in=64, d_out=130) for m in (5, 25, 60)] +
+       [_rag(3, 1023, 1, k_hi=129, d_out=515), _rag(3, 1000, 0, k_hi=1), _rag(4, 776, 1, batch=3, k_hi=32, d_out=33),
+        _rag(3, 5, 1, k_hi=1), _rag(3, 9, 1, k_hi=3)])
+
+
+@pytest.mark.parametrize("w", RAG, ids=[w.name for w in RAG])
+def test_blocked_haar_of_any_length(w):
+    for y in ("f32", "bf16"):
+        tl.full_case(w, with_bias=True, check_unfused=False, y_dtype=y)
