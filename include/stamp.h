@@ -252,7 +252,9 @@ stamp_status_t stamp_debug_weight_codes(const stamp_plan_t* plan, int8_t* qW_hos
  *   6 conversion of the packed 4-bit rows to the FP6 engine's operand layout (FP6 engine only; with
  *     that engine stage 4 is the GEMM alone and reads what stage 6 wrote to the workspace)
  * Plans whose transform has no levels above the blocks: stage 0 also quantizes the block sums, stage 2 writes
- * the block sums of the inverse itself, stages 1 and 3 launch nothing.
+ * the block sums of the inverse itself, stages 1 and 3 launch nothing.  Plans with few 8-bit rows over the batch: stage 2
+ * converts them, multiplies them on the FP6 pipeline and writes the block sums (without a transform: their rows of Y),
+ * stage 3 launches nothing.
  * Plans without transform: 0 the quantization kernel, 2 GEMM of the 8-bit rows, 3 their output pass,
  * 6 and 4 as above; 1 and 5 return STAMP_ERR_UNSUPPORTED. */
 stamp_status_t stamp_debug_run_stage(const stamp_plan_t* plan, int32_t stage, const void* X_dev,
@@ -278,7 +280,8 @@ stamp_status_t stamp_plan_set_unfused(stamp_plan_t* plan, int32_t unfused);
  *                    acc / 64 exactly (|acc| <= 49 d_in < 2^24).  Costs one conversion pass over the
  *                    packed rows inside stamp_linear_forward(_q);
  *   STAMP_GEMM_INT8  the codes as int8, int8 x int8 -> int32 MFMA.
- * The 8-bit rows always run on the int8 pipeline.  May be changed between calls (it modifies the plan:
+ * The 8-bit rows run on the int8 pipeline, or (few of them over the batch) as two 4-bit rows each on the FP6 pipeline,
+ * with the same integer sums, whatever this setting is.  May be changed between calls (it modifies the plan:
  * not thread-safe, no call on the plan may be in progress on another host thread); the workspace size
  * does not depend on it.  Returns STAMP_ERR_UNSUPPORTED for any other value. */
 typedef enum { STAMP_GEMM_INT8 = 0, STAMP_GEMM_FP6 = 1 } stamp_gemm_engine_t;

@@ -240,7 +240,10 @@ void layout_workspace(stamp_plan* p) {
     // lie over the former, its block sums over the latter (a plan for which they do not fit keeps the level kernels)
     p->ws_ba6 = p->ws_T[0];
     p->ws_bP = p->ws_Yt[0];
-    if (p->rag.on && (stamp_rag_a6_bytes(p) > p->ws_Yt[0] - p->ws_T[0] ||
+    p->ws_hi6 = p->ws_T[2];
+    p->hi6[0] = stamp_hi6_fits(p, 0) && stamp_hi6_bytes(p, 0) <= p->ws_Yt[0] - p->ws_T[2];
+    p->hi6[1] = 0;
+    if (p->rag.on && (stamp_rag_a6_bytes(p) > p->ws_T[2] - p->ws_T[0] ||
                       (size_t)g.B * g.khi * p->Npad * sizeof(float) > p->ws_codes8 - p->ws_Yt[0]))
       p->rag.on = 0;
     return;
@@ -264,6 +267,17 @@ void layout_workspace(stamp_plan* p) {
   p->ws_ytlo = off;
   if (p->unfused || !p->fused_ok) take((size_t)g.B * g.s * g.N * sizeof(float));
   p->ws_total = off;
+  // The 8-bit rows' FP6 operand lies over the quantizer's scratch, which is free by then, or (a dozen rows or fewer, the
+  // operand is padded to 32) behind everything else, unless that would put the plan beyond the static scratch array.
+  for (int own = 0; own < 2; ++own) {
+    p->hi6[own] = stamp_hi6_fits(p, own);
+    if (!p->hi6[own]) continue;
+    const size_t need = stamp_hi6_bytes(p, own);
+    if (need <= p->ws_qhi - p->ws_abot) continue;
+    if (off <= STAMP_STATIC_SCRATCH_BYTES && align256(off + need) > STAMP_STATIC_SCRATCH_BYTES) p->hi6[own] = 0;
+    else if (p->ws_total < align256(off + need)) p->ws_total = align256(off + need);
+  }
+  p->ws_hi6 = p->ws_total > off ? off : p->ws_abot;
 }
 
 inline bool ws_ok(const stamp_plan* p, const void* ws, size_t bytes, size_t need) {
@@ -283,12 +297,20 @@ inline bool own_top(const stamp_plan* p) {
 }
 
 // block sums of the first khi blocks of every sequence -> P [B * khi][Npad]
-inline hipError_t stamp_launch_block_sums_own(const stamp_plan* p, const int8_t* q_hi, const float* scales, float* ythi,
-                                              float* P, hipStream_t st) {
+inline hipError_t launch_block_sums_own(const stamp_plan* p, const int8_t* q_hi, const float* scales, float* ythi,
+                                        float* P, const uint8_t* hi6, hipStream_t st) {
+  if (p->hi6[1]) return stamp_launch_hi6(p, hi6, scales, 0, P, p->Npad, 1, nullptr, 1.0f, st);
   if (p->hi_ksplit_own <= 1) return stamp_launch_gemm_hi(p, q_hi, scales, 1, P, st, p->Npad, true);
   const hipError_t e = stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st, 0, true);
   if (e != hipSuccess) return e;
   return stamp_launch_sum_parts(ythi, p->hi_ksplit_own, p->geom.B * p->geom.khi, p->geom.N, P, p->Npad, st);
+}
+
+// Packed codes -> FP6 operands, one launch: the 4-bit rows (q_lo given) and the 8-bit rows (hi).
+inline hipError_t convert_rows(const stamp_plan* p, const int8_t* q_hi, const uint8_t* q_lo, uint8_t* a6, bool hi, int own, void* ws,
+                               hipStream_t st) {
+  const StampHi6Pack hp = hi ? stamp_hi6_pack(p, q_hi, at(ws, p->ws_hi6), own) : StampHi6Pack{};
+  return stamp_launch_repack6(p, q_lo, a6, st, &hp);
 }
 
 // Blocked form of the 1-D Haar transform of any length (rules: rag_geometry): block sums from the 8-bit rows, then the
@@ -300,16 +322,19 @@ stamp_status_t rag_forward_q(const stamp_plan* p, const int8_t* q_hi, const uint
   float* ythi = reinterpret_cast<float*>(at(ws, p->ws_ythi));
   float* P = reinterpret_cast<float*>(at(ws, p->ws_bP));
   uint8_t* blk = at(ws, p->ws_ba6);
-  if (stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st) != hipSuccess) return STAMP_ERR_DEVICE;
-  if (stamp_launch_rag_top(p, ythi, p->hi_ksplit, P, Y, st) != hipSuccess) return STAMP_ERR_DEVICE;
-  hipError_t e;
-  if (p->engine == STAMP_GEMM_FP6) {
-    e = stamp_launch_repack6_rag(p, q_lo, blk, st);
-    if (e == hipSuccess) e = stamp_launch_gemm_lo6_rag(p, blk, scales, Y, P, st);
+  uint8_t* hi6 = at(ws, p->ws_hi6);
+  const bool fp6 = p->engine == STAMP_GEMM_FP6;
+  const StampHi6Pack hp = p->hi6[0] ? stamp_hi6_pack(p, q_hi, hi6, 0) : StampHi6Pack{};
+  hipError_t e = fp6 ? stamp_launch_repack6_rag(p, q_lo, blk, st, &hp) : stamp_launch_gather_lo_rag(p, q_lo, blk, st);
+  if (e == hipSuccess && !fp6) e = stamp_launch_repack6(p, nullptr, nullptr, st, &hp);
+  if (e != hipSuccess) return STAMP_ERR_DEVICE;
+  if (p->hi6[0]) {
+    e = stamp_launch_hi6(p, hi6, scales, 3, P, p->Npad, 0, Y, stamp_haar_norm_host(p->rag.r), st);
   } else {
-    e = stamp_launch_gather_lo_rag(p, q_lo, blk, st);
-    if (e == hipSuccess) e = stamp_launch_gemm_lo_rag(p, blk, scales, Y, P, st);
+    e = stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st);
+    if (e == hipSuccess) e = stamp_launch_rag_top(p, ythi, p->hi_ksplit, P, Y, st);
   }
+  if (e == hipSuccess) e = fp6 ? stamp_launch_gemm_lo6_rag(p, blk, scales, Y, P, st) : stamp_launch_gemm_lo_rag(p, blk, scales, Y, P, st);
   return e == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
 }
 
@@ -328,14 +353,17 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
       // q_hi carries every token's int8 codes, scales one per token and 64-channel group
       if (stamp_launch_gemm_grouped(p, q_hi, scales, yt[0], st) != hipSuccess) return STAMP_ERR_DEVICE;
     } else {
-      if (p->geom.k > 0) {
+      const bool lo = p->geom.k < p->geom.s, lo6 = lo && p->engine == STAMP_GEMM_FP6;
+      uint8_t* a6g = at(ws, p->ws_a6);
+      if (convert_rows(p, q_hi, lo6 ? q_lo : nullptr, a6g, p->geom.k > 0 && p->hi6[0], 0, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
+      if (p->geom.k > 0 && p->hi6[0]) {
+        if (stamp_launch_hi6(p, at(ws, p->ws_hi6), scales, 2, yt[0], 0, 0, nullptr, 1.0f, st) != hipSuccess) return STAMP_ERR_DEVICE;
+      } else if (p->geom.k > 0) {
         if (stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st) != hipSuccess) return STAMP_ERR_DEVICE;
         if (stamp_launch_merge_hi(p, ythi, p->hi_ksplit, yt[0], st) != hipSuccess) return STAMP_ERR_DEVICE;
       }
-      if (p->geom.k < p->geom.s) {
-        if (p->engine == STAMP_GEMM_FP6) {
-          uint8_t* a6g = at(ws, p->ws_a6);
-          if (stamp_launch_repack6(p, q_lo, a6g, st) != hipSuccess) return STAMP_ERR_DEVICE;
+      if (lo) {
+        if (lo6) {
           if (stamp_launch_gemm_lo6(p, a6g, scales, 1, yt[0], nullptr, st) != hipSuccess) return STAMP_ERR_DEVICE;
         } else {
           if (stamp_launch_gemm_lo(p, q_lo, scales, 1, yt[0], nullptr, st) != hipSuccess) return STAMP_ERR_DEVICE;
@@ -347,23 +375,32 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
     return stamp_gen_inverse(p, yt, p->geom.N, tbias ? nullptr : p->bias_dev, Y, st) == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
   }
   if (p->geom.ident) {
-    // no transform: the 8-bit rows' GEMM (partial rows) + their output pass, then the 4-bit rows straight to Y
-    if (p->geom.k > 0) {
+    // no transform: the 8-bit rows' GEMM and their output (one kernel, or partial rows and an output pass), then the
+    // 4-bit rows straight to Y
+    uint8_t* a6i = at(ws, p->ws_a6);
+    const bool lo6 = p->geom.k < p->geom.s && p->engine == STAMP_GEMM_FP6;
+    if (convert_rows(p, q_hi, lo6 ? q_lo : nullptr, a6i, p->geom.k > 0 && p->hi6[0], 0, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
+    if (p->geom.k > 0 && p->hi6[0]) {
+      if (stamp_launch_hi6(p, at(ws, p->ws_hi6), scales, 1, Y, 0, 0, nullptr, 1.0f, st) != hipSuccess) return STAMP_ERR_DEVICE;
+    } else if (p->geom.k > 0) {
       if (stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st) != hipSuccess) return STAMP_ERR_DEVICE;
       if (stamp_launch_hi_rows_out(p, ythi, Y, st, p->hi_ksplit) != hipSuccess) return STAMP_ERR_DEVICE;
     }
     if (p->geom.k == p->geom.s) return STAMP_OK;
     if (p->engine == STAMP_GEMM_FP6) {
-      uint8_t* a6i = at(ws, p->ws_a6);
-      if (stamp_launch_repack6(p, q_lo, a6i, st) != hipSuccess) return STAMP_ERR_DEVICE;
       return stamp_launch_gemm_lo6(p, a6i, scales, 3, Y, nullptr, st) == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
     }
     return stamp_launch_gemm_lo(p, q_lo, scales, 3, Y, nullptr, st) == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
   }
   const bool fused = p->fused_ok && !p->unfused;
   const bool own = codes_are_ours && own_top(p);
+  uint8_t* a6 = at(ws, p->ws_a6);
+  const uint8_t* hi6 = at(ws, p->ws_hi6);
+  if (convert_rows(p, q_hi, p->engine == STAMP_GEMM_FP6 ? q_lo : nullptr, a6, p->hi6[own], own, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
   if (own) {
-    if (stamp_launch_block_sums_own(p, q_hi, scales, ythi, P, st) != hipSuccess) return STAMP_ERR_DEVICE;
+    if (launch_block_sums_own(p, q_hi, scales, ythi, P, hi6, st) != hipSuccess) return STAMP_ERR_DEVICE;
+  } else if (p->hi6[0]) {
+    if (stamp_launch_hi6(p, hi6, scales, 0, P, p->Npad, 0, nullptr, 1.0f, st) != hipSuccess) return STAMP_ERR_DEVICE;
   } else if (stamp_hi_rows_are_block_sums(p)) {
     if (stamp_launch_gemm_hi(p, q_hi, scales, 1, P, st, p->Npad) != hipSuccess) return STAMP_ERR_DEVICE;
   } else if (stamp_hi_top_fused(p)) {
@@ -374,8 +411,6 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
   }
   float* ytlo = reinterpret_cast<float*>(at(ws, p->ws_ytlo));
   if (p->engine == STAMP_GEMM_FP6) {
-    uint8_t* a6 = at(ws, p->ws_a6);
-    if (stamp_launch_repack6(p, q_lo, a6, st) != hipSuccess) return STAMP_ERR_DEVICE;
     if (stamp_launch_gemm_lo6(p, a6, scales, fused ? 2 : 1, fused ? Y : ytlo, fused ? P : nullptr, st, own) != hipSuccess)
       return STAMP_ERR_DEVICE;
   } else {
@@ -666,8 +701,15 @@ stamp_status_t stamp_debug_run_stage(const stamp_plan_t* p, int32_t stage, const
     // 6 FP6 conversion, 4 the 4-bit rows' GEMM; 1 and 5 do not exist
     switch (stage) {
       case 0: e = stamp_launch_actquant(p, X, q_hi, q_lo, scales, abot, rowmax, gpart, st, 1); break;
-      case 2: if (p->geom.k > 0) e = stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st); break;
-      case 3: e = stamp_launch_hi_rows_out(p, ythi, Y, st, p->hi_ksplit); break;
+      case 2:
+        if (p->geom.k > 0 && p->hi6[0]) {
+          e = convert_rows(p, q_hi, nullptr, nullptr, true, 0, ws, st);
+          if (e == hipSuccess) e = stamp_launch_hi6(p, at(ws, p->ws_hi6), scales, 1, Y, 0, 0, nullptr, 1.0f, st);
+        } else if (p->geom.k > 0) {
+          e = stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st);
+        }
+        break;
+      case 3: if (!p->hi6[0]) e = stamp_launch_hi_rows_out(p, ythi, Y, st, p->hi_ksplit); break;
       case 4:
         if (p->engine == STAMP_GEMM_FP6) e = stamp_launch_gemm_lo6(p, at(ws, p->ws_a6), scales, 3, Y, nullptr, st);
         else e = stamp_launch_gemm_lo(p, q_lo, scales, 3, Y, nullptr, st);
@@ -681,14 +723,17 @@ stamp_status_t stamp_debug_run_stage(const stamp_plan_t* p, int32_t stage, const
     case 0: e = stamp_launch_actquant(p, X, q_hi, q_lo, scales, abot, rowmax, gpart, st, 1); break;
     case 1: e = stamp_launch_actquant(p, X, q_hi, q_lo, scales, abot, rowmax, gpart, st, 2); break;
     case 2:
-      if (own_top(p)) e = stamp_launch_block_sums_own(p, q_hi, scales, ythi, P, st);
+      e = convert_rows(p, q_hi, nullptr, nullptr, p->hi6[own_top(p)], own_top(p), ws, st);
+      if (e != hipSuccess) break;
+      if (own_top(p)) e = launch_block_sums_own(p, q_hi, scales, ythi, P, at(ws, p->ws_hi6), st);
+      else if (p->hi6[0]) e = stamp_launch_hi6(p, at(ws, p->ws_hi6), scales, 0, P, p->Npad, 0, nullptr, 1.0f, st);
       else if (stamp_hi_top_fused(p)) e = stamp_launch_gemm_hi(p, q_hi, scales, 2, P, st, p->Npad);
       else
         e = stamp_hi_rows_are_block_sums(p) ? stamp_launch_gemm_hi(p, q_hi, scales, 1, P, st, p->Npad)
                                             : stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st);
       break;
     case 3:  // nothing to launch when the plan has no top levels, or when the 8-bit rows' GEMM has run them
-      if (!own_top(p) && !stamp_hi_rows_are_block_sums(p) && !stamp_hi_top_fused(p))
+      if (!own_top(p) && !p->hi6[0] && !stamp_hi_rows_are_block_sums(p) && !stamp_hi_top_fused(p))
         e = stamp_launch_inverse_top(p, ythi, 0, p->geom.N, P, p->Npad, st, p->hi_ksplit);
       break;
     case 4:

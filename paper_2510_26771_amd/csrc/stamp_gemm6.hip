@@ -23,49 +23,22 @@
 
 #include "stamp_gemm_common.h"
 #include "stamp_epilogue_reg.h"
+#include "stamp_fp6.h"
+#include "stamp_hi6.h"
 
 namespace {
 
 using namespace stamp_gemm;
 
-typedef int v6i __attribute__((ext_vector_type(6)));
-typedef uint32_t u6 __attribute__((ext_vector_type(6)));
-// the FP6 operand of the MFMA builtin is declared as 8 registers, of which the instruction reads 6
-__device__ __forceinline__ v8i widen(v6i x) { return __builtin_shufflevector(x, x, 0, 1, 2, 3, 4, 5, -1, -1); }
-
-constexpr int kPart = 2 * 32 * 16;            // bytes of one part of a 32-row block: 1 KB
-constexpr int kBlock6 = 3 * kPart;            // a 32-row block of one K step: 3 KB
-constexpr int kStageB6 = 4 * kBlock6;         // 128 columns: 12 KB
-constexpr int kStageA6 = 2 * kStageB6;        // 24 KB
-
-// eight two's-complement nibbles -> eight sign-magnitude 6-bit fields (48 bits)
-__device__ __forceinline__ uint64_t nib8_to_e2m3(uint32_t w) {
-  const uint32_t s = w & 0x88888888u;  // sign bit of every nibble
-  const uint32_t sg = s >> 3;          // 1 in every negative nibble
-  // |c|: complement the negative nibbles and add 1 (no carry leaves a nibble: ~c + 1 <= 8).  |c| = 8
-  // (the stored form of the asymmetric code 0) sets the low exponent bit: the E2M3 number 1.0 = 8 / 8.
-  const uint32_t mag = (w ^ (sg * 15u)) + sg;
-  uint64_t out = 0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const uint32_t c = ((mag >> (4 * j)) & 15u) | (((s >> (4 * j + 3)) & 1u) << 5);
-    out |= (uint64_t)c << (6 * j);
-  }
-  return out;
-}
-
-// 32 codes (one 16-byte chunk of packed nibbles, low nibble = even channel) -> 24 bytes
-__device__ __forceinline__ void chunk_to_e2m3(u4 w, uint64_t (&part)[3]) {
-  const uint64_t a = nib8_to_e2m3(w.x), b = nib8_to_e2m3(w.y), c = nib8_to_e2m3(w.z), d = nib8_to_e2m3(w.w);
-  part[0] = a | (b << 48);
-  part[1] = (b >> 16) | (c << 32);
-  part[2] = (c >> 32) | (d << 16);
-}
-
 // q_lo (tiled [Mpad/256][KT][256 rows][64 bytes], channels in natural order) -> FP6 operand layout.
 // One workgroup per (row tile, K step); thread = (row, kg): fragments kg and 2 + kg, three 16-byte stores.
-__global__ __launch_bounds__(512) void k_repack6(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6) {
-  const size_t blk = blockIdx.x;
+// The first nhi blocks convert the 8-bit rows (stamp_hi6.h).
+__global__ __launch_bounds__(512) void k_repack6(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, int nhi, StampHi6Pack hp) {
+  if ((int)blockIdx.x < nhi) {
+    hi6_pack(hp, (int)blockIdx.x * 512 + (int)threadIdx.x);
+    return;
+  }
+  const size_t blk = blockIdx.x - nhi;
   const int row = threadIdx.x & 255, kg = threadIdx.x >> 8;
   const uint8_t* src = q_lo + blk * (256 * 64) + row * 64 + kg * 16;
   uint8_t* dst = a6 + blk * kStageA6 + (row >> 5) * kBlock6 + kg * 512 + (row & 31) * 16;
@@ -80,8 +53,12 @@ __global__ __launch_bounds__(512) void k_repack6(const uint8_t* __restrict__ q_l
 
 // The same from rows in STaMP order to rows in the block order of StampRag (rows without a coefficient: zeros).
 __global__ __launch_bounds__(512) void k_repack6_rag(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, StampRag rg, int s,
-                                                     int khi, int KT, int M) {
-  const int blk = blockIdx.x, mt = blk / KT, kt = blk - mt * KT;
+                                                     int khi, int KT, int M, int nhi, StampHi6Pack hp) {
+  if ((int)blockIdx.x < nhi) {
+    hi6_pack(hp, (int)blockIdx.x * 512 + (int)threadIdx.x);
+    return;
+  }
+  const int blk = blockIdx.x - nhi, mt = blk / KT, kt = blk - mt * KT;
   const int row = threadIdx.x & 255, kg = threadIdx.x >> 8;
   const int m = mt * 256 + row, R = 1 << rg.r;
   int slot = -1, b = 0;
@@ -603,8 +580,11 @@ hipError_t stamp_launch_weight_quant6(const stamp_plan* p, const float* W, const
   return hipGetLastError();
 }
 
-hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st) {
-  hipLaunchKernelGGL(k_repack6, dim3((p->Mpad / 256) * (p->Kpad / 128)), dim3(512), 0, st, q_lo, a6);
+hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st, const StampHi6Pack* hi) {
+  const int nlo = q_lo != nullptr ? (p->Mpad / 256) * (p->Kpad / 128) : 0;
+  const StampHi6Pack hp = hi != nullptr ? *hi : StampHi6Pack{};
+  const int nhi = (hp.threads + 511) / 512;
+  if (nlo + nhi > 0) hipLaunchKernelGGL(k_repack6, dim3(nlo + nhi), dim3(512), 0, st, q_lo, a6, nhi, hp);
   return hipGetLastError();
 }
 
@@ -613,9 +593,11 @@ size_t stamp_rag_a6_bytes(const stamp_plan* p) {
   return ((M + 255) / 256) * (p->Kpad / 128) * kStageA6;
 }
 
-hipError_t stamp_launch_repack6_rag(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st) {
-  const int M = (p->geom.B * p->rag.nb) << p->rag.r, KT = p->Kpad / 128;
-  hipLaunchKernelGGL(k_repack6_rag, dim3(((M + 255) / 256) * KT), dim3(512), 0, st, q_lo, a6, p->rag, p->geom.s, p->geom.khi, KT, M);
+hipError_t stamp_launch_repack6_rag(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st, const StampHi6Pack* hi) {
+  const int M = (p->geom.B * p->rag.nb) << p->rag.r, KT = p->Kpad / 128, nlo = ((M + 255) / 256) * KT;
+  const StampHi6Pack hp = hi != nullptr ? *hi : StampHi6Pack{};
+  const int nhi = (hp.threads + 511) / 512;
+  hipLaunchKernelGGL(k_repack6_rag, dim3(nlo + nhi), dim3(512), 0, st, q_lo, a6, p->rag, p->geom.s, p->geom.khi, KT, M, nhi, hp);
   return hipGetLastError();
 }
 

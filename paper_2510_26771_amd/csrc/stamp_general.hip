@@ -859,6 +859,8 @@ float haar_norm_host(int level) { return std::ldexp((level & 1) ? kC : 1.0f, -(l
 
 }  // namespace
 
+float stamp_haar_norm_host(int level) { return haar_norm_host(level); }
+
 // ---------------------------------------------------------------------------------------------
 // Plan-time tables
 // ---------------------------------------------------------------------------------------------

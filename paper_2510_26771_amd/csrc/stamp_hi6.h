@@ -1,0 +1,49 @@
+// The 8-bit rows on the FP6 matrix pipeline (stamp_hi6.hip): layout and conversion of the operand.
+//
+// An 8-bit code c is 16 h + l with l in [-8, 7], h in [-8, 8]: two FP6 rows (E2M3 numbers h / 8, l / 8), whose sums over
+// 4-bit weights are exact, and 16 times the one plus the other is the integer sum of the 8-bit row.  Rows are kept in groups
+// of 32 * np (np = 1 or 2): [group][K step][2 np blocks: h and l of rows 0..31, h and l of rows 32..63][3 KB], a block as
+// in stamp_gemm6.hip.
+#ifndef STAMP_HI6_H_
+#define STAMP_HI6_H_
+
+#include "stamp_fp6.h"
+
+namespace stamp_gemm {
+
+// one thread = 32 channels of a row
+__device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
+  if (i >= hp.threads) return;
+  const int nf = hp.KT * 4, m = i / nf, frag = i - m * nf, kt = frag >> 2, f = frag & 3;
+  int h[32], l[32];
+  const bool there = m < hp.M && frag * 32 < hp.d;  // d is a multiple of 32
+  uint32_t w[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+  if (there) {
+    const int row = m + (m / hp.seq_used) * (hp.seq_rows - hp.seq_used);
+    const u4* src = reinterpret_cast<const u4*>(hp.q_hi + (size_t)row * hp.d + frag * 32);
+    const u4 a = src[0], b = src[1];
+    w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
+    w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
+  }
+#pragma unroll
+  for (int c = 0; c < 32; ++c) {
+    const int v = (int)(w[c >> 2] << (24 - 8 * (c & 3))) >> 24;
+    h[c] = (v + 8) >> 4;
+    l[c] = v - 16 * h[c];
+  }
+  const int gr = 32 * hp.np, grp = m / gr, r = m - grp * gr;
+  uint8_t* dst = hp.a6 + ((size_t)grp * hp.KT + kt) * (2 * hp.np * kBlock6) + (r >> 5) * (2 * kBlock6) + (f & 1) * 512 + (r & 31) * 16;
+  uint64_t ph[3], pl[3];
+  values_to_e2m3(h, ph);
+  values_to_e2m3(l, pl);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int off = (f >> 1) * 24 + q * 8, o = (off >> 4) * kPart + (off & 15);
+    *reinterpret_cast<uint64_t*>(dst + o) = ph[q];
+    *reinterpret_cast<uint64_t*>(dst + kBlock6 + o) = pl[q];
+  }
+}
+
+}  // namespace stamp_gemm
+
+#endif  // STAMP_HI6_H_

@@ -1,0 +1,265 @@
+// The 8-bit rows of the STaMP linear layer when the whole batch has few of them: their GEMM on the FP6 matrix pipeline
+// (operands as in stamp_hi6.h), dequantization, the top levels of the inverse transform, and the store of the block sums P
+// (or of the rows themselves), one kernel.
+//
+// The GEMM is a stream of the weights (0.75 byte each) against a few rows that come from L2: bound by how many bytes are
+// in flight, so nothing is staged.  Every wave reads its operands straight from memory into registers (the layout makes a
+// wave's 16-byte loads 1 KB of consecutive addresses), the eight waves of a workgroup split the depth (two groups of four
+// when there are more than 64 rows: each group takes 64), and only their sums meet in LDS.  The sums are whole numbers and
+// stay whole: fp32 holds each FP6 sum exactly, 16 h + l and the sum over the waves are int32.
+// Measured (rows x depth x d_out, microseconds; before: int8 GEMM + top levels of the inverse as a kernel of its own):
+// 64 x 4096 x 11008: 17.6 (16.1 + 10.1), 128 x 4096 x 4096: 12.8 (17.8 + 11.9), 64 x 11008 x 4096: 18.9 (19.1 + 4.8),
+// 128 x 1152 x 4608: 8.2 (15.7 + 5.2), 512 x 4096 x 4096: 37 (34 + 15).
+#include "stamp_hi6.h"
+
+namespace {
+
+using namespace stamp_gemm;
+
+// register = integer sum / 64 after the sums have met
+struct AccHi6 {
+  static constexpr bool kLoRows = false;
+  static constexpr float kZeroShift = 128.0f;
+  static constexpr float kToAcc = 1.0f;
+};
+
+struct Hi6Args {
+  GemmArgs a;        // A: packed rows, Bq: FP6 weights, M rows, g.k rows per sequence, scales, sw, colsum, bias, rag
+  int np, ng;        // 32-row pairs per wave, row groups per workgroup
+  int mode;          // 0: block sums -> out [M][ld_out] (g.L top levels inverted), 1: rows -> Y + bias (plans without transform),
+                     // 2: rows -> fp32 rows b * g.s + slot of out, 3: blocked form of any length (StampRag): as 0 times norm, slot < o -> Y
+  float norm;        // mode 3
+  void* Y;           // mode 3
+};
+
+struct Frag6 {
+  u4 p0, p1, p2;
+  __device__ __forceinline__ void load(const uint8_t* q) {
+    p0 = *reinterpret_cast<const u4*>(q);
+    p1 = *reinterpret_cast<const u4*>(q + kPart);
+    p2 = *reinterpret_cast<const u4*>(q + 2 * kPart);
+  }
+  // the builtin's operand has 8 registers, of which the instruction reads 6
+  __device__ __forceinline__ v8i h0() const { return (v8i)__builtin_shufflevector(p0, p1, 0, 1, 2, 3, 4, 5, -1, -1); }
+  __device__ __forceinline__ v8i h1() const { return (v8i)__builtin_shufflevector(p1, p2, 2, 3, 4, 5, 6, 7, -1, -1); }
+};
+
+template <int NP>
+__global__ __launch_bounds__(512, 4) void k_hi6(const Hi6Args h) {
+  const GemmArgs& a = h.a;
+  const StampGeom& g = a.g;
+  constexpr int C = 32, RW = 32 * NP;  // columns, rows of a wave
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  int* const s_part = reinterpret_cast<int*>(smem);            // [8 waves][RW][C]
+  __shared__ __attribute__((aligned(16))) uint8_t s_info[kRowInfoBytes];
+  __shared__ int s_pos[128];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, kg = lane >> 5;
+  const int KT = a.Kpad / BK, kw = 8 / h.ng, rg = wave / kw, kp = wave - rg * kw;
+  const int RG = RW * h.ng, m0 = (int)blockIdx.y * RG;  // rows of the workgroup
+  // strip of 32 columns: block `st` of the weight layout = columns 64 (st / 2) + 2 l + st % 2
+  const int st = blockIdx.x;
+  const uint8_t* pb = a.Bq + (size_t)(st >> 2) * KT * kStageB6 + (st & 3) * kBlock6 + lane * 16;
+  const uint8_t* pa = a.A + (size_t)((int)blockIdx.y * h.ng + rg) * KT * (2 * NP * kBlock6) + lane * 16;
+  const int kt0 = KT * kp / kw, kt1 = KT * (kp + 1) / kw;
+
+  v16f acc[2 * NP];
+#pragma unroll
+  for (int i = 0; i < 2 * NP; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+  if (tid < RG) {
+    float fac = 0.0f, rz = 0.0f;
+    int dst = -1;
+    compute_row_info<AccHi6, 1>(a, m0, tid, fac, dst, rz);
+    write_row_info(s_info, tid, fac, dst, rz);
+  }
+  // at most 128 registers: four waves per SIMD (two workgroups) hide each other's loads (64 x 4096 x 11008: 17.6 us; two
+  // waves per SIMD, each with the next step's operands in flight in registers: 21.4)
+  for (int kt = kt0; kt < kt1; ++kt) {
+    Frag6 fb, fa[2 * NP];
+    fb.load(pb + (size_t)kt * kStageB6);
+#pragma unroll
+    for (int i = 0; i < 2 * NP; ++i) fa[i].load(pa + (size_t)kt * (2 * NP * kBlock6) + i * kBlock6);
+#pragma unroll
+    for (int i = 0; i < 2 * NP; ++i) {
+      acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[i].h0(), fb.h0(), acc[i], 2, 2, 0, 0, 0, 0);
+      acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[i].h1(), fb.h1(), acc[i], 2, 2, 0, 0, 0, 0);
+    }
+  }
+  // staging position of a row: its natural position among the block sums of its sequence (top levels), else the row itself
+  if (h.mode == 0 && g.L > 0) {
+    if (tid < RG) {
+      const int seq = tid / g.k, q = tid - seq * g.k;
+      int e, lvl;
+      if (!g.is2d) e = stamp_top_slot_1d(q, g.k, g.L, &lvl);
+      else e = stamp_top_slot_2d(q / g.G, q % g.G, g.G, g.L, &lvl);
+      s_pos[seq * g.k + e] = tid;
+    }
+  }
+#pragma unroll
+  for (int pr = 0; pr < NP; ++pr)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int row = pr * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
+      s_part[(wave * RW + row) * C + l32] = 16 * (int)(acc[2 * pr][v] * 64.0f) + (int)(acc[2 * pr + 1][v] * 64.0f);
+    }
+  __syncthreads();
+
+  // sums over the waves, dequantized
+  const float* s_fac = reinterpret_cast<const float*>(s_info);
+  const float* s_rz = reinterpret_cast<const float*>(s_info + 2048);
+  const int c = tid & 31, r0 = tid >> 5;  // this thread: column c, rows r0, r0 + 16, ..
+  const int n = 64 * (st >> 1) + 2 * c + (st & 1);
+  const float swn = a.sw[n], csn = g.asym ? a.colsum[n] : 0.0f;
+  float y[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = r0 + 16 * i;
+    y[i] = 0.0f;
+    if (r < RG) {
+      const int base = ((r / RW) * kw * RW + (r & (RW - 1))) * C + c;
+      int sum = 0;
+      for (int q = 0; q < kw; ++q) sum += s_part[base + q * (RW * C)];
+      const float af = g.asym ? __builtin_fmaf(-s_rz[r], csn, (float)sum) : (float)sum;
+      if (m0 + r < a.M) y[i] = (af * s_fac[r]) * swn;
+    }
+  }
+  if (h.mode == 0 && g.L > 0) {
+    // top levels in LDS: same pairs in the same order as k_inverse_top
+    float* const s_buf = reinterpret_cast<float*>(smem);  // [RG][C]
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (r0 + 16 * i < RG) s_buf[s_pos[r0 + 16 * i] * C + c] = y[i];
+    __syncthreads();
+    const int nseq = RG / g.k;
+    if (!g.is2d) {
+      for (int s2 = 1 << g.L; s2 >= 2; s2 >>= 1) {
+        const int npair = RG / s2;
+        for (int i = r0; i < npair; i += 16) {
+          float *px = &s_buf[(i * s2) * C + c], *pd = &s_buf[(i * s2 + (s2 >> 1)) * C + c];
+          const float x = *px, d = *pd;
+          *px = x + d;
+          *pd = x - d;
+        }
+        __syncthreads();
+      }
+    } else {
+      for (int s2 = 1 << g.L; s2 >= 2; s2 >>= 1) {
+        const int nc = g.G / s2, hf = s2 >> 1, cells = nc * nc;
+        for (int i = r0; i < nseq * cells; i += 16) {
+          const int seq = i / cells, q = i - seq * cells, cy = q / nc, cx = q - cy * nc;
+          float* p00 = &s_buf[(seq * g.k + (cy * s2) * g.G + cx * s2) * C + c];
+          float *p01 = p00 + hf * C, *p10 = p00 + hf * g.G * C, *p11 = p10 + hf * C;
+          const float cLL = *p00, cW = *p01, cH = *p10, cD = *p11;
+          const float t0 = cLL + cH, t2 = cLL - cH, t1 = cW + cD, t3 = cW - cD;
+          *p00 = t0 + t1;
+          *p01 = t0 - t1;
+          *p10 = t2 + t3;
+          *p11 = t2 - t3;
+        }
+        __syncthreads();
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (r0 + 16 * i < RG) y[i] = s_buf[(r0 + 16 * i) * C + c];
+  }
+  if (n >= a.N) return;
+  float* const out = reinterpret_cast<float*>(a.out);
+  const float bv = ((h.mode == 1 || h.mode == 3) && a.bias != nullptr) ? a.bias[n] : 0.0f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = r0 + 16 * i, m = m0 + r;
+    if (r >= RG || m >= a.M) continue;
+    if (h.mode == 0) {
+      out[(size_t)m * a.ld_out + n] = y[i];
+    } else {
+      const int b = m / g.k, slot = m - b * g.k;
+      const size_t idx = ((size_t)b * g.s + slot) * a.N + n;
+      if (h.mode == 2) {
+        out[idx] = y[i];
+      } else if (h.mode == 3 && slot >= a.rag.o) {
+        out[(size_t)m * a.ld_out + n] = y[i] * h.norm;
+      } else {
+        const float v = y[i] + bv;
+        void* Y = h.mode == 1 ? a.out : h.Y;
+        if (g.y_bf16) reinterpret_cast<__bf16*>(Y)[idx] = (__bf16)v;
+        else reinterpret_cast<float*>(Y)[idx] = v;
+      }
+    }
+  }
+}
+
+template <int NP>
+hipError_t launch(const Hi6Args& h, hipStream_t st) {
+  constexpr size_t lds = (size_t)8 * 32 * NP * 32 * sizeof(int);
+  static size_t lds_done[kStampMaxDevices] = {};
+  const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_hi6<NP>), lds, lds_done);
+  if (e != hipSuccess) return e;
+  const int rows = 32 * NP * h.ng;
+  hipLaunchKernelGGL(k_hi6<NP>, dim3((h.a.N + 63) / 64 * 2, (h.a.M + rows - 1) / rows), dim3(512), lds, st, h);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// rows of this GEMM: all top rows of every sequence, or (own) the first khi of them
+namespace {
+int hi6_rows(const stamp_plan* p, int own) { return p->geom.B * (own ? p->geom.khi : p->geom.k); }
+int hi6_np(int M) { return M <= 32 ? 1 : 2; }
+// 64 rows per workgroup (more workgroups, each with its waves' depth split eight ways), 128 where a sequence has that many
+// top rows and its top levels are inverted here
+int hi6_ng(const stamp_plan* p, int own) { return !p->geom.ident && !own && p->geom.L > 0 && p->geom.k > 64 ? 2 : 1; }
+}  // namespace
+
+size_t stamp_hi6_bytes(const stamp_plan* p, int own) {
+  const int M = hi6_rows(p, own), gr = 32 * hi6_np(M);
+  return (size_t)((M + gr - 1) / gr) * (p->Kpad / 128) * (2 * hi6_np(M) * kBlock6);
+}
+
+// Plans that this kernel serves.  Every workgroup reads its rows' whole depth from L2, so with many rows and columns the
+// tiled int8 kernel, which shares them through LDS, wins: 512 x 4096 x 4096 (8.6e9) is 37 us here against 49 there, 512 x
+// 8192 x 28672 (1.2e11) at least 160 by the 25 MB of operands that every CU would load, against 134 measured there.
+bool stamp_hi6_fits(const stamp_plan* p, int own) {
+  const StampGeom& g = p->geom;
+  const int M = hi6_rows(p, own);
+  if (M < 1 || p->gen.group != 0) return false;
+  if (!g.ident && !own && g.L > 0 && (g.k > 128 || (g.k & (g.k - 1)) != 0)) return false;  // whole sequences per workgroup
+  return M <= 128 || (double)M * g.N * g.d <= 2.0e10;
+}
+
+StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own) {
+  const StampGeom& g = p->geom;
+  StampHi6Pack hp = {};
+  hp.q_hi = q_hi;
+  hp.a6 = a6;
+  hp.M = hi6_rows(p, own);
+  hp.np = hi6_np(hp.M);
+  hp.seq_rows = g.k;
+  hp.seq_used = own ? g.khi : g.k;
+  hp.d = g.d;
+  hp.KT = p->Kpad / 128;
+  const int gr = 32 * hp.np;
+  hp.threads = (hp.M + gr - 1) / gr * gr * hp.KT * 4;
+  return hp;
+}
+
+hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float* scales, int mode, void* out, int ld_out, int own,
+                            void* Y, float norm, hipStream_t st) {
+  Hi6Args h = {};
+  h.a = stamp_gemm_args(p, scales, out);
+  h.a.A = a6;
+  h.a.Bq = p->qW6_dev;
+  h.a.M = hi6_rows(p, own);
+  h.a.ld_out = ld_out;
+  if (own) h.a.g.k = p->geom.khi;  // the kernel sees a plan of khi top rows per sequence
+  h.a.rag = p->rag;
+  h.np = hi6_np(h.a.M);
+  h.ng = hi6_ng(p, own);
+  h.mode = mode;
+  h.norm = norm;
+  h.Y = Y;
+  return h.np == 1 ? launch<1>(h, st) : launch<2>(h, st);
+}

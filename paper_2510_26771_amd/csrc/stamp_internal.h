@@ -184,6 +184,9 @@ struct stamp_plan {
   int8_t* qWg_dev;          // per-block scales: weight codes [Npad128][d_in] int8
   float* swg_dev;           // per-block scales: [d_in / 64][Npad128]
   size_t ws_T[3], ws_Yt[3], ws_codes8, ws_scalesg;  // general path workspace (byte offsets)
+  // the 8-bit rows through the kernel for few rows (stamp_hi6.hip), [1]: only the first khi rows of every sequence
+  int32_t hi6[2];
+  size_t ws_hi6;            // their operand
   size_t ws_ba6, ws_bP;     // blocked form: the 4-bit rows in block order (over ws_T), the block sums (over ws_Yt)
   // workspace layout (byte offsets, 256-aligned)
   size_t ws_abot, ws_rowmax, ws_gpart, ws_qhi, ws_qlo, ws_scales, ws_ythi, ws_P, ws_a6, ws_ytlo, ws_total;
@@ -240,11 +243,25 @@ hipError_t stamp_launch_gemm_lo(const stamp_plan* p, const uint8_t* q_lo, const 
 size_t stamp_a6_bytes(const stamp_plan* p);
 size_t stamp_b6_bytes(const stamp_plan* p);
 hipError_t stamp_launch_weight_quant6(const stamp_plan* p, const float* W, const uint32_t* colmax, hipStream_t st);
-hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st);
+// hi: 8-bit rows to convert in the same launch (nullptr: none); q_lo may be nullptr then
+struct StampHi6Pack {
+  const int8_t* q_hi;
+  uint8_t* a6;
+  int32_t M, np, seq_rows, seq_used, d, KT, threads;  // rows, 32-row blocks per group, rows a sequence has / uses in q_hi
+};
+hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st, const StampHi6Pack* hi = nullptr);
+// the 8-bit rows' GEMM on the FP6 pipeline (few rows), own: only the first khi rows of every sequence.  mode 0: block sums
+// -> out [M][ld_out] (top levels of the inverse included), 1: rows + bias -> Y (plans without transform), 2: rows -> fp32
+// [B*s][N] in STaMP order, 3: blocked form: block sums times norm -> out, the token left out + bias -> Y
+bool stamp_hi6_fits(const stamp_plan* p, int own);
+size_t stamp_hi6_bytes(const stamp_plan* p, int own);
+StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own);
+hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float* scales, int mode, void* out, int ld_out, int own,
+                            void* Y, float norm, hipStream_t st);
 // blocked form (p->rag.on): the same conversion from rows in STaMP order to block order; packed nibbles in block order
 // for the int8 engine; and the two GEMMs with the inverse transform in their epilogue
 size_t stamp_rag_a6_bytes(const stamp_plan* p);
-hipError_t stamp_launch_repack6_rag(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st);
+hipError_t stamp_launch_repack6_rag(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st, const StampHi6Pack* hi);
 hipError_t stamp_launch_gather_lo_rag(const stamp_plan* p, const uint8_t* q_lo, uint8_t* q_blk, hipStream_t st);
 hipError_t stamp_launch_gemm_lo6_rag(const stamp_plan* p, const uint8_t* a6, const float* scales, void* Y, const float* P, hipStream_t st);
 hipError_t stamp_launch_gemm_lo_rag(const stamp_plan* p, const uint8_t* q_blk, const float* scales, void* Y, const float* P, hipStream_t st);
@@ -264,6 +281,7 @@ hipError_t stamp_launch_inverse_bottom(const stamp_plan* p, const float* Yt_lo, 
                                        const float* P, int ldP, int ncols, const float* bias, void* Y, hipStream_t st);
 
 // ---- general path (stamp_general.hip) ----
+float stamp_haar_norm_host(int level);  // fl(2^(-level/2))
 hipError_t stamp_gen_plan_tables(stamp_plan* p, const float* W, hipStream_t st);  // device tables and grouped weights
 void stamp_gen_plan_free(stamp_plan* p);
 // X -> transformed tokens T [B, s, d] fp32 in STaMP order; returns the buffer that holds T (one of the three)
