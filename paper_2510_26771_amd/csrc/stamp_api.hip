@@ -192,6 +192,25 @@ stamp_status_t validate(const stamp_plan_desc_t* d, StampGeom* g, int* fused_ok,
   return STAMP_OK;
 }
 
+// Per-block scales on a 2-D Haar transform with the fast path's block structure (4 x 4 or 8 x 8 token blocks; top levels over
+// at most 8 x 8 block sums, which a lane of their kernel holds), even d_out (the epilogue stores pairs), bias after the
+// inverse.  Everything else runs level by level.
+void grp_geometry(stamp_plan* p) {
+  const stamp_plan_desc_t& d = p->desc;
+  p->grp = 0;
+  if (p->gen.kind != kGenHaar2d || p->gen.group != 64 || p->gen.bias_mode != 0 || d.grid_h != d.grid_w || d.d_out % 2 != 0) return;
+  StampGeom g = p->geom;
+  g.J = d.levels;
+  g.k = g.khi = d.k_hi;
+  g.ident = 0;
+  int fused = 0;
+  if (fast_geometry(&d, &g, &fused, d.grid_h) != STAMP_OK || !fused) return;
+  if (g.L > 0 && g.k > 64) return;
+  if (g.s % 64 != 0 || g.khi < 1) return;
+  p->bgeom = g;
+  p->grp = 1;
+}
+
 // Blocked form of a plan of the general path (1-D Haar of any length): per-token scales, bias after the inverse, 3 to 6
 // levels (blocks of 8 .. 64 tokens: what the GEMM epilogues invert), 8-bit tokens among the approximations (and the
 // token left out, which has to be one of them).  Everything else runs level by level.
@@ -246,6 +265,18 @@ void layout_workspace(stamp_plan* p) {
     if (p->rag.on && (stamp_rag_a6_bytes(p) > p->ws_T[2] - p->ws_T[0] ||
                       (size_t)g.B * g.khi * p->Npad * sizeof(float) > p->ws_codes8 - p->ws_Yt[0]))
       p->rag.on = 0;
+    if (p->grp) {
+      // over the fp32 copies, like the blocked 1-D form: block sums of X | operands of the 4-bit rows, then block sums of
+      // the inverse | operands of the 8-bit rows
+      size_t n[4];
+      stamp_grp_bytes(p, n);
+      const size_t xs = align256((size_t)g.B * p->bgeom.k * g.d * sizeof(float)), ys = align256((size_t)g.B * p->bgeom.k * p->Npad * sizeof(float));
+      p->ws_grp[0] = p->ws_T[0] + xs;
+      p->ws_grp[1] = p->ws_grp[0] + n[0];
+      p->ws_grp[2] = p->ws_Yt[0] + ys;
+      p->ws_grp[3] = p->ws_grp[2] + n[2];
+      if (p->ws_grp[1] + n[1] > p->ws_Yt[0] || p->ws_grp[3] + n[3] > p->ws_codes8) p->grp = 0;
+    }
     return;
   }
   p->ws_abot = take((size_t)g.B * g.k * g.d * sizeof(float));
@@ -344,6 +375,11 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
                          void* ws, hipStream_t st, bool codes_are_ours) {
   float* ythi = reinterpret_cast<float*>(at(ws, p->ws_ythi));
   float* P = reinterpret_cast<float*>(at(ws, p->ws_P));
+  if (p->grp && (reinterpret_cast<uintptr_t>(Y) & 15) == 0) {
+    uint8_t* const buf[4] = {at(ws, p->ws_grp[0]), at(ws, p->ws_grp[1]), at(ws, p->ws_grp[2]), at(ws, p->ws_grp[3])};
+    return stamp_launch_grp_forward(p, q_hi, scales, buf, reinterpret_cast<float*>(at(ws, p->ws_Yt[0])), Y, st) == hipSuccess
+               ? STAMP_OK : STAMP_ERR_DEVICE;
+  }
   if (rag_route(p, Y)) return rag_forward_q(p, q_hi, q_lo, scales, Y, ws, st);
   if (p->gen.kind != kGenNone) {
     // general path: dequantized rows in STaMP order -> (transformed bias) -> inverse level by level -> Y
@@ -424,6 +460,9 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
 
 // general path, steps 1-2: forward transform level by level, then the row quantizer
 stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, void* ws, hipStream_t st) {
+  if (p->grp && (reinterpret_cast<uintptr_t>(X) & 15) == 0)
+    return stamp_launch_grp_quant(p, X, q_hi, scales, reinterpret_cast<float*>(at(ws, p->ws_T[0])), st) == hipSuccess ? STAMP_OK
+                                                                                                                     : STAMP_ERR_DEVICE;
   if (stamp_rag_quantizes(p, X))
     return stamp_launch_actquant_rag(p, X, q_hi, q_lo, scales, st) == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
   float* const tb[3] = {reinterpret_cast<float*>(at(ws, p->ws_T[0])), reinterpret_cast<float*>(at(ws, p->ws_T[1])),
@@ -478,6 +517,7 @@ stamp_status_t stamp_plan_create(const stamp_plan_desc_t* desc, const void* W_de
   p->hi_ksplit = gen.group ? 1 : stamp_hi_ksplit(p, g.k);
   p->hi_ksplit_own = gen.group ? 1 : stamp_hi_ksplit(p, g.khi);
   rag_geometry(p);
+  grp_geometry(p);
   layout_workspace(p);
 
   // physical row of every STaMP slot

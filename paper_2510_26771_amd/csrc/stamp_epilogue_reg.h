@@ -201,7 +201,8 @@ __device__ __forceinline__ void dfs2d_reg(const float (&acc)[4][NI][16], float a
 // rowz0 = that row's entry of the per-row tables.  Per block: c = (acc - rowz * colsum) * rowfac in place, the
 // dequantized coefficient without the weight scale (symmetric plans have rowz = 0 and colsum operand 0: the fma
 // then leaves the sum as it is), then the depth-first inverse.
-template <int RB, bool IS2D, int T, int NB, bool YBF16, bool VEC, bool SYM, bool RAG, int NP>
+// GRP: the accumulators are dequantized already (per-block scales), a 4-bit block sum is known by its index.
+template <int RB, bool IS2D, int T, int NB, bool YBF16, bool VEC, bool SYM, bool RAG, bool GRP, int NP>
 __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI][16], const f2 (&P)[NP], f2 bias, f2 cs,
                                            RegOut<YBF16, VEC, !IS2D>& o, const float* rowfac0, const float* rowz0, int mrow0,
                                            int n, int m0) {
@@ -213,7 +214,7 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
     const int mrow = mrow0 + 2 * T * R;
     if (mrow < a.M && o.nvalid > 0) {
 #pragma unroll
-      for (int e4 = 0; e4 < R; e4 += 4) {
+      for (int e4 = 0; e4 < (GRP ? 0 : R); e4 += 4) {
         const f4 rf = *reinterpret_cast<const f4*>(rowfac0 + 2 * T * R + e4);
         f4 rz = {0.0f, 0.0f, 0.0f, 0.0f};
         if constexpr (!SYM) rz = *reinterpret_cast<const f4*>(rowz0 + 2 * T * R + e4);
@@ -232,7 +233,9 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
       }
       // The block sum comes from the 8-bit rows' GEMM (P), or - plans without top levels, blocks from khi on, marked
       // in the row table - it is the block's own coefficient 0, dequantized above like every other row.
-      const bool own = reinterpret_cast<const int*>(rowfac0)[256 + 2 * T * R] == 1;
+      bool own;
+      if constexpr (GRP) own = a.own_top != 0 && (mrow % g.s) / R >= g.khi;
+      else own = reinterpret_cast<const int*>(rowfac0)[256 + 2 * T * R] == 1;
       const float bs0 = own ? acc[RM::mi(T, 0)][0][RM::v(T, 0)] * o.sw0 : P[T][0];
       const float bs1 = own ? acc[RM::mi(T, 0)][1][RM::v(T, 0)] * o.sw1 : P[T][1];
       o.off0 = bs0 + bias[0];
@@ -270,7 +273,7 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
         dfs2d_reg<RB, T, 0, 0, 0, RegOut<YBF16, VEC, false>>(acc, 0.0f, 0.0f, o);
       }
     }
-    blocks_reg<RB, IS2D, T + 1, NB, YBF16, VEC, SYM, RAG, NP>(a, acc, P, bias, cs, o, rowfac0, rowz0, mrow0, n, m0);
+    blocks_reg<RB, IS2D, T + 1, NB, YBF16, VEC, SYM, RAG, GRP, NP>(a, acc, P, bias, cs, o, rowfac0, rowz0, mrow0, n, m0);
   }
 }
 
@@ -278,7 +281,7 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
 // EPI 3: plans without a sequence transform (rows are tokens).
 // accv: the wave's accumulators, 4 x NIW blocks; this call handles the column pair PAIR (blocks 2 PAIR, 2 PAIR + 1:
 // the 64 columns from nw on).
-template <int EPI, int RB, bool IS2D, bool YBF16, bool VEC, int NIW, int PAIR, bool SYM, bool RAG>
+template <int EPI, int RB, bool IS2D, bool YBF16, bool VEC, int NIW, int PAIR, bool SYM, bool RAG, bool GRP = false>
 __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const v16f (&accv)[4][NIW], const uint8_t* row_info,
                                                   const RegEpiOperands<EPI, (IS2D ? 2 * RB : RB), RAG>& eo, int m0, int nw,
                                                   int wm, int lane) {
@@ -359,7 +362,7 @@ __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const v16f 
       o.tok_stride = (size_t)a.N;
       o.row_stride = (size_t)g.gridW * a.N;
     }
-    blocks_reg<RB, IS2D, 0, nb, YBF16, VEC, SYM, RAG>(a, acc, eo.P, eo.bias, eo.cs, o, s_rowfac + wm * 128 + kg * R, s_rowz + wm * 128 + kg * R,
+    blocks_reg<RB, IS2D, 0, nb, YBF16, VEC, SYM, RAG, GRP>(a, acc, eo.P, eo.bias, eo.cs, o, s_rowfac + wm * 128 + kg * R, s_rowz + wm * 128 + kg * R,
                                             m0 + wm * 128 + kg * R, n, m0);
   }
 }

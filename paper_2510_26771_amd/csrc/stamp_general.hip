@@ -870,6 +870,10 @@ void stamp_gen_plan_free(stamp_plan* p) {
   if (p->dct_dev) (void)hipFree(p->dct_dev);
   if (p->qWg_dev) (void)hipFree(p->qWg_dev);
   if (p->swg_dev) (void)hipFree(p->swg_dev);
+  if (p->qWg6_dev) (void)hipFree(p->qWg6_dev);
+  if (p->swg6_dev) (void)hipFree(p->swg6_dev);
+  p->qWg6_dev = nullptr;
+  p->swg6_dev = nullptr;
   p->ell_dev = p->swg_dev = nullptr;
   p->perm_dev = nullptr;
   p->dct_dev = nullptr;
@@ -995,6 +999,7 @@ hipError_t stamp_gen_plan_tables(stamp_plan* p, const float* W, hipStream_t st) 
     const size_t sc = p->desc.w_is_out_by_in ? 1 : (size_t)g.N, sn = p->desc.w_is_out_by_in ? (size_t)g.d : 1;
     hipLaunchKernelGGL(k_gen_wquant_grouped, dim3(Npad / 256 + 1, G), dim3(256), 0, st, W, p->qWg_dev, p->swg_dev, g.d, g.N, Npad, sc, sn);
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (p->grp && (e = stamp_grp_plan_weights(p, st)) != hipSuccess) return e;
   }
   return hipSuccess;
 }

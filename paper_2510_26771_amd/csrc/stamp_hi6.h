@@ -11,6 +11,19 @@
 
 namespace stamp_gemm {
 
+// one fragment (48 bytes) of a lane, read from memory
+struct Frag6 {
+  u4 p0, p1, p2;
+  __device__ __forceinline__ void load(const uint8_t* q) {
+    p0 = *reinterpret_cast<const u4*>(q);
+    p1 = *reinterpret_cast<const u4*>(q + kPart);
+    p2 = *reinterpret_cast<const u4*>(q + 2 * kPart);
+  }
+  // the builtin's operand has 8 registers, of which the instruction reads 6
+  __device__ __forceinline__ v8i h0() const { return (v8i)__builtin_shufflevector(p0, p1, 0, 1, 2, 3, 4, 5, -1, -1); }
+  __device__ __forceinline__ v8i h1() const { return (v8i)__builtin_shufflevector(p1, p2, 2, 3, 4, 5, 6, 7, -1, -1); }
+};
+
 // one thread = 32 channels of a row
 __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
   if (i >= hp.threads) return;

@@ -30,21 +30,11 @@ struct Hi6Args {
                      // 2: rows -> fp32 rows b * g.s + slot of out, 3: blocked form of any length (StampRag): as 0 times norm, slot < o -> Y
   float norm;        // mode 3
   void* Y;           // mode 3
+  const float *sa, *sw;  // GRP: [row group][K step][rows][2], [column tile][K step][4 blocks][32][2]
 };
 
-struct Frag6 {
-  u4 p0, p1, p2;
-  __device__ __forceinline__ void load(const uint8_t* q) {
-    p0 = *reinterpret_cast<const u4*>(q);
-    p1 = *reinterpret_cast<const u4*>(q + kPart);
-    p2 = *reinterpret_cast<const u4*>(q + 2 * kPart);
-  }
-  // the builtin's operand has 8 registers, of which the instruction reads 6
-  __device__ __forceinline__ v8i h0() const { return (v8i)__builtin_shufflevector(p0, p1, 0, 1, 2, 3, 4, 5, -1, -1); }
-  __device__ __forceinline__ v8i h1() const { return (v8i)__builtin_shufflevector(p1, p2, 2, 3, 4, 5, 6, 7, -1, -1); }
-};
-
-template <int NP>
+// GRP: one scale per 64 channels (a half of a K step) and row / column: the sums are rescaled half by half, s_part holds fp32
+template <int NP, bool GRP>
 __global__ __launch_bounds__(512, 4) void k_hi6(const Hi6Args h) {
   const GemmArgs& a = h.a;
   const StampGeom& g = a.g;
@@ -63,12 +53,12 @@ __global__ __launch_bounds__(512, 4) void k_hi6(const Hi6Args h) {
   const uint8_t* pa = a.A + (size_t)((int)blockIdx.y * h.ng + rg) * KT * (2 * NP * kBlock6) + lane * 16;
   const int kt0 = KT * kp / kw, kt1 = KT * (kp + 1) / kw;
 
-  v16f acc[2 * NP];
+  v16f acc[GRP ? NP : 2 * NP];
 #pragma unroll
-  for (int i = 0; i < 2 * NP; ++i)
+  for (int i = 0; i < (GRP ? NP : 2 * NP); ++i)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
-  if (tid < RG) {
+  if (!GRP && tid < RG) {
     float fac = 0.0f, rz = 0.0f;
     int dst = -1;
     compute_row_info<AccHi6, 1>(a, m0, tid, fac, dst, rz);
@@ -81,8 +71,28 @@ __global__ __launch_bounds__(512, 4) void k_hi6(const Hi6Args h) {
     fb.load(pb + (size_t)kt * kStageB6);
 #pragma unroll
     for (int i = 0; i < 2 * NP; ++i) fa[i].load(pa + (size_t)kt * (2 * NP * kBlock6) + i * kBlock6);
+    if constexpr (GRP) {
+      // S = row scale times column scale (k = 1 of the product is zero)
+      const f2 sw = reinterpret_cast<const f2*>(h.sw)[((size_t)(st >> 2) * KT + kt) * 128 + (st & 3) * 32 + l32];
+      const v16f zero = {};
 #pragma unroll
-    for (int i = 0; i < 2 * NP; ++i) {
+      for (int pr = 0; pr < NP; ++pr) {
+        const f2 sa = reinterpret_cast<const f2*>(h.sa)[((size_t)((int)blockIdx.y * h.ng + rg) * KT + kt) * RW + pr * 32 + l32];
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          const v16f th = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(hf ? fa[2 * pr].h1() : fa[2 * pr].h0(), hf ? fb.h1() : fb.h0(), zero, 2,
+                                                                          2, 0, 0, 0, 0);
+          const v16f tl = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(hf ? fa[2 * pr + 1].h1() : fa[2 * pr + 1].h0(),
+                                                                          hf ? fb.h1() : fb.h0(), zero, 2, 2, 0, 0, 0, 0);
+          const v16f S = __builtin_amdgcn_mfma_f32_32x32x2f32(kg == 0 ? sa[hf] : 0.0f, kg == 0 ? sw[hf] : 0.0f, zero, 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[pr][v] = __builtin_fmaf(__builtin_fmaf(16.0f, th[v], tl[v]), S[v], acc[pr][v]);
+        }
+      }
+      continue;
+    }
+#pragma unroll
+    for (int i = 0; i < (GRP ? 0 : 2 * NP); ++i) {
       acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[i].h0(), fb.h0(), acc[i], 2, 2, 0, 0, 0, 0);
       acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[i].h1(), fb.h1(), acc[i], 2, 2, 0, 0, 0, 0);
     }
@@ -102,7 +112,8 @@ __global__ __launch_bounds__(512, 4) void k_hi6(const Hi6Args h) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int row = pr * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
-      s_part[(wave * RW + row) * C + l32] = 16 * (int)(acc[2 * pr][v] * 64.0f) + (int)(acc[2 * pr + 1][v] * 64.0f);
+      if constexpr (GRP) s_part[(wave * RW + row) * C + l32] = __float_as_int(acc[pr][v]);
+      else s_part[(wave * RW + row) * C + l32] = 16 * (int)(acc[2 * pr][v] * 64.0f) + (int)(acc[2 * pr + 1][v] * 64.0f);
     }
   __syncthreads();
 
@@ -111,7 +122,7 @@ __global__ __launch_bounds__(512, 4) void k_hi6(const Hi6Args h) {
   const float* s_rz = reinterpret_cast<const float*>(s_info + 2048);
   const int c = tid & 31, r0 = tid >> 5;  // this thread: column c, rows r0, r0 + 16, ..
   const int n = 64 * (st >> 1) + 2 * c + (st & 1);
-  const float swn = a.sw[n], csn = g.asym ? a.colsum[n] : 0.0f;
+  const float swn = GRP ? 0.0f : a.sw[n], csn = !GRP && g.asym ? a.colsum[n] : 0.0f;
   float y[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -119,6 +130,12 @@ __global__ __launch_bounds__(512, 4) void k_hi6(const Hi6Args h) {
     y[i] = 0.0f;
     if (r < RG) {
       const int base = ((r / RW) * kw * RW + (r & (RW - 1))) * C + c;
+      if constexpr (GRP) {
+        float sum = 0.0f;
+        for (int q = 0; q < kw; ++q) sum += __int_as_float(s_part[base + q * (RW * C)]);
+        if (m0 + r < a.M) y[i] = sum;
+        continue;
+      }
       int sum = 0;
       for (int q = 0; q < kw; ++q) sum += s_part[base + q * (RW * C)];
       const float af = g.asym ? __builtin_fmaf(-s_rz[r], csn, (float)sum) : (float)sum;
@@ -192,14 +209,14 @@ __global__ __launch_bounds__(512, 4) void k_hi6(const Hi6Args h) {
   }
 }
 
-template <int NP>
+template <int NP, bool GRP>
 hipError_t launch(const Hi6Args& h, hipStream_t st) {
   constexpr size_t lds = (size_t)8 * 32 * NP * 32 * sizeof(int);
   static size_t lds_done[kStampMaxDevices] = {};
-  const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_hi6<NP>), lds, lds_done);
+  const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_hi6<NP, GRP>), lds, lds_done);
   if (e != hipSuccess) return e;
   const int rows = 32 * NP * h.ng;
-  hipLaunchKernelGGL(k_hi6<NP>, dim3((h.a.N + 63) / 64 * 2, (h.a.M + rows - 1) / rows), dim3(512), lds, st, h);
+  hipLaunchKernelGGL((k_hi6<NP, GRP>), dim3((h.a.N + 63) / 64 * 2, (h.a.M + rows - 1) / rows), dim3(512), lds, st, h);
   return hipGetLastError();
 }
 
@@ -261,5 +278,22 @@ hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float*
   h.mode = mode;
   h.norm = norm;
   h.Y = Y;
-  return h.np == 1 ? launch<1>(h, st) : launch<2>(h, st);
+  return h.np == 1 ? launch<1, false>(h, st) : launch<2, false>(h, st);
+}
+
+hipError_t stamp_launch_hi6_grp(const stamp_plan* p, const uint8_t* h6, const float* sh, float* P, int own, hipStream_t st) {
+  Hi6Args h = {};
+  h.a = stamp_gemm_args(p, nullptr, P);
+  h.a.A = h6;
+  h.a.Bq = p->qWg6_dev;
+  h.a.g = p->bgeom;
+  if (own) h.a.g.k = p->bgeom.khi;
+  h.a.M = h.a.g.B * h.a.g.k;
+  h.a.ld_out = p->Npad;
+  h.np = hi6_np(h.a.M);
+  h.ng = 1;
+  h.norm = 1.0f;
+  h.sa = sh;
+  h.sw = p->swg6_dev;
+  return h.np == 1 ? launch<1, true>(h, st) : launch<2, true>(h, st);
 }

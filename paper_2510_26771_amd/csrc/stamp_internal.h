@@ -183,6 +183,10 @@ struct stamp_plan {
   double* dct_dev;          // general path, DCT: [s][s] orthonormal DCT-II matrix
   int8_t* qWg_dev;          // per-block scales: weight codes [Npad128][d_in] int8
   float* swg_dev;           // per-block scales: [d_in / 64][Npad128]
+  int32_t grp;              // per-block scales on the blocked 2-D Haar transform (stamp_grouped.hip), geometry in bgeom
+  uint8_t* qWg6_dev;        // its weights as FP6 operand and their scales
+  float* swg6_dev;
+  size_t ws_grp[4];         // its scratch (over ws_T, ws_Yt)
   size_t ws_T[3], ws_Yt[3], ws_codes8, ws_scalesg;  // general path workspace (byte offsets)
   // the 8-bit rows through the kernel for few rows (stamp_hi6.hip), [1]: only the first khi rows of every sequence
   int32_t hi6[2];
@@ -293,6 +297,14 @@ bool stamp_rag_quantizes(const stamp_plan* p, const void* X);
 hipError_t stamp_launch_actquant_rag(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st);
 hipError_t stamp_launch_quant_rows_f32(const stamp_plan* p, const float* T, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st);
 hipError_t stamp_launch_quant_rows_grouped(const stamp_plan* p, const float* T, int8_t* codes, float* scales, hipStream_t st);
+// per-block scales, blocked 2-D Haar (p->grp): X -> codes and scales in STaMP order (abot: [B*k][d] fp32 scratch), and from
+// there to Y
+void stamp_grp_bytes(const stamp_plan* p, size_t (&n)[4]);
+hipError_t stamp_grp_plan_weights(stamp_plan* p, hipStream_t st);
+hipError_t stamp_launch_grp_quant(const stamp_plan* p, const void* X, int8_t* codes, float* scales, float* abot, hipStream_t st);
+hipError_t stamp_launch_grp_forward(const stamp_plan* p, const int8_t* codes, const float* scales, uint8_t* const (&buf)[4], float* P, void* Y,
+                                    hipStream_t st);
+hipError_t stamp_launch_hi6_grp(const stamp_plan* p, const uint8_t* h6, const float* sh, float* P, int own, hipStream_t st);
 hipError_t stamp_launch_gemm_grouped(const stamp_plan* p, const int8_t* codes, const float* scales, float* Yt, hipStream_t st);
 hipError_t stamp_launch_bf16_to_f32(const void* src, float* dst, size_t n, hipStream_t st);
 hipError_t stamp_launch_merge_hi(const stamp_plan* p, const float* ythi, int nparts, float* Yt, hipStream_t st);

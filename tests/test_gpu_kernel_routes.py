@@ -109,3 +109,21 @@ RAG = ([_rag(3, 40 + m, m & 1, batch=3, d_in=96, d_out=68) for m in range(1, 9)]
 def test_blocked_haar_of_any_length(w):
     for y in ("f32", "bf16"):
         tl.full_case(w, with_bias=True, check_unfused=False, y_dtype=y)
+
+
+# ---- per-block scales on blocks of 4 x 4 and 8 x 8 tokens: with and without top levels, 4-bit approximations, a depth
+# that ends in half a K step, output widths off the tile, several sequences
+def _grp(side, J, k, d, n, **kw):
+    return _wl(f"grp_{side}_J{J}_k{k}_d{d}_n{n}", seq_len=side * side, grid_h=side, grid_w=side, xform="haar2d", levels=J, k_hi=k,
+               d_in=d, d_out=n, group_size=64, corr_len=4.0, seed=400 + d + n, **kw)
+
+
+GRP = [_grp(64, 3, 64, 192, 130), _grp(32, 3, 64, 64, 258, batch=2, x_dtype="bf16"), _grp(32, 5, 64, 320, 66, batch=3),
+       _grp(64, 6, 64, 128, 514), _grp(32, 2, 16, 128, 192, x_dtype="bf16"), _grp(32, 3, 4, 256, 128), _grp(8, 1, 4, 64, 64),
+       _grp(8, 3, 4, 192, 200, batch=5), _grp(16, 2, 16, 448, 64, batch=9), _grp(32, 3, 64, 128, 131)]
+
+
+@pytest.mark.parametrize("w", GRP, ids=[w.name for w in GRP])
+def test_per_block_scales_on_token_blocks(w):
+    for y in ("f32", "bf16"):
+        tl.grouped_case(w, with_bias=True, y_dtype=y)
