@@ -614,6 +614,17 @@ __global__ __launch_bounds__(1024) void k_gen_dct_fft(const cd* __restrict__ tab
   }
 }
 
+// the factors of k_gen_dct_fft
+__global__ void k_gen_dct_factors(cd* __restrict__ tab, int N) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x, M = N >> 1;
+  if (i >= M + 2 * (M + 1)) return;
+  // angle in units of 2 pi, exact (N is a power of two)
+  const double turn = i < M ? (double)i / M : i <= 2 * M ? (double)(i - M) / (4.0 * N) : (double)(i - 2 * M - 1) / N;
+  double sn, cs;
+  sincospi(2.0 * turn, &sn, &cs);
+  tab[i] = {cs, -sn};
+}
+
 __global__ void k_gen_dct_matrix(double* __restrict__ Cm, int s) {
   const int n = blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;
   if (n >= s) return;
@@ -973,17 +984,10 @@ hipError_t stamp_gen_plan_tables(stamp_plan* p, const float* W, hipStream_t st) 
   }
   if (gn.kind == kGenDct && dct_has_fft(s)) {
     // e^{-2 pi i k / M}, k < M; e^{-i pi k / 2N}, k <= M; e^{-2 pi i k / N}, k <= M (M = N / 2)
-    const int M = s / 2;
-    std::vector<double> tab;
-    auto put = [&](double frac) {  // e^{-2 pi i frac}
-      const long double a = 2.0L * 3.14159265358979323846264338327950288L * (long double)frac;
-      tab.push_back((double)std::cos(a));
-      tab.push_back((double)-std::sin(a));
-    };
-    for (int k = 0; k < M; ++k) put((double)k / M);
-    for (int k = 0; k <= M; ++k) put((double)k / (4.0 * s));
-    for (int k = 0; k <= M; ++k) put((double)k / s);
-    if ((e = upload(&p->dct_dev, tab, st)) != hipSuccess) return e;
+    const int n = s / 2 + 2 * (s / 2 + 1);
+    if ((e = hipMalloc(reinterpret_cast<void**>(&p->dct_dev), sizeof(cd) * (size_t)n)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_gen_dct_factors, dim3((n + 255) / 256), dim3(256), 0, st, reinterpret_cast<cd*>(p->dct_dev), s);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   } else if (gn.kind == kGenDct) {
     if ((e = hipMalloc(reinterpret_cast<void**>(&p->dct_dev), sizeof(double) * (size_t)s * s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_gen_dct_matrix, dim3((s + 255) / 256, s), dim3(256), 0, st, p->dct_dev, s);
