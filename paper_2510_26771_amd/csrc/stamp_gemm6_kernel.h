@@ -1,0 +1,515 @@
+// The FP6 GEMM kernel over the 4-bit rows and its launchers for one tile size (STAMP_GEMM6_WAVES waves per workgroup: 8 or 4).
+// Operand layout: stamp_gemm6.hip.
+#ifndef STAMP_GEMM6_KERNEL_H_
+#define STAMP_GEMM6_KERNEL_H_
+
+#include <type_traits>
+
+#include "stamp_epilogue_reg.h"
+#include "stamp_fp6.h"
+
+namespace {
+
+using namespace stamp_gemm;
+
+// Workgroup: 8 waves (2 x 4), tile 256 x 256, one workgroup per CU with two waves on every SIMD, all
+// eight sharing one operand stage: 48 KB per K step for 256 x 256 x 128 products, a third less L2 -> LDS
+// traffic per product than two independent 256 x 128 workgroups would need (the FP6 pipeline consumes a K
+// step in half the time of the int8 one, which makes that traffic the bound).  Three stages: while step kt is
+// multiplied, the stage of step kt+1 has landed or is landing and that of step kt+2 is in flight; the request for
+// step kt+3 goes out late in step kt, into the stage that step kt has just given up.
+//
+// The kernel is persistent: one workgroup per CU walks its share of the tiles (the XCD-aware order of
+// tile_of_sid, every workgroup of an XCD taking every wx-th tile of that XCD's range), and the operand
+// pipeline runs on across tile boundaries: the first three K steps of the next tile are requested during the last
+// three steps of the current one, so they, and the stores of the epilogue, are in flight while the epilogue
+// computes.  The epilogue works in registers (stamp_epilogue_reg.h) and leaves the operand stages alone.
+//
+// Inside a step nothing waits for what it has just asked for: the LDS reads of an activation block fly under the
+// MFMAs of the block before it, the one workgroup barrier sits before the last block (whose MFMAs cover the reads
+// of the next step's first fragments), and the six loads of a stage request are issued one at a time among MFMAs (three in that last
+// block, three in the first two blocks of the next step).
+//
+// WAVES = 4: tile 128 x 256, one wave on every SIMD, 36 KB per K step; the same loop, nine loads per wave and step.  A tile
+// takes 0.64 of the time of a 256 x 256 one (8.5 us + 0.455 us per K step against 12.8 + 0.72, all CUs busy): for shapes that
+// leave CUs idle (the rule stands at gemm6_half_tiles).
+constexpr int BN6 = 256;
+constexpr int kNumStage6 = 3;
+template <int WAVES>
+struct Tile6 {
+  static constexpr int BMW = 32 * WAVES;                    // rows
+  static constexpr int kStageA = BMW / 32 * kBlock6;        // bytes of the activation part of a stage
+  static constexpr int kStage = kStageA + 2 * kStageB6;     // 48 or 36 KB
+};
+
+// tile of position sid in the walk: 8 M-tiles, then the next N-tile, group of 8 M-tiles after group
+__device__ __forceinline__ void tile_of_sid(int sid, int mt, int nt, int& tm, int& tn) {
+  const int per_group = kGroupM * nt;
+  const int grp = sid / per_group, in_grp = sid - grp * per_group;
+  const int gm = min(kGroupM, mt - grp * kGroupM);
+  tm = grp * kGroupM + in_grp % gm;
+  tn = in_grp / gm;
+}
+
+// SYM: a fused-mode kernel for plans with symmetric activation codes (no offset term in the epilogue)
+// RAG: fused mode over the blocks of a 1-D Haar transform of any length (StampRag); ODD: for odd d_out
+template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM = false, bool RAG = false, bool ODD = false, int WAVES = 8>
+__global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(const GemmArgs a) {
+  using Acc = AccF6Lo;
+  constexpr int BMW = Tile6<WAVES>::BMW, kStageA = Tile6<WAVES>::kStageA, kStage6 = Tile6<WAVES>::kStage;
+  constexpr int NIW = NI;  // 32-column MFMA blocks per wave along N
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  constexpr int NT = 64 * WAVES;  // threads
+  constexpr int kMainBytes = kNumStage6 * kStage6;
+  uint8_t* const row_info = smem + kMainBytes;  // two buffers, alternating from tile to tile
+  constexpr int kRowInfo = kRowInfoBytes + (RAG ? 256 : 0);  // RAG: + the token factors of a short block
+  constexpr int nA = kStageA / (NT * 16), nB = 2 * kStageB6 / (NT * 16);  // 16-byte chunks per thread and step
+  constexpr int kLoadsPerStep = nA + nB;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
+  // wave tile: rows [128 wm, +128), columns [32 NIW wn, +32 NIW)
+  const int wm = wave >> 2, wn = wave & 3;
+  const int KT = a.Kpad / BK;
+  const int mt = (a.M + BMW - 1) / BMW, nt = a.Npad / BN6, total = mt * nt;
+
+  // tiles of this workgroup: the XCD's contiguous range of the walk, every wx-th position from `local` on
+  const int nwg = (int)gridDim.x, xcd = (int)blockIdx.x % kNumXcd, local = (int)blockIdx.x / kNumXcd;
+  const int wx = (nwg - xcd + kNumXcd - 1) / kNumXcd;  // workgroups that run on this XCD
+  const int tall = total / kNumXcd, rem = total % kNumXcd;
+  const int first = xcd * tall + min(xcd, rem), count = tall + (xcd < rem ? 1 : 0);
+  if (local >= count) return;
+
+  // global image = LDS image: chunk q = i * NT + tid of an operand's stage goes to byte 16 q.  The
+  // weight stage is two column tiles of 128 (KT * 12 KB apart in memory): chunks 0..767 and 768..1535;
+  // the boundary falls between waves, so the source tile of a pass is wave-uniform.  Addresses are a
+  // wave-uniform base (tile, K step, pass) plus this thread's constant 32-bit offset.
+  const uint32_t off16 = (uint32_t)tid * 16u;
+  // cursor of the requests: request rq_kt of the tile at position rq_pos of this workgroup's walk (all scalar).  The
+  // loads address memory through two buffer descriptors (the tile's activation panel; its two weight panels, KT * 12 KB
+  // apart) + a scalar byte offset + this thread's constant 32-bit offset: no vector address arithmetic per load.
+  // K step of a tile's first request.  The workgroups of an XCD that share an operand panel (same row or column of
+  // the XCD's 8 x 4 window of tiles) ask for a line at the same moment when they walk K in step: one misses L2, the
+  // others wait on the same miss.  Started a few K steps apart (every tile walks all KT steps once, from its own
+  // start, wrapping: an fp32 sum of these integers is exact in any order), most of them find the line in L2.
+  int rq_k0;
+  {
+    int tm0_, tn0_;
+    tile_of_sid(first + local, mt, nt, tm0_, tn0_);
+    rq_k0 = (((tm0_ & 7) + 2 * (tn0_ & 3)) & 7) % KT;
+  }
+  int rq_pos = local, rq_kt = 0, rq_stg = 0, rq_kk = rq_k0;  // rq_kt counts the tile's requests, rq_kk is their K step
+  __amdgpu_buffer_rsrc_t rdA, rdB;
+  auto rq_tile = [&]() {
+    int tm_, tn_;
+    tile_of_sid(first + rq_pos, mt, nt, tm_, tn_);
+    // (a 128-row tile is one half of a 256-row tile of the layout: its blocks are contiguous in every K step)
+    const uint8_t* pa_ = WAVES == 8 ? a.A + (size_t)tm_ * KT * kStageA6 : a.A + (size_t)(tm_ >> 1) * KT * kStageA6 + (tm_ & 1) * kStageA;
+    rdA = __builtin_amdgcn_make_buffer_rsrc((void*)pa_, 0, 0x7fffffff, 0x00020000);
+    rdB = __builtin_amdgcn_make_buffer_rsrc((void*)(a.Bq + (size_t)(2 * tn_) * KT * kStageB6), 0, 0x7fffffff, 0x00020000);
+  };
+  rq_tile();
+  // A request = the kLoadsPerStep loads of the next K step of the walk into the next stage of the ring.  rq_begin
+  // fixes its addresses and advances the cursor, rq_issue<i> issues its i-th load: the
+  // main loop spreads them among its MFMAs (eight waves issuing all their loads at once keep the address unit busy
+  // for several hundred cycles, during which none of them can issue anything else).
+  // Of a request's six loads three go out among the MFMAs of the step's last block, the others in the next step: two
+  // in its first block (rq_tail2: still to be issued), the last before its second block (rq_tail3)
+  bool rq_tail2 = false, rq_tail3 = false;
+  uint8_t* rq_so = nullptr;
+  uint32_t rq_oa = 0, rq_ob = 0;  // byte offsets of the request's K step in the activation / weight panels
+  auto rq_begin = [&]() {
+    if (__builtin_expect(rq_kt == KT, 0)) {  // the tile of the request before this one is complete: its descriptors are no longer needed
+      rq_kt = 0;
+      rq_pos += wx;
+      if (rq_pos < count) {
+        rq_tile();
+      } else {
+        // the walk is over: the remaining requests read nothing (a descriptor without records; the loads still count,
+        // so every wait of the main loop is for the same number of them)
+        rdA = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0, 0x00020000);
+        rdB = rdA;
+      }
+    }
+    rq_so = smem + rq_stg * kStage6 + wave * 1024;
+    rq_oa = (uint32_t)rq_kk * (uint32_t)kStageA6;
+    rq_ob = (uint32_t)rq_kk * (uint32_t)kStageB6;
+    rq_kk = (rq_kk == KT - 1) ? 0 : rq_kk + 1;
+    rq_stg = (rq_stg == kNumStage6 - 1) ? 0 : rq_stg + 1;
+    ++rq_kt;
+  };
+  auto rq_issue = [&](auto i_tag) __attribute__((always_inline)) {
+    constexpr int li = decltype(i_tag)::value;
+    if constexpr (li < nA) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rdA, (void __attribute__((address_space(3)))*)(rq_so + li * (NT * 16)), 16, off16,
+                                               rq_oa + (uint32_t)(li * (NT * 16)), 0, 0);
+    } else {
+      constexpr int i = li - nA;
+      // chunk i * NT + tid of the 1536: column tile 1 (KT stages further on) from chunk 768 on (a whole number of waves)
+      const bool half = (i * NT + wave * 64) >= 768;
+      const uint32_t ob = rq_ob + (half ? (uint32_t)KT * (uint32_t)kStageB6 + (uint32_t)(i * NT * 16 - 768 * 16) : (uint32_t)(i * NT * 16));
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rdB, (void __attribute__((address_space(3)))*)(rq_so + kStageA + i * (NT * 16)), 16,
+                                               off16, ob, 0, 0);
+    }
+  };
+  static_assert(kLoadsPerStep == (WAVES == 8 ? 6 : 9), "the main loop spreads six (nine) loads per wave and step");
+  // load i, and with four waves load i + 3 as well
+  auto rq_issue2 = [&](auto i_tag) __attribute__((always_inline)) {
+    rq_issue(i_tag);
+    if constexpr (WAVES == 4) rq_issue(std::integral_constant<int, decltype(i_tag)::value + 3>{});
+  };
+  auto request_next = [&]() {
+    rq_begin();
+    rq_issue(std::integral_constant<int, 0>{});
+    rq_issue(std::integral_constant<int, 1>{});
+    rq_issue(std::integral_constant<int, 2>{});
+    rq_issue2(std::integral_constant<int, 3>{});
+    rq_issue2(std::integral_constant<int, 4>{});
+    rq_issue2(std::integral_constant<int, 5>{});
+  };
+
+  // LDS byte addresses of part 0 of this lane's 48 bytes in stage 0: 32-row block, then lane * 16
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
+  const uint32_t adrA0 = (uint32_t)((wm * 4) * kBlock6 + lane * 16);
+  const uint32_t adrB0 = (uint32_t)(kStageA + (wn >> 1) * kStageB6 + ((wn & 1) * 2) * kBlock6 + lane * 16);
+
+  // ---- prologue: stages 0 and 1 requested, landed and published by a barrier; stage 2 requested ----
+  request_next();
+  request_next();
+  {
+    int tm0, tn0;
+    tile_of_sid(first + local, mt, nt, tm0, tn0);
+    if (tid < BMW) store_row_info<Acc, EPI, RAG>(a, tm0 * BMW, tid, row_info);
+    if constexpr (RAG) {
+      if (tid < 64) {
+        const float f = tid < a.rag.mlast ? rag_leaf(a.rag, tid) : 0.0f;
+        reinterpret_cast<float*>(row_info + kRowInfoBytes)[tid] = f;
+        reinterpret_cast<float*>(row_info + kRowInfo + kRowInfoBytes)[tid] = f;
+      }
+    }
+  }
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  request_next();
+  int landed = 1;  // steps from here on whose loads are known to have landed (their barrier needs no wait)
+  int stg = 0;     // stage of the step about to be multiplied
+  int rbuf = 0;    // row-info buffer of the current tile
+
+  // Fragment registers.  A lane's 48 bytes of one 32-row block and K step are the two 24-byte MFMA operands of the
+  // step's halves, read as three 16-byte parts.  The parts of a fragment must land in 12 CONSECUTIVE registers (the
+  // first operand is registers 0..5, the second 6..11), which the register allocator does not arrange for separate
+  // asm outputs (it copies parts into fresh tuples and runs out of registers); the fragments therefore live in fixed
+  // registers v184..v255: two activation sets (block mi + 1 is read while block mi is multiplied) and the weights'
+  // NIW = 2 blocks double-buffered from step to step.
+  static_assert(NIW == 2, "fixed fragment registers are laid out for two weight blocks per wave");
+  struct Frag {
+    u6 h0, h1;
+  };
+#define STAMP_RD3(f, H0, H1, P0, P1, P2, base, off)                                                                   \
+  asm volatile("ds_read_b128 " P0 ", %2 offset:%3\n\tds_read_b128 " P1 ", %2 offset:%4\n\tds_read_b128 " P2 ", %2 offset:%5" \
+               : "=&{" H0 "}"(f.h0), "=&{" H1 "}"(f.h1)                                                               \
+               : "v"(base), "n"(off), "n"((off) + kPart), "n"((off) + 2 * kPart))
+#define STAMP_RD_AS0(base, off) STAMP_RD3(As0, "v[184:189]", "v[190:195]", "v[184:187]", "v[188:191]", "v[192:195]", base, off)
+#define STAMP_RD_AS1(base, off) STAMP_RD3(As1, "v[196:201]", "v[202:207]", "v[196:199]", "v[200:203]", "v[204:207]", base, off)
+  // activation block 0 and the two weight blocks of a step in one statement, parts 0 and 1 of all three first (the
+  // first MFMA half's operands), then the parts 2
+#define STAMP_RD9(fa, fb0, fb1, AH0, AH1, B0H0, B0H1, B1H0, B1H1, A0, A1, A2, B00_, B01_, B02_, B10_, B11_, B12_, basea, baseb)         \
+  asm volatile("ds_read_b128 " A0 ", %6 offset:0\n\tds_read_b128 " A1 ", %6 offset:%8\n\t"                                          \
+               "ds_read_b128 " B00_ ", %7 offset:0\n\tds_read_b128 " B01_ ", %7 offset:%8\n\t"                                      \
+               "ds_read_b128 " B10_ ", %7 offset:%10\n\tds_read_b128 " B11_ ", %7 offset:%11\n\t"                                   \
+               "ds_read_b128 " A2 ", %6 offset:%9\n\tds_read_b128 " B02_ ", %7 offset:%9\n\tds_read_b128 " B12_ ", %7 offset:%12"   \
+               : "=&{" AH0 "}"(fa.h0), "=&{" AH1 "}"(fa.h1), "=&{" B0H0 "}"(fb0.h0), "=&{" B0H1 "}"(fb0.h1), "=&{" B1H0 "}"(fb1.h0),  \
+                 "=&{" B1H1 "}"(fb1.h1)                                                                                              \
+               : "v"(basea), "v"(baseb), "n"(kPart), "n"(2 * kPart), "n"(kBlock6), "n"(kBlock6 + kPart), "n"(kBlock6 + 2 * kPart))
+#define STAMP_RD9_PB0(basea, baseb)                                                                                                  \
+  STAMP_RD9(As0, B00, B01, "v[184:189]", "v[190:195]", "v[208:213]", "v[214:219]", "v[220:225]", "v[226:231]", "v[184:187]", "v[188:191]", \
+            "v[192:195]", "v[208:211]", "v[212:215]", "v[216:219]", "v[220:223]", "v[224:227]", "v[228:231]", basea, baseb)
+#define STAMP_RD9_PB1(basea, baseb)                                                                                                  \
+  STAMP_RD9(As0, B10, B11, "v[184:189]", "v[190:195]", "v[232:237]", "v[238:243]", "v[244:249]", "v[250:255]", "v[184:187]", "v[188:191]", \
+            "v[192:195]", "v[232:235]", "v[236:239]", "v[240:243]", "v[244:247]", "v[248:251]", "v[252:255]", basea, baseb)
+  // a wait names the fragments it covers (same registers in and out), which keeps their MFMAs behind it
+#define STAMP_WAIT2(cnt, x, XR, y, YR) asm volatile("s_waitcnt lgkmcnt(" #cnt ")" : "={" XR "}"(x), "={" YR "}"(y) : "0"(x), "1"(y))
+#define STAMP_WAITH(cnt, x, XR) asm volatile("s_waitcnt lgkmcnt(" #cnt ")" : "={" XR "}"(x) : "0"(x))
+#define STAMP_WAIT1(cnt, f, H0, H1) asm volatile("s_waitcnt lgkmcnt(" #cnt ")" : "={" H0 "}"(f.h0), "={" H1 "}"(f.h1) : "0"(f.h0), "1"(f.h1))
+#define STAMP_WAIT_AS0(cnt) STAMP_WAIT1(cnt, As0, "v[184:189]", "v[190:195]")
+#define STAMP_WAIT_AS1(cnt) STAMP_WAIT1(cnt, As1, "v[196:201]", "v[202:207]")
+
+  for (int pos = local; pos < count; pos += wx) {
+    int tm, tn;
+    tile_of_sid(first + pos, mt, nt, tm, tn);
+    const int m0 = tm * BMW, n0 = tn * BN6;
+    const int nw = n0 + wn * (32 * NIW);
+
+    v16f acc[4][NIW];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < NIW; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+    Frag As0, As1, B00, B01, B10, B11;  // per tile: no fragment is carried across the epilogue
+    // the four MFMAs of activation block mi: both halves against both weight blocks
+    auto mfma4 = [&](const Frag& A, const Frag& W0, const Frag& W1, auto mi_tag) __attribute__((always_inline)) {
+      constexpr int mi = decltype(mi_tag)::value;
+      acc[mi][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)A.h0), widen((v6i)W0.h0), acc[mi][0], 2, 2, 0, 0, 0, 0);
+      acc[mi][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)A.h0), widen((v6i)W1.h0), acc[mi][1], 2, 2, 0, 0, 0, 0);
+      acc[mi][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)A.h1), widen((v6i)W0.h1), acc[mi][0], 2, 2, 0, 0, 0, 0);
+      acc[mi][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)A.h1), widen((v6i)W1.h1), acc[mi][1], 2, 2, 0, 0, 0, 0);
+    };
+
+    // Step kt (pb = 0: weights in B00, B01, the next step's go to B10, B11; pb = 1: the other way round).  On entry
+    // the reads of the step's weights and of activation block 0 have been issued (by the head of the tile or by the
+    // step before).  Block 1 is requested, block 0 multiplied, block 2 requested, block 1 multiplied, ...: the LDS
+    // reads of a block fly under the MFMAs of the block before.  After block 2 every read of this stage has
+    // returned: the wave waits for its own loads of the NEXT step's stage (the step after that may still be in
+    // flight), meets the others at the workgroup barrier (next stage visible, this stage free), requests the step
+    // three ahead into this stage, issues the reads of the next step's block 0 and weights, and multiplies block 3
+    // under them.  One barrier per step, none between a read and its use.
+    auto step = [&](auto pb_tag) __attribute__((always_inline)) {
+      constexpr int pb = decltype(pb_tag)::value;
+      const uint32_t sa = lds0 + (uint32_t)(stg * kStage6);
+      __builtin_amdgcn_sched_barrier(0);
+      STAMP_RD_AS1(sa + adrA0, 1 * kBlock6);
+      // block 0: of the 12 reads in flight the first 4 feed the first MFMA, 6 the second, 8 the third, 9 the fourth
+      if constexpr (pb == 0) {
+        STAMP_WAIT2(8, As0.h0, "v[184:189]", B00.h0, "v[208:213]");
+        acc[0][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h0), widen((v6i)B00.h0), acc[0][0], 2, 2, 0, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (rq_tail2) rq_issue2(std::integral_constant<int, 3>{});
+        __builtin_amdgcn_sched_barrier(0);
+        STAMP_WAITH(6, B01.h0, "v[220:225]");
+        acc[0][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h0), widen((v6i)B01.h0), acc[0][1], 2, 2, 0, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (rq_tail2) rq_issue2(std::integral_constant<int, 4>{});
+        rq_tail3 = rq_tail2;
+        rq_tail2 = false;
+        __builtin_amdgcn_sched_barrier(0);
+        STAMP_WAIT2(4, As0.h1, "v[190:195]", B00.h1, "v[214:219]");
+        acc[0][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h1), widen((v6i)B00.h1), acc[0][0], 2, 2, 0, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        STAMP_WAITH(3, B01.h1, "v[226:231]");
+        acc[0][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h1), widen((v6i)B01.h1), acc[0][1], 2, 2, 0, 0, 0, 0);
+      } else {
+        STAMP_WAIT2(8, As0.h0, "v[184:189]", B10.h0, "v[232:237]");
+        acc[0][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h0), widen((v6i)B10.h0), acc[0][0], 2, 2, 0, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (rq_tail2) rq_issue2(std::integral_constant<int, 3>{});
+        __builtin_amdgcn_sched_barrier(0);
+        STAMP_WAITH(6, B11.h0, "v[244:249]");
+        acc[0][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h0), widen((v6i)B11.h0), acc[0][1], 2, 2, 0, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (rq_tail2) rq_issue2(std::integral_constant<int, 4>{});
+        rq_tail3 = rq_tail2;
+        rq_tail2 = false;
+        __builtin_amdgcn_sched_barrier(0);
+        STAMP_WAIT2(4, As0.h1, "v[190:195]", B10.h1, "v[238:243]");
+        acc[0][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h1), widen((v6i)B10.h1), acc[0][0], 2, 2, 0, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        STAMP_WAITH(3, B11.h1, "v[250:255]");
+        acc[0][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h1), widen((v6i)B11.h1), acc[0][1], 2, 2, 0, 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      STAMP_RD_AS0(sa + adrA0, 2 * kBlock6);
+      if (rq_tail3) rq_issue2(std::integral_constant<int, 5>{});
+      STAMP_WAIT_AS1(3);
+      if constexpr (pb == 0) mfma4(As1, B00, B01, std::integral_constant<int, 1>{});
+      else mfma4(As1, B10, B11, std::integral_constant<int, 1>{});
+      __builtin_amdgcn_sched_barrier(0);
+      STAMP_RD_AS1(sa + adrA0, 3 * kBlock6);
+      rq_tail3 = false;
+      STAMP_WAIT_AS0(3);
+      if constexpr (pb == 0) mfma4(As0, B00, B01, std::integral_constant<int, 2>{});
+      else mfma4(As0, B10, B11, std::integral_constant<int, 2>{});
+      __builtin_amdgcn_sched_barrier(0);
+      STAMP_WAIT_AS1(0);
+      // ---- the next step's stage ----
+      asm volatile("" ::: "memory");
+      if (landed > 0) {
+        --landed;
+      } else {
+        __builtin_amdgcn_s_waitcnt(0x0F70 | kLoadsPerStep);  // vmcnt(one step's loads): the request of the step before may be in flight
+      }
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      rq_begin();
+      __builtin_amdgcn_sched_barrier(0);
+      stg = (stg == kNumStage6 - 1) ? 0 : stg + 1;
+      {
+        // (after the tile's last step these reads fetch the next tile's first fragments, which the epilogue's
+        // registers cannot keep: they are dropped and read again by the next head)
+        const uint32_t sn = lds0 + (uint32_t)(stg * kStage6);
+        if constexpr (pb == 0) STAMP_RD9_PB1(sn + adrA0, sn + adrB0);
+        else STAMP_RD9_PB0(sn + adrA0, sn + adrB0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // block 3, the request's loads spread among its MFMAs
+      const Frag& W0 = pb == 0 ? B00 : B10;
+      const Frag& W1 = pb == 0 ? B01 : B11;
+      rq_issue(std::integral_constant<int, 0>{});
+      __builtin_amdgcn_sched_barrier(0);
+      acc[3][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As1.h0), widen((v6i)W0.h0), acc[3][0], 2, 2, 0, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      rq_issue(std::integral_constant<int, 1>{});
+      __builtin_amdgcn_sched_barrier(0);
+      acc[3][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As1.h0), widen((v6i)W1.h0), acc[3][1], 2, 2, 0, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      rq_issue(std::integral_constant<int, 2>{});
+      __builtin_amdgcn_sched_barrier(0);
+      acc[3][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As1.h1), widen((v6i)W0.h1), acc[3][0], 2, 2, 0, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_sched_barrier(0);
+      acc[3][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As1.h1), widen((v6i)W1.h1), acc[3][1], 2, 2, 0, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      rq_tail2 = true;  // loads 3, 4 and 5 follow among the MFMAs of the next step (or after the tile's last step)
+    };
+    // head of the tile: the barrier that published its first stage lies behind (prologue, or the last step of the
+    // tile before)
+    {
+      const uint32_t sh = lds0 + (uint32_t)(stg * kStage6);
+      STAMP_RD9_PB0(sh + adrA0, sh + adrB0);
+    }
+    for (int kt = 0; kt + 1 < KT; kt += 2) {
+      step(std::integral_constant<int, 0>{});
+      step(std::integral_constant<int, 1>{});
+    }
+    if (KT & 1) step(std::integral_constant<int, 0>{});
+    if (rq_tail2) {
+      rq_issue2(std::integral_constant<int, 3>{});
+      rq_issue2(std::integral_constant<int, 4>{});
+      rq_issue2(std::integral_constant<int, 5>{});
+      rq_tail2 = false;
+    }
+    // the last step's look-ahead reads must have returned before their registers are used for anything else
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+
+    // Everything requested so far (the next tile's first steps included) must have landed before the epilogue issues
+    // its stores: the counter retires in order, so a later wait for a load would also wait for every store before
+    // it.  The epilogue waits for that itself, after its lane swaps (the plain modes: before they start); after it
+    // the next two steps therefore need no wait.
+    landed = 2;
+    // Per-lane values of the epilogue are derived from an opaque copy of the lane number, so that they are
+    // computed here, once per tile, instead of being carried in registers across the main loop (which has none
+    // to spare: a spilled value would be reloaded with a wait for all outstanding loads inside that loop).
+    int lane_e = lane, tid_e = tid;
+    asm volatile("" : "+v"(lane_e), "+v"(tid_e));
+    // the epilogue's operands from global memory: their latency passes under the lane swaps
+    RegEpiOperands<EPI, (IS2D ? 2 * RB : RB), RAG> eo;
+    if constexpr (EPI >= 2) eo.request(a, m0, nw, wm, lane_e);
+    // row factors of the next tile: loaded now, written to the other buffer after the epilogue (a barrier of
+    // the next tile's first step publishes them long before its epilogue reads them)
+    float nfac = 0.0f, nrz = 0.0f;
+    int ndst = -1;
+    const bool has_next = pos + wx < count;
+    if (has_next && tid_e < BMW) {
+      int tm1, tn1;
+      tile_of_sid(first + pos + wx, mt, nt, tm1, tn1);
+      compute_row_info<Acc, EPI, RAG>(a, tm1 * BMW, tid_e, nfac, ndst, nrz);
+    }
+    const uint8_t* ri = row_info + rbuf * kRowInfo;
+    if constexpr (EPI != 2) {
+      // The loads just requested complete here, on every path and in a form the compiler's wait-count bookkeeping
+      // sees: a load it believed pending at the end of the tile would make it wait for ALL loads inside the next
+      // main loop.  (The fused epilogue places this wait after its lane swaps.)
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    }
+    if constexpr (EPI >= 2) {
+      epilogue_reg<EPI, RB, IS2D, YBF16, NI, 0, SYM, RAG, ODD>(a, acc, ri, eo, m0, nw, wm, lane_e);
+    } else {
+      EpiOperands<EPI, RB, IS2D> none;
+      epilogue<Acc, EPI, RB, IS2D, YBF16, true>(a, acc, smem, ri, none, m0, n0, lane_e, wave, wm, wn);
+    }
+    rbuf ^= 1;
+    if (has_next && tid_e < BMW) write_row_info(row_info + rbuf * kRowInfo, tid_e, nfac, ndst, nrz);
+  }
+}
+
+int gemm6_cus() {
+  static int cus = 0;
+  if (cus == 0) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+      cus = 256;
+  }
+  return cus;
+}
+int gemm6_workgroups(int tiles) { return tiles < gemm6_cus() ? tiles : gemm6_cus(); }
+
+template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM, bool RAG = false, bool ODD = false>
+hipError_t launch_k(const GemmArgs& a, hipStream_t st) {
+  constexpr int WAVES = STAMP_GEMM6_WAVES;
+  constexpr size_t lds = (size_t)kNumStage6 * Tile6<WAVES>::kStage + 2 * (kRowInfoBytes + (RAG ? 256 : 0));
+  static size_t lds_done[kStampMaxDevices] = {};
+  hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD, WAVES>), lds, lds_done);
+  if (e != hipSuccess) return e;
+  const int mt = (a.M + Tile6<WAVES>::BMW - 1) / Tile6<WAVES>::BMW, nt = a.Npad / BN6;
+  hipLaunchKernelGGL((k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD, WAVES>), dim3(gemm6_workgroups(mt * nt)), dim3(64 * WAVES), lds, st, a);
+  return hipGetLastError();
+}
+
+template <int EPI, int RB, bool IS2D, bool YBF16>
+hipError_t launch_y(const GemmArgs& a, hipStream_t st) {
+  if constexpr (EPI == 2) {
+    if (!a.g.asym) return launch_k<EPI, RB, IS2D, YBF16, true>(a, st);
+  }
+  return launch_k<EPI, RB, IS2D, YBF16, false>(a, st);
+}
+
+template <int EPI, int RB, bool IS2D>
+hipError_t launch(const GemmArgs& a, hipStream_t st) {
+  if constexpr (EPI >= 2) {
+    if (a.g.y_bf16) return launch_y<EPI, RB, IS2D, true>(a, st);
+  }
+  return launch_y<EPI, RB, IS2D, false>(a, st);
+}
+
+
+template <int RB, bool ODD>
+hipError_t launch_rag_n(const GemmArgs& a, hipStream_t st) {
+  if (a.g.y_bf16) return a.g.asym ? launch_k<2, RB, false, true, false, true, ODD>(a, st) : launch_k<2, RB, false, true, true, true, ODD>(a, st);
+  return a.g.asym ? launch_k<2, RB, false, false, false, true, ODD>(a, st) : launch_k<2, RB, false, false, true, true, ODD>(a, st);
+}
+template <int RB>
+hipError_t launch_rag(const GemmArgs& a, hipStream_t st) {
+  return (a.N & 1) ? launch_rag_n<RB, true>(a, st) : launch_rag_n<RB, false>(a, st);
+}
+
+// the GEMM of one mode on this tile size
+hipError_t gemm6_run(const GemmArgs& a, int mode, hipStream_t st) {
+  if (mode == 1) return launch<1, 0, false>(a, st);
+  if (mode == 3) return launch<3, 0, false>(a, st);
+#if STAMP_GEMM6_WAVES == 8
+  if (mode == 0) return launch<0, 0, false>(a, st);
+#endif
+  if (mode != 2) return hipErrorInvalidValue;
+  if (a.rag.on) {
+    switch (a.g.r) {
+      case 3: return launch_rag<3>(a, st);
+      case 4: return launch_rag<4>(a, st);
+      case 5: return launch_rag<5>(a, st);
+      case 6: return launch_rag<6>(a, st);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  if (!a.g.is2d) {
+    switch (a.g.r) {
+      case 3: return launch<2, 3, false>(a, st);
+      case 4: return launch<2, 4, false>(a, st);
+      case 5: return launch<2, 5, false>(a, st);
+      case 6: return launch<2, 6, false>(a, st);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  switch (a.g.r) {
+    case 2: return launch<2, 2, true>(a, st);
+    case 3: return launch<2, 3, true>(a, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
+#endif  // STAMP_GEMM6_KERNEL_H_

@@ -623,5 +623,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, typename Acc::V (&ac
 
 // arguments common to every GEMM launch of a plan (host)
 stamp_gemm::GemmArgs stamp_gemm_args(const stamp_plan* p, const float* scales, void* out);
+// the FP6 GEMM on 128 x 256 tiles
+hipError_t stamp_gemm6_half(const stamp_gemm::GemmArgs& a, int mode, hipStream_t st);
 
 #endif  // STAMP_GEMM_COMMON_H_

@@ -127,3 +127,25 @@ GRP = [_grp(64, 3, 64, 192, 130), _grp(32, 3, 64, 64, 258, batch=2, x_dtype="bf1
 def test_per_block_scales_on_token_blocks(w):
     for y in ("f32", "bf16"):
         tl.grouped_case(w, with_bias=True, y_dtype=y)
+
+
+# ---- 4-bit rows' GEMM: both tile sizes (128 x 256 where that leaves fewer rounds, else 256 x 256), with one row more than a
+# tile and a depth of one, two and an odd number of K steps
+def _tiles(name, m, n, d, **kw):
+    return _wl(name, seq_len=m, d_in=d, d_out=n, k_hi=kw.pop("k_hi", 16), seed=500 + m + n, **kw)
+
+
+TILES = [_tiles("t256_ident_odd_rows", 8193, 2050, 64, xform="identity", levels=0),
+         _tiles("t256_rag", 2049, 8190, 96, levels=3, skip_first=True),
+         _tiles("t256_rag_odd_n", 2050, 8065, 96, levels=4, skip_first=True, act_quant="asym"),
+         _tiles("t256_haar", 2048, 7938, 160, levels=11, k_hi=64),
+         _tiles("t256_wht", 2048, 7938, 32, xform="wht", levels=0),
+         _tiles("t256_grid", 4096, 4098, 288, xform="haar2d", grid_h=64, grid_w=64, levels=3, k_hi=64, corr_len=4.0),
+         _tiles("t128_ident_rows", 257, 300, 32, xform="identity", levels=0),
+         _tiles("t128_haar_129_tiles", 1024, 8300, 416, levels=10, k_hi=32, act_quant="asym"),
+         _tiles("t128_grid4", 1024, 514, 160, xform="haar2d", grid_h=32, grid_w=32, levels=5, k_hi=64, corr_len=4.0)]
+
+
+@pytest.mark.parametrize("w", TILES, ids=[w.name for w in TILES])
+def test_both_gemm_tile_sizes(w):
+    tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16" if w.d_out % 4 else "f32", check_acc=False)
