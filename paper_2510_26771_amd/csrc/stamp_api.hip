@@ -262,6 +262,7 @@ void layout_workspace(stamp_plan* p) {
     p->ws_hi6 = p->ws_T[2];
     p->hi6[0] = stamp_hi6_fits(p, 0) && stamp_hi6_bytes(p, 0) <= p->ws_Yt[0] - p->ws_T[2];
     p->hi6[1] = 0;
+    p->direct_ok = !grouped && (g.k == 0 || (p->hi6[0] && stamp_hi6_bytes(p, 0) <= p->ws_scales - p->ws_qhi));
     if (p->rag.on && (stamp_rag_a6_bytes(p) > p->ws_T[2] - p->ws_T[0] ||
                       (size_t)g.B * g.khi * p->Npad * sizeof(float) > p->ws_codes8 - p->ws_Yt[0]))
       p->rag.on = 0;
@@ -309,6 +310,9 @@ void layout_workspace(stamp_plan* p) {
     else if (p->ws_total < align256(off + need)) p->ws_total = align256(off + need);
   }
   p->ws_hi6 = p->ws_total > off ? off : p->ws_abot;
+  // written by the quantizer itself it lies over the packed codes, which are not used then
+  const size_t room = p->ws_scales - p->ws_qhi;
+  p->direct_ok = (g.ident && g.k == 0) || ((p->hi6[0] || p->hi6[1]) && stamp_hi6_bytes(p, 0) <= room && stamp_hi6_bytes(p, 1) <= room);
 }
 
 inline bool ws_ok(const stamp_plan* p, const void* ws, size_t bytes, size_t need) {
@@ -349,15 +353,18 @@ inline hipError_t convert_rows(const stamp_plan* p, const int8_t* q_hi, const ui
 inline bool rag_route(const stamp_plan* p, const void* Y) { return p->rag.on && (reinterpret_cast<uintptr_t>(Y) & 15) == 0; }
 
 stamp_status_t rag_forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t* q_lo, const float* scales, void* Y, void* ws,
-                             hipStream_t st) {
+                             hipStream_t st, const StampDirect* dir) {
   float* ythi = reinterpret_cast<float*>(at(ws, p->ws_ythi));
   float* P = reinterpret_cast<float*>(at(ws, p->ws_bP));
   uint8_t* blk = at(ws, p->ws_ba6);
-  uint8_t* hi6 = at(ws, p->ws_hi6);
+  uint8_t* hi6 = dir != nullptr ? dir->h6 : at(ws, p->ws_hi6);
   const bool fp6 = p->engine == STAMP_GEMM_FP6;
-  const StampHi6Pack hp = p->hi6[0] ? stamp_hi6_pack(p, q_hi, hi6, 0) : StampHi6Pack{};
-  hipError_t e = fp6 ? stamp_launch_repack6_rag(p, q_lo, blk, st, &hp) : stamp_launch_gather_lo_rag(p, q_lo, blk, st);
-  if (e == hipSuccess && !fp6) e = stamp_launch_repack6(p, nullptr, nullptr, st, &hp);
+  hipError_t e = hipSuccess;
+  if (dir == nullptr) {
+    const StampHi6Pack hp = p->hi6[0] ? stamp_hi6_pack(p, q_hi, hi6, 0) : StampHi6Pack{};
+    e = fp6 ? stamp_launch_repack6_rag(p, q_lo, blk, st, &hp) : stamp_launch_gather_lo_rag(p, q_lo, blk, st);
+    if (e == hipSuccess && !fp6) e = stamp_launch_repack6(p, nullptr, nullptr, st, &hp);
+  }
   if (e != hipSuccess) return STAMP_ERR_DEVICE;
   if (p->hi6[0]) {
     e = stamp_launch_hi6(p, hi6, scales, 3, P, p->Npad, 0, Y, stamp_haar_norm_host(p->rag.r), st);
@@ -372,7 +379,7 @@ stamp_status_t rag_forward_q(const stamp_plan* p, const int8_t* q_hi, const uint
 // codes_are_ours: q_hi / q_lo were written by this library's quantizer (which also fills the rows of q_lo that
 // own_top reads); buffers a caller packed need not hold them
 stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t* q_lo, const float* scales, void* Y,
-                         void* ws, hipStream_t st, bool codes_are_ours) {
+                         void* ws, hipStream_t st, bool codes_are_ours, const StampDirect* dir = nullptr) {
   float* ythi = reinterpret_cast<float*>(at(ws, p->ws_ythi));
   float* P = reinterpret_cast<float*>(at(ws, p->ws_P));
   if (p->grp && (reinterpret_cast<uintptr_t>(Y) & 15) == 0) {
@@ -380,7 +387,7 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
     return stamp_launch_grp_forward(p, q_hi, scales, buf, reinterpret_cast<float*>(at(ws, p->ws_Yt[0])), Y, st) == hipSuccess
                ? STAMP_OK : STAMP_ERR_DEVICE;
   }
-  if (rag_route(p, Y)) return rag_forward_q(p, q_hi, q_lo, scales, Y, ws, st);
+  if (rag_route(p, Y)) return rag_forward_q(p, q_hi, q_lo, scales, Y, ws, st, dir);
   if (p->gen.kind != kGenNone) {
     // general path: dequantized rows in STaMP order -> (transformed bias) -> inverse level by level -> Y
     float* const yt[3] = {reinterpret_cast<float*>(at(ws, p->ws_Yt[0])), reinterpret_cast<float*>(at(ws, p->ws_Yt[1])),
@@ -391,9 +398,10 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
     } else {
       const bool lo = p->geom.k < p->geom.s, lo6 = lo && p->engine == STAMP_GEMM_FP6;
       uint8_t* a6g = at(ws, p->ws_a6);
-      if (convert_rows(p, q_hi, lo6 ? q_lo : nullptr, a6g, p->geom.k > 0 && p->hi6[0], 0, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
+      if (dir == nullptr &&
+          convert_rows(p, q_hi, lo6 ? q_lo : nullptr, a6g, p->geom.k > 0 && p->hi6[0], 0, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
       if (p->geom.k > 0 && p->hi6[0]) {
-        if (stamp_launch_hi6(p, at(ws, p->ws_hi6), scales, 2, yt[0], 0, 0, nullptr, 1.0f, st) != hipSuccess) return STAMP_ERR_DEVICE;
+        if (stamp_launch_hi6(p, dir != nullptr ? dir->h6 : at(ws, p->ws_hi6), scales, 2, yt[0], 0, 0, nullptr, 1.0f, st) != hipSuccess) return STAMP_ERR_DEVICE;
       } else if (p->geom.k > 0) {
         if (stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st) != hipSuccess) return STAMP_ERR_DEVICE;
         if (stamp_launch_merge_hi(p, ythi, p->hi_ksplit, yt[0], st) != hipSuccess) return STAMP_ERR_DEVICE;
@@ -415,9 +423,10 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
     // 4-bit rows straight to Y
     uint8_t* a6i = at(ws, p->ws_a6);
     const bool lo6 = p->geom.k < p->geom.s && p->engine == STAMP_GEMM_FP6;
-    if (convert_rows(p, q_hi, lo6 ? q_lo : nullptr, a6i, p->geom.k > 0 && p->hi6[0], 0, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
+    if (dir == nullptr &&
+        convert_rows(p, q_hi, lo6 ? q_lo : nullptr, a6i, p->geom.k > 0 && p->hi6[0], 0, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
     if (p->geom.k > 0 && p->hi6[0]) {
-      if (stamp_launch_hi6(p, at(ws, p->ws_hi6), scales, 1, Y, 0, 0, nullptr, 1.0f, st) != hipSuccess) return STAMP_ERR_DEVICE;
+      if (stamp_launch_hi6(p, dir != nullptr ? dir->h6 : at(ws, p->ws_hi6), scales, 1, Y, 0, 0, nullptr, 1.0f, st) != hipSuccess) return STAMP_ERR_DEVICE;
     } else if (p->geom.k > 0) {
       if (stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st) != hipSuccess) return STAMP_ERR_DEVICE;
       if (stamp_launch_hi_rows_out(p, ythi, Y, st, p->hi_ksplit) != hipSuccess) return STAMP_ERR_DEVICE;
@@ -431,8 +440,8 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
   const bool fused = p->fused_ok && !p->unfused;
   const bool own = codes_are_ours && own_top(p);
   uint8_t* a6 = at(ws, p->ws_a6);
-  const uint8_t* hi6 = at(ws, p->ws_hi6);
-  if (convert_rows(p, q_hi, p->engine == STAMP_GEMM_FP6 ? q_lo : nullptr, a6, p->hi6[own], own, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
+  const uint8_t* hi6 = dir != nullptr ? dir->h6 : at(ws, p->ws_hi6);
+  if (dir == nullptr && convert_rows(p, q_hi, p->engine == STAMP_GEMM_FP6 ? q_lo : nullptr, a6, p->hi6[own], own, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
   if (own) {
     if (launch_block_sums_own(p, q_hi, scales, ythi, P, hi6, st) != hipSuccess) return STAMP_ERR_DEVICE;
   } else if (p->hi6[0]) {
@@ -459,19 +468,39 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
 }
 
 // general path, steps 1-2: forward transform level by level, then the row quantizer
-stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, void* ws, hipStream_t st) {
+stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, void* ws, hipStream_t st,
+                            const StampDirect* dir = nullptr) {
   if (p->grp && (reinterpret_cast<uintptr_t>(X) & 15) == 0)
     return stamp_launch_grp_quant(p, X, q_hi, scales, reinterpret_cast<float*>(at(ws, p->ws_T[0])), st) == hipSuccess ? STAMP_OK
                                                                                                                      : STAMP_ERR_DEVICE;
   if (stamp_rag_quantizes(p, X))
-    return stamp_launch_actquant_rag(p, X, q_hi, q_lo, scales, st) == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
+    return stamp_launch_actquant_rag(p, X, q_hi, q_lo, scales, st, dir) == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
   float* const tb[3] = {reinterpret_cast<float*>(at(ws, p->ws_T[0])), reinterpret_cast<float*>(at(ws, p->ws_T[1])),
                         reinterpret_cast<float*>(at(ws, p->ws_T[2]))};
   float* T = nullptr;
   if (stamp_gen_forward(p, X, tb, &T, st) != hipSuccess) return STAMP_ERR_DEVICE;
   const hipError_t e = p->gen.group ? stamp_launch_quant_rows_grouped(p, T, q_hi, scales, st)
-                                    : stamp_launch_quant_rows_f32(p, T, q_hi, q_lo, scales, st);
+                                    : stamp_launch_quant_rows_f32(p, T, q_hi, q_lo, scales, st, dir);
   return e == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
+}
+
+// stamp_linear_forward: the quantizer writes the FP6 operands itself (no packed codes, no conversion pass) on the default route:
+// FP6 engine, fused inverse (or none), 8-bit rows through the kernel for few rows.  Its stores are 8 bytes of 24-byte
+// fragments where packed codes are 4-byte words of whole lines: that costs what the conversion pass costs without its
+// launch, so it pays on small activations only, and only where a workgroup has few rows to store one after another (row
+// quantizers, 1-D blocks of 8 and 16 tokens).  Layers, microseconds, conversion pass against direct: 2048 tokens 4096 ->
+// 11008, 3 levels, first token left out 96.2, 91.1; 11008 -> 4096, 3 levels 134.5, 130.5; DCT 4096 -> 4096 137, 131; 3 x 777
+// tokens 38.3, 35.1; but 1-D blocks of 32 (4096 -> 11008) 102.8, 103.3; 8 x 8 blocks (1152 -> 4608) 74.1, 76.1; 8 x 4096 tokens,
+// blocks of 64 382, 407.  Beyond 2^25 elements the launch no longer counts: 4 x 8192 tokens 4096 -> 4096, 3 levels 359, 359,
+// WHT 1772, 1806.
+bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
+  const StampGeom& g = p->geom;
+  if (!p->direct_ok || p->engine != STAMP_GEMM_FP6 || p->gen.group || (int64_t)g.B * g.s * g.d > (1 << 25)) return false;
+  if (p->rag.on ? p->rag.r > 4 : (!g.ident && (g.is2d || g.r > 4))) return false;
+  if (p->gen.kind != kGenNone || g.ident) return !p->rag.on || (rag_route(p, Y) && stamp_rag_quantizes(p, X) && p->hi6[0]);
+  if (!p->fused_ok || p->unfused) return false;
+  if (own_top(p)) return p->hi6[1];
+  return p->hi6[0] && (g.L > 0 || g.khi == g.k);
 }
 
 }  // namespace
@@ -650,19 +679,27 @@ stamp_status_t stamp_linear_forward(const stamp_plan_t* p, const void* X, void* 
   int8_t* q_hi = reinterpret_cast<int8_t*>(at(ws, p->ws_qhi));
   uint8_t* q_lo = at(ws, p->ws_qlo);
   float* scales = reinterpret_cast<float*>(at(ws, p->ws_scales));
+  StampDirect dir = {};
+  const bool direct = direct_route(p, X, Y);
+  if (direct) {
+    dir.a6 = at(ws, p->rag.on ? p->ws_ba6 : p->ws_a6);
+    dir.h6 = at(ws, p->ws_qhi);
+    dir.np = stamp_hi6_np(p, own_top(p));
+  }
+  const StampDirect* const dp = direct ? &dir : nullptr;
   if (p->gen.kind != kGenNone) {
     if (p->gen.group) {
       q_hi = reinterpret_cast<int8_t*>(at(ws, p->ws_codes8));
       scales = reinterpret_cast<float*>(at(ws, p->ws_scalesg));
     }
-    const stamp_status_t qs = gen_quantize(p, X, q_hi, q_lo, scales, ws, st);
-    return qs != STAMP_OK ? qs : forward_q(p, q_hi, q_lo, scales, Y, ws, st, true);
+    const stamp_status_t qs = gen_quantize(p, X, q_hi, q_lo, scales, ws, st, dp);
+    return qs != STAMP_OK ? qs : forward_q(p, q_hi, q_lo, scales, Y, ws, st, true, dp);
   }
   hipError_t e = stamp_launch_actquant(p, X, q_hi, q_lo, scales, reinterpret_cast<float*>(at(ws, p->ws_abot)),
                                        reinterpret_cast<uint32_t*>(at(ws, p->ws_rowmax)),
-                                       reinterpret_cast<uint32_t*>(at(ws, p->ws_gpart)), st);
+                                       reinterpret_cast<uint32_t*>(at(ws, p->ws_gpart)), st, 3, dp);
   if (e != hipSuccess) return STAMP_ERR_DEVICE;
-  return forward_q(p, q_hi, q_lo, scales, Y, ws, st, true);
+  return forward_q(p, q_hi, q_lo, scales, Y, ws, st, true, dp);
 }
 
 stamp_status_t stamp_linear_forward_static(const stamp_plan_t* p, const void* X, void* Y, void* hip_stream) {

@@ -231,6 +231,8 @@ int hi6_np(int M) { return M <= 32 ? 1 : 2; }
 int hi6_ng(const stamp_plan* p, int own) { return !p->geom.ident && !own && p->geom.L > 0 && p->geom.k > 64 ? 2 : 1; }
 }  // namespace
 
+int stamp_hi6_np(const stamp_plan* p, int own) { return hi6_np(hi6_rows(p, own)); }
+
 size_t stamp_hi6_bytes(const stamp_plan* p, int own) {
   const int M = hi6_rows(p, own), gr = 32 * hi6_np(M);
   return (size_t)((M + gr - 1) / gr) * (p->Kpad / 128) * (2 * hi6_np(M) * kBlock6);

@@ -191,6 +191,7 @@ struct stamp_plan {
   // the 8-bit rows through the kernel for few rows (stamp_hi6.hip), [1]: only the first khi rows of every sequence
   int32_t hi6[2];
   size_t ws_hi6;            // their operand
+  int32_t direct_ok;        // the quantizer may write the FP6 operands itself (the 8-bit rows' over ws_qhi)
   size_t ws_ba6, ws_bP;     // blocked form: the 4-bit rows in block order (over ws_T), the block sums (over ws_Yt)
   // workspace layout (byte offsets, 256-aligned)
   size_t ws_abot, ws_rowmax, ws_gpart, ws_qhi, ws_qlo, ws_scales, ws_ythi, ws_P, ws_a6, ws_ytlo, ws_total;
@@ -223,8 +224,14 @@ hipError_t stamp_launch_weight_quant(const stamp_plan* p, const float* W, hipStr
 int stamp_actquant_nsplit(const stamp_plan* p);
 // plans without top levels and without channel splits: the bottom kernel also quantizes the block sums (no k_top, no k_quant_hi)
 bool stamp_top_in_bottom(const stamp_plan* p);
+// dir: the codes leave as FP6 operands (4-bit rows, 8-bit rows) instead of in q_hi / q_lo, which are not written
+struct StampDirect {
+  uint8_t *a6, *h6;
+  int32_t np;
+};
 hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo,
-                                 float* scales, float* abot, uint32_t* rowmax, uint32_t* gpart, hipStream_t st, int part = 3);
+                                 float* scales, float* abot, uint32_t* rowmax, uint32_t* gpart, hipStream_t st, int part = 3,
+                                 const StampDirect* dir = nullptr);
 // mode: 0 = int32 accumulators in STaMP row order (debug), 1 = dequantized fp32 rows (hi -> Yt_hi
 // [hi_ksplit][B*k, N] partial rows, lo -> Yt_lo [B*s, N] physical rows), 2 = lo rows with fused in-block inverse -> Y,
 // 3 = lo rows of an identity plan: dequantized + bias -> Y.
@@ -259,6 +266,7 @@ hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_
 // [B*s][N] in STaMP order, 3: blocked form: block sums times norm -> out, the token left out + bias -> Y
 bool stamp_hi6_fits(const stamp_plan* p, int own);
 size_t stamp_hi6_bytes(const stamp_plan* p, int own);
+int stamp_hi6_np(const stamp_plan* p, int own);
 StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own);
 hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float* scales, int mode, void* out, int ld_out, int own,
                             void* Y, float norm, hipStream_t st);
@@ -294,8 +302,10 @@ hipError_t stamp_gen_forward(const stamp_plan* p, const void* X, float* const (&
 hipError_t stamp_gen_inverse(const stamp_plan* p, float* const (&buf)[3], int ncols, const float* bias, void* Y, hipStream_t st);
 // blocked form: X -> codes and scales in STaMP order in one pass; false where the kernel does not take the plan or X
 bool stamp_rag_quantizes(const stamp_plan* p, const void* X);
-hipError_t stamp_launch_actquant_rag(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st);
-hipError_t stamp_launch_quant_rows_f32(const stamp_plan* p, const float* T, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st);
+hipError_t stamp_launch_actquant_rag(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st,
+                                     const StampDirect* dir = nullptr);
+hipError_t stamp_launch_quant_rows_f32(const stamp_plan* p, const float* T, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st,
+                                       const StampDirect* dir = nullptr);
 hipError_t stamp_launch_quant_rows_grouped(const stamp_plan* p, const float* T, int8_t* codes, float* scales, hipStream_t st);
 // per-block scales, blocked 2-D Haar (p->grp): X -> codes and scales in STaMP order (abot: [B*k][d] fp32 scratch), and from
 // there to Y
