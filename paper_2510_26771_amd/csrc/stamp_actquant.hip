@@ -46,7 +46,7 @@ namespace {
 constexpr int kTopCh = 32;
 
 // asym: the partial maxima are order keys of max t; those of max -t follow npart words further on.
-// L = number of top levels (0: the block sums are only normalised).
+// L = number of top levels, at least 1 (without any the bottom kernel has finished the block sums).
 __global__ __launch_bounds__(256) void k_top(float* __restrict__ abot, uint32_t* __restrict__ rowmax_part, int k, int d,
                                              int is2d, int G, int r_bottom, int L, int asym, size_t npart) {
   extern __shared__ float s_buf[];  // [k][kTopCh + 1]
@@ -55,23 +55,19 @@ __global__ __launch_bounds__(256) void k_top(float* __restrict__ abot, uint32_t*
   const int stride = kTopCh + 1;
   const bool cact = (c_base + ch) < d;
   float* base = abot + (size_t)b * k * d;
-  // Plans without top levels may have more than 256 block sums per sequence: nothing is transformed, so every
-  // workgroup (blockIdx.z) takes its own 256 rows [q0, q0 + kq); with top levels kq = k.
-  const int q0 = (int)blockIdx.z * 256, kq = min(k - q0, 256);
-  base += (size_t)q0 * d;
   // four independent loads in flight per thread before the first LDS write (one load per loop trip would
   // pay one memory latency per row)
-  for (int j0 = grp; j0 < kq; j0 += 4 * ngrp) {
+  for (int j0 = grp; j0 < k; j0 += 4 * ngrp) {
     float v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int j = j0 + u * ngrp;
-      v[u] = (cact && j < kq) ? base[(size_t)j * d + c_base + ch] : 0.0f;
+      v[u] = (cact && j < k) ? base[(size_t)j * d + c_base + ch] : 0.0f;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int j = j0 + u * ngrp;
-      if (j < kq) s_buf[j * stride + ch] = v[u];
+      if (j < k) s_buf[j * stride + ch] = v[u];
     }
   }
   __syncthreads();
@@ -108,7 +104,7 @@ __global__ __launch_bounds__(256) void k_top(float* __restrict__ abot, uint32_t*
     }
   }
   // normalise, scatter to STaMP order, row absmax over this slice
-  for (int q = grp; q < kq; q += ngrp) {
+  for (int q = grp; q < k; q += ngrp) {
     int e, lvl_top;  // level counted within the top part (1 = first top level); slot 0 gets the deepest
     if (!is2d) {
       e = stamp_top_slot_1d(q, k, L, &lvl_top);
@@ -116,7 +112,6 @@ __global__ __launch_bounds__(256) void k_top(float* __restrict__ abot, uint32_t*
       const int y = q / G, x = q - y * G;
       e = stamp_top_slot_2d(y, x, G, L, &lvl_top);
     }
-    // (q0 > 0 only without top levels, where slot = position: e = q, counted from q0 like `base`)
     const int level = r_bottom + lvl_top;
     const float nrm = is2d ? ldexpf(1.0f, -level) : haar_norm(level);
     const float t = __fmul_rn(s_buf[q * stride + ch], nrm);
@@ -131,7 +126,7 @@ __global__ __launch_bounds__(256) void k_top(float* __restrict__ abot, uint32_t*
       yv = (uint32_t)__shfl_xor((int)x, 16, 64); x = max(x, yv);
       return x;
     };
-    const size_t slot = ((size_t)b * k + q0 + e) * gridDim.x + blockIdx.x;
+    const size_t slot = ((size_t)b * k + e) * gridDim.x + blockIdx.x;
     if (!asym) {
       const uint32_t x = max32(absbits(t));
       if (ch == 0) rowmax_part[slot] = x;
@@ -145,12 +140,11 @@ __global__ __launch_bounds__(256) void k_top(float* __restrict__ abot, uint32_t*
 }
 
 // one workgroup per 8-bit row.  asym: min-max form, the stored code is code - 128 and the offset z goes
-// zeros_off floats behind the row's scale.
-// hi6.p != nullptr: the 8-bit rows (all of them, or the first khi of a sequence) and the 4-bit ones (a6) leave as FP6 operands.
+// zeros_off floats behind the row's scale.  hi6.p != nullptr: the rows leave as FP6 operand.
 __global__ __launch_bounds__(256) void k_quant_hi(const float* __restrict__ ttop, const uint32_t* __restrict__ rowmax_part,
                                                   int nslices, int8_t* __restrict__ q_hi, float* __restrict__ scales,
-                                                  int k, int khi, int d, int s, int R, int asym, size_t npart,
-                                                  size_t zeros_off, uint8_t* __restrict__ q_lo, int Kpad, Hi6Out hi6) {
+                                                  int k, int d, int s, int R, int asym, size_t npart,
+                                                  size_t zeros_off, int Kpad, Hi6Out hi6) {
   __shared__ uint32_t s_red[8];
   const int p = blockIdx.x, b = blockIdx.y;
   {
@@ -167,65 +161,37 @@ __global__ __launch_bounds__(256) void k_quant_hi(const float* __restrict__ ttop
   }
   const uint32_t mp = max(max(s_red[0], s_red[1]), max(s_red[2], s_red[3]));
   const uint32_t mn = max(max(s_red[4], s_red[5]), max(s_red[6], s_red[7]));
-  // rows beyond the first khi are 4-bit rows (same data path, codes held as int8)
-  const bool row8 = p < khi;
-  const float qmax_s = row8 ? 127.0f : 7.0f, qmax_u = row8 ? 255.0f : 15.0f;
   float scale = 0.0f, inv = 0.0f, z = 0.0f;
   if (!asym) {
     const float a = __uint_as_float(mp);
     if (a > 0.0f) {
-      scale = __fdiv_rn(a, qmax_s);
-      inv = __fdiv_rn(qmax_s, a);
+      scale = __fdiv_rn(a, 127.0f);
+      inv = __fdiv_rn(127.0f, a);
     }
   } else {
-    asym_params(fkey_inv(mp), fkey_inv(mn), qmax_u, scale, inv, z);
+    asym_params(fkey_inv(mp), fkey_inv(mn), 255.0f, scale, inv, z);
   }
   if (threadIdx.x == 0) {
     scales[(size_t)b * s + (size_t)p * R] = scale;
     if (asym) scales[zeros_off + (size_t)b * s + (size_t)p * R] = z;
   }
-  const float qlo = asym ? 0.0f : -qmax_s, qhi = asym ? qmax_u : qmax_s, shift = asym ? (row8 ? 128.0f : 8.0f) : 0.0f;
+  const float qlo = asym ? 0.0f : -127.0f, qhi = asym ? 255.0f : 127.0f, shift = asym ? 128.0f : 0.0f;
+  auto code = [&](float v) { return (int)(fminf(fmaxf(__fadd_rn(rintf(__fmul_rn(v, inv)), z), qlo), qhi) - shift); };
   const float* src = ttop + ((size_t)b * k + p) * d;
   if (hi6.p != nullptr) {
-    const size_t row = (size_t)b * s + (size_t)p * R;
     for (int cb = 0; cb < d; cb += 256 * 8) {  // whole quads stay together: d is a multiple of 32
       const int c = cb + (int)threadIdx.x * 8, cl = min(c, d - 8);
       const float4 t0 = *reinterpret_cast<const float4*>(src + cl), t1 = *reinterpret_cast<const float4*>(src + cl + 4);
-      const float v[8] = {t0.x, t0.y, t0.z, t0.w, t1.x, t1.y, t1.z, t1.w};
-      int qi[8];
-      uint32_t w4 = 0;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        float q = __fadd_rn(rintf(__fmul_rn(v[i], inv)), z);
-        qi[i] = (int)(fminf(fmaxf(q, qlo), qhi) - shift);
-        w4 |= ((uint32_t)qi[i] & 0xFu) << (4 * i);
-      }
-      if (row8) {
-        store_hi48(hi6, b * khi + p, Kpad >> 7, qi, c, c < d);
-      } else {
-        uint32_t w0, w1;
-        nib8_to_48(w4, w0, w1);
-        store48(q_lo + a6_row(row, Kpad >> 7) + off48(c, kStageA6), w0, w1, c, c < d);
-      }
+      const int qi[8] = {code(t0.x), code(t0.y), code(t0.z), code(t0.w), code(t1.x), code(t1.y), code(t1.z), code(t1.w)};
+      store_hi48(hi6, b * k + p, Kpad >> 7, qi, c, c < d);
     }
     return;
   }
   int8_t* dst = q_hi + ((size_t)b * k + p) * d;
   for (int c = threadIdx.x * 4; c < d; c += 256 * 4) {
     const float4 t = *reinterpret_cast<const float4*>(src + c);
-    const float v[4] = {t.x, t.y, t.z, t.w};
-    uint32_t w = 0, w4 = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float q = __fadd_rn(rintf(__fmul_rn(v[i], inv)), z);
-      q = fminf(fmaxf(q, qlo), qhi) - shift;
-      w |= ((uint32_t)((int)q) & 0xFFu) << (8 * i);
-      w4 |= ((uint32_t)((int)q) & 0xFu) << (4 * i);
-    }
-    *reinterpret_cast<uint32_t*>(dst + c) = w;
-    // plans without top levels: a 4-bit row also goes, packed, to its block's row 0 of q_lo (see finish_top_row)
-    if (q_lo != nullptr && !row8)
-      *reinterpret_cast<uint16_t*>(q_lo + stamp_qlo_offset((size_t)b * s + (size_t)p * R, c, Kpad)) = (uint16_t)w4;
+    *reinterpret_cast<uint32_t*>(dst + c) = ((uint32_t)code(t.x) & 0xFFu) | (((uint32_t)code(t.y) & 0xFFu) << 8) |
+                                            (((uint32_t)code(t.z) & 0xFFu) << 16) | ((uint32_t)code(t.w) << 24);
   }
 }
 
@@ -368,7 +334,7 @@ hipError_t stamp_launch_quant_rows_f32(const stamp_plan* p, const float* T, int8
 }
 
 bool stamp_top_in_bottom(const stamp_plan* p) {
-  return !p->geom.ident && p->geom.L == 0 && stamp_actquant_nsplit(p) == 1;
+  return !p->geom.ident && p->geom.L == 0;
 }
 
 int stamp_actquant_nsplit(const stamp_plan* p) {
@@ -399,7 +365,8 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
   sp.nsplit = stamp_actquant_nsplit(p);
   sp.c_split = (sp.nsplit == 1) ? g.d : (((g.d + sp.nsplit - 1) / sp.nsplit + 511) / 512) * 512;
   if (sp.nsplit > 1 && gpart == nullptr) return hipErrorInvalidValue;
-  // no top levels: the bottom kernel finishes the block sums itself (one launch instead of three)
+  // No top levels: the bottom kernel finishes the block sums itself, with split channels too (their maxima travel with the
+  // other rows').  Bottom kernel, k_top and k_quant_hi, 256 block sums x 11008 channels: 31.1 + 19.3 + 8.4 us; now 32.7.
   const bool top_in_bottom = stamp_top_in_bottom(p);
   sp.q_hi = top_in_bottom ? q_hi : nullptr;
   sp.khi = g.khi;
@@ -455,15 +422,14 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (!(part & 2) || top_in_bottom) return hipSuccess;
-  if (g.k > 256 && g.L != 0) return hipErrorInvalidValue;  // plan creation admits that many top rows only without top levels
-  const size_t lds = (size_t)(g.k < 256 ? g.k : 256) * (kTopCh + 1) * sizeof(float);
+  if (g.k > 256) return hipErrorInvalidValue;  // plan creation admits that many top rows only without top levels
+  const size_t lds = (size_t)g.k * (kTopCh + 1) * sizeof(float);
   const int nslices = (g.d + kTopCh - 1) / kTopCh;
   const size_t npart = (size_t)g.B * g.k * nslices;
-  hipLaunchKernelGGL(k_top, dim3(nslices, g.B, (g.k + 255) / 256), dim3(256), lds, st, abot, rowmax, g.k, g.d, g.is2d, g.G, g.r, g.L, g.asym,
-                     npart);
+  hipLaunchKernelGGL(k_top, dim3(nslices, g.B), dim3(256), lds, st, abot, rowmax, g.k, g.d, g.is2d, g.G, g.r, g.L, g.asym, npart);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_quant_hi, dim3(g.k, g.B), dim3(256), 0, st, abot, rowmax, nslices, q_hi, scales, g.k, g.khi, g.d, g.s, g.R,
-                     g.asym, npart, zeros_off, g.L == 0 ? q_lo : nullptr, p->Kpad, sp.hi6);
+  hipLaunchKernelGGL(k_quant_hi, dim3(g.k, g.B), dim3(256), 0, st, abot, rowmax, nslices, q_hi, scales, g.k, g.d, g.s, g.R, g.asym,
+                     npart, zeros_off, p->Kpad, sp.hi6);
   return hipGetLastError();
 }

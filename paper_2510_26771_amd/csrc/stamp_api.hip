@@ -489,7 +489,7 @@ stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, ui
 // fragments where packed codes are 4-byte words of whole lines: that costs what the conversion pass costs without its
 // launch, so it pays on small activations only, and only where a workgroup has few rows to store one after another (row
 // quantizers, 1-D blocks of 8 and 16 tokens).  Layers, microseconds, conversion pass against direct: 2048 tokens 4096 ->
-// 11008, 3 levels, first token left out 96.2, 91.1; 11008 -> 4096, 3 levels 134.5, 130.5; DCT 4096 -> 4096 137, 131; 3 x 777
+// 11008, 3 levels, first token left out 96.2, 91.1; 11008 -> 4096, 3 levels (block sums still by kernels of their own) 134.5, 130.5; DCT 4096 -> 4096 137, 131; 3 x 777
 // tokens 38.3, 35.1; but 1-D blocks of 32 (4096 -> 11008) 102.8, 103.3; 8 x 8 blocks (1152 -> 4608) 74.1, 76.1; 8 x 4096 tokens,
 // blocks of 64 382, 407.  Beyond 2^25 elements the launch no longer counts: 4 x 8192 tokens 4096 -> 4096, 3 levels 359, 359,
 // WHT 1772, 1806.

@@ -374,28 +374,50 @@ __device__ __forceinline__ void flush_rows(float (&rowv)[NR][8], MetaFn meta, in
 // word of it), which no other coefficient uses: the 4-bit rows' GEMM can then take the block sum from its own rows.
 // RAG: 4-bit rows have no place in q_hi.
 // OUT6: q_lo_row is this thread's place in the FP6 operand, the 8-bit rows go to hi6 (row hi_row).
-template <bool IS2D, bool ASYM, bool RAG = false, bool OUT6 = false>
+// Channel split: row 0 of a block's maxima is free (no bottom coefficient has position 0) and holds the block sum's:
+// PASS 1 leaves its part in part_max[0] and [part_neg], PASS 2 reads the whole from s_amax[0] and [kMaxBlockRows].
+template <bool IS2D, bool ASYM, bool RAG = false, bool OUT6 = false, int PASS = 0>
 __device__ __forceinline__ void finish_top_row(const float (&top)[8], int level, uint32_t* part /* >= 32 words, free */,
                                                int8_t* q_hi_row, uint8_t* q_lo_row, float* scale_out, size_t zeros_off,
-                                               bool row8, bool active, int tid, Hi6Out hi6 = Hi6Out{}, int hi_row = 0, int KT = 0, int c0 = 0) {
+                                               bool row8, bool active, int tid, Hi6Out hi6 = Hi6Out{}, int hi_row = 0, int KT = 0, int c0 = 0,
+                                               uint32_t* part_max = nullptr, size_t part_neg = 0, const uint32_t* s_amax = nullptr) {
   const int lane = tid & 63, wave = tid >> 6, nw = (int)(blockDim.x >> 6);
   const float nrm = IS2D ? ldexpf(1.0f, -level) : haar_norm(level);
   float t[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c) t[c] = __fmul_rn(top[c], nrm);
-  uint32_t pos, neg = 0u;
-  if constexpr (ASYM) {
-    row_posneg_bits(t, pos, neg);
-    if (!active) pos = neg = 0u;
-  } else {
-    pos = row_absmax_bits(t);
-  }
-  pos = wave_max_u32(pos);
-  neg = wave_max_u32(neg);
-  if (lane == 0) { part[wave] = pos; part[16 + wave] = neg; }
-  __syncthreads();
   uint32_t mp = 0u, mn = 0u;
-  for (int i = 0; i < nw; ++i) { mp = max(mp, part[i]); mn = max(mn, part[16 + i]); }
+  if constexpr (PASS == 2) {
+    mp = s_amax[0];
+    mn = s_amax[kMaxBlockRows];
+  } else {
+    uint32_t pos = 0u, neg = 0u;
+    if constexpr (PASS == 1) {  // maxima of the patterns, as the top part's kernel takes them: a NaN is the largest
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        pos = max(pos, ASYM ? fkey(t[c]) : absbits(t[c]));
+        if constexpr (ASYM) neg = max(neg, fkey(-t[c]));
+      }
+      if (ASYM && !active) pos = neg = 0u;
+    } else if constexpr (ASYM) {
+      row_posneg_bits(t, pos, neg);
+      if (!active) pos = neg = 0u;
+    } else {
+      pos = row_absmax_bits(t);
+    }
+    pos = wave_max_u32(pos);
+    neg = wave_max_u32(neg);
+    if (lane == 0) { part[wave] = pos; part[16 + wave] = neg; }
+    __syncthreads();
+    for (int i = 0; i < nw; ++i) { mp = max(mp, part[i]); mn = max(mn, part[16 + i]); }
+    if constexpr (PASS == 1) {
+      if (tid == 0) {
+        part_max[0] = mp;
+        if constexpr (ASYM) part_max[part_neg] = mn;
+      }
+      return;
+    }
+  }
   const float qmax = ASYM ? (row8 ? 255.0f : 15.0f) : (row8 ? 127.0f : 7.0f);
   float scale = 0.0f, inv = 0.0f, z = 0.0f;
   if constexpr (ASYM) {
@@ -407,7 +429,7 @@ __device__ __forceinline__ void finish_top_row(const float (&top)[8], int level,
       inv = __fdiv_rn(qmax, a);
     }
   }
-  if (tid == 0) {
+  if (tid == 0 && (PASS == 0 || blockIdx.z == 0)) {
     scale_out[0] = scale;
     if constexpr (ASYM) scale_out[zeros_off] = z;
   }
@@ -654,14 +676,13 @@ __global__ __launch_bounds__(1024) void k_bottom1d(const void* __restrict__ X, u
   run1d<RLOG, BF16, ASYM, PASS, false, OUT6>(std::make_integer_sequence<int, R / 4>{}, X_blk, x_off, row_bytes, stage, nthreads, active,
                                              tid, pend, top, s_max, q_blk, q_off, scales + row0, zeros_off, gpart_blk,
                                              (size_t)sp.nsplit * sp.part_rows, s_amax, PASS == 0 || blockIdx.z == 0, RagArgs{}, row0 & 255);
-  if constexpr (PASS == 0) {
-    if (sp.q_hi != nullptr) {
-      // s_max[R/4 & 1] was last used two steps ago: every thread has passed a barrier since
-      finish_top_row<false, ASYM, false, OUT6>(top, RLOG, &s_max[(R / 4) & 1][0], sp.q_hi + ((size_t)b * k + j) * d + c0,
-                                               (OUT6 ? q_lo + a6_row(row0, Kpad >> 7) : q_blk) + q_off, scales + row0, zeros_off, j < sp.khi,
-                                               active, tid, sp.hi6, b * sp.khi + j, Kpad >> 7, c0);
-      return;
-    }
+  if (sp.q_hi != nullptr) {
+    // s_max[R/4 & 1] was last used two steps ago: every thread has passed a barrier since
+    finish_top_row<false, ASYM, false, OUT6, PASS>(top, RLOG, &s_max[(R / 4) & 1][0], sp.q_hi + ((size_t)b * k + j) * d + c0,
+                                                   (OUT6 ? q_lo + a6_row(row0, Kpad >> 7) : q_blk) + q_off, scales + row0, zeros_off,
+                                                   j < sp.khi, active, tid, sp.hi6, b * sp.khi + j, Kpad >> 7, c0, gpart_blk,
+                                                   (size_t)sp.nsplit * sp.part_rows, s_amax);
+    return;
   }
   if (active && PASS != 1) {
     float4* o = reinterpret_cast<float4*>(abot + ((size_t)b * k + j) * d + c0);
@@ -846,13 +867,12 @@ __global__ __launch_bounds__(512) void k_bottom2d(const void* __restrict__ X, ui
   run2d<RLOG, BF16, ASYM, PASS>(std::make_integer_sequence<int, (g == 4 ? 1 : 4)>{}, X, tok0 * d + c0, gridW, d, c0, active,
                                       tid, pend, top, s_max, q_blk, q_off, scales + prow0, zeros_off, gpart_blk,
                                       (size_t)sp.nsplit * sp.part_rows, s_amax, PASS == 0 || blockIdx.z == 0);
-  if constexpr (PASS == 0) {
-    if (sp.q_hi != nullptr) {
-      constexpr int nsteps = (g == 4) ? 1 : 4;
-      finish_top_row<true, ASYM>(top, RLOG, &s_max[nsteps & 1][0], sp.q_hi + ((size_t)b * k + j) * d + c0,
-                                              q_blk + q_off, scales + prow0, zeros_off, j < sp.khi, active, tid);
-      return;
-    }
+  if (sp.q_hi != nullptr) {
+    constexpr int nsteps = (g == 4) ? 1 : 4;
+    finish_top_row<true, ASYM, false, false, PASS>(top, RLOG, &s_max[nsteps & 1][0], sp.q_hi + ((size_t)b * k + j) * d + c0, q_blk + q_off,
+                                                   scales + prow0, zeros_off, j < sp.khi, active, tid, Hi6Out{}, 0, 0, c0, gpart_blk,
+                                                   (size_t)sp.nsplit * sp.part_rows, s_amax);
+    return;
   }
   if (active && PASS != 1) {
     float4* o = reinterpret_cast<float4*>(abot + ((size_t)b * k + j) * d + c0);

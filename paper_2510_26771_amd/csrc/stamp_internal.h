@@ -222,7 +222,7 @@ hipError_t stamp_launch_weight_quant(const stamp_plan* p, const float* W, hipStr
 // scales: [B*s] scales, followed by [B*s] offsets z for asymmetric plans
 // gpart: [2][nsplit][B*s] partial row maxima when the channels are split over workgroups (nsplit > 1), else unused
 int stamp_actquant_nsplit(const stamp_plan* p);
-// plans without top levels and without channel splits: the bottom kernel also quantizes the block sums (no k_top, no k_quant_hi)
+// plans without top levels: the bottom kernel also quantizes the block sums (no k_top, no k_quant_hi)
 bool stamp_top_in_bottom(const stamp_plan* p);
 // dir: the codes leave as FP6 operands (4-bit rows, 8-bit rows) instead of in q_hi / q_lo, which are not written
 struct StampDirect {

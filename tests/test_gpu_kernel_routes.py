@@ -149,3 +149,17 @@ TILES = [_tiles("t256_ident_odd_rows", 8193, 2050, 64, xform="identity", levels=
 @pytest.mark.parametrize("w", TILES, ids=[w.name for w in TILES])
 def test_both_gemm_tile_sizes(w):
     tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16" if w.d_out % 4 else "f32", check_acc=False)
+
+
+# ---- split channels without top levels: the bottom kernel's two passes carry the block sums' maxima too (a last split of one
+# channel group, both quantizer forms, every block sum at 8 bits or only some, one block length of the packed codes)
+SPLIT_TOP = [_wl("split_top_f32_asym", seq_len=64, d_in=4128, k_hi=3, act_quant="asym", mean_shift=0.5, seed=601),
+             _wl("split_top_all_8bit", seq_len=128, d_in=8224, k_hi=8, levels=4, x_dtype="bf16", batch=2, seed=602),
+             _wl("split_top_32_asym", seq_len=256, d_in=4640, k_hi=5, levels=5, act_quant="asym", mean_shift=-0.3, seed=603),
+             _wl("split_top_grid_all", seq_len=64, d_in=8192, d_out=66, k_hi=4, levels=2, xform="haar2d", grid_h=8, grid_w=8,
+                 corr_len=2.0, x_dtype="bf16", seed=604)]
+
+
+@pytest.mark.parametrize("w", SPLIT_TOP, ids=[w.name for w in SPLIT_TOP])
+def test_split_channels_without_top_levels(w):
+    tl.full_case(w, with_bias=True)
