@@ -8,7 +8,7 @@
 // when there are more than 64 rows: each group takes 64), and only their sums meet in LDS.  The sums are whole numbers and
 // stay whole: fp32 holds each FP6 sum exactly, 16 h + l and the sum over the waves are int32.
 // Measured (rows x depth x d_out, microseconds; before: int8 GEMM + top levels of the inverse as a kernel of its own):
-// 64 x 4096 x 11008: 17.6 (16.1 + 10.1), 128 x 4096 x 4096: 12.8 (17.8 + 11.9), 64 x 11008 x 4096: 18.9 (19.1 + 4.8),
+// 64 x 4096 x 11008: 17.4 (16.1 + 10.1), 128 x 4096 x 4096: 11.9 (17.8 + 11.9), 64 x 11008 x 4096: 16.9 (19.1 + 4.8),
 // 128 x 1152 x 4608: 8.2 (15.7 + 5.2), 512 x 4096 x 4096: 37 (34 + 15).
 #include "stamp_hi6.h"
 
@@ -34,8 +34,11 @@ struct Hi6Args {
 };
 
 // GRP: one scale per 64 channels (a half of a K step) and row / column: the sums are rescaled half by half, s_part holds fp32
-template <int NP, bool GRP>
-__global__ __launch_bounds__(512, 4) void k_hi6(const Hi6Args h) {
+// AHEAD: the next step's operands are in flight while a step is multiplied.  That takes twice the registers, so it is for
+// launches that leave no CU a second workgroup: 64 x 11008 x 4096 (128 workgroups) 16.9 us against 18.9, 128 x 4096 x 4096
+// (256) 11.9 against 12.8, but 64 x 4096 x 11008 (344) 21.4 against 17.4.
+template <int NP, bool GRP, bool AHEAD>
+__global__ __launch_bounds__(512, AHEAD ? 2 : 4) void k_hi6(const Hi6Args h) {
   const GemmArgs& a = h.a;
   const StampGeom& g = a.g;
   constexpr int C = 32, RW = 32 * NP;  // columns, rows of a wave
@@ -64,9 +67,36 @@ __global__ __launch_bounds__(512, 4) void k_hi6(const Hi6Args h) {
     compute_row_info<AccHi6, 1>(a, m0, tid, fac, dst, rz);
     write_row_info(s_info, tid, fac, dst, rz);
   }
-  // at most 128 registers: four waves per SIMD (two workgroups) hide each other's loads (64 x 4096 x 11008: 17.6 us; two
-  // waves per SIMD, each with the next step's operands in flight in registers: 21.4)
-  for (int kt = kt0; kt < kt1; ++kt) {
+  // Not AHEAD: at most 128 registers, four waves per SIMD (two workgroups per CU) hide each other's loads.
+  if constexpr (AHEAD) {
+    Frag6 fb[2], fa[2][2 * NP];
+    auto fetch = [&](int kt, Frag6& b, Frag6 (&f)[2 * NP]) {
+      b.load(pb + (size_t)kt * kStageB6);
+#pragma unroll
+      for (int i = 0; i < 2 * NP; ++i) f[i].load(pa + (size_t)kt * (2 * NP * kBlock6) + i * kBlock6);
+    };
+    auto multiply = [&](const Frag6& b, const Frag6 (&f)[2 * NP]) {
+#pragma unroll
+      for (int i = 0; i < 2 * NP; ++i) {
+        acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[i].h0(), b.h0(), acc[i], 2, 2, 0, 0, 0, 0);
+        acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[i].h1(), b.h1(), acc[i], 2, 2, 0, 0, 0, 0);
+      }
+    };
+    int kt = kt0;
+    if (kt < kt1) {
+      fetch(kt, fb[0], fa[0]);
+      for (; kt + 2 < kt1; kt += 2) {
+        fetch(kt + 1, fb[1], fa[1]);
+        multiply(fb[0], fa[0]);
+        fetch(kt + 2, fb[0], fa[0]);
+        multiply(fb[1], fa[1]);
+      }
+      if (kt + 1 < kt1) fetch(kt + 1, fb[1], fa[1]);
+      multiply(fb[0], fa[0]);
+      if (kt + 1 < kt1) multiply(fb[1], fa[1]);
+    }
+  }
+  for (int kt = AHEAD ? kt1 : kt0; kt < kt1; ++kt) {
     Frag6 fb, fa[2 * NP];
     fb.load(pb + (size_t)kt * kStageB6);
 #pragma unroll
@@ -209,14 +239,14 @@ __global__ __launch_bounds__(512, 4) void k_hi6(const Hi6Args h) {
   }
 }
 
-template <int NP, bool GRP>
+template <int NP, bool GRP, bool AHEAD>
 hipError_t launch(const Hi6Args& h, hipStream_t st) {
   constexpr size_t lds = (size_t)8 * 32 * NP * 32 * sizeof(int);
   static size_t lds_done[kStampMaxDevices] = {};
-  const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_hi6<NP, GRP>), lds, lds_done);
+  const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_hi6<NP, GRP, AHEAD>), lds, lds_done);
   if (e != hipSuccess) return e;
   const int rows = 32 * NP * h.ng;
-  hipLaunchKernelGGL((k_hi6<NP, GRP>), dim3((h.a.N + 63) / 64 * 2, (h.a.M + rows - 1) / rows), dim3(512), lds, st, h);
+  hipLaunchKernelGGL((k_hi6<NP, GRP, AHEAD>), dim3((h.a.N + 63) / 64 * 2, (h.a.M + rows - 1) / rows), dim3(512), lds, st, h);
   return hipGetLastError();
 }
 
@@ -280,7 +310,9 @@ hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float*
   h.mode = mode;
   h.norm = norm;
   h.Y = Y;
-  return h.np == 1 ? launch<1, false>(h, st) : launch<2, false>(h, st);
+  // workgroups up to one per CU (256): the rule of AHEAD
+  if (h.np == 2 && (int64_t)((h.a.N + 63) / 64 * 2) * ((h.a.M + 64 * h.ng - 1) / (64 * h.ng)) <= 256) return launch<2, false, true>(h, st);
+  return h.np == 1 ? launch<1, false, false>(h, st) : launch<2, false, false>(h, st);
 }
 
 hipError_t stamp_launch_hi6_grp(const stamp_plan* p, const uint8_t* h6, const float* sh, float* P, int own, hipStream_t st) {
@@ -297,5 +329,5 @@ hipError_t stamp_launch_hi6_grp(const stamp_plan* p, const uint8_t* h6, const fl
   h.norm = 1.0f;
   h.sa = sh;
   h.sw = p->swg6_dev;
-  return h.np == 1 ? launch<1, true>(h, st) : launch<2, true>(h, st);
+  return h.np == 1 ? launch<1, true, false>(h, st) : launch<2, true, false>(h, st);
 }
