@@ -337,6 +337,11 @@ bool stamp_top_in_bottom(const stamp_plan* p) {
   return !p->geom.ident && p->geom.L == 0;
 }
 
+bool stamp_bottom_quads(const stamp_plan* p) {
+  const StampGeom& g = p->geom;
+  return !g.ident && g.is2d && g.r == 3 && g.d <= 1536 && g.B * g.k <= 512;
+}
+
 int stamp_actquant_nsplit(const stamp_plan* p) {
   const StampGeom& g = p->geom;
   if (g.ident) return 1;
@@ -371,8 +376,9 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
   sp.q_hi = top_in_bottom ? q_hi : nullptr;
   sp.khi = g.khi;
   sp.hi6 = hi6_out(dir);
+  const bool quads = stamp_bottom_quads(p);
   if (dir != nullptr) {
-    if (g.is2d) return hipErrorInvalidValue;  // direct_route
+    if (g.is2d && !quads) return hipErrorInvalidValue;  // direct_route
     q_lo = dir->a6;
   }
   const int nthreads = ((sp.c_split / 8 + 63) / 64) * 64;
@@ -390,6 +396,14 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
   do {                                                                                                    \
     if (sp.nsplit == 1) { LAUNCH2D__(RL, BF, AS, 0); }                                                    \
     else { LAUNCH2D__(RL, BF, AS, 1); LAUNCH2D__(RL, BF, AS, 2); }                                        \
+  } while (0)
+#define LAUNCHQ_(BF, AS, O6)                                                                              \
+  hipLaunchKernelGGL((k_bottom2d_quads<BF, AS, O6>), grid, dim3(4 * nthreads), (size_t)4 * nthreads * 32, st, X, q_lo, scales, abot, \
+                     g.s, g.d, g.G, g.gridW, p->Kpad, zeros_off, sp)
+#define LAUNCHQ(BF, AS)                                                                                   \
+  do {                                                                                                    \
+    if (dir != nullptr) LAUNCHQ_(BF, AS, true);                                                           \
+    else LAUNCHQ_(BF, AS, false);                                                                         \
   } while (0)
 #define LAUNCH2D(RL)                                                                                      \
   do {                                                                                                    \
@@ -409,7 +423,10 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
     }
   } else {
     if (nthreads > 512) return hipErrorInvalidValue;
-    switch (g.r) {
+    if (quads) {
+      if (g.asym) { if (g.x_bf16) LAUNCHQ(true, true); else LAUNCHQ(false, true); }
+      else { if (g.x_bf16) LAUNCHQ(true, false); else LAUNCHQ(false, false); }
+    } else switch (g.r) {
       case 2: LAUNCH2D(2); break;
       case 3: LAUNCH2D(3); break;
       default: return hipErrorInvalidValue;
@@ -419,6 +436,8 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
 #undef LAUNCH2D
 #undef LAUNCH2D_
 #undef LAUNCH2D__
+#undef LAUNCHQ
+#undef LAUNCHQ_
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (!(part & 2) || top_in_bottom) return hipSuccess;

@@ -488,15 +488,15 @@ stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, ui
 // FP6 engine, fused inverse (or none), 8-bit rows through the kernel for few rows.  Its stores are 8 bytes of 24-byte
 // fragments where packed codes are 4-byte words of whole lines: that costs what the conversion pass costs without its
 // launch, so it pays on small activations only, and only where a workgroup has few rows to store one after another (row
-// quantizers, 1-D blocks of 8 and 16 tokens).  Layers, microseconds, conversion pass against direct: 2048 tokens 4096 ->
+// quantizers, 1-D blocks of 8 and 16 tokens, 8 x 8 blocks by sub-blocks).  Layers, microseconds, conversion pass against direct: 2048 tokens 4096 ->
 // 11008, 3 levels, first token left out 96.2, 91.1; 11008 -> 4096, 3 levels (block sums still by kernels of their own) 134.5, 130.5; DCT 4096 -> 4096 137, 131; 3 x 777
-// tokens 38.3, 35.1; but 1-D blocks of 32 (4096 -> 11008) 102.8, 103.3; 8 x 8 blocks (1152 -> 4608) 74.1, 76.1; 8 x 4096 tokens,
+// tokens 38.3, 35.1; but 1-D blocks of 32 (4096 -> 11008) 102.8, 103.3; 8 x 8 blocks one sub-block after another (1152 -> 4608) 74.1, 76.1; 8 x 4096 tokens,
 // blocks of 64 382, 407.  Beyond 2^25 elements the launch no longer counts: 4 x 8192 tokens 4096 -> 4096, 3 levels 359, 359,
 // WHT 1772, 1806.
 bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
   const StampGeom& g = p->geom;
   if (!p->direct_ok || p->engine != STAMP_GEMM_FP6 || p->gen.group || (int64_t)g.B * g.s * g.d > (1 << 25)) return false;
-  if (p->rag.on ? p->rag.r > 4 : (!g.ident && (g.is2d || g.r > 4))) return false;
+  if (p->rag.on ? p->rag.r > 4 : (!g.ident && (g.is2d ? !stamp_bottom_quads(p) : g.r > 4))) return false;
   if (p->gen.kind != kGenNone || g.ident) return !p->rag.on || (rag_route(p, Y) && stamp_rag_quantizes(p, X) && p->hi6[0]);
   if (!p->fused_ok || p->unfused) return false;
   if (own_top(p)) return p->hi6[1];

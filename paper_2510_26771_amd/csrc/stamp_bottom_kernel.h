@@ -234,7 +234,7 @@ __device__ __forceinline__ void flush_rows(float (&rowv)[NR][8], MetaFn meta, in
                                            uint32_t* gpart_blk /* PASS 1: this split's partial maxima of the block's row e=0 */,
                                            size_t gpart_neg /* PASS 1: distance to the negative parts */,
                                            const uint32_t* s_amax /* PASS 2: [2][kMaxBlockRows] */, bool write_scales,
-                                           size_t row0 = 0, int Kpad = 0) {
+                                           size_t row0 = 0, int Kpad = 0, int nwaves = 0 /* waves that share a row, 0: the workgroup's */) {
   // Values derived from the thread index are recomputed in every step from an opaque copy: cheap, and it
   // keeps them from being carried (and spilled: a scratch reload waits for ALL outstanding memory
   // operations, the asynchronous loads of the next batches included) across the whole unrolled kernel.
@@ -272,7 +272,7 @@ __device__ __forceinline__ void flush_rows(float (&rowv)[NR][8], MetaFn meta, in
   {
     const int r = lane < NR ? lane : 0;
     const RowMeta rm = meta(r);
-    const int nw = (int)(blockDim.x >> 6);
+    const int nw = nwaves != 0 ? nwaves : (int)(blockDim.x >> 6);
     // The partial maxima are read by hand-written LDS reads: the compiler cannot tell this array from the
     // staging buffer that the asynchronous global -> LDS loads of the NEXT batches are writing, and would
     // make every ordinary LDS read here wait for all of them (vmcnt(0)), i.e. serialise memory and compute.
@@ -750,16 +750,9 @@ __device__ __forceinline__ void cell2d(const float (&p)[8], const float (&q)[8],
   }
 }
 
-template <int RLOG, bool BF16, bool ASYM, int PASS, int SB>
-__device__ __forceinline__ void step2d(const void* X, size_t blk_elem_off, int gridW, int d, int c0, bool active, int tid,
-                                       float (&pend)[4][8], float (&top)[8], uint32_t (*s_max)[kPartWords],
-                                       uint8_t* q_lo_blk, uint32_t q_off, float* scales_blk, size_t zeros_off,
-                                       uint32_t* gpart_blk, size_t gpart_neg, const uint32_t* s_amax, bool write_scales) {
-  constexpr int g = 1 << RLOG;
-  constexpr int sby = (g == 4) ? 0 : (SB >> 1), sbx = (g == 4) ? 0 : (SB & 1);
-  constexpr bool LAST = (g == 8) && (SB == 3);
-  constexpr int NR = LAST ? 18 : 15;
-  float rowv[NR][8];
+// 16 tokens from eoff0 on (4 x 4) -> 12 coefficients of level 1 and 3 of level 2 (rowv), their sum
+template <bool BF16, int NR>
+__device__ __forceinline__ void quad2d(const void* X, size_t eoff0, int gridW, int d, bool active, float (&rowv)[NR][8], float (&ll2)[8]) {
   float ll1[4][8];
   // all 16 tokens of the sub-block are requested before the first cell is computed (one memory latency per
   // sub-block instead of one per cell); the raw words give way to finished rows as the cells are consumed
@@ -768,8 +761,8 @@ __device__ __forceinline__ void step2d(const void* X, size_t blk_elem_off, int g
 #pragma unroll
   for (int tkn = 0; tkn < 16; ++tkn) {
     const int ci = tkn >> 2, q = tkn & 3;
-    const int y = 4 * sby + 2 * (ci >> 1) + (q >> 1), x = 4 * sbx + 2 * (ci & 1) + (q & 1);
-    const size_t eoff = blk_elem_off + ((size_t)y * gridW + x) * d;
+    const int y = 2 * (ci >> 1) + (q >> 1), x = 2 * (ci & 1) + (q & 1);
+    const size_t eoff = eoff0 + ((size_t)y * gridW + x) * d;
 #pragma unroll
     for (int h = 0; h < WPT; ++h) {
       if (active) {
@@ -798,8 +791,43 @@ __device__ __forceinline__ void step2d(const void* X, size_t blk_elem_off, int g
     }
     cell2d(t[0], t[1], t[2], t[3], ll1[ci], rowv[3 * ci + 0], rowv[3 * ci + 1], rowv[3 * ci + 2]);
   }
-  float ll2[8];
   cell2d(ll1[0], ll1[1], ll1[2], ll1[3], ll2, rowv[12], rowv[13], rowv[14]);
+}
+
+// level and in-block position of row r of sub-block (sby, sbx)
+template <int RLOG>
+__device__ __forceinline__ RowMeta meta2d(int r, int sby, int sbx) {
+  constexpr int g = 1 << RLOG;
+  RowMeta m;
+  if (r < 12) {
+    const int ci = r / 3, bd = r - 3 * ci;
+    constexpr int g1 = g >> 1;
+    m.level = 1;
+    m.e = g1 * g1 * (1 + bd) + (2 * sby + (ci >> 1)) * g1 + (2 * sbx + (ci & 1));
+  } else if (r < 15) {
+    constexpr int g2 = g >> 2;
+    m.level = 2;
+    m.e = g2 * g2 * (1 + (r - 12)) + sby * g2 + sbx;
+  } else {
+    m.level = 3;
+    m.e = 1 + (r - 15);
+  }
+  m.pos = m.e;
+  return m;
+}
+
+template <int RLOG, bool BF16, bool ASYM, int PASS, int SB>
+__device__ __forceinline__ void step2d(const void* X, size_t blk_elem_off, int gridW, int d, int c0, bool active, int tid,
+                                       float (&pend)[4][8], float (&top)[8], uint32_t (*s_max)[kPartWords],
+                                       uint8_t* q_lo_blk, uint32_t q_off, float* scales_blk, size_t zeros_off,
+                                       uint32_t* gpart_blk, size_t gpart_neg, const uint32_t* s_amax, bool write_scales) {
+  constexpr int g = 1 << RLOG;
+  constexpr int sby = (g == 4) ? 0 : (SB >> 1), sbx = (g == 4) ? 0 : (SB & 1);
+  constexpr bool LAST = (g == 8) && (SB == 3);
+  constexpr int NR = LAST ? 18 : 15;
+  float rowv[NR][8];
+  float ll2[8];
+  quad2d<BF16, NR>(X, blk_elem_off + ((size_t)(4 * sby) * gridW + 4 * sbx) * d, gridW, d, active, rowv, ll2);
   if constexpr (g == 4) {
 #pragma unroll
     for (int c = 0; c < 8; ++c) top[c] = ll2[c];
@@ -809,24 +837,7 @@ __device__ __forceinline__ void step2d(const void* X, size_t blk_elem_off, int g
 #pragma unroll
     for (int c = 0; c < 8; ++c) pend[SB][c] = ll2[c];
   }
-  auto meta = [](int r) -> RowMeta {
-    RowMeta m;
-    if (r < 12) {
-      const int ci = r / 3, bd = r - 3 * ci;
-      constexpr int g1 = g >> 1;
-      m.level = 1;
-      m.e = g1 * g1 * (1 + bd) + (2 * sby + (ci >> 1)) * g1 + (2 * sbx + (ci & 1));
-    } else if (r < 15) {
-      constexpr int g2 = g >> 2;
-      m.level = 2;
-      m.e = g2 * g2 * (1 + (r - 12)) + sby * g2 + sbx;
-    } else {
-      m.level = 3;
-      m.e = 1 + (r - 15);
-    }
-    m.pos = m.e;
-    return m;
-  };
+  auto meta = [](int r) -> RowMeta { return meta2d<RLOG>(r, sby, sbx); };
   flush_rows<NR, true, ASYM, PASS>(rowv, meta, SB, s_max, q_lo_blk, q_off, scales_blk, zeros_off, active, tid, gpart_blk,
                                    gpart_neg, s_amax, write_scales);
 }
@@ -878,6 +889,133 @@ __global__ __launch_bounds__(512) void k_bottom2d(const void* __restrict__ X, ui
     float4* o = reinterpret_cast<float4*>(abot + ((size_t)b * k + j) * d + c0);
     o[0] = make_float4(top[0], top[1], top[2], top[3]);
     o[1] = make_float4(top[4], top[5], top[6], top[7]);
+  }
+}
+
+// 8 x 8 blocks of up to 1536 channels: the four 4 x 4 sub-blocks side by side, a group of waves each (nthr threads), their
+// sums through LDS, the last level's four rows a group each.  A block's rows need all its channels, so there are no more
+// workgroups than blocks: k_bottom2d, whose workgroup takes the sub-blocks one after another, left the CUs three waves each.
+// Bound by the instructions of the rounding and the packing on the CUs that have a block.  Layers, k_bottom2d against this
+// one, microseconds: 2 x 4096 tokens 1152 -> 4608 72.4, 64.5; 512 -> 1152 39.5, 26.9; 4096 tokens 1536 -> 1536, 6 levels 58.9,
+// 47.5; 6 x 4096 tokens (384 blocks) 1152 -> 1152 70.4, 68.7; 16 x 4096 tokens (1024 blocks) 149.7, 151.2.
+template <bool BF16, bool ASYM, bool OUT6>
+__global__ __launch_bounds__(768) void k_bottom2d_quads(const void* __restrict__ X, uint8_t* __restrict__ q_lo, float* __restrict__ scales,
+                                                         float* __restrict__ abot, int s, int d, int G, int gridW, int Kpad,
+                                                         size_t zeros_off, SplitArgs sp) {
+  __shared__ __attribute__((aligned(16))) uint32_t s_max[4][2][kPartWords];
+  __shared__ uint32_t s_amax[2 * kMaxBlockRows];
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // [4][nthr][8] sums
+  float* const s_sum = reinterpret_cast<float*>(smem);
+  const int nthr = (int)blockDim.x >> 2, nw = nthr >> 6;
+  const int j = blockIdx.x, b = blockIdx.y, qd = __builtin_amdgcn_readfirstlane((int)threadIdx.x / nthr), tid = (int)threadIdx.x - qd * nthr;
+  const int by = j / G, bx = j - by * G, k = G * G, c0 = tid * 8, sby = qd >> 1, sbx = qd & 1;
+  const bool active = c0 < d;
+  const size_t tok0 = (size_t)b * s + (size_t)(by * 8 + 4 * sby) * gridW + bx * 8 + 4 * sbx, prow0 = (size_t)b * s + (size_t)j * 64;
+  uint8_t* const q_blk = OUT6 ? q_lo + (prow0 >> 8) * (size_t)(Kpad >> 7) * kStageA6 : q_lo + stamp_qlo_offset(prow0, 0, Kpad);
+  const uint32_t q_off = OUT6 ? off48(c0, kStageA6) : (uint32_t)stamp_qlo_offset(0, c0, Kpad);
+  // two rows of cells after one another: 15 finished rows at once would not fit the registers of 12 waves
+  {
+    constexpr int WPT = BF16 ? 1 : 2;
+    uint4 raw[2][8][WPT];
+    const size_t eoff0 = tok0 * d + min(c0, d - 8);  // threads beyond d_in / 8 redo the last channels, see k_bottom1d
+    auto request = [&](int h) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const size_t eoff = eoff0 + ((size_t)(2 * h + ((i >> 1) & 1)) * gridW + 2 * (i >> 2) + (i & 1)) * d;
+#pragma unroll
+        for (int w = 0; w < WPT; ++w)
+          raw[h][i][w] = BF16 ? *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(X) + eoff)
+                              : *reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(X) + eoff + 4 * w);
+      }
+    };
+    float ll1[4][8];
+    auto cell = [&](int h, int x, float (&W)[8], float (&H)[8], float (&D)[8]) {
+      float t[4][8];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint4 w0 = raw[h][4 * x + q][0], w1 = raw[h][4 * x + q][WPT - 1];
+        if constexpr (BF16) {
+          t[q][0] = bf16lo(w0.x); t[q][1] = bf16hi(w0.x); t[q][2] = bf16lo(w0.y); t[q][3] = bf16hi(w0.y);
+          t[q][4] = bf16lo(w0.z); t[q][5] = bf16hi(w0.z); t[q][6] = bf16lo(w0.w); t[q][7] = bf16hi(w0.w);
+        } else {
+          t[q][0] = __uint_as_float(w0.x); t[q][1] = __uint_as_float(w0.y); t[q][2] = __uint_as_float(w0.z);
+          t[q][3] = __uint_as_float(w0.w); t[q][4] = __uint_as_float(w1.x); t[q][5] = __uint_as_float(w1.y);
+          t[q][6] = __uint_as_float(w1.z); t[q][7] = __uint_as_float(w1.w);
+        }
+      }
+      cell2d(t[0], t[1], t[2], t[3], ll1[2 * h + x], W, H, D);
+    };
+    request(0);
+    if constexpr (BF16) request(1);
+    {
+      float rowv[6][8];
+      cell(0, 0, rowv[0], rowv[1], rowv[2]);
+      cell(0, 1, rowv[3], rowv[4], rowv[5]);
+      if constexpr (!BF16) request(1);
+      auto meta = [=](int r) -> RowMeta { return meta2d<3>(r, sby, sbx); };
+      flush_rows<6, true, ASYM, 0, false, OUT6>(rowv, meta, 0, s_max[qd], q_blk, q_off, scales + prow0, zeros_off, active, tid, nullptr, 0,
+                                                nullptr, true, prow0 & 255, 0, nw);
+    }
+    float rowv[9][8], sum[8];
+    cell(1, 0, rowv[0], rowv[1], rowv[2]);
+    cell(1, 1, rowv[3], rowv[4], rowv[5]);
+    cell2d(ll1[0], ll1[1], ll1[2], ll1[3], sum, rowv[6], rowv[7], rowv[8]);
+    float4* const mine = reinterpret_cast<float4*>(s_sum + (size_t)threadIdx.x * 8);
+    mine[0] = make_float4(sum[0], sum[1], sum[2], sum[3]);
+    mine[1] = make_float4(sum[4], sum[5], sum[6], sum[7]);
+    auto meta = [=](int r) -> RowMeta { return meta2d<3>(r + 6, sby, sbx); };
+    flush_rows<9, true, ASYM, 0, false, OUT6>(rowv, meta, 1, s_max[qd], q_blk, q_off, scales + prow0, zeros_off, active, tid, nullptr, 0,
+                                              nullptr, true, prow0 & 255, 0, nw);
+  }
+  __syncthreads();
+  float row[1][8], ll[4][8];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4* o = reinterpret_cast<const float4*>(s_sum + (size_t)(q * nthr + tid) * 8);
+    const float4 v0 = o[0], v1 = o[1];
+    ll[q][0] = v0.x; ll[q][1] = v0.y; ll[q][2] = v0.z; ll[q][3] = v0.w;
+    ll[q][4] = v1.x; ll[q][5] = v1.y; ll[q][6] = v1.z; ll[q][7] = v1.w;
+  }
+  float LL[8], W[8], H[8], D[8];
+  cell2d(ll[0], ll[1], ll[2], ll[3], LL, W, H, D);
+#pragma unroll
+  for (int c = 0; c < 8; ++c) row[0][c] = qd == 0 ? LL[c] : qd == 1 ? W[c] : qd == 2 ? H[c] : D[c];
+  // the row's range, one group each: parts per wave, then s_amax[row] (the block sum's: of its normalised values)
+  uint32_t pos, neg = 0u;
+  {
+    float v[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = qd == 0 ? __fmul_rn(row[0][c], 0.125f) : row[0][c];
+    if constexpr (ASYM) {
+      row_posneg_bits(v, pos, neg);
+      if (!active) pos = neg = 0u;
+    } else {
+      pos = row_absmax_bits(v);
+    }
+  }
+  pos = wave_max_u32(pos);
+  neg = wave_max_u32(neg);
+  uint32_t* const part = &s_max[qd][0][0];  // flush_rows used [1] last
+  if ((tid & 63) == 0) { part[tid >> 6] = pos; part[16 + (tid >> 6)] = neg; }
+  __syncthreads();
+  if (tid == 0) {
+    for (int i = 0; i < nw; ++i) { pos = max(pos, part[i]); neg = max(neg, part[16 + i]); }
+    s_amax[qd] = pos;
+    s_amax[kMaxBlockRows + qd] = neg;
+  }
+  __syncthreads();
+  if (qd != 0) {
+    auto meta = [=](int) -> RowMeta { return RowMeta{3, qd, qd}; };
+    flush_rows<1, true, ASYM, 2, false, OUT6>(row, meta, 0, s_max[qd], q_blk, q_off, scales + prow0, zeros_off, active, tid, nullptr, 0,
+                                              s_amax, true, prow0 & 255, 0, nw);
+  } else if (sp.q_hi != nullptr) {
+    finish_top_row<true, ASYM, false, OUT6, 2>(row[0], 3, nullptr, sp.q_hi + ((size_t)b * k + j) * d + c0,
+                                               (OUT6 ? q_lo + a6_row(prow0, Kpad >> 7) : q_blk) + q_off, scales + prow0, zeros_off, j < sp.khi,
+                                               active, tid, sp.hi6, b * sp.khi + j, Kpad >> 7, c0, nullptr, 0, s_amax);
+  } else if (active) {
+    float4* o = reinterpret_cast<float4*>(abot + ((size_t)b * k + j) * d + c0);
+    o[0] = make_float4(row[0][0], row[0][1], row[0][2], row[0][3]);
+    o[1] = make_float4(row[0][4], row[0][5], row[0][6], row[0][7]);
   }
 }
 

@@ -224,6 +224,9 @@ hipError_t stamp_launch_weight_quant(const stamp_plan* p, const float* W, hipStr
 int stamp_actquant_nsplit(const stamp_plan* p);
 // plans without top levels: the bottom kernel also quantizes the block sums (no k_top, no k_quant_hi)
 bool stamp_top_in_bottom(const stamp_plan* p);
+// 8 x 8 blocks whose four sub-blocks one workgroup takes side by side (k_bottom2d_quads: up to 1536 channels by its threads;
+// up to two blocks per CU, 512: with more the CUs are full either way)
+bool stamp_bottom_quads(const stamp_plan* p);
 // dir: the codes leave as FP6 operands (4-bit rows, 8-bit rows) instead of in q_hi / q_lo, which are not written
 struct StampDirect {
   uint8_t *a6, *h6;

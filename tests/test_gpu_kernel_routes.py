@@ -163,3 +163,22 @@ SPLIT_TOP = [_wl("split_top_f32_asym", seq_len=64, d_in=4128, k_hi=3, act_quant=
 @pytest.mark.parametrize("w", SPLIT_TOP, ids=[w.name for w in SPLIT_TOP])
 def test_split_channels_without_top_levels(w):
     tl.full_case(w, with_bias=True)
+
+
+# ---- 8 x 8 blocks of a grid: sub-blocks side by side up to 1536 channels, one after another beyond; with and without top
+# levels, every block sum at 8 bits or only some, both quantizer forms and input types
+def _quads(name, d, **kw):
+    return _wl(name, xform="haar2d", grid_h=16, grid_w=16, seq_len=256, d_in=d, corr_len=4.0, seed=700 + d, **kw)
+
+
+QUADS = [_quads("quads_1536", 1536, levels=4, k_hi=4, x_dtype="bf16"),
+         _quads("quads_1536_f32_asym", 1536, levels=3, k_hi=3, act_quant="asym", mean_shift=0.5),
+         _quads("quads_1568", 1568, levels=3, k_hi=4, x_dtype="bf16"),
+         _quads("quads_544_few", 544, levels=3, k_hi=1, x_dtype="bf16", batch=3),
+         _quads("quads_32_asym", 32, levels=4, k_hi=4, act_quant="asym", mean_shift=-0.3, x_dtype="bf16", batch=2)]
+
+
+@pytest.mark.parametrize("w", QUADS, ids=[w.name for w in QUADS])
+def test_grid_blocks_by_sub_blocks(w):
+    tl.full_case(w, with_bias=True)
+    tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16")
