@@ -503,6 +503,15 @@ bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
   return p->hi6[0] && (g.L > 0 || g.khi == g.k);
 }
 
+// stamp_linear_forward, plans with top levels whose bottom kernel leaves packed codes: their conversion shares the launch of
+// the top levels, which do not need it, and the 8-bit rows' quantizer writes their operand (the layer's one conversion launch
+// less: 2048 tokens 4096 -> 11008, blocks of 32, 102.5 us, now 99.4).
+bool convert_beside_top(const stamp_plan* p) {
+  const StampGeom& g = p->geom;
+  return p->direct_ok && p->engine == STAMP_GEMM_FP6 && p->gen.kind == kGenNone && !g.ident && p->fused_ok && !p->unfused && g.L > 0 &&
+         p->hi6[0];
+}
+
 }  // namespace
 
 extern "C" {
@@ -686,7 +695,15 @@ stamp_status_t stamp_linear_forward(const stamp_plan_t* p, const void* X, void* 
     dir.h6 = at(ws, p->ws_qhi);
     dir.np = stamp_hi6_np(p, own_top(p));
   }
-  const StampDirect* const dp = direct ? &dir : nullptr;
+  const bool beside = !direct && convert_beside_top(p);
+  if (beside) {
+    // the 8-bit rows' operand is written when the packed codes have been converted, over them
+    dir.a6 = at(ws, p->ws_a6);
+    dir.h6 = at(ws, p->ws_qhi);
+    dir.np = stamp_hi6_np(p, 0);
+    dir.lo_packed = 1;
+  }
+  const StampDirect* const dp = direct || beside ? &dir : nullptr;
   if (p->gen.kind != kGenNone) {
     if (p->gen.group) {
       q_hi = reinterpret_cast<int8_t*>(at(ws, p->ws_codes8));

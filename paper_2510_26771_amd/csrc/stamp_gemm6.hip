@@ -37,17 +37,7 @@ __global__ __launch_bounds__(512) void k_repack6(const uint8_t* __restrict__ q_l
     hi6_pack(hp, (int)blockIdx.x * 512 + (int)threadIdx.x);
     return;
   }
-  const size_t blk = blockIdx.x - nhi;
-  const int row = threadIdx.x & 255, kg = threadIdx.x >> 8;
-  const uint8_t* src = q_lo + blk * (256 * 64) + row * 64 + kg * 16;
-  uint8_t* dst = a6 + blk * kStageA6 + (row >> 5) * kBlock6 + kg * 512 + (row & 31) * 16;
-  uint64_t lo[3], hi[3];
-  chunk_to_e2m3(*reinterpret_cast<const u4*>(src), lo);
-  chunk_to_e2m3(*reinterpret_cast<const u4*>(src + 32), hi);
-  typedef uint64_t ul2 __attribute__((ext_vector_type(2)));
-  *reinterpret_cast<ul2*>(dst) = ul2{lo[0], lo[1]};
-  *reinterpret_cast<ul2*>(dst + kPart) = ul2{lo[2], hi[0]};
-  *reinterpret_cast<ul2*>(dst + 2 * kPart) = ul2{hi[1], hi[2]};
+  repack6_rows(q_lo, a6, blockIdx.x - nhi, threadIdx.x & 255, threadIdx.x >> 8);
 }
 
 // The same from rows in STaMP order to rows in the block order of StampRag (rows without a coefficient: zeros).

@@ -57,6 +57,19 @@ __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
   }
 }
 
+// packed 4-bit rows -> operand: block `blk` = (row tile, K step), one row of it and kg: fragments kg and 2 + kg
+__device__ __forceinline__ void repack6_rows(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, size_t blk, int row, int kg) {
+  const uint8_t* src = q_lo + blk * (256 * 64) + row * 64 + kg * 16;
+  uint8_t* dst = a6 + blk * kStageA6 + (row >> 5) * kBlock6 + kg * 512 + (row & 31) * 16;
+  uint64_t lo[3], hi[3];
+  chunk_to_e2m3(*reinterpret_cast<const u4*>(src), lo);
+  chunk_to_e2m3(*reinterpret_cast<const u4*>(src + 32), hi);
+  typedef uint64_t ul2 __attribute__((ext_vector_type(2)));
+  *reinterpret_cast<ul2*>(dst) = ul2{lo[0], lo[1]};
+  *reinterpret_cast<ul2*>(dst + kPart) = ul2{lo[2], hi[0]};
+  *reinterpret_cast<ul2*>(dst + 2 * kPart) = ul2{hi[1], hi[2]};
+}
+
 }  // namespace stamp_gemm
 
 #endif  // STAMP_HI6_H_

@@ -231,6 +231,7 @@ bool stamp_bottom_quads(const stamp_plan* p);
 struct StampDirect {
   uint8_t *a6, *h6;
   int32_t np;
+  int32_t lo_packed;  // the 4-bit rows do leave in q_lo, and the top levels' launch converts them
 };
 hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo,
                                  float* scales, float* abot, uint32_t* rowmax, uint32_t* gpart, hipStream_t st, int part = 3,

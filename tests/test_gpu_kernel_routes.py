@@ -182,3 +182,19 @@ QUADS = [_quads("quads_1536", 1536, levels=4, k_hi=4, x_dtype="bf16"),
 def test_grid_blocks_by_sub_blocks(w):
     tl.full_case(w, with_bias=True)
     tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16")
+
+
+# ---- conversion of the packed codes beside the top levels: one and several row tiles and K steps, 8-bit rows that do not
+# fill their operand's groups, an operand larger than the 8-bit codes it lies over, blocks on a line and on a grid
+BESIDE = [_wl("beside_32", seq_len=256, levels=8, k_hi=8, d_in=160, x_dtype="bf16", seed=801),
+          _wl("beside_64_b3_asym", batch=3, seq_len=1024, levels=10, k_hi=16, d_in=96, act_quant="asym", mean_shift=0.5, seed=802),
+          _wl("beside_32_b5", batch=5, seq_len=64, levels=6, k_hi=2, d_in=32, seed=803),
+          _wl("beside_grid4", batch=2, seq_len=256, levels=4, k_hi=16, d_in=288, xform="haar2d", grid_h=16, grid_w=16, corr_len=4.0,
+              x_dtype="bf16", seed=804),
+          _wl("beside_wide", seq_len=512, levels=9, k_hi=16, d_in=8224, x_dtype="bf16", seed=805)]
+
+
+@pytest.mark.parametrize("w", BESIDE, ids=[w.name for w in BESIDE])
+def test_codes_converted_beside_the_top_levels(w):
+    tl.full_case(w, with_bias=True)
+    tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16")
