@@ -194,7 +194,10 @@ stamp_status_t validate(const stamp_plan_desc_t* d, StampGeom* g, int* fused_ok,
 
 // Per-block scales on a 2-D Haar transform with the fast path's block structure (4 x 4 or 8 x 8 token blocks; top levels over
 // at most 8 x 8 block sums, which a lane of their kernel holds), even d_out (the epilogue stores pairs), bias after the
-// inverse.  Everything else runs level by level.
+// inverse.  Everything else runs level by level, and so do small layers, whose few GEMM tiles of 256 x 128 leave CUs idle for
+// a whole tile's depth.  Microseconds, level by level against this form: with top levels, 1024 tokens 512 -> 512 (16 tiles)
+// 27.6, 35.0; 4608 -> 1152 (40) 90.6, 96.1; 2048 tokens 896 -> 1608 (112) 43.1, 43.9; 1024 tokens 1152 -> 4608 (144) 52.5,
+// 47.0; without, 4096 tokens 512 -> 512 (64) 37.6, 29.2.
 void grp_geometry(stamp_plan* p) {
   const stamp_plan_desc_t& d = p->desc;
   p->grp = 0;
@@ -207,6 +210,8 @@ void grp_geometry(stamp_plan* p) {
   if (fast_geometry(&d, &g, &fused, d.grid_h) != STAMP_OK || !fused) return;
   if (g.L > 0 && g.k > 64) return;
   if (g.s % 64 != 0 || g.khi < 1) return;
+  const int64_t rows = (int64_t)g.B * g.s, tiles = (rows + 255) / 256 * ((d.d_out + 255) / 256 * 2);
+  if (tiles < 128 && (g.L > 0 || rows < 4096)) return;
   p->bgeom = g;
   p->grp = 1;
 }

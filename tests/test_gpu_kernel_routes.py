@@ -120,7 +120,11 @@ def _grp(side, J, k, d, n, **kw):
 
 GRP = [_grp(64, 3, 64, 192, 130), _grp(32, 3, 64, 64, 258, batch=2, x_dtype="bf16"), _grp(32, 5, 64, 320, 66, batch=3),
        _grp(64, 6, 64, 128, 514), _grp(32, 2, 16, 128, 192, x_dtype="bf16"), _grp(32, 3, 4, 256, 128), _grp(8, 1, 4, 64, 64),
-       _grp(8, 3, 4, 192, 200, batch=5), _grp(16, 2, 16, 448, 64, batch=9), _grp(32, 3, 64, 128, 131)]
+       _grp(8, 3, 4, 192, 200, batch=5), _grp(16, 2, 16, 448, 64, batch=9), _grp(32, 3, 64, 128, 131),
+       # (the sizes from which on the block kernels serve such plans: smaller ones run level by level)
+       _grp(32, 5, 64, 320, 1410, batch=3), _grp(64, 6, 64, 128, 1026), _grp(32, 3, 64, 64, 2050, batch=2, x_dtype="bf16"),
+       _grp(8, 3, 4, 192, 1026, batch=70), _grp(16, 2, 16, 448, 64, batch=17), _grp(32, 3, 4, 256, 128, batch=4),
+       _grp(32, 2, 16, 128, 192, batch=5, x_dtype="bf16")]
 
 
 @pytest.mark.parametrize("w", GRP, ids=[w.name for w in GRP])
