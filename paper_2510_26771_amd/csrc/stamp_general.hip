@@ -460,6 +460,10 @@ __device__ __forceinline__ cd c_mul(cd a, cd b) {
   return {__builtin_fma(a.re, b.re, -(a.im * b.im)), __builtin_fma(a.re, b.im, a.im * b.re)};
 }
 __device__ __forceinline__ cd c_conj(cd a) { return {a.re, -a.im}; }
+// An infinity enters as a number far beyond the range of fp32, so that every coefficient it is part of leaves as an infinity
+// of its sign, as in the sum that defines it; an infinity itself would meet 0 * inf in the first product with a factor and
+// leave NaNs, which the row maxima of the quantizer pass over.
+__device__ __forceinline__ double dct_in(float x) { return __builtin_isinf(x) ? __builtin_copysign(1e300, (double)x) : (double)x; }
 
 template <bool INV>
 __device__ __forceinline__ void lds_fft(cd* s, const cd* tw, int m, int chlog, int tid, int nthr) {
@@ -533,7 +537,7 @@ __global__ __launch_bounds__(1024) void k_gen_dct_fft(const cd* __restrict__ tab
         const int n = n0 + j * (N >> 3);
         const int nv = (n & 1) ? N - 1 - (n >> 1) : (n >> 1);
         const int pos = (int)(__brev((unsigned)(nv >> 1)) >> (32 - m));
-        sd[2 * ((pos << chlog) + ch) + (nv & 1)] = (double)x[j];
+        sd[2 * ((pos << chlog) + ch) + (nv & 1)] = dct_in(x[j]);
       }
     }
     __syncthreads();
@@ -575,8 +579,8 @@ __global__ __launch_bounds__(1024) void k_gen_dct_fft(const cd* __restrict__ tab
         // k = 0 reads coefficients 0, M and (for V[M/2]) M / 2, M + M / 2
         const float* i = S + bo + c;
         const int h = M >> 1;
-        const double x0 = (double)i[(size_t)k * ld], x1 = (double)i[(size_t)(k == 0 ? M : N - k) * ld];
-        const double x2 = (double)i[(size_t)(k == 0 ? h : M - k) * ld], x3 = (double)i[(size_t)(k == 0 ? M + h : M + k) * ld];
+        const double x0 = dct_in(i[(size_t)k * ld]), x1 = dct_in(i[(size_t)(k == 0 ? M : N - k) * ld]);
+        const double x2 = dct_in(i[(size_t)(k == 0 ? h : M - k) * ld]), x3 = dct_in(i[(size_t)(k == 0 ? M + h : M + k) * ld]);
         if (k == 0) {
           const double v0 = x0 * (sqrt((double)N) / M), vm = x1 * (sc * sqrt(2.0));
           tk = {0.5 * (v0 + vm), 0.5 * (v0 - vm)};

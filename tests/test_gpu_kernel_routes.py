@@ -76,6 +76,45 @@ def test_dct_inverse_against_the_dense_product(s):
     plan.destroy()
 
 
+@pytest.mark.parametrize("s", [8, 64, 1024, 8192])
+def test_dct_of_infinities(s):
+    """An infinite activation makes every coefficient of its channel infinite, so every scale of that sequence is, and no
+    output of it looks like a number; an infinite coefficient makes its whole column infinite, each token with the sign of
+    its cosine.  The other sequence and the other columns do not notice."""
+    import torch
+    import paper_2510_26771_amd as st
+    w = _wl(f"dct_inf_{s}", batch=2, xform="dct", levels=0, seq_len=s, k_hi=2, d_in=64, d_out=37)
+    inp = tl.make_inputs(w)
+    plan = st.StampPlan(tl.plan_desc_for(w, "f32"), torch.from_numpy(inp["W"]).cuda())
+    X = tl.to_device_x(inp, w)
+    ws = plan.alloc_workspace()
+    good, bad = plan.alloc_act_buffers(), plan.alloc_act_buffers()
+    Y, Yb = (torch.zeros((2, s, 37), dtype=torch.float32, device="cuda") for _ in range(2))
+    plan.quantize_act(X, *good, ws)
+    plan.linear_forward(X, Y, ws)
+    X[0, s // 2 + 1, 5] = float("inf")
+    X[0, 1, 9] = float("-inf")
+    plan.quantize_act(X, *bad, ws)
+    plan.linear_forward(X, Yb, ws)
+    torch.cuda.synchronize()
+    assert torch.isinf(bad[2][0]).all(), "a scale that does not show the infinity"
+    assert not torch.isfinite(Yb[0]).any()
+    assert torch.equal(bad[2][1], good[2][1]) and torch.equal(Yb[1], Y[1])
+    # stamp_inverse: coefficient k infinite
+    k, col = s // 2 + 1, 3
+    Yt = torch.randn((2, s, 37), device="cuda")
+    inv_ws = torch.empty(2 * (-(-(2 * s * 37 * 4) // 256) * 256), dtype=torch.uint8, device="cuda")
+    plan.inverse(Yt, 37, Y, inv_ws)
+    Yt[1, k, col] = float("-inf")
+    plan.inverse(Yt, 37, Yb, inv_ws)
+    torch.cuda.synchronize()
+    cosine = np.cos(np.pi * (((2 * np.arange(s, dtype=np.int64) + 1) * k) % (4 * s)) / (2.0 * s))
+    assert np.array_equal(Yb[1, :, col].cpu().numpy(), np.where(cosine > 0, -np.inf, np.inf))
+    Yb[1, :, col] = Y[1, :, col]
+    assert torch.equal(Yb, Y)
+    plan.destroy()
+
+
 # ---- WHT in one pass (64 .. 4096 tokens): every split of the stages, the lengths on either side of the range, channel
 # counts that leave the last workgroup partly empty
 WHT = [_wl(f"wht_{1 << J}", batch=2 if J < 10 else 1, xform="wht", levels=0, seq_len=1 << J, k_hi=1 << (J // 2), d_in=32 * (J - 3),
