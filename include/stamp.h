@@ -287,6 +287,30 @@ stamp_status_t stamp_plan_set_unfused(stamp_plan_t* plan, int32_t unfused);
 typedef enum { STAMP_GEMM_INT8 = 0, STAMP_GEMM_FP6 = 1 } stamp_gemm_engine_t;
 stamp_status_t stamp_plan_set_gemm_engine(stamp_plan_t* plan, int32_t engine);
 
+/* Which kernels serve a plan is decided by rules on its sizes.  For tests and measurements, one of them can be overridden:
+ *   STAMP_CHOICE_HI_ROWS   GEMM of the 8-bit rows: 1 = int8 pipeline, 2 = FP6 pipeline (where that kernel can run them at all)
+ *   STAMP_CHOICE_OPERANDS  codes of stamp_linear_forward: 1 = packed as stamp_quantize_act leaves them, then converted by
+ *                          a pass of their own, 2 = written as FP6 operands by the quantizer (where it can)
+ * and 0 = by rule again.  It modifies the plan (not thread-safe, no call on the plan may be in progress on another host
+ * thread) and may change stamp_plan_workspace_bytes, which must be queried again.  STAMP_ERR_SHAPE for any other value.
+ * Plans with per-block scales have neither choice. */
+typedef enum { STAMP_CHOICE_HI_ROWS = 0, STAMP_CHOICE_OPERANDS = 1, STAMP_CHOICE_COUNT = 2 } stamp_choice_t;
+stamp_status_t stamp_debug_set_choice(stamp_plan_t* plan, int32_t choice, int32_t value);
+
+/* What stamp_linear_forward runs for 16-byte aligned X and Y, as a sum of stamp_route_t bits; 0 for a NULL plan. */
+typedef enum {
+  STAMP_ROUTE_GENERAL = 1,            /* the general path */
+  STAMP_ROUTE_ANY_LENGTH_BLOCKS = 2,  /* its 1-D Haar transform block by block, inverse in the GEMM's epilogue */
+  STAMP_ROUTE_GROUP_BLOCKS = 4,       /* per-block scales on blocks of a token grid, likewise */
+  STAMP_ROUTE_DIRECT = 8,             /* the quantizer writes the FP6 operands */
+  STAMP_ROUTE_BESIDE_TOP = 16,        /* packed codes are converted in the launch of the top levels */
+  STAMP_ROUTE_HI_FP6 = 32,            /* 8-bit rows on the FP6 pipeline */
+  STAMP_ROUTE_HI_TOP_FUSED = 64,      /* 8-bit rows on the int8 pipeline, top levels of the inverse in the epilogue */
+  STAMP_ROUTE_HI_SPLIT = 128,         /* 8-bit rows on the int8 pipeline in several parts of the depth */
+  STAMP_ROUTE_TILES_128 = 256         /* 4-bit rows in 128 x 256 tiles instead of 256 x 256 */
+} stamp_route_t;
+int32_t stamp_debug_routes(const stamp_plan_t* plan);
+
 /* Measurement aid (not part of the layer): the rate, in 1e12 operations per second, that the matrix
  * pipeline of `engine` sustains on the current device over pseudo-random 4-bit codes held in registers,
  * with no memory traffic: the ceiling that the GEMM of that engine can approach on such values (it

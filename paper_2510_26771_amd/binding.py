@@ -24,7 +24,12 @@ EXPORTS = ["stamp_plan_create", "stamp_plan_destroy", "stamp_plan_workspace_byte
            "stamp_plan_row_of_coeff",
            "stamp_quantize_act", "stamp_linear_forward", "stamp_linear_forward_static", "stamp_linear_forward_q", "stamp_inverse",
            "stamp_debug_gemm_acc", "stamp_debug_weight_codes", "stamp_debug_run_stage", "stamp_plan_set_unfused", "stamp_plan_set_gemm_engine",
-           "stamp_debug_mfma_rate", "stamp_status_string"]
+           "stamp_debug_set_choice", "stamp_debug_routes", "stamp_debug_mfma_rate", "stamp_status_string"]
+
+# stamp_choice_t and stamp_route_t (include/stamp.h)
+CHOICES = {"hi_rows": 0, "operands": 1}
+ROUTES = {"general": 1, "any_length_blocks": 2, "group_blocks": 4, "direct": 8, "beside_top": 16, "hi_fp6": 32,
+          "hi_top_fused": 64, "hi_split": 128, "tiles_128": 256}
 
 
 class StampError(RuntimeError):
@@ -119,6 +124,10 @@ def load_library():
     lib.stamp_plan_set_unfused.restype = C.c_int
     lib.stamp_plan_set_gemm_engine.argtypes = [vp, i32]
     lib.stamp_plan_set_gemm_engine.restype = C.c_int
+    lib.stamp_debug_set_choice.argtypes = [vp, i32, i32]
+    lib.stamp_debug_set_choice.restype = C.c_int
+    lib.stamp_debug_routes.argtypes = [vp]
+    lib.stamp_debug_routes.restype = i32
     lib.stamp_debug_mfma_rate.argtypes = [i32, C.POINTER(C.c_double)]
     lib.stamp_debug_mfma_rate.restype = C.c_int
     lib.stamp_status_string.argtypes = [C.c_int]
@@ -196,6 +205,15 @@ class StampPlan:
 
     def set_unfused(self, unfused: bool):
         _check(self.lib.stamp_plan_set_unfused(self._h, int(bool(unfused))), "stamp_plan_set_unfused")
+
+    def set_choice(self, choice: str, value: int):
+        """For tests: override a rule that picks kernels (CHOICES; 0 = by rule).  Changes workspace_bytes()."""
+        _check(self.lib.stamp_debug_set_choice(self._h, CHOICES[choice], int(value)), "stamp_debug_set_choice")
+
+    def routes(self) -> set:
+        """Names (ROUTES) of what linear_forward runs for 16-byte aligned tensors."""
+        r = int(self.lib.stamp_debug_routes(self._h))
+        return {n for n, b in ROUTES.items() if r & b}
 
     def alloc_workspace(self, device="cuda"):
         import torch

@@ -500,7 +500,8 @@ stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, ui
 // WHT 1772, 1806.
 bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
   const StampGeom& g = p->geom;
-  if (!p->direct_ok || p->engine != STAMP_GEMM_FP6 || p->gen.group || (int64_t)g.B * g.s * g.d > (1 << 25)) return false;
+  if (!p->direct_ok || p->engine != STAMP_GEMM_FP6 || p->gen.group || p->dbg[STAMP_CHOICE_OPERANDS] == 1) return false;
+  if (p->dbg[STAMP_CHOICE_OPERANDS] == 0 && (int64_t)g.B * g.s * g.d > (1 << 25)) return false;
   if (p->rag.on ? p->rag.r > 4 : (!g.ident && (g.is2d ? !stamp_bottom_quads(p) : g.r > 4))) return false;
   if (p->gen.kind != kGenNone || g.ident) return !p->rag.on || (rag_route(p, Y) && stamp_rag_quantizes(p, X) && p->hi6[0]);
   if (!p->fused_ok || p->unfused) return false;
@@ -513,7 +514,7 @@ bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
 // less: 2048 tokens 4096 -> 11008, blocks of 32, 102.5 us, now 99.4).
 bool convert_beside_top(const stamp_plan* p) {
   const StampGeom& g = p->geom;
-  return p->direct_ok && p->engine == STAMP_GEMM_FP6 && p->gen.kind == kGenNone && !g.ident && p->fused_ok && !p->unfused && g.L > 0 &&
+  return p->direct_ok && p->engine == STAMP_GEMM_FP6 && p->dbg[STAMP_CHOICE_OPERANDS] != 1 && p->gen.kind == kGenNone && !g.ident && p->fused_ok && !p->unfused && g.L > 0 &&
          p->hi6[0];
 }
 
@@ -653,6 +654,37 @@ stamp_status_t stamp_plan_set_gemm_engine(stamp_plan_t* p, int32_t engine) {
   if (engine != STAMP_GEMM_INT8 && engine != STAMP_GEMM_FP6) return STAMP_ERR_UNSUPPORTED;
   p->engine = engine;
   return STAMP_OK;
+}
+
+stamp_status_t stamp_debug_set_choice(stamp_plan_t* p, int32_t choice, int32_t value) {
+  if (p == nullptr) return STAMP_ERR_NULL;
+  if (choice < 0 || choice >= STAMP_CHOICE_COUNT || value < 0 || value > 2) return STAMP_ERR_SHAPE;
+  if (p->gen.group) return STAMP_OK;
+  p->dbg[choice] = value;
+  layout_workspace(p);
+  return STAMP_OK;
+}
+
+int32_t stamp_debug_routes(const stamp_plan_t* p) {
+  if (p == nullptr) return 0;
+  const StampGeom& g = p->geom;
+  const void* const aligned = reinterpret_cast<const void*>((uintptr_t)256);
+  const bool own = own_top(p), rag = rag_route(p, aligned);
+  int32_t r = 0;
+  if (p->gen.kind != kGenNone) r |= STAMP_ROUTE_GENERAL;
+  if (p->grp) r |= STAMP_ROUTE_GROUP_BLOCKS;
+  if (rag) r |= STAMP_ROUTE_ANY_LENGTH_BLOCKS;
+  if (p->gen.group) return r;
+  if (direct_route(p, aligned, aligned)) r |= STAMP_ROUTE_DIRECT;
+  else if (convert_beside_top(p)) r |= STAMP_ROUTE_BESIDE_TOP;
+  if ((own ? g.khi : g.k) > 0) {
+    if (p->hi6[own]) r |= STAMP_ROUTE_HI_FP6;
+    else if (!own && stamp_hi_top_fused(p)) r |= STAMP_ROUTE_HI_TOP_FUSED;
+    else if ((own ? p->hi_ksplit_own : p->hi_ksplit) > 1) r |= STAMP_ROUTE_HI_SPLIT;
+  }
+  const int M = rag ? (g.B * p->rag.nb) << p->rag.r : g.B * g.s;
+  if (p->engine == STAMP_GEMM_FP6 && stamp_gemm6_half_tiles(M, p->Npad)) r |= STAMP_ROUTE_TILES_128;
+  return r;
 }
 
 stamp_status_t stamp_plan_row_of_coeff(const stamp_plan_t* p, int32_t* host_out) {

@@ -155,18 +155,19 @@ hipError_t stamp_launch_repack6_rag(const stamp_plan* p, const uint8_t* q_lo, ui
   return hipGetLastError();
 }
 
-namespace {
 // 128 x 256 tiles where the rounds they need (tiles over CUs, rounded up), at two thirds of a round of 256 x 256 tiles each,
 // take less time.  Depth 4096, 1-D blocks of 32, 2048 rows, microseconds, 256 x 256 against 128 x 256: 128 tiles of 256 x 256
 // 28.3, 23.0; 344 (2 rounds against 3) 58.1, 57.4; depth 11008, 128 tiles: 64.4, 47; at full rounds (256 tiles) 35.8 against
 // twice 23.
-bool gemm6_half_tiles(const GemmArgs& a) {
-  const int cus = gemm6_cus(), nt = a.Npad / BN6;
-  const int r8 = ((a.M + 255) / 256 * nt + cus - 1) / cus, r4 = ((a.M + 127) / 128 * nt + cus - 1) / cus;
+bool stamp_gemm6_half_tiles(int M, int Npad) {
+  const int cus = gemm6_cus(), nt = Npad / BN6;
+  const int r8 = ((M + 255) / 256 * nt + cus - 1) / cus, r4 = ((M + 127) / 128 * nt + cus - 1) / cus;
   return 100 * r8 > 68 * r4;
 }
+
+namespace {
 hipError_t gemm6(const GemmArgs& a, int mode, hipStream_t st) {
-  return mode != 0 && gemm6_half_tiles(a) ? stamp_gemm6_half(a, mode, st) : gemm6_run(a, mode, st);
+  return mode != 0 && stamp_gemm6_half_tiles(a.M, a.Npad) ? stamp_gemm6_half(a, mode, st) : gemm6_run(a, mode, st);
 }
 }  // namespace
 

@@ -276,6 +276,8 @@ bool stamp_hi6_fits(const stamp_plan* p, int own) {
   const int M = hi6_rows(p, own);
   if (M < 1 || p->gen.group != 0) return false;
   if (!g.ident && !own && g.L > 0 && (g.k > 128 || (g.k & (g.k - 1)) != 0)) return false;  // whole sequences per workgroup
+  const int choice = p->dbg[STAMP_CHOICE_HI_ROWS];
+  if (choice != 0) return choice == 2;
   return M <= 128 || (double)M * g.N * g.d <= 2.0e10;
 }
 

@@ -192,6 +192,7 @@ struct stamp_plan {
   int32_t hi6[2];
   size_t ws_hi6;            // their operand
   int32_t direct_ok;        // the quantizer may write the FP6 operands itself (the 8-bit rows' over ws_qhi)
+  int32_t dbg[STAMP_CHOICE_COUNT];  // stamp_debug_set_choice: 0 by rule, 1 / 2 the one or the other form
   size_t ws_ba6, ws_bP;     // blocked form: the 4-bit rows in block order (over ws_T), the block sums (over ws_Yt)
   // workspace layout (byte offsets, 256-aligned)
   size_t ws_abot, ws_rowmax, ws_gpart, ws_qhi, ws_qlo, ws_scales, ws_ythi, ws_P, ws_a6, ws_ytlo, ws_total;
@@ -288,6 +289,8 @@ hipError_t stamp_launch_rag_top(const stamp_plan* p, const float* ythi, int npar
 // a 4-bit row of a6 like any other (the quantizer writes it there as well), and P holds khi rows per sequence
 hipError_t stamp_launch_gemm_lo6(const stamp_plan* p, const uint8_t* a6, const float* scales, int mode, void* out,
                                  const float* P, hipStream_t st, int own_top = 0);
+// whether the FP6 GEMM over M rows takes 128 x 256 tiles
+bool stamp_gemm6_half_tiles(int M, int Npad);
 // identity plans: 8-bit rows' dequantized partial rows [nparts][B*k][N] (+ bias) -> Y rows of tokens 0..k-1
 hipError_t stamp_launch_hi_rows_out(const stamp_plan* p, const float* Yt_hi, void* Y, hipStream_t st, int nparts);
 // P: block sums [B*k][ldP]; nparts partial sources (each B*k*ncols floats apart) are added while reading

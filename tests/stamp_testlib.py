@@ -187,10 +187,20 @@ def y_to_numpy(Y, y_is_bf16: bool) -> np.ndarray:
     return Y.cpu().numpy()
 
 
+def check_routes(plan, w: Workload, routes: Tuple[str, ...]):
+    """A case that is there for one kernel fails when a rule sends its plan elsewhere."""
+    have = plan.routes()
+    for r in routes:
+        assert (r[1:] not in have) if r.startswith("-") else (r in have), f"{w.name} runs {sorted(have)}, expected {routes}"
+
+
 def full_case(w: Workload, with_bias: bool = False, y_dtype: str = "f32", cols: Optional[np.ndarray] = None,
               check_acc: bool = True, check_unfused: bool = True,
-              engines: Tuple[str, ...] = ("fp6", "int8"), also_f32_out: bool = False) -> Dict[str, float]:
+              engines: Tuple[str, ...] = ("fp6", "int8"), also_f32_out: bool = False, hi_rows: int = 0,
+              routes: Tuple[str, ...] = ()) -> Dict[str, float]:
     """Everything the ABI exposes, on one workload, against the oracle, under each GEMM engine.
+    hi_rows: which GEMM takes the 8-bit rows (StampPlan.set_choice; 0 = by the library's rule).
+    routes: kernels that the plan has to run by default ("-name": must not run), see StampPlan.routes.
     also_f32_out: a second plan with fp32 output runs the fused path on the same inputs and is held to the
     plain 1e-3 bar (for cases whose main plan stores bf16)."""
     import torch
@@ -205,6 +215,8 @@ def full_case(w: Workload, with_bias: bool = False, y_dtype: str = "f32", cols: 
     Wd = torch.from_numpy(inp["W"]).cuda()
     bd = None if inp["bias"] is None else torch.from_numpy(inp["bias"]).cuda()
     plan = st.StampPlan(plan_desc_for(w, y_dtype), Wd, bd)
+    plan.set_choice("hi_rows", hi_rows)
+    check_routes(plan, w, routes)
     report: Dict[str, float] = {}
 
     # weights
@@ -302,7 +314,7 @@ def full_case(w: Workload, with_bias: bool = False, y_dtype: str = "f32", cols: 
     return report
 
 
-def grouped_case(w: Workload, with_bias: bool = False, y_dtype: str = "f32") -> Dict[str, float]:
+def grouped_case(w: Workload, with_bias: bool = False, y_dtype: str = "f32", routes: Tuple[str, ...] = ()) -> Dict[str, float]:
     """Per-block (group_size = 64) scales: weight codes and scales, activation codes and scales bit for bit, the
     layer's output to the output bar, and quantize_act + linear_forward_q against linear_forward."""
     import torch
@@ -319,6 +331,7 @@ def grouped_case(w: Workload, with_bias: bool = False, y_dtype: str = "f32") -> 
     Wd = torch.from_numpy(inp["W"]).cuda()
     bd = None if inp["bias"] is None else torch.from_numpy(inp["bias"]).cuda()
     plan = st.StampPlan(plan_desc_for(w, y_dtype), Wd, bd)
+    check_routes(plan, w, routes)
     qw, swg = plan.debug_weight_codes()
     assert np.array_equal(qw, ora["qw"]), "weight codes differ"
     assert np.array_equal(swg.view(np.uint32), ora["swg"].view(np.uint32)), "weight scales differ"

@@ -122,6 +122,8 @@ def test_null_arguments(lib):
     assert lib.stamp_debug_run_stage(None, 0, None, None, None, None, None, None, 0, None) == 1
     assert lib.stamp_plan_set_unfused(None, 1) == 1
     assert lib.stamp_plan_set_gemm_engine(None, 1) == 1
+    assert lib.stamp_debug_set_choice(None, 0, 0) == 1
+    assert lib.stamp_debug_routes(None) == 0
     assert lib.stamp_debug_mfma_rate(0, None) == 1
     assert lib.stamp_debug_mfma_rate(7, None) == 1  # the null check comes first
 

@@ -107,6 +107,27 @@ def test_wht_and_dct_along_the_tokens(w):
     tl.full_case(w, with_bias=True, check_unfused=False)
 
 
+# 8-bit rows on the int8 pipeline, in one piece and in parts, merged into their slots (level by level) or made block sums
+# (blocked form, with and without the token left out; a short last block; odd d_out)
+INT8_ROWS = [
+    (_wl("merge_whole", seq_len=300, levels=2, k_hi=150, d_in=96, seed=121), ("-any_length_blocks", "-hi_split")),
+    (_wl("merge_parts_asym", batch=2, seq_len=300, levels=2, k_hi=70, d_in=1024, act_quant="asym", mean_shift=0.4, seed=122),
+     ("-any_length_blocks", "hi_split")),
+    (_wl("merge_parts_wht", seq_len=256, xform="wht", levels=0, k_hi=20, d_in=2048, d_out=66, seed=123), ("hi_split",)),
+    (_wl("blocks_whole", batch=2, seq_len=1005, levels=3, k_hi=100, d_in=96, seed=124), ("any_length_blocks", "-hi_split")),
+    (_wl("blocks_parts_skip", batch=3, seq_len=1003, levels=3, k_hi=100, d_in=1088, skip_first=True, seed=125,
+         first_token_scale=50.0), ("any_length_blocks", "hi_split")),
+    (_wl("blocks_parts_skip_asym_odd", seq_len=700, levels=4, k_hi=30, d_in=1024, d_out=131, skip_first=True, act_quant="asym",
+         mean_shift=-0.3, seed=126, x_dtype="bf16"), ("any_length_blocks", "hi_split")),
+]
+
+
+@pytest.mark.parametrize("w,routes", INT8_ROWS, ids=[w.name for w, _ in INT8_ROWS])
+def test_8bit_rows_on_the_int8_pipeline(w, routes):
+    for y in ("f32", "bf16"):
+        tl.full_case(w, with_bias=True, check_unfused=False, y_dtype=y, hi_rows=1, routes=routes + ("-hi_fp6",))
+
+
 def test_bf16_output_on_the_general_path():
     tl.full_case(_wl("rag_500_bf16out", seq_len=500, levels=4, x_dtype="bf16", seed=47), with_bias=True, y_dtype="bf16",
                  check_unfused=False)
@@ -294,13 +315,22 @@ def test_general_path_under_hip_graph_capture_and_static_scratch():
     library's static scratch array."""
     import torch
     import paper_2510_26771_amd as st
-    for w in (_wl("graph_skip", batch=2, seq_len=300, levels=4, skip_first=True, d_in=160, d_out=300, seed=81),
-              _wl("graph_g64_2d", seq_len=256, xform="haar2d", levels=3, grid_h=16, grid_w=16, k_hi=4, d_in=128,
-                  d_out=130, group_size=64, seed=82),
-              _wl("graph_wht_tb", seq_len=128, xform="wht", levels=0, bias_mode="transformed", act_quant="asym", seed=83)):
+    skip = _wl("graph_skip", batch=2, seq_len=300, levels=4, skip_first=True, d_in=160, d_out=300, seed=81)
+    for w, hi_rows, routes in (
+            (skip, 0, ("any_length_blocks", "direct", "hi_fp6")), (skip, 1, ("any_length_blocks", "-hi_fp6")),
+            (_wl("graph_g64_2d", seq_len=256, xform="haar2d", levels=3, grid_h=16, grid_w=16, k_hi=4, d_in=128,
+                 d_out=130, group_size=64, seed=82), 0, ("-group_blocks",)),
+            (_wl("graph_g64_blocks", seq_len=4096, xform="haar2d", levels=3, grid_h=64, grid_w=64, k_hi=64, d_in=128,
+                 d_out=130, group_size=64, seed=84), 0, ("group_blocks",)),
+            (_wl("graph_g64_blocks_top", batch=17, seq_len=256, xform="haar2d", levels=4, grid_h=16, grid_w=16, k_hi=16, d_in=128,
+                 d_out=1026, group_size=64, seed=85), 0, ("group_blocks",)),
+            (_wl("graph_dct_fft", seq_len=256, xform="dct", levels=0, k_hi=8, seed=86), 0, ()),
+            (_wl("graph_wht_tb", seq_len=128, xform="wht", levels=0, bias_mode="transformed", act_quant="asym", seed=83), 0, ())):
         inp = make_inputs(w, with_bias=True)
         plan = st.StampPlan(tl.plan_desc_for(w, "bf16"), torch.from_numpy(inp["W"]).cuda(),
                             torch.from_numpy(inp["bias"]).cuda())
+        plan.set_choice("hi_rows", hi_rows)
+        tl.check_routes(plan, w, routes)
         X = tl.to_device_x(inp, w)
         ws = plan.alloc_workspace()
         Y_eager = torch.zeros((w.batch, w.seq_len, w.d_out), dtype=torch.int16, device="cuda")

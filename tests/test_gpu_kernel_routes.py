@@ -157,19 +157,73 @@ def _grp(side, J, k, d, n, **kw):
                d_in=d, d_out=n, group_size=64, corr_len=4.0, seed=400 + d + n, **kw)
 
 
-GRP = [_grp(64, 3, 64, 192, 130), _grp(32, 3, 64, 64, 258, batch=2, x_dtype="bf16"), _grp(32, 5, 64, 320, 66, batch=3),
-       _grp(64, 6, 64, 128, 514), _grp(32, 2, 16, 128, 192, x_dtype="bf16"), _grp(32, 3, 4, 256, 128), _grp(8, 1, 4, 64, 64),
-       _grp(8, 3, 4, 192, 200, batch=5), _grp(16, 2, 16, 448, 64, batch=9), _grp(32, 3, 64, 128, 131),
-       # (the sizes from which on the block kernels serve such plans: smaller ones run level by level)
-       _grp(32, 5, 64, 320, 1410, batch=3), _grp(64, 6, 64, 128, 1026), _grp(32, 3, 64, 64, 2050, batch=2, x_dtype="bf16"),
-       _grp(8, 3, 4, 192, 1026, batch=70), _grp(16, 2, 16, 448, 64, batch=17), _grp(32, 3, 4, 256, 128, batch=4),
-       _grp(32, 2, 16, 128, 192, batch=5, x_dtype="bf16")]
+GRP_LEVELS = [_grp(64, 3, 64, 192, 131), _grp(32, 3, 64, 64, 258, batch=2, x_dtype="bf16"), _grp(32, 5, 64, 320, 66, batch=3),
+              _grp(64, 6, 64, 128, 514), _grp(32, 2, 16, 128, 192, x_dtype="bf16"), _grp(32, 3, 4, 256, 128), _grp(8, 1, 4, 64, 64),
+              _grp(8, 3, 4, 192, 200, batch=5), _grp(16, 2, 16, 448, 64, batch=9), _grp(32, 3, 64, 128, 131)]
+# (the sizes from which on the block kernels serve such plans: smaller ones, and odd widths, run level by level)
+GRP = [_grp(64, 3, 64, 192, 130), _grp(32, 5, 64, 320, 1410, batch=3), _grp(64, 6, 64, 128, 1026),
+       _grp(32, 3, 64, 64, 2050, batch=2, x_dtype="bf16"), _grp(8, 3, 4, 192, 1026, batch=70), _grp(16, 2, 16, 448, 64, batch=17),
+       _grp(32, 3, 4, 256, 128, batch=4), _grp(32, 2, 16, 128, 192, batch=5, x_dtype="bf16"),
+       # top levels over 4 x 4 block sums, to the last one and not; at most 32 8-bit rows over the batch
+       _grp(16, 4, 16, 128, 1026, batch=17), _grp(16, 3, 16, 320, 1290, batch=15, x_dtype="bf16"),
+       _grp(32, 4, 16, 192, 2050, batch=2), _grp(32, 5, 16, 64, 2306, batch=2, x_dtype="bf16")]
 
 
 @pytest.mark.parametrize("w", GRP, ids=[w.name for w in GRP])
 def test_per_block_scales_on_token_blocks(w):
     for y in ("f32", "bf16"):
-        tl.grouped_case(w, with_bias=True, y_dtype=y)
+        tl.grouped_case(w, with_bias=True, y_dtype=y, routes=("group_blocks",))
+
+
+@pytest.mark.parametrize("w", GRP_LEVELS, ids=[w.name for w in GRP_LEVELS])
+def test_per_block_scales_level_by_level(w):
+    for y in ("f32", "bf16"):
+        tl.grouped_case(w, with_bias=True, y_dtype=y, routes=("-group_blocks",))
+
+
+# ---- the blocked forms take 16-byte aligned X and Y; others run level by level.  Codes are the same either way, so the two
+# halves of a layer may take different forms.
+ALIGN = [(_rag(3, 203, 1, batch=2, d_in=96, d_out=72), "any_length_blocks"),
+         (_rag(4, 300, 0, d_in=64, d_out=67, act_quant="asym", mean_shift=0.3, x_dtype="bf16"), "any_length_blocks"),
+         (_grp(64, 3, 64, 128, 130), "group_blocks"), (_grp(16, 4, 16, 64, 1026, batch=17, x_dtype="bf16"), "group_blocks")]
+
+
+@pytest.mark.parametrize("w,route", ALIGN, ids=[w.name for w, _ in ALIGN])
+def test_tensors_off_the_16_byte_grid(w, route):
+    import torch
+    import paper_2510_26771_amd as st
+
+    def off_by_one(t):
+        buf = torch.zeros(t.numel() + 1, dtype=t.dtype, device="cuda")
+        buf[1:] = t.reshape(-1)
+        return buf[1:].view(t.shape)
+
+    inp = tl.make_inputs(w, with_bias=True)
+    ora = (so.stamp_linear_forward_grouped(inp["X_f32"], inp["W"], w.xform, w.levels, w.k_hi, 64, w.bits_hi, w.bits_lo, w.bits_w,
+                                           w.grid_h, w.grid_w, inp["bias"]) if w.group_size else tl.run_oracle(w, inp))
+    X = tl.to_device_x(inp, w)
+    for y_dtype, ydt in (("f32", torch.float32), ("bf16", torch.int16)):
+        plan = st.StampPlan(tl.plan_desc_for(w, y_dtype), torch.from_numpy(inp["W"]).cuda(), torch.from_numpy(inp["bias"]).cuda())
+        tl.check_routes(plan, w, (route,))
+        ws = plan.alloc_workspace()
+        acts = []
+        for x in (X, off_by_one(X)):
+            q = plan.alloc_act_buffers()
+            q[0].zero_()
+            plan.quantize_act(x, *q, ws)
+            acts.append(q)
+            for aligned in (True, False):
+                Y = torch.zeros((w.batch, w.seq_len, w.d_out), dtype=ydt, device="cuda")
+                Y = Y if aligned else off_by_one(Y)
+                assert (Y.data_ptr() % 16 == 0) == aligned
+                plan.linear_forward(x, Y, ws)
+                Yq = torch.zeros_like(Y) if aligned else off_by_one(torch.zeros_like(Y))
+                plan.linear_forward_q(*q, Yq, ws)
+                torch.cuda.synchronize()
+                tl.check_output(tl.y_to_numpy(Y, y_dtype == "bf16"), ora["Y"], y_dtype == "bf16", f"{w.name} Y aligned={aligned}")
+                assert torch.equal(Y, Yq)
+        assert all(torch.equal(a, b) for a, b in zip(*acts)), "codes depend on the alignment of X"
+        plan.destroy()
 
 
 # ---- 4-bit rows' GEMM: both tile sizes (128 x 256 where that leaves fewer rounds, else 256 x 256), with one row more than a

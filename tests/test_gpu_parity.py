@@ -168,7 +168,55 @@ TOP_IN_GEMM = [
 
 @pytest.mark.parametrize("w", TOP_IN_GEMM, ids=[w.name for w in TOP_IN_GEMM])
 def test_top_levels_inverted_in_the_8bit_rows_gemm(w):
-    r = tl.full_case(w, with_bias=True)
+    r = tl.full_case(w, with_bias=True, hi_rows=1, routes=("hi_top_fused",))
+    assert r["code_mismatches"] == 0
+
+
+@pytest.mark.parametrize("w", TOP_IN_GEMM, ids=[w.name for w in TOP_IN_GEMM])
+def test_top_levels_inverted_by_the_kernel_of_the_rule(w):
+    """The same plans through whichever kernel the library takes for so little depth."""
+    r = tl.full_case(w, with_bias=True, check_acc=False, check_unfused=False)
+    assert r["code_mismatches"] == 0
+
+
+# 8-bit rows on the int8 pipeline with their depth in several parts (few tiles), and the kernel that adds the parts in each
+# kind of plan: top levels of the inverse, block sums alone, the first k_hi rows only, no transform.  More than 128 rows (up
+# to four parts of two K steps or more) and fewer (parts of four), both quantizer forms.
+SPLIT = [
+    _wl("split_top_1d_k64", batch=3, seq_len=512, levels=9, k_hi=64, d_in=1024, d_out=192, seed=171),
+    _wl("split_top_1d_k16_asym", batch=2, seq_len=256, levels=8, k_hi=16, d_in=1056, d_out=130, seed=172, act_quant="asym",
+        mean_shift=0.4),
+    _wl("split_top_2d_k16_b9_asym", batch=9, seq_len=256, xform="haar2d", levels=4, grid_h=16, grid_w=16, k_hi=16, d_in=544,
+        d_out=200, corr_len=4.0, seed=173, act_quant="asym", mean_shift=-0.3),
+    _wl("split_sums_1d_J3", batch=3, seq_len=512, levels=3, k_hi=64, d_in=1024, d_out=136, seed=174),
+    _wl("split_sums_2d_J2", batch=1, seq_len=1024, xform="haar2d", levels=2, grid_h=32, grid_w=32, k_hi=64, d_in=1088,
+        d_out=72, corr_len=6.0, seed=175),
+    _wl("split_own_1d_J3_k70_asym", batch=2, seq_len=1024, levels=3, k_hi=70, d_in=576, d_out=264, seed=176, act_quant="asym",
+        mean_shift=0.3),
+    _wl("split_own_2d_J2_k9", batch=3, seq_len=256, xform="haar2d", levels=2, grid_h=16, grid_w=16, k_hi=9, d_in=2080,
+        d_out=66, corr_len=4.0, seed=177),
+    _wl("split_ident_k80_asym", xform="identity", levels=0, batch=2, seq_len=200, k_hi=80, d_in=1024, d_out=257, seed=178,
+        act_quant="asym", mean_shift=0.6),
+    _wl("split_ident_k9", xform="identity", levels=0, batch=2, seq_len=33, k_hi=9, d_in=1024, d_out=64, seed=179),
+]
+
+
+@pytest.mark.parametrize("w", SPLIT, ids=[w.name for w in SPLIT])
+def test_8bit_rows_in_several_parts_of_the_depth(w):
+    r = tl.full_case(w, with_bias=True, hi_rows=1, routes=("hi_split",), check_unfused=w.xform != "identity")
+    assert r["code_mismatches"] == 0
+
+
+# the same in one piece (a depth too short to split) where the rows' way out is a kernel of its own
+WHOLE = [_wl("whole_ident_k80", xform="identity", levels=0, batch=2, seq_len=200, k_hi=80, d_in=160, d_out=257, seed=180),
+         _wl("whole_own_J3_k70", batch=2, seq_len=1024, levels=3, k_hi=70, d_in=160, d_out=264, seed=181),
+         _wl("whole_top_k16", batch=2, seq_len=256, levels=8, k_hi=16, d_in=160, d_out=130, seed=182)]
+
+
+@pytest.mark.parametrize("w", WHOLE, ids=[w.name for w in WHOLE])
+def test_8bit_rows_on_the_int8_pipeline_in_one_piece(w):
+    r = tl.full_case(w, with_bias=True, hi_rows=1, routes=("-hi_split", "-hi_fp6", "-hi_top_fused"),
+                     check_unfused=w.xform != "identity")
     assert r["code_mismatches"] == 0
 
 
@@ -471,16 +519,22 @@ def test_forward_under_hip_graph_capture():
     memset): it can be captured into a HIP graph, and every replay reproduces the eager result bit for bit."""
     import torch
     import paper_2510_26771_amd as st
-    for w in (_wl("graph_1d", batch=2, seq_len=512, levels=9, k_hi=16, d_in=160, d_out=300, seed=81),
-              _wl("graph_2d", batch=1, seq_len=256, xform="haar2d", levels=4, grid_h=16, grid_w=16, k_hi=4, d_in=96,
-                  d_out=128, seed=82, act_quant="asym"),
-              # no top levels, 4-bit approximations in the 4-bit rows' GEMM, the 8-bit rows' depth split (parts added by a kernel)
-              _wl("graph_1d_few", batch=2, seq_len=1024, levels=3, k_hi=8, d_in=1024, d_out=192, seed=85),
-              # the 8-bit rows' GEMM runs the top levels of the inverse itself
-              _wl("graph_1d_topfused", batch=3, seq_len=512, levels=9, k_hi=64, d_in=64, d_out=16640, seed=86)):
+    few = _wl("graph_1d_few", batch=2, seq_len=1024, levels=3, k_hi=8, d_in=1024, d_out=192, seed=85)
+    topfused = _wl("graph_1d_topfused", batch=3, seq_len=512, levels=9, k_hi=64, d_in=64, d_out=16640, seed=86)
+    for w, hi_rows, routes in (
+            (_wl("graph_1d", batch=2, seq_len=512, levels=9, k_hi=16, d_in=160, d_out=300, seed=81), 0, ("beside_top", "hi_fp6")),
+            (_wl("graph_2d", batch=1, seq_len=256, xform="haar2d", levels=4, grid_h=16, grid_w=16, k_hi=4, d_in=96,
+                 d_out=128, seed=82, act_quant="asym"), 0, ("hi_fp6",)),
+            # no top levels, 4-bit approximations in the 4-bit rows' GEMM, the 8-bit rows on either pipeline (int8: the depth
+            # split, parts added by a kernel)
+            (few, 0, ("direct", "hi_fp6")), (few, 1, ("hi_split",)),
+            # the 8-bit rows' GEMM runs the top levels of the inverse itself
+            (topfused, 0, ()), (topfused, 1, ("hi_top_fused",))):
         inp = make_inputs(w, with_bias=True)
         plan = st.StampPlan(tl.plan_desc_for(w, "bf16"), torch.from_numpy(inp["W"]).cuda(),
                             torch.from_numpy(inp["bias"]).cuda())
+        plan.set_choice("hi_rows", hi_rows)
+        tl.check_routes(plan, w, routes)
         X = tl.to_device_x(inp, w)
         ws = plan.alloc_workspace()
         Y_eager = torch.zeros((w.batch, w.seq_len, w.d_out), dtype=torch.int16, device="cuda")
