@@ -268,9 +268,15 @@ size_t stamp_hi6_bytes(const stamp_plan* p, int own) {
   return (size_t)((M + gr - 1) / gr) * (p->Kpad / 128) * (2 * hi6_np(M) * kBlock6);
 }
 
-// Plans that this kernel serves.  Every workgroup reads its rows' whole depth from L2, so with many rows and columns the
-// tiled int8 kernel, which shares them through LDS, wins: 512 x 4096 x 4096 (8.6e9) is 37 us here against 49 there, 512 x
-// 8192 x 28672 (1.2e11) at least 160 by the 25 MB of operands that every CU would load, against 134 measured there.
+// Plans that this kernel serves.  Every workgroup reads its rows' and columns' whole depth from L2, so its time goes with
+// the product M N d (about 2.3e14 a second); the tiled int8 kernel shares operands through LDS and splits a tile's depth
+// while it has few tiles: its time hardly grows until its tiles fill the CUs, but it needs a second launch (parts, top levels) or
+// its longer start.  Layers with int8 against FP6, microseconds.  Without transform, all M rows at 8 bits: 512 x 4096 x 4096 40,
+// 34, 1024 x 4096 x 4096 48, 57; 8192 x 1536 x 1536 75, 113; 2048 x 2048 x 2048 40, 45; 1024 x 2048 x 2048 36, 27; 4096 x
+// 1024 x 1024 38, 35, 8192: 47, 62; 4096 x 4096 x 512 38, 55.  64 top rows a sequence, top levels: 2048 x 2048 x 4096 212 against 258 at
+// depth 4096, 104 against 126 at depth 1024; 512 x 4096 x 4096 89, 76.  The lines fitted to 740 such pairs (M 192 .. 8192,
+// depth 192 .. 11008, d_out 256 .. 11008; five kinds of plan): M (d_out + 256) up to 6e6 and up to 1.2e6 + 7e9 / depth: 0.2 %
+// above always taking the better one on average (15 % at worst), where a bound of 2e10 on the product is 3.4 % (104 %).
 bool stamp_hi6_fits(const stamp_plan* p, int own) {
   const StampGeom& g = p->geom;
   const int M = hi6_rows(p, own);
@@ -278,7 +284,8 @@ bool stamp_hi6_fits(const stamp_plan* p, int own) {
   if (!g.ident && !own && g.L > 0 && (g.k > 128 || (g.k & (g.k - 1)) != 0)) return false;  // whole sequences per workgroup
   const int choice = p->dbg[STAMP_CHOICE_HI_ROWS];
   if (choice != 0) return choice == 2;
-  return M <= 128 || (double)M * g.N * g.d <= 2.0e10;
+  const double mn = (double)M * (g.N + 256);
+  return M <= 128 || (mn <= 6.0e6 && mn <= 1.2e6 + 7.0e9 / g.d);
 }
 
 StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own) {

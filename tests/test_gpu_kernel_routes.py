@@ -26,6 +26,33 @@ def _wl(name, **kw):
     return Workload(name, **base)
 
 
+# ---- which pipeline takes the 8-bit rows: sizes on either side of the rule, all of them where one form takes at least 1.2
+# times as long as the other (all tokens at 8 bits; 64 top rows a sequence with and without top levels; any length)
+HI_RULE = [(dict(xform="identity", levels=0, seq_len=8192, k_hi=8192, d_in=1536, d_out=1536), False),
+           (dict(xform="identity", levels=0, seq_len=2048, k_hi=2048, d_in=1152, d_out=4608), False),
+           (dict(xform="identity", levels=0, seq_len=4096, k_hi=4096, d_in=4096, d_out=512), False),
+           (dict(xform="identity", levels=0, seq_len=1024, k_hi=1024, d_in=2048, d_out=2048), True),
+           (dict(xform="identity", levels=0, seq_len=8192, k_hi=8192, d_in=256, d_out=256), True),
+           (dict(batch=32, seq_len=512, levels=9, k_hi=64, d_in=4096, d_out=4096), False),
+           (dict(batch=32, seq_len=512, levels=9, k_hi=64, d_in=512, d_out=4096), False),
+           (dict(batch=8, seq_len=512, levels=9, k_hi=64, d_in=2048, d_out=2048), True),
+           (dict(batch=32, seq_len=512, levels=3, k_hi=63, d_in=2048, d_out=4096), False),
+           (dict(batch=4, seq_len=512, levels=3, k_hi=63, d_in=4096, d_out=1024), True),
+           (dict(batch=64, seq_len=481, levels=3, k_hi=60, d_in=4096, d_out=2048, skip_first=True), False),
+           (dict(batch=8, seq_len=481, levels=3, k_hi=60, d_in=4096, d_out=1024, skip_first=True), True),
+           (dict(batch=2, seq_len=64, levels=6, k_hi=64, d_in=11008, d_out=11008), True)]  # up to 128 rows
+
+
+@pytest.mark.parametrize("kw,fp6", HI_RULE, ids=["-".join(str(v) for v in kw.values()) for kw, _ in HI_RULE])
+def test_rule_of_the_8bit_rows_pipeline(kw, fp6):
+    import torch
+    import paper_2510_26771_amd as st
+    w = _wl("rule", x_dtype="bf16", **kw)
+    plan = st.StampPlan(tl.plan_desc_for(w, "bf16"), torch.zeros((w.d_in, w.d_out), dtype=torch.float32, device="cuda"))
+    tl.check_routes(plan, w, ("hi_fp6" if fp6 else "-hi_fp6",))
+    plan.destroy()
+
+
 # ---- DCT of power-of-two lengths (FFT): odd and even numbers of radix-2 stages, one and several channels per
 # workgroup, the shortest length of the route and the longest of the library
 DCT = [_wl("dct_8", batch=2, xform="dct", levels=0, seq_len=8, k_hi=1, seed=201),
