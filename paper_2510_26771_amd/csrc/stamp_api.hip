@@ -491,17 +491,24 @@ stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, ui
 
 // stamp_linear_forward: the quantizer writes the FP6 operands itself (no packed codes, no conversion pass) on the default route:
 // FP6 engine, fused inverse (or none), 8-bit rows through the kernel for few rows.  Its stores are 8 bytes of 24-byte
-// fragments where packed codes are 4-byte words of whole lines: that costs what the conversion pass costs without its
-// launch, so it pays on small activations only, and only where a workgroup has few rows to store one after another (row
-// quantizers, 1-D blocks of 8 and 16 tokens, 8 x 8 blocks by sub-blocks).  Layers, microseconds, conversion pass against direct: 2048 tokens 4096 ->
-// 11008, 3 levels, first token left out 96.2, 91.1; 11008 -> 4096, 3 levels (block sums still by kernels of their own) 134.5, 130.5; DCT 4096 -> 4096 137, 131; 3 x 777
-// tokens 38.3, 35.1; but 1-D blocks of 32 (4096 -> 11008) 102.8, 103.3; 8 x 8 blocks one sub-block after another (1152 -> 4608) 74.1, 76.1; 8 x 4096 tokens,
-// blocks of 64 382, 407.  Beyond 2^25 elements the launch no longer counts: 4 x 8192 tokens 4096 -> 4096, 3 levels 359, 359,
-// WHT 1772, 1806.
+// fragments where packed codes are 4-byte words of whole lines; it pays while the conversion's launch counts, and where a
+// workgroup stores a few neighbouring rows, not one after another (1-D blocks of 8 and 16 tokens, 8 x 8 blocks by
+// sub-blocks; not 1-D blocks of 32, 4096 -> 11008: 102.8, 103.3, or 8 x 8 blocks one sub-block after another, 1152 -> 4608: 74.1,
+// 76.1).  Layers, microseconds, conversion pass against direct: 2048 tokens 4096 -> 11008, 3 levels, first token left out 96.2,
+// 91.1; 3 x 777 tokens 38.3, 35.1; with 256 outputs, blocks of 8: 65536 tokens x 512 50, 46, x 1024 72, 65, 32768 x 4096 135, 132,
+// 262144 x 256 110, 112, 65536 x 256 with 8192 8-bit rows 73, 81.  The row quantizer's workgroups hold one row each, whose fragments
+// share no line: 2048 x 4096 41.5, 38, 4096 x 2048 36, 33, but 8192 x 512 28, 29, 4096 x 256 all at 8 bits 19.4, 20.9, 32768 x 256
+// 45, 57, 262144 x 256 224, 337.  Lines fitted to 1210 such pairs (256 .. 262144 rows, depth 32 .. 11008).
+bool direct_pays(const stamp_plan* p) {
+  const StampGeom& g = p->geom;
+  const int64_t rows = (int64_t)g.B * g.s, hi = (int64_t)g.B * g.khi;
+  if (g.ident && !p->rag.on) return rows + hi <= 6144 && rows * g.d <= (1 << 24);
+  return rows + 16 * hi <= 140000 && rows * g.d <= (1 << 27);
+}
 bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
   const StampGeom& g = p->geom;
   if (!p->direct_ok || p->engine != STAMP_GEMM_FP6 || p->gen.group || p->dbg[STAMP_CHOICE_OPERANDS] == 1) return false;
-  if (p->dbg[STAMP_CHOICE_OPERANDS] == 0 && (int64_t)g.B * g.s * g.d > (1 << 25)) return false;
+  if (p->dbg[STAMP_CHOICE_OPERANDS] == 0 && !direct_pays(p)) return false;
   if (p->rag.on ? p->rag.r > 4 : (!g.ident && (g.is2d ? !stamp_bottom_quads(p) : g.r > 4))) return false;
   if (p->gen.kind != kGenNone || g.ident) return !p->rag.on || (rag_route(p, Y) && stamp_rag_quantizes(p, X) && p->hi6[0]);
   if (!p->fused_ok || p->unfused) return false;
@@ -511,11 +518,12 @@ bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
 
 // stamp_linear_forward, plans with top levels whose bottom kernel leaves packed codes: their conversion shares the launch of
 // the top levels, which do not need it, and the 8-bit rows' quantizer writes their operand (the layer's one conversion launch
-// less: 2048 tokens 4096 -> 11008, blocks of 32, 102.5 us, now 99.4).
+// less: 2048 tokens 4096 -> 11008, blocks of 32, 102.5 us, now 99.4).  Measured 2 to 12 us less from 512 to 131072 tokens and
+// depths of 64 to 4096; with 8192 8-bit rows, whose operand leaves in small pieces, no less at depth 256 and 5 more at 64.
 bool convert_beside_top(const stamp_plan* p) {
   const StampGeom& g = p->geom;
   return p->direct_ok && p->engine == STAMP_GEMM_FP6 && p->dbg[STAMP_CHOICE_OPERANDS] != 1 && p->gen.kind == kGenNone && !g.ident && p->fused_ok && !p->unfused && g.L > 0 &&
-         p->hi6[0];
+         p->hi6[0] && (int64_t)g.B * g.k <= 4096;
 }
 
 }  // namespace

@@ -53,6 +53,31 @@ def test_rule_of_the_8bit_rows_pipeline(kw, fp6):
     plan.destroy()
 
 
+# ---- who writes the FP6 operands: the quantizer, or a pass over packed codes (sizes where one form is at least 1.05 times as
+# fast: quantizers by rows, by blocks on a line, of any length, on a grid)
+OPERANDS = [(dict(xform="identity", levels=0, batch=32, seq_len=1024, k_hi=2, d_in=256), False),
+            (dict(xform="identity", levels=0, seq_len=4096, k_hi=4096, d_in=256), False),
+            (dict(xform="wht", levels=0, batch=64, seq_len=1024, k_hi=1, d_in=32), False),
+            (dict(xform="identity", levels=0, batch=2, seq_len=1024, k_hi=32, d_in=2048), True),
+            (dict(xform="wht", levels=0, batch=1, seq_len=1024, k_hi=64, d_in=512), True),
+            (dict(batch=64, seq_len=1024, k_hi=1, d_in=1024), True),
+            (dict(batch=256, seq_len=1024, k_hi=1, d_in=32), False),
+            (dict(batch=128, seq_len=512, levels=9, k_hi=64, d_in=256), False),
+            (dict(batch=128, seq_len=513, k_hi=1, d_in=512, skip_first=True), True),
+            (dict(xform="haar2d", batch=4, seq_len=1024, grid_h=32, grid_w=32, k_hi=16, d_in=512), True),
+            (dict(batch=2, seq_len=1024, levels=10, k_hi=32, d_in=512), False)]  # blocks of 32: packed
+
+
+@pytest.mark.parametrize("kw,direct", OPERANDS, ids=["-".join(str(v) for v in kw.values()) for kw, _ in OPERANDS])
+def test_rule_of_the_operands(kw, direct):
+    import torch
+    import paper_2510_26771_amd as st
+    w = _wl("operands", x_dtype="bf16", d_out=256, **kw)
+    plan = st.StampPlan(tl.plan_desc_for(w, "bf16"), torch.zeros((w.d_in, w.d_out), dtype=torch.float32, device="cuda"))
+    tl.check_routes(plan, w, ("direct" if direct else "-direct",))
+    plan.destroy()
+
+
 # ---- DCT of power-of-two lengths (FFT): odd and even numbers of radix-2 stages, one and several channels per
 # workgroup, the shortest length of the route and the longest of the library
 DCT = [_wl("dct_8", batch=2, xform="dct", levels=0, seq_len=8, k_hi=1, seed=201),
