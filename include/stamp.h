@@ -209,7 +209,7 @@ stamp_status_t stamp_linear_forward(const stamp_plan_t* plan, const void* X_dev,
  * scratch memory is a static device array of STAMP_STATIC_SCRATCH_BYTES inside the library (one per GPU, held
  * until the process ends) instead of a caller workspace.  The call allocates nothing.  A plan whose
  * stamp_plan_workspace_bytes exceeds STAMP_STATIC_SCRATCH_BYTES is refused with STAMP_ERR_WORKSPACE before
- * anything is launched.  Every call on one GPU shares that GPU's array: calls that overlap in time on one GPU
+ * anything is launched (up to 2 MiB more are taken where a few 8-bit rows' operand lies behind everything else).  Every call on one GPU shares that GPU's array: calls that overlap in time on one GPU
  * (different streams or threads) race; issue them on one stream, or order them with events.  Nothing in the
  * array has to be cleared between calls (each call writes what it later reads). */
 #define STAMP_STATIC_SCRATCH_BYTES ((size_t)64 << 20)

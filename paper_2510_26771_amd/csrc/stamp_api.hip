@@ -8,7 +8,10 @@
 
 // Scratch memory of stamp_linear_forward_static: one array per GPU, part of the loaded code object.  In host
 // code this name only stands for the symbol; the device address comes from hipGetSymbolAddress (static_scratch()).
-static __device__ __align__(256) unsigned char scratch[STAMP_STATIC_SCRATCH_BYTES];
+// Behind the documented size: room for the FP6 operand of up to 128 8-bit rows, at most 32 rows x 32768 channels x 1.5 bytes
+// where nothing else in the workspace is large enough to hold it (place_hi6).
+constexpr size_t kHi6Tail = (size_t)2 << 20;
+static __device__ __align__(256) unsigned char scratch[STAMP_STATIC_SCRATCH_BYTES + kHi6Tail];
 
 namespace {
 
@@ -241,6 +244,22 @@ void rag_geometry(stamp_plan* p) {
   p->bgeom.k = r.nb;
 }
 
+// Where the 8-bit rows' FP6 operand lies: over a region that is free by then, or (a dozen rows or fewer, the operand is padded
+// to 32; narrow layers, padded to 128 channels) behind everything else.  stamp_linear_forward_static keeps taking the plans
+// whose workspace without it fits: beyond kHi6Tail it must not push them out.
+void place_hi6(stamp_plan* p, size_t region, size_t room) {
+  const size_t base = p->ws_base;
+  p->ws_total = base;
+  for (int own = 0; own < 2; ++own) {
+    if (!p->hi6[own]) continue;
+    const size_t need = stamp_hi6_bytes(p, own);
+    if (need <= room) continue;
+    if (need > kHi6Tail && base <= STAMP_STATIC_SCRATCH_BYTES && align256(base + need) > STAMP_STATIC_SCRATCH_BYTES) p->hi6[own] = 0;
+    else if (p->ws_total < align256(base + need)) p->ws_total = align256(base + need);
+  }
+  p->ws_hi6 = p->ws_total > base ? base : region;
+}
+
 void layout_workspace(stamp_plan* p) {
   const StampGeom& g = p->geom;
   size_t off = 0;
@@ -259,14 +278,14 @@ void layout_workspace(stamp_plan* p) {
     for (size_t& o : p->ws_Yt) o = take((size_t)g.B * g.s * g.N * sizeof(float));
     p->ws_codes8 = take(grouped ? (size_t)g.B * g.s * g.d : 0);
     p->ws_scalesg = take(grouped ? (size_t)g.B * g.s * (g.d / 64) * sizeof(float) : 0);
-    p->ws_total = off;
+    p->ws_base = off;
+    p->hi6[0] = stamp_hi6_fits(p, 0);
+    p->hi6[1] = 0;
+    place_hi6(p, p->ws_T[2], p->ws_Yt[0] - p->ws_T[2]);
     // the blocked form uses neither the fp32 copies of the activation nor those of the output: its rows in block order
     // lie over the former, its block sums over the latter (a plan for which they do not fit keeps the level kernels)
     p->ws_ba6 = p->ws_T[0];
     p->ws_bP = p->ws_Yt[0];
-    p->ws_hi6 = p->ws_T[2];
-    p->hi6[0] = stamp_hi6_fits(p, 0) && stamp_hi6_bytes(p, 0) <= p->ws_Yt[0] - p->ws_T[2];
-    p->hi6[1] = 0;
     p->direct_ok = !grouped && (g.k == 0 || (p->hi6[0] && stamp_hi6_bytes(p, 0) <= p->ws_scales - p->ws_qhi));
     if (p->rag.on && (stamp_rag_a6_bytes(p) > p->ws_T[2] - p->ws_T[0] ||
                       (size_t)g.B * g.khi * p->Npad * sizeof(float) > p->ws_codes8 - p->ws_Yt[0]))
@@ -303,18 +322,9 @@ void layout_workspace(stamp_plan* p) {
   p->ws_a6 = take(stamp_a6_bytes(p));
   p->ws_ytlo = off;
   if (p->unfused || !p->fused_ok) take((size_t)g.B * g.s * g.N * sizeof(float));
-  p->ws_total = off;
-  // The 8-bit rows' FP6 operand lies over the quantizer's scratch, which is free by then, or (a dozen rows or fewer, the
-  // operand is padded to 32) behind everything else, unless that would put the plan beyond the static scratch array.
-  for (int own = 0; own < 2; ++own) {
-    p->hi6[own] = stamp_hi6_fits(p, own);
-    if (!p->hi6[own]) continue;
-    const size_t need = stamp_hi6_bytes(p, own);
-    if (need <= p->ws_qhi - p->ws_abot) continue;
-    if (off <= STAMP_STATIC_SCRATCH_BYTES && align256(off + need) > STAMP_STATIC_SCRATCH_BYTES) p->hi6[own] = 0;
-    else if (p->ws_total < align256(off + need)) p->ws_total = align256(off + need);
-  }
-  p->ws_hi6 = p->ws_total > off ? off : p->ws_abot;
+  p->ws_base = off;
+  for (int own = 0; own < 2; ++own) p->hi6[own] = stamp_hi6_fits(p, own);
+  place_hi6(p, p->ws_abot, p->ws_qhi - p->ws_abot);  // over the quantizer's scratch
   // written by the quantizer itself it lies over the packed codes, which are not used then
   const size_t room = p->ws_scales - p->ws_qhi;
   p->direct_ok = (g.ident && g.k == 0) || ((p->hi6[0] || p->hi6[1]) && stamp_hi6_bytes(p, 0) <= room && stamp_hi6_bytes(p, 1) <= room);
@@ -766,11 +776,11 @@ stamp_status_t stamp_linear_forward(const stamp_plan_t* p, const void* X, void* 
 
 stamp_status_t stamp_linear_forward_static(const stamp_plan_t* p, const void* X, void* Y, void* hip_stream) {
   if (p == nullptr || X == nullptr || Y == nullptr) return STAMP_ERR_NULL;
-  if (p->ws_total > STAMP_STATIC_SCRATCH_BYTES) return STAMP_ERR_WORKSPACE;  // the plan needs more than the static array holds
+  if (p->ws_base > STAMP_STATIC_SCRATCH_BYTES) return STAMP_ERR_WORKSPACE;  // the plan needs more than the static array holds
   void* ws = nullptr;
   const stamp_status_t ss = static_scratch(&ws);
   if (ss != STAMP_OK) return ss;
-  return stamp_linear_forward(p, X, Y, ws, STAMP_STATIC_SCRATCH_BYTES, hip_stream);
+  return stamp_linear_forward(p, X, Y, ws, STAMP_STATIC_SCRATCH_BYTES + kHi6Tail, hip_stream);
 }
 
 stamp_status_t stamp_inverse(const stamp_plan_t* p, const float* Yt, int32_t n_cols, void* Y, void* ws, size_t ws_bytes,

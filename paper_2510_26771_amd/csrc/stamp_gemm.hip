@@ -466,8 +466,8 @@ bool stamp_hi_wide_tiles(int M, int Npad) {
 // is split (then the partial rows go through the top inverse like any others: it adds the parts and moves nothing).
 bool stamp_hi_rows_are_block_sums(const stamp_plan* p) { return !p->geom.ident && p->geom.L == 0 && p->hi_ksplit <= 1; }
 
-// up to this many 8-bit rows over the whole batch the depth is split for one workgroup per CU (k_gemm over them only
-// runs where the FP6 kernel for few rows, stamp_hi6.hip, has no room in the plan's scratch)
+// up to this many 8-bit rows over the whole batch the depth is split for one workgroup per CU (by rule the FP6 kernel,
+// stamp_hi6.hip, takes them; k_gemm only where a test says so)
 constexpr int kHiFewRows = 128;
 
 // Plans with top levels whose 8-bit rows' GEMM keeps its depth in one piece and runs the tiled kernel: a tile of 256

@@ -196,6 +196,7 @@ struct stamp_plan {
   size_t ws_ba6, ws_bP;     // blocked form: the 4-bit rows in block order (over ws_T), the block sums (over ws_Yt)
   // workspace layout (byte offsets, 256-aligned)
   size_t ws_abot, ws_rowmax, ws_gpart, ws_qhi, ws_qlo, ws_scales, ws_ythi, ws_P, ws_a6, ws_ytlo, ws_total;
+  size_t ws_base;           // ws_total without an 8-bit operand behind everything else
 };
 
 // Dynamic-LDS limit of a kernel, raised once per device and kernel (the attribute belongs to the device's

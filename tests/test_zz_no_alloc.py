@@ -65,3 +65,34 @@ def test_static_scratch_refuses_plans_beyond_its_size():
         plan.linear_forward_static(X, Y)
     assert e.value.status == 4
     plan.destroy()
+
+
+@pytest.mark.parametrize("w", [
+    # no larger region to lie over: few tokens, few channels
+    _wl("few_rows_dct_40", seq_len=40, xform="dct", levels=0, k_hi=3, d_in=32, d_out=128, x_dtype="f32", seed=101),
+    _wl("few_rows_wht_4", batch=4, seq_len=4, xform="wht", levels=0, k_hi=4, d_in=32, d_out=408, seed=102),
+    _wl("few_rows_skip_18", batch=5, seq_len=18, levels=1, k_hi=18, d_in=64, d_out=63, x_dtype="f32", skip_first=True, seed=103),
+    # 30 KB of the 64 MiB left, the operand of 8 rows needs 384 KB
+    _wl("few_rows_at_the_limit", seq_len=6400, xform="identity", levels=0, k_hi=8, d_in=8192, d_out=7168, seed=104)],
+    ids=lambda w: w.name)
+def test_few_8bit_rows_keep_their_kernel_whatever_the_room(w):
+    """Up to 128 8-bit rows run on the FP6 kernel even where its operand fits no region of the workspace, and the entry point
+    on the static scratch takes every plan that it took without that operand."""
+    import torch
+    import paper_2510_26771_amd as st
+    inp = make_inputs(w, with_bias=True)
+    plan = st.StampPlan(st.plan_desc_for(w, "f32"), torch.from_numpy(inp["W"]).cuda(), torch.from_numpy(inp["bias"]).cuda())
+    assert "hi_fp6" in plan.routes()
+    plan.set_choice("hi_rows", 1)
+    assert plan.workspace_bytes() <= st.binding.STAMP_STATIC_SCRATCH_BYTES
+    X = st.to_device_x(inp, w)
+    Y_int8, Y_ws, Y = (torch.full((w.batch, w.seq_len, w.d_out), float("nan"), dtype=torch.float32, device="cuda") for _ in range(3))
+    plan.linear_forward(X, Y_int8, plan.alloc_workspace())
+    plan.set_choice("hi_rows", 0)
+    plan.linear_forward(X, Y_ws, plan.alloc_workspace())
+    plan.linear_forward_static(X, Y)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, Y_ws), "static scratch and caller workspace disagree"
+    # the integer sums are the same; the int8 kernel adds up to four dequantized parts, each rounded to fp32
+    assert float((Y - Y_int8).abs().max()) <= 8 * 2.0 ** -24 * w.seq_len ** 0.5 * float(Y.abs().max())
+    plan.destroy()
