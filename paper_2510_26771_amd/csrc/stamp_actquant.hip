@@ -255,9 +255,9 @@ __global__ __launch_bounds__(256) void k_quant_rows(const void* __restrict__ X, 
     scales[m] = scale;
     if constexpr (ASYM) scales[zeros_off + m] = z;
   }
-  for (int cb = 0; cb < d; cb += 256 * 8) {  // whole quads of threads stay together
-    const int c = cb + tid * 8;
-    if (!OUT6 && c >= d) break;
+  // OUT6: whole quads of threads stay together (a loop that every thread leaves at the same time costs narrow rows in
+  // packed form 15 us in 75: 7 x 16384 tokens x 32, fp32)
+  for (int c = tid * 8; (OUT6 ? c - tid * 8 : c) < d; c += 256 * 8) {
     float v[8];
     load8(X, xoff + (OUT6 ? min(c, d - 8) : c), BF16, true, v);
     if (hi) {
