@@ -301,13 +301,14 @@ stamp_status_t stamp_debug_set_choice(stamp_plan_t* plan, int32_t choice, int32_
 typedef enum {
   STAMP_ROUTE_GENERAL = 1,            /* the general path */
   STAMP_ROUTE_ANY_LENGTH_BLOCKS = 2,  /* its 1-D Haar transform block by block, inverse in the GEMM's epilogue */
-  STAMP_ROUTE_GROUP_BLOCKS = 4,       /* per-block scales on blocks of a token grid, likewise */
+  STAMP_ROUTE_GROUP_BLOCKS = 4,       /* per-block scales on blocks of a token grid: inverse in the GEMM's epilogue */
   STAMP_ROUTE_DIRECT = 8,             /* the quantizer writes the FP6 operands */
   STAMP_ROUTE_BESIDE_TOP = 16,        /* packed codes are converted in the launch of the top levels */
   STAMP_ROUTE_HI_FP6 = 32,            /* 8-bit rows on the FP6 pipeline */
   STAMP_ROUTE_HI_TOP_FUSED = 64,      /* 8-bit rows on the int8 pipeline, top levels of the inverse in the epilogue */
   STAMP_ROUTE_HI_SPLIT = 128,         /* 8-bit rows on the int8 pipeline in several parts of the depth */
-  STAMP_ROUTE_TILES_128 = 256         /* 4-bit rows in 128 x 256 tiles instead of 256 x 256 */
+  STAMP_ROUTE_TILES_128 = 256,        /* 4-bit rows in 128 x 256 tiles instead of 256 x 256 */
+  STAMP_ROUTE_GROUP_QUANT = 512       /* per-block scales on blocks of a token grid: transform and quantizer in one kernel */
 } stamp_route_t;
 int32_t stamp_debug_routes(const stamp_plan_t* plan);
 

@@ -197,13 +197,17 @@ stamp_status_t validate(const stamp_plan_desc_t* d, StampGeom* g, int* fused_ok,
 
 // Per-block scales on a 2-D Haar transform with the fast path's block structure (4 x 4 or 8 x 8 token blocks; top levels over
 // at most 8 x 8 block sums, which a lane of their kernel holds), even d_out (the epilogue stores pairs), bias after the
-// inverse.  Everything else runs level by level, and so do small layers, whose few GEMM tiles of 256 x 128 leave CUs idle for
-// a whole tile's depth.  Microseconds, level by level against this form: with top levels, 1024 tokens 512 -> 512 (16 tiles)
-// 27.6, 35.0; 4608 -> 1152 (40) 90.6, 96.1; 2048 tokens 896 -> 1608 (112) 43.1, 43.9; 1024 tokens 1152 -> 4608 (144) 52.5,
-// 47.0; without, 4096 tokens 512 -> 512 (64) 37.6, 29.2.
+// inverse.  Everything else runs level by level, and so do small layers: the quantizer by blocks, level by level against this
+// form (whole layers, microseconds), with top levels, 1024 tokens 512 -> 512 27.6, 35.0; 4608 -> 1152 90.6, 96.1; 2048 tokens
+// 896 -> 1608 (112 tiles of 256 x 128) 43.1, 43.9; 1024 tokens 1152 -> 4608 (144) 52.5, 47.0; without, 4096 tokens 512 -> 512
+// (64) 37.6, 29.2.
+// The GEMM with the inverse in its epilogue needs tiles for the CUs, as every tile walks its whole depth, and d_out that is
+// worth the conversion of all codes.  linear_forward_q, level by level against this form: 1152 channels, 8192 tokens 512 outputs
+// (128 tiles) 31.7, 36.6, 768 (192) 39.7, 36.3; 4096 tokens 1024 (128) 35.3, 34.7; 2048 tokens 2304 (144) 40.6, 35.0; 4 x 4 blocks,
+// 16384 tokens 384 (192) 37.3, 40.0, 512 (256) 41.5, 40.7.
 void grp_geometry(stamp_plan* p) {
   const stamp_plan_desc_t& d = p->desc;
-  p->grp = 0;
+  p->grp_quant = p->grp = 0;
   if (p->gen.kind != kGenHaar2d || p->gen.group != 64 || p->gen.bias_mode != 0 || d.grid_h != d.grid_w || d.d_out % 2 != 0) return;
   StampGeom g = p->geom;
   g.J = d.levels;
@@ -213,10 +217,11 @@ void grp_geometry(stamp_plan* p) {
   if (fast_geometry(&d, &g, &fused, d.grid_h) != STAMP_OK || !fused) return;
   if (g.L > 0 && g.k > 64) return;
   if (g.s % 64 != 0 || g.khi < 1) return;
-  const int64_t rows = (int64_t)g.B * g.s, tiles = (rows + 255) / 256 * ((d.d_out + 255) / 256 * 2);
-  if (tiles < 128 && (g.L > 0 || rows < 4096)) return;
+  const int64_t rows = (int64_t)g.B * g.s, mt = (rows + 255) / 256, tiles = mt * ((d.d_out + 127) / 128);
+  if (mt * ((d.d_out + 255) / 256 * 2) < 128 && (g.L > 0 || rows < 4096)) return;
   p->bgeom = g;
-  p->grp = 1;
+  p->grp_quant = 1;
+  p->grp = tiles >= (g.R == 16 ? 256 : 192) || (tiles >= 128 && d.d_out >= 1024);
 }
 
 // Blocked form of a plan of the general path (1-D Haar of any length): per-token scales, bias after the inverse, 3 to 6
@@ -490,7 +495,7 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
 // general path, steps 1-2: forward transform level by level, then the row quantizer
 stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, void* ws, hipStream_t st,
                             const StampDirect* dir = nullptr) {
-  if (p->grp && (reinterpret_cast<uintptr_t>(X) & 15) == 0)
+  if (p->grp_quant && (reinterpret_cast<uintptr_t>(X) & 15) == 0)
     return stamp_launch_grp_quant(p, X, q_hi, scales, reinterpret_cast<float*>(at(ws, p->ws_T[0])), st) == hipSuccess ? STAMP_OK
                                                                                                                      : STAMP_ERR_DEVICE;
   if (stamp_rag_quantizes(p, X))
@@ -695,6 +700,7 @@ int32_t stamp_debug_routes(const stamp_plan_t* p) {
   const bool own = own_top(p), rag = rag_route(p, aligned);
   int32_t r = 0;
   if (p->gen.kind != kGenNone) r |= STAMP_ROUTE_GENERAL;
+  if (p->grp_quant) r |= STAMP_ROUTE_GROUP_QUANT;
   if (p->grp) r |= STAMP_ROUTE_GROUP_BLOCKS;
   if (rag) r |= STAMP_ROUTE_ANY_LENGTH_BLOCKS;
   if (p->gen.group) return r;

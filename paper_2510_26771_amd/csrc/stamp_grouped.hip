@@ -363,7 +363,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm6_grp(const GrpGemm ga) {
   const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, kg = lane >> 5;
   const int KT = a.Kpad / BK;
   int tm, tn;
-  tile_of_block(a.M, a.Npad, 128, tm, tn);
+  tile_of_block(a.M, (a.N + 127) / 128 * 128, 128, tm, tn);
   const int m0 = tm * BM, nw = tn * 128 + wn * 64;
   const uint8_t *gA = a.A + (size_t)tm * KT * kStageA6, *gB = a.Bq + (size_t)tn * KT * kStageB6;
   const uint8_t *gSA = reinterpret_cast<const uint8_t*>(ga.sa) + (size_t)tm * KT * 2048,
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm6_grp(const GrpGemm ga) {
 
 template <int RB, bool YBF16>
 hipError_t launch_grp(const GrpGemm& ga, hipStream_t st) {
-  const int tiles = ((ga.a.M + BM - 1) / BM) * (ga.a.Npad / 128);
+  const int tiles = ((ga.a.M + BM - 1) / BM) * ((ga.a.N + 127) / 128);  // Npad may end in a tile without columns
   static size_t lds_done[kStampMaxDevices] = {};
   const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gemm6_grp<RB, YBF16>), 2 * kGrpStage, lds_done);
   if (e != hipSuccess) return e;

@@ -183,7 +183,8 @@ struct stamp_plan {
   double* dct_dev;          // general path, DCT: [s][s] orthonormal DCT-II matrix
   int8_t* qWg_dev;          // per-block scales: weight codes [Npad128][d_in] int8
   float* swg_dev;           // per-block scales: [d_in / 64][Npad128]
-  int32_t grp;              // per-block scales on the blocked 2-D Haar transform (stamp_grouped.hip), geometry in bgeom
+  // per-block scales on the blocked 2-D Haar transform (stamp_grouped.hip), geometry in bgeom: quantizer, GEMM with inverse
+  int32_t grp_quant, grp;
   uint8_t* qWg6_dev;        // its weights as FP6 operand and their scales
   float* swg6_dev;
   size_t ws_grp[4];         // its scratch (over ws_T, ws_Yt)

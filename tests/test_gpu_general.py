@@ -321,7 +321,7 @@ def test_general_path_under_hip_graph_capture_and_static_scratch():
             (_wl("graph_g64_2d", seq_len=256, xform="haar2d", levels=3, grid_h=16, grid_w=16, k_hi=4, d_in=128,
                  d_out=130, group_size=64, seed=82), 0, ("-group_blocks",)),
             (_wl("graph_g64_blocks", seq_len=4096, xform="haar2d", levels=3, grid_h=64, grid_w=64, k_hi=64, d_in=128,
-                 d_out=130, group_size=64, seed=84), 0, ("group_blocks",)),
+                 d_out=1026, group_size=64, seed=84), 0, ("group_blocks",)),
             (_wl("graph_g64_blocks_top", batch=17, seq_len=256, xform="haar2d", levels=4, grid_h=16, grid_w=16, k_hi=16, d_in=128,
                  d_out=1026, group_size=64, seed=85), 0, ("group_blocks",)),
             (_wl("graph_dct_fft", seq_len=256, xform="dct", levels=0, k_hi=8, seed=86), 0, ()),

@@ -213,31 +213,44 @@ GRP_LEVELS = [_grp(64, 3, 64, 192, 131), _grp(32, 3, 64, 64, 258, batch=2, x_dty
               _grp(64, 6, 64, 128, 514), _grp(32, 2, 16, 128, 192, x_dtype="bf16"), _grp(32, 3, 4, 256, 128), _grp(8, 1, 4, 64, 64),
               _grp(8, 3, 4, 192, 200, batch=5), _grp(16, 2, 16, 448, 64, batch=9), _grp(32, 3, 64, 128, 131)]
 # (the sizes from which on the block kernels serve such plans: smaller ones, and odd widths, run level by level)
-GRP = [_grp(64, 3, 64, 192, 130), _grp(32, 5, 64, 320, 1410, batch=3), _grp(64, 6, 64, 128, 1026),
-       _grp(32, 3, 64, 64, 2050, batch=2, x_dtype="bf16"), _grp(8, 3, 4, 192, 1026, batch=70), _grp(16, 2, 16, 448, 64, batch=17),
-       _grp(32, 3, 4, 256, 128, batch=4), _grp(32, 2, 16, 128, 192, batch=5, x_dtype="bf16"),
+GRP = [_grp(64, 3, 64, 192, 1026), _grp(32, 5, 64, 320, 1410, batch=3), _grp(64, 6, 64, 128, 1026),
+       _grp(32, 3, 64, 64, 2050, batch=2, x_dtype="bf16"), _grp(8, 3, 4, 192, 1026, batch=70), _grp(16, 2, 16, 448, 1026, batch=17),
+       _grp(32, 3, 4, 256, 1026, batch=4), _grp(32, 2, 16, 128, 1090, batch=4, x_dtype="bf16"),
        # top levels over 4 x 4 block sums, to the last one and not; at most 32 8-bit rows over the batch
        _grp(16, 4, 16, 128, 1026, batch=17), _grp(16, 3, 16, 320, 1290, batch=15, x_dtype="bf16"),
-       _grp(32, 4, 16, 192, 2050, batch=2), _grp(32, 5, 16, 64, 2306, batch=2, x_dtype="bf16")]
+       _grp(32, 4, 16, 192, 2050, batch=2), _grp(32, 5, 16, 64, 2306, batch=2, x_dtype="bf16"),
+       # the last 256 columns of the stored weights hold one tile of outputs and one of nothing
+       _grp(16, 2, 16, 64, 66, batch=256, x_dtype="bf16")]
 
 
 @pytest.mark.parametrize("w", GRP, ids=[w.name for w in GRP])
 def test_per_block_scales_on_token_blocks(w):
     for y in ("f32", "bf16"):
-        tl.grouped_case(w, with_bias=True, y_dtype=y, routes=("group_blocks",))
+        tl.grouped_case(w, with_bias=True, y_dtype=y, routes=("group_blocks", "group_quant"))
+
+
+# blocks for the quantizer only: too few tiles for the GEMM with the inverse
+GRP_QUANT = [_grp(64, 3, 64, 192, 130), _grp(16, 2, 16, 448, 64, batch=17), _grp(32, 3, 4, 256, 128, batch=4),
+             _grp(32, 2, 16, 128, 192, batch=5, x_dtype="bf16"), _grp(64, 6, 64, 64, 510, batch=2, x_dtype="bf16")]
+
+
+@pytest.mark.parametrize("w", GRP_QUANT, ids=[w.name for w in GRP_QUANT])
+def test_per_block_scales_quantized_on_token_blocks(w):
+    for y in ("f32", "bf16"):
+        tl.grouped_case(w, with_bias=True, y_dtype=y, routes=("-group_blocks", "group_quant"))
 
 
 @pytest.mark.parametrize("w", GRP_LEVELS, ids=[w.name for w in GRP_LEVELS])
 def test_per_block_scales_level_by_level(w):
     for y in ("f32", "bf16"):
-        tl.grouped_case(w, with_bias=True, y_dtype=y, routes=("-group_blocks",))
+        tl.grouped_case(w, with_bias=True, y_dtype=y, routes=("-group_blocks", "-group_quant"))
 
 
 # ---- the blocked forms take 16-byte aligned X and Y; others run level by level.  Codes are the same either way, so the two
 # halves of a layer may take different forms.
 ALIGN = [(_rag(3, 203, 1, batch=2, d_in=96, d_out=72), "any_length_blocks"),
          (_rag(4, 300, 0, d_in=64, d_out=67, act_quant="asym", mean_shift=0.3, x_dtype="bf16"), "any_length_blocks"),
-         (_grp(64, 3, 64, 128, 130), "group_blocks"), (_grp(16, 4, 16, 64, 1026, batch=17, x_dtype="bf16"), "group_blocks")]
+         (_grp(64, 3, 64, 128, 1026), "group_blocks"), (_grp(16, 4, 16, 64, 1026, batch=17, x_dtype="bf16"), "group_blocks")]
 
 
 @pytest.mark.parametrize("w,route", ALIGN, ids=[w.name for w, _ in ALIGN])
