@@ -900,6 +900,9 @@ namespace {
 // N <= 16384, which is also the longest DCT of the library); other lengths take the dense product.
 bool dct_has_fft(int s) { return s >= 8 && s <= 16384 && (s & (s - 1)) == 0; }
 
+// Lengths 2^J whose WHT runs in one pass, which computes its slots; others read them from a table.
+bool wht_in_one_pass(int J) { return J >= 6 && J <= 12; }
+
 // l = L 1 in fp32, following the forward transform's operation order (host)
 std::vector<float> ell_of(const stamp_plan* p) {
   const StampGen& gn = p->gen;
@@ -973,18 +976,14 @@ hipError_t stamp_gen_plan_tables(stamp_plan* p, const float* W, hipStream_t st) 
   const int s = g.s;
   hipError_t e = hipSuccess;
   if (gn.kind == kGenWht) {
-    // STaMP slot q (sequency q) takes row rev(gray(q)) of the Hadamard-ordered result: stored inverted, the slot of
-    // every row, for the scatter of the transform's last pass
+    // the slot of every row of the Hadamard-ordered result, for the scatter of the last of several passes
     int J = 0;
     while ((1 << J) < s) ++J;
-    std::vector<int32_t> inv(s);
-    for (int q = 0; q < s; ++q) {
-      const int gr = q ^ (q >> 1);
-      int rev = 0;
-      for (int b = 0; b < J; ++b) rev |= ((gr >> b) & 1) << (J - 1 - b);
-      inv[rev] = q;
+    if (!wht_in_one_pass(J)) {
+      std::vector<int32_t> inv(s);
+      for (int r = 0; r < s; ++r) inv[r] = wht_slot(r, J);
+      if ((e = upload(&p->perm_dev, inv, st)) != hipSuccess) return e;
     }
-    if ((e = upload(&p->perm_dev, inv, st)) != hipSuccess) return e;
   }
   if (gn.kind == kGenDct && dct_has_fft(s)) {
     // e^{-2 pi i k / M}, k < M; e^{-i pi k / 2N}, k <= M; e^{-2 pi i k / N}, k <= M (M = N / 2)
@@ -1045,9 +1044,8 @@ void launch_wht(dim3 grid, hipStream_t st, const void* in, int in_kind, float* o
   hipLaunchKernelGGL(k_gen_wht<NLEV>, grid, dim3(rows_block(ld, grid.y, grid.z)), 0, st, in, in_kind, out, Y, out_kind, inv_perm, norm, bias, y_bf16, s, ld, h_lo);
 }
 
-// WHT of 2^J tokens, 6 <= J <= 12, in one pass.  Channels per workgroup: what 132 KB of LDS hold (64 at most), fewer
-// while the chip is short of workgroups, down to 16 (whole 64-byte runs of fp32 rows; 4096 tokens: 8).
-bool wht_in_one_pass(int J) { return J >= 6 && J <= 12; }
+// WHT of 2^J tokens in one pass.  Channels per workgroup: what 132 KB of LDS hold (64 at most), fewer while the chip is
+// short of workgroups, down to 16 (whole 64-byte runs of fp32 rows; 4096 tokens: 8).
 template <int N1, int N2>
 hipError_t launch_wht_lds_n(const stamp_plan* p, const void* in, int in_kind, float* out, void* Y, int out_kind, float norm,
                             const float* bias, int ld, hipStream_t st) {

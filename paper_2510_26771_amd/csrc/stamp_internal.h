@@ -178,7 +178,7 @@ struct stamp_plan {
   StampGen gen;             // general path (kind != kGenNone)
   StampRag rag;             // general path, 1-D Haar of any length: blocked form (rag.on), geometry in bgeom
   StampGeom bgeom;
-  int32_t* perm_dev;        // general path, WHT: [s] STaMP slot of every row of the Hadamard-ordered result
+  int32_t* perm_dev;        // general path, WHT in several passes: [s] STaMP slot of every row of the Hadamard-ordered result
   float* ell_dev;           // general path, transformed bias: [s] l = L 1
   double* dct_dev;          // general path, DCT: [s][s] orthonormal DCT-II matrix
   int8_t* qWg_dev;          // per-block scales: weight codes [Npad128][d_in] int8
