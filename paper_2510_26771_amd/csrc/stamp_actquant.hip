@@ -349,7 +349,7 @@ bool stamp_top_in_bottom(const stamp_plan* p) {
 
 bool stamp_bottom_quads(const stamp_plan* p) {
   const StampGeom& g = p->geom;
-  return !g.ident && g.is2d && g.r == 3 && g.d <= 1536 && g.B * g.k <= 512;
+  return !g.ident && g.is2d && g.r == 3 && g.d <= 1536 && g.B * g.k <= 2 * stamp_device_cus();
 }
 
 int stamp_actquant_nsplit(const stamp_plan* p) {

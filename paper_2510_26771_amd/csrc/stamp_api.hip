@@ -517,12 +517,12 @@ stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, ui
 // 76.1).  Layers, microseconds, conversion pass against direct: 2048 tokens 4096 -> 11008, 3 levels, first token left out 96.2,
 // 91.1; 3 x 777 tokens 38.3, 35.1; with 256 outputs, blocks of 8: 65536 tokens x 512 50, 46, x 1024 72, 65, 32768 x 4096 135, 132,
 // 262144 x 256 110, 112, 65536 x 256 with 8192 8-bit rows 73, 81.  The row quantizer's workgroups hold one row each, whose fragments
-// share no line: 2048 x 4096 41.5, 38, 4096 x 2048 36, 33, but 8192 x 512 28, 29, 4096 x 256 all at 8 bits 19.4, 20.9, 32768 x 256
-// 45, 57, 262144 x 256 224, 337.  Lines fitted to 1210 such pairs (256 .. 262144 rows, depth 32 .. 11008).
+// share no line: 1024 x 4096 39, 36, 4096 x 2048 35.5, 33.1, but 4096 x 4096 47.5, 49.1, 8192 x 512 26.8, 29.2, 4096 x 256 all at 8
+// bits 19.4, 20.9, 32768 x 256 41, 58, 262144 x 256 192, 338.  Lines fitted to 1210 such pairs (256 .. 262144 rows, depth 32 .. 11008).
 bool direct_pays(const stamp_plan* p) {
   const StampGeom& g = p->geom;
   const int64_t rows = (int64_t)g.B * g.s, hi = (int64_t)g.B * g.khi;
-  if (g.ident && !p->rag.on) return rows + hi <= 6144 && rows * g.d <= (1 << 24);
+  if (g.ident && !p->rag.on) return rows + hi <= 6144 && rows * g.d <= (3 << 22);
   return rows + 16 * hi <= 140000 && rows * g.d <= (1 << 27);
 }
 bool direct_route(const stamp_plan* p, const void* X, const void* Y) {

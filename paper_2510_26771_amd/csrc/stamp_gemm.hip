@@ -441,24 +441,20 @@ hipError_t launch(const GemmArgs& a, hipStream_t st) {
 
 }  // namespace
 
-namespace {
-int device_cus() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-      cus = 256;
-  }
+int stamp_device_cus() {
+  static const int cus = [] {
+    int dev = 0, n = 0;
+    const bool ok = hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess;
+    return ok && n > 0 ? n : 256;
+  }();
   return cus;
 }
-}  // namespace
 
 // The 8-bit rows' GEMM keeps one 256 x 128 workgroup per CU (its stages hold unpacked int8 rows).  When
 // that needs more than one round of tiles, 256 x 256 tiles (half as many, one round) finish sooner.
 bool stamp_hi_wide_tiles(int M, int Npad) {
   const int tiles128 = ((M + stamp_gemm::BM - 1) / stamp_gemm::BM) * (Npad / 128);
-  return tiles128 > device_cus();
+  return tiles128 > stamp_device_cus();
 }
 
 // Plans without top levels: the dequantized top rows ARE the block sums P of the inverse (the top inverse has
@@ -488,7 +484,7 @@ int stamp_hi_ksplit(const stamp_plan* p, int rows_per_seq) {
   if (M <= kHiFewRows) {
     // few rows: enough parts for one workgroup per CU, each with at least four K steps
     const int tiles = p->Npad / 128, KT = p->Kpad / stamp_gemm::BK;
-    int s = (device_cus() + tiles - 1) / tiles;
+    int s = (stamp_device_cus() + tiles - 1) / tiles;
     if (s > KT / 4) s = KT / 4;
     if (s > 4) s = 4;
     return s < 1 ? 1 : s;
@@ -496,7 +492,7 @@ int stamp_hi_ksplit(const stamp_plan* p, int rows_per_seq) {
   const int mt = (M + stamp_gemm::BM - 1) / stamp_gemm::BM;
   const int tiles = mt * (p->Npad / (stamp_hi_wide_tiles(M, p->Npad) ? 256 : 128));
   const int KT = p->Kpad / stamp_gemm::BK;
-  int s = device_cus() / tiles;
+  int s = stamp_device_cus() / tiles;
   if (s > 4) s = 4;
   while (s > 1 && KT / s < 2) --s;
   return s < 2 ? 1 : s;

@@ -160,7 +160,7 @@ hipError_t stamp_launch_repack6_rag(const stamp_plan* p, const uint8_t* q_lo, ui
 // 28.3, 23.0; 344 (2 rounds against 3) 58.1, 57.4; depth 11008, 128 tiles: 64.4, 47; at full rounds (256 tiles) 35.8 against
 // twice 23.
 bool stamp_gemm6_half_tiles(int M, int Npad) {
-  const int cus = gemm6_cus(), nt = Npad / BN6;
+  const int cus = stamp_device_cus(), nt = Npad / BN6;
   const int r8 = ((M + 255) / 256 * nt + cus - 1) / cus, r4 = ((M + 127) / 128 * nt + cus - 1) / cus;
   return 100 * r8 > 68 * r4;
 }

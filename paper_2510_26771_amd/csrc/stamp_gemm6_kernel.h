@@ -426,17 +426,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
   }
 }
 
-int gemm6_cus() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-      cus = 256;
-  }
-  return cus;
-}
-int gemm6_workgroups(int tiles) { return tiles < gemm6_cus() ? tiles : gemm6_cus(); }
+int gemm6_workgroups(int tiles) { return tiles < stamp_device_cus() ? tiles : stamp_device_cus(); }
 
 template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM, bool RAG = false, bool ODD = false>
 hipError_t launch_k(const GemmArgs& a, hipStream_t st) {

@@ -1053,7 +1053,7 @@ hipError_t launch_wht_lds_n(const stamp_plan* p, const void* in, int in_kind, fl
   const int B = p->geom.B;
   int chlog = 6;
   while (((size_t)4 * s << chlog) > 128 * 1024) --chlog;
-  while (chlog > 4 && (size_t)((ld + (1 << chlog) - 1) >> chlog) * B < 256) --chlog;
+  while (chlog > 4 && (int64_t)((ld + (1 << chlog) - 1) >> chlog) * B < stamp_device_cus()) --chlog;
   const size_t lds = (size_t)4 * ((1 << N2) * ((1 << N1) + 1)) << chlog;
   static size_t done[kStampMaxDevices] = {};
   const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gen_wht_lds<N1, N2>), lds, done);
@@ -1085,7 +1085,7 @@ hipError_t launch_dct_fft(const stamp_plan* p, int inv, const void* src, int in_
   while ((1 << lgn) < s) ++lgn;
   while (chlog > 0 && ((size_t)8 * s << chlog) > 128 * 1024) --chlog;
   // fewer channels per workgroup while the chip is short of workgroups, down to 4 (16-byte runs of a row)
-  while (chlog > 2 && (size_t)((ld + (1 << chlog) - 1) >> chlog) * B < 256) --chlog;
+  while (chlog > 2 && (int64_t)((ld + (1 << chlog) - 1) >> chlog) * B < stamp_device_cus()) --chlog;
   // the stages' factors (4 N bytes) go to LDS where they fit next to the points
   const int tw_lds = s <= 4096;
   const size_t lds = ((size_t)8 * s << chlog) + (tw_lds ? (size_t)4 * s : 0);

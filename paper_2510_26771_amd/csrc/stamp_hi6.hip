@@ -319,8 +319,8 @@ hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float*
   h.mode = mode;
   h.norm = norm;
   h.Y = Y;
-  // workgroups up to one per CU (256): the rule of AHEAD
-  if (h.np == 2 && (int64_t)((h.a.N + 63) / 64 * 2) * ((h.a.M + 64 * h.ng - 1) / (64 * h.ng)) <= 256) return launch<2, false, true>(h, st);
+  // workgroups up to one per CU: the rule of AHEAD
+  if (h.np == 2 && (int64_t)((h.a.N + 63) / 64 * 2) * ((h.a.M + 64 * h.ng - 1) / (64 * h.ng)) <= stamp_device_cus()) return launch<2, false, true>(h, st);
   return h.np == 1 ? launch<1, false, false>(h, st) : launch<2, false, false>(h, st);
 }
 

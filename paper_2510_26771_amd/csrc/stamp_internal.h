@@ -219,6 +219,9 @@ inline hipError_t stamp_allow_lds(const void* kernel, size_t bytes, size_t (&don
   return e;
 }
 
+// compute units of the device that is current at the first call
+int stamp_device_cus();
+
 // ---- launchers implemented in the kernel files (all asynchronous on `st`) ----
 hipError_t stamp_launch_weight_quant(const stamp_plan* p, const float* W, hipStream_t st, uint32_t* colmax_tmp);
 // part: 1 = bottom kernel only, 2 = top + 8-bit rows only, 3 = both
@@ -228,7 +231,7 @@ int stamp_actquant_nsplit(const stamp_plan* p);
 // plans without top levels: the bottom kernel also quantizes the block sums (no k_top, no k_quant_hi)
 bool stamp_top_in_bottom(const stamp_plan* p);
 // 8 x 8 blocks whose four sub-blocks one workgroup takes side by side (k_bottom2d_quads: up to 1536 channels by its threads;
-// up to two blocks per CU, 512: with more the CUs are full either way)
+// up to two blocks per CU: with more the CUs are full either way)
 bool stamp_bottom_quads(const stamp_plan* p);
 // dir: the codes leave as FP6 operands (4-bit rows, 8-bit rows) instead of in q_hi / q_lo, which are not written
 struct StampDirect {
