@@ -204,7 +204,7 @@ stamp_status_t validate(const stamp_plan_desc_t* d, StampGeom* g, int* fused_ok,
 // The GEMM with the inverse in its epilogue needs tiles for the CUs, as every tile walks its whole depth, and d_out that is
 // worth the conversion of all codes.  linear_forward_q, level by level against this form: 1152 channels, 8192 tokens 512 outputs
 // (128 tiles) 31.7, 36.6, 768 (192) 39.7, 36.3; 4096 tokens 1024 (128) 35.3, 34.7; 2048 tokens 2304 (144) 40.6, 35.0; 4 x 4 blocks,
-// 16384 tokens 384 (192) 37.3, 40.0, 512 (256) 41.5, 40.7.
+// 16384 tokens 384 (192) 37.3, 40.0, 512 (256) 41.5, 40.7; one column of tiles: 81920 tokens 112 (320) 59, 69.
 void grp_geometry(stamp_plan* p) {
   const stamp_plan_desc_t& d = p->desc;
   p->grp_quant = p->grp = 0;
@@ -221,7 +221,7 @@ void grp_geometry(stamp_plan* p) {
   if (mt * ((d.d_out + 255) / 256 * 2) < 128 && (g.L > 0 || rows < 4096)) return;
   p->bgeom = g;
   p->grp_quant = 1;
-  p->grp = tiles >= (g.R == 16 ? 256 : 192) || (tiles >= 128 && d.d_out >= 1024);
+  p->grp = d.d_out > 128 && (tiles >= (g.R == 16 ? 256 : 192) || (tiles >= 128 && d.d_out >= 1024));
 }
 
 // Blocked form of a plan of the general path (1-D Haar of any length): per-token scales, bias after the inverse, 3 to 6

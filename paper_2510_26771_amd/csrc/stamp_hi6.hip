@@ -274,9 +274,10 @@ size_t stamp_hi6_bytes(const stamp_plan* p, int own) {
 // its longer start.  Layers with int8 against FP6, microseconds.  Without transform, all M rows at 8 bits: 512 x 4096 x 4096 40,
 // 34, 1024 x 4096 x 4096 48, 57; 8192 x 1536 x 1536 75, 113; 2048 x 2048 x 2048 40, 45; 1024 x 2048 x 2048 36, 27; 4096 x
 // 1024 x 1024 38, 35, 8192: 47, 62; 4096 x 4096 x 512 38, 55.  64 top rows a sequence, top levels: 2048 x 2048 x 4096 212 against 258 at
-// depth 4096, 104 against 126 at depth 1024; 512 x 4096 x 4096 89, 76.  The lines fitted to 740 such pairs (M 192 .. 8192,
-// depth 192 .. 11008, d_out 256 .. 11008; five kinds of plan): M (d_out + 256) up to 6e6 and up to 1.2e6 + 7e9 / depth: 0.2 %
-// above always taking the better one on average (15 % at worst), where a bound of 2e10 on the product is 3.4 % (104 %).
+// depth 4096, 104 against 126 at depth 1024; 512 x 4096 x 4096 89, 76.  The lines fitted to 1364 such pairs (M 192 .. 16384,
+// depth 192 .. 11008, d_out 16 .. 11008; five kinds of plan): M (d_out + 256) up to 6.5e6, and M (d_out + 768), the larger share of
+// the rows' own operand, up to 8e5 + 8e9 / depth.  That is 0.3 % above always taking the better one on average and 22 % at worst,
+// where a bound of 2e10 on the product is 6 % and 359 % (linear_forward_q of 7820 rows x 2656 x 12 27 us against 38).
 bool stamp_hi6_fits(const stamp_plan* p, int own) {
   const StampGeom& g = p->geom;
   const int M = hi6_rows(p, own);
@@ -284,8 +285,7 @@ bool stamp_hi6_fits(const stamp_plan* p, int own) {
   if (!g.ident && !own && g.L > 0 && (g.k > 128 || (g.k & (g.k - 1)) != 0)) return false;  // whole sequences per workgroup
   const int choice = p->dbg[STAMP_CHOICE_HI_ROWS];
   if (choice != 0) return choice == 2;
-  const double mn = (double)M * (g.N + 256);
-  return M <= 128 || (mn <= 6.0e6 && mn <= 1.2e6 + 7.0e9 / g.d);
+  return M <= 128 || ((double)M * (g.N + 256) <= 6.5e6 && (double)M * (g.N + 768) <= 8.0e5 + 8.0e9 / g.d);
 }
 
 StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own) {

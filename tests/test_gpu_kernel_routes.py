@@ -31,6 +31,8 @@ def _wl(name, **kw):
 HI_RULE = [(dict(xform="identity", levels=0, seq_len=8192, k_hi=8192, d_in=1536, d_out=1536), False),
            (dict(xform="identity", levels=0, seq_len=2048, k_hi=2048, d_in=1152, d_out=4608), False),
            (dict(xform="identity", levels=0, seq_len=4096, k_hi=4096, d_in=4096, d_out=512), False),
+           (dict(xform="identity", levels=0, seq_len=7820, k_hi=7820, d_in=2656, d_out=12), False),
+           (dict(xform="identity", levels=0, seq_len=8192, k_hi=8192, d_in=192, d_out=64), True),
            (dict(xform="identity", levels=0, seq_len=1024, k_hi=1024, d_in=2048, d_out=2048), True),
            (dict(xform="identity", levels=0, seq_len=8192, k_hi=8192, d_in=256, d_out=256), True),
            (dict(batch=32, seq_len=512, levels=9, k_hi=64, d_in=4096, d_out=4096), False),
@@ -220,7 +222,7 @@ GRP = [_grp(64, 3, 64, 192, 1026), _grp(32, 5, 64, 320, 1410, batch=3), _grp(64,
        _grp(16, 4, 16, 128, 1026, batch=17), _grp(16, 3, 16, 320, 1290, batch=15, x_dtype="bf16"),
        _grp(32, 4, 16, 192, 2050, batch=2), _grp(32, 5, 16, 64, 2306, batch=2, x_dtype="bf16"),
        # the last 256 columns of the stored weights hold one tile of outputs and one of nothing
-       _grp(16, 2, 16, 64, 66, batch=256, x_dtype="bf16")]
+       _grp(64, 3, 64, 64, 322, batch=4, x_dtype="bf16")]
 
 
 @pytest.mark.parametrize("w", GRP, ids=[w.name for w in GRP])
@@ -231,7 +233,8 @@ def test_per_block_scales_on_token_blocks(w):
 
 # blocks for the quantizer only: too few tiles for the GEMM with the inverse
 GRP_QUANT = [_grp(64, 3, 64, 192, 130), _grp(16, 2, 16, 448, 64, batch=17), _grp(32, 3, 4, 256, 128, batch=4),
-             _grp(32, 2, 16, 128, 192, batch=5, x_dtype="bf16"), _grp(64, 6, 64, 64, 510, batch=2, x_dtype="bf16")]
+             _grp(32, 2, 16, 128, 192, batch=5, x_dtype="bf16"), _grp(64, 6, 64, 64, 510, batch=2, x_dtype="bf16"),
+             _grp(16, 2, 16, 64, 66, batch=256, x_dtype="bf16")]
 
 
 @pytest.mark.parametrize("w", GRP_QUANT, ids=[w.name for w in GRP_QUANT])
