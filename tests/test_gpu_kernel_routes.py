@@ -363,3 +363,37 @@ BESIDE = [_wl("beside_32", seq_len=256, levels=8, k_hi=8, d_in=160, x_dtype="bf1
 def test_codes_converted_beside_the_top_levels(w):
     tl.full_case(w, with_bias=True)
     tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16")
+
+
+# ---- two streams on one plan, each with its own workspace, on the routes whose buffers lie over one another
+STREAMS = [(_wl("streams_direct", batch=2, seq_len=512, levels=3, k_hi=16, d_in=256, d_out=384, x_dtype="bf16", seed=901), ("direct", "hi_fp6")),
+           (_wl("streams_beside", batch=2, seq_len=2048, levels=11, k_hi=64, d_in=512, d_out=768, x_dtype="bf16", seed=902), ("beside_top",)),
+           (_rag(3, 1003, 1, batch=2, d_in=256, d_out=515, x_dtype="bf16"), ("any_length_blocks", "direct")),
+           (_grp(64, 3, 64, 128, 1026), ("group_blocks",)),
+           (_wl("streams_dct", seq_len=1024, xform="dct", levels=0, k_hi=64, d_in=256, d_out=384, seed=903), ("hi_fp6",))]
+
+
+@pytest.mark.parametrize("w,routes", STREAMS, ids=[w.name for w, _ in STREAMS])
+def test_two_streams_with_distinct_workspaces(w, routes):
+    import torch
+    import paper_2510_26771_amd as st
+    inp = tl.make_inputs(w, with_bias=True)
+    plan = st.StampPlan(tl.plan_desc_for(w, "bf16"), torch.from_numpy(inp["W"]).cuda(), torch.from_numpy(inp["bias"]).cuda())
+    tl.check_routes(plan, w, routes)
+    X1 = tl.to_device_x(inp, w)
+    X2 = X1.flip(1).contiguous()
+    ws1, ws2 = plan.alloc_workspace(), plan.alloc_workspace()
+    ref1, ref2 = (torch.zeros((w.batch, w.seq_len, w.d_out), dtype=torch.int16, device="cuda") for _ in range(2))
+    plan.linear_forward(X1, ref1, ws1)
+    plan.linear_forward(X2, ref2, ws1)
+    torch.cuda.synchronize()
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    for it in range(3):
+        Y1, Y2 = torch.zeros_like(ref1), torch.zeros_like(ref1)
+        torch.cuda.synchronize()
+        for _ in range(4):
+            plan.linear_forward(X1, Y1, ws1, stream=s1)
+            plan.linear_forward(X2, Y2, ws2, stream=s2)
+        torch.cuda.synchronize()
+        assert torch.equal(Y1, ref1) and torch.equal(Y2, ref2), f"round {it}"
+    plan.destroy()
