@@ -109,7 +109,7 @@ def time_layer(st, torch, w, inp, args):
         extra["quantize_act_ms"] = stage_time_ms(lambda: plan.quantize_act(Xd, q_hi, q_lo, scales, ws), args.stage_iters, torch)
         fms = stage_time_ms(lambda: plan.linear_forward_q(q_hi, q_lo, scales, Y, ws), args.stage_iters, torch)
         extra["gemm_dequant_inverse_ms"] = fms
-        extra["gemm_int8_TOPs_lower_bound"] = 2.0 * w.batch * w.seq_len * w.d_in * w.d_out / (fms * 1e-3) / 1e12
+        extra["gemm_TOPs_lower_bound"] = 2.0 * w.batch * w.seq_len * w.d_in * w.d_out / (fms * 1e-3) / 1e12
     plan.destroy()
     del ws, Y, Xd, Wd
     return ms, extra

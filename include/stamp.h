@@ -142,13 +142,18 @@ typedef struct {
  * last one is carried to the next level unchanged; every level is the orthonormal butterfly (x0 +- x1) * fl(1/sqrt 2))
  * with 0 <= levels <= the depth that leaves one approximation, skip_first, HAAR2D on a rectangular grid (sides powers of
  * two), WHT (seq_len a power of two), DCT, bias_mode 1, group_size 64, and the HAAR1D / HAAR2D settings outside the
- * fast path's block structure (any 0 <= k_hi <= seq_len, any depth, any block size).  The transform runs as a few passes
- * (several levels each) over fp32 copies of the activation in the workspace, the quantizer and the GEMM treat the
- * transformed tokens as rows in STaMP order (physical row = STaMP slot), the inverse again runs in passes after the GEMM.
+ * fast path's block structure (any 0 <= k_hi <= seq_len, any depth, any block size).  The quantizer's rows are in STaMP order
+ * (physical row = STaMP slot).  In general the transform runs as one or a few passes (several levels each) over fp32 copies
+ * of the activation in the workspace, the GEMM writes its rows in fp32, the inverse again runs in passes after it.  Two kinds
+ * of plan run block by block instead, for 16-byte aligned X (transform and quantizer in one kernel) and Y (inverse in the
+ * GEMM's epilogue), same codes: HAAR1D of any seq_len or with skip_first, 3 to 6 levels, per-token scales, bias_mode 0 and
+ * the 8-bit tokens among the approximations (and the first token); and group_size 64 on HAAR2D grids with the fast path's
+ * blocks, even d_out, bias_mode 0, large enough (stamp_debug_routes tells).
  * Limits of the general path (STAMP_ERR_UNSUPPORTED beyond them): bits 8/4/4; d_in a multiple of 32, at most 32768;
  * d_out at most 2^21 (both paths);
  * group_size 0 or 64, and 64 needs d_in a multiple of 64 and the symmetric quantizer; seq_len <= 65535, batch <= 65535,
- * batch * k_hi <= 65535 (grid dimensions); DCT: seq_len <= 16384 (a dense seq_len x seq_len matrix).  With group_size =
+ * batch * k_hi <= 65535 (grid dimensions); DCT: seq_len <= 16384 (what a workgroup's LDS holds of a channel; lengths that are
+ * no power of two multiply by a dense seq_len x seq_len matrix).  With group_size =
  * 64 the buffers of stamp_quantize_act / stamp_linear_forward_q are: q_hi [batch, seq_len, d_in] int8 codes of ALL
  * tokens in STaMP order (stamp_plan_hi_rows returns seq_len), q_lo unused (may be NULL), scales [batch, seq_len,
  * d_in / 64].
@@ -197,8 +202,8 @@ stamp_status_t stamp_quantize_act(const stamp_plan_t* plan, const void* X_dev, i
 
 /* The whole layer, Algorithm "STaMP Linear": quantize_act, the integer GEMM on the matrix cores (the
  * exact integer sums under either engine, see stamp_plan_set_gemm_engine; the default is the FP6 pipeline
- * for the 4-bit rows and the int8 pipeline for the 8-bit rows), dequantization, inverse transform, bias,
- * store Y.  The 8-bit rows' integer sums are converted to fp32 exactly while 128 * 7 * d_in < 2^24
+ * for the 4-bit rows; the 8-bit rows run on it as two 4-bit rows each while there are few, else on the int8
+ * pipeline), dequantization, inverse transform, bias, store Y.  The 8-bit rows' integer sums are converted to fp32 exactly while 128 * 7 * d_in < 2^24
  * (d_in <= 18720); on wider layers a sum beyond 2^24 (only reachable by adversarial inputs) is rounded
  * to fp32 (relative 2^-24) before it is scaled. */
 stamp_status_t stamp_linear_forward(const stamp_plan_t* plan, const void* X_dev, void* Y_dev,
@@ -252,7 +257,7 @@ stamp_status_t stamp_debug_weight_codes(const stamp_plan_t* plan, int8_t* qW_hos
  *   6 conversion of the packed 4-bit rows to the FP6 engine's operand layout (FP6 engine only; with
  *     that engine stage 4 is the GEMM alone and reads what stage 6 wrote to the workspace)
  * Plans whose transform has no levels above the blocks: stage 0 also quantizes the block sums, stage 2 writes
- * the block sums of the inverse itself, stages 1 and 3 launch nothing.  Plans with few 8-bit rows over the batch: stage 2
+ * the block sums of the inverse itself, stages 1 and 3 launch nothing.  Plans with few 8-bit rows for their size: stage 2
  * converts them, multiplies them on the FP6 pipeline and writes the block sums (without a transform: their rows of Y),
  * stage 3 launches nothing.
  * Plans without transform: 0 the quantization kernel, 2 GEMM of the 8-bit rows, 3 their output pass,
@@ -277,10 +282,11 @@ stamp_status_t stamp_plan_set_unfused(stamp_plan_t* plan, int32_t unfused);
  * in one piece, where the other setting may add them up from dequantized partial sums over parts of the depth):
  *   STAMP_GEMM_FP6   (default) the codes as 6-bit floating point numbers code / 8 (E2M3, exact),
  *                    FP6 x FP6 -> fp32 MFMA, twice the int8 rate per clock; the fp32 accumulator holds
- *                    acc / 64 exactly (|acc| <= 49 d_in < 2^24).  Costs one conversion pass over the
- *                    packed rows inside stamp_linear_forward(_q);
+ *                    acc / 64 exactly (|acc| <= 49 d_in < 2^24).  Packed codes are converted by a pass inside
+ *                    stamp_linear_forward_q; stamp_linear_forward writes the operands from the quantizer or
+ *                    converts beside the top levels where that is faster;
  *   STAMP_GEMM_INT8  the codes as int8, int8 x int8 -> int32 MFMA.
- * The 8-bit rows run on the int8 pipeline, or (few of them over the batch) as two 4-bit rows each on the FP6 pipeline,
+ * The 8-bit rows run on the int8 pipeline, or (few of them for the layer's size) as two 4-bit rows each on the FP6 pipeline,
  * with the same integer sums, whatever this setting is.  May be changed between calls (it modifies the plan:
  * not thread-safe, no call on the plan may be in progress on another host thread); the workspace size
  * does not depend on it.  Returns STAMP_ERR_UNSUPPORTED for any other value. */
