@@ -195,13 +195,21 @@ RAG = ([_rag(3, 40 + m, m & 1, batch=3, d_in=96, d_out=68) for m in range(1, 9)]
        [_rag(5, 513 + m, 1, d_in=160, d_out=257, x_dtype="bf16") for m in (0, 6, 31)] +
        [_rag(6, 700 + m, 1, batch=2, d_in=64, d_out=130) for m in (5, 25, 60)] +
        [_rag(3, 1023, 1, k_hi=129, d_out=515), _rag(3, 1000, 0, k_hi=1), _rag(4, 776, 1, batch=3, k_hi=32, d_out=33),
-        _rag(3, 5, 1, k_hi=1), _rag(3, 9, 1, k_hi=3)])
+        _rag(3, 5, 1, k_hi=1, batch=64), _rag(3, 9, 1, k_hi=3, batch=64)])
+# (the rows in block order lie over the workspace's fp32 copies of X: plans whose copies are smaller run level by level)
+RAG_SMALL = [_rag(3, 5, 1, k_hi=1), _rag(3, 9, 1, k_hi=3)]
 
 
 @pytest.mark.parametrize("w", RAG, ids=[w.name for w in RAG])
 def test_blocked_haar_of_any_length(w):
     for y in ("f32", "bf16"):
-        tl.full_case(w, with_bias=True, check_unfused=False, y_dtype=y)
+        tl.full_case(w, with_bias=True, check_unfused=False, y_dtype=y, routes=("any_length_blocks", "hi_fp6"))
+
+
+@pytest.mark.parametrize("w", RAG_SMALL, ids=[w.name for w in RAG_SMALL])
+def test_short_sequences_level_by_level(w):
+    for y in ("f32", "bf16"):
+        tl.full_case(w, with_bias=True, check_unfused=False, y_dtype=y, routes=("-any_length_blocks",))
 
 
 # ---- per-block scales on blocks of 4 x 4 and 8 x 8 tokens: with and without top levels, 4-bit approximations, a depth
@@ -307,13 +315,16 @@ TILES = [_tiles("t256_ident_odd_rows", 8193, 2050, 64, xform="identity", levels=
          _tiles("t256_wht", 2048, 7938, 32, xform="wht", levels=0),
          _tiles("t256_grid", 4096, 4098, 288, xform="haar2d", grid_h=64, grid_w=64, levels=3, k_hi=64, corr_len=4.0),
          _tiles("t128_ident_rows", 257, 300, 32, xform="identity", levels=0),
-         _tiles("t128_haar_129_tiles", 1024, 8300, 416, levels=10, k_hi=32, act_quant="asym"),
+         # 132 and 128 tiles of 256 x 256: either side of one round of half tiles
+         _tiles("t256_haar_132_tiles", 1024, 8300, 416, levels=10, k_hi=32, act_quant="asym"),
+         _tiles("t128_haar_128_tiles", 1024, 8180, 416, levels=10, k_hi=32, act_quant="asym"),
          _tiles("t128_grid4", 1024, 514, 160, xform="haar2d", grid_h=32, grid_w=32, levels=5, k_hi=64, corr_len=4.0)]
 
 
 @pytest.mark.parametrize("w", TILES, ids=[w.name for w in TILES])
 def test_both_gemm_tile_sizes(w):
-    tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16" if w.d_out % 4 else "f32", check_acc=False)
+    tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16" if w.d_out % 4 else "f32", check_acc=False,
+                 routes=("tiles_128" if w.name.startswith("t128") else "-tiles_128",))
 
 
 # ---- split channels without top levels: the bottom kernel's two passes carry the block sums' maxima too (a last split of one
@@ -361,8 +372,8 @@ BESIDE = [_wl("beside_32", seq_len=256, levels=8, k_hi=8, d_in=160, x_dtype="bf1
 
 @pytest.mark.parametrize("w", BESIDE, ids=[w.name for w in BESIDE])
 def test_codes_converted_beside_the_top_levels(w):
-    tl.full_case(w, with_bias=True)
-    tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16")
+    tl.full_case(w, with_bias=True, routes=("beside_top",))
+    tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16", routes=("beside_top",))
 
 
 # ---- two streams on one plan, each with its own workspace, on the routes whose buffers lie over one another
