@@ -607,11 +607,14 @@ stamp_status_t stamp_plan_create(const stamp_plan_desc_t* desc, const void* W_de
 
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   uint32_t* colmax = nullptr;
-  bool ok = hipMalloc(reinterpret_cast<void**>(&p->qW_dev), (size_t)p->Npad * p->Kpad) == hipSuccess &&
-            hipMalloc(reinterpret_cast<void**>(&p->qW6_dev), stamp_b6_bytes(p)) == hipSuccess &&
-            hipMalloc(reinterpret_cast<void**>(&p->sw_dev), sizeof(float) * p->Npad) == hipSuccess &&
+  // per-block scales: the weights have a layout of their own (stamp_gen_plan_tables); the GEMM's epilogue reads (and drops) sw
+  const bool per_column = gen.group == 0;
+  bool ok = hipMalloc(reinterpret_cast<void**>(&p->sw_dev), sizeof(float) * p->Npad) == hipSuccess &&
             hipMalloc(reinterpret_cast<void**>(&p->colsum_dev), sizeof(float) * p->Npad) == hipSuccess &&
             hipMalloc(reinterpret_cast<void**>(&colmax), sizeof(uint32_t) * g.N) == hipSuccess;
+  if (per_column)
+    ok = ok && hipMalloc(reinterpret_cast<void**>(&p->qW_dev), (size_t)p->Npad * p->Kpad) == hipSuccess &&
+         hipMalloc(reinterpret_cast<void**>(&p->qW6_dev), stamp_b6_bytes(p)) == hipSuccess;
   if (ok && bias_dev != nullptr) ok = hipMalloc(reinterpret_cast<void**>(&p->bias_dev), sizeof(float) * p->Npad) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
@@ -638,8 +641,11 @@ stamp_status_t stamp_plan_create(const stamp_plan_desc_t* desc, const void* W_de
     dev_ok = hipMemsetAsync(p->bias_dev, 0, sizeof(float) * p->Npad, st) == hipSuccess &&
              hipMemcpyAsync(p->bias_dev, bias_dev, sizeof(float) * g.N, hipMemcpyDeviceToDevice, st) == hipSuccess;
   }
-  if (dev_ok) dev_ok = stamp_launch_weight_quant(p, Wf, st, colmax) == hipSuccess;
-  if (dev_ok) dev_ok = stamp_launch_weight_quant6(p, Wf, colmax, st) == hipSuccess;
+  if (dev_ok && per_column)
+    dev_ok = stamp_launch_weight_quant(p, Wf, st, colmax) == hipSuccess && stamp_launch_weight_quant6(p, Wf, colmax, st) == hipSuccess;
+  if (dev_ok && !per_column)
+    dev_ok = hipMemsetAsync(p->sw_dev, 0, sizeof(float) * p->Npad, st) == hipSuccess &&
+             hipMemsetAsync(p->colsum_dev, 0, sizeof(float) * p->Npad, st) == hipSuccess;
   if (dev_ok && gen.kind != kGenNone) dev_ok = stamp_gen_plan_tables(p, Wf, st) == hipSuccess;
   // the scratch buffers must outlive the kernels just enqueued: hipFree waits for the device
   (void)hipFree(colmax);

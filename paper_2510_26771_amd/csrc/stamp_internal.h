@@ -164,8 +164,8 @@ struct stamp_plan {
   StampGeom geom;
   int32_t Kpad, Npad;       // GEMM-padded depth and width of the stored weight
   int32_t Mpad;             // batch * seq_len rounded up to the GEMM's 256-row tile
-  int8_t* qW_dev;           // tiled int8 weight codes * 16 (see stamp_w_offset), K order permuted per 16 channels
-  float* sw_dev;            // [Npad] weight scales (0 beyond d_out)
+  int8_t* qW_dev;           // tiled int8 weight codes * 16 (see stamp_w_offset), K order permuted per 16 channels (not with per-block scales)
+  float* sw_dev;            // [Npad] weight scales (0 beyond d_out, and with per-block scales)
   float* bias_dev;          // [Npad] bias or nullptr
   float* colsum_dev;        // [Npad] sum over input channels of the weight codes (exact integers as fp32)
   int32_t* row_of_coeff;    // host, [s]
