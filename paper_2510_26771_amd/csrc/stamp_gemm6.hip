@@ -63,14 +63,7 @@ __global__ __launch_bounds__(512) void k_repack6_rag(const uint8_t* __restrict__
     w0 = *reinterpret_cast<const u4*>(src);
     w1 = *reinterpret_cast<const u4*>(src + 32);
   }
-  uint8_t* dst = a6 + (size_t)blk * kStageA6 + (row >> 5) * kBlock6 + kg * 512 + (row & 31) * 16;
-  uint64_t lo[3], hi[3];
-  chunk_to_e2m3(w0, lo);
-  chunk_to_e2m3(w1, hi);
-  typedef uint64_t ul2 __attribute__((ext_vector_type(2)));
-  *reinterpret_cast<ul2*>(dst) = ul2{lo[0], lo[1]};
-  *reinterpret_cast<ul2*>(dst + kPart) = ul2{lo[2], hi[0]};
-  *reinterpret_cast<ul2*>(dst + 2 * kPart) = ul2{hi[1], hi[2]};
+  repack6_store(a6 + (size_t)blk * kStageA6 + (row >> 5) * kBlock6 + kg * 512 + (row & 31) * 16, w0, w1);
 }
 
 // Plan-time weight codes in that layout: per output channel n, code = rne(W_cn * (7 / max)) as in
@@ -114,10 +107,7 @@ __global__ __launch_bounds__(256) void k_w_quant6(const float* __restrict__ W, c
   // two neighbouring output columns (stamp_epilogue_reg.h)
   const int blk = ((n & 127) >> 6) * 2 + (n & 1), rowb = (n & 63) >> 1;
   uint8_t* dst = b6 + ((size_t)(n >> 7) * KT + kt) * kStageB6 + (size_t)blk * kBlock6 + (f & 1) * 512 + rowb * 16;
-  for (int p = 0; p < 3; ++p) {
-    const int off = (f >> 1) * 24 + p * 8;
-    *reinterpret_cast<uint64_t*>(dst + (off >> 4) * kPart + (off & 15)) = part[p];
-  }
+  store_frag(dst, f, part);
 }
 
 }  // namespace

@@ -235,13 +235,6 @@ __device__ __forceinline__ f2 row_scales(const GrpPack& q, size_t row, int kt, f
   const float* s = q.scales + row * ng + 2 * kt;
   return f2{s[0] * f, 2 * kt + 1 < ng ? s[1] * f : 0.0f};
 }
-__device__ __forceinline__ void store_frag(uint8_t* dst, int f, const uint64_t (&part)[3]) {
-#pragma unroll
-  for (int w = 0; w < 3; ++w) {
-    const int off = (f >> 1) * 24 + w * 8;
-    *reinterpret_cast<uint64_t*>(dst + (off >> 4) * kPart + (off & 15)) = part[w];
-  }
-}
 __global__ __launch_bounds__(256) void k_grp_pack(const GrpPack q) {
   const StampGeom& g = q.g;
   int i = blockIdx.x * 256 + threadIdx.x;

@@ -24,6 +24,15 @@ struct Frag6 {
   __device__ __forceinline__ v8i h1() const { return (v8i)__builtin_shufflevector(p1, p2, 2, 3, 4, 5, 6, 7, -1, -1); }
 };
 
+// a fragment's 24 bytes -> its places in a block; dst = (lane group, row) of the block
+__device__ __forceinline__ void store_frag(uint8_t* dst, int f, const uint64_t (&part)[3]) {
+#pragma unroll
+  for (int w = 0; w < 3; ++w) {
+    const int off = (f >> 1) * 24 + w * 8;
+    *reinterpret_cast<uint64_t*>(dst + (off >> 4) * kPart + (off & 15)) = part[w];
+  }
+}
+
 // one thread = 32 channels of a row
 __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
   if (i >= hp.threads) return;
@@ -51,25 +60,26 @@ __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
       part[q] |= field << sh;
       if (sh > 58) part[q + 1] |= field >> (64 - sh);
     }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int off = (f >> 1) * 24 + q * 8;
-      *reinterpret_cast<uint64_t*>(dst + half * kBlock6 + (off >> 4) * kPart + (off & 15)) = part[q];
-    }
+    store_frag(dst + half * kBlock6, f, part);
   }
+}
+
+// 64 packed codes of a row (fragments kg and 2 + kg) -> their 48 bytes of a block
+__device__ __forceinline__ void repack6_store(uint8_t* dst, u4 w0, u4 w1) {
+  uint64_t lo[3], hi[3];
+  chunk_to_e2m3(w0, lo);
+  chunk_to_e2m3(w1, hi);
+  typedef uint64_t ul2 __attribute__((ext_vector_type(2)));
+  *reinterpret_cast<ul2*>(dst) = ul2{lo[0], lo[1]};
+  *reinterpret_cast<ul2*>(dst + kPart) = ul2{lo[2], hi[0]};
+  *reinterpret_cast<ul2*>(dst + 2 * kPart) = ul2{hi[1], hi[2]};
 }
 
 // packed 4-bit rows -> operand: block `blk` = (row tile, K step), one row of it and kg: fragments kg and 2 + kg
 __device__ __forceinline__ void repack6_rows(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, size_t blk, int row, int kg) {
   const uint8_t* src = q_lo + blk * (256 * 64) + row * 64 + kg * 16;
-  uint8_t* dst = a6 + blk * kStageA6 + (row >> 5) * kBlock6 + kg * 512 + (row & 31) * 16;
-  uint64_t lo[3], hi[3];
-  chunk_to_e2m3(*reinterpret_cast<const u4*>(src), lo);
-  chunk_to_e2m3(*reinterpret_cast<const u4*>(src + 32), hi);
-  typedef uint64_t ul2 __attribute__((ext_vector_type(2)));
-  *reinterpret_cast<ul2*>(dst) = ul2{lo[0], lo[1]};
-  *reinterpret_cast<ul2*>(dst + kPart) = ul2{lo[2], hi[0]};
-  *reinterpret_cast<ul2*>(dst + 2 * kPart) = ul2{hi[1], hi[2]};
+  repack6_store(a6 + blk * kStageA6 + (row >> 5) * kBlock6 + kg * 512 + (row & 31) * 16, *reinterpret_cast<const u4*>(src),
+                *reinterpret_cast<const u4*>(src + 32));
 }
 
 }  // namespace stamp_gemm
