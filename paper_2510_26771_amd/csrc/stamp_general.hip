@@ -462,8 +462,21 @@ __device__ __forceinline__ cd c_mul(cd a, cd b) {
 __device__ __forceinline__ cd c_conj(cd a) { return {a.re, -a.im}; }
 // An infinity enters as a number far beyond the range of fp32, so that every coefficient it is part of leaves as an infinity
 // of its sign, as in the sum that defines it; an infinity itself would meet 0 * inf in the first product with a factor and
-// leave NaNs, which the row maxima of the quantizer pass over.
-__device__ __forceinline__ double dct_in(float x) { return __builtin_isinf(x) ? __builtin_copysign(1e300, (double)x) : (double)x; }
+// leave NaNs, which the row maxima of the quantizer pass over.  One test for all of a thread's values.
+template <int n>
+__device__ __forceinline__ void dct_in(const float (&x)[n], double (&v)[n]) {
+  float m = 0.0f;
+#pragma unroll
+  for (int j = 0; j < n; ++j) {
+    m = fmaxf(m, fabsf(x[j]));
+    v[j] = (double)x[j];
+  }
+  if (__builtin_isinf(m)) {
+#pragma unroll
+    for (int j = 0; j < n; ++j)
+      if (__builtin_isinf(x[j])) v[j] = __builtin_copysign(1e300, v[j]);
+  }
+}
 
 template <bool INV>
 __device__ __forceinline__ void lds_fft(cd* s, const cd* tw, int m, int chlog, int tid, int nthr) {
@@ -532,12 +545,14 @@ __global__ __launch_bounds__(1024) void k_gen_dct_fft(const cd* __restrict__ tab
       const int ch = u & (CH - 1), n0 = u >> chlog, c = min(c0 + ch, ld - 1);
       float x[8];
       gen_load_rows<8>(src, in_kind, bo + (size_t)n0 * ld + c, (size_t)(N >> 3) * ld, x);
+      double xd[8];
+      dct_in(x, xd);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int n = n0 + j * (N >> 3);
         const int nv = (n & 1) ? N - 1 - (n >> 1) : (n >> 1);
         const int pos = (int)(__brev((unsigned)(nv >> 1)) >> (32 - m));
-        sd[2 * ((pos << chlog) + ch) + (nv & 1)] = dct_in(x[j]);
+        sd[2 * ((pos << chlog) + ch) + (nv & 1)] = xd[j];
       }
     }
     __syncthreads();
@@ -579,8 +594,11 @@ __global__ __launch_bounds__(1024) void k_gen_dct_fft(const cd* __restrict__ tab
         // k = 0 reads coefficients 0, M and (for V[M/2]) M / 2, M + M / 2
         const float* i = S + bo + c;
         const int h = M >> 1;
-        const double x0 = dct_in(i[(size_t)k * ld]), x1 = dct_in(i[(size_t)(k == 0 ? M : N - k) * ld]);
-        const double x2 = dct_in(i[(size_t)(k == 0 ? h : M - k) * ld]), x3 = dct_in(i[(size_t)(k == 0 ? M + h : M + k) * ld]);
+        const float xf[4] = {i[(size_t)k * ld], i[(size_t)(k == 0 ? M : N - k) * ld], i[(size_t)(k == 0 ? h : M - k) * ld],
+                             i[(size_t)(k == 0 ? M + h : M + k) * ld]};
+        double xd[4];
+        dct_in(xf, xd);
+        const double x0 = xd[0], x1 = xd[1], x2 = xd[2], x3 = xd[3];
         if (k == 0) {
           const double v0 = x0 * (sqrt((double)N) / M), vm = x1 * (sc * sqrt(2.0));
           tk = {0.5 * (v0 + vm), 0.5 * (v0 - vm)};
