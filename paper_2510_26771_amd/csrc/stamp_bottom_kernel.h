@@ -9,9 +9,11 @@
 
 namespace {
 
+using stamp_gemm::cell2d;
 using stamp_gemm::kBlock6;
 using stamp_gemm::kPart;
 using stamp_gemm::kStageA6;
+using stamp_gemm::nib8_to_48;
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2v __attribute__((ext_vector_type(2)));
 
@@ -91,19 +93,6 @@ __device__ __forceinline__ uint32_t pack8_uint4(const float (&p)[8], float z) {
 
 // ---- codes straight to the FP6 GEMMs' operand layout (stamp_gemm6.hip; a thread owns 8 channels = 48 bits, the four
 // threads of a quad one 24-byte fragment of 32 channels) ----
-
-// eight two's-complement nibbles -> eight sign-magnitude 6-bit fields
-__device__ __forceinline__ void nib8_to_48(uint32_t w, uint32_t& w0, uint32_t& w1) {
-  const uint32_t s = w & 0x88888888u, sg = s >> 3;
-  const uint32_t mag = (w ^ ((s << 1) - sg)) + sg;
-  auto spread = [](uint32_t x) {  // four nibbles to bits 0, 6, 12, 18
-    const uint32_t t = (x & 0x00FFu) | ((x & 0xFF00u) << 4);
-    return (t & 0x00F00Fu) | ((t & 0x0F00F0u) << 2);
-  };
-  const uint32_t lo = spread(mag & 0xFFFFu) | (spread(sg & 0xFFFFu) << 5), hi = spread(mag >> 16) | (spread(sg >> 16) << 5);
-  w0 = lo | (hi << 24);
-  w1 = hi >> 8;
-}
 
 // byte offset, inside a 32-row block of K steps `kt_bytes` apart, of the 8 bytes that this thread stores: thread t of a quad
 // stores bytes 8 t .. 8 t + 7 of the fragment (t = 3 stores nothing); c = the thread's first channel
@@ -735,21 +724,6 @@ __global__ __launch_bounds__(1024) void k_bottom1d_rag(const void* __restrict__ 
 // ------------------------------------------------------------------------------------------
 // 2-D bottom kernel: block of g x g tokens (g = 2^RLOG, RLOG in {2,3}), streamed in 4x4 sub-blocks
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ void cell2d(const float (&p)[8], const float (&q)[8], const float (&u)[8], const float (&v)[8],
-                                       float (&LL)[8], float (&W)[8], float (&H)[8], float (&D)[8]) {
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const float t0 = __fadd_rn(p[c], q[c]);
-    const float t1 = __fsub_rn(p[c], q[c]);
-    const float t2 = __fadd_rn(u[c], v[c]);
-    const float t3 = __fsub_rn(u[c], v[c]);
-    LL[c] = __fadd_rn(t0, t2);
-    W[c] = __fadd_rn(t1, t3);
-    H[c] = __fsub_rn(t0, t2);
-    D[c] = __fsub_rn(t1, t3);
-  }
-}
-
 // 16 tokens from eoff0 on (4 x 4) -> 12 coefficients of level 1 and 3 of level 2 (rowv), their sum
 template <bool BF16, int NR>
 __device__ __forceinline__ void quad2d(const void* X, size_t eoff0, int gridW, int d, bool active, float (&rowv)[NR][8], float (&ll2)[8]) {

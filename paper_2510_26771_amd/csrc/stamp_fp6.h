@@ -17,28 +17,31 @@ constexpr int kBlock6 = 3 * kPart;            // a 32-row block of one K step: 3
 constexpr int kStageB6 = 4 * kBlock6;         // 128 columns: 12 KB
 constexpr int kStageA6 = 2 * kStageB6;        // 24 KB
 
-// eight two's-complement nibbles -> eight sign-magnitude 6-bit fields (48 bits)
-__device__ __forceinline__ uint64_t nib8_to_e2m3(uint32_t w) {
-  const uint32_t s = w & 0x88888888u;  // sign bit of every nibble
-  const uint32_t sg = s >> 3;          // 1 in every negative nibble
+// eight two's-complement nibbles -> eight sign-magnitude 6-bit fields
+__device__ __forceinline__ void nib8_to_48(uint32_t w, uint32_t& w0, uint32_t& w1) {
+  const uint32_t s = w & 0x88888888u, sg = s >> 3;
   // |c|: complement the negative nibbles and add 1 (no carry leaves a nibble: ~c + 1 <= 8).  |c| = 8
   // (the stored form of the asymmetric code 0) sets the low exponent bit: the E2M3 number 1.0 = 8 / 8.
-  const uint32_t mag = (w ^ (sg * 15u)) + sg;
-  uint64_t out = 0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const uint32_t c = ((mag >> (4 * j)) & 15u) | (((s >> (4 * j + 3)) & 1u) << 5);
-    out |= (uint64_t)c << (6 * j);
-  }
-  return out;
+  const uint32_t mag = (w ^ ((s << 1) - sg)) + sg;
+  auto spread = [](uint32_t x) {  // four nibbles to bits 0, 6, 12, 18
+    const uint32_t t = (x & 0x00FFu) | ((x & 0xFF00u) << 4);
+    return (t & 0x00F00Fu) | ((t & 0x0F00F0u) << 2);
+  };
+  const uint32_t lo = spread(mag & 0xFFFFu) | (spread(sg & 0xFFFFu) << 5), hi = spread(mag >> 16) | (spread(sg >> 16) << 5);
+  w0 = lo | (hi << 24);
+  w1 = hi >> 8;
 }
 
 // 32 codes (one 16-byte chunk of packed nibbles, low nibble = even channel) -> 24 bytes
 __device__ __forceinline__ void chunk_to_e2m3(u4 w, uint64_t (&part)[3]) {
-  const uint64_t a = nib8_to_e2m3(w.x), b = nib8_to_e2m3(w.y), c = nib8_to_e2m3(w.z), d = nib8_to_e2m3(w.w);
-  part[0] = a | (b << 48);
-  part[1] = (b >> 16) | (c << 32);
-  part[2] = (c >> 32) | (d << 16);
+  uint32_t lo[4], hi[4];
+  nib8_to_48(w.x, lo[0], hi[0]);
+  nib8_to_48(w.y, lo[1], hi[1]);
+  nib8_to_48(w.z, lo[2], hi[2]);
+  nib8_to_48(w.w, lo[3], hi[3]);
+  part[0] = lo[0] | ((uint64_t)(hi[0] | (lo[1] << 16)) << 32);
+  part[1] = ((lo[1] >> 16) | (hi[1] << 16)) | ((uint64_t)lo[2] << 32);
+  part[2] = (hi[2] | (lo[3] << 16)) | ((uint64_t)((lo[3] >> 16) | (hi[3] << 16)) << 32);
 }
 
 // 32 signed values of magnitude at most 8 -> 24 bytes of E2M3 numbers value / 8

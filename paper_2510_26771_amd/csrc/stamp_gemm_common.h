@@ -37,6 +37,22 @@ constexpr int kGroupM = 8;
 
 constexpr float kInvSqrt2 = 0.70710678118654752440f;
 
+// one 2 x 2 cell of tokens, 8 channels: sum and the three differences (without norms)
+__device__ __forceinline__ void cell2d(const float (&p)[8], const float (&q)[8], const float (&u)[8], const float (&v)[8],
+                                       float (&LL)[8], float (&W)[8], float (&H)[8], float (&D)[8]) {
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const float t0 = __fadd_rn(p[c], q[c]);
+    const float t1 = __fsub_rn(p[c], q[c]);
+    const float t2 = __fadd_rn(u[c], v[c]);
+    const float t3 = __fsub_rn(u[c], v[c]);
+    LL[c] = __fadd_rn(t0, t2);
+    W[c] = __fadd_rn(t1, t3);
+    H[c] = __fsub_rn(t0, t2);
+    D[c] = __fsub_rn(t1, t3);
+  }
+}
+
 __device__ __forceinline__ float haar_norm_dev(int level, int is2d) {
   return is2d ? ldexpf(1.0f, -level) : ldexpf((level & 1) ? kInvSqrt2 : 1.0f, -(level >> 1));
 }

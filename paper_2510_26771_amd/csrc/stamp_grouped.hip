@@ -54,18 +54,6 @@ __device__ __forceinline__ void quant_row8(const float (&t)[8], float qmax, int8
   if (active && first) *scale_out = scale;
 }
 
-__device__ __forceinline__ void cell8(const float (&p)[8], const float (&q)[8], const float (&u)[8], const float (&v)[8], float (&LL)[8],
-                                      float (&W)[8], float (&H)[8], float (&D)[8]) {
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const float t0 = __fadd_rn(p[c], q[c]), t1 = __fsub_rn(p[c], q[c]), t2 = __fadd_rn(u[c], v[c]), t3 = __fsub_rn(u[c], v[c]);
-    LL[c] = __fadd_rn(t0, t2);
-    W[c] = __fadd_rn(t1, t3);
-    H[c] = __fsub_rn(t0, t2);
-    D[c] = __fsub_rn(t1, t3);
-  }
-}
-
 // X -> codes and scales in STaMP order.  A wave takes 64 tokens (one 8 x 8 block, or four 4 x 4 blocks: RLOG 3 or 2) of
 // 128 channels: a lane one 4 x 4 sub-block of 8 channels, held in registers; the third level of an 8 x 8 block exchanges
 // the four sub-blocks' sums between lanes 16 and 32 apart.  Ranges are per 64 channels, i.e. over 8 lanes: no LDS, no
@@ -123,13 +111,13 @@ __global__ __launch_bounds__(256) void k_grp_quant(const void* __restrict__ X, i
         t[q][4] = __uint_as_float(w1.x); t[q][5] = __uint_as_float(w1.y); t[q][6] = __uint_as_float(w1.z); t[q][7] = __uint_as_float(w1.w);
       }
     }
-    cell8(t[0], t[1], t[2], t[3], ll1[ci], band[0], band[1], band[2]);
+    cell2d(t[0], t[1], t[2], t[3], ll1[ci], band[0], band[1], band[2]);
 #pragma unroll
     for (int bd = 0; bd < 3; ++bd)
       emit(band[bd], 1, g1 * g1 * (1 + bd) + (2 * sby + (ci >> 1)) * g1 + 2 * sbx + (ci & 1), 7.0f);
   }
   float ll2[8];
-  cell8(ll1[0], ll1[1], ll1[2], ll1[3], ll2, band[0], band[1], band[2]);
+  cell2d(ll1[0], ll1[1], ll1[2], ll1[3], ll2, band[0], band[1], band[2]);
 #pragma unroll
   for (int bd = 0; bd < 3; ++bd) emit(band[bd], 2, g2 * g2 * (1 + bd) + sby * g2 + sbx, 7.0f);
   int e_top = 0;
