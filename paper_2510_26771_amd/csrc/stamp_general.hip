@@ -21,18 +21,11 @@
 #include <cstdlib>
 #include <vector>
 
-#include "stamp_internal.h"
+#include "stamp_gen_io.h"
 
 namespace {
 
 constexpr float kC = 0.70710678118654752440f;  // fl(1 / sqrt 2) = 0x3F3504F3
-
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
 
 // grid: x = ceil(row_elems / blockDim.x), y = rows of this launch, z = batch; one thread per element of a row
 #define GEN_INDEX                                      \
@@ -46,30 +39,6 @@ __global__ __launch_bounds__(256) void k_gen_cast(const void* __restrict__ X, fl
   GEN_INDEX;
   const size_t idx = bo + (size_t)i * ld + c;
   dst[idx] = bf16 ? __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(X)[idx] << 16) : reinterpret_cast<const float*>(X)[idx];
-}
-
-// One element of the input of a transform pass: X itself (bf16 or fp32) or an fp32 work buffer.
-__device__ __forceinline__ float gen_load(const void* in, int kind, size_t idx) {
-  return kind == 2 ? __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(in)[idx] << 16) : reinterpret_cast<const float*>(in)[idx];
-}
-// n elements, `step` apart.  One branch on the type for all of them: a branch per element would make every load wait for
-// the one before it (s = 2048, 4096 channels, 32 rows per thread: WHT 41 -> 25 us).
-template <int n>
-__device__ __forceinline__ void gen_load_rows(const void* in, int kind, size_t idx, size_t step, float (&v)[n]) {
-  if (kind == 2) {
-    uint32_t w[n];
-#pragma unroll
-    for (int j = 0; j < n; ++j) w[j] = reinterpret_cast<const uint16_t*>(in)[idx + j * step];
-#pragma unroll
-    for (int j = 0; j < n; ++j) v[j] = __uint_as_float(w[j] << 16);
-  } else {
-#pragma unroll
-    for (int j = 0; j < n; ++j) v[j] = reinterpret_cast<const float*>(in)[idx + j * step];
-  }
-}
-__device__ __forceinline__ void gen_store_y(void* Y, int y_bf16, size_t idx, float v) {
-  if (y_bf16) reinterpret_cast<uint16_t*>(Y)[idx] = f32_to_bf16_rne(v);
-  else reinterpret_cast<float*>(Y)[idx] = v;
 }
 
 // per-pass factors of the power-of-two ("classic") arithmetic: det[i] multiplies the details of the pass's i-th
@@ -448,36 +417,10 @@ __global__ __launch_bounds__(256) void k_gen_dct(const double* __restrict__ Cm, 
 // backwards.  The FFT is in place in LDS, decimation in time (the load puts every point at its bit-reversed place),
 // two radix-2 stages per pass.
 // What bounds it: LDS, 16 N bytes per channel and pass; the dense fp64 product it replaces runs 2 N^2 operations per
-// channel on the fp64 matrix pipe (N = 2048, 4096 channels: 992 us per transform, this kernel 36 and 38).
+// channel on the fp64 matrix pipe (N = 2048, 4096 channels: 992 us per transform, this kernel 36 and 38).  Lengths of 1024 to
+// 4096, and 512 where there are many channels, have a kernel with fewer passes through LDS (stamp_dct.hip).
 // A workgroup holds 2^chlog neighbouring channels, as many as 128 KB of LDS take (8 N bytes each), at most 32.
 // tab: e^{-2 pi i k / M}, k < M, then e^{-i pi k / 2N}, k <= M, then e^{-2 pi i k / N}, k <= M.
-struct cd {
-  double re, im;
-};
-__device__ __forceinline__ cd c_add(cd a, cd b) { return {a.re + b.re, a.im + b.im}; }
-__device__ __forceinline__ cd c_sub(cd a, cd b) { return {a.re - b.re, a.im - b.im}; }
-__device__ __forceinline__ cd c_mul(cd a, cd b) {
-  return {__builtin_fma(a.re, b.re, -(a.im * b.im)), __builtin_fma(a.re, b.im, a.im * b.re)};
-}
-__device__ __forceinline__ cd c_conj(cd a) { return {a.re, -a.im}; }
-// An infinity enters as a number far beyond the range of fp32, so that every coefficient it is part of leaves as an infinity
-// of its sign, as in the sum that defines it; an infinity itself would meet 0 * inf in the first product with a factor and
-// leave NaNs, which the row maxima of the quantizer pass over.  One test for all of a thread's values.
-template <int n>
-__device__ __forceinline__ void dct_in(const float (&x)[n], double (&v)[n]) {
-  float m = 0.0f;
-#pragma unroll
-  for (int j = 0; j < n; ++j) {
-    m = fmaxf(m, fabsf(x[j]));
-    v[j] = (double)x[j];
-  }
-  if (__builtin_isinf(m)) {
-#pragma unroll
-    for (int j = 0; j < n; ++j)
-      if (__builtin_isinf(x[j])) v[j] = __builtin_copysign(1e300, v[j]);
-  }
-}
-
 template <bool INV>
 __device__ __forceinline__ void lds_fft(cd* s, const cd* tw, int m, int chlog, int tid, int nthr) {
   const int M = 1 << m, CH = 1 << chlog;
@@ -1099,6 +1042,7 @@ hipError_t launch_wht_lds(const stamp_plan* p, int J, const void* in, int in_kin
 hipError_t launch_dct_fft(const stamp_plan* p, int inv, const void* src, int in_kind, float* T, void* Y, const float* bias, int ld,
                           hipStream_t st) {
   const int s = p->geom.s, B = p->geom.B;
+  if (stamp_dct_in_registers(s, B, ld)) return stamp_launch_dct_reg(p, inv, src, in_kind, T, Y, bias, ld, st);
   int lgn = 0, chlog = 5;
   while ((1 << lgn) < s) ++lgn;
   while (chlog > 0 && ((size_t)8 * s << chlog) > 128 * 1024) --chlog;

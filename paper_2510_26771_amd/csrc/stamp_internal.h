@@ -312,6 +312,10 @@ void stamp_gen_plan_free(stamp_plan* p);
 hipError_t stamp_gen_forward(const stamp_plan* p, const void* X, float* const (&buf)[3], float** T_out, hipStream_t st);
 // Yt [B, s, ncols] fp32 in STaMP order (buf[0], only read) -> Y; buf[1], buf[2]: the levels' work buffers
 hipError_t stamp_gen_inverse(const stamp_plan* p, float* const (&buf)[3], int ncols, const float* bias, void* Y, hipStream_t st);
+// DCT of a power-of-two length with the points in registers (stamp_dct.hip): plans it takes, and src -> T (inv = 0), src -> Y (+ bias)
+bool stamp_dct_in_registers(int s, int B, int ld);
+hipError_t stamp_launch_dct_reg(const stamp_plan* p, int inv, const void* src, int in_kind, float* T, void* Y, const float* bias, int ld,
+                                hipStream_t st);
 // blocked form: X -> codes and scales in STaMP order in one pass; false where the kernel does not take the plan or X
 bool stamp_rag_quantizes(const stamp_plan* p, const void* X);
 hipError_t stamp_launch_actquant_rag(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, hipStream_t st,

@@ -85,7 +85,16 @@ def test_rule_of_the_operands(kw, direct):
 DCT = [_wl("dct_8", batch=2, xform="dct", levels=0, seq_len=8, k_hi=1, seed=201),
        _wl("dct_16_bf16", xform="dct", levels=0, seq_len=16, k_hi=2, x_dtype="bf16", seed=202),
        _wl("dct_512", batch=3, xform="dct", levels=0, seq_len=512, d_in=160, d_out=131, seed=203),
-       _wl("dct_1024_asym", xform="dct", levels=0, seq_len=1024, act_quant="asym", mean_shift=0.5, seed=204)]
+       _wl("dct_1024_asym", xform="dct", levels=0, seq_len=1024, act_quant="asym", mean_shift=0.5, seed=204),
+       # points in registers: four and eight channels per workgroup, last pass of radix 1, 2, 4 and 8, a last group of channels
+       # that is not full
+       _wl("dct_512_reg", batch=13, xform="dct", levels=0, seq_len=512, d_in=160, d_out=163, k_hi=8, x_dtype="bf16", seed=205),
+       _wl("dct_1024_reg", batch=13, xform="dct", levels=0, seq_len=1024, d_in=160, d_out=163, k_hi=8, seed=206),
+       _wl("dct_2048_reg", batch=8, xform="dct", levels=0, seq_len=2048, d_in=256, d_out=258, k_hi=8, x_dtype="bf16", seed=207),
+       # (the oracle's angles are rounded to 2^-52 pi s, some 1e-5 of a coefficient's fp32 spacing: with seed 208 a row maximum lies
+       # 4e-6 of it from a rounding boundary and falls on the other side; with 214 none is nearer than 4.6e-4)
+       _wl("dct_2048_few", xform="dct", levels=0, seq_len=2048, d_in=96, d_out=33, k_hi=8, x_dtype="bf16", seed=214),
+       _wl("dct_4096_reg", batch=8, xform="dct", levels=0, seq_len=4096, d_in=256, d_out=257, k_hi=8, seed=209)]
 
 
 @pytest.mark.parametrize("w", DCT, ids=[w.name for w in DCT])
@@ -130,7 +139,7 @@ def test_dct_inverse_against_the_dense_product(s):
     plan.destroy()
 
 
-@pytest.mark.parametrize("s", [8, 64, 1024, 8192])
+@pytest.mark.parametrize("s", [8, 64, 1024, 2048, 8192])
 def test_dct_of_infinities(s):
     """An infinite activation makes every coefficient of its channel infinite, so every scale of that sequence is, and no
     output of it looks like a number; an infinite coefficient makes its whole column infinite, each token with the sign of
