@@ -326,6 +326,7 @@ hipError_t stamp_launch_actquant_rag(const stamp_plan* p, const void* X, int8_t*
                                      const StampDirect* dir) {
   const Hi6Out hi6 = hi6_out(dir);
   if (dir != nullptr) q_lo = dir->a6;
+  if (dir != nullptr && stamp_lanes1d_fits(p, p->rag.r)) return stamp_launch_lanes1d(p, p->rag.r, X, q_lo, scales, nullptr, hi6.p, hi6.np, st);
   switch (p->rag.r) {
     case 3: return stamp_bottom1d_rag_3(p, X, q_hi, q_lo, scales, hi6.p, hi6.np, st);
     case 4: return stamp_bottom1d_rag_4(p, X, q_hi, q_lo, scales, hi6.p, hi6.np, st);
@@ -423,6 +424,9 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
   } while (0)
   if (!(part & 1)) {
     // bottom kernel skipped
+  } else if (!g.is2d && bot != nullptr && stamp_lanes1d_fits(p, g.r)) {
+    const hipError_t le = stamp_launch_lanes1d(p, g.r, X, q_lo, scales, top_in_bottom ? nullptr : abot, sp.hi6.p, sp.hi6.np, st);
+    if (le != hipSuccess) return le;
   } else if (!g.is2d) {
     switch (g.r) {
       case 3: LAUNCH1D(3); break;

@@ -523,6 +523,10 @@ bool direct_pays(const stamp_plan* p) {
   const StampGeom& g = p->geom;
   const int64_t rows = (int64_t)g.B * g.s, hi = (int64_t)g.B * g.khi;
   if (g.ident && !p->rag.on) return rows + hi <= 6144 && rows * g.d <= (3 << 22);
+  // 1-D blocks of 8 and 16 tokens by stamp_lanes1d: whole fragments leave in 16 and 8 bytes, at any size as fast as they can be made;
+  // only many 8-bit rows cost (packed, direct: 32768 x 4096 136, 112, x 8192 310, 233, 16 x 5000 x 4096 375, 288, 262144 x 256 106, 83;
+  // 128 sequences of 512 with 64 8-bit rows each, x 256 71.5, 75.5, 64 of them 51.8, 49.1, 256 with 32 each 73.6, 66.4)
+  if (!g.is2d && stamp_lanes1d_fits(p, p->rag.on ? p->rag.r : g.r)) return rows + 16 * hi <= 140000 || 16 * hi <= rows;
   return rows + 16 * hi <= 140000 && rows * g.d <= (1 << 27);
 }
 bool direct_route(const stamp_plan* p, const void* X, const void* Y) {

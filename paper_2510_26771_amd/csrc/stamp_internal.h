@@ -312,6 +312,11 @@ void stamp_gen_plan_free(stamp_plan* p);
 hipError_t stamp_gen_forward(const stamp_plan* p, const void* X, float* const (&buf)[3], float** T_out, hipStream_t st);
 // Yt [B, s, ncols] fp32 in STaMP order (buf[0], only read) -> Y; buf[1], buf[2]: the levels' work buffers
 hipError_t stamp_gen_inverse(const stamp_plan* p, float* const (&buf)[3], int ncols, const float* bias, void* Y, hipStream_t st);
+// Bottom kernels that leave FP6 operands (stamp_lanes1d.hip): blocks of 2^rlog tokens (3, 4), or parts of longer ones with their
+// sums left in abot.
+bool stamp_lanes1d_fits(const stamp_plan* p, int rlog);
+hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, uint8_t* a6, float* scales, float* abot, uint8_t* h6, int np,
+                                hipStream_t st);
 // DCT of a power-of-two length with the points in registers (stamp_dct.hip): plans it takes, and src -> T (inv = 0), src -> Y (+ bias)
 bool stamp_dct_in_registers(int s, int B, int ld);
 hipError_t stamp_launch_dct_reg(const stamp_plan* p, int inv, const void* src, int in_kind, float* T, void* Y, const float* bias, int ld,

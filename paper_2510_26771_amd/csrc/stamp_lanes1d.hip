@@ -1,0 +1,422 @@
+// Bottom kernels that leave FP6 operands: 1-D blocks of 8 and 16 tokens (parts of longer blocks too), rows without
+// transform.
+//
+// v_cvt_scalef32_2xpk16_fp6_f32 rounds 32 floats to E2M3 numbers (with scale 8: to the nearest integers, ties to even, of a
+// magnitude up to 15) and packs them: one instruction makes the 24-byte operand fragment of a row's 32 channels, for
+// which the streaming kernels (stamp_bottom_kernel.h: 8 channels a thread) spend eight per value.  So a lane holds 32 consecutive
+// channels, of two tokens; the block's other tokens are with its neighbours, and levels above the first pass sums from lane
+// to lane.  The pair of a level leaves its sum in the lower lane and its difference, a finished coefficient, in the
+// upper one: a lane ends with two rows of 32 channels, its tokens' difference and one other.  The rows' maxima meet in one
+// exchange and one barrier.
+// Same operations on the same values as the streaming kernels, same codes.
+// What bounds it: the vector ALU (about 22 instructions per channel and token pair) and the bytes, about alike: 8 x 2048 tokens x
+// 4096 channels 34.2 us (5.4 TB/s; streaming 47.0), 2048 x 4096 8.9 us (11.0) of which 5 are the launch and its first loads.
+#include "stamp_bottom_kernel.h"
+
+namespace {
+
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef uint32_t u6v __attribute__((ext_vector_type(6)));
+
+struct LaneArgs {
+  const void* X;
+  uint8_t* a6;       // operand of the 4-bit rows
+  float* scales;
+  float* abot;       // top levels: the block sums [B][s / 2^RLOG][d] go here, unfinished; else nullptr
+  int s, d, k, khi, KT;
+  int R;             // the plan's block length: 2^RLOG tokens are one of its parts
+  size_t zeros_off;
+  Hi6Out hi6;
+  StampRag rag;
+};
+
+// 24 bytes of a fragment -> its places; dst = (lane group, row) of a block, half = fragment / 2
+__device__ __forceinline__ void store24(uint8_t* dst, u6v w, bool half) {
+  const u4 a = {half ? w[2] : w[0], half ? w[3] : w[1], half ? w[4] : w[2], half ? w[5] : w[3]};
+  const u2v b = {half ? w[0] : w[4], half ? w[1] : w[5]};
+  *reinterpret_cast<u4*>(dst + (half ? 2 * kPart : 0)) = a;
+  *reinterpret_cast<u2v*>(dst + kPart + (half ? 8 : 0)) = b;
+}
+// channels 2 i in ev[i], 2 i + 1 in od[i]: integers of magnitude up to 8 (or values that round to such)
+__device__ __forceinline__ u6v to_e2m3(f16v ev, f16v od) { return (u6v)__builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(ev, od, 8.0f); }
+
+// codes of 8-bit rows, 16 h + l, as two fragments
+__device__ __forceinline__ void store_hi24(const Hi6Out& o, int m, int KT, f16v ev, f16v od, int c) {
+  f16v hv[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) hv[h][i] = floorf(__builtin_fmaf(h ? od[i] : ev[i], 0.0625f, 0.5f));
+  const int gr = 32 * o.np, grp = m / gr, r = m - grp * gr, f = (c >> 5) & 3;
+  uint8_t* dst = o.p + ((size_t)grp * KT + (c >> 7)) * (2 * o.np * kBlock6) + (r >> 5) * (2 * kBlock6) + (f & 1) * 512 + (r & 31) * 16;
+  store24(dst, to_e2m3(hv[0], hv[1]), f >> 1);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    ev[i] = __builtin_fmaf(-16.0f, hv[0][i], ev[i]);
+    od[i] = __builtin_fmaf(-16.0f, hv[1][i], od[i]);
+  }
+  store24(dst + kBlock6, to_e2m3(ev, od), f >> 1);
+}
+
+// the sum of this lane's partner at lane distance 2^(l - 2)
+template <int l>
+__device__ __forceinline__ float partner(float x) {
+  const int i = __float_as_int(x);
+  if constexpr (l == 2) return __int_as_float(__builtin_amdgcn_update_dpp(0, i, 0xB1, 0xF, 0xF, true));       // quad_perm [1,0,3,2]
+  else if constexpr (l == 3) return __int_as_float(__builtin_amdgcn_update_dpp(0, i, 0x4E, 0xF, 0xF, true));  // quad_perm [2,3,0,1]
+  else {
+    static_assert(l == 4, "");
+    const int lo = __builtin_amdgcn_update_dpp(0, i, 0x104, 0xF, 0xF, true);             // row_shl 4: lane n takes lane n + 4
+    return __int_as_float(__builtin_amdgcn_update_dpp(lo, i, 0x114, 0xF, 0xA, false));   // row_shr 4 into the odd quads
+  }
+}
+
+// largest over the lanes of equal token pair (NL lanes apart)
+template <int NL>
+__device__ __forceinline__ uint32_t across_groups(uint32_t x) {
+  if constexpr (NL <= 4) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xF, 0xF, true));  // row_ror 4
+  if constexpr (NL <= 8) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true));  // row_ror 8
+  auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = max(p[0], p[1]);
+  auto q = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return max(q[0], q[1]);
+}
+
+// largest magnitude (ASYM: order key of the largest value) of 32 channels.  A NaN is passed over unless it has eight
+// neighbours of its kind (one thread's share in the streaming kernels); nan_max: it is the largest value.
+template <bool ASYM>
+struct RowMax {
+  float hi[4], lo[4], nan = 0.0f;  // nan: not 0 if a value is no number or infinite
+  template <bool NANMAX>
+  __device__ __forceinline__ void add(int c, float v) {
+    const float x = ASYM ? v : fabsf(v);
+    hi[c >> 3] = (c & 7) == 0 ? x : fmaxf(hi[c >> 3], x);
+    if constexpr (ASYM) lo[c >> 3] = (c & 7) == 0 ? x : fminf(lo[c >> 3], x);
+    if constexpr (NANMAX) nan = __builtin_fmaf(v, 0.0f, nan);
+  }
+  __device__ __forceinline__ uint32_t pos() const {
+    uint32_t m = 0u;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) m = max(m, ASYM ? fkey(hi[g]) : __float_as_uint(hi[g]));
+    return m;
+  }
+  __device__ __forceinline__ uint32_t neg() const {
+    uint32_t m = 0u;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) m = max(m, fkey(-lo[g]));
+    return m;
+  }
+};
+
+// scale, reciprocal and offset of a row from its maxima (already times the row's norm)
+template <bool ASYM>
+__device__ __forceinline__ void row_params(float hi, float nlo, float qmax, float& scale, float& inv, float& z) {
+  scale = inv = z = 0.0f;
+  if constexpr (ASYM) {
+    asym_params(hi, nlo, qmax, scale, inv, z);
+  } else if (hi > 0.0f) {
+    scale = __fdiv_rn(hi, qmax);
+    inv = __fdiv_rn(qmax, hi);
+  }
+}
+
+// RAG: blocks of a 1-D Haar transform of any length (StampRag), one more workgroup for the token left out.
+// NG = 2: a lane holds two groups of 32 channels, for layers as wide as a
+// model's down-projection.  NANMAX: a NaN is the largest value of a block sum's row.
+template <int RLOG, bool BF16, bool ASYM, bool RAG, int NG, bool NANMAX>
+__global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs a) {
+  constexpr int RK = 1 << RLOG, NL = RK / 2, CPR = BF16 ? 4 : 8;  // tokens, lanes per group of channels, 16-byte loads per token
+  __shared__ __attribute__((aligned(16))) uint32_t s_max[2][RK][16];  // [sign][row][wave]
+  extern __shared__ __attribute__((aligned(16))) uint8_t s_row[];     // NG = 2: row A of the first group, [8][threads] 16 bytes
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = (int)(blockDim.x >> 6);
+  const int tl = lane & (NL - 1), b = blockIdx.y;
+  const int parts = RAG ? 1 : a.R >> RLOG, j = (int)blockIdx.x / parts, part = (int)blockIdx.x - j * parts;  // block, part of it
+  const size_t seq0 = (size_t)b * a.s, row_bytes = (size_t)a.d * (BF16 ? 2 : 4);
+  const bool left_out = RAG && j == a.rag.nb;  // the token left out: a row of its own, in the lanes of tl = 0
+  const int m = left_out ? 1 : RAG && j == a.rag.nb - 1 ? a.rag.mlast : RK;
+  const uint8_t* const X_blk =
+      reinterpret_cast<const uint8_t*>(a.X) + (seq0 + (left_out || !RAG ? 0 : a.rag.o) + (left_out ? 0 : (size_t)blockIdx.x * RK)) * row_bytes;
+  int c0[NG];
+  u4 raw[NG][2][CPR];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    c0[g] = ((g * nw + wave) * (64 / NL) + lane / NL) * 32;
+    // lanes beyond d_in redo the last channels: duplicates cannot change a row maximum, and they store nothing
+    const uint32_t off = (uint32_t)(min(c0[g], a.d - 32) * (BF16 ? 2 : 4));
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const uint32_t trow = (uint32_t)(RAG ? min(2 * tl + t, m - 1) : 2 * tl + t) * (uint32_t)row_bytes;
+#pragma unroll
+      for (int h = 0; h < CPR; ++h) raw[g][t][h] = *reinterpret_cast<const u4*>(X_blk + (trow + off) + 16 * h);
+    }
+  }
+  // per lane and level: sign of its own sum (+ in the lower lane of a pair), whether the lane takes part, whether its pair is whole
+  float sg[RLOG + 1];
+  bool in[RLOG + 1], whole[RLOG + 1];
+#pragma unroll
+  for (int l = 2; l <= RLOG; ++l) {
+    sg[l] = (tl >> (l - 2)) & 1 ? -1.0f : 1.0f;
+    in[l] = (tl & ((1 << (l - 2)) - 1)) == 0;
+    whole[l] = !RAG || 2 * (tl & ~((1 << (l - 1)) - 1)) + (1 << (l - 1)) < m;
+  }
+  // channel c of this lane: va its level-1 difference, vb its other row (not normalised; RAG: scaled at every level)
+  auto transform = [&](const u4 (&w)[2][CPR], int c, float& va, float& vb) __attribute__((always_inline)) {
+    float x[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      if constexpr (BF16) x[t] = (c & 1) ? bf16hi(w[t][c >> 3][(c >> 1) & 3]) : bf16lo(w[t][c >> 3][(c >> 1) & 3]);
+      else x[t] = __uint_as_float(w[t][BF16 ? 0 : c >> 2][c & 3]);
+    }
+    float s = __fadd_rn(x[0], x[1]);
+    va = __fsub_rn(x[0], x[1]);
+    if constexpr (RAG) {
+      s = 2 * tl + 1 < m ? __fmul_rn(s, kInvSqrt2) : x[0];
+      va = __fmul_rn(va, kInvSqrt2);
+    }
+    auto level = [&](auto l_tag) __attribute__((always_inline)) {
+      constexpr int l = decltype(l_tag)::value;
+      if constexpr (l <= RLOG) {
+        // lower lane: own + partner's, upper lane: partner's - own (the product is exact)
+        float r = __builtin_fmaf(s, sg[l], partner<l>(s));
+        if constexpr (RAG) {
+          r = __fmul_rn(r, kInvSqrt2);
+          s = in[l] && (whole[l] || sg[l] < 0.0f) ? r : s;
+        } else {
+          s = l == 2 || in[l] ? r : s;
+        }
+      }
+    };
+    level(std::integral_constant<int, 2>{});
+    level(std::integral_constant<int, 3>{});
+    level(std::integral_constant<int, 4>{});
+    vb = s;
+  };
+  float ra[32], rb[NG][32];  // rows A and B
+  uint32_t pos[2] = {0u, 0u}, neg[2] = {0u, 0u};
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    RowMax<ASYM> ma, mb;
+#pragma unroll
+    for (int c = 0; c < 32; ++c) {
+      if ((c & 7) == 0) __builtin_amdgcn_sched_barrier(0);  // the loaded words give way to the rows
+      float va, vb;
+      transform(raw[g], c, va, vb);
+      ra[c] = va;
+      rb[g][c] = vb;
+      ma.template add<false>(c, va);
+      mb.template add<NANMAX>(c, vb);
+    }
+    if constexpr (NG == 2) {
+      if (g == 0) {  // (they do not fit the registers beside the second group's)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          *reinterpret_cast<float4*>(s_row + (i * (int)blockDim.x + tid) * 16) = make_float4(ra[4 * i], ra[4 * i + 1], ra[4 * i + 2], ra[4 * i + 3]);
+      }
+    }
+    // lanes beyond d_in: the asymmetric form's keys must not see them (in the symmetric one their duplicates change nothing)
+    const bool live = !ASYM || c0[g] < a.d;
+    pos[0] = max(pos[0], live ? ma.pos() : 0u);
+    pos[1] = max(pos[1], live ? mb.pos() : 0u);
+    if constexpr (ASYM) {
+      neg[0] = max(neg[0], live ? ma.neg() : 0u);
+      neg[1] = max(neg[1], live ? mb.neg() : 0u);
+    }
+    if constexpr (NANMAX) {
+      if (mb.nan != 0.0f && tl == 0 && live) {  // rare
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+          pos[1] = max(pos[1], ASYM ? fkey(rb[g][i]) : absbits(rb[g][i]));
+          if constexpr (ASYM) neg[1] = max(neg[1], fkey(-rb[g][i]));
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    pos[h] = across_groups<NL>(pos[h]);
+    if constexpr (ASYM) neg[h] = across_groups<NL>(neg[h]);
+    if (lane < NL) {
+      s_max[0][h * NL + tl][wave] = pos[h];
+      if constexpr (ASYM) s_max[1][h * NL + tl][wave] = neg[h];
+    }
+  }
+  __syncthreads();
+  auto reduce = [&](int sign, int row) {
+    const u4* q = reinterpret_cast<const u4*>(&s_max[sign][row][0]);
+    uint32_t mx = 0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const u4 v = q[i];
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        if (4 * i + w < nw) mx = max(mx, v[w]);
+    }
+    return mx;
+  };
+  // the two rows of this lane: level (0: no norm), position in the plan's block, row of the sequence (RAG: STaMP slot, < 0: no
+  // such coefficient)
+  const int z2 = tl == 0 ? RLOG : __builtin_ctz((unsigned)tl) + 2;  // level of row B (the block sum: that of the last difference)
+  const int R = RAG ? RK : a.R;
+  const int ea = (R >> 1) + NL * part + tl, eb = tl == 0 ? 0 : (R >> z2) + (RK >> z2) * part + (tl >> (z2 - 1));
+  const int sa = RAG ? (left_out ? -1 : stamp_rag_slot(a.rag, j, ea)) : j * R + ea;
+  const int sb = RAG ? (left_out ? (tl == 0 ? 0 : -1) : stamp_rag_slot(a.rag, j, eb)) : j * R + eb;
+  const int top_slot = RAG ? (left_out ? 0 : a.rag.o + j) : j;
+  const bool sum_out = !RAG && a.abot != nullptr, row8 = !sum_out && top_slot < a.khi;  // (uniform)
+  const float na = RAG ? 1.0f : kInvSqrt2, nb = RAG ? 1.0f : haar_norm(z2);
+  const float qb = ASYM ? (tl == 0 && row8 ? 255.0f : 15.0f) : (tl == 0 && row8 ? 127.0f : 7.0f);
+  float scale_a, inv_a, za, scale_b, inv_b, zb;
+  if constexpr (ASYM) {
+    row_params<true>(__fmul_rn(fkey_inv(reduce(0, tl)), na), __fmul_rn(fkey_inv(reduce(1, tl)), na), 15.0f, scale_a, inv_a, za);
+    row_params<true>(__fmul_rn(fkey_inv(reduce(0, NL + tl)), nb), __fmul_rn(fkey_inv(reduce(1, NL + tl)), nb), qb, scale_b, inv_b, zb);
+  } else {
+    row_params<false>(__fmul_rn(__uint_as_float(reduce(0, tl)), na), 0.0f, 7.0f, scale_a, inv_a, za);
+    row_params<false>(__fmul_rn(__uint_as_float(reduce(0, NL + tl)), nb), 0.0f, qb, scale_b, inv_b, zb);
+  }
+  if (tid < NL) {
+    if (sa >= 0) {
+      a.scales[seq0 + sa] = scale_a;
+      if constexpr (ASYM) a.scales[a.zeros_off + seq0 + sa] = za;
+    }
+    if (sb >= 0 && !(sum_out && tl == 0)) {
+      a.scales[seq0 + sb] = scale_b;
+      if constexpr (ASYM) a.scales[a.zeros_off + seq0 + sb] = zb;
+    }
+  }
+  // differences of even levels: their norm, a power of two, is part of the multiplier
+  const bool fold = !RAG && tl != 0 && (z2 & 1) == 0;
+  const float mb_ = fold ? __fmul_rn(inv_b, nb) : inv_b, nb_ = fold ? 1.0f : nb;
+  const size_t brow = RAG ? ((size_t)b * a.rag.nb + j) * RK : seq0 + (size_t)j * R;
+  uint8_t* const out = a.a6 + (brow >> 8) * (size_t)a.KT * kStageA6;
+  auto place = [&](int e, int c) {
+    const uint32_t mr = (uint32_t)(brow & 255) + (uint32_t)e;
+    return out + ((uint32_t)(c >> 7) * (uint32_t)kStageA6 + (mr >> 5) * kBlock6 + (mr & 31) * 16 + ((c >> 5) & 1) * 512);
+  };
+  // codes of 16 values; shift: what the stored code is below the unsigned one
+  auto code = [&](const float (&x)[32], int odd, float n, float mul, float z, bool two) __attribute__((always_inline)) {
+    f16v v;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float p = __fmul_rn(two ? __fmul_rn(x[2 * i + odd], n) : x[2 * i + odd], mul);
+      v[i] = ASYM ? __builtin_amdgcn_fmed3f(__fadd_rn(rintf(p), z - 8.0f), -8.0f, 7.0f) : p;
+    }
+    return v;
+  };
+#pragma unroll
+  for (int g = NG - 1; g >= 0; --g) {
+    const int c = c0[g];
+    const bool active = c < a.d, half = (c >> 6) & 1;
+    if constexpr (NG == 2) {
+      if (g == 0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float4 v = *reinterpret_cast<const float4*>(s_row + (i * (int)blockDim.x + tid) * 16);
+          ra[4 * i] = v.x;
+          ra[4 * i + 1] = v.y;
+          ra[4 * i + 2] = v.z;
+          ra[4 * i + 3] = v.w;
+        }
+      }
+    }
+    const u6v wa = to_e2m3(code(ra, 0, na, inv_a, za, !RAG), code(ra, 1, na, inv_a, za, !RAG));
+    if (active && (!RAG || sa >= 0)) store24(place(ea, c), wa, half);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const int c = c0[g];
+    const bool active = c < a.d, half = (c >> 6) & 1;
+    if (sum_out) {
+      if (active && tl == 0) {
+        float4* o = reinterpret_cast<float4*>(a.abot + ((size_t)b * (a.s >> RLOG) + blockIdx.x) * a.d + c);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] = make_float4(rb[g][4 * i], rb[g][4 * i + 1], rb[g][4 * i + 2], rb[g][4 * i + 3]);
+      }
+    } else if (row8) {
+      if (active && tl == 0) {
+        const float qlo = ASYM ? 0.0f : -127.0f, qhi = ASYM ? 255.0f : 127.0f, shift = ASYM ? 128.0f : 0.0f;
+        f16v qe, qo;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float te = RAG ? rb[g][2 * i] : __fmul_rn(rb[g][2 * i], nb), to = RAG ? rb[g][2 * i + 1] : __fmul_rn(rb[g][2 * i + 1], nb);
+          qe[i] = fminf(fmaxf(__fadd_rn(rintf(__fmul_rn(te, inv_b)), zb), qlo), qhi) - shift;
+          qo[i] = fminf(fmaxf(__fadd_rn(rintf(__fmul_rn(to, inv_b)), zb), qlo), qhi) - shift;
+        }
+        store_hi24(a.hi6, b * a.khi + top_slot, a.KT, qe, qo, c);
+      }
+    }
+    const u6v wb = to_e2m3(code(rb[g], 0, nb_, mb_, zb, !RAG), code(rb[g], 1, nb_, mb_, zb, !RAG));
+    if (active && (!RAG || sb >= 0) && !(tl == 0 && (sum_out || row8))) store24(place(eb, c), wb, half);
+  }
+}
+
+template <int RLOG, bool BF16, bool ASYM, bool RAG>
+hipError_t launch_n(const LaneArgs& a, int blocks, int B, hipStream_t st) {
+  constexpr int CW = 64 / (1 << (RLOG - 1)) * 32;  // channels of a wave
+  const int waves = (a.d + CW - 1) / CW;
+  const dim3 grid(blocks, B);
+  const bool nan_max = !RAG && a.d > (BF16 ? 8192 : 4096);  // as the streaming kernels with split channels
+  if (waves > 16) {
+    if constexpr (BF16 && !RAG && RLOG == 3) {
+      if (waves > 24 || !nan_max) return hipErrorInvalidValue;
+      const int threads = (waves + 1) / 2 * 64;
+      const size_t lds = (size_t)threads * 128;
+      static size_t lds_done[kStampMaxDevices] = {};
+      const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_lanes1d<RLOG, BF16, ASYM, false, 2, true>), lds, lds_done);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL((k_lanes1d<RLOG, BF16, ASYM, false, 2, true>), grid, dim3(threads), lds, st, a);
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+  }
+  if constexpr (!RAG && RLOG == 3) {
+    if (nan_max) {
+      hipLaunchKernelGGL((k_lanes1d<RLOG, BF16, ASYM, false, 1, true>), grid, dim3(waves * 64), 0, st, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_lanes1d<RLOG, BF16, ASYM, RAG, 1, false>), grid, dim3(waves * 64), 0, st, a);
+  return hipGetLastError();
+}
+template <int RLOG, bool RAG>
+hipError_t launch(const LaneArgs& a, int x_bf16, int asym, int blocks, int B, hipStream_t st) {
+  if (x_bf16) return asym ? launch_n<RLOG, true, true, RAG>(a, blocks, B, st) : launch_n<RLOG, true, false, RAG>(a, blocks, B, st);
+  return asym ? launch_n<RLOG, false, true, RAG>(a, blocks, B, st) : launch_n<RLOG, false, false, RAG>(a, blocks, B, st);
+}
+
+}  // namespace
+
+// Plans that these kernels serve: the channels fit one workgroup; more than its 16 waves hold in one group of 32 per lane only
+// where the blocks fill more than half of the CUs (2 against 1 pass over X: 512 x 11008 16.1 us in two passes over split channels,
+// 17.7 here, 1024: 17.1, 17.8, 2048: 32.5, 21.5, 4096 (min-max codes): 66.6, 35.8).
+bool stamp_lanes1d_fits(const stamp_plan* p, int rlog) {
+  const StampGeom& g = p->geom;
+  if (g.d < 64) return false;  // two of a wave's 64 lanes per token pair: 16 x 1024 tokens x 32 18.8 us streaming, 19.2 here
+  if (rlog == 4) return g.d <= 4096;
+  if (rlog != 3) return false;
+  if (g.d <= 8192) return true;
+  return g.x_bf16 && !p->rag.on && g.d <= 12288 && (int64_t)g.B * g.s > 4 * stamp_device_cus();
+}
+
+hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, uint8_t* a6, float* scales, float* abot, uint8_t* h6, int np,
+                                hipStream_t st) {
+  const StampGeom& g = p->geom;
+  LaneArgs a = {};
+  a.X = X;
+  a.a6 = a6;
+  a.scales = scales;
+  a.abot = abot;
+  a.R = g.R;
+  a.s = g.s;
+  a.d = g.d;
+  a.k = g.k;
+  a.khi = g.khi;
+  a.KT = p->Kpad >> 7;
+  a.zeros_off = (size_t)g.B * g.s;
+  a.hi6 = Hi6Out{h6, np};
+  a.rag = p->rag;
+  if (p->rag.on) {
+    const int blocks = p->rag.nb + p->rag.o;
+    return rlog == 3 ? launch<3, true>(a, g.x_bf16, g.asym, blocks, g.B, st) : launch<4, true>(a, g.x_bf16, g.asym, blocks, g.B, st);
+  }
+  return rlog == 3 ? launch<3, false>(a, g.x_bf16, g.asym, g.s / 8, g.B, st) : launch<4, false>(a, g.x_bf16, g.asym, g.s / 16, g.B, st);
+}

@@ -55,6 +55,40 @@ def test_rule_of_the_8bit_rows_pipeline(kw, fp6):
     plan.destroy()
 
 
+# ---- blocks of 8 and 16 tokens by lanes (FP6 operands straight from the quantizer): the widths on either side of what one group of
+# channels per lane holds and the widest of all, a last wave that is partly empty, blocks of any length, several sequences
+def _lanes(d, levels=3, **kw):
+    base = dict(seq_len=2048 if d > 8192 else 128, levels=levels, k_hi=16, d_in=d, d_out=66, seed=600 + d)
+    base.update(kw)
+    return _wl("lanes_d%d_l%d_%s" % (d, levels, "_".join(f"{k}{v}" for k, v in kw.items())), **base)
+
+
+LANES = [_lanes(64, batch=3, x_dtype="bf16"), _lanes(96, act_quant="asym", mean_shift=0.4), _lanes(544, levels=4, k_hi=8, x_dtype="bf16"),
+         _lanes(4096, levels=4, k_hi=8), _lanes(4064, levels=4, k_hi=8, act_quant="asym", mean_shift=0.4, x_dtype="bf16"),
+         _lanes(8192, x_dtype="bf16"), _lanes(8192, act_quant="asym"), _lanes(4128), _lanes(8224, x_dtype="bf16"),
+         _lanes(12288, x_dtype="bf16", act_quant="asym", mean_shift=0.4), _lanes(1184, levels=7, k_hi=16, x_dtype="bf16"),
+         _lanes(1056, levels=8, k_hi=16, seq_len=256, batch=2, act_quant="asym"), _lanes(8192, seq_len=131, skip_first=True, x_dtype="bf16"),
+         _lanes(224, levels=4, seq_len=402, skip_first=True, batch=2, act_quant="asym", mean_shift=0.4), _lanes(4096, levels=4, seq_len=203)]
+
+
+@pytest.mark.parametrize("w", LANES, ids=[w.name for w in LANES])
+def test_blocks_by_lanes(w):
+    import torch
+    import paper_2510_26771_amd as st
+    tl.full_case(w, with_bias=True, check_unfused=False, engines=("fp6",), routes=("direct",))
+    # the same codes as the quantizer that packs them: the same output bit for bit
+    inp = tl.make_inputs(w)
+    plan = st.StampPlan(tl.plan_desc_for(w, "f32"), torch.from_numpy(inp["W"]).cuda())
+    X = tl.to_device_x(inp, w)
+    Y = [torch.empty((w.batch, w.seq_len, w.d_out), dtype=torch.float32, device="cuda") for _ in range(2)]
+    for packed in (0, 1):
+        plan.set_choice("operands", packed)
+        plan.linear_forward(X, Y[packed], plan.alloc_workspace())
+    torch.cuda.synchronize()
+    assert torch.equal(Y[0], Y[1])
+    plan.destroy()
+
+
 # ---- who writes the FP6 operands: the quantizer, or a pass over packed codes (sizes where one form is at least 1.05 times as
 # fast: quantizers by rows, by blocks on a line, of any length, on a grid)
 OPERANDS = [(dict(xform="identity", levels=0, batch=32, seq_len=1024, k_hi=2, d_in=256), False),
