@@ -294,7 +294,8 @@ typedef enum { STAMP_GEMM_INT8 = 0, STAMP_GEMM_FP6 = 1 } stamp_gemm_engine_t;
 stamp_status_t stamp_plan_set_gemm_engine(stamp_plan_t* plan, int32_t engine);
 
 /* Which kernels serve a plan is decided by rules on its sizes.  For tests and measurements, one of them can be overridden:
- *   STAMP_CHOICE_HI_ROWS   GEMM of the 8-bit rows: 1 = int8 pipeline, 2 = FP6 pipeline (where that kernel can run them at all)
+ *   STAMP_CHOICE_HI_ROWS   GEMM of the 8-bit rows: 1 = int8 pipeline, 2 = their own kernel on the FP6 pipeline (where that can run
+ *                          them at all)
  *   STAMP_CHOICE_OPERANDS  codes of stamp_linear_forward: 1 = packed as stamp_quantize_act leaves them, then converted by
  *                          a pass of their own, 2 = written as FP6 operands by the quantizer (where it can)
  * and 0 = by rule again.  It modifies the plan (not thread-safe, no call on the plan may be in progress on another host
@@ -314,7 +315,8 @@ typedef enum {
   STAMP_ROUTE_HI_TOP_FUSED = 64,      /* 8-bit rows on the int8 pipeline, top levels of the inverse in the epilogue */
   STAMP_ROUTE_HI_SPLIT = 128,         /* 8-bit rows on the int8 pipeline in several parts of the depth */
   STAMP_ROUTE_TILES_128 = 256,        /* 4-bit rows in 128 x 256 tiles instead of 256 x 256 */
-  STAMP_ROUTE_GROUP_QUANT = 512       /* per-block scales on blocks of a token grid: transform and quantizer in one kernel */
+  STAMP_ROUTE_GROUP_QUANT = 512,      /* per-block scales on blocks of a token grid: transform and quantizer in one kernel */
+  STAMP_ROUTE_HI_IN_TILES = 1024      /* 8-bit rows in the tiles of the 4-bit rows' GEMM */
 } stamp_route_t;
 int32_t stamp_debug_routes(const stamp_plan_t* plan);
 

@@ -32,10 +32,10 @@ hipError_t stamp_bottom1d_4(const stamp_plan* p, const void* X, uint8_t* q_lo, f
 hipError_t stamp_bottom1d_5(const stamp_plan* p, const void* X, uint8_t* q_lo, float* scales, float* abot, int nthreads, const void* split, hipStream_t st);
 hipError_t stamp_bottom1d_6(const stamp_plan* p, const void* X, uint8_t* q_lo, float* scales, float* abot, int nthreads, const void* split, hipStream_t st);
 hipError_t stamp_bottom1d_7(const stamp_plan* p, const void* X, uint8_t* q_lo, float* scales, float* abot, int nthreads, const void* split, hipStream_t st);
-hipError_t stamp_bottom1d_rag_3(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, uint8_t* h6, int np, hipStream_t st);
-hipError_t stamp_bottom1d_rag_4(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, uint8_t* h6, int np, hipStream_t st);
-hipError_t stamp_bottom1d_rag_5(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, uint8_t* h6, int np, hipStream_t st);
-hipError_t stamp_bottom1d_rag_6(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, uint8_t* h6, int np, hipStream_t st);
+hipError_t stamp_bottom1d_rag_3(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, const StampHiOut& hi6, hipStream_t st);
+hipError_t stamp_bottom1d_rag_4(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, const StampHiOut& hi6, hipStream_t st);
+hipError_t stamp_bottom1d_rag_5(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, const StampHiOut& hi6, hipStream_t st);
+hipError_t stamp_bottom1d_rag_6(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, const StampHiOut& hi6, hipStream_t st);
 
 namespace {
 
@@ -300,10 +300,7 @@ __global__ __launch_bounds__(256) void k_quant_rows(const void* __restrict__ X, 
 }  // namespace
 
 namespace {
-Hi6Out hi6_out(const StampDirect* dir) {
-  if (dir == nullptr) return Hi6Out{nullptr, 1};
-  return Hi6Out{dir->h6, dir->np};
-}
+Hi6Out hi6_out(const StampDirect* dir) { return dir != nullptr ? dir->hi : Hi6Out{}; }
 template <bool BF16, bool ASYM>
 void launch_quant_rows(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, const StampDirect* dir, hipStream_t st) {
   const StampGeom& g = p->geom;
@@ -326,12 +323,12 @@ hipError_t stamp_launch_actquant_rag(const stamp_plan* p, const void* X, int8_t*
                                      const StampDirect* dir) {
   const Hi6Out hi6 = hi6_out(dir);
   if (dir != nullptr) q_lo = dir->a6;
-  if (dir != nullptr && stamp_lanes1d_fits(p, p->rag.r)) return stamp_launch_lanes1d(p, p->rag.r, X, q_lo, scales, nullptr, hi6.p, hi6.np, st);
+  if (dir != nullptr && stamp_lanes1d_fits(p, p->rag.r)) return stamp_launch_lanes1d(p, p->rag.r, X, q_lo, scales, nullptr, hi6, st);
   switch (p->rag.r) {
-    case 3: return stamp_bottom1d_rag_3(p, X, q_hi, q_lo, scales, hi6.p, hi6.np, st);
-    case 4: return stamp_bottom1d_rag_4(p, X, q_hi, q_lo, scales, hi6.p, hi6.np, st);
-    case 5: return stamp_bottom1d_rag_5(p, X, q_hi, q_lo, scales, hi6.p, hi6.np, st);
-    case 6: return stamp_bottom1d_rag_6(p, X, q_hi, q_lo, scales, hi6.p, hi6.np, st);
+    case 3: return stamp_bottom1d_rag_3(p, X, q_hi, q_lo, scales, hi6, st);
+    case 4: return stamp_bottom1d_rag_4(p, X, q_hi, q_lo, scales, hi6, st);
+    case 5: return stamp_bottom1d_rag_5(p, X, q_hi, q_lo, scales, hi6, st);
+    case 6: return stamp_bottom1d_rag_6(p, X, q_hi, q_lo, scales, hi6, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -425,7 +422,7 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
   if (!(part & 1)) {
     // bottom kernel skipped
   } else if (!g.is2d && bot != nullptr && stamp_lanes1d_fits(p, g.r)) {
-    const hipError_t le = stamp_launch_lanes1d(p, g.r, X, q_lo, scales, top_in_bottom ? nullptr : abot, sp.hi6.p, sp.hi6.np, st);
+    const hipError_t le = stamp_launch_lanes1d(p, g.r, X, q_lo, scales, top_in_bottom ? nullptr : abot, sp.hi6, st);
     if (le != hipSuccess) return le;
   } else if (!g.is2d) {
     switch (g.r) {

@@ -365,8 +365,26 @@ inline hipError_t launch_block_sums_own(const stamp_plan* p, const int8_t* q_hi,
 // stay int8, the 4-bit rows are converted right before their GEMM instead (stamp_launch_repack6): the pass takes 6.8 us after the
 // 8-bit rows' GEMM and 10.0 before it (16384 x 1024).
 inline hipError_t convert_rows(const stamp_plan* p, const int8_t* q_hi, const uint8_t* q_lo, uint8_t* a6, int own, void* ws, hipStream_t st) {
-  const StampHi6Pack hp = stamp_hi6_pack(p, q_hi, at(ws, p->ws_hi6), own);
+  const StampHi6Pack hp = stamp_hi6_pack(p, q_hi, at(ws, p->ws_hi6), own, StampHiTiles{});
   return stamp_launch_repack6(p, q_lo, a6, st, &hp);
+}
+
+// The 8-bit rows' operand in the tiles of the 4-bit rows, when it is converted from codes (hi.ht.on: the plan takes them along and
+// there is room): over the quantizer's scratch, or over the block sums and their parts, which that form does not have.
+inline StampHiOut tiles_operand(const stamp_plan* p, int own, void* ws) {
+  StampHiTiles ht = stamp_hi_tiles(p, own);
+  size_t off = p->ws_abot;
+  if (ht.on) {
+    const size_t need = stamp_hi_tiles_bytes(p);
+    if (p->rag.on) {
+      off = p->ws_T[2];
+      ht.on = need <= p->ws_Yt[0] - p->ws_T[2];
+    } else if (need > p->ws_qhi - p->ws_abot) {
+      off = p->ws_ythi;
+      ht.on = need <= p->ws_a6 - p->ws_ythi;
+    }
+  }
+  return stamp_hi6_out(p, at(ws, off), own, ht);
 }
 
 // Blocked form of the 1-D Haar transform of any length (rules: rag_geometry): block sums from the 8-bit rows, then the
@@ -378,12 +396,21 @@ stamp_status_t rag_forward_q(const stamp_plan* p, const int8_t* q_hi, const uint
   float* ythi = reinterpret_cast<float*>(at(ws, p->ws_ythi));
   float* P = reinterpret_cast<float*>(at(ws, p->ws_bP));
   uint8_t* blk = at(ws, p->ws_ba6);
-  uint8_t* hi6 = dir != nullptr ? dir->h6 : at(ws, p->ws_hi6);
+  uint8_t* hi6 = dir != nullptr ? dir->hi.p : at(ws, p->ws_hi6);
   const bool fp6 = p->engine == STAMP_GEMM_FP6;
   hipError_t e = hipSuccess;
+  const StampHiOut hi = dir != nullptr ? dir->hi : tiles_operand(p, 0, ws);
+  if (hi.ht.on) {
+    if (dir == nullptr) {
+      const StampHi6Pack hp = stamp_hi6_pack(p, q_hi, hi.p, 0, hi.ht);
+      e = stamp_launch_repack6_rag(p, q_lo, blk, st, &hp);
+    }
+    if (e == hipSuccess) e = stamp_launch_gemm_lo6_rag(p, blk, scales, Y, nullptr, st, &hi);
+    return e == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
+  }
   if (p->hi6[0]) {
     if (dir == nullptr) {
-      const StampHi6Pack hp = stamp_hi6_pack(p, q_hi, hi6, 0);
+      const StampHi6Pack hp = stamp_hi6_pack(p, q_hi, hi6, 0, StampHiTiles{});
       e = fp6 ? stamp_launch_repack6_rag(p, q_lo, blk, st, &hp) : stamp_launch_repack6(p, nullptr, nullptr, st, &hp);
     }
     if (e == hipSuccess) e = stamp_launch_hi6(p, hi6, scales, 3, P, p->Npad, 0, Y, stamp_haar_norm_host(p->rag.r), st);
@@ -422,7 +449,7 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
       const bool hi6 = p->geom.k > 0 && p->hi6[0];
       if (hi6) {
         if (dir == nullptr && convert_rows(p, q_hi, lo6 ? q_lo : nullptr, a6g, 0, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
-        if (stamp_launch_hi6(p, dir != nullptr ? dir->h6 : at(ws, p->ws_hi6), scales, 2, yt[0], 0, 0, nullptr, 1.0f, st) != hipSuccess) return STAMP_ERR_DEVICE;
+        if (stamp_launch_hi6(p, dir != nullptr ? dir->hi.p : at(ws, p->ws_hi6), scales, 2, yt[0], 0, 0, nullptr, 1.0f, st) != hipSuccess) return STAMP_ERR_DEVICE;
       } else if (p->geom.k > 0) {
         if (stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st) != hipSuccess) return STAMP_ERR_DEVICE;
         if (stamp_launch_merge_hi(p, ythi, p->hi_ksplit, yt[0], st) != hipSuccess) return STAMP_ERR_DEVICE;
@@ -448,7 +475,7 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
     const bool hi6 = p->geom.k > 0 && p->hi6[0];
     if (hi6) {
       if (dir == nullptr && convert_rows(p, q_hi, lo6 ? q_lo : nullptr, a6i, 0, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
-      if (stamp_launch_hi6(p, dir != nullptr ? dir->h6 : at(ws, p->ws_hi6), scales, 1, Y, 0, 0, nullptr, 1.0f, st) != hipSuccess) return STAMP_ERR_DEVICE;
+      if (stamp_launch_hi6(p, dir != nullptr ? dir->hi.p : at(ws, p->ws_hi6), scales, 1, Y, 0, 0, nullptr, 1.0f, st) != hipSuccess) return STAMP_ERR_DEVICE;
     } else if (p->geom.k > 0) {
       if (stamp_launch_gemm_hi(p, q_hi, scales, 1, ythi, st) != hipSuccess) return STAMP_ERR_DEVICE;
       if (stamp_launch_hi_rows_out(p, ythi, Y, st, p->hi_ksplit) != hipSuccess) return STAMP_ERR_DEVICE;
@@ -463,8 +490,16 @@ stamp_status_t forward_q(const stamp_plan* p, const int8_t* q_hi, const uint8_t*
   const bool fused = p->fused_ok && !p->unfused;
   const bool own = codes_are_ours && own_top(p);
   uint8_t* a6 = at(ws, p->ws_a6);
-  const uint8_t* hi6 = dir != nullptr ? dir->h6 : at(ws, p->ws_hi6);
+  const uint8_t* hi6 = dir != nullptr ? dir->hi.p : at(ws, p->ws_hi6);
   const bool fp6 = p->engine == STAMP_GEMM_FP6;
+  const StampHiOut hi = dir != nullptr ? dir->hi : tiles_operand(p, own, ws);
+  if (hi.ht.on) {
+    if (dir == nullptr) {
+      const StampHi6Pack hp = stamp_hi6_pack(p, q_hi, hi.p, own, hi.ht);
+      if (stamp_launch_repack6(p, q_lo, a6, st, &hp) != hipSuccess) return STAMP_ERR_DEVICE;
+    }
+    return stamp_launch_gemm_lo6(p, a6, scales, 2, Y, nullptr, st, own, &hi) == hipSuccess ? STAMP_OK : STAMP_ERR_DEVICE;
+  }
   if (dir == nullptr && p->hi6[own] && convert_rows(p, q_hi, fp6 ? q_lo : nullptr, a6, own, ws, st) != hipSuccess) return STAMP_ERR_DEVICE;
   if (own) {
     if (launch_block_sums_own(p, q_hi, scales, ythi, P, hi6, st) != hipSuccess) return STAMP_ERR_DEVICE;
@@ -538,6 +573,13 @@ bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
   if (!p->fused_ok || p->unfused) return false;
   if (own_top(p)) return p->hi6[1];
   return p->hi6[0] && (g.L > 0 || g.khi == g.k);
+}
+
+// Written by the quantizer itself the 8-bit rows' operand lies over the packed codes.
+StampHiOut direct_operand(const stamp_plan* p, int own, void* ws) {
+  StampHiTiles ht = stamp_hi_tiles(p, own);
+  if (ht.on && stamp_hi_tiles_bytes(p) > p->ws_scales - p->ws_qhi) ht.on = 0;
+  return stamp_hi6_out(p, at(ws, p->ws_qhi), own, ht);
 }
 
 // stamp_linear_forward, plans with top levels whose bottom kernel leaves packed codes: their conversion shares the launch of
@@ -721,6 +763,7 @@ int32_t stamp_debug_routes(const stamp_plan_t* p) {
     else if (!own && stamp_hi_top_fused(p)) r |= STAMP_ROUTE_HI_TOP_FUSED;
     else if ((own ? p->hi_ksplit_own : p->hi_ksplit) > 1) r |= STAMP_ROUTE_HI_SPLIT;
   }
+  if (stamp_hi_tiles(p, own).on) r |= STAMP_ROUTE_HI_IN_TILES;
   const int M = rag ? (g.B * p->rag.nb) << p->rag.r : g.B * g.s;
   if (p->engine == STAMP_GEMM_FP6 && stamp_gemm6_half_tiles(M, p->Npad)) r |= STAMP_ROUTE_TILES_128;
   return r;
@@ -768,15 +811,13 @@ stamp_status_t stamp_linear_forward(const stamp_plan_t* p, const void* X, void* 
   const bool direct = direct_route(p, X, Y);
   if (direct) {
     dir.a6 = at(ws, p->rag.on ? p->ws_ba6 : p->ws_a6);
-    dir.h6 = at(ws, p->ws_qhi);
-    dir.np = stamp_hi6_np(p, own_top(p));
+    dir.hi = direct_operand(p, own_top(p), ws);
   }
   const bool beside = !direct && convert_beside_top(p);
   if (beside) {
     // the 8-bit rows' operand is written when the packed codes have been converted, over them
     dir.a6 = at(ws, p->ws_a6);
-    dir.h6 = at(ws, p->ws_qhi);
-    dir.np = stamp_hi6_np(p, 0);
+    dir.hi = direct_operand(p, 0, ws);
     dir.lo_packed = 1;
   }
   const StampDirect* const dp = direct || beside ? &dir : nullptr;

@@ -11,7 +11,6 @@ hipError_t stamp_bottom1d_3(const stamp_plan* p, const void* X, uint8_t* q_lo, f
                   : launch_bottom1d<3, false, false>(p, X, q_lo, scales, abot, nthreads, sp, st);
 }
 
-hipError_t stamp_bottom1d_rag_3(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, uint8_t* h6, int np,
-                                hipStream_t st) {
-  return launch_rag_t<3>(p, X, q_hi, q_lo, scales, Hi6Out{h6, np}, st);
+hipError_t stamp_bottom1d_rag_3(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, const StampHiOut& hi6, hipStream_t st) {
+  return launch_rag_t<3>(p, X, q_hi, q_lo, scales, hi6, st);
 }

@@ -118,10 +118,21 @@ __device__ __forceinline__ size_t a6_row(size_t m, int KT) {
 }
 
 // an 8-bit row: codes 16 h + l to the operand of the kernel for few rows (stamp_hi6.h), row m of it
-struct Hi6Out {
-  uint8_t* p;  // nullptr: none
-  int np;
-};
+typedef StampHiOut Hi6Out;
+// K step stride of that operand, and every place of row m (offset of its h field of K step 0; l follows at *lo)
+__device__ __forceinline__ uint32_t hi_step_bytes(const Hi6Out& o) { return o.ht.on ? (uint32_t)kBlock6 : (uint32_t)(2 * o.np * kBlock6); }
+template <typename Store>
+__device__ __forceinline__ void hi_rows(const Hi6Out& o, int m, int KT, Store store) {
+  if (o.ht.on) {
+    const int b = m / o.seq;
+    int tile, ntiles, place;
+    stamp_hi_places(o.ht, b, m - b * o.seq, &tile, &ntiles, &place);
+    for (int i = 0; i < ntiles; ++i) store(o.p + (size_t)(tile + i) * KT * kBlock6 + place * 16, kHiPlaces * 16);
+  } else {
+    const int gr = 32 * o.np, grp = m / gr, r = m - grp * gr;
+    store(o.p + (size_t)grp * KT * (2 * o.np * kBlock6) + (r >> 5) * (2 * kBlock6) + (r & 31) * 16, kBlock6);
+  }
+}
 __device__ __forceinline__ void store_hi48(const Hi6Out& o, int m, int KT, const int (&q)[8], int c, bool active) {
   uint64_t h = 0, l = 0;
 #pragma unroll
@@ -130,11 +141,11 @@ __device__ __forceinline__ void store_hi48(const Hi6Out& o, int m, int KT, const
     h |= (uint64_t)((uint32_t)abs(hv) | ((uint32_t)(hv >> 31) & 32u)) << (6 * i);
     l |= (uint64_t)((uint32_t)abs(lv) | ((uint32_t)(lv >> 31) & 32u)) << (6 * i);
   }
-  const int gr = 32 * o.np, grp = m / gr, r = m - grp * gr;
-  const uint32_t ktb = (uint32_t)(2 * o.np * kBlock6);
-  uint8_t* dst = o.p + (size_t)grp * KT * ktb + (r >> 5) * (2 * kBlock6) + (r & 31) * 16 + off48(c, ktb);
-  store48(dst, (uint32_t)h, (uint32_t)(h >> 32), c, active);
-  store48(dst + kBlock6, (uint32_t)l, (uint32_t)(l >> 32), c, active);
+  const uint32_t off = off48(c, hi_step_bytes(o));
+  hi_rows(o, m, KT, [&](uint8_t* dst, int lo) {
+    store48(dst + off, (uint32_t)h, (uint32_t)(h >> 32), c, active);
+    store48(dst + off + lo, (uint32_t)l, (uint32_t)(l >> 32), c, active);
+  });
 }
 
 // max over the 8 values of v and of -v, as order keys

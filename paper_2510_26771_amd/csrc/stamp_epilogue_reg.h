@@ -94,13 +94,17 @@ struct RegEpiOperands {
   static constexpr int nb = (EPI == 2) ? 64 / (1 << RL) : 1;
   f2 sw, bias, cs;
   f2 P[nb];
+  template <bool WITH_P = true>
   __device__ __forceinline__ void request(const GemmArgs& a, int m0, int nw, int wm, int lane) {
     const int l32 = lane & 31, kg = lane >> 5;
     const int n = nw + 2 * l32;  // Npad is a multiple of 256: always inside the padded arrays
     sw = *reinterpret_cast<const f2*>(a.sw + n);
     bias = (a.bias != nullptr) ? *reinterpret_cast<const f2*>(a.bias + n) : (f2){0.0f, 0.0f};
     cs = a.g.asym ? *reinterpret_cast<const f2*>(a.colsum + n) : (f2){0.0f, 0.0f};
-    if constexpr (EPI == 2) {
+    if constexpr (EPI == 2 && !WITH_P) {
+#pragma unroll
+      for (int t = 0; t < nb; ++t) P[t] = (f2){0.0f, 0.0f};
+    } else if constexpr (EPI == 2) {
       constexpr int R = 1 << RL;
 #pragma unroll
       for (int t = 0; t < nb; ++t) {

@@ -521,6 +521,8 @@ stamp_gemm::GemmArgs stamp_gemm_args(const stamp_plan* p, const float* scales, v
   a.a_seq_rows = a.a_seq_used = 1;
   a.own_top = 0;
   a.rag = StampRag{};
+  a.H = nullptr;
+  a.ht = StampHiTiles{};
   return a;
 }
 

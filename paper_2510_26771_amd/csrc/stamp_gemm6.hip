@@ -157,11 +157,13 @@ bool stamp_gemm6_half_tiles(int M, int Npad) {
 
 namespace {
 hipError_t gemm6(const GemmArgs& a, int mode, hipStream_t st) {
+  if (a.ht.on) return mode == 2 ? stamp_gemm6_half_hi(a, st) : hipErrorInvalidValue;
   return mode != 0 && stamp_gemm6_half_tiles(a.M, a.Npad) ? stamp_gemm6_half(a, mode, st) : gemm6_run(a, mode, st);
 }
 }  // namespace
 
-hipError_t stamp_launch_gemm_lo6_rag(const stamp_plan* p, const uint8_t* a6, const float* scales, void* Y, const float* P, hipStream_t st) {
+hipError_t stamp_launch_gemm_lo6_rag(const stamp_plan* p, const uint8_t* a6, const float* scales, void* Y, const float* P, hipStream_t st,
+                                     const StampHiOut* hi) {
   GemmArgs a = stamp_gemm_args(p, scales, Y);
   a.A = a6;
   a.Bq = p->qW6_dev;
@@ -169,16 +171,24 @@ hipError_t stamp_launch_gemm_lo6_rag(const stamp_plan* p, const uint8_t* a6, con
   a.rag = p->rag;
   a.M = a.g.B * a.g.k * a.g.R;
   a.P = P;
+  if (hi != nullptr) {
+    a.H = hi->p;
+    a.ht = hi->ht;
+  }
   return gemm6(a, 2, st);
 }
 
 hipError_t stamp_launch_gemm_lo6(const stamp_plan* p, const uint8_t* a6, const float* scales, int mode, void* out,
-                                 const float* P, hipStream_t st, int own_top) {
+                                 const float* P, hipStream_t st, int own_top, const StampHiOut* hi) {
   GemmArgs a = stamp_gemm_args(p, scales, out);
   a.A = a6;
   a.Bq = p->qW6_dev;
   a.M = p->geom.B * p->geom.s;
   a.P = P;
   a.own_top = (mode == 2) ? own_top : 0;
+  if (hi != nullptr) {
+    a.H = hi->p;
+    a.ht = hi->ht;
+  }
   return gemm6(a, mode, st);
 }

@@ -35,12 +35,113 @@ using namespace stamp_gemm;
 // leave CUs idle (the rule stands at stamp_gemm6_half_tiles).
 constexpr int BN6 = 256;
 constexpr int kNumStage6 = 3;
-template <int WAVES>
+//
+// HI (WAVES = 4): the tile's 8-bit rows ride along as a fifth block of 32 operand rows (h of 16 places, then l; stamp_hi_places),
+// 3 KB more per K step and two MFMAs more per wave and half; their sums, the levels above and the block sums stay in
+// registers.  A launch and the stream of the weights a second time are saved (figures at stamp_hi_tiles).
+template <int WAVES, bool HI = false>
 struct Tile6 {
   static constexpr int BMW = 32 * WAVES;                    // rows
   static constexpr int kStageA = BMW / 32 * kBlock6;        // bytes of the activation part of a stage
-  static constexpr int kStage = kStageA + 2 * kStageB6;     // 48 or 36 KB
+  static constexpr int kStageAB = kStageA + 2 * kStageB6;
+  static constexpr int kStage = kStageAB + (HI ? 4096 : 0);  // 48, 36 or 40 KB
 };
+constexpr int kHiInfoBytes = 2 * kHiPlaces * 4;  // row factors and offsets of the places
+
+// whether one of the tile's blocks has an 8-bit row (or lends its place to the token left out)
+__device__ __forceinline__ bool hi_tile_has(const StampHiTiles& t, int tile) {
+  if (t.L > 0) return true;
+  const int j = (tile << t.lognb) % t.k;
+  return j < t.khi || j + (1 << t.lognb) > t.k;
+}
+// row factor and offset of one of a tile's places (0 where it has no row); the sums are of whole codes
+template <bool RAG>
+__device__ __forceinline__ void hi_place_info(const GemmArgs& a, int tile, int p, float& fac, float& rz) {
+  const StampGeom& g = a.g;
+  const StampHiTiles& t = a.ht;
+  fac = rz = 0.0f;
+  int b, up;
+  const int slot = stamp_hi_slot_of_place(t, g.B, tile, p, &b, &up);
+  if (slot < 0) return;
+  const size_t row = RAG ? (size_t)b * g.s + slot : (size_t)b * g.s + (size_t)slot * g.R;
+  const size_t zeros_off = (size_t)g.B * g.s;
+  fac = a.scales[row] * (RAG ? 1.0f : haar_norm_dev(g.r + up, g.is2d));
+  if (g.asym) rz = a.scales[zeros_off + row] - (slot < g.khi ? 128.0f : 8.0f);
+}
+// The 8-bit rows' block -> sums of the lane's blocks (eo.P); the token left out -> Y.  acch: register v is row 8 (v / 4) + 4 kg + v % 4,
+// i.e. h of a place in registers 0..7, l in 8..15.  Same operations in the same order as k_hi6.
+template <int RL, bool YBF16, bool SYM, bool RAG, typename Eo>
+__device__ __forceinline__ void hi_block_sums(const GemmArgs& a, const v16f (&acch)[2], const float* info, Eo& eo, int tile, int nw, int lane) {
+  constexpr int lognb = 7 - RL, nb = 1 << lognb;
+  const StampHiTiles& t = a.ht;
+  const int l32 = lane & 31, kg = lane >> 5, n = nw + 2 * l32;
+  float val[kHiPlaces][2];
+#pragma unroll
+  for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+      float x = __builtin_fmaf(16.0f, acch[ni][v], acch[ni][v + 8]) * 64.0f, y = x;
+      swap32(x, y);  // x: lane group 0's row, y: lane group 1's, in both
+      val[8 * (v >> 2) + (v & 3)][ni] = x;
+      val[8 * (v >> 2) + 4 + (v & 3)][ni] = y;
+    }
+#pragma unroll
+  for (int p = 0; p < kHiPlaces; ++p) {
+    const float fac = info[p], rz = SYM ? 0.0f : info[kHiPlaces + p];
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni) {
+      const float af = SYM ? val[p][ni] : __builtin_fmaf(-rz, eo.cs[ni], val[p][ni]);
+      val[p][ni] = (af * fac) * eo.sw[ni];
+    }
+  }
+  if constexpr (RAG) {
+    if (t.o) {  // the token left out has the place of block khi - 1
+      const int g0 = tile << lognb;
+      int b = g0 / t.k, j = g0 - b * t.k;
+#pragma unroll
+      for (int p = 0; p < nb; ++p) {
+        if (j == t.khi - 1 && b < a.g.B && kg == 0 && n < a.N)
+          put_pair<YBF16, false>(a.out, (size_t)b * a.g.s * a.N + n, val[p][0] + eo.bias[0], val[p][1] + eo.bias[1], a.N - n);
+        if (++j == t.k) {
+          j = 0;
+          ++b;
+        }
+      }
+    }
+    const float nrm = haar_norm_dev(a.g.r, 0);
+#pragma unroll
+    for (int p = 0; p < nb; ++p)
+#pragma unroll
+      for (int ni = 0; ni < 2; ++ni) val[p][ni] *= nrm;
+  } else if (t.L > 0) {
+    const int j0 = (tile << lognb) % t.k;
+#pragma unroll
+    for (int p = kHiPlaces - 1; p >= nb; --p) {  // the levels above the tile's sub-tree, coarsest first
+      const int up = lognb + 1 + p - nb;
+      if (up <= t.L) {
+        const float s = (j0 >> (up - 1)) & 1 ? -1.0f : 1.0f;
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) val[0][ni] = __builtin_fmaf(val[p][ni], s, val[0][ni]);
+      }
+    }
+#pragma unroll
+    for (int lev = lognb; lev >= 1; --lev)
+      if (lev <= t.L) {
+#pragma unroll
+        for (int i = 0; i < nb; i += 1 << lev)
+#pragma unroll
+          for (int ni = 0; ni < 2; ++ni) {
+            const float x = val[i][ni], d = val[i + (1 << (lev - 1))][ni];
+            val[i][ni] = x + d;
+            val[i + (1 << (lev - 1))][ni] = x - d;
+          }
+      }
+  }
+#pragma unroll
+  for (int q = 0; q < nb / 2; ++q)
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni) eo.P[q][ni] = kg ? val[2 * q + 1][ni] : val[2 * q][ni];
+}
 
 // tile of position sid in the walk: 8 M-tiles, then the next N-tile, group of 8 M-tiles after group
 __device__ __forceinline__ void tile_of_sid(int sid, int mt, int nt, int& tm, int& tn) {
@@ -53,18 +154,20 @@ __device__ __forceinline__ void tile_of_sid(int sid, int mt, int nt, int& tm, in
 
 // SYM: a fused-mode kernel for plans with symmetric activation codes (no offset term in the epilogue)
 // RAG: fused mode over the blocks of a 1-D Haar transform of any length (StampRag); ODD: for odd d_out
-template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM = false, bool RAG = false, bool ODD = false, int WAVES = 8>
-__global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(const GemmArgs a) {
+template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM = false, bool RAG = false, bool ODD = false, int WAVES = 8, bool HI = false>
+__global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm6(const GemmArgs a) {
   using Acc = AccF6Lo;
-  constexpr int BMW = Tile6<WAVES>::BMW, kStageA = Tile6<WAVES>::kStageA, kStage6 = Tile6<WAVES>::kStage;
+  constexpr int BMW = Tile6<WAVES, HI>::BMW, kStageA = Tile6<WAVES, HI>::kStageA, kStage6 = Tile6<WAVES, HI>::kStage;
+  constexpr int kStageAB = Tile6<WAVES, HI>::kStageAB;
   constexpr int NIW = NI;  // 32-column MFMA blocks per wave along N
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   constexpr int NT = 64 * WAVES;  // threads
   constexpr int kMainBytes = kNumStage6 * kStage6;
   uint8_t* const row_info = smem + kMainBytes;  // two buffers, alternating from tile to tile
-  constexpr int kRowInfo = kRowInfoBytes + (RAG ? 256 : 0);  // RAG: + the token factors of a short block
+  constexpr int kHiInfo = kRowInfoBytes + (RAG ? 256 : 0);  // RAG: + the token factors of a short block
+  constexpr int kRowInfo = kHiInfo + (HI ? kHiInfoBytes : 0);
   constexpr int nA = kStageA / (NT * 16), nB = 2 * kStageB6 / (NT * 16);  // 16-byte chunks per thread and step
-  constexpr int kLoadsPerStep = nA + nB;
+  constexpr int kLoadsPerStep = nA + nB + (HI ? 1 : 0);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
   // wave tile: rows [128 wm, +128), columns [32 NIW wn, +32 NIW)
@@ -99,6 +202,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
   }
   int rq_pos = local, rq_kt = 0, rq_stg = 0, rq_kk = rq_k0;  // rq_kt counts the tile's requests, rq_kk is their K step
   __amdgpu_buffer_rsrc_t rdA, rdB;
+  [[maybe_unused]] __amdgpu_buffer_rsrc_t rdH;  // HI: no records where the tile has no 8-bit row
   auto rq_tile = [&]() {
     int tm_, tn_;
     tile_of_sid(first + rq_pos, mt, nt, tm_, tn_);
@@ -106,6 +210,8 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
     const uint8_t* pa_ = WAVES == 8 ? a.A + (size_t)tm_ * KT * kStageA6 : a.A + (size_t)(tm_ >> 1) * KT * kStageA6 + (tm_ & 1) * kStageA;
     rdA = __builtin_amdgcn_make_buffer_rsrc((void*)pa_, 0, 0x7fffffff, 0x00020000);
     rdB = __builtin_amdgcn_make_buffer_rsrc((void*)(a.Bq + (size_t)(2 * tn_) * KT * kStageB6), 0, 0x7fffffff, 0x00020000);
+    if constexpr (HI)
+      rdH = __builtin_amdgcn_make_buffer_rsrc((void*)(a.H + (size_t)tm_ * KT * kBlock6), 0, hi_tile_has(a.ht, tm_) ? 0x7fffffff : 0, 0x00020000);
   };
   rq_tile();
   // A request = the kLoadsPerStep loads of the next K step of the walk into the next stage of the ring.  rq_begin
@@ -116,6 +222,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
   // in its first block (rq_tail2: still to be issued), the last before its second block (rq_tail3)
   bool rq_tail2 = false, rq_tail3 = false;
   uint8_t* rq_so = nullptr;
+  [[maybe_unused]] uint32_t rq_oh = 0;
   uint32_t rq_oa = 0, rq_ob = 0;  // byte offsets of the request's K step in the activation / weight panels
   auto rq_begin = [&]() {
     if (__builtin_expect(rq_kt == KT, 0)) {  // the tile of the request before this one is complete: its descriptors are no longer needed
@@ -128,11 +235,13 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
         // so every wait of the main loop is for the same number of them)
         rdA = __builtin_amdgcn_make_buffer_rsrc((void*)a.A, 0, 0, 0x00020000);
         rdB = rdA;
+        if constexpr (HI) rdH = rdA;
       }
     }
     rq_so = smem + rq_stg * kStage6 + wave * 1024;
     rq_oa = (uint32_t)rq_kk * (uint32_t)kStageA6;
     rq_ob = (uint32_t)rq_kk * (uint32_t)kStageB6;
+    if constexpr (HI) rq_oh = (uint32_t)rq_kk * (uint32_t)kBlock6;
     rq_kk = (rq_kk == KT - 1) ? 0 : rq_kk + 1;
     rq_stg = (rq_stg == kNumStage6 - 1) ? 0 : rq_stg + 1;
     ++rq_kt;
@@ -142,6 +251,9 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
     if constexpr (li < nA) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rdA, (void __attribute__((address_space(3)))*)(rq_so + li * (NT * 16)), 16, off16,
                                                rq_oa + (uint32_t)(li * (NT * 16)), 0, 0);
+    } else if constexpr (li >= nA + nB) {
+      // the fourth wave's kilobyte is the next K step's (its place in the stage is not read)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rdH, (void __attribute__((address_space(3)))*)(rq_so + kStageAB), 16, off16, rq_oh, 0, 0);
     } else {
       constexpr int i = li - nA;
       // chunk i * NT + tid of the 1536: column tile 1 (KT stages further on) from chunk 768 on (a whole number of waves)
@@ -151,11 +263,12 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
                                                off16, ob, 0, 0);
     }
   };
-  static_assert(kLoadsPerStep == (WAVES == 8 ? 6 : 9), "the main loop spreads six (nine) loads per wave and step");
+  static_assert(nA + nB == (WAVES == 8 ? 6 : 9), "the main loop spreads six (nine) loads per wave and step");
   // load i, and with four waves load i + 3 as well
   auto rq_issue2 = [&](auto i_tag) __attribute__((always_inline)) {
     rq_issue(i_tag);
     if constexpr (WAVES == 4) rq_issue(std::integral_constant<int, decltype(i_tag)::value + 3>{});
+    if constexpr (HI && decltype(i_tag)::value == 5) rq_issue(std::integral_constant<int, 9>{});
   };
   auto request_next = [&]() {
     rq_begin();
@@ -170,6 +283,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
   // LDS byte addresses of part 0 of this lane's 48 bytes in stage 0: 32-row block, then lane * 16
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
   const uint32_t adrA0 = (uint32_t)((wm * 4) * kBlock6 + lane * 16);
+  const uint32_t adrH0 = (uint32_t)(kStageAB + lane * 16);
   const uint32_t adrB0 = (uint32_t)(kStageA + (wn >> 1) * kStageB6 + ((wn & 1) * 2) * kBlock6 + lane * 16);
 
   // ---- prologue: stages 0 and 1 requested, landed and published by a barrier; stage 2 requested ----
@@ -179,6 +293,14 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
     int tm0, tn0;
     tile_of_sid(first + local, mt, nt, tm0, tn0);
     if (tid < BMW) store_row_info<Acc, EPI, RAG>(a, tm0 * BMW, tid, row_info);
+    if constexpr (HI) {
+      if (tid >= BMW && tid < BMW + kHiPlaces) {
+        float fac, rz;
+        hi_place_info<RAG>(a, tm0, tid - BMW, fac, rz);
+        reinterpret_cast<float*>(row_info + kHiInfo)[tid - BMW] = fac;
+        reinterpret_cast<float*>(row_info + kHiInfo)[kHiPlaces + tid - BMW] = rz;
+      }
+    }
     if constexpr (RAG) {
       if (tid < 64) {
         const float f = tid < a.rag.mlast ? rag_leaf(a.rag, tid) : 0.0f;
@@ -211,6 +333,8 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
                : "=&{" H0 "}"(f.h0), "=&{" H1 "}"(f.h1)                                                               \
                : "v"(base), "n"(off), "n"((off) + kPart), "n"((off) + 2 * kPart))
 #define STAMP_RD_AS0(base, off) STAMP_RD3(As0, "v[184:189]", "v[190:195]", "v[184:187]", "v[188:191]", "v[192:195]", base, off)
+#define STAMP_RD_HS(base, off) STAMP_RD3(Hs, "v[172:177]", "v[178:183]", "v[172:175]", "v[176:179]", "v[180:183]", base, off)
+#define STAMP_WAIT_HS(cnt) STAMP_WAIT1(cnt, Hs, "v[172:177]", "v[178:183]")
 #define STAMP_RD_AS1(base, off) STAMP_RD3(As1, "v[196:201]", "v[202:207]", "v[196:199]", "v[200:203]", "v[204:207]", base, off)
   // activation block 0 and the two weight blocks of a step in one statement, parts 0 and 1 of all three first (the
   // first MFMA half's operands), then the parts 2
@@ -249,6 +373,15 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
+    [[maybe_unused]] v16f acch[NIW];  // HI: the 8-bit rows' block
+    [[maybe_unused]] const bool has_hi = HI && hi_tile_has(a.ht, tm);
+    if constexpr (HI) {
+#pragma unroll
+      for (int j = 0; j < NIW; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acch[j][v] = 0.0f;
+    }
+    [[maybe_unused]] Frag Hs;
     Frag As0, As1, B00, B01, B10, B11;  // per tile: no fragment is carried across the epilogue
     // the four MFMAs of activation block mi: both halves against both weight blocks
     auto mfma4 = [&](const Frag& A, const Frag& W0, const Frag& W1, auto mi_tag) __attribute__((always_inline)) {
@@ -319,11 +452,17 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
       __builtin_amdgcn_sched_barrier(0);
       STAMP_RD_AS1(sa + adrA0, 3 * kBlock6);
       rq_tail3 = false;
-      STAMP_WAIT_AS0(3);
+      if constexpr (HI) {
+        STAMP_RD_HS(sa + adrH0, 0);
+        STAMP_WAIT_AS0(6);
+      } else {
+        STAMP_WAIT_AS0(3);
+      }
       if constexpr (pb == 0) mfma4(As0, B00, B01, std::integral_constant<int, 2>{});
       else mfma4(As0, B10, B11, std::integral_constant<int, 2>{});
       __builtin_amdgcn_sched_barrier(0);
       STAMP_WAIT_AS1(0);
+      if constexpr (HI) STAMP_WAIT_HS(0);
       // ---- the next step's stage ----
       asm volatile("" ::: "memory");
       if (landed > 0) {
@@ -362,6 +501,15 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
       __builtin_amdgcn_sched_barrier(0);
       acc[3][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As1.h1), widen((v6i)W1.h1), acc[3][1], 2, 2, 0, 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (HI) {
+        if (has_hi) {
+          acch[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)Hs.h0), widen((v6i)W0.h0), acch[0], 2, 2, 0, 0, 0, 0);
+          acch[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)Hs.h0), widen((v6i)W1.h0), acch[1], 2, 2, 0, 0, 0, 0);
+          acch[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)Hs.h1), widen((v6i)W0.h1), acch[0], 2, 2, 0, 0, 0, 0);
+          acch[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)Hs.h1), widen((v6i)W1.h1), acch[1], 2, 2, 0, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
       rq_tail2 = true;  // loads 3, 4 and 5 follow among the MFMAs of the next step (or after the tile's last step)
     };
     // head of the tile: the barrier that published its first stage lies behind (prologue, or the last step of the
@@ -396,7 +544,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
     asm volatile("" : "+v"(lane_e), "+v"(tid_e));
     // the epilogue's operands from global memory: their latency passes under the lane swaps
     RegEpiOperands<EPI, (IS2D ? 2 * RB : RB), RAG> eo;
-    if constexpr (EPI >= 2) eo.request(a, m0, nw, wm, lane_e);
+    if constexpr (EPI >= 2) eo.template request<!HI>(a, m0, nw, wm, lane_e);
     // row factors of the next tile: loaded now, written to the other buffer after the epilogue (a barrier of
     // the next tile's first step publishes them long before its epilogue reads them)
     float nfac = 0.0f, nrz = 0.0f;
@@ -407,6 +555,13 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
       tile_of_sid(first + pos + wx, mt, nt, tm1, tn1);
       compute_row_info<Acc, EPI, RAG>(a, tm1 * BMW, tid_e, nfac, ndst, nrz);
     }
+    if constexpr (HI) {
+      if (has_next && tid_e >= BMW && tid_e < BMW + kHiPlaces) {
+        int tm1, tn1;
+        tile_of_sid(first + pos + wx, mt, nt, tm1, tn1);
+        hi_place_info<RAG>(a, tm1, tid_e - BMW, nfac, nrz);
+      }
+    }
     const uint8_t* ri = row_info + rbuf * kRowInfo;
     if constexpr (EPI != 2) {
       // The loads just requested complete here, on every path and in a form the compiler's wait-count bookkeeping
@@ -414,6 +569,10 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
       // main loop.  (The fused epilogue places this wait after its lane swaps.)
       asm volatile("" ::: "memory");
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    }
+    if constexpr (HI) {
+      // (their loads have landed: eo.sw, eo.cs)
+      if (has_hi) hi_block_sums<(IS2D ? 2 * RB : RB), YBF16, SYM, RAG>(a, acch, reinterpret_cast<const float*>(ri + kHiInfo), eo, tm, nw, lane_e);
     }
     if constexpr (EPI >= 2) {
       epilogue_reg<EPI, RB, IS2D, YBF16, NI, 0, SYM, RAG, ODD>(a, acc, ri, eo, m0, nw, wm, lane_e);
@@ -423,20 +582,34 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 1 : 2)) void k_gemm6(cons
     }
     rbuf ^= 1;
     if (has_next && tid_e < BMW) write_row_info(row_info + rbuf * kRowInfo, tid_e, nfac, ndst, nrz);
+    if constexpr (HI) {
+      if (has_next && tid_e >= BMW && tid_e < BMW + kHiPlaces) {
+        float* t = reinterpret_cast<float*>(row_info + rbuf * kRowInfo + kHiInfo) + tid_e - BMW;
+        t[0] = nfac;
+        t[kHiPlaces] = nrz;
+      }
+    }
   }
 }
 
+// whether this file's kernels take the 8-bit rows along
+#ifdef STAMP_GEMM6_HI
+constexpr bool kHiTiles = true;
+#else
+constexpr bool kHiTiles = false;
+#endif
+
 int gemm6_workgroups(int tiles) { return tiles < stamp_device_cus() ? tiles : stamp_device_cus(); }
 
-template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM, bool RAG = false, bool ODD = false>
+template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM, bool RAG = false, bool ODD = false, bool HI = kHiTiles>
 hipError_t launch_k(const GemmArgs& a, hipStream_t st) {
   constexpr int WAVES = STAMP_GEMM6_WAVES;
-  constexpr size_t lds = (size_t)kNumStage6 * Tile6<WAVES>::kStage + 2 * (kRowInfoBytes + (RAG ? 256 : 0));
+  constexpr size_t lds = (size_t)kNumStage6 * Tile6<WAVES, HI>::kStage + 2 * (kRowInfoBytes + (RAG ? 256 : 0) + (HI ? kHiInfoBytes : 0));
   static size_t lds_done[kStampMaxDevices] = {};
-  hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD, WAVES>), lds, lds_done);
+  hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD, WAVES, HI>), lds, lds_done);
   if (e != hipSuccess) return e;
   const int mt = (a.M + Tile6<WAVES>::BMW - 1) / Tile6<WAVES>::BMW, nt = a.Npad / BN6;
-  hipLaunchKernelGGL((k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD, WAVES>), dim3(gemm6_workgroups(mt * nt)), dim3(64 * WAVES), lds, st, a);
+  hipLaunchKernelGGL((k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD, WAVES, HI>), dim3(gemm6_workgroups(mt * nt)), dim3(64 * WAVES), lds, st, a);
   return hipGetLastError();
 }
 
@@ -469,8 +642,10 @@ hipError_t launch_rag(const GemmArgs& a, hipStream_t st) {
 
 // the GEMM of one mode on this tile size
 hipError_t gemm6_run(const GemmArgs& a, int mode, hipStream_t st) {
+#ifndef STAMP_GEMM6_HI
   if (mode == 1) return launch<1, 0, false>(a, st);
   if (mode == 3) return launch<3, 0, false>(a, st);
+#endif
 #if STAMP_GEMM6_WAVES == 8
   if (mode == 0) return launch<0, 0, false>(a, st);
 #endif

@@ -78,6 +78,8 @@ struct GemmArgs {
   int own_top;           // 4-bit rows, fused mode: coefficient 0 of the blocks from g.khi on is a 4-bit row of A (see
                          // compute_row_info); P then holds g.khi rows per sequence
   StampGeom g;
+  const uint8_t* H;      // 8-bit rows in the tiles' places (ht.on), 3 KB per 128-row tile and K step
+  StampHiTiles ht;
   StampRag rag;          // RAG kernels: rows in the block order of StampRag (g.k = blocks, g.khi = 8-bit slots), scales in
                          // STaMP order, P row b * g.khi + slot
 };
@@ -641,5 +643,6 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, typename Acc::V (&ac
 stamp_gemm::GemmArgs stamp_gemm_args(const stamp_plan* p, const float* scales, void* out);
 // the FP6 GEMM on 128 x 256 tiles
 hipError_t stamp_gemm6_half(const stamp_gemm::GemmArgs& a, int mode, hipStream_t st);
+hipError_t stamp_gemm6_half_hi(const stamp_gemm::GemmArgs& a, hipStream_t st);  // a.ht.on: the 8-bit rows along
 
 #endif  // STAMP_GEMM_COMMON_H_

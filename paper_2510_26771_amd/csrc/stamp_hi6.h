@@ -33,20 +33,31 @@ __device__ __forceinline__ void store_frag(uint8_t* dst, int f, const uint64_t (
   }
 }
 
-// one thread = 32 channels of a row
+// one thread = 32 channels of a row, or of a place in the tiles of the 4-bit rows
 __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
   if (i >= hp.threads) return;
+  const StampHiOut& o = hp.out;
   const int nf = hp.KT * 4, m = i / nf, frag = i - m * nf, kt = frag >> 2, f = frag & 3;
-  const bool there = m < hp.M && frag * 32 < hp.d;  // d is a multiple of 32
+  int row;
+  uint8_t* dst;
+  if (o.ht.on) {
+    const int tile = m / kHiPlaces, place = m - tile * kHiPlaces;
+    int b, up;
+    const int slot = stamp_hi_slot_of_place(o.ht, hp.nseq, tile, place, &b, &up);
+    if (slot < 0) return;  // (a place without a row may hold anything)
+    row = b * hp.seq_rows + slot;
+    dst = o.p + ((size_t)tile * hp.KT + kt) * kBlock6 + (f & 1) * 512 + place * 16;
+  } else {
+    const int gr = 32 * o.np, grp = m / gr, r = m - grp * gr;
+    row = m < hp.M ? m + (m / o.seq) * (hp.seq_rows - o.seq) : -1;
+    dst = o.p + ((size_t)grp * hp.KT + kt) * (2 * o.np * kBlock6) + (r >> 5) * (2 * kBlock6) + (f & 1) * 512 + (r & 31) * 16;
+  }
   u4 w[2] = {};
-  if (there) {
-    const int row = m + (m / hp.seq_used) * (hp.seq_rows - hp.seq_used);
+  if (row >= 0 && frag * 32 < hp.d) {  // d is a multiple of 32
     const u4* src = reinterpret_cast<const u4*>(hp.q_hi + (size_t)row * hp.d + frag * 32);
     w[0] = src[0];
     w[1] = src[1];
   }
-  const int gr = 32 * hp.np, grp = m / gr, r = m - grp * gr;
-  uint8_t* dst = hp.a6 + ((size_t)grp * hp.KT + kt) * (2 * hp.np * kBlock6) + (r >> 5) * (2 * kBlock6) + (f & 1) * 512 + (r & 31) * 16;
   // h, then l: 32 fields at a time, so that the kernels that call this for a few of their blocks keep their occupancy (one
   // pass with both: 70 registers, seven waves per SIMD; 16384 x 1024 4-bit rows beside 2048 8-bit ones 10.9 us, now 10.1)
 #pragma unroll
@@ -60,7 +71,7 @@ __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
       part[q] |= field << sh;
       if (sh > 58) part[q + 1] |= field >> (64 - sh);
     }
-    store_frag(dst + half * kBlock6, f, part);
+    store_frag(dst + (half ? (o.ht.on ? kHiPlaces * 16 : kBlock6) : 0), f, part);
   }
 }
 

@@ -261,8 +261,6 @@ int hi6_np(int M) { return M <= 32 ? 1 : 2; }
 int hi6_ng(const stamp_plan* p, int own) { return !p->geom.ident && !own && p->geom.L > 0 && p->geom.k > 64 ? 2 : 1; }
 }  // namespace
 
-int stamp_hi6_np(const stamp_plan* p, int own) { return hi6_np(hi6_rows(p, own)); }
-
 size_t stamp_hi6_bytes(const stamp_plan* p, int own) {
   const int M = hi6_rows(p, own), gr = 32 * hi6_np(M);
   return (size_t)((M + gr - 1) / gr) * (p->Kpad / 128) * (2 * hi6_np(M) * kBlock6);
@@ -288,19 +286,51 @@ bool stamp_hi6_fits(const stamp_plan* p, int own) {
   return M <= 128 || ((double)M * (g.N + 256) <= 6.5e6 && (double)M * (g.N + 768) <= 8.0e5 + 8.0e9 / g.d);
 }
 
-StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own) {
+// Plans whose 4-bit rows' GEMM takes the 8-bit rows along: 128-row tiles (their kernel has the registers), whole blocks per tile and
+// places for the rows above them (1-D, not below blocks of 16 tokens with many top levels), sums that fp32 holds exactly.
+StampHiTiles stamp_hi_tiles(const stamp_plan* p, int own) {
+  StampHiTiles t = {};
+  const bool rag = p->rag.on;
+  const StampGeom& g = rag ? p->bgeom : p->geom;
+  if (p->engine != STAMP_GEMM_FP6 || p->gen.group != 0 || p->dbg[STAMP_CHOICE_HI_ROWS] != 0) return t;
+  if (!rag && (p->gen.kind != kGenNone || g.ident || !p->fused_ok || p->unfused)) return t;
+  const int rl = g.is2d ? 2 * g.r : g.r, khi = own || rag ? g.khi : g.k, L = rag ? 0 : g.L;
+  if (rl < 3 || rl > 6 || khi < 1 || (g.is2d && L > 0) || g.d > 18720) return t;  // 128 * 7 * 18720 < 2^24
+  const int lognb = 7 - rl, above = L > lognb ? L - lognb : 0;
+  if ((1 << lognb) + above > kHiPlaces) return t;
+  if (rag && p->rag.o && khi - 1 >= p->rag.nb) return t;  // no block left whose place the token left out could have
+  const int M = rag ? (g.B * p->rag.nb) << p->rag.r : g.B * g.s;
+  if (!stamp_gemm6_half_tiles(M, p->Npad)) return t;
+  t.on = 1;
+  t.lognb = lognb;
+  t.k = rag ? p->rag.nb : g.k;
+  t.khi = khi;
+  t.L = L;
+  t.o = rag ? p->rag.o : 0;
+  return t;
+}
+size_t stamp_hi_tiles_bytes(const stamp_plan* p) {
+  const size_t M = p->rag.on ? (size_t)(p->geom.B * p->rag.nb) << p->rag.r : (size_t)p->geom.B * p->geom.s;
+  return (M + 127) / 128 * (p->Kpad / 128) * kBlock6 + 1024;  // (the last stage load of a tile reads 1 KB on)
+}
+
+StampHiOut stamp_hi6_out(const stamp_plan* p, uint8_t* a6, int own, const StampHiTiles& ht) {
+  return StampHiOut{a6, hi6_np(hi6_rows(p, own)), own ? p->geom.khi : p->geom.k, ht};
+}
+
+StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own, const StampHiTiles& ht) {
   const StampGeom& g = p->geom;
   StampHi6Pack hp = {};
   hp.q_hi = q_hi;
-  hp.a6 = a6;
+  hp.out = stamp_hi6_out(p, a6, own, ht);
   hp.M = hi6_rows(p, own);
-  hp.np = hi6_np(hp.M);
   hp.seq_rows = g.k;
-  hp.seq_used = own ? g.khi : g.k;
   hp.d = g.d;
   hp.KT = p->Kpad / 128;
-  const int gr = 32 * hp.np;
-  hp.threads = (hp.M + gr - 1) / gr * gr * hp.KT * 4;
+  hp.nseq = g.B;
+  const int gr = 32 * hp.out.np;  // (the rows' own kernel reads whole groups)
+  const int rows = ht.on ? ((g.B * ht.k + (1 << ht.lognb) - 1) >> ht.lognb) * kHiPlaces : (hp.M + gr - 1) / gr * gr;
+  hp.threads = rows * hp.KT * 4;
   return hp;
 }
 

@@ -54,6 +54,61 @@ struct StampGen {
 struct StampRag {
   int32_t on, o, n, nb, mlast, r;
 };
+// The 8-bit rows in the tiles of the 4-bit rows' GEMM (128 rows of 2^lognb blocks): a tile's outputs need the sums of its own
+// blocks, hence their 8-bit rows and, with top levels, the rows above them in the tree.  Every tile has 16 places for such rows: its
+// blocks' rows where the in-place network of the top levels leaves them, then one place per level above the tile's
+// sub-tree, finest first.  A row that several tiles need is stored for each.
+struct StampHiTiles {
+  int32_t on, lognb;
+  int32_t k, khi;    // blocks per sequence, 8-bit rows per sequence
+  int32_t L, o;      // top levels; 1: the token left out is 8-bit row 0 (its place: that of the first block with a 4-bit sum)
+};
+constexpr int kHiPlaces = 16;
+// 8-bit row `slot` of sequence b: its place in the tiles tile .. tile + ntiles - 1
+STAMP_HD void stamp_hi_places(const StampHiTiles& t, int b, int slot, int* tile, int* ntiles, int* place) {
+  const int nb = 1 << t.lognb;
+  *ntiles = 1;
+  if (t.L == 0) {
+    const int j = t.o ? (slot == 0 ? t.khi - 1 : slot - 1) : slot, g = b * t.k + j;
+    *tile = g >> t.lognb;
+    *place = g & (nb - 1);
+    return;
+  }
+  const bool apx = slot < (t.k >> t.L);
+  const int m = apx ? 0 : 31 - __builtin_clz((unsigned)slot);
+  const int lev = apx ? t.L : 31 - __builtin_clz((unsigned)t.k) - m, i = apx ? slot : slot - (1 << m);
+  const int g = b * t.k + (i << lev);  // the first of the row's 2^lev blocks
+  *tile = g >> t.lognb;
+  if (lev <= t.lognb) {
+    *place = (g & (nb - 1)) + (apx ? 0 : 1 << (lev - 1));
+  } else {
+    *ntiles = 1 << (lev - t.lognb);
+    *place = apx ? 0 : nb + lev - t.lognb - 1;
+  }
+}
+
+// The other way round: the row (of sequence *b, its level within the top part: *up) at a tile's place, -1: none
+STAMP_HD int stamp_hi_slot_of_place(const StampHiTiles& t, int nseq, int tile, int p, int* b, int* up) {
+  const int nb = 1 << t.lognb, g = (tile << t.lognb) + (p < nb ? p : 0);
+  *b = g / t.k;
+  *up = 0;
+  const int j = g - *b * t.k;
+  if (*b >= nseq) return -1;
+  if (t.L == 0) {
+    if (p >= nb || j >= t.khi) return -1;
+    return t.o ? (j == t.khi - 1 ? 0 : j + 1) : j;
+  }
+  const int lev = p < nb ? (j == 0 ? 32 : __builtin_ctz((unsigned)j)) + 1 : t.lognb + 1 + p - nb;
+  if (p >= nb && lev > t.L) return -1;
+  // place 0 of a tile below the tree's top: its approximation
+  if (p < nb && (lev > t.L || (p == 0 && t.lognb < t.L))) {
+    *up = t.L;
+    return j >> t.L;
+  }
+  *up = lev;
+  return (t.k >> lev) + (j >> lev);
+}
+
 // STaMP slot of in-block position e of block j, -1 where a short block has no such coefficient.  The details of level l
 // sit from slot o + ceil(n / 2^l) on; one exists where both of its halves do.
 STAMP_HD int stamp_rag_slot(const StampRag& q, int j, int e) {
@@ -234,9 +289,17 @@ bool stamp_top_in_bottom(const stamp_plan* p);
 // up to two blocks per CU: with more the CUs are full either way)
 bool stamp_bottom_quads(const stamp_plan* p);
 // dir: the codes leave as FP6 operands (4-bit rows, 8-bit rows) instead of in q_hi / q_lo, which are not written
-struct StampDirect {
-  uint8_t *a6, *h6;
+// The FP6 operand of the 8-bit rows: for the kernel of their own (stamp_hi6.h; np, rows m), or in the places of the 4-bit rows'
+// tiles (ht.on).
+struct StampHiOut {
+  uint8_t* p;    // nullptr: none
   int32_t np;
+  int32_t seq;   // 8-bit rows per sequence: row m is row m % seq of sequence m / seq
+  StampHiTiles ht;
+};
+struct StampDirect {
+  uint8_t* a6;
+  StampHiOut hi;
   int32_t lo_packed;  // the 4-bit rows do leave in q_lo, and the top levels' launch converts them
 };
 hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo,
@@ -267,8 +330,8 @@ hipError_t stamp_launch_weight_quant6(const stamp_plan* p, const float* W, const
 // hi: 8-bit rows to convert in the same launch (nullptr: none); q_lo may be nullptr then
 struct StampHi6Pack {
   const int8_t* q_hi;
-  uint8_t* a6;
-  int32_t M, np, seq_rows, seq_used, d, KT, threads;  // rows, 32-row blocks per group, rows a sequence has / uses in q_hi
+  StampHiOut out;
+  int32_t M, seq_rows, nseq, d, KT, threads;  // rows, rows a sequence has in q_hi (it uses out.seq)
 };
 hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st, const StampHi6Pack* hi = nullptr);
 // the 8-bit rows' GEMM on the FP6 pipeline (few rows), own: only the first khi rows of every sequence.  mode 0: block sums
@@ -276,8 +339,12 @@ hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_
 // [B*s][N] in STaMP order, 3: blocked form: block sums times norm -> out, the token left out + bias -> Y
 bool stamp_hi6_fits(const stamp_plan* p, int own);
 size_t stamp_hi6_bytes(const stamp_plan* p, int own);
-int stamp_hi6_np(const stamp_plan* p, int own);
-StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own);
+// the operand at `a6`; ht: in the tiles' places instead
+StampHiOut stamp_hi6_out(const stamp_plan* p, uint8_t* a6, int own, const StampHiTiles& ht);
+StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own, const StampHiTiles& ht);
+// whether the 4-bit rows' GEMM takes the 8-bit rows along (ht.on), and the bytes of their operand
+StampHiTiles stamp_hi_tiles(const stamp_plan* p, int own);
+size_t stamp_hi_tiles_bytes(const stamp_plan* p);
 hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float* scales, int mode, void* out, int ld_out, int own,
                             void* Y, float norm, hipStream_t st);
 // blocked form (p->rag.on): the same conversion from rows in STaMP order to block order; packed nibbles in block order
@@ -285,7 +352,9 @@ hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float*
 size_t stamp_rag_a6_bytes(const stamp_plan* p);
 hipError_t stamp_launch_repack6_rag(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st, const StampHi6Pack* hi);
 hipError_t stamp_launch_gather_lo_rag(const stamp_plan* p, const uint8_t* q_lo, uint8_t* q_blk, hipStream_t st);
-hipError_t stamp_launch_gemm_lo6_rag(const stamp_plan* p, const uint8_t* a6, const float* scales, void* Y, const float* P, hipStream_t st);
+// hi (ht.on): the 8-bit rows' operand in the tiles' places, P is not read then
+hipError_t stamp_launch_gemm_lo6_rag(const stamp_plan* p, const uint8_t* a6, const float* scales, void* Y, const float* P, hipStream_t st,
+                                     const StampHiOut* hi = nullptr);
 hipError_t stamp_launch_gemm_lo_rag(const stamp_plan* p, const uint8_t* q_blk, const float* scales, void* Y, const float* P, hipStream_t st);
 // 8-bit rows' partial rows [nparts][B*khi][N] -> block sums P [B*khi][Npad] (times the blocks' norm); with the first
 // token left out, its row (+ bias) -> Y
@@ -293,7 +362,7 @@ hipError_t stamp_launch_rag_top(const stamp_plan* p, const float* ythi, int npar
 // own_top (mode 2, plans without top levels): the blocks from khi on take their sum from their own coefficient 0,
 // a 4-bit row of a6 like any other (the quantizer writes it there as well), and P holds khi rows per sequence
 hipError_t stamp_launch_gemm_lo6(const stamp_plan* p, const uint8_t* a6, const float* scales, int mode, void* out,
-                                 const float* P, hipStream_t st, int own_top = 0);
+                                 const float* P, hipStream_t st, int own_top = 0, const StampHiOut* hi = nullptr);
 // whether the FP6 GEMM over M rows takes 128 x 256 tiles
 bool stamp_gemm6_half_tiles(int M, int Npad);
 // identity plans: 8-bit rows' dequantized partial rows [nparts][B*k][N] (+ bias) -> Y rows of tokens 0..k-1
@@ -315,7 +384,7 @@ hipError_t stamp_gen_inverse(const stamp_plan* p, float* const (&buf)[3], int nc
 // Bottom kernels that leave FP6 operands (stamp_lanes1d.hip): blocks of 2^rlog tokens (3, 4), or parts of longer ones with their
 // sums left in abot.
 bool stamp_lanes1d_fits(const stamp_plan* p, int rlog);
-hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, uint8_t* a6, float* scales, float* abot, uint8_t* h6, int np,
+hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, uint8_t* a6, float* scales, float* abot, const StampHiOut& hi,
                                 hipStream_t st);
 // DCT of a power-of-two length with the points in registers (stamp_dct.hip): plans it takes, and src -> T (inv = 0), src -> Y (+ bias)
 bool stamp_dct_in_registers(int s, int B, int ld);

@@ -47,15 +47,18 @@ __device__ __forceinline__ void store_hi24(const Hi6Out& o, int m, int KT, f16v 
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int i = 0; i < 16; ++i) hv[h][i] = floorf(__builtin_fmaf(h ? od[i] : ev[i], 0.0625f, 0.5f));
-  const int gr = 32 * o.np, grp = m / gr, r = m - grp * gr, f = (c >> 5) & 3;
-  uint8_t* dst = o.p + ((size_t)grp * KT + (c >> 7)) * (2 * o.np * kBlock6) + (r >> 5) * (2 * kBlock6) + (f & 1) * 512 + (r & 31) * 16;
-  store24(dst, to_e2m3(hv[0], hv[1]), f >> 1);
+  const u6v h = to_e2m3(hv[0], hv[1]);
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     ev[i] = __builtin_fmaf(-16.0f, hv[0][i], ev[i]);
     od[i] = __builtin_fmaf(-16.0f, hv[1][i], od[i]);
   }
-  store24(dst + kBlock6, to_e2m3(ev, od), f >> 1);
+  const u6v l = to_e2m3(ev, od);
+  const uint32_t off = (uint32_t)(c >> 7) * hi_step_bytes(o) + ((c >> 5) & 1) * 512;
+  hi_rows(o, m, KT, [&](uint8_t* dst, int lo) {
+    store24(dst + off, h, (c >> 6) & 1);
+    store24(dst + off + lo, l, (c >> 6) & 1);
+  });
 }
 
 // the sum of this lane's partner at lane distance 2^(l - 2)
@@ -397,7 +400,7 @@ bool stamp_lanes1d_fits(const stamp_plan* p, int rlog) {
   return g.x_bf16 && !p->rag.on && g.d <= 12288 && (int64_t)g.B * g.s > 4 * stamp_device_cus();
 }
 
-hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, uint8_t* a6, float* scales, float* abot, uint8_t* h6, int np,
+hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, uint8_t* a6, float* scales, float* abot, const StampHiOut& hi,
                                 hipStream_t st) {
   const StampGeom& g = p->geom;
   LaneArgs a = {};
@@ -412,7 +415,7 @@ hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, ui
   a.khi = g.khi;
   a.KT = p->Kpad >> 7;
   a.zeros_off = (size_t)g.B * g.s;
-  a.hi6 = Hi6Out{h6, np};
+  a.hi6 = hi;
   a.rag = p->rag;
   if (p->rag.on) {
     const int blocks = p->rag.nb + p->rag.o;
