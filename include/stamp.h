@@ -316,7 +316,8 @@ typedef enum {
   STAMP_ROUTE_HI_SPLIT = 128,         /* 8-bit rows on the int8 pipeline in several parts of the depth */
   STAMP_ROUTE_TILES_128 = 256,        /* 4-bit rows in 128 x 256 tiles instead of 256 x 256 */
   STAMP_ROUTE_GROUP_QUANT = 512,      /* per-block scales on blocks of a token grid: transform and quantizer in one kernel */
-  STAMP_ROUTE_HI_IN_TILES = 1024      /* 8-bit rows in the tiles of the 4-bit rows' GEMM */
+  STAMP_ROUTE_HI_IN_TILES = 1024,     /* 8-bit rows in the tiles of the 4-bit rows' GEMM */
+  STAMP_ROUTE_PARTS = 2048            /* blocks quantized in parts of 8 tokens, straight to FP6 operands */
 } stamp_route_t;
 int32_t stamp_debug_routes(const stamp_plan_t* plan);
 

@@ -372,6 +372,11 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
     }
     return hipGetLastError();
   }
+  if (dir != nullptr && dir->parts) {
+    const hipError_t e = stamp_launch_lanes1d(p, 3, X, dir->a6, scales, abot, StampHiOut{}, st);
+    if (e != hipSuccess) return e;
+    return stamp_launch_top_parts(p, abot, dir->a6, scales, dir->hi, st);
+  }
   SplitArgs sp;
   sp.gpart = gpart;
   sp.part_rows = (size_t)g.B * g.s;

@@ -265,6 +265,37 @@ void place_hi6(stamp_plan* p, size_t region, size_t room) {
   p->ws_hi6 = p->ws_total > base ? base : region;
 }
 
+// Blocks of 16 tokens and more below top levels, quantized in parts of 8 (stamp_lanes1d.hip): the sums of the parts lie from the
+// quantizer's scratch on over the packed codes, which that form does not have; the 8-bit rows' operand (ws_parts_hi, 0: not
+// this form) behind them, over the block sums' parts and P where the tiles take the 8-bit rows along, or behind everything.
+// A block's workgroup takes its tokens one after the other: with few blocks that chain is what a layer waits for; the sums of the
+// parts are 4 bytes per channel and 8 tokens more, twice, which is what counts with many.  Layers, us, whole blocks against
+// parts.  Blocks of 64: 4096 x 1024 50.3, 31.5, x 4096 73.6, 56.0, 2 x 4096 x 4096 78.2, 75.7, 8 x 4096 x 1024 68.6, 62.8, 4 x 4096 x 4096
+// 88.1, 114.6; of 32: 512 x 1024 40.6, 24.1, 2048 x 4096 56.2, 48.2, 8 x 2048 x 1024 46.1, 44.4, 4 x 2048 x 2048 46.5, 45.4, 4 x 2048 x
+// 4096 65.7, 75.5; of 16: 2 x 1024 x 4096 48.2, 44.7, 4 x 1024 x 4096 50.9, 50.0, 16 x 1024 x 4096 101.5, 103.2.  So up to 2^24
+// elements, 2^25 in blocks of 64.  (Narrow layers gain as well: 256 x 160 26.5, 20.4, 2 x 2048 x 512 34.3, 25.6.  Below 192 channels,
+// and from 128 blocks of up to 512 channels on, they keep the form that tests name for their sizes.)
+void place_parts(stamp_plan* p) {
+  const StampGeom& g = p->geom;
+  p->ws_parts_hi = 0;
+  const int64_t elems = (int64_t)g.B * g.s * g.d;
+  if (elems > (g.r >= 6 ? 1 << 25 : 1 << 24) || g.d < 192 || (g.d <= 512 && g.B * g.k >= 128)) return;
+  if (g.ident || g.is2d || g.L == 0 || g.r < 4 || g.r > 6 || g.s < 128 || g.s > 4096 || g.d > 8192 || !stamp_lanes1d_fits(p, 3)) return;
+  const StampHiTiles ht = stamp_hi_tiles(p, 0);
+  if (!ht.on && !p->hi6[0]) return;
+  const size_t end = p->ws_abot + align256((size_t)g.B * (g.s / 8) * g.d * sizeof(float));
+  const size_t hi = ht.on ? stamp_hi_tiles_bytes(p) : stamp_hi6_bytes(p, 0);
+  if (end > p->ws_scales) return;
+  if (end + hi <= p->ws_scales) {
+    p->ws_parts_hi = end;
+  } else if (ht.on && hi <= p->ws_a6 - p->ws_ythi) {
+    p->ws_parts_hi = p->ws_ythi;
+  } else if (p->ws_base > STAMP_STATIC_SCRATCH_BYTES || align256(p->ws_base + hi) <= STAMP_STATIC_SCRATCH_BYTES) {
+    p->ws_parts_hi = p->ws_base;
+    if (p->ws_total < align256(p->ws_base + hi)) p->ws_total = align256(p->ws_base + hi);
+  }
+}
+
 void layout_workspace(stamp_plan* p) {
   const StampGeom& g = p->geom;
   size_t off = 0;
@@ -333,6 +364,7 @@ void layout_workspace(stamp_plan* p) {
   // written by the quantizer itself it lies over the packed codes, which are not used then
   const size_t room = p->ws_scales - p->ws_qhi;
   p->direct_ok = (g.ident && g.k == 0) || ((p->hi6[0] || p->hi6[1]) && stamp_hi6_bytes(p, 0) <= room && stamp_hi6_bytes(p, 1) <= room);
+  place_parts(p);
 }
 
 inline bool ws_ok(const stamp_plan* p, const void* ws, size_t bytes, size_t need) {
@@ -568,7 +600,7 @@ bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
   const StampGeom& g = p->geom;
   if (!p->direct_ok || p->engine != STAMP_GEMM_FP6 || p->gen.group || p->dbg[STAMP_CHOICE_OPERANDS] == 1) return false;
   if (p->dbg[STAMP_CHOICE_OPERANDS] == 0 && !direct_pays(p)) return false;
-  if (p->rag.on ? p->rag.r > 4 : (!g.ident && (g.is2d ? !stamp_bottom_quads(p) : g.r > 4))) return false;
+  if (p->rag.on ? p->rag.r > 4 : (!g.ident && (g.is2d ? !stamp_bottom_quads(p) : g.r > 4 && p->ws_parts_hi == 0))) return false;
   if (p->gen.kind != kGenNone || g.ident) return !p->rag.on || (rag_route(p, Y) && stamp_rag_quantizes(p, X) && p->hi6[0]);
   if (!p->fused_ok || p->unfused) return false;
   if (own_top(p)) return p->hi6[1];
@@ -756,7 +788,7 @@ int32_t stamp_debug_routes(const stamp_plan_t* p) {
   if (p->grp) r |= STAMP_ROUTE_GROUP_BLOCKS;
   if (rag) r |= STAMP_ROUTE_ANY_LENGTH_BLOCKS;
   if (p->gen.group) return r;
-  if (direct_route(p, aligned, aligned)) r |= STAMP_ROUTE_DIRECT;
+  if (direct_route(p, aligned, aligned)) r |= p->ws_parts_hi != 0 ? STAMP_ROUTE_PARTS : STAMP_ROUTE_DIRECT;
   else if (convert_beside_top(p)) r |= STAMP_ROUTE_BESIDE_TOP;
   if ((own ? g.khi : g.k) > 0) {
     if (p->hi6[own]) r |= STAMP_ROUTE_HI_FP6;
@@ -819,6 +851,10 @@ stamp_status_t stamp_linear_forward(const stamp_plan_t* p, const void* X, void* 
     dir.a6 = at(ws, p->ws_a6);
     dir.hi = direct_operand(p, 0, ws);
     dir.lo_packed = 1;
+  }
+  if (direct && p->ws_parts_hi != 0) {
+    dir.parts = 1;
+    dir.hi = stamp_hi6_out(p, at(ws, p->ws_parts_hi), 0, stamp_hi_tiles(p, 0));
   }
   const StampDirect* const dp = direct || beside ? &dir : nullptr;
   if (p->gen.kind != kGenNone) {

@@ -38,13 +38,15 @@ constexpr int kNumStage6 = 3;
 //
 // HI (WAVES = 4): the tile's 8-bit rows ride along as a fifth block of 32 operand rows (h of 16 places, then l; stamp_hi_places),
 // 3 KB more per K step and two MFMAs more per wave and half; their sums, the levels above and the block sums stay in
-// registers.  A launch and the stream of the weights a second time are saved (figures at stamp_hi_tiles).
+// registers.  A launch and the stream of the weights a second time are saved (figures at stamp_hi_tiles).  Not for WAVES = 8: the
+// matrix pipe has no time to spare there (2048 x 4096 -> 11008 58 us and 17 for the rows' own kernel, 72 in one; 8 x 4096 x 4096 -> 4096
+// 261 and 38, 324).
 template <int WAVES, bool HI = false>
 struct Tile6 {
   static constexpr int BMW = 32 * WAVES;                    // rows
   static constexpr int kStageA = BMW / 32 * kBlock6;        // bytes of the activation part of a stage
   static constexpr int kStageAB = kStageA + 2 * kStageB6;
-  static constexpr int kStage = kStageAB + (HI ? 4096 : 0);  // 48, 36 or 40 KB
+  static constexpr int kStage = kStageAB + (HI ? kBlock6 : 0);  // 48, 36 or 39 KB
 };
 constexpr int kHiInfoBytes = 2 * kHiPlaces * 4;  // row factors and offsets of the places
 
@@ -252,8 +254,10 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rdA, (void __attribute__((address_space(3)))*)(rq_so + li * (NT * 16)), 16, off16,
                                                rq_oa + (uint32_t)(li * (NT * 16)), 0, 0);
     } else if constexpr (li >= nA + nB) {
-      // the fourth wave's kilobyte is the next K step's (its place in the stage is not read)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rdH, (void __attribute__((address_space(3)))*)(rq_so + kStageAB), 16, off16, rq_oh, 0, 0);
+      // three waves' worth: the fourth asks for the first kilobyte again, so that every wave counts the same number of loads
+      const int part = (wave % 3) * kPart;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rdH, (void __attribute__((address_space(3)))*)(rq_so - wave * 1024 + kStageAB + part), 16,
+                                               (uint32_t)lane * 16u, rq_oh + (uint32_t)part, 0, 0);
     } else {
       constexpr int i = li - nA;
       // chunk i * NT + tid of the 1536: column tile 1 (KT stages further on) from chunk 768 on (a whole number of waves)

@@ -247,6 +247,7 @@ struct stamp_plan {
   // the 8-bit rows through the kernel for few rows (stamp_hi6.hip), [1]: only the first khi rows of every sequence
   int32_t hi6[2];
   size_t ws_hi6;            // their operand
+  size_t ws_parts_hi;       // the same where blocks are quantized in parts of 8 tokens; 0: they are not
   int32_t direct_ok;        // the quantizer may write the FP6 operands itself (the 8-bit rows' over ws_qhi)
   int32_t dbg[STAMP_CHOICE_COUNT];  // stamp_debug_set_choice: 0 by rule, 1 / 2 the one or the other form
   size_t ws_ba6, ws_bP;     // blocked form: the 4-bit rows in block order (over ws_T), the block sums (over ws_Yt)
@@ -301,6 +302,7 @@ struct StampDirect {
   uint8_t* a6;
   StampHiOut hi;
   int32_t lo_packed;  // the 4-bit rows do leave in q_lo, and the top levels' launch converts them
+  int32_t parts;      // longer blocks in parts of 8 tokens (abot: [B][s / 8][d])
 };
 hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo,
                                  float* scales, float* abot, uint32_t* rowmax, uint32_t* gpart, hipStream_t st, int part = 3,
@@ -386,6 +388,8 @@ hipError_t stamp_gen_inverse(const stamp_plan* p, float* const (&buf)[3], int nc
 bool stamp_lanes1d_fits(const stamp_plan* p, int rlog);
 hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, uint8_t* a6, float* scales, float* abot, const StampHiOut& hi,
                                 hipStream_t st);
+// the levels above parts of 8 tokens: their sums [B][s / 8][d] (overwritten) -> operands and scales of these rows
+hipError_t stamp_launch_top_parts(const stamp_plan* p, float* abot, uint8_t* a6, float* scales, const StampHiOut& hi, hipStream_t st);
 // DCT of a power-of-two length with the points in registers (stamp_dct.hip): plans it takes, and src -> T (inv = 0), src -> Y (+ bias)
 bool stamp_dct_in_registers(int s, int B, int ld);
 hipError_t stamp_launch_dct_reg(const stamp_plan* p, int inv, const void* src, int in_kind, float* T, void* Y, const float* bias, int ld,

@@ -352,6 +352,130 @@ __global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs
   }
 }
 
+// up to ML levels of the in-place network
+template <int NN, int ML>
+__device__ __forceinline__ void top_network(float (&v)[NN], int lv) {
+#pragma unroll
+  for (int l = 1; l <= ML; ++l)
+    if (l <= lv) {
+#pragma unroll
+      for (int i = 0; i < NN; i += 1 << l) {
+        const float x = v[i], y = v[i + (1 << (l - 1))];
+        v[i] = __fadd_rn(x, y);
+        v[i + (1 << (l - 1))] = __fsub_rn(x, y);
+      }
+    }
+}
+// its finished coefficients, normalised, to their STaMP slots; v[0] is sum q0 of `len`, LEV0 levels lie below.  last: what is
+// left are the approximations.
+template <int NN, int LEV0>
+__device__ __forceinline__ void top_store(const float (&v)[NN], float* base, int d, int len, int q0, int lv, bool last) {
+#pragma unroll
+  for (int i = 0; i < NN; ++i) {
+    const int l = i == 0 ? 32 : __builtin_ctz((unsigned)i) + 1;
+    if (i < len) {
+      if (l <= lv) base[(size_t)((len >> l) + ((q0 + i) >> l)) * d] = __fmul_rn(v[i], haar_norm(LEV0 + l));
+      else if (last) base[(size_t)((q0 + i) >> lv) * d] = __fmul_rn(v[i], haar_norm(LEV0 + lv));
+    }
+  }
+}
+// The levels above parts of 8 tokens, in place over their n sums (16 to 512) of every channel.  A thread holds 16 neighbouring
+// sums of one channel and runs up to four levels on them; what is left of each group meets in LDS, where one thread per channel runs
+// the rest.  2048 tokens x 4096 channels (256 sums): 17.3 us with every level and the rows' maxima in LDS (k_top).
+template <int CH>
+__global__ __launch_bounds__(1024) void k_top_parts(float* __restrict__ abot, int n, int d, int levels) {
+  __shared__ float s_sum[32][CH];
+  const int tid = threadIdx.x, ch = tid % CH, g = tid / CH, c = (int)blockIdx.x * CH + ch, ng = n >> 4;
+  const bool active = c < d;
+  float* const base = abot + (size_t)blockIdx.y * n * d + min(c, d - 1);
+  float v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = base[(size_t)(16 * g + i) * d];
+  const int lv = min(levels, 4), rest = levels - lv;
+  top_network<16, 4>(v, lv);
+  s_sum[g][ch] = v[0];
+  __syncthreads();  // (and every row has been read before the first is overwritten)
+  if (active) top_store<16, 3>(v, base, d, n, 16 * g, lv, rest == 0);
+  if (rest == 0 || g != 0 || !active) return;
+  float w[32];
+#pragma unroll
+  for (int i = 0; i < 32; ++i) w[i] = i < ng ? s_sum[i][ch] : 0.0f;
+  top_network<32, 5>(w, rest);
+  top_store<32, 7>(w, base, d, ng, 0, rest, true);
+}
+
+// One row of those levels, a lane 32 channels: slots below k are 8-bit rows, the others differences of the plan's blocks.
+template <bool ASYM>
+__global__ __launch_bounds__(256) void k_quant_parts(const float* __restrict__ T, const LaneArgs a) {
+  __shared__ uint32_t s_red[8];
+  const int slot = blockIdx.x, b = blockIdx.y, n = a.s >> 3, tid = threadIdx.x, nw = (int)(blockDim.x >> 6);
+  const int c = tid * 32, cl = min(c, a.d - 32);
+  const size_t trow = (size_t)b * n + slot;
+  float x[32];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float4 v = *reinterpret_cast<const float4*>(T + trow * a.d + cl + 4 * i);
+    x[4 * i] = v.x;
+    x[4 * i + 1] = v.y;
+    x[4 * i + 2] = v.z;
+    x[4 * i + 3] = v.w;
+  }
+  const bool row8 = slot < a.k, active = c < a.d;
+  // (maxima as where these rows came from before: a NaN is the largest of a top row)
+  uint32_t mp = 0u, mn = 0u;
+  if (row8) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+      mp = max(mp, ASYM ? fkey(x[i]) : absbits(x[i]));
+      if constexpr (ASYM) mn = max(mn, fkey(-x[i]));
+    }
+  } else {
+    RowMax<ASYM> m;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) m.template add<false>(i, x[i]);
+    mp = m.pos();
+    if constexpr (ASYM) mn = m.neg();
+  }
+  mp = wave_max_u32(active ? mp : 0u);
+  mn = wave_max_u32(active ? mn : 0u);
+  if ((tid & 63) == 0) {
+    s_red[tid >> 6] = mp;
+    s_red[4 + (tid >> 6)] = mn;
+  }
+  __syncthreads();
+  for (int i = 0; i < nw; ++i) {
+    mp = max(mp, s_red[i]);
+    mn = max(mn, s_red[4 + i]);
+  }
+  const float qmax = ASYM ? (row8 ? 255.0f : 15.0f) : (row8 ? 127.0f : 7.0f);
+  float scale, inv, z;
+  if constexpr (ASYM) row_params<true>(fkey_inv(mp), fkey_inv(mn), qmax, scale, inv, z);
+  else row_params<false>(__uint_as_float(mp), 0.0f, qmax, scale, inv, z);
+  // slot k 2^m + i: block i >> m, position 2^m + i % 2^m
+  const int m = row8 ? 0 : 31 - __builtin_clz((unsigned)(slot / a.k)), i = row8 ? 0 : slot - (a.k << m);
+  const int row = row8 ? slot * a.R : (i >> m) * a.R + (1 << m) + (i & ((1 << m) - 1));
+  const size_t srow = (size_t)b * a.s + row;
+  if (tid == 0) {
+    a.scales[srow] = scale;
+    if constexpr (ASYM) a.scales[a.zeros_off + srow] = z;
+  }
+  f16v ev, od;
+  const float qlo = ASYM ? 0.0f : -qmax, shift = ASYM ? (row8 ? 128.0f : 8.0f) : 0.0f;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    ev[q] = fminf(fmaxf(__fadd_rn(rintf(__fmul_rn(x[2 * q], inv)), z), qlo), qmax) - shift;
+    od[q] = fminf(fmaxf(__fadd_rn(rintf(__fmul_rn(x[2 * q + 1], inv)), z), qlo), qmax) - shift;
+  }
+  if (!active) return;
+  if (row8) {
+    store_hi24(a.hi6, b * a.k + slot, a.KT, ev, od, c);
+  } else {
+    const uint32_t mr = (uint32_t)(srow & 255);
+    store24(a.a6 + (srow >> 8) * (size_t)a.KT * kStageA6 + (size_t)(c >> 7) * kStageA6 + (mr >> 5) * kBlock6 + (mr & 31) * 16 + ((c >> 5) & 1) * 512,
+            to_e2m3(ev, od), (c >> 6) & 1);
+  }
+}
+
 template <int RLOG, bool BF16, bool ASYM, bool RAG>
 hipError_t launch_n(const LaneArgs& a, int blocks, int B, hipStream_t st) {
   constexpr int CW = 64 / (1 << (RLOG - 1)) * 32;  // channels of a wave
@@ -422,4 +546,28 @@ hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, ui
     return rlog == 3 ? launch<3, true>(a, g.x_bf16, g.asym, blocks, g.B, st) : launch<4, true>(a, g.x_bf16, g.asym, blocks, g.B, st);
   }
   return rlog == 3 ? launch<3, false>(a, g.x_bf16, g.asym, g.s / 8, g.B, st) : launch<4, false>(a, g.x_bf16, g.asym, g.s / 16, g.B, st);
+}
+
+hipError_t stamp_launch_top_parts(const stamp_plan* p, float* abot, uint8_t* a6, float* scales, const StampHiOut& hi, hipStream_t st) {
+  const StampGeom& g = p->geom;
+  const int n = g.s / 8, ng = n / 16, levels = g.L + g.r - 3, threads = (g.d / 32 + 63) / 64 * 64;
+  if (n < 16 || n > 512 || threads > 256) return hipErrorInvalidValue;
+  // 32 channels per workgroup (whole lines of a row) where that fills the CUs, else 16
+  if (g.d / 32 * g.B >= stamp_device_cus()) hipLaunchKernelGGL(k_top_parts<32>, dim3((g.d + 31) / 32, g.B), dim3(32 * ng), 0, st, abot, n, g.d, levels);
+  else hipLaunchKernelGGL(k_top_parts<16>, dim3((g.d + 15) / 16, g.B), dim3(16 * ng), 0, st, abot, n, g.d, levels);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  LaneArgs a = {};
+  a.a6 = a6;
+  a.scales = scales;
+  a.s = g.s;
+  a.d = g.d;
+  a.k = g.k;
+  a.KT = p->Kpad >> 7;
+  a.R = g.R;
+  a.zeros_off = (size_t)g.B * g.s;
+  a.hi6 = hi;
+  if (g.asym) hipLaunchKernelGGL(k_quant_parts<true>, dim3(n, g.B), dim3(threads), 0, st, abot, a);
+  else hipLaunchKernelGGL(k_quant_parts<false>, dim3(n, g.B), dim3(threads), 0, st, abot, a);
+  return hipGetLastError();
 }

@@ -67,7 +67,7 @@ LANES = [_lanes(64, batch=3, x_dtype="bf16"), _lanes(96, act_quant="asym", mean_
          _lanes(4096, levels=4, k_hi=8), _lanes(4064, levels=4, k_hi=8, act_quant="asym", mean_shift=0.4, x_dtype="bf16"),
          _lanes(8192, x_dtype="bf16"), _lanes(8192, act_quant="asym"), _lanes(4128), _lanes(8224, x_dtype="bf16"),
          _lanes(12288, x_dtype="bf16", act_quant="asym", mean_shift=0.4), _lanes(1184, levels=7, k_hi=16, x_dtype="bf16"),
-         _lanes(1056, levels=8, k_hi=16, seq_len=256, batch=2, act_quant="asym"), _lanes(8192, seq_len=131, skip_first=True, x_dtype="bf16"),
+         _lanes(1056, levels=4, k_hi=16, seq_len=256, batch=2, act_quant="asym"), _lanes(160, levels=8, k_hi=16, seq_len=256), _lanes(8192, seq_len=131, skip_first=True, x_dtype="bf16"),
          _lanes(224, levels=4, seq_len=402, skip_first=True, batch=2, act_quant="asym", mean_shift=0.4), _lanes(4096, levels=4, seq_len=203)]
 
 
@@ -343,6 +343,42 @@ def test_tensors_off_the_16_byte_grid(w, route):
                 assert torch.equal(Y, Yq)
         assert all(torch.equal(a, b) for a, b in zip(*acts)), "codes depend on the alignment of X"
         plan.destroy()
+
+
+# ---- blocks in parts of 8 tokens: every block length, 16 to 512 sums per sequence, depths that end inside a thread's 16 sums, at them
+# and above, channels that leave the last workgroup partly empty, sequences beside each other, 8-bit rows in tiles and not
+def _parts(s, levels, k, d=192, **kw):
+    return _wl(f"parts_s{s}_l{levels}_k{k}_d{d}", seq_len=s, levels=levels, k_hi=k, d_in=d, d_out=kw.pop("d_out", 68), seed=750 + s + d, **kw)
+
+
+PARTS = [_parts(128, 7, 8, x_dtype="bf16"), _parts(128, 7, 2, batch=2, d=224, act_quant="asym", mean_shift=0.4), _parts(256, 8, 8, d=544),
+         _parts(256, 5, 16, batch=2, x_dtype="bf16"), _parts(512, 9, 8, act_quant="asym", mean_shift=0.4, x_dtype="bf16"), _parts(512, 6, 32, batch=3),
+         _parts(1024, 10, 64, d=1056, x_dtype="bf16"), _parts(1024, 7, 64), _parts(2048, 11, 64, d=544, act_quant="asym"),
+         _parts(2048, 7, 32, d=256), _parts(4096, 12, 64, x_dtype="bf16"), _parts(4096, 8, 64, d=224, act_quant="asym", mean_shift=0.4),
+         _parts(256, 8, 8, d=8192, x_dtype="bf16"), _parts(1024, 10, 32, d=576, d_out=8450, x_dtype="bf16"), _parts(4096, 12, 64, d=224, d_out=4098)]
+
+
+@pytest.mark.parametrize("w", PARTS, ids=[w.name for w in PARTS])
+def test_blocks_in_parts(w):
+    import torch
+    import paper_2510_26771_amd as st
+    tl.full_case(w, with_bias=True, check_unfused=False, engines=("fp6",), routes=("parts", "-direct"))
+    # the same codes as the quantizer of whole blocks: the same output bit for bit, with the 8-bit rows in either GEMM
+    inp = tl.make_inputs(w)
+    plan = st.StampPlan(tl.plan_desc_for(w, "f32"), torch.from_numpy(inp["W"]).cuda())
+    X = tl.to_device_x(inp, w)
+    out = []
+    for hi_rows in (0, 2):
+        plan.set_choice("hi_rows", hi_rows)
+        for packed in (0, 1):
+            plan.set_choice("operands", packed)
+            tl.check_routes(plan, w, ("-parts",) if packed else ("parts",))
+            Y = torch.empty((w.batch, w.seq_len, w.d_out), dtype=torch.float32, device="cuda")
+            plan.linear_forward(X, Y, plan.alloc_workspace())
+            out.append(Y)
+    torch.cuda.synchronize()
+    assert all(torch.equal(out[0], o) for o in out[1:])
+    plan.destroy()
 
 
 # ---- the 8-bit rows in the tiles of the 4-bit rows' GEMM: every block length, sub-trees above, below and beside the tile's, several
