@@ -583,18 +583,26 @@ stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, ui
 // sub-blocks; not 1-D blocks of 32, 4096 -> 11008: 102.8, 103.3, or 8 x 8 blocks one sub-block after another, 1152 -> 4608: 74.1,
 // 76.1).  Layers, microseconds, conversion pass against direct: 2048 tokens 4096 -> 11008, 3 levels, first token left out 96.2,
 // 91.1; 3 x 777 tokens 38.3, 35.1; with 256 outputs, blocks of 8: 65536 tokens x 512 50, 46, x 1024 72, 65, 32768 x 4096 135, 132,
-// 262144 x 256 110, 112, 65536 x 256 with 8192 8-bit rows 73, 81.  The row quantizer's workgroups hold one row each, whose fragments
-// share no line: 1024 x 4096 39, 36, 4096 x 2048 35.5, 33.1, but 4096 x 4096 47.5, 49.1, 8192 x 512 26.8, 29.2, 4096 x 256 all at 8
-// bits 19.4, 20.9, 32768 x 256 41, 58, 262144 x 256 192, 338.  Lines fitted to 1210 such pairs (256 .. 262144 rows, depth 32 .. 11008).
+// 262144 x 256 110, 112, 65536 x 256 with 8192 8-bit rows 73, 81.
+// Lines fitted to 1210 such pairs (256 .. 262144 rows, depth 32 .. 11008).
 bool direct_pays(const stamp_plan* p) {
   const StampGeom& g = p->geom;
   const int64_t rows = (int64_t)g.B * g.s, hi = (int64_t)g.B * g.khi;
-  if (g.ident && !p->rag.on) return rows + hi <= 6144 && rows * g.d <= (3 << 22);
+  // rows by lanes, four to a workgroup, two where d > 8192: always (packed, direct, 256 outputs: 262144 x 256 188, 75, 65536 x 1024 83,
+  // 50, 4096 x 8192 fp32 96, 75, 256 x 32 19.3, 16.0); one to a workgroup, whose pieces of 16 bytes meet in no line, while the
+  // output is small (2048 x 24576 156, 152, but 4096 x 24576 with 256 8-bit rows 229, 233, 2048 x 32768 fp32 271, 274)
+  if (g.ident && !p->rag.on) return g.d <= 16384 || rows * g.d <= (3 << 24);
   // 1-D blocks of 8 and 16 tokens by stamp_lanes1d: whole fragments leave in 16 and 8 bytes, at any size as fast as they can be made;
   // only many 8-bit rows cost (packed, direct: 32768 x 4096 136, 112, x 8192 310, 233, 16 x 5000 x 4096 375, 288, 262144 x 256 106, 83;
   // 128 sequences of 512 with 64 8-bit rows each, x 256 71.5, 75.5, 64 of them 51.8, 49.1, 256 with 32 each 73.6, 66.4)
   if (!g.is2d && stamp_lanes1d_fits(p, p->rag.on ? p->rag.r : g.r)) return rows + 16 * hi <= 140000 || 16 * hi <= rows;
   return rows + 16 * hi <= 140000 && rows * g.d <= (1 << 27);
+}
+// rows that STAMP_ROUTE_ROWS names, not STAMP_ROUTE_DIRECT
+bool many_rows(const stamp_plan* p) {
+  const StampGeom& g = p->geom;
+  const int64_t rows = (int64_t)g.B * g.s;
+  return g.ident && !p->rag.on && (rows + (int64_t)g.B * g.khi > 6144 || rows * g.d > (3 << 22));
 }
 bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
   const StampGeom& g = p->geom;
@@ -788,7 +796,7 @@ int32_t stamp_debug_routes(const stamp_plan_t* p) {
   if (p->grp) r |= STAMP_ROUTE_GROUP_BLOCKS;
   if (rag) r |= STAMP_ROUTE_ANY_LENGTH_BLOCKS;
   if (p->gen.group) return r;
-  if (direct_route(p, aligned, aligned)) r |= p->ws_parts_hi != 0 ? STAMP_ROUTE_PARTS : STAMP_ROUTE_DIRECT;
+  if (direct_route(p, aligned, aligned)) r |= p->ws_parts_hi != 0 ? STAMP_ROUTE_PARTS : (many_rows(p) ? STAMP_ROUTE_ROWS : STAMP_ROUTE_DIRECT);
   else if (convert_beside_top(p)) r |= STAMP_ROUTE_BESIDE_TOP;
   if ((own ? g.khi : g.k) > 0) {
     if (p->hi6[own]) r |= STAMP_ROUTE_HI_FP6;

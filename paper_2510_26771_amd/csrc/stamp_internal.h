@@ -388,6 +388,8 @@ hipError_t stamp_gen_inverse(const stamp_plan* p, float* const (&buf)[3], int nc
 bool stamp_lanes1d_fits(const stamp_plan* p, int rlog);
 hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, uint8_t* a6, float* scales, float* abot, const StampHiOut& hi,
                                 hipStream_t st);
+// rows as they are (k = the first 8-bit rows of every sequence) -> operands and scales
+hipError_t stamp_launch_lanes_rows(const stamp_plan* p, const void* X, int x_bf16, uint8_t* a6, float* scales, const StampHiOut& hi, hipStream_t st);
 // the levels above parts of 8 tokens: their sums [B][s / 8][d] (overwritten) -> operands and scales of these rows
 hipError_t stamp_launch_top_parts(const stamp_plan* p, float* abot, uint8_t* a6, float* scales, const StampHiOut& hi, hipStream_t st);
 // DCT of a power-of-two length with the points in registers (stamp_dct.hip): plans it takes, and src -> T (inv = 0), src -> Y (+ bias)

@@ -77,6 +77,8 @@ __device__ __forceinline__ float partner(float x) {
 // largest over the lanes of equal token pair (NL lanes apart)
 template <int NL>
 __device__ __forceinline__ uint32_t across_groups(uint32_t x) {
+  if constexpr (NL <= 1) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xF, 0xF, true));  // row_ror 1
+  if constexpr (NL <= 2) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xF, 0xF, true));  // row_ror 2
   if constexpr (NL <= 4) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xF, 0xF, true));  // row_ror 4
   if constexpr (NL <= 8) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true));  // row_ror 8
   auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
@@ -476,6 +478,85 @@ __global__ __launch_bounds__(256) void k_quant_parts(const float* __restrict__ T
   }
 }
 
+// Rows as they are (plans without transform, transformed tokens of the general path): a lane holds 32 channels of one row, a
+// workgroup ROWS neighbouring rows, whose 16-byte pieces of the operand lie side by side.  The first k rows of a sequence are
+// 8-bit rows.  Each value is read once.  What bounds it: the launch and its first loads on few rows, memory on many.
+// 2048 rows x 4096 channels fp32 9.0 us (a workgroup per row that reads it twice and stores 8 bytes at a time: 14.2),
+// 262144 x 256 bf16, the whole layer with 256 outputs, 75 (packed codes and a pass that converts them 188).
+template <int ROWS, bool BF16, bool ASYM>
+__global__ __launch_bounds__(1024) void k_lanes_rows(const LaneArgs a, int rows) {
+  constexpr int CPR = BF16 ? 4 : 8;
+  __shared__ __attribute__((aligned(16))) uint32_t s_max[2][ROWS][16];  // [sign][row][wave]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = (int)(blockDim.x >> 6);
+  const int tl = lane & (ROWS - 1), m = (int)blockIdx.x * ROWS + tl, mr = min(m, rows - 1);
+  const int c = (wave * (64 / ROWS) + lane / ROWS) * 32, cl = min(c, a.d - 32);
+  u4 raw[CPR];
+  const uint8_t* const src = reinterpret_cast<const uint8_t*>(a.X) + ((size_t)mr * a.d + cl) * (BF16 ? 2 : 4);
+#pragma unroll
+  for (int h = 0; h < CPR; ++h) raw[h] = *reinterpret_cast<const u4*>(src + 16 * h);
+  float x[32];
+  RowMax<ASYM> mx;
+#pragma unroll
+  for (int i = 0; i < 32; ++i) {
+    if constexpr (BF16) x[i] = (i & 1) ? bf16hi(raw[i >> 3][(i >> 1) & 3]) : bf16lo(raw[i >> 3][(i >> 1) & 3]);
+    else x[i] = __uint_as_float(raw[BF16 ? 0 : i >> 2][i & 3]);
+    mx.template add<false>(i, x[i]);
+  }
+  const bool live = !ASYM || c < a.d;
+  const uint32_t pos = across_groups<ROWS>(live ? mx.pos() : 0u);
+  uint32_t neg = 0u;
+  if constexpr (ASYM) neg = across_groups<ROWS>(live ? mx.neg() : 0u);
+  if (lane < ROWS) {
+    s_max[0][tl][wave] = pos;
+    if constexpr (ASYM) s_max[1][tl][wave] = neg;
+  }
+  __syncthreads();
+  auto reduce = [&](int sign) {
+    const u4* q = reinterpret_cast<const u4*>(&s_max[sign][tl][0]);
+    uint32_t r = 0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const u4 v = q[i];
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        if (4 * i + w < nw) r = max(r, v[w]);
+    }
+    return r;
+  };
+  const int b = mr / a.s, pr = mr - b * a.s;
+  const bool row8 = pr < a.k;
+  const float qmax = ASYM ? (row8 ? 255.0f : 15.0f) : (row8 ? 127.0f : 7.0f);
+  float scale, inv, z;
+  if constexpr (ASYM) row_params<true>(fkey_inv(reduce(0)), fkey_inv(reduce(1)), qmax, scale, inv, z);
+  else row_params<false>(__uint_as_float(reduce(0)), 0.0f, qmax, scale, inv, z);
+  if (tid < ROWS && m < rows) {
+    a.scales[m] = scale;
+    if constexpr (ASYM) a.scales[a.zeros_off + m] = z;
+  }
+  const float qlo = ASYM ? 0.0f : -qmax, shift = ASYM ? (row8 ? 128.0f : 8.0f) : 0.0f;
+  f16v ev, od;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const float p = __fmul_rn(x[2 * i], inv), q = __fmul_rn(x[2 * i + 1], inv);
+    ev[i] = __builtin_amdgcn_fmed3f(__fadd_rn(rintf(p), z), qlo, qmax) - shift;
+    od[i] = __builtin_amdgcn_fmed3f(__fadd_rn(rintf(q), z), qlo, qmax) - shift;
+  }
+  if (c >= a.d || m >= rows) return;
+  if (row8) {
+    store_hi24(a.hi6, b * a.k + pr, a.KT, ev, od, c);
+  } else {
+    store24(a.a6 + (size_t)(m >> 8) * a.KT * kStageA6 + (size_t)(c >> 7) * kStageA6 + ((m & 255) >> 5) * kBlock6 + (m & 31) * 16 + ((c >> 5) & 1) * 512,
+            to_e2m3(ev, od), (c >> 6) & 1);
+  }
+}
+
+template <int ROWS, bool BF16>
+void launch_rows(bool asym, const LaneArgs& a, int rows, hipStream_t st) {
+  const dim3 grid((rows + ROWS - 1) / ROWS), blk((a.d * ROWS + 2047) / 2048 * 64);
+  if (asym) hipLaunchKernelGGL((k_lanes_rows<ROWS, BF16, true>), grid, blk, 0, st, a, rows);
+  else hipLaunchKernelGGL((k_lanes_rows<ROWS, BF16, false>), grid, blk, 0, st, a, rows);
+}
+
 template <int RLOG, bool BF16, bool ASYM, bool RAG>
 hipError_t launch_n(const LaneArgs& a, int blocks, int B, hipStream_t st) {
   constexpr int CW = 64 / (1 << (RLOG - 1)) * 32;  // channels of a wave
@@ -569,5 +650,25 @@ hipError_t stamp_launch_top_parts(const stamp_plan* p, float* abot, uint8_t* a6,
   a.hi6 = hi;
   if (g.asym) hipLaunchKernelGGL(k_quant_parts<true>, dim3(n, g.B), dim3(threads), 0, st, abot, a);
   else hipLaunchKernelGGL(k_quant_parts<false>, dim3(n, g.B), dim3(threads), 0, st, abot, a);
+  return hipGetLastError();
+}
+
+hipError_t stamp_launch_lanes_rows(const stamp_plan* p, const void* X, int x_bf16, uint8_t* a6, float* scales, const StampHiOut& hi, hipStream_t st) {
+  const StampGeom& g = p->geom;
+  LaneArgs a = {};
+  a.X = X;
+  a.a6 = a6;
+  a.scales = scales;
+  a.s = g.s;
+  a.d = g.d;
+  a.k = g.k;
+  a.KT = p->Kpad >> 7;
+  a.zeros_off = (size_t)g.B * g.s;
+  a.hi6 = hi;
+  const int rows = g.B * g.s;
+  const int n = g.d <= 8192 ? 4 : (g.d <= 16384 ? 2 : 1);  // as many rows as 1024 threads hold
+  if (n == 4) x_bf16 ? launch_rows<4, true>(g.asym, a, rows, st) : launch_rows<4, false>(g.asym, a, rows, st);
+  else if (n == 2) x_bf16 ? launch_rows<2, true>(g.asym, a, rows, st) : launch_rows<2, false>(g.asym, a, rows, st);
+  else x_bf16 ? launch_rows<1, true>(g.asym, a, rows, st) : launch_rows<1, false>(g.asym, a, rows, st);
   return hipGetLastError();
 }

@@ -89,6 +89,37 @@ def test_blocks_by_lanes(w):
     plan.destroy()
 
 
+# ---- rows by lanes: four, two and one of them to a workgroup, the widths on either side; rows and 8-bit rows that are no multiple
+# of that; a last wave that is partly empty; the smallest; all rows at 8 bits; rows of the general path
+def _rows(d, s, batch, k, xform="identity", **kw):
+    base = dict(xform=xform, levels=0, seq_len=s, batch=batch, k_hi=k, d_in=d, d_out=66, seed=700 + d)
+    base.update(kw)
+    return _wl("rows_%s_%dx%dx%d_k%d_%s" % (xform, batch, s, d, k, "_".join(f"{a}{b}" for a, b in kw.items())), **base)
+
+
+ROWS = [_rows(32, 3, 1, 1), _rows(96, 131, 3, 5, x_dtype="bf16"), _rows(544, 37, 2, 0, act_quant="asym", mean_shift=0.4),
+        _rows(2080, 130, 1, 33, x_dtype="bf16", act_quant="asym"), _rows(8192, 21, 1, 4, x_dtype="bf16"), _rows(8224, 21, 1, 4, x_dtype="bf16"),
+        _rows(8224, 19, 1, 3, act_quant="asym", mean_shift=0.4), _rows(16384, 7, 3, 2), _rows(16416, 5, 3, 2), _rows(16416, 5, 3, 2, x_dtype="bf16"),
+        _rows(96, 4100, 2, 16, x_dtype="bf16"), _rows(160, 64, 3, 5, xform="wht"), _rows(1056, 33, 3, 2, xform="dct", act_quant="asym", x_dtype="bf16")]
+
+
+@pytest.mark.parametrize("w", ROWS, ids=[w.name for w in ROWS])
+def test_rows_by_lanes(w):
+    import torch
+    import paper_2510_26771_amd as st
+    tl.full_case(w, with_bias=True, check_unfused=False, engines=("fp6",), routes=("rows" if w.batch * w.seq_len > 6144 else "direct",))
+    inp = tl.make_inputs(w)
+    plan = st.StampPlan(tl.plan_desc_for(w, "f32"), torch.from_numpy(inp["W"]).cuda())
+    X = tl.to_device_x(inp, w)
+    Y = [torch.empty((w.batch, w.seq_len, w.d_out), dtype=torch.float32, device="cuda") for _ in range(2)]
+    for packed in (0, 1):
+        plan.set_choice("operands", packed)
+        plan.linear_forward(X, Y[packed], plan.alloc_workspace())
+    torch.cuda.synchronize()
+    assert torch.equal(Y[0], Y[1])
+    plan.destroy()
+
+
 # ---- who writes the FP6 operands: the quantizer, or a pass over packed codes (sizes where one form is at least 1.05 times as
 # fast: quantizers by rows, by blocks on a line, of any length, on a grid)
 OPERANDS = [(dict(xform="identity", levels=0, batch=32, seq_len=1024, k_hi=2, d_in=256), False),
