@@ -378,7 +378,7 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
   sp.hi6 = hi6_out(bot);
   const bool quads = stamp_bottom_quads(p);
   if (bot != nullptr) {
-    if (g.is2d && !quads) return hipErrorInvalidValue;  // direct_route
+    if (g.is2d && !stamp_lanes2d_fits(p)) return hipErrorInvalidValue;  // direct_route
     q_lo = dir->a6;
   }
   const int nthreads = ((sp.c_split / 8 + 63) / 64) * 64;
@@ -397,14 +397,9 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
     if (sp.nsplit == 1) { LAUNCH2D__(RL, BF, AS, 0); }                                                    \
     else { LAUNCH2D__(RL, BF, AS, 1); LAUNCH2D__(RL, BF, AS, 2); }                                        \
   } while (0)
-#define LAUNCHQ_(BF, AS, O6)                                                                              \
-  hipLaunchKernelGGL((k_bottom2d_quads<BF, AS, O6>), grid, dim3(4 * nthreads), (size_t)4 * nthreads * 32, st, X, q_lo, scales, abot, \
-                     g.s, g.d, g.G, g.gridW, p->Kpad, zeros_off, sp)
 #define LAUNCHQ(BF, AS)                                                                                   \
-  do {                                                                                                    \
-    if (bot != nullptr) LAUNCHQ_(BF, AS, true);                                                           \
-    else LAUNCHQ_(BF, AS, false);                                                                         \
-  } while (0)
+  hipLaunchKernelGGL((k_bottom2d_quads<BF, AS>), grid, dim3(4 * nthreads), (size_t)4 * nthreads * 32, st, X, q_lo, scales, abot, \
+                     g.s, g.d, g.G, g.gridW, p->Kpad, zeros_off, sp)
 #define LAUNCH2D(RL)                                                                                      \
   do {                                                                                                    \
     if (g.asym) { if (g.x_bf16) LAUNCH2D_(RL, true, true); else LAUNCH2D_(RL, false, true); }             \
@@ -412,6 +407,9 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
   } while (0)
   if (!(part & 1)) {
     // bottom kernel skipped
+  } else if (g.is2d && bot != nullptr) {
+    const hipError_t le = stamp_launch_lanes2d(p, X, q_lo, scales, top_in_bottom ? nullptr : abot, sp.hi6, st);
+    if (le != hipSuccess) return le;
   } else if (!g.is2d && bot != nullptr && stamp_lanes1d_fits(p, g.r)) {
     const hipError_t le = stamp_launch_lanes1d(p, g.r, X, q_lo, scales, top_in_bottom ? nullptr : abot, sp.hi6, st);
     if (le != hipSuccess) return le;
@@ -440,7 +438,6 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
 #undef LAUNCH2D_
 #undef LAUNCH2D__
 #undef LAUNCHQ
-#undef LAUNCHQ_
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (!(part & 2) || top_in_bottom) return hipSuccess;

@@ -579,9 +579,8 @@ stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, ui
 // stamp_linear_forward: the quantizer writes the FP6 operands itself (no packed codes, no conversion pass) on the default route:
 // FP6 engine, fused inverse (or none), 8-bit rows through the kernel for few rows.  Its stores are 8 bytes of 24-byte
 // fragments where packed codes are 4-byte words of whole lines; it pays while the conversion's launch counts, and where a
-// workgroup stores a few neighbouring rows, not one after another (1-D blocks of 8 and 16 tokens, 8 x 8 blocks by
-// sub-blocks; not 1-D blocks of 32, 4096 -> 11008: 102.8, 103.3, or 8 x 8 blocks one sub-block after another, 1152 -> 4608: 74.1,
-// 76.1).  Layers, microseconds, conversion pass against direct: 2048 tokens 4096 -> 11008, 3 levels, first token left out 96.2,
+// workgroup stores a few neighbouring rows, not one after another (1-D blocks of 8 and 16 tokens, blocks of a grid by lanes; not 1-D
+// blocks of 32, 4096 -> 11008: 102.8, 103.3).  Layers, microseconds, conversion pass against direct: 2048 tokens 4096 -> 11008, 3 levels, first token left out 96.2,
 // 91.1; 3 x 777 tokens 38.3, 35.1; with 256 outputs, blocks of 8: 65536 tokens x 512 50, 46, x 1024 72, 65, 32768 x 4096 135, 132,
 // 262144 x 256 110, 112, 65536 x 256 with 8192 8-bit rows 73, 81.
 // Lines fitted to 1210 such pairs (256 .. 262144 rows, depth 32 .. 11008).
@@ -592,10 +591,10 @@ bool direct_pays(const stamp_plan* p) {
   // 50, 4096 x 8192 fp32 96, 75, 256 x 32 19.3, 16.0); one to a workgroup, whose pieces of 16 bytes meet in no line, while the
   // output is small (2048 x 24576 156, 152, but 4096 x 24576 with 256 8-bit rows 229, 233, 2048 x 32768 fp32 271, 274)
   if (g.ident && !p->rag.on) return g.d <= 16384 || rows * g.d <= (3 << 24);
-  // 1-D blocks of 8 and 16 tokens by stamp_lanes1d: whole fragments leave in 16 and 8 bytes, at any size as fast as they can be made;
+  // 1-D blocks of 8 and 16 tokens by stamp_lanes1d, blocks of a grid by stamp_lanes2d (32 x 4096 x 512 92, 80): whole fragments leave in 16 and 8 bytes, at any size as fast as they can be made;
   // only many 8-bit rows cost (packed, direct: 32768 x 4096 136, 112, x 8192 310, 233, 16 x 5000 x 4096 375, 288, 262144 x 256 106, 83;
   // 128 sequences of 512 with 64 8-bit rows each, x 256 71.5, 75.5, 64 of them 51.8, 49.1, 256 with 32 each 73.6, 66.4)
-  if (!g.is2d && stamp_lanes1d_fits(p, p->rag.on ? p->rag.r : g.r)) return rows + 16 * hi <= 140000 || 16 * hi <= rows;
+  if (g.is2d || stamp_lanes1d_fits(p, p->rag.on ? p->rag.r : g.r)) return rows + 16 * hi <= 140000 || 16 * hi <= rows;
   return rows + 16 * hi <= 140000 && rows * g.d <= (1 << 27);
 }
 // rows that STAMP_ROUTE_ROWS names, not STAMP_ROUTE_DIRECT
@@ -608,7 +607,7 @@ bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
   const StampGeom& g = p->geom;
   if (!p->direct_ok || p->engine != STAMP_GEMM_FP6 || p->gen.group || p->dbg[STAMP_CHOICE_OPERANDS] == 1) return false;
   if (p->dbg[STAMP_CHOICE_OPERANDS] == 0 && !direct_pays(p)) return false;
-  if (p->rag.on ? p->rag.r > 4 : (!g.ident && (g.is2d ? !stamp_bottom_quads(p) : g.r > 4 && p->ws_parts_hi == 0))) return false;
+  if (p->rag.on ? p->rag.r > 4 : (!g.ident && (g.is2d ? !stamp_lanes2d_fits(p) : g.r > 4 && p->ws_parts_hi == 0))) return false;
   if (p->gen.kind != kGenNone || g.ident) return !p->rag.on || (rag_route(p, Y) && stamp_rag_quantizes(p, X) && p->hi6[0]);
   if (!p->fused_ok || p->unfused) return false;
   if (own_top(p)) return p->hi6[1];

@@ -880,10 +880,11 @@ __global__ __launch_bounds__(512) void k_bottom2d(const void* __restrict__ X, ui
 // 8 x 8 blocks of up to 1536 channels: the four 4 x 4 sub-blocks side by side, a group of waves each (nthr threads), their
 // sums through LDS, the last level's four rows a group each.  A block's rows need all its channels, so there are no more
 // workgroups than blocks: k_bottom2d, whose workgroup takes the sub-blocks one after another, left the CUs three waves each.
-// Bound by the instructions of the rounding and the packing on the CUs that have a block.  Layers, k_bottom2d against this
+// Packed codes (FP6 operands: stamp_lanes2d.hip).  Bound by the instructions of the rounding and the packing on the CUs that have
+// a block.  Layers, k_bottom2d against this
 // one, microseconds: 2 x 4096 tokens 1152 -> 4608 72.4, 64.5; 512 -> 1152 39.5, 26.9; 4096 tokens 1536 -> 1536, 6 levels 58.9,
 // 47.5; 6 x 4096 tokens (384 blocks) 1152 -> 1152 70.4, 68.7; 16 x 4096 tokens (1024 blocks) 149.7, 151.2.
-template <bool BF16, bool ASYM, bool OUT6>
+template <bool BF16, bool ASYM>
 __global__ __launch_bounds__(768) void k_bottom2d_quads(const void* __restrict__ X, uint8_t* __restrict__ q_lo, float* __restrict__ scales,
                                                          float* __restrict__ abot, int s, int d, int G, int gridW, int Kpad,
                                                          size_t zeros_off, SplitArgs sp) {
@@ -896,8 +897,8 @@ __global__ __launch_bounds__(768) void k_bottom2d_quads(const void* __restrict__
   const int by = j / G, bx = j - by * G, k = G * G, c0 = tid * 8, sby = qd >> 1, sbx = qd & 1;
   const bool active = c0 < d;
   const size_t tok0 = (size_t)b * s + (size_t)(by * 8 + 4 * sby) * gridW + bx * 8 + 4 * sbx, prow0 = (size_t)b * s + (size_t)j * 64;
-  uint8_t* const q_blk = OUT6 ? q_lo + (prow0 >> 8) * (size_t)(Kpad >> 7) * kStageA6 : q_lo + stamp_qlo_offset(prow0, 0, Kpad);
-  const uint32_t q_off = OUT6 ? off48(c0, kStageA6) : (uint32_t)stamp_qlo_offset(0, c0, Kpad);
+  uint8_t* const q_blk = q_lo + stamp_qlo_offset(prow0, 0, Kpad);
+  const uint32_t q_off = (uint32_t)stamp_qlo_offset(0, c0, Kpad);
   // two rows of cells after one another: 15 finished rows at once would not fit the registers of 12 waves
   {
     constexpr int WPT = BF16 ? 1 : 2;
@@ -938,8 +939,8 @@ __global__ __launch_bounds__(768) void k_bottom2d_quads(const void* __restrict__
       cell(0, 1, rowv[3], rowv[4], rowv[5]);
       if constexpr (!BF16) request(1);
       auto meta = [=](int r) -> RowMeta { return meta2d<3>(r, sby, sbx); };
-      flush_rows<6, true, ASYM, 0, false, OUT6>(rowv, meta, 0, s_max[qd], q_blk, q_off, scales + prow0, zeros_off, active, tid, nullptr, 0,
-                                                nullptr, true, prow0 & 255, 0, nw);
+      flush_rows<6, true, ASYM, 0>(rowv, meta, 0, s_max[qd], q_blk, q_off, scales + prow0, zeros_off, active, tid, nullptr, 0, nullptr,
+                                true, 0, 0, nw);
     }
     float rowv[9][8], sum[8];
     cell(1, 0, rowv[0], rowv[1], rowv[2]);
@@ -949,8 +950,8 @@ __global__ __launch_bounds__(768) void k_bottom2d_quads(const void* __restrict__
     mine[0] = make_float4(sum[0], sum[1], sum[2], sum[3]);
     mine[1] = make_float4(sum[4], sum[5], sum[6], sum[7]);
     auto meta = [=](int r) -> RowMeta { return meta2d<3>(r + 6, sby, sbx); };
-    flush_rows<9, true, ASYM, 0, false, OUT6>(rowv, meta, 1, s_max[qd], q_blk, q_off, scales + prow0, zeros_off, active, tid, nullptr, 0,
-                                              nullptr, true, prow0 & 255, 0, nw);
+    flush_rows<9, true, ASYM, 0>(rowv, meta, 1, s_max[qd], q_blk, q_off, scales + prow0, zeros_off, active, tid, nullptr, 0, nullptr,
+                                true, 0, 0, nw);
   }
   __syncthreads();
   float row[1][8], ll[4][8];
@@ -991,11 +992,11 @@ __global__ __launch_bounds__(768) void k_bottom2d_quads(const void* __restrict__
   __syncthreads();
   if (qd != 0) {
     auto meta = [=](int) -> RowMeta { return RowMeta{3, qd, qd}; };
-    flush_rows<1, true, ASYM, 2, false, OUT6>(row, meta, 0, s_max[qd], q_blk, q_off, scales + prow0, zeros_off, active, tid, nullptr, 0,
-                                              s_amax, true, prow0 & 255, 0, nw);
+    flush_rows<1, true, ASYM, 2>(row, meta, 0, s_max[qd], q_blk, q_off, scales + prow0, zeros_off, active, tid, nullptr, 0,
+                                              s_amax, true, 0, 0, nw);
   } else if (sp.q_hi != nullptr) {
-    finish_top_row<true, ASYM, false, OUT6, 2>(row[0], 3, nullptr, sp.q_hi + ((size_t)b * k + j) * d + c0,
-                                               (OUT6 ? q_lo + a6_row(prow0, Kpad >> 7) : q_blk) + q_off, scales + prow0, zeros_off, j < sp.khi,
+    finish_top_row<true, ASYM, false, false, 2>(row[0], 3, nullptr, sp.q_hi + ((size_t)b * k + j) * d + c0,
+                                               q_blk + q_off, scales + prow0, zeros_off, j < sp.khi,
                                                active, tid, sp.hi6, b * sp.khi + j, Kpad >> 7, c0, nullptr, 0, s_amax);
   } else if (active) {
     float4* o = reinterpret_cast<float4*>(abot + ((size_t)b * k + j) * d + c0);

@@ -286,7 +286,7 @@ hipError_t stamp_launch_weight_quant(const stamp_plan* p, const float* W, hipStr
 int stamp_actquant_nsplit(const stamp_plan* p);
 // plans without top levels: the bottom kernel also quantizes the block sums (no k_top, no k_quant_hi)
 bool stamp_top_in_bottom(const stamp_plan* p);
-// 8 x 8 blocks whose four sub-blocks one workgroup takes side by side (k_bottom2d_quads: up to 1536 channels by its threads;
+// packed codes of 8 x 8 blocks whose four sub-blocks one workgroup takes side by side (k_bottom2d_quads: up to 1536 channels by its threads;
 // up to two blocks per CU: with more the CUs are full either way)
 bool stamp_bottom_quads(const stamp_plan* p);
 // dir: the codes leave as FP6 operands (4-bit rows, 8-bit rows) instead of in q_hi / q_lo, which are not written
@@ -388,6 +388,9 @@ hipError_t stamp_gen_inverse(const stamp_plan* p, float* const (&buf)[3], int nc
 bool stamp_lanes1d_fits(const stamp_plan* p, int rlog);
 hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, uint8_t* a6, float* scales, float* abot, const StampHiOut& hi,
                                 hipStream_t st);
+// the same for 4 x 4 and 8 x 8 blocks of a token grid
+bool stamp_lanes2d_fits(const stamp_plan* p);
+hipError_t stamp_launch_lanes2d(const stamp_plan* p, const void* X, uint8_t* a6, float* scales, float* abot, const StampHiOut& hi, hipStream_t st);
 // rows as they are (k = the first 8-bit rows of every sequence) -> operands and scales
 hipError_t stamp_launch_lanes_rows(const stamp_plan* p, const void* X, int x_bf16, uint8_t* a6, float* scales, const StampHiOut& hi, hipStream_t st);
 // the levels above parts of 8 tokens: their sums [B][s / 8][d] (overwritten) -> operands and scales of these rows

@@ -1,0 +1,135 @@
+// What the bottom kernels by lanes share (stamp_lanes1d.hip, stamp_lanes2d.hip): a lane holds 32 consecutive channels of its tokens.
+#ifndef STAMP_LANES_H_
+#define STAMP_LANES_H_
+#include "stamp_bottom_kernel.h"
+
+namespace {
+
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef uint32_t u6v __attribute__((ext_vector_type(6)));
+
+struct LaneArgs {
+  const void* X;
+  uint8_t* a6;       // operand of the 4-bit rows
+  float* scales;
+  float* abot;       // top levels: the block sums [B][s / 2^RLOG][d] go here, unfinished; else nullptr
+  int s, d, k, khi, KT;
+  int R;             // the plan's block length: 2^RLOG tokens are one of its parts
+  size_t zeros_off;
+  Hi6Out hi6;
+  StampRag rag;
+  int G, gridW;      // token grid: blocks per row, tokens per row
+};
+
+// 24 bytes of a fragment -> its places; dst = (lane group, row) of a block, half = fragment / 2
+__device__ __forceinline__ void store24(uint8_t* dst, u6v w, bool half) {
+  const u4 a = {half ? w[2] : w[0], half ? w[3] : w[1], half ? w[4] : w[2], half ? w[5] : w[3]};
+  const u2v b = {half ? w[0] : w[4], half ? w[1] : w[5]};
+  *reinterpret_cast<u4*>(dst + (half ? 2 * kPart : 0)) = a;
+  *reinterpret_cast<u2v*>(dst + kPart + (half ? 8 : 0)) = b;
+}
+// channels 2 i in ev[i], 2 i + 1 in od[i]: integers of magnitude up to 8 (or values that round to such)
+__device__ __forceinline__ u6v to_e2m3(f16v ev, f16v od) { return (u6v)__builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(ev, od, 8.0f); }
+
+// codes of 8-bit rows, 16 h + l, as two fragments
+__device__ __forceinline__ void store_hi24(const Hi6Out& o, int m, int KT, f16v ev, f16v od, int c) {
+  f16v hv[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) hv[h][i] = floorf(__builtin_fmaf(h ? od[i] : ev[i], 0.0625f, 0.5f));
+  const u6v h = to_e2m3(hv[0], hv[1]);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    ev[i] = __builtin_fmaf(-16.0f, hv[0][i], ev[i]);
+    od[i] = __builtin_fmaf(-16.0f, hv[1][i], od[i]);
+  }
+  const u6v l = to_e2m3(ev, od);
+  const uint32_t off = (uint32_t)(c >> 7) * hi_step_bytes(o) + ((c >> 5) & 1) * 512;
+  hi_rows(o, m, KT, [&](uint8_t* dst, int lo) {
+    store24(dst + off, h, (c >> 6) & 1);
+    store24(dst + off + lo, l, (c >> 6) & 1);
+  });
+}
+
+// the sum of this lane's partner at lane distance 2^(l - 2)
+template <int l>
+__device__ __forceinline__ float partner(float x) {
+  const int i = __float_as_int(x);
+  if constexpr (l == 2) return __int_as_float(__builtin_amdgcn_update_dpp(0, i, 0xB1, 0xF, 0xF, true));       // quad_perm [1,0,3,2]
+  else if constexpr (l == 3) return __int_as_float(__builtin_amdgcn_update_dpp(0, i, 0x4E, 0xF, 0xF, true));  // quad_perm [2,3,0,1]
+  else {
+    static_assert(l == 4, "");
+    const int lo = __builtin_amdgcn_update_dpp(0, i, 0x104, 0xF, 0xF, true);             // row_shl 4: lane n takes lane n + 4
+    return __int_as_float(__builtin_amdgcn_update_dpp(lo, i, 0x114, 0xF, 0xA, false));   // row_shr 4 into the odd quads
+  }
+}
+
+// largest over the lanes of equal token pair (NL lanes apart)
+template <int NL>
+__device__ __forceinline__ uint32_t across_groups(uint32_t x) {
+  if constexpr (NL <= 1) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xF, 0xF, true));  // row_ror 1
+  if constexpr (NL <= 2) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xF, 0xF, true));  // row_ror 2
+  if constexpr (NL <= 4) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xF, 0xF, true));  // row_ror 4
+  if constexpr (NL <= 8) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true));  // row_ror 8
+  auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = max(p[0], p[1]);
+  auto q = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return max(q[0], q[1]);
+}
+
+// largest magnitude (ASYM: order key of the largest value) of 32 channels.  A NaN is passed over unless it has eight
+// neighbours of its kind (one thread's share in the streaming kernels); nan_max: it is the largest value.
+template <bool ASYM>
+struct RowMax {
+  float hi[4], lo[4], nan = 0.0f;  // nan: not 0 if a value is no number or infinite
+  template <bool NANMAX>
+  __device__ __forceinline__ void add(int c, float v) {
+    const float x = ASYM ? v : fabsf(v);
+    hi[c >> 3] = (c & 7) == 0 ? x : fmaxf(hi[c >> 3], x);
+    if constexpr (ASYM) lo[c >> 3] = (c & 7) == 0 ? x : fminf(lo[c >> 3], x);
+    if constexpr (NANMAX) nan = __builtin_fmaf(v, 0.0f, nan);
+  }
+  __device__ __forceinline__ uint32_t pos() const {
+    uint32_t m = 0u;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) m = max(m, ASYM ? fkey(hi[g]) : __float_as_uint(hi[g]));
+    return m;
+  }
+  __device__ __forceinline__ uint32_t neg() const {
+    uint32_t m = 0u;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) m = max(m, fkey(-lo[g]));
+    return m;
+  }
+};
+
+// scale, reciprocal and offset of a row from its maxima (already times the row's norm)
+template <bool ASYM>
+__device__ __forceinline__ void row_params(float hi, float nlo, float qmax, float& scale, float& inv, float& z) {
+  scale = inv = z = 0.0f;
+  if constexpr (ASYM) {
+    asym_params(hi, nlo, qmax, scale, inv, z);
+  } else if (hi > 0.0f) {
+    scale = __fdiv_rn(hi, qmax);
+    inv = __fdiv_rn(qmax, hi);
+  }
+}
+
+// largest over the waves of one row's maxima
+__device__ __forceinline__ uint32_t max_of_waves(const uint32_t (&part)[16], int nw) {
+  const u4* q = reinterpret_cast<const u4*>(&part[0]);
+  uint32_t mx = 0u;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const u4 v = q[i];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (4 * i + w < nw) mx = max(mx, v[w]);
+  }
+  return mx;
+}
+
+}  // namespace
+
+#endif  // STAMP_LANES_H_

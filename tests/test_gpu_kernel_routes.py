@@ -89,6 +89,38 @@ def test_blocks_by_lanes(w):
     plan.destroy()
 
 
+# ---- blocks of a token grid by lanes: the widths of one wave, of several and the widest, a last wave that is partly empty, grids that
+# are no square, blocks whose sums are 8-bit rows, 4-bit rows or go to levels above
+def _lanes2(d, levels, gh, gw, k, batch=1, **kw):
+    base = dict(xform="haar2d", grid_h=gh, grid_w=gw, seq_len=gh * gw, batch=batch, levels=levels, k_hi=k, d_in=d, d_out=66, seed=900 + d, corr_len=4.0)
+    base.update(kw)
+    return _wl("lanes2_%dx%dx%dx%d_J%d_k%d_%s" % (batch, gh, gw, d, levels, k, "_".join(f"{a}{b}" for a, b in kw.items())), **base)
+
+
+LANES2 = [_lanes2(32, 3, 16, 16, 4, x_dtype="bf16"), _lanes2(160, 3, 16, 32, 8, act_quant="asym", mean_shift=0.4),
+          _lanes2(1536, 3, 16, 16, 4, x_dtype="bf16", act_quant="asym"), _lanes2(1536, 3, 16, 16, 4), _lanes2(1184, 3, 32, 16, 5, batch=2),
+          _lanes2(288, 4, 32, 32, 16, x_dtype="bf16"), _lanes2(1056, 4, 32, 32, 16, act_quant="asym", mean_shift=-0.3),
+          _lanes2(32, 2, 16, 16, 16, batch=3, x_dtype="bf16"), _lanes2(544, 2, 8, 16, 8, act_quant="asym", mean_shift=0.4), _lanes2(1184, 2, 16, 8, 5, batch=2),
+          _lanes2(4096, 2, 16, 16, 16, x_dtype="bf16"), _lanes2(4064, 2, 16, 16, 16, act_quant="asym")]
+
+
+@pytest.mark.parametrize("w", LANES2, ids=[w.name for w in LANES2])
+def test_grid_blocks_by_lanes(w):
+    import torch
+    import paper_2510_26771_amd as st
+    tl.full_case(w, with_bias=True, check_unfused=False, engines=("fp6",), routes=("direct",))
+    inp = tl.make_inputs(w)
+    plan = st.StampPlan(tl.plan_desc_for(w, "f32"), torch.from_numpy(inp["W"]).cuda())
+    X = tl.to_device_x(inp, w)
+    Y = [torch.empty((w.batch, w.seq_len, w.d_out), dtype=torch.float32, device="cuda") for _ in range(2)]
+    for packed in (0, 1):
+        plan.set_choice("operands", packed)
+        plan.linear_forward(X, Y[packed], plan.alloc_workspace())
+    torch.cuda.synchronize()
+    assert torch.equal(Y[0], Y[1])
+    plan.destroy()
+
+
 # ---- rows by lanes: four, two and one of them to a workgroup, the widths on either side; rows and 8-bit rows that are no multiple
 # of that; a last wave that is partly empty; the smallest; all rows at 8 bits; rows of the general path
 def _rows(d, s, batch, k, xform="identity", **kw):
