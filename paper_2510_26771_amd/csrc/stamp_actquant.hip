@@ -13,7 +13,7 @@
 // clamp(rne(fl(T * inv)) + z, 0, qmax), stored as code - 2^(b-1).  This file is compiled with
 // -ffp-contract=off.
 //
-// Kernels:
+// Kernels (those that leave FP6 operands: stamp_lanes1d.hip, stamp_lanes2d.hip):
 //   k_bottom1d / k_bottom2d  one workgroup per (sequence, block of R tokens), all d_in channels;
 //                            each thread owns 8 channels for every token of the block, so the
 //                            butterflies stay in registers; only the per-row absmax crosses lanes
@@ -290,13 +290,12 @@ __global__ __launch_bounds__(256) void k_quant_rows(const void* __restrict__ X, 
 namespace {
 Hi6Out hi6_out(const StampDirect* dir) { return dir != nullptr ? dir->hi : Hi6Out{}; }
 template <bool BF16, bool ASYM>
-void launch_quant_rows(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, const StampDirect* dir, hipStream_t st) {
+hipError_t launch_quant_rows(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, const StampDirect* dir, hipStream_t st) {
   const StampGeom& g = p->geom;
   const size_t zoff = (size_t)g.B * g.s;
-  if (dir != nullptr)
-    (void)stamp_launch_lanes_rows(p, X, BF16, dir->a6, scales, dir->hi, st);
-  else
-    hipLaunchKernelGGL((k_quant_rows<BF16, ASYM>), dim3(g.s, g.B), dim3(256), 0, st, X, q_hi, q_lo, scales, g.s, g.d, g.k, p->Kpad, zoff);
+  if (dir != nullptr) return stamp_launch_lanes_rows(p, X, BF16, dir->a6, scales, dir->hi, st);
+  hipLaunchKernelGGL((k_quant_rows<BF16, ASYM>), dim3(g.s, g.B), dim3(256), 0, st, X, q_hi, q_lo, scales, g.s, g.d, g.k, p->Kpad, zoff);
+  return hipGetLastError();
 }
 }  // namespace
 
@@ -322,9 +321,8 @@ hipError_t stamp_launch_actquant_rag(const stamp_plan* p, const void* X, int8_t*
 // general path: per-token quantization of the transformed tokens T [B, s, d] fp32 (rows = STaMP slots)
 hipError_t stamp_launch_quant_rows_f32(const stamp_plan* p, const float* T, int8_t* q_hi, uint8_t* q_lo, float* scales,
                                        hipStream_t st, const StampDirect* dir) {
-  if (p->geom.asym) launch_quant_rows<false, true>(p, T, q_hi, q_lo, scales, dir, st);
-  else launch_quant_rows<false, false>(p, T, q_hi, q_lo, scales, dir, st);
-  return hipGetLastError();
+  return p->geom.asym ? launch_quant_rows<false, true>(p, T, q_hi, q_lo, scales, dir, st)
+                      : launch_quant_rows<false, false>(p, T, q_hi, q_lo, scales, dir, st);
 }
 
 bool stamp_top_in_bottom(const stamp_plan* p) {
@@ -349,14 +347,11 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
   const StampGeom& g = p->geom;
   if (g.ident) {
     if (!(part & 1)) return hipSuccess;
-    if (g.asym) {
-      if (g.x_bf16) launch_quant_rows<true, true>(p, X, q_hi, q_lo, scales, dir, st);
-      else launch_quant_rows<false, true>(p, X, q_hi, q_lo, scales, dir, st);
-    } else {
-      if (g.x_bf16) launch_quant_rows<true, false>(p, X, q_hi, q_lo, scales, dir, st);
-      else launch_quant_rows<false, false>(p, X, q_hi, q_lo, scales, dir, st);
-    }
-    return hipGetLastError();
+    if (g.asym)
+      return g.x_bf16 ? launch_quant_rows<true, true>(p, X, q_hi, q_lo, scales, dir, st)
+                      : launch_quant_rows<false, true>(p, X, q_hi, q_lo, scales, dir, st);
+    return g.x_bf16 ? launch_quant_rows<true, false>(p, X, q_hi, q_lo, scales, dir, st)
+                    : launch_quant_rows<false, false>(p, X, q_hi, q_lo, scales, dir, st);
   }
   if (dir != nullptr && dir->parts) {
     const hipError_t e = stamp_launch_lanes1d(p, 3, X, dir->a6, scales, abot, StampHiOut{}, st);

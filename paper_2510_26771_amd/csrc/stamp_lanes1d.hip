@@ -534,7 +534,9 @@ hipError_t stamp_launch_lanes_rows(const stamp_plan* p, const void* X, int x_bf1
   a.zeros_off = (size_t)g.B * g.s;
   a.hi6 = hi;
   const int rows = g.B * g.s;
-  const int n = g.d <= 8192 ? 4 : (g.d <= 16384 ? 2 : 1);  // as many rows as 1024 threads hold
+  // as many rows as 1024 threads hold, two where four leave CUs without a workgroup (WHT of 256 x 1312, layer to 512: 34.4 with four, 33.5;
+  // 1024 x 4096 55.4, 55.5, 2048 x 4096 66.0, 67.0)
+  const int n = g.d <= 8192 && rows > 2 * stamp_device_cus() ? 4 : (g.d <= 16384 ? 2 : 1);
   if (n == 4) x_bf16 ? launch_rows<4, true>(g.asym, a, rows, st) : launch_rows<4, false>(g.asym, a, rows, st);
   else if (n == 2) x_bf16 ? launch_rows<2, true>(g.asym, a, rows, st) : launch_rows<2, false>(g.asym, a, rows, st);
   else x_bf16 ? launch_rows<1, true>(g.asym, a, rows, st) : launch_rows<1, false>(g.asym, a, rows, st);

@@ -132,7 +132,7 @@ def _rows(d, s, batch, k, xform="identity", **kw):
 ROWS = [_rows(32, 3, 1, 1), _rows(96, 131, 3, 5, x_dtype="bf16"), _rows(544, 37, 2, 0, act_quant="asym", mean_shift=0.4),
         _rows(2080, 130, 1, 33, x_dtype="bf16", act_quant="asym"), _rows(8192, 21, 1, 4, x_dtype="bf16"), _rows(8224, 21, 1, 4, x_dtype="bf16"),
         _rows(8224, 19, 1, 3, act_quant="asym", mean_shift=0.4), _rows(16384, 7, 3, 2), _rows(16416, 5, 3, 2), _rows(16416, 5, 3, 2, x_dtype="bf16"),
-        _rows(96, 4100, 2, 16, x_dtype="bf16"), _rows(160, 64, 3, 5, xform="wht"), _rows(1056, 33, 3, 2, xform="dct", act_quant="asym", x_dtype="bf16")]
+        _rows(96, 4100, 2, 16, x_dtype="bf16"), _rows(1056, 1030, 1, 7, act_quant="asym", mean_shift=0.4), _rows(8192, 517, 1, 4), _rows(160, 64, 3, 5, xform="wht"), _rows(1056, 33, 3, 2, xform="dct", act_quant="asym", x_dtype="bf16")]
 
 
 @pytest.mark.parametrize("w", ROWS, ids=[w.name for w in ROWS])
