@@ -323,6 +323,11 @@ typedef enum {
 } stamp_route_t;
 int32_t stamp_debug_routes(const stamp_plan_t* plan);
 
+/* For tests, on the host alone: how a plan's workspace is laid out.  out[0] = stamp_plan_workspace_bytes, out[1] =
+ * stamp_debug_routes, out[2] .. out[4] = offset of the 8-bit rows' FP6 operand in stamp_linear_forward, its bytes, and the bytes that
+ * are free there.  relaid = 1: of a plan laid out again (stamp_plan_set_unfused) while STAMP_GEMM_INT8 was selected. */
+stamp_status_t stamp_debug_layout(const stamp_plan_desc_t* desc, int32_t relaid, size_t* out);
+
 /* Measurement aid (not part of the layer): the rate, in 1e12 operations per second, that the matrix
  * pipeline of `engine` sustains on the current device over pseudo-random 4-bit codes held in registers,
  * with no memory traffic: the ceiling that the GEMM of that engine can approach on such values (it

@@ -24,7 +24,7 @@ EXPORTS = ["stamp_plan_create", "stamp_plan_destroy", "stamp_plan_workspace_byte
            "stamp_plan_row_of_coeff",
            "stamp_quantize_act", "stamp_linear_forward", "stamp_linear_forward_static", "stamp_linear_forward_q", "stamp_inverse",
            "stamp_debug_gemm_acc", "stamp_debug_weight_codes", "stamp_debug_run_stage", "stamp_plan_set_unfused", "stamp_plan_set_gemm_engine",
-           "stamp_debug_set_choice", "stamp_debug_routes", "stamp_debug_mfma_rate", "stamp_status_string"]
+           "stamp_debug_set_choice", "stamp_debug_routes", "stamp_debug_layout", "stamp_debug_mfma_rate", "stamp_status_string"]
 
 # stamp_choice_t and stamp_route_t (include/stamp.h)
 CHOICES = {"hi_rows": 0, "operands": 1}
@@ -130,6 +130,8 @@ def load_library():
     lib.stamp_debug_set_choice.restype = C.c_int
     lib.stamp_debug_routes.argtypes = [vp]
     lib.stamp_debug_routes.restype = i32
+    lib.stamp_debug_layout.argtypes = [C.POINTER(_Desc), i32, C.POINTER(sz)]
+    lib.stamp_debug_layout.restype = C.c_int
     lib.stamp_debug_mfma_rate.argtypes = [i32, C.POINTER(C.c_double)]
     lib.stamp_debug_mfma_rate.restype = C.c_int
     lib.stamp_status_string.argtypes = [C.c_int]

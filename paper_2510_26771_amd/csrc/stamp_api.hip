@@ -281,7 +281,7 @@ void place_parts(stamp_plan* p) {
   const int64_t elems = (int64_t)g.B * g.s * g.d;
   if (elems > (g.r >= 6 ? 1 << 25 : 1 << 24) || g.d < 192 || (g.d <= 512 && g.B * g.k >= 128)) return;
   if (g.ident || g.is2d || g.L == 0 || g.r < 4 || g.r > 6 || g.s < 128 || g.s > 4096 || g.d > 8192 || !stamp_lanes1d_fits(p, 3)) return;
-  const StampHiTiles ht = stamp_hi_tiles(p, 0);
+  const StampHiTiles ht = p->parts_tiles = stamp_hi_tiles(p, 0);
   if (!ht.on && !p->hi6[0]) return;
   const size_t end = p->ws_abot + align256((size_t)g.B * (g.s / 8) * g.d * sizeof(float));
   const size_t hi = ht.on ? stamp_hi_tiles_bytes(p) : stamp_hi6_bytes(p, 0);
@@ -367,6 +367,25 @@ void layout_workspace(stamp_plan* p) {
   place_parts(p);
 }
 
+// everything of a new plan that needs no device
+void init_plan(stamp_plan* p, const stamp_plan_desc_t* desc, const StampGeom& g, int fused_ok, const StampGen& gen) {
+  memset(p, 0, sizeof(*p));
+  p->desc = *desc;
+  p->geom = g;
+  p->gen = gen;
+  p->fused_ok = fused_ok && (g.ident || g.N % 2 == 0);  // the fused inverse stores pairs of columns: even d_out
+  p->unfused = 0;
+  p->engine = STAMP_GEMM_FP6;
+  p->Kpad = ((g.d + 127) / 128) * 128;
+  p->Npad = ((g.N + 255) / 256) * 256;
+  p->Mpad = ((g.B * g.s + 255) / 256) * 256;
+  p->hi_ksplit = gen.group ? 1 : stamp_hi_ksplit(p, g.k);
+  p->hi_ksplit_own = gen.group ? 1 : stamp_hi_ksplit(p, g.khi);
+  rag_geometry(p);
+  grp_geometry(p);
+  layout_workspace(p);
+}
+
 inline bool ws_ok(const stamp_plan* p, const void* ws, size_t bytes, size_t need) {
   (void)p;
   return ws != nullptr && (reinterpret_cast<uintptr_t>(ws) & 255) == 0 && bytes >= need;
@@ -401,23 +420,31 @@ inline hipError_t convert_rows(const stamp_plan* p, const int8_t* q_hi, const ui
   return stamp_launch_repack6(p, q_lo, a6, st, &hp);
 }
 
-// The 8-bit rows' operand in the tiles of the 4-bit rows, when it is converted from codes (hi.ht.on: the plan takes them along and
-// there is room): over the quantizer's scratch, or over the block sums and their parts, which that form does not have.
-inline StampHiOut tiles_operand(const stamp_plan* p, int own, void* ws) {
-  StampHiTiles ht = stamp_hi_tiles(p, own);
-  size_t off = p->ws_abot;
+// Where a call keeps the FP6 operand of the 8-bit rows: its form, and what is free there.
+struct HiPlace {
+  StampHiTiles ht;
+  size_t off, bytes, room;
+};
+inline size_t hi_place_bytes(const stamp_plan* p, const StampHiTiles& ht, int own) { return ht.on ? stamp_hi_tiles_bytes(p) : stamp_hi6_bytes(p, own); }
+
+// Converted from codes: in the tiles of the 4-bit rows (ht.on: the plan takes them along and there is room) over the quantizer's
+// scratch, or over the block sums and their parts, which that form does not have; else for the rows' own kernel (place_hi6).
+inline HiPlace converted_place(const stamp_plan* p, int own) {
+  StampHiTiles ht = p->engine == STAMP_GEMM_FP6 ? stamp_hi_tiles(p, own) : StampHiTiles{};
+  const bool gen = p->gen.kind != kGenNone;
+  const size_t scratch = gen ? p->ws_T[2] : p->ws_abot, room = gen ? p->ws_Yt[0] - p->ws_T[2] : p->ws_qhi - p->ws_abot;
   if (ht.on) {
-    const size_t need = stamp_hi_tiles_bytes(p);
-    if (p->rag.on) {
-      off = p->ws_T[2];
-      ht.on = need <= p->ws_Yt[0] - p->ws_T[2];
-    } else if (need > p->ws_qhi - p->ws_abot) {
-      off = p->ws_ythi;
-      ht.on = need <= p->ws_a6 - p->ws_ythi;
-    }
+    const size_t need = stamp_hi_tiles_bytes(p), ythi = gen ? 0 : p->ws_a6 - p->ws_ythi;
+    if (need <= room) return {ht, scratch, need, room};
+    if (need <= ythi) return {ht, p->ws_ythi, need, ythi};
+    ht.on = 0;
   }
-  return stamp_hi6_out(p, at(ws, off), own, ht);
+  return {ht, p->ws_hi6, stamp_hi6_bytes(p, own), p->ws_hi6 >= p->ws_base ? p->ws_total - p->ws_hi6 : room};
 }
+inline StampHiOut hi_operand(const stamp_plan* p, const HiPlace& place, int own, void* ws) {
+  return stamp_hi6_out(p, at(ws, place.off), own, place.ht);
+}
+inline StampHiOut tiles_operand(const stamp_plan* p, int own, void* ws) { return hi_operand(p, converted_place(p, own), own, ws); }
 
 // Blocked form of the 1-D Haar transform of any length (rules: rag_geometry): block sums from the 8-bit rows, then the
 // 4-bit rows' GEMM with the inverse in its epilogue writes Y.  Y has to be aligned for its vector stores.
@@ -615,10 +642,16 @@ bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
 }
 
 // Written by the quantizer itself the 8-bit rows' operand lies over the packed codes.
-StampHiOut direct_operand(const stamp_plan* p, int own, void* ws) {
+inline HiPlace direct_place(const stamp_plan* p, int own) {
   StampHiTiles ht = stamp_hi_tiles(p, own);
-  if (ht.on && stamp_hi_tiles_bytes(p) > p->ws_scales - p->ws_qhi) ht.on = 0;
-  return stamp_hi6_out(p, at(ws, p->ws_qhi), own, ht);
+  const size_t room = p->ws_scales - p->ws_qhi;
+  if (ht.on && stamp_hi_tiles_bytes(p) > room) ht.on = 0;
+  return {ht, p->ws_qhi, hi_place_bytes(p, ht, own), room};
+}
+// Blocks in parts of 8 tokens: place and form are the layout's (place_parts).
+inline HiPlace parts_place(const stamp_plan* p) {
+  const size_t off = p->ws_parts_hi;
+  return {p->parts_tiles, off, hi_place_bytes(p, p->parts_tiles, 0), (off >= p->ws_base ? p->ws_total : off >= p->ws_ythi ? p->ws_a6 : p->ws_scales) - off};
 }
 
 // stamp_linear_forward, plans with top levels whose bottom kernel leaves packed codes: their conversion shares the launch of
@@ -629,6 +662,23 @@ bool convert_beside_top(const stamp_plan* p) {
   const StampGeom& g = p->geom;
   return p->direct_ok && p->engine == STAMP_GEMM_FP6 && p->dbg[STAMP_CHOICE_OPERANDS] != 1 && p->gen.kind == kGenNone && !g.ident && p->fused_ok && !p->unfused && g.L > 0 &&
          p->hi6[0] && (int64_t)g.B * g.k <= 4096;
+}
+
+// what stamp_linear_forward does for these tensors
+struct ForwardRoute {
+  bool direct, beside, parts;
+  int own;
+  HiPlace hi;
+};
+ForwardRoute forward_route(const stamp_plan* p, const void* X, const void* Y) {
+  ForwardRoute r = {};
+  r.own = own_top(p);
+  r.direct = direct_route(p, X, Y);
+  r.beside = !r.direct && convert_beside_top(p);
+  r.parts = r.direct && p->ws_parts_hi != 0;
+  // (beside: written when the packed codes have been converted, over them)
+  r.hi = r.parts ? parts_place(p) : r.direct || r.beside ? direct_place(p, r.own) : converted_place(p, r.own);
+  return r;
 }
 
 }  // namespace
@@ -661,21 +711,7 @@ stamp_status_t stamp_plan_create(const stamp_plan_desc_t* desc, const void* W_de
 
   stamp_plan* p = new (std::nothrow) stamp_plan;
   if (p == nullptr) return STAMP_ERR_ALLOC;
-  memset(p, 0, sizeof(*p));
-  p->desc = *desc;
-  p->geom = g;
-  p->gen = gen;
-  p->fused_ok = fused_ok && (g.ident || g.N % 2 == 0);  // the fused inverse stores pairs of columns: even d_out
-  p->unfused = 0;
-  p->engine = STAMP_GEMM_FP6;
-  p->Kpad = ((g.d + 127) / 128) * 128;
-  p->Npad = ((g.N + 255) / 256) * 256;
-  p->Mpad = ((g.B * g.s + 255) / 256) * 256;
-  p->hi_ksplit = gen.group ? 1 : stamp_hi_ksplit(p, g.k);
-  p->hi_ksplit_own = gen.group ? 1 : stamp_hi_ksplit(p, g.khi);
-  rag_geometry(p);
-  grp_geometry(p);
-  layout_workspace(p);
+  init_plan(p, desc, g, fused_ok, gen);
 
   // physical row of every STaMP slot
   p->row_of_coeff = static_cast<int32_t*>(malloc(sizeof(int32_t) * (size_t)g.s));
@@ -802,10 +838,34 @@ int32_t stamp_debug_routes(const stamp_plan_t* p) {
     else if (!own && stamp_hi_top_fused(p)) r |= STAMP_ROUTE_HI_TOP_FUSED;
     else if ((own ? p->hi_ksplit_own : p->hi_ksplit) > 1) r |= STAMP_ROUTE_HI_SPLIT;
   }
-  if (stamp_hi_tiles(p, own).on) r |= STAMP_ROUTE_HI_IN_TILES;
+  if (p->engine == STAMP_GEMM_FP6 && stamp_hi_tiles(p, own).on) r |= STAMP_ROUTE_HI_IN_TILES;
   const int M = rag ? (g.B * p->rag.nb) << p->rag.r : g.B * g.s;
   if (p->engine == STAMP_GEMM_FP6 && stamp_gemm6_half_tiles(M, p->Npad)) r |= STAMP_ROUTE_TILES_128;
   return r;
+}
+
+stamp_status_t stamp_debug_layout(const stamp_plan_desc_t* desc, int32_t relaid, size_t* out) {
+  if (desc == nullptr || out == nullptr) return STAMP_ERR_NULL;
+  StampGeom g;
+  int fused_ok = 0;
+  StampGen gen;
+  const stamp_status_t vs = validate(desc, &g, &fused_ok, &gen);
+  if (vs != STAMP_OK) return vs;
+  stamp_plan p;
+  init_plan(&p, desc, g, fused_ok, gen);
+  if (relaid) {
+    (void)stamp_plan_set_gemm_engine(&p, STAMP_GEMM_INT8);
+    (void)stamp_plan_set_unfused(&p, 0);
+    (void)stamp_plan_set_gemm_engine(&p, STAMP_GEMM_FP6);
+  }
+  const void* const aligned = reinterpret_cast<const void*>((uintptr_t)256);
+  const HiPlace hi = forward_route(&p, aligned, aligned).hi;
+  out[0] = p.ws_total;
+  out[1] = (size_t)stamp_debug_routes(&p);
+  out[2] = hi.off;
+  out[3] = hi.bytes;
+  out[4] = hi.room;
+  return STAMP_OK;
 }
 
 stamp_status_t stamp_plan_row_of_coeff(const stamp_plan_t* p, int32_t* host_out) {
@@ -846,24 +906,15 @@ stamp_status_t stamp_linear_forward(const stamp_plan_t* p, const void* X, void* 
   int8_t* q_hi = reinterpret_cast<int8_t*>(at(ws, p->ws_qhi));
   uint8_t* q_lo = at(ws, p->ws_qlo);
   float* scales = reinterpret_cast<float*>(at(ws, p->ws_scales));
+  const ForwardRoute route = forward_route(p, X, Y);
   StampDirect dir = {};
-  const bool direct = direct_route(p, X, Y);
-  if (direct) {
+  if (route.direct || route.beside) {
     dir.a6 = at(ws, p->rag.on ? p->ws_ba6 : p->ws_a6);
-    dir.hi = direct_operand(p, own_top(p), ws);
+    dir.hi = hi_operand(p, route.hi, route.own, ws);
+    dir.lo_packed = route.beside;
+    dir.parts = route.parts;
   }
-  const bool beside = !direct && convert_beside_top(p);
-  if (beside) {
-    // the 8-bit rows' operand is written when the packed codes have been converted, over them
-    dir.a6 = at(ws, p->ws_a6);
-    dir.hi = direct_operand(p, 0, ws);
-    dir.lo_packed = 1;
-  }
-  if (direct && p->ws_parts_hi != 0) {
-    dir.parts = 1;
-    dir.hi = stamp_hi6_out(p, at(ws, p->ws_parts_hi), 0, stamp_hi_tiles(p, 0));
-  }
-  const StampDirect* const dp = direct || beside ? &dir : nullptr;
+  const StampDirect* const dp = route.direct || route.beside ? &dir : nullptr;
   if (p->gen.kind != kGenNone) {
     if (p->gen.group) {
       q_hi = reinterpret_cast<int8_t*>(at(ws, p->ws_codes8));

@@ -294,7 +294,7 @@ StampHiTiles stamp_hi_tiles(const stamp_plan* p, int own) {
   StampHiTiles t = {};
   const bool rag = p->rag.on;
   const StampGeom& g = rag ? p->bgeom : p->geom;
-  if (p->engine != STAMP_GEMM_FP6 || p->gen.group != 0 || p->dbg[STAMP_CHOICE_HI_ROWS] != 0) return t;
+  if (p->gen.group != 0 || p->dbg[STAMP_CHOICE_HI_ROWS] != 0) return t;
   if (!rag && (p->gen.kind != kGenNone || g.ident || !p->fused_ok || p->unfused)) return t;
   const int rl = g.is2d ? 2 * g.r : g.r, khi = own || rag ? g.khi : g.k, L = rag ? 0 : g.L;
   if (rl < 3 || rl > 6 || khi < 1 || (g.is2d && L > 0) || g.d > 18720) return t;  // 128 * 7 * 18720 < 2^24

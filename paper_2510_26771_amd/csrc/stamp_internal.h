@@ -247,7 +247,9 @@ struct stamp_plan {
   // the 8-bit rows through the kernel for few rows (stamp_hi6.hip), [1]: only the first khi rows of every sequence
   int32_t hi6[2];
   size_t ws_hi6;            // their operand
-  size_t ws_parts_hi;       // the same where blocks are quantized in parts of 8 tokens; 0: they are not
+  // the same where blocks are quantized in parts of 8 tokens, 0: they are not; in which form (the layout's room is for that one)
+  size_t ws_parts_hi;
+  StampHiTiles parts_tiles;
   int32_t direct_ok;        // the quantizer may write the FP6 operands itself (the 8-bit rows' over ws_qhi)
   int32_t dbg[STAMP_CHOICE_COUNT];  // stamp_debug_set_choice: 0 by rule, 1 / 2 the one or the other form
   size_t ws_ba6, ws_bP;     // blocked form: the 4-bit rows in block order (over ws_T), the block sums (over ws_Yt)
@@ -344,7 +346,8 @@ size_t stamp_hi6_bytes(const stamp_plan* p, int own);
 // the operand at `a6`; ht: in the tiles' places instead
 StampHiOut stamp_hi6_out(const stamp_plan* p, uint8_t* a6, int own, const StampHiTiles& ht);
 StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own, const StampHiTiles& ht);
-// whether the 4-bit rows' GEMM takes the 8-bit rows along (ht.on), and the bytes of their operand
+// whether the 4-bit rows' GEMM (FP6 engine: the layout does not depend on the engine, callers ask for it) takes the 8-bit
+// rows along (ht.on), and the bytes of their operand
 StampHiTiles stamp_hi_tiles(const stamp_plan* p, int own);
 size_t stamp_hi_tiles_bytes(const stamp_plan* p);
 hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float* scales, int mode, void* out, int ld_out, int own,

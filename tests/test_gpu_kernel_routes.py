@@ -444,6 +444,31 @@ def test_blocks_in_parts(w):
     plan.destroy()
 
 
+@pytest.mark.parametrize("w", [_parts(512, 9, 8, d=512, d_out=512), _parts(4096, 12, 64, d=1024, d_out=1024)], ids=lambda w: w.name)
+def test_parts_after_a_layout_under_the_int8_engine(w):
+    """A plan that was laid out again while the other engine was selected gives what a new one gives, in the same workspace."""
+    import torch
+    import paper_2510_26771_amd as st
+    inp = tl.make_inputs(w)
+    X, out = tl.to_device_x(inp, w), []
+    for relaid in (False, True):
+        plan = st.StampPlan(tl.plan_desc_for(w, "f32"), torch.from_numpy(inp["W"]).cuda())
+        if relaid:
+            plan.set_gemm_engine("int8")
+            plan.set_unfused(False)
+            plan.set_gemm_engine("fp6")
+        tl.check_routes(plan, w, ("parts", "hi_in_tiles"))
+        n = plan.workspace_bytes()
+        ws = torch.full((n + 65536,), 0x5A, dtype=torch.uint8, device="cuda")
+        Y = torch.empty((w.batch, w.seq_len, w.d_out), dtype=torch.float32, device="cuda")
+        plan.linear_forward(X, Y, ws[:n])
+        torch.cuda.synchronize()
+        assert (ws[n:] == 0x5A).all(), "writes behind the workspace"
+        out.append((n, Y))
+        plan.destroy()
+    assert out[0][0] == out[1][0] and torch.equal(out[0][1], out[1][1])
+
+
 # ---- the 8-bit rows in the tiles of the 4-bit rows' GEMM: every block length, sub-trees above, below and beside the tile's, several
 # sequences per tile, partial depths, 4-bit sums beside 8-bit ones, the token left out in its own tile and in the next, a
 # last tile that is partly empty, grids; against the oracle, and bit for bit against the rows' own kernel
