@@ -838,7 +838,8 @@ int32_t stamp_debug_routes(const stamp_plan_t* p) {
     else if (!own && stamp_hi_top_fused(p)) r |= STAMP_ROUTE_HI_TOP_FUSED;
     else if ((own ? p->hi_ksplit_own : p->hi_ksplit) > 1) r |= STAMP_ROUTE_HI_SPLIT;
   }
-  if (p->engine == STAMP_GEMM_FP6 && stamp_hi_tiles(p, own).on) r |= STAMP_ROUTE_HI_IN_TILES;
+  if (forward_route(p, aligned, aligned).hi.ht.on) r |= STAMP_ROUTE_HI_IN_TILES;
+  if (converted_place(p, 0).ht.on) r |= STAMP_ROUTE_Q_HI_IN_TILES;
   const int M = rag ? (g.B * p->rag.nb) << p->rag.r : g.B * g.s;
   if (p->engine == STAMP_GEMM_FP6 && stamp_gemm6_half_tiles(M, p->Npad)) r |= STAMP_ROUTE_TILES_128;
   return r;

@@ -471,7 +471,8 @@ def test_parts_after_a_layout_under_the_int8_engine(w):
 
 # ---- the 8-bit rows in the tiles of the 4-bit rows' GEMM: every block length, sub-trees above, below and beside the tile's, several
 # sequences per tile, partial depths, 4-bit sums beside 8-bit ones, the token left out in its own tile and in the next, a
-# last tile that is partly empty, grids; against the oracle, and bit for bit against the rows' own kernel
+# last tile that is partly empty, grids; against the oracle, and bit for bit against the rows' own kernel.  (Codes that were
+# converted need room for the operand beside them, blocks of 64 tokens d_out accordingly: r6_one, r6_own.)
 def _hit(name, **kw):
     base = dict(d_in=160, d_out=132, k_hi=8, seed=700 + len(name))
     base.update(kw)
@@ -483,20 +484,24 @@ HIT = [_hit("r3_own", batch=3, seq_len=512, levels=3, k_hi=20, x_dtype="bf16"), 
        _hit("r4_full", batch=3, seq_len=1024, levels=10, k_hi=64, act_quant="asym", mean_shift=0.4), _hit("r4_k256", seq_len=4096, levels=12, k_hi=256, x_dtype="bf16"),
        _hit("r4_partial", batch=2, seq_len=1024, levels=8, k_hi=64), _hit("r4_below_tile", batch=2, seq_len=512, levels=6, k_hi=32),
        _hit("r5_full", batch=2, seq_len=1024, levels=10, k_hi=32, x_dtype="bf16"), _hit("r5_tiles_and_more", seq_len=256, levels=8, k_hi=8, d_out=700),
-       _hit("r6_full", batch=2, seq_len=2048, levels=11, k_hi=32, d_in=416), _hit("r6_one", batch=3, seq_len=64, levels=6, k_hi=1),
-       _hit("r6_own", batch=2, seq_len=1024, levels=6, k_hi=5, act_quant="asym", mean_shift=0.4),
+       _hit("r6_full", batch=2, seq_len=2048, levels=11, k_hi=32, d_in=416), _hit("r6_one", batch=3, seq_len=64, levels=6, k_hi=1, d_out=700),
+       _hit("r6_own", batch=2, seq_len=1024, levels=6, k_hi=5, d_out=700, act_quant="asym", mean_shift=0.4),
        _hit("grid4", batch=3, seq_len=256, grid_h=16, grid_w=16, xform="haar2d", levels=2, k_hi=16, corr_len=4.0),
        _hit("grid8_own", batch=2, seq_len=1024, grid_h=32, grid_w=32, xform="haar2d", levels=3, k_hi=7, corr_len=4.0, x_dtype="bf16"),
        _rag(3, 1000, 1, k_hi=17, d_out=131), _rag(3, 1000, 1, k_hi=16, d_out=130, batch=2), _rag(3, 401, 1, k_hi=9, batch=3, act_quant="asym", mean_shift=0.3),
        _rag(4, 402, 1, k_hi=20, batch=3, x_dtype="bf16"), _rag(5, 999, 0, k_hi=32, batch=2), _rag(6, 1500, 1, k_hi=3, d_out=65)]
 
 
+HIT_NO_ROOM_Q = ("hit_r6_full", "hit_grid8_own")  # linear_forward_q runs the rows' own kernel
+
+
 @pytest.mark.parametrize("w", HIT, ids=[w.name for w in HIT])
 def test_8bit_rows_in_the_tiles(w):
     import torch
     import paper_2510_26771_amd as st
+    by_rule = ("hi_in_tiles", "-q_hi_in_tiles" if w.name in HIT_NO_ROOM_Q else "q_hi_in_tiles")
     for y in ("f32", "bf16"):
-        tl.full_case(w, with_bias=True, check_unfused=False, engines=("fp6",), y_dtype=y, routes=("hi_in_tiles",))
+        tl.full_case(w, with_bias=True, check_unfused=False, engines=("fp6",), y_dtype=y, routes=by_rule)
     inp = tl.make_inputs(w, with_bias=True)
     plan = st.StampPlan(tl.plan_desc_for(w, "f32"), torch.from_numpy(inp["W"]).cuda(), torch.from_numpy(inp["bias"]).cuda())
     X = tl.to_device_x(inp, w)
@@ -506,9 +511,11 @@ def test_8bit_rows_in_the_tiles(w):
     for choice in (0, 2):  # by rule; the kernel of their own
         plan.set_choice("hi_rows", choice)
         # (the rows' own kernel takes up to 128 of a sequence through their top levels, the int8 pipeline more: same sums)
-        tl.check_routes(plan, w, ("hi_in_tiles",) if choice == 0 else ("-hi_in_tiles",) + (("hi_fp6",) if w.k_hi <= 128 else ()))
+        tl.check_routes(plan, w, by_rule if choice == 0 else ("-hi_in_tiles", "-q_hi_in_tiles") + (("hi_fp6",) if w.k_hi <= 128 else ()))
         for operands in (0, 1):
             plan.set_choice("operands", operands)
+            if choice == 0 and w.name not in HIT_NO_ROOM_Q:
+                tl.check_routes(plan, w, by_rule)  # packed codes (operands 1) are converted as those of linear_forward_q
             Y, Yq = (torch.zeros((w.batch, w.seq_len, w.d_out), dtype=torch.float32, device="cuda") for _ in range(2))
             ws = plan.alloc_workspace()
             plan.linear_forward(X, Y, ws)

@@ -70,5 +70,5 @@ def test_operand_of_the_8bit_rows_fits_its_place(lib):
         routes |= fresh["routes"]
         assert fresh["bytes"] <= fresh["room"] and fresh["off"] + fresh["bytes"] <= fresh["total"], desc
         assert _layout(lib, desc, 1) == (0, fresh), desc
-    for name in ("general", "any_length_blocks", "direct", "beside_top", "hi_fp6", "tiles_128", "hi_in_tiles", "parts"):
+    for name in ("general", "any_length_blocks", "direct", "beside_top", "hi_fp6", "tiles_128", "hi_in_tiles", "q_hi_in_tiles", "parts"):
         assert routes & binding.ROUTES[name], name
