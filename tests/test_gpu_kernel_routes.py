@@ -89,8 +89,9 @@ def test_blocks_by_lanes(w):
     plan.destroy()
 
 
-# ---- blocks of a token grid by lanes: the widths of one wave, of several and the widest, a last wave that is partly empty, grids that
-# are no square, blocks whose sums are 8-bit rows, 4-bit rows or go to levels above
+# ---- blocks of a token grid by lanes: the widths of one wave, of several and the widest, a last wave that is partly empty, blocks
+# whose sums are 8-bit rows, 4-bit rows (k_hi below the approximations; both block sizes and code forms) or go to levels above; grids
+# that are no square, which run level by level and then by rows
 def _lanes2(d, levels, gh, gw, k, batch=1, **kw):
     base = dict(xform="haar2d", grid_h=gh, grid_w=gw, seq_len=gh * gw, batch=batch, levels=levels, k_hi=k, d_in=d, d_out=66, seed=900 + d, corr_len=4.0)
     base.update(kw)
@@ -101,14 +102,16 @@ LANES2 = [_lanes2(32, 3, 16, 16, 4, x_dtype="bf16"), _lanes2(160, 3, 16, 32, 8, 
           _lanes2(1536, 3, 16, 16, 4, x_dtype="bf16", act_quant="asym"), _lanes2(1536, 3, 16, 16, 4), _lanes2(1184, 3, 32, 16, 5, batch=2),
           _lanes2(288, 4, 32, 32, 16, x_dtype="bf16"), _lanes2(1056, 4, 32, 32, 16, act_quant="asym", mean_shift=-0.3),
           _lanes2(32, 2, 16, 16, 16, batch=3, x_dtype="bf16"), _lanes2(544, 2, 8, 16, 8, act_quant="asym", mean_shift=0.4), _lanes2(1184, 2, 16, 8, 5, batch=2),
-          _lanes2(4096, 2, 16, 16, 16, x_dtype="bf16"), _lanes2(4064, 2, 16, 16, 16, act_quant="asym")]
+          _lanes2(4096, 2, 16, 16, 16, x_dtype="bf16"), _lanes2(4064, 2, 16, 16, 16, act_quant="asym"),
+          _lanes2(544, 2, 16, 16, 5, act_quant="asym", mean_shift=0.4), _lanes2(1184, 2, 16, 16, 5, batch=2, x_dtype="bf16"),
+          _lanes2(160, 3, 32, 32, 7, act_quant="asym", mean_shift=0.4), _lanes2(1184, 3, 32, 32, 5, batch=2)]
 
 
 @pytest.mark.parametrize("w", LANES2, ids=[w.name for w in LANES2])
 def test_grid_blocks_by_lanes(w):
     import torch
     import paper_2510_26771_amd as st
-    tl.full_case(w, with_bias=True, check_unfused=False, engines=("fp6",), routes=("direct",))
+    tl.full_case(w, with_bias=True, check_unfused=False, engines=("fp6",), routes=("direct", "-general" if w.grid_h == w.grid_w else "general"))
     inp = tl.make_inputs(w)
     plan = st.StampPlan(tl.plan_desc_for(w, "f32"), torch.from_numpy(inp["W"]).cuda())
     X = tl.to_device_x(inp, w)
@@ -490,7 +493,6 @@ HIT = [_hit("r3_own", batch=3, seq_len=512, levels=3, k_hi=20, x_dtype="bf16"), 
        _hit("grid8_own", batch=2, seq_len=1024, grid_h=32, grid_w=32, xform="haar2d", levels=3, k_hi=7, corr_len=4.0, x_dtype="bf16"),
        _rag(3, 1000, 1, k_hi=17, d_out=131), _rag(3, 1000, 1, k_hi=16, d_out=130, batch=2), _rag(3, 401, 1, k_hi=9, batch=3, act_quant="asym", mean_shift=0.3),
        _rag(4, 402, 1, k_hi=20, batch=3, x_dtype="bf16"), _rag(5, 999, 0, k_hi=32, batch=2), _rag(6, 1500, 1, k_hi=3, d_out=65)]
-
 
 HIT_NO_ROOM_Q = ("hit_r6_full", "hit_grid8_own")  # linear_forward_q runs the rows' own kernel
 
