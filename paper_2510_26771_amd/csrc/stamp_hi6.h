@@ -41,10 +41,17 @@ __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
   int row;
   uint8_t* dst;
   if (o.ht.on) {
-    const int tile = m / kHiPlaces, place = m - tile * kHiPlaces;
-    int b, up;
-    const int slot = stamp_hi_slot_of_place(o.ht, hp.nseq, tile, place, &b, &up);
-    if (slot < 0) return;  // (a place without a row may hold anything)
+    int b, slot, tile, place, n;
+    if (hp.places == 0) {
+      b = m / o.seq;
+      slot = m - b * o.seq;
+      stamp_hi_places(o.ht, b, slot, &tile, &n, &place);
+    } else {
+      tile = m / hp.places;
+      place = m - tile * hp.places;
+      slot = stamp_hi_slot_of_place(o.ht, hp.nseq, tile, place, &b, &n);
+      if (slot < 0) return;  // (a place without a row may hold anything)
+    }
     row = b * hp.seq_rows + slot;
     dst = o.p + ((size_t)tile * hp.KT + kt) * kBlock6 + (f & 1) * 512 + place * 16;
   } else {

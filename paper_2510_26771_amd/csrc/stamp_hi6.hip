@@ -331,7 +331,15 @@ StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6
   hp.KT = p->Kpad / 128;
   hp.nseq = g.B;
   const int gr = 32 * hp.out.np;  // (the rows' own kernel reads whole groups)
-  const int rows = ht.on ? ((g.B * ht.k + (1 << ht.lognb) - 1) >> ht.lognb) * kHiPlaces : (hp.M + gr - 1) / gr * gr;
+  // A thread converts 32 channels with some 1500 instructions, and a wave with a few of them takes as long as a full one: narrow layers
+  // have threads for the rows (no top levels: each has one place), or for the places that can hold one, the first of a
+  // tile.  Wide ones, where a place is whole waves, have them for all 16, which spreads those with work over more CUs.
+  // linear_forward_q, us, all 16 places against these: blocks of 64, 4 x 1024 x 64 -> 1024 18.8, 12.4 (the rows' own kernel 15.3), 8 x
+  // 1024 x 64 -> 256 16.8, 12.8; 16 x 200 x 128 -> 64, blocks of 16 16.5, 13.1.  Full depth, 16 against the 7 that can hold a row:
+  // 8 x 4096 x 1024 -> 256 33.7, 34.6, 4 x 4096 x 2048 -> 512 36.4, 37.3.
+  const bool narrow = p->Kpad <= 512;
+  hp.places = !narrow ? kHiPlaces : ht.L == 0 ? 0 : (1 << ht.lognb) + (ht.L > ht.lognb ? ht.L - ht.lognb : 0);
+  const int rows = !ht.on ? (hp.M + gr - 1) / gr * gr : hp.places == 0 ? hp.M : ((g.B * ht.k + (1 << ht.lognb) - 1) >> ht.lognb) * hp.places;
   hp.threads = rows * hp.KT * 4;
   return hp;
 }

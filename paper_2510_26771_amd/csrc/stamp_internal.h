@@ -336,6 +336,7 @@ struct StampHi6Pack {
   const int8_t* q_hi;
   StampHiOut out;
   int32_t M, seq_rows, nseq, d, KT, threads;  // rows, rows a sequence has in q_hi (it uses out.seq)
+  int32_t places;                             // of a tile that threads are launched for; 0: threads for the rows
 };
 hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_t* a6, hipStream_t st, const StampHi6Pack* hi = nullptr);
 // the 8-bit rows' GEMM on the FP6 pipeline (few rows), own: only the first khi rows of every sequence.  mode 0: block sums

@@ -492,7 +492,10 @@ HIT = [_hit("r3_own", batch=3, seq_len=512, levels=3, k_hi=20, x_dtype="bf16"), 
        _hit("grid4", batch=3, seq_len=256, grid_h=16, grid_w=16, xform="haar2d", levels=2, k_hi=16, corr_len=4.0),
        _hit("grid8_own", batch=2, seq_len=1024, grid_h=32, grid_w=32, xform="haar2d", levels=3, k_hi=7, corr_len=4.0, x_dtype="bf16"),
        _rag(3, 1000, 1, k_hi=17, d_out=131), _rag(3, 1000, 1, k_hi=16, d_out=130, batch=2), _rag(3, 401, 1, k_hi=9, batch=3, act_quant="asym", mean_shift=0.3),
-       _rag(4, 402, 1, k_hi=20, batch=3, x_dtype="bf16"), _rag(5, 999, 0, k_hi=32, batch=2), _rag(6, 1500, 1, k_hi=3, d_out=65)]
+       _rag(4, 402, 1, k_hi=20, batch=3, x_dtype="bf16"), _rag(5, 999, 0, k_hi=32, batch=2), _rag(6, 1500, 1, k_hi=3, d_out=65),
+       # codes converted by 16 places a tile: more than 512 channels, with and without top levels
+       _hit("r5_wide", batch=2, seq_len=1024, levels=10, k_hi=32, d_in=608, d_out=700), _hit("r4_wide_own", batch=3, seq_len=512, levels=4, k_hi=9, d_in=576)]
+
 
 HIT_NO_ROOM_Q = ("hit_r6_full", "hit_grid8_own")  # linear_forward_q runs the rows' own kernel
 
