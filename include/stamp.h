@@ -317,10 +317,8 @@ typedef enum {
   STAMP_ROUTE_TILES_128 = 256,        /* 4-bit rows in 128 x 256 tiles instead of 256 x 256 */
   STAMP_ROUTE_GROUP_QUANT = 512,      /* per-block scales on blocks of a token grid: transform and quantizer in one kernel */
   STAMP_ROUTE_HI_IN_TILES = 1024,     /* 8-bit rows in the tiles of the 4-bit rows' GEMM */
-  STAMP_ROUTE_Q_HI_IN_TILES = 8192,   /* the same in stamp_linear_forward_q, whose operand has a place of its own */
-  STAMP_ROUTE_PARTS = 2048,           /* blocks quantized in parts of 8 tokens, straight to FP6 operands */
-  STAMP_ROUTE_ROWS = 4096             /* rows without transform, straight to FP6 operands, more of them than STAMP_ROUTE_DIRECT
-                                         names: rows + 8-bit rows > 6144, or rows x depth > 3 x 2^22 */
+  STAMP_ROUTE_PARTS = 2048,           /* with STAMP_ROUTE_DIRECT: blocks quantized in parts of 8 tokens */
+  STAMP_ROUTE_Q_HI_IN_TILES = 4096    /* STAMP_ROUTE_HI_IN_TILES in stamp_linear_forward_q, whose operand has a place of its own */
 } stamp_route_t;
 int32_t stamp_debug_routes(const stamp_plan_t* plan);
 

@@ -31,7 +31,7 @@ CHOICES = {"hi_rows": 0, "operands": 1}
 ROUTES = {"general": 1, "any_length_blocks": 2, "group_blocks": 4, "direct": 8, "beside_top": 16, "hi_fp6": 32,
           "hi_top_fused": 64, "hi_split": 128, "tiles_128": 256,
           "group_quant": 512, "hi_in_tiles": 1024,
-          "parts": 2048, "rows": 4096, "q_hi_in_tiles": 8192}
+          "parts": 2048, "q_hi_in_tiles": 4096}
 
 
 class StampError(RuntimeError):

@@ -624,12 +624,6 @@ bool direct_pays(const stamp_plan* p) {
   if (g.is2d || stamp_lanes1d_fits(p, p->rag.on ? p->rag.r : g.r)) return rows + 16 * hi <= 140000 || 16 * hi <= rows;
   return rows + 16 * hi <= 140000 && rows * g.d <= (1 << 27);
 }
-// rows that STAMP_ROUTE_ROWS names, not STAMP_ROUTE_DIRECT
-bool many_rows(const stamp_plan* p) {
-  const StampGeom& g = p->geom;
-  const int64_t rows = (int64_t)g.B * g.s;
-  return g.ident && !p->rag.on && (rows + (int64_t)g.B * g.khi > 6144 || rows * g.d > (3 << 22));
-}
 bool direct_route(const stamp_plan* p, const void* X, const void* Y) {
   const StampGeom& g = p->geom;
   if (!p->direct_ok || p->engine != STAMP_GEMM_FP6 || p->gen.group || p->dbg[STAMP_CHOICE_OPERANDS] == 1) return false;
@@ -831,14 +825,16 @@ int32_t stamp_debug_routes(const stamp_plan_t* p) {
   if (p->grp) r |= STAMP_ROUTE_GROUP_BLOCKS;
   if (rag) r |= STAMP_ROUTE_ANY_LENGTH_BLOCKS;
   if (p->gen.group) return r;
-  if (direct_route(p, aligned, aligned)) r |= p->ws_parts_hi != 0 ? STAMP_ROUTE_PARTS : (many_rows(p) ? STAMP_ROUTE_ROWS : STAMP_ROUTE_DIRECT);
-  else if (convert_beside_top(p)) r |= STAMP_ROUTE_BESIDE_TOP;
+  const ForwardRoute fr = forward_route(p, aligned, aligned);
+  if (fr.direct) r |= STAMP_ROUTE_DIRECT;
+  if (fr.parts) r |= STAMP_ROUTE_PARTS;
+  if (fr.beside) r |= STAMP_ROUTE_BESIDE_TOP;
   if ((own ? g.khi : g.k) > 0) {
     if (p->hi6[own]) r |= STAMP_ROUTE_HI_FP6;
     else if (!own && stamp_hi_top_fused(p)) r |= STAMP_ROUTE_HI_TOP_FUSED;
     else if ((own ? p->hi_ksplit_own : p->hi_ksplit) > 1) r |= STAMP_ROUTE_HI_SPLIT;
   }
-  if (forward_route(p, aligned, aligned).hi.ht.on) r |= STAMP_ROUTE_HI_IN_TILES;
+  if (fr.hi.ht.on) r |= STAMP_ROUTE_HI_IN_TILES;
   if (converted_place(p, 0).ht.on) r |= STAMP_ROUTE_Q_HI_IN_TILES;
   const int M = rag ? (g.B * p->rag.nb) << p->rag.r : g.B * g.s;
   if (p->engine == STAMP_GEMM_FP6 && stamp_gemm6_half_tiles(M, p->Npad)) r |= STAMP_ROUTE_TILES_128;
