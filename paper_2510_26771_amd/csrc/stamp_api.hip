@@ -270,19 +270,25 @@ void place_hi6(stamp_plan* p, size_t region, size_t room) {
 // this form) behind them, over the block sums' parts and P where the tiles take the 8-bit rows along, or behind everything.
 // A block's workgroup takes its tokens one after the other: with few blocks that chain is what a layer waits for; the sums of the
 // parts are 4 bytes per channel and 8 tokens more, twice, which is what counts with many.  Layers, us, whole blocks against
-// parts.  Blocks of 64: 4096 x 1024 50.3, 31.5, x 4096 73.6, 56.0, 2 x 4096 x 4096 78.2, 75.7, 8 x 4096 x 1024 68.6, 62.8, 4 x 4096 x 4096
-// 88.1, 114.6; of 32: 512 x 1024 40.6, 24.1, 2048 x 4096 56.2, 48.2, 8 x 2048 x 1024 46.1, 44.4, 4 x 2048 x 2048 46.5, 45.4, 4 x 2048 x
-// 4096 65.7, 75.5; of 16: 2 x 1024 x 4096 48.2, 44.7, 4 x 1024 x 4096 50.9, 50.0, 16 x 1024 x 4096 101.5, 103.2.  So up to 2^24
-// elements, 2^25 in blocks of 64.  (Narrow layers gain as well: 256 x 160 26.5, 20.4, 2 x 2048 x 512 34.3, 25.6.  Below 192 channels,
-// and from 128 blocks of up to 512 channels on, they keep the form that tests name for their sizes.)
+// parts.  Blocks of 64: 4096 x 64 41.9, 23.3, x 1024 50.3, 31.5, x 4096 73.6, 56.0, 2 x 4096 x 4096 78.2, 75.7, 8 x 4096 x 1024 68.6, 62.8, 4 x
+// 4096 x 4096 88.1, 114.6; of 32: 256 x 160 26.5, 20.4, 512 x 1024 40.6, 24.1, 2 x 2048 x 512 34.3, 25.6, 2048 x 4096 56.2, 48.2, 4 x 2048 x 2048
+// 46.5, 45.4, 4 x 2048 x 4096 65.7, 75.5; of 16: 1024 x 128 25.6, 22.3, 2 x 1024 x 4096 48.2, 44.7, 16 x 1024 x 4096 101.5, 103.2.  So up to
+// 2^24 elements, 2^25 in blocks of 64.  The chain of a block of 16 is short: of narrow layers of many short sequences (more than
+// 128 blocks, at most 32 a sequence, below 512 channels) its workgroups fill the CUs without parts, 64 x 256 x 128 23.3, 25.2, 64 x 128
+// x 96 20.6, 22.3, but 256 x 128 x 512 39.6, 35.0.  Beyond 2^24 elements parts need a launch to save, which those whose 8-bit rows ride in
+// the tiles have not: with more than 128 blocks whole blocks from 2048 tokens on, and of fp32 (256 outputs, 8 x 2048 x 2048 bf16 57.6,
+// 63.3, fp32 62.0, 73.3, 16 x 1024 x 2048 fp32 61.7, 67.9; 16 x 1024 x 2048 bf16 58.0, 58.2, 32 x 512 x 2048 59.3, 55.6).
+// 1657 such pairs (128 .. 4096 tokens, 64 .. 8192 channels): 0.3 % above always taking the better one on average, 13 % at worst.
 void place_parts(stamp_plan* p) {
   const StampGeom& g = p->geom;
   p->ws_parts_hi = 0;
   const int64_t elems = (int64_t)g.B * g.s * g.d;
-  if (elems > (g.r >= 6 ? 1 << 25 : 1 << 24) || g.d < 192 || (g.d <= 512 && g.B * g.k >= 128)) return;
+  if (elems > (g.r >= 6 ? 1 << 25 : 1 << 24)) return;
+  if (g.r == 4 && g.B * g.k > 128 && g.k <= 32 && g.d < 512) return;
   if (g.ident || g.is2d || g.L == 0 || g.r < 4 || g.r > 6 || g.s < 128 || g.s > 4096 || g.d > 8192 || !stamp_lanes1d_fits(p, 3)) return;
   const StampHiTiles ht = p->parts_tiles = stamp_hi_tiles(p, 0);
   if (!ht.on && !p->hi6[0]) return;
+  if (ht.on && elems > 1 << 24 && g.B * g.k > 128 && (g.s >= 2048 || !g.x_bf16)) return;
   const size_t end = p->ws_abot + align256((size_t)g.B * (g.s / 8) * g.d * sizeof(float));
   const size_t hi = ht.on ? stamp_hi_tiles_bytes(p) : stamp_hi6_bytes(p, 0);
   if (end > p->ws_scales) return;

@@ -170,6 +170,30 @@ OPERANDS = [(dict(xform="identity", levels=0, batch=32, seq_len=1024, k_hi=2, d_
             (dict(xform="haar2d", batch=4, seq_len=1024, grid_h=32, grid_w=32, k_hi=16, d_in=512), True),  # 24.7, 19.6
             (dict(batch=2, seq_len=1024, levels=10, k_hi=32, d_in=512), True)]  # blocks of 32, in parts: 29.6 (beside the top levels), 22.7
 
+# ---- blocks below top levels: in parts of 8 tokens or not (us, whole blocks and parts)
+PARTS_RULE = [(dict(seq_len=4096, levels=12, k_hi=64, d_in=64), True),  # 42.1, 23.4
+              (dict(seq_len=256, levels=8, k_hi=8, d_in=128), True),  # 25.1, 19.4
+              (dict(batch=2, seq_len=2048, levels=11, k_hi=64, d_in=512), True),  # 33.9, 25.1
+              (dict(seq_len=1024, levels=10, k_hi=64, d_in=128), True),  # 23.0, 20.1
+              (dict(batch=64, seq_len=128, levels=7, k_hi=8, d_in=96), False),  # 20.6, 22.3
+              (dict(batch=64, seq_len=256, levels=8, k_hi=16, d_in=128), False),  # 23.5, 25.3
+              (dict(batch=256, seq_len=128, levels=7, k_hi=8, d_in=512), True),  # 39.6, 35.0
+              (dict(batch=4, seq_len=2048, levels=11, k_hi=64, d_in=4096), False),  # 62.3, 71.8
+              (dict(batch=8, seq_len=2048, levels=11, k_hi=32, d_in=2048), False),  # 57.6, 63.3
+              (dict(batch=32, seq_len=512, levels=9, k_hi=8, d_in=2048), True),  # 59.3, 55.6
+              (dict(batch=8, seq_len=2048, levels=11, k_hi=32, d_in=1024), True)]  # 49.3, 42.6
+
+
+@pytest.mark.parametrize("kw,parts", PARTS_RULE, ids=["-".join(str(v) for v in kw.values()) for kw, _ in PARTS_RULE])
+def test_rule_of_the_parts(kw, parts):
+    import torch
+    import paper_2510_26771_amd as st
+    w = _wl("parts_rule", x_dtype="bf16", d_out=256, **kw)
+    plan = st.StampPlan(tl.plan_desc_for(w, "bf16"), torch.zeros((w.d_in, w.d_out), dtype=torch.float32, device="cuda"))
+    tl.check_routes(plan, w, ("parts" if parts else "-parts",))
+    plan.destroy()
+
+
 
 @pytest.mark.parametrize("kw,direct", OPERANDS, ids=["-".join(str(v) for v in kw.values()) for kw, _ in OPERANDS])
 def test_rule_of_the_operands(kw, direct):
@@ -422,7 +446,9 @@ PARTS = [_parts(128, 7, 8, x_dtype="bf16"), _parts(128, 7, 2, batch=2, d=224, ac
          _parts(256, 5, 16, batch=2, x_dtype="bf16"), _parts(512, 9, 8, act_quant="asym", mean_shift=0.4, x_dtype="bf16"), _parts(512, 6, 32, batch=3),
          _parts(1024, 10, 64, d=1056, x_dtype="bf16"), _parts(1024, 7, 64), _parts(2048, 11, 64, d=544, act_quant="asym"),
          _parts(2048, 7, 32, d=256), _parts(4096, 12, 64, x_dtype="bf16"), _parts(4096, 8, 64, d=224, act_quant="asym", mean_shift=0.4),
-         _parts(256, 8, 8, d=8192, x_dtype="bf16"), _parts(1024, 10, 32, d=576, d_out=8450, x_dtype="bf16"), _parts(4096, 12, 64, d=224, d_out=4098)]
+         _parts(256, 8, 8, d=8192, x_dtype="bf16"), _parts(1024, 10, 32, d=576, d_out=8450, x_dtype="bf16"), _parts(4096, 12, 64, d=224, d_out=4098),
+         _parts(256, 8, 8, d=160, x_dtype="bf16"), _parts(1024, 10, 16, d=96, batch=3, act_quant="asym", mean_shift=0.5), _parts(512, 9, 8, d=64, batch=2),
+         _parts(2048, 11, 64, d=512, batch=2, d_out=768, x_dtype="bf16")]
 
 
 @pytest.mark.parametrize("w", PARTS, ids=[w.name for w in PARTS])
@@ -593,8 +619,8 @@ def test_grid_blocks_by_sub_blocks(w):
 
 # ---- conversion of the packed codes beside the top levels: one and several row tiles and K steps, 8-bit rows that do not
 # fill their operand's groups, an operand larger than the 8-bit codes it lies over, blocks on a line and on a grid
-BESIDE = [_wl("beside_32", seq_len=256, levels=8, k_hi=8, d_in=160, x_dtype="bf16", seed=801),
-          _wl("beside_64_b3_asym", batch=3, seq_len=1024, levels=10, k_hi=16, d_in=96, act_quant="asym", mean_shift=0.5, seed=802),
+BESIDE = [_wl("beside_32", batch=2, seq_len=64, levels=6, k_hi=2, d_in=160, x_dtype="bf16", seed=801),
+          _wl("beside_64_b3_asym", batch=3, seq_len=1024, levels=10, k_hi=16, d_in=32, act_quant="asym", mean_shift=0.5, seed=802),
           _wl("beside_32_b5", batch=5, seq_len=64, levels=6, k_hi=2, d_in=32, seed=803),
           _wl("beside_grid4", batch=2, seq_len=256, levels=4, k_hi=16, d_in=288, xform="haar2d", grid_h=16, grid_w=16, corr_len=4.0,
               x_dtype="bf16", seed=804),
@@ -609,7 +635,8 @@ def test_codes_converted_beside_the_top_levels(w):
 
 # ---- two streams on one plan, each with its own workspace, on the routes whose buffers lie over one another
 STREAMS = [(_wl("streams_direct", batch=2, seq_len=512, levels=3, k_hi=16, d_in=256, d_out=384, x_dtype="bf16", seed=901), ("direct", "hi_fp6")),
-           (_wl("streams_beside", batch=2, seq_len=2048, levels=11, k_hi=64, d_in=512, d_out=768, x_dtype="bf16", seed=902), ("beside_top",)),
+           (_wl("streams_beside", batch=2, seq_len=2048, levels=11, k_hi=64, d_in=32, d_out=768, x_dtype="bf16", seed=902), ("beside_top",)),
+           (_wl("streams_parts", batch=2, seq_len=2048, levels=11, k_hi=64, d_in=512, d_out=768, x_dtype="bf16", seed=902), ("parts",)),
            (_rag(3, 1003, 1, batch=2, d_in=256, d_out=515, x_dtype="bf16"), ("any_length_blocks", "direct")),
            (_grp(64, 3, 64, 128, 1026), ("group_blocks",)),
            (_wl("streams_dct", seq_len=1024, xform="dct", levels=0, k_hi=64, d_in=256, d_out=384, seed=903), ("hi_fp6",))]

@@ -522,7 +522,8 @@ def test_forward_under_hip_graph_capture():
     few = _wl("graph_1d_few", batch=2, seq_len=1024, levels=3, k_hi=8, d_in=1024, d_out=192, seed=85)
     topfused = _wl("graph_1d_topfused", batch=3, seq_len=512, levels=9, k_hi=64, d_in=64, d_out=16640, seed=86)
     for w, hi_rows, routes in (
-            (_wl("graph_1d", batch=2, seq_len=512, levels=9, k_hi=16, d_in=160, d_out=300, seed=81), 0, ("beside_top", "hi_fp6")),
+            (_wl("graph_1d", batch=2, seq_len=512, levels=9, k_hi=16, d_in=160, d_out=300, seed=81), 0, ("parts", "hi_fp6")),
+            (_wl("graph_1d_beside", batch=2, seq_len=512, levels=9, k_hi=16, d_in=32, d_out=300, seed=81), 0, ("beside_top", "hi_fp6")),
             (_wl("graph_2d", batch=1, seq_len=256, xform="haar2d", levels=4, grid_h=16, grid_w=16, k_hi=4, d_in=96,
                  d_out=128, seed=82, act_quant="asym"), 0, ("hi_fp6",)),
             # no top levels, 4-bit approximations in the 4-bit rows' GEMM, the 8-bit rows on either pipeline (int8: the depth
