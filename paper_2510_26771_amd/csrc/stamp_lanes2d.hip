@@ -175,10 +175,16 @@ hipError_t launch2d(const LaneArgs& a, int x_bf16, int asym, int B, hipStream_t 
 
 }  // namespace
 
-// the channels that 12 waves hold (4 x 4 blocks below top levels keep the form that tests name for them)
+// The channels that 12 waves hold.  4 x 4 blocks below top levels, layers to 256 outputs, us, packed codes that are converted beside
+// these levels against this: 2 x 64 tokens x 160 26.1, 24.8, 64 x 256 x 512 37.4, 36.9, 128 x 256 x 1152 73.9, 67.0, 32 x 1024 x 1152 73.2,
+// 66.9, 128 x 256 x 2048 100.3, 92.9; not narrow layers of more than 4096 blocks (128 x 1024 x 64 81.8, 87.9, x 160 90.5, 93.8; x 512 118.6,
+// 115.9), whose conversion is small, nor wide ones of few blocks (256 x 4096 44.0, 44.8, 4 x 1024 x 2048 44.2, 44.4).
 bool stamp_lanes2d_fits(const stamp_plan* p) {
   const StampGeom& g = p->geom;
-  return g.is2d && !g.ident && (g.r == 3 ? g.d <= 1536 : g.r == 2 && g.L == 0 && g.d <= 4096);
+  if (!g.is2d || g.ident || g.d > (g.r == 3 ? 1536 : 4096)) return false;
+  if (g.r == 3 || g.L == 0) return true;
+  const int64_t blocks = (int64_t)g.B * g.k;
+  return g.d <= 1536 ? blocks <= 4096 || g.d >= 512 : blocks >= 256;
 }
 
 hipError_t stamp_launch_lanes2d(const stamp_plan* p, const void* X, uint8_t* a6, float* scales, float* abot, const StampHiOut& hi, hipStream_t st) {

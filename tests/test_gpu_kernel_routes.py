@@ -104,7 +104,10 @@ LANES2 = [_lanes2(32, 3, 16, 16, 4, x_dtype="bf16"), _lanes2(160, 3, 16, 32, 8, 
           _lanes2(32, 2, 16, 16, 16, batch=3, x_dtype="bf16"), _lanes2(544, 2, 8, 16, 8, act_quant="asym", mean_shift=0.4), _lanes2(1184, 2, 16, 8, 5, batch=2),
           _lanes2(4096, 2, 16, 16, 16, x_dtype="bf16"), _lanes2(4064, 2, 16, 16, 16, act_quant="asym"),
           _lanes2(544, 2, 16, 16, 5, act_quant="asym", mean_shift=0.4), _lanes2(1184, 2, 16, 16, 5, batch=2, x_dtype="bf16"),
-          _lanes2(160, 3, 32, 32, 7, act_quant="asym", mean_shift=0.4), _lanes2(1184, 3, 32, 32, 5, batch=2)]
+          _lanes2(160, 3, 32, 32, 7, act_quant="asym", mean_shift=0.4), _lanes2(1184, 3, 32, 32, 5, batch=2),
+          # 4 x 4 blocks below top levels
+          _lanes2(288, 4, 16, 16, 16, batch=2, x_dtype="bf16"), _lanes2(1056, 3, 16, 16, 16, act_quant="asym", mean_shift=0.4), _lanes2(32, 3, 8, 8, 4, batch=3),
+          _lanes2(2080, 4, 16, 16, 16, batch=16, x_dtype="bf16")]
 
 
 @pytest.mark.parametrize("w", LANES2, ids=[w.name for w in LANES2])
@@ -168,6 +171,8 @@ OPERANDS = [(dict(xform="identity", levels=0, batch=32, seq_len=1024, k_hi=2, d_
             (dict(batch=128, seq_len=512, levels=9, k_hi=64, d_in=256), False),  # 70.7, 77.2
             (dict(batch=128, seq_len=513, k_hi=1, d_in=512, skip_first=True), True),  # 52.5, 38.9
             (dict(xform="haar2d", batch=4, seq_len=1024, grid_h=32, grid_w=32, k_hi=16, d_in=512), True),  # 24.7, 19.6
+            (dict(xform="haar2d", batch=32, seq_len=1024, grid_h=32, grid_w=32, levels=5, k_hi=64, d_in=1152), True),  # 73.2 (beside the top levels), 66.9
+            (dict(xform="haar2d", batch=128, seq_len=1024, grid_h=32, grid_w=32, levels=5, k_hi=64, d_in=64), False),  # 82.4, 87.2
             (dict(batch=2, seq_len=1024, levels=10, k_hi=32, d_in=512), True)]  # blocks of 32, in parts: 29.6 (beside the top levels), 22.7
 
 # ---- blocks below top levels: in parts of 8 tokens or not (us, whole blocks and parts)
@@ -622,7 +627,7 @@ def test_grid_blocks_by_sub_blocks(w):
 BESIDE = [_wl("beside_32", batch=2, seq_len=64, levels=6, k_hi=2, d_in=160, x_dtype="bf16", seed=801),
           _wl("beside_64_b3_asym", batch=3, seq_len=1024, levels=10, k_hi=16, d_in=32, act_quant="asym", mean_shift=0.5, seed=802),
           _wl("beside_32_b5", batch=5, seq_len=64, levels=6, k_hi=2, d_in=32, seed=803),
-          _wl("beside_grid4", batch=2, seq_len=256, levels=4, k_hi=16, d_in=288, xform="haar2d", grid_h=16, grid_w=16, corr_len=4.0,
+          _wl("beside_grid4", batch=2, seq_len=256, levels=4, k_hi=16, d_in=1568, xform="haar2d", grid_h=16, grid_w=16, corr_len=4.0,
               x_dtype="bf16", seed=804),
           _wl("beside_wide", seq_len=512, levels=9, k_hi=16, d_in=8224, x_dtype="bf16", seed=805)]
 
