@@ -270,11 +270,11 @@ void place_hi6(stamp_plan* p, size_t region, size_t room) {
 // this form) behind them, over the block sums' parts and P where the tiles take the 8-bit rows along, or behind everything.
 // A block's workgroup takes its tokens one after the other: with few blocks that chain is what a layer waits for; the sums of the
 // parts are 4 bytes per channel and 8 tokens more, twice, which is what counts with many.  Layers, us, whole blocks against
-// parts.  Blocks of 64: 4096 x 64 41.9, 23.3, x 1024 50.3, 31.5, x 4096 73.6, 56.0, 2 x 4096 x 4096 78.2, 75.7, 8 x 4096 x 1024 68.6, 62.8, 4 x
+// parts.  Blocks of 64: 4096 x 64 42.1, 23.4, x 1024 50.3, 31.5, x 4096 73.6, 56.0, 2 x 4096 x 4096 78.2, 75.7, 8 x 4096 x 1024 68.6, 62.8, 4 x
 // 4096 x 4096 88.1, 114.6; of 32: 256 x 160 26.5, 20.4, 512 x 1024 40.6, 24.1, 2 x 2048 x 512 34.3, 25.6, 2048 x 4096 56.2, 48.2, 4 x 2048 x 2048
-// 46.5, 45.4, 4 x 2048 x 4096 65.7, 75.5; of 16: 1024 x 128 25.6, 22.3, 2 x 1024 x 4096 48.2, 44.7, 16 x 1024 x 4096 101.5, 103.2.  So up to
+// 46.5, 45.4, 4 x 2048 x 4096 65.7, 75.5; of 16: 1024 x 128 23.0, 20.1, 2 x 1024 x 4096 48.2, 44.7, 16 x 1024 x 4096 101.5, 103.2.  So up to
 // 2^24 elements, 2^25 in blocks of 64.  The chain of a block of 16 is short: of narrow layers of many short sequences (more than
-// 128 blocks, at most 32 a sequence, below 512 channels) its workgroups fill the CUs without parts, 64 x 256 x 128 23.3, 25.2, 64 x 128
+// 128 blocks, at most 32 a sequence, below 512 channels) its workgroups fill the CUs without parts, 64 x 256 x 128 23.5, 25.3, 64 x 128
 // x 96 20.6, 22.3, but 256 x 128 x 512 39.6, 35.0.  Beyond 2^24 elements parts need a launch to save, which those whose 8-bit rows ride in
 // the tiles have not: with more than 128 blocks whole blocks from 2048 tokens on, and of fp32 (256 outputs, 8 x 2048 x 2048 bf16 57.6,
 // 63.3, fp32 62.0, 73.3, 16 x 1024 x 2048 fp32 61.7, 67.9; 16 x 1024 x 2048 bf16 58.0, 58.2, 32 x 512 x 2048 59.3, 55.6).
@@ -620,9 +620,11 @@ stamp_status_t gen_quantize(const stamp_plan* p, const void* X, int8_t* q_hi, ui
 bool direct_pays(const stamp_plan* p) {
   const StampGeom& g = p->geom;
   const int64_t rows = (int64_t)g.B * g.s, hi = (int64_t)g.B * g.khi;
-  // rows by lanes, four to a workgroup, two where d > 8192: always (packed, direct, 256 outputs: 262144 x 256 188, 75, 65536 x 1024 83,
-  // 50, 4096 x 8192 fp32 96, 75, 256 x 32 19.3, 16.0); one to a workgroup, whose pieces of 16 bytes meet in no line, while the
-  // output is small (2048 x 24576 156, 152, but 4096 x 24576 with 256 8-bit rows 229, 233, 2048 x 32768 fp32 271, 274)
+  // rows by lanes, four to a workgroup, two where d > 8192: always, however many of them are 8-bit rows (packed, direct, 256 outputs:
+  // 262144 x 256 188, 75, 65536 x 1024 83, 50, 4096 x 8192 fp32 96, 75, 256 x 32 19.3, 16.0; a quarter at 8 bits, 16384 x 1024 46.0, 34.6; all,
+  // 4096 x 256 18.3, 12.7, x 1024 25.9, 20.8; 408 plans from 64 rows on, none the other way); one to a workgroup, whose pieces of 16 bytes
+  // meet in no line, while the output is small (2048 x 24576 156, 152, but 4096 x 24576 with 256 8-bit rows 229, 233, 2048 x 32768 fp32
+  // 271, 274)
   if (g.ident && !p->rag.on) return g.d <= 16384 || rows * g.d <= (3 << 24);
   // 1-D blocks of 8 and 16 tokens by stamp_lanes1d, blocks of a grid by stamp_lanes2d (32 x 4096 x 512 92, 80): whole fragments leave in 16 and 8 bytes, at any size as fast as they can be made;
   // only many 8-bit rows cost (packed, direct: 32768 x 4096 136, 112, x 8192 310, 233, 16 x 5000 x 4096 375, 288, 262144 x 256 106, 83;
