@@ -209,12 +209,13 @@ __global__ __launch_bounds__(256) void k_quant_hi(const float* __restrict__ ttop
 // Plans without a sequence transform (the layers the paper leaves un-transformed, and the baseline the
 // transform's cost is measured against): per-token quantization of X itself (Background, Eq. 1), tokens
 // 0..k-1 of every sequence at 8 bits, the rest at 4 bits.  One workgroup per token: the row is read twice
-// (range, then codes; the second read comes from cache).  Packed codes; stamp_launch_lanes_rows writes FP6 operands.
+// (range, then codes; the second read comes from cache).
+// OUT6: q_lo is the FP6 operand of the 4-bit rows, the 8-bit rows go to hi6; for few rows, see launch_quant_rows.
 // ------------------------------------------------------------------------------------------
-template <bool BF16, bool ASYM>
+template <bool BF16, bool ASYM, bool OUT6>
 __global__ __launch_bounds__(256) void k_quant_rows(const void* __restrict__ X, int8_t* __restrict__ q_hi,
                                                     uint8_t* __restrict__ q_lo, float* __restrict__ scales, int s, int d,
-                                                    int k, int Kpad, size_t zeros_off) {
+                                                    int k, int Kpad, size_t zeros_off, Hi6Out hi6) {
   __shared__ uint32_t s_red[8];
   const int pr = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   const size_t m = (size_t)b * s + pr;
@@ -254,19 +255,24 @@ __global__ __launch_bounds__(256) void k_quant_rows(const void* __restrict__ X, 
     scales[m] = scale;
     if constexpr (ASYM) scales[zeros_off + m] = z;
   }
-  for (int c = tid * 8; c < d; c += 256 * 8) {
+  // OUT6: whole quads of threads stay together (a loop that every thread leaves at the same time costs narrow rows in
+  // packed form 15 us in 75: 7 x 16384 tokens x 32, fp32)
+  for (int c = tid * 8; (OUT6 ? c - tid * 8 : c) < d; c += 256 * 8) {
     float v[8];
-    load8(X, xoff + c, BF16, true, v);
+    load8(X, xoff + (OUT6 ? min(c, d - 8) : c), BF16, true, v);
     if (hi) {
       const float qlo = ASYM ? 0.0f : -127.0f, qhi = ASYM ? 255.0f : 127.0f, shift = ASYM ? 128.0f : 0.0f;
       uint32_t w[2] = {0u, 0u};
+      int qi[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         float q = __fadd_rn(rintf(__fmul_rn(v[i], inv)), z);
         q = fminf(fmaxf(q, qlo), qhi) - shift;
+        qi[i] = (int)q;
         w[i >> 2] |= ((uint32_t)((int)q) & 0xFFu) << (8 * (i & 3));
       }
-      *reinterpret_cast<uint2*>(q_hi + ((size_t)b * k + pr) * d + c) = make_uint2(w[0], w[1]);
+      if constexpr (OUT6) store_hi48(hi6, b * k + pr, Kpad >> 7, qi, c, c < d);
+      else *reinterpret_cast<uint2*>(q_hi + ((size_t)b * k + pr) * d + c) = make_uint2(w[0], w[1]);
     } else {
       float pq[8];
 #pragma unroll
@@ -280,7 +286,13 @@ __global__ __launch_bounds__(256) void k_quant_rows(const void* __restrict__ X, 
       } else {
         w = pack8_int4(pq);
       }
-      *reinterpret_cast<uint32_t*>(q_lo + stamp_qlo_offset(m, c, Kpad)) = w;
+      if constexpr (OUT6) {
+        uint32_t w0, w1;
+        nib8_to_48(w, w0, w1);
+        store48(q_lo + a6_row(m, Kpad >> 7) + off48(c, kStageA6), w0, w1, c, c < d);
+      } else {
+        *reinterpret_cast<uint32_t*>(q_lo + stamp_qlo_offset(m, c, Kpad)) = w;
+      }
     }
   }
 }
@@ -289,12 +301,22 @@ __global__ __launch_bounds__(256) void k_quant_rows(const void* __restrict__ X, 
 
 namespace {
 Hi6Out hi6_out(const StampDirect* dir) { return dir != nullptr ? dir->hi : Hi6Out{}; }
+// FP6 operands of few rows: 8 channels a thread.  A lane of k_lanes_rows has 32 to go through, one after the other, while most CUs
+// have no row at all.  One 8-bit row, layers to 256 outputs, us in a graph, k_lanes_rows against this: WHT 16 x 256 23.1, 22.9, 64 x 2048 29.7,
+// 29.2, 128 x 1024 28.9, 28.7; rows without transform, fp32 16 x 512 13.6, 13.4, 256 x 1024 17.7, 17.6; from one row per CU on, and where
+// a row is several passes of a workgroup, the other way (mean over the depths up to 4096: 512 rows 0.2 us, 1024 rows 1.0; bf16
+// rows of 4096 0.5, of 11008 2.4).
 template <bool BF16, bool ASYM>
 hipError_t launch_quant_rows(const stamp_plan* p, const void* X, int8_t* q_hi, uint8_t* q_lo, float* scales, const StampDirect* dir, hipStream_t st) {
   const StampGeom& g = p->geom;
   const size_t zoff = (size_t)g.B * g.s;
-  if (dir != nullptr) return stamp_launch_lanes_rows(p, X, BF16, dir->a6, scales, dir->hi, st);
-  hipLaunchKernelGGL((k_quant_rows<BF16, ASYM>), dim3(g.s, g.B), dim3(256), 0, st, X, q_hi, q_lo, scales, g.s, g.d, g.k, p->Kpad, zoff);
+  const dim3 grid(g.s, g.B), blk(256);
+  if (dir == nullptr)
+    hipLaunchKernelGGL((k_quant_rows<BF16, ASYM, false>), grid, blk, 0, st, X, q_hi, q_lo, scales, g.s, g.d, g.k, p->Kpad, zoff, Hi6Out{});
+  else if ((int64_t)g.B * g.s <= stamp_device_cus() && g.d <= (BF16 ? 2048 : 4096))
+    hipLaunchKernelGGL((k_quant_rows<BF16, ASYM, true>), grid, blk, 0, st, X, q_hi, dir->a6, scales, g.s, g.d, g.k, p->Kpad, zoff, dir->hi);
+  else
+    return stamp_launch_lanes_rows(p, X, BF16, dir->a6, scales, dir->hi, st);
   return hipGetLastError();
 }
 }  // namespace

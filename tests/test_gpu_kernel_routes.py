@@ -128,7 +128,8 @@ def test_grid_blocks_by_lanes(w):
 
 
 # ---- rows by lanes: four, two and one of them to a workgroup, the widths on either side; rows and 8-bit rows that are no multiple
-# of that; a last wave that is partly empty; the smallest; all rows at 8 bits; rows of the general path
+# of that; a last wave that is partly empty; all rows at 8 bits; rows of the general path; few rows by 8 channels a thread, on either
+# side of their line (256 rows; 2048 channels bf16, 4096 fp32)
 def _rows(d, s, batch, k, xform="identity", **kw):
     base = dict(xform=xform, levels=0, seq_len=s, batch=batch, k_hi=k, d_in=d, d_out=66, seed=700 + d)
     base.update(kw)
@@ -138,7 +139,10 @@ def _rows(d, s, batch, k, xform="identity", **kw):
 ROWS = [_rows(32, 3, 1, 1), _rows(96, 131, 3, 5, x_dtype="bf16"), _rows(544, 37, 2, 0, act_quant="asym", mean_shift=0.4),
         _rows(2080, 130, 1, 33, x_dtype="bf16", act_quant="asym"), _rows(8192, 21, 1, 4, x_dtype="bf16"), _rows(8224, 21, 1, 4, x_dtype="bf16"),
         _rows(8224, 19, 1, 3, act_quant="asym", mean_shift=0.4), _rows(16384, 7, 3, 2), _rows(16416, 5, 3, 2), _rows(16416, 5, 3, 2, x_dtype="bf16"),
-        _rows(96, 4100, 2, 16, x_dtype="bf16"), _rows(1056, 1030, 1, 7, act_quant="asym", mean_shift=0.4), _rows(8192, 517, 1, 4), _rows(160, 64, 3, 5, xform="wht"), _rows(1056, 33, 3, 2, xform="dct", act_quant="asym", x_dtype="bf16")]
+        _rows(96, 4100, 2, 16, x_dtype="bf16"), _rows(1056, 1030, 1, 7, act_quant="asym", mean_shift=0.4), _rows(8192, 517, 1, 4), _rows(160, 64, 3, 5, xform="wht"), _rows(1056, 33, 3, 2, xform="dct", act_quant="asym", x_dtype="bf16"),
+        _rows(96, 256, 1, 5), _rows(544, 257, 1, 5), _rows(2048, 85, 3, 9, x_dtype="bf16"), _rows(2080, 85, 3, 9, x_dtype="bf16", act_quant="asym"),
+        _rows(4096, 16, 1, 1, act_quant="asym", mean_shift=0.4), _rows(4128, 16, 1, 16), _rows(32, 20, 2, 20, x_dtype="bf16", act_quant="asym"),
+        _rows(1056, 300, 1, 33, act_quant="asym"), _rows(96, 257, 2, 40, x_dtype="bf16")]
 
 
 @pytest.mark.parametrize("w", ROWS, ids=[w.name for w in ROWS])
