@@ -445,6 +445,34 @@ def test_tensors_off_the_16_byte_grid(w, route):
         plan.destroy()
 
 
+# ---- the quantizers by lanes read X in 16-byte words wherever it lies: the same bits from an X one element off the 16-byte grid
+OFF_GRID = [_lanes(544, levels=4, k_hi=8, x_dtype="bf16"), _lanes(4128), _lanes(8224, x_dtype="bf16"), _lanes(1184, levels=7, k_hi=16, x_dtype="bf16"),
+            _lanes2(288, 3, 16, 16, 4, x_dtype="bf16"), _lanes2(160, 2, 16, 16, 16), _rows(1056, 1030, 1, 7, x_dtype="bf16"), _rows(544, 300, 2, 5),
+            _rows(16416, 5, 3, 2, x_dtype="bf16"), _rows(96, 20, 3, 5, x_dtype="bf16"), _rows(96, 20, 3, 5)]
+
+
+@pytest.mark.parametrize("w", OFF_GRID, ids=[w.name for w in OFF_GRID])
+def test_quantizers_by_lanes_off_the_16_byte_grid(w):
+    import torch
+    import paper_2510_26771_amd as st
+    inp = tl.make_inputs(w)
+    plan = st.StampPlan(tl.plan_desc_for(w, "f32"), torch.from_numpy(inp["W"]).cuda())
+    tl.check_routes(plan, w, ("direct",))
+    X = tl.to_device_x(inp, w)
+    buf = torch.zeros(X.numel() + 16, dtype=X.dtype, device="cuda")
+    buf[1:X.numel() + 1] = X.reshape(-1)
+    off = buf[1:X.numel() + 1].view(X.shape)
+    assert off.data_ptr() % 16 == X.element_size()
+    out = []
+    for x in (X, off):
+        Y = torch.empty((w.batch, w.seq_len, w.d_out), dtype=torch.float32, device="cuda")
+        plan.linear_forward(x, Y, plan.alloc_workspace())
+        out.append(Y)
+    torch.cuda.synchronize()
+    assert torch.equal(*out)
+    plan.destroy()
+
+
 # ---- blocks in parts of 8 tokens: every block length, 16 to 512 sums per sequence, depths that end inside a thread's 16 sums, at them
 # and above, channels that leave the last workgroup partly empty, sequences beside each other, 8-bit rows in tiles and not
 def _parts(s, levels, k, d=192, **kw):
