@@ -311,10 +311,11 @@ def wht_inverse(t: np.ndarray, dtype=np.float32) -> np.ndarray:
 
 
 def dct_matrix(s: int) -> np.ndarray:
-    """Dense fp64 orthonormal DCT-II matrix C[k, n]."""
-    k = np.arange(s, dtype=np.float64)[:, None]
-    n = np.arange(s, dtype=np.float64)[None, :]
-    C = np.cos(np.pi * (2.0 * n + 1.0) * k / (2.0 * s)) * math.sqrt(2.0 / s)
+    """Dense fp64 orthonormal DCT-II matrix C[k, n].  The angles pi (2 n + 1) k / (2 s) are reduced to one turn as integers: in
+    floating point the largest would carry 2^-52 pi s into its cosine, enough to move a scale across a rounding boundary."""
+    k = np.arange(s, dtype=np.int64)[:, None]
+    n = np.arange(s, dtype=np.int64)[None, :]
+    C = np.cos(np.pi * ((2 * n + 1) * k % (4 * s)) / (2.0 * s)) * math.sqrt(2.0 / s)
     C[0, :] = math.sqrt(1.0 / s)
     return C
 

@@ -225,8 +225,8 @@ DCT = [_wl("dct_8", batch=2, xform="dct", levels=0, seq_len=8, k_hi=1, seed=201)
        _wl("dct_512_reg", batch=13, xform="dct", levels=0, seq_len=512, d_in=160, d_out=163, k_hi=8, x_dtype="bf16", seed=205),
        _wl("dct_1024_reg", batch=13, xform="dct", levels=0, seq_len=1024, d_in=160, d_out=163, k_hi=8, seed=206),
        _wl("dct_2048_reg", batch=8, xform="dct", levels=0, seq_len=2048, d_in=256, d_out=258, k_hi=8, x_dtype="bf16", seed=207),
-       # (the oracle's angles are rounded to 2^-52 pi s, some 1e-5 of a coefficient's fp32 spacing: with seed 208 a row maximum lies
-       # 4e-6 of it from a rounding boundary and falls on the other side; with 214 none is nearer than 4.6e-4)
+       # with seed 208 a row maximum lies 4e-6 of its fp32 spacing from a rounding boundary
+       _wl("dct_2048_near", xform="dct", levels=0, seq_len=2048, d_in=96, d_out=33, k_hi=8, x_dtype="bf16", seed=208),
        _wl("dct_2048_few", xform="dct", levels=0, seq_len=2048, d_in=96, d_out=33, k_hi=8, x_dtype="bf16", seed=214),
        _wl("dct_4096_reg", batch=8, xform="dct", levels=0, seq_len=4096, d_in=256, d_out=257, k_hi=8, seed=209)]
 
@@ -238,9 +238,8 @@ def test_dct_of_power_of_two_lengths(w):
 
 @pytest.mark.parametrize("s", [8, 64, 2048, 4096, 16384])
 def test_dct_inverse_against_the_dense_product(s):
-    """stamp_inverse of an odd number of columns: fp64 all the way, one rounding at the end.  Both sides are fp64 sums (the
-    dense one carries the rounding of its angles, up to 2^-52 pi s, into the cosines), so they agree to 2^-24 of the
-    column plus that."""
+    """stamp_inverse of an odd number of columns: fp64 all the way, one rounding at the end.  Both sides are fp64 sums, so they
+    agree to 2^-24 of the column plus the rounding of s terms."""
     import torch
     import paper_2510_26771_amd as st
     w = _wl(f"inv_dct_{s}", batch=2 if s <= 64 else 1, seq_len=s, xform="dct", levels=0, k_hi=1, d_in=32, d_out=37)
