@@ -317,6 +317,8 @@ def dct_matrix(s: int) -> np.ndarray:
     n = np.arange(s, dtype=np.int64)[None, :]
     C = np.cos(np.pi * ((2 * n + 1) * k % (4 * s)) / (2.0 * s)) * math.sqrt(2.0 / s)
     C[0, :] = math.sqrt(1.0 / s)
+    if s % 2 == 0:  # +- sqrt(1/2) sqrt(2/s), a power of two for s a power of four
+        C[s // 2] = math.sqrt(1.0 / s) * np.where((np.arange(s) + 1) % 4 < 2, 1.0, -1.0)
     return C
 
 

@@ -150,6 +150,8 @@ __global__ __launch_bounds__(16 * R * CH, 4) void k_dct_reg(const cd* __restrict
   using Pl = Places<R>;
   constexpr int M = 256 * R, N = 2 * M, T = Pl::T, NB = 16 / R;  // NB butterflies of the last pass
   constexpr double kNrm = (R == 1 ? 1.0 : R == 2 ? kSqrtHalf : R == 4 ? 0.5 : 0.5 * kSqrtHalf) / 16.0;  // sqrt(2 / N)
+  // sqrt(1 / N): a power of two for 1024 and 4096, so that a sum of bf16 tokens that lies between two fp32 numbers is rounded as such
+  constexpr double kNrm0 = (R == 1 ? kSqrtHalf : R == 2 ? 0.5 : R == 4 ? 0.5 * kSqrtHalf : 0.25) / 16.0;
   extern __shared__ __attribute__((aligned(16))) uint8_t dct_reg_smem[];  // [Places::kPoints][CH]
   const int tid = threadIdx.x, ch = tid % CH, t = tid / CH;
   // neighbouring channel groups share cache lines: keep them on one XCD
@@ -233,8 +235,8 @@ __global__ __launch_bounds__(16 * R * CH, 4) void k_dct_reg(const cd* __restrict
           if (l >= h && R > 1) k = first ? 128 + 256 * (l - h) : k;
           if (l == 0 && first) {
             const cd hh = c_mul(te[M / 2], c_conj(b));
-            put(0, (a.re + a.im) * (kNrm * kSqrtHalf));
-            put((uint32_t)M * row, (a.re - a.im) * kSqrtHalf * kNrm);
+            put(0, (a.re + a.im) * kNrm0);
+            put((uint32_t)M * row, (a.re - a.im) * kNrm0);
             put((uint32_t)(M / 2) * row, kNrm * hh.re);
             put((uint32_t)(M + M / 2) * row, -kNrm * hh.im);
             continue;

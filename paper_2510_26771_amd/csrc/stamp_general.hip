@@ -508,8 +508,9 @@ __global__ __launch_bounds__(1024) void k_gen_dct_fft(const cd* __restrict__ tab
       float* o = T + bo + c;
       if (k == 0) {
         const cd t = s[ch], h = c_mul(te[M >> 1], c_conj(s[((M >> 1) << chlog) + ch]));
-        o[0] = (float)((t.re + t.im) * sqrt(1.0 / N));
-        o[(size_t)M * ld] = (float)((t.re - t.im) * sqrt(0.5) * nrm);
+        const double nrm0 = sqrt(1.0 / N);  // exact for N a power of four: see stamp_dct.hip
+        o[0] = (float)((t.re + t.im) * nrm0);
+        o[(size_t)M * ld] = (float)((t.re - t.im) * nrm0);
         o[(size_t)(M >> 1) * ld] = (float)(nrm * h.re);
         o[(size_t)(M + (M >> 1)) * ld] = (float)(-nrm * h.im);
         continue;

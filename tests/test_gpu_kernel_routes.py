@@ -236,6 +236,25 @@ def test_dct_of_power_of_two_lengths(w):
     tl.full_case(w, with_bias=True, check_unfused=False)
 
 
+@pytest.mark.parametrize("s", [16, 64, 256, 1024, 4096, 16384])
+def test_dct_rows_of_one_magnitude_are_rounded_once(s):
+    """Coefficients 0 and s / 2 are signed sums of tokens over sqrt(s).  For s a power of four that is exact in fp64, and a sum
+    half way between two fp32 numbers goes to the even one."""
+    import torch
+    import paper_2510_26771_amd as st
+    w = _wl(f"dct_tie_{s}", xform="dct", levels=0, seq_len=s, k_hi=1, d_in=32, d_out=16, x_dtype="bf16")
+    X = torch.zeros((1, s, 32), dtype=torch.bfloat16, device="cuda")
+    # tokens 0 and 3 enter both with a plus: 2^14 + 2^-10, 25 bits
+    X[0, 0], X[0, 3] = 2.0 ** 14, 2.0 ** -10
+    plan = st.StampPlan(tl.plan_desc_for(w, "f32"), torch.zeros((32, 16), dtype=torch.float32, device="cuda"))
+    q = plan.alloc_act_buffers()
+    plan.quantize_act(X, *q, plan.alloc_workspace())
+    torch.cuda.synchronize()
+    row = np.float32(2.0 ** 14 / np.sqrt(float(s)))
+    assert q[2][0, 0].item() == row / np.float32(127) and q[2][0, s // 2].item() == row / np.float32(7)
+    plan.destroy()
+
+
 @pytest.mark.parametrize("s", [8, 64, 2048, 4096, 16384])
 def test_dct_inverse_against_the_dense_product(s):
     """stamp_inverse of an odd number of columns: fp64 all the way, one rounding at the end.  Both sides are fp64 sums, so they
