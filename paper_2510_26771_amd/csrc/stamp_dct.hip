@@ -8,7 +8,8 @@
 // after the other, so that a workgroup needs 8 bytes of LDS per point and two workgroups of 2048 tokens share a CU: one loads
 // while the other computes.
 // What bounds it: the fp64 vector ALU (about 900 operations per 16 points and direction, 7 us for 2048 tokens x 4096 channels),
-// beside rows that arrive and leave in runs of CH channels.  2048 x 4096, forward and inverse: 20.4 and 23.7 us, 36.7 and 38.6
+// beside rows that arrive and leave in runs of CH channels; the forward form of 4096 tokens also moves 16 values a thread through
+// scratch memory.  2048 x 4096, forward and inverse: 20.4 and 23.7 us, 36.7 and 38.6
 // with every radix-4 pass through LDS.
 #include "stamp_gen_io.h"
 
