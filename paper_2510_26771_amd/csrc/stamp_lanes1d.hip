@@ -19,7 +19,7 @@ namespace {
 // NG = 2: a lane holds two groups of 32 channels, for layers as wide as a
 // model's down-projection.  Beside the first group's row A, which waits in LDS, 36 of the second group's values find no register and go
 // through scratch memory (148 bytes a lane; fp32 and bf16 rows beyond the streaming kernels' split, NG = 1, 6 and 4): 2048 x 11008 21.4 us
-// for 79 MB, where the narrower layers above run at 5.4 TB/s.  NANMAX: a NaN is the largest value of a block sum's row.
+// for 62 MB (2.9 TB/s).  NANMAX: a NaN is the largest value of a block sum's row.
 template <int RLOG, bool BF16, bool ASYM, bool RAG, int NG, bool NANMAX>
 __global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs a) {
   constexpr int RK = 1 << RLOG, NL = RK / 2, CPR = BF16 ? 4 : 8;  // tokens, lanes per group of channels, 16-byte loads per token
