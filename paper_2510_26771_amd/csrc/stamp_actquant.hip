@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void k_top(float* __restrict__ abot, uint32_t*
   extern __shared__ float s_buf[];  // [k][kTopCh + 1]
   if ((int)blockIdx.x >= ntop) {
 #pragma unroll
-    for (int kg = 0; kg < 2; ++kg) stamp_gemm::repack6_rows(q_lo, a6, blockIdx.x - ntop, threadIdx.x, kg);
+    for (int i = 0; i < 2; ++i) stamp_gemm::repack6_rows(q_lo, a6, blockIdx.x - ntop, i * 256 + threadIdx.x);
     return;
   }
   const int b = (int)blockIdx.x / nslices, slice = (int)blockIdx.x - b * nslices, c_base = slice * kTopCh, tid = threadIdx.x;
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256) void k_quant_rows(const void* __restrict__ X, 
       if constexpr (OUT6) {
         uint32_t w0, w1;
         nib8_to_48(w, w0, w1);
-        store48(q_lo + a6_row(m, Kpad >> 7) + off48(c, kStageA6), w0, w1, c, c < d);
+        store48(q_lo + a6_row(m, Kpad >> 7) + off48(c, kStageA6), row_half6(m), w0, w1, c, c < d);
       } else {
         *reinterpret_cast<uint32_t*>(q_lo + stamp_qlo_offset(m, c, Kpad)) = w;
       }

@@ -14,6 +14,10 @@ using stamp_gemm::kBlock6;
 using stamp_gemm::kPart;
 using stamp_gemm::kStageA6;
 using stamp_gemm::nib8_to_48;
+using stamp_gemm::chan_off6;
+using stamp_gemm::row_half6;
+using stamp_gemm::row_lane6;
+using stamp_gemm::row_off6;
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2v __attribute__((ext_vector_type(2)));
 
@@ -94,32 +98,34 @@ __device__ __forceinline__ uint32_t pack8_uint4(const float (&p)[8], float z) {
 // ---- codes straight to the FP6 GEMMs' operand layout (stamp_gemm6.hip; a thread owns 8 channels = 48 bits, the four
 // threads of a quad one 24-byte fragment of 32 channels) ----
 
-// byte offset, inside a 32-row block of K steps `kt_bytes` apart, of the 8 bytes that this thread stores: thread t of a quad
+// byte offset, from its row's place on, of the 8 bytes that this thread stores for a row of half 0: thread t of a quad
 // stores bytes 8 t .. 8 t + 7 of the fragment (t = 3 stores nothing); c = the thread's first channel
 __device__ __forceinline__ uint32_t off48(int c, uint32_t kt_bytes) {
-  const int f = (c >> 5) & 3, po = (f >> 1) * 24 + ((c >> 3) & 3) * 8;
-  return (uint32_t)(c >> 7) * kt_bytes + (uint32_t)((po >> 4) * kPart + (f & 1) * 512 + (po & 15));
+  const int t = (c >> 3) & 3;
+  return chan_off6((uint32_t)c, kt_bytes) + (uint32_t)((t >> 1) * kPart + (t & 1) * 8);
 }
 
-// the quad's 4 x 48 bits -> 24 bytes; every lane of the quad has to call this
-__device__ __forceinline__ void store48(uint8_t* dst, uint32_t w0, uint32_t w1, int c, bool active) {
+// the quad's 4 x 48 bits -> 24 bytes (half: row_half6 of the row); every lane of the quad has to call this
+__device__ __forceinline__ void store48(uint8_t* dst, bool half, uint32_t w0, uint32_t w1, int c, bool active) {
   const uint32_t n0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w0, 0xF9, 0xF, 0xF, false);  // quad_perm [1,2,3,3]
   const uint32_t n1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w1, 0xF9, 0xF, 0xF, false);
   const uint32_t d1 = w1 | (n0 << 16), d2 = (n0 >> 16) | (n1 << 16);  // w0, d1, d2: 96 bits from this thread's first one on
   const int t = (c >> 3) & 3;
   const uint32_t a = t == 2 ? d1 : __builtin_amdgcn_alignbit(d1, w0, 16 * t);
   const uint32_t b = t == 2 ? d2 : __builtin_amdgcn_alignbit(d2, d1, 16 * t);
-  if (active && t != 3) *reinterpret_cast<u2v*>(dst) = u2v{a, b};
+  // half 1 starts at byte 24 of the lane's 48
+  if (active && t != 3) *reinterpret_cast<u2v*>(dst + (half ? (t == 1 ? 2 * kPart - 8 : kPart + 8) : 0)) = u2v{a, b};
 }
 
 // row m of the 4-bit operand: byte offset of its place in K step 0
 __device__ __forceinline__ size_t a6_row(size_t m, int KT) {
-  return (m >> 8) * (size_t)KT * kStageA6 + ((m & 255) >> 5) * kBlock6 + (m & 31) * 16;
+  return (m >> 8) * (size_t)KT * kStageA6 + row_off6((uint32_t)m & 255);
 }
 
 // an 8-bit row: codes 16 h + l to the operand of the kernel for few rows (stamp_hi6.h), row m of it
 typedef StampHiOut Hi6Out;
-// K step stride of that operand, and every place of row m (offset of its h field of K step 0; l follows at *lo)
+// K step stride of that operand, and every place of row m: store(its h fragments' lane in K step 0, their half, where the l ones
+// follow, their half)
 __device__ __forceinline__ uint32_t hi_step_bytes(const Hi6Out& o) { return o.ht.on ? (uint32_t)kBlock6 : (uint32_t)(2 * o.np * kBlock6); }
 template <typename Store>
 __device__ __forceinline__ void hi_rows(const Hi6Out& o, int m, int KT, Store store) {
@@ -127,10 +133,10 @@ __device__ __forceinline__ void hi_rows(const Hi6Out& o, int m, int KT, Store st
     const int b = m / o.seq;
     int tile, ntiles, place;
     stamp_hi_places(o.ht, b, m - b * o.seq, &tile, &ntiles, &place);
-    for (int i = 0; i < ntiles; ++i) store(o.p + (size_t)(tile + i) * KT * kBlock6 + place * 16, kHiPlaces * 16);
+    for (int i = 0; i < ntiles; ++i) store(o.p + (size_t)(tile + i) * KT * kBlock6 + place * 16, false, 0, true);
   } else {
     const int gr = 32 * o.np, grp = m / gr, r = m - grp * gr;
-    store(o.p + (size_t)grp * KT * (2 * o.np * kBlock6) + (r >> 5) * (2 * kBlock6) + (r & 31) * 16, kBlock6);
+    store(o.p + (size_t)grp * KT * (2 * o.np * kBlock6) + (r >> 5) * (2 * kBlock6) + row_lane6(r & 31), row_half6(r), kBlock6, row_half6(r));
   }
 }
 __device__ __forceinline__ void store_hi48(const Hi6Out& o, int m, int KT, const int (&q)[8], int c, bool active) {
@@ -142,9 +148,9 @@ __device__ __forceinline__ void store_hi48(const Hi6Out& o, int m, int KT, const
     l |= (uint64_t)((uint32_t)abs(lv) | ((uint32_t)(lv >> 31) & 32u)) << (6 * i);
   }
   const uint32_t off = off48(c, hi_step_bytes(o));
-  hi_rows(o, m, KT, [&](uint8_t* dst, int lo) {
-    store48(dst + off, (uint32_t)h, (uint32_t)(h >> 32), c, active);
-    store48(dst + off + lo, (uint32_t)l, (uint32_t)(l >> 32), c, active);
+  hi_rows(o, m, KT, [&](uint8_t* dst, bool hh, int lo, bool lh) {
+    store48(dst + off, hh, (uint32_t)h, (uint32_t)(h >> 32), c, active);
+    store48(dst + off + lo, lh, (uint32_t)l, (uint32_t)(l >> 32), c, active);
   });
 }
 
@@ -358,7 +364,7 @@ __device__ __forceinline__ void flush_rows(float (&rowv)[NR][8], MetaFn meta, in
       uint32_t w0, w1;
       nib8_to_48(w, w0, w1);
       const uint32_t m = (uint32_t)row0 + (uint32_t)rm.pos;
-      store48(q_lo_blk + ((m >> 5) * kBlock6 + (m & 31) * 16) + q_off, w0, w1, tid * 8, active && (!RAG || rm.e >= 0));
+      store48(q_lo_blk + row_off6(m) + q_off, row_half6(m), w0, w1, tid * 8, active && (!RAG || rm.e >= 0));
     } else if constexpr (RAG) {
       if (active && rm.e >= 0) *reinterpret_cast<uint32_t*>(q_lo_blk + stamp_qlo_offset(row0 + rm.e, 0, Kpad) + q_off) = w;
     } else {
@@ -450,7 +456,7 @@ __device__ __forceinline__ void finish_top_row(const float (&top)[8], int level,
     } else {
       uint32_t w0, w1;
       nib8_to_48(w4, w0, w1);
-      store48(q_lo_row, w0, w1, c0, active);
+      store48(q_lo_row, false, w0, w1, c0, active);  // (a block's first row)
     }
     return;
   }

@@ -3,14 +3,19 @@
 // Algorithm "STaMP Linear", valid per output column by the commutation identity of section "Method"), bias and
 // the store of Y, all without leaving the registers.
 //
-// A wave owns 128 rows x 64 columns as 4 x 2 MFMA blocks of 32 x 32; lane (kg = lane / 32, l32 = lane % 32)
-// holds of block (mi, ni) the column l32 and the rows 32 mi + 8 q + 4 kg + j (register v = 4 q + j).  One
-// v_permlane32_swap per register pair exchanges the rows 8 q + 4 + j of lane group 0 with the rows 8 q + j of
-// lane group 1, after which each lane group holds WHOLE blocks of R = 8 .. 64 rows (Haar sub-trees) of its
-// column: lane group kg owns the blocks 2 t + kg of the wave tile, t < 64 / R.  The inverse butterflies are then
-// plain register arithmetic.  The weights are stored so that MFMA column l32 of block ni is output column
-// 2 l32 + ni of the wave's 64: a lane's two results are neighbours, one 4-byte (bf16) or 8-byte (fp32) store per
-// token, and the 32 lanes of a group write one contiguous 128- or 256-byte run.
+// A wave owns 128 rows x 64 columns as 4 x 2 blocks of 32 x 32 operand rows and columns, each 2 x 2 MFMA tiles of 16 x 16
+// (row tile th, column tile tc).  Lane 16 f + i holds column i of a tile and its rows 4 f + v, and the operand's rows are laid
+// out (row_off6) so that these are the rows 32 f + 8 mi + 4 th + v of the wave tile (register 8 tc + 4 th + v of block (mi, ni)).
+// One v_permlane16_swap per register pair exchanges tc = 1 of even f with tc = 0 of odd f, after which lane (kg = lane / 32,
+// l32 = lane % 32) holds the column l32 and 64 neighbouring rows 64 kg .. 64 kg + 63: WHOLE blocks of R = 8 .. 64 rows (Haar
+// sub-trees).  The inverse butterflies are then plain register arithmetic.  The weights are stored so that column l32 of block ni is
+// output column 2 l32 + ni of the wave's 64: a lane's two results are neighbours, one 4-byte (bf16) or 8-byte (fp32) store per
+// token, and the 32 lanes of a group write one contiguous 128- or 256-byte run.  (Without the swaps a lane has 32 rows of two
+// column pairs, enough for R up to 32; its runs of 64 bytes cost more than the swaps: GEMM of 2048 x 4096 -> 4096
+// to fp32 rows 34.6 us against 33.5.)
+// Per-block scales (GRP): MFMA blocks of 32 x 32, lane (kg, l32) holds the column l32 and the rows
+// 32 mi + 8 q + 4 kg + j (register 4 q + j); one v_permlane32_swap per register pair exchanges the rows 8 q + 4 + j of lane
+// group 0 with the rows 8 q + j of lane group 1, after which lane group kg owns the blocks 2 t + kg.
 #ifndef STAMP_EPILOGUE_REG_H_
 #define STAMP_EPILOGUE_REG_H_
 
@@ -19,19 +24,24 @@
 namespace stamp_gemm {
 
 // Register (mi, v) that holds, after the swaps, coefficient e (in-block position) of the lane's t-th block.
-template <int RL>
+template <int RL, bool GRP = false>
 struct RegMap {
   static constexpr int R = 1 << RL;
   static constexpr int nb = 64 / R;  // blocks per lane
   static_assert(RL >= 3 && RL <= 6, "blocks of 8 .. 64 rows");
   static constexpr int mi(int t, int e) {
+    if (!GRP) return ((t * R + e) >> 3) & 3;
     return RL == 6 ? ((e >> 5) + 2 * ((e >> 2) & 1)) : RL == 5 ? (2 * t + ((e >> 2) & 1)) : RL == 4 ? t : (t >> 1);
   }
   static constexpr int v(int t, int e) {
+    if (!GRP) return 8 * ((t * R + e) >> 5) + (e & 7);
     return RL >= 5   ? (4 * ((e >> 3) & 3) + (e & 3))
            : RL == 4 ? (4 * (((e >> 3) & 1) + 2 * ((e >> 2) & 1)) + (e & 3))
                      : (4 * (2 * (t & 1) + ((e >> 2) & 1)) + (e & 3));
   }
+  // lane group kg's t-th block of the wave tile
+  static constexpr int stride = GRP ? 2 : 1;
+  static STAMP_HD constexpr int block(int t, int kg) { return (GRP ? kg : kg * nb) + stride * t; }
 };
 
 // Four independent swaps in one statement: the wait states are needed once before the first and once after the last
@@ -42,6 +52,20 @@ __device__ __forceinline__ void swap32x4(float& x0, float& y0, float& x1, float&
       "v_permlane32_swap_b32 %6, %7\n\ts_nop 1"
       : "+v"(x0), "+v"(y0), "+v"(x1), "+v"(y1), "+v"(x2), "+v"(y2), "+v"(x3), "+v"(y3));
 }
+
+__device__ __forceinline__ void swap16x4(float& x0, float& y0, float& x1, float& y1, float& x2, float& y2, float& x3, float& y3) {
+  asm volatile(
+      "s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\tv_permlane16_swap_b32 %2, %3\n\tv_permlane16_swap_b32 %4, %5\n\t"
+      "v_permlane16_swap_b32 %6, %7\n\ts_nop 1"
+      : "+v"(x0), "+v"(y0), "+v"(x1), "+v"(y1), "+v"(x2), "+v"(y2), "+v"(x3), "+v"(y3));
+}
+// registers 8 tc + i (i = 4 th + v) of a block -> register 8 h + i: row i of what lane group 2 kg + h had, column l32
+__device__ __forceinline__ void columns16(float (&r)[16]) {
+#pragma unroll
+  for (int h = 0; h < 8; h += 4) swap16x4(r[h], r[8 + h], r[h + 1], r[9 + h], r[h + 2], r[10 + h], r[h + 3], r[11 + h]);
+}
+// row of the wave tile in register v of block (mi, .) after that, less 64 kg
+STAMP_HD constexpr int row16(int mi, int v) { return 32 * (v >> 3) + 8 * mi + (v & 7); }
 
 __device__ __forceinline__ void swap32(float& x, float& y) {
   // lanes 32..63 of x <-> lanes 0..31 of y.  Written as an asm statement: the builtin form is treated as
@@ -88,8 +112,14 @@ __device__ __forceinline__ void put_pair_at(char* base, uint32_t byte_off, float
   }
 }
 
+// accumulators of a 32 x 32 block: MFMA tiles 2 tc + th
+struct AccTiles {
+  f4 q[4];
+  __device__ __forceinline__ float operator[](int i) const { return q[i >> 2][i & 3]; }
+};
+
 // Operands of the epilogue that come from global memory: requested during the last K step of a tile.
-template <int EPI, int RL, bool RAG = false>
+template <int EPI, int RL, bool RAG = false, bool GRP = false>
 struct RegEpiOperands {
   static constexpr int nb = (EPI == 2) ? 64 / (1 << RL) : 1;
   f2 sw, bias, cs;
@@ -99,7 +129,7 @@ struct RegEpiOperands {
     const int l32 = lane & 31, kg = lane >> 5;
     const int n = nw + 2 * l32;  // Npad is a multiple of 256: always inside the padded arrays
     sw = *reinterpret_cast<const f2*>(a.sw + n);
-    bias = (a.bias != nullptr) ? *reinterpret_cast<const f2*>(a.bias + n) : (f2){0.0f, 0.0f};
+    bias = (EPI != 1 && a.bias != nullptr) ? *reinterpret_cast<const f2*>(a.bias + n) : (f2){0.0f, 0.0f};
     cs = a.g.asym ? *reinterpret_cast<const f2*>(a.colsum + n) : (f2){0.0f, 0.0f};
     if constexpr (EPI == 2 && !WITH_P) {
 #pragma unroll
@@ -108,7 +138,7 @@ struct RegEpiOperands {
       constexpr int R = 1 << RL;
 #pragma unroll
       for (int t = 0; t < nb; ++t) {
-        const int mrow = min(m0 + wm * 128 + (2 * t + kg) * R, a.M - 1);
+        const int mrow = min(m0 + wm * 128 + RegMap<RL, GRP>::block(t, kg) * R, a.M - 1);
         // P holds the first pk block sums of every sequence (all k of them unless the blocks beyond khi carry their
         // own, see blocks_reg); blocks beyond read a row that is there and is not used
         const int blk = mrow / R, pk = a.own_top ? a.g.khi : a.g.k;
@@ -174,9 +204,9 @@ __device__ __forceinline__ void dfs1d_reg(const float (&acc)[4][NI][16], float a
 }
 
 // 2-D: quadtree node (IY, IX) of level M (side 2^M); bands W, H, D at e = 4^M (1 + band) + IY 2^M + IX.
-template <int RB, int T, int M, int IY, int IX, typename Out>
+template <int RB, bool GRP, int T, int M, int IY, int IX, typename Out>
 __device__ __forceinline__ void dfs2d_reg(const float (&acc)[4][NI][16], float a0, float a1, const Out& o) {
-  using RM = RegMap<2 * RB>;
+  using RM = RegMap<2 * RB, GRP>;
   if constexpr (M == RB) {
     o.put(o.base + (typename Out::IDX)IY * o.row_stride + (typename Out::IDX)IX * o.tok_stride, a0, a1, 0);
     if constexpr ((IY & 1) && (IX & 1)) __builtin_amdgcn_sched_barrier(0);
@@ -194,10 +224,10 @@ __device__ __forceinline__ void dfs2d_reg(const float (&acc)[4][NI][16], float a
       t1[ni] = cW + cD;
       t3[ni] = cW - cD;
     }
-    dfs2d_reg<RB, T, M + 1, 2 * IY, 2 * IX, Out>(acc, t0[0] + t1[0], t0[1] + t1[1], o);
-    dfs2d_reg<RB, T, M + 1, 2 * IY, 2 * IX + 1, Out>(acc, t0[0] - t1[0], t0[1] - t1[1], o);
-    dfs2d_reg<RB, T, M + 1, 2 * IY + 1, 2 * IX, Out>(acc, t2[0] + t3[0], t2[1] + t3[1], o);
-    dfs2d_reg<RB, T, M + 1, 2 * IY + 1, 2 * IX + 1, Out>(acc, t2[0] - t3[0], t2[1] - t3[1], o);
+    dfs2d_reg<RB, GRP, T, M + 1, 2 * IY, 2 * IX, Out>(acc, t0[0] + t1[0], t0[1] + t1[1], o);
+    dfs2d_reg<RB, GRP, T, M + 1, 2 * IY, 2 * IX + 1, Out>(acc, t0[0] - t1[0], t0[1] - t1[1], o);
+    dfs2d_reg<RB, GRP, T, M + 1, 2 * IY + 1, 2 * IX, Out>(acc, t2[0] + t3[0], t2[1] + t3[1], o);
+    dfs2d_reg<RB, GRP, T, M + 1, 2 * IY + 1, 2 * IX + 1, Out>(acc, t2[0] - t3[0], t2[1] - t3[1], o);
   }
 }
 
@@ -213,15 +243,16 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
   if constexpr (T < NB) {
     constexpr int RL = IS2D ? 2 * RB : RB;
     constexpr int R = 1 << RL;
-    using RM = RegMap<RL>;
+    using RM = RegMap<RL, GRP>;
+    constexpr int TR = RM::stride * T * R;
     const StampGeom& g = a.g;
-    const int mrow = mrow0 + 2 * T * R;
+    const int mrow = mrow0 + TR;
     if (mrow < a.M && o.nvalid > 0) {
 #pragma unroll
       for (int e4 = 0; e4 < (GRP ? 0 : R); e4 += 4) {
-        const f4 rf = *reinterpret_cast<const f4*>(rowfac0 + 2 * T * R + e4);
+        const f4 rf = *reinterpret_cast<const f4*>(rowfac0 + TR + e4);
         f4 rz = {0.0f, 0.0f, 0.0f, 0.0f};
-        if constexpr (!SYM) rz = *reinterpret_cast<const f4*>(rowz0 + 2 * T * R + e4);
+        if constexpr (!SYM) rz = *reinterpret_cast<const f4*>(rowz0 + TR + e4);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int e = e4 + u;
@@ -239,7 +270,7 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
       // in the row table - it is the block's own coefficient 0, dequantized above like every other row.
       bool own;
       if constexpr (GRP) own = a.own_top != 0 && (mrow % g.s) / R >= g.khi;
-      else own = reinterpret_cast<const int*>(rowfac0)[256 + 2 * T * R] == 1;
+      else own = reinterpret_cast<const int*>(rowfac0)[256 + TR] == 1;
       const float bs0 = own ? acc[RM::mi(T, 0)][0][RM::v(T, 0)] * o.sw0 : P[T][0];
       const float bs1 = own ? acc[RM::mi(T, 0)][1][RM::v(T, 0)] * o.sw1 : P[T][1];
       o.off0 = bs0 + bias[0];
@@ -274,7 +305,7 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
         const int j = pr / g.R;
         const int bi = j / g.G, bj = j - bi * g.G;
         o.base = ((size_t)b * g.s + (size_t)(bi << RB) * g.gridW + (size_t)(bj << RB)) * a.N + n;
-        dfs2d_reg<RB, T, 0, 0, 0, RegOut<YBF16, VEC, false>>(acc, 0.0f, 0.0f, o);
+        dfs2d_reg<RB, GRP, T, 0, 0, 0, RegOut<YBF16, VEC, false>>(acc, 0.0f, 0.0f, o);
       }
     }
     blocks_reg<RB, IS2D, T + 1, NB, YBF16, VEC, SYM, RAG, GRP, NP>(a, acc, P, bias, cs, o, rowfac0, rowz0, mrow0, n, m0);
@@ -282,12 +313,12 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
 }
 
 // EPI 2: fused in-block inverse (RB = log2 of the block length in 1-D, of the block side in 2-D);
-// EPI 3: plans without a sequence transform (rows are tokens).
+// EPI 3: plans without a sequence transform (rows are tokens); EPI 1: dequantized fp32 rows.
 // accv: the wave's accumulators, 4 x NIW blocks; this call handles the column pair PAIR (blocks 2 PAIR, 2 PAIR + 1:
 // the 64 columns from nw on).
-template <int EPI, int RB, bool IS2D, bool YBF16, bool VEC, int NIW, int PAIR, bool SYM, bool RAG, bool GRP = false>
-__device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const v16f (&accv)[4][NIW], const uint8_t* row_info,
-                                                  const RegEpiOperands<EPI, (IS2D ? 2 * RB : RB), RAG>& eo, int m0, int nw,
+template <int EPI, int RB, bool IS2D, bool YBF16, bool VEC, int NIW, int PAIR, bool SYM, bool RAG, bool GRP = false, typename Acc = AccTiles>
+__device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const Acc (&accv)[4][NIW], const uint8_t* row_info,
+                                                  const RegEpiOperands<EPI, (IS2D ? 2 * RB : RB), RAG, GRP>& eo, int m0, int nw,
                                                   int wm, int lane) {
   const StampGeom& g = a.g;
   // single registers from here on (the accumulator tuples are dead after this copy)
@@ -295,21 +326,25 @@ __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const v16f 
 #pragma unroll
   for (int mi = 0; mi < 4; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
+    for (int ni = 0; ni < NI; ++ni) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mi][ni][v] = accv[mi][2 * PAIR + ni][v];
+      if constexpr (!GRP && EPI == 2) columns16(acc[mi][ni]);
+    }
   const int l32 = lane & 31, kg = lane >> 5;
   const float* s_rowfac = reinterpret_cast<const float*>(row_info);
   const int* s_rowdst = reinterpret_cast<const int*>(row_info + 1024);
   const float* s_rowz = reinterpret_cast<const float*>(row_info + 2048);
   const int n = nw + 2 * l32;
   const int nvalid = a.N - n;
-  if constexpr (EPI == 3) {
+  if constexpr (EPI == 1 || EPI == 3) {
 #pragma unroll
     for (int mi = 0; mi < 4; ++mi) {
 #pragma unroll
+      for (int ni = 0; ni < NI; ++ni) columns16(acc[mi][ni]);
+#pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int r0 = wm * 128 + mi * 32 + 8 * q + 4 * kg;
+        const int r0 = wm * 128 + 64 * kg + row16(mi, 4 * q);
         const f4 rf = *reinterpret_cast<const f4*>(s_rowfac + r0);
         const f4 rz = *reinterpret_cast<const f4*>(s_rowz + r0);
         const v4i rd = *reinterpret_cast<const v4i*>(s_rowdst + r0);
@@ -320,28 +355,41 @@ __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const v16f 
             c0 = __builtin_fmaf(-rz[j], eo.cs[0], c0);
             c1 = __builtin_fmaf(-rz[j], eo.cs[1], c1);
           }
-          if (rd[j] >= 0 && nvalid > 0)
-            put_pair<YBF16, VEC>(a.out, (size_t)rd[j] * a.N + n, __builtin_fmaf(c0 * rf[j], eo.sw[0], eo.bias[0]),
-                                 __builtin_fmaf(c1 * rf[j], eo.sw[1], eo.bias[1]), nvalid);
+          if (rd[j] >= 0 && nvalid > 0) {
+            if constexpr (EPI == 1) {  // (fp32 rows that the next kernel reads: kept in the caches)
+              float* const o = reinterpret_cast<float*>(a.out) + (size_t)rd[j] * a.ld_out + n;
+              const float y0 = (c0 * rf[j]) * eo.sw[0], y1 = (c1 * rf[j]) * eo.sw[1];
+              if constexpr (VEC) {
+                *reinterpret_cast<f2*>(o) = f2{y0, y1};
+              } else {
+                o[0] = y0;
+                if (nvalid > 1) o[1] = y1;
+              }
+            } else {
+              put_pair<YBF16, VEC>(a.out, (size_t)rd[j] * a.N + n, __builtin_fmaf(c0 * rf[j], eo.sw[0], eo.bias[0]),
+                                   __builtin_fmaf(c1 * rf[j], eo.sw[1], eo.bias[1]), nvalid);
+            }
+          }
         }
       }
     }
   } else {
     constexpr int RL = IS2D ? 2 * RB : RB;
-    using RM = RegMap<RL>;
-    constexpr int R = RM::R, nb = RM::nb;
-    // lane group kg takes the rows 8 q + 4 + j of its own blocks from the other group
+    using RM = RegMap<RL, GRP>;
+    constexpr int R = RM::R;
+    if constexpr (GRP) {
+      // lane group kg takes the rows 8 q + 4 + j of its own blocks from the other group
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
+      for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-      for (int t = 0; t < nb; ++t)
+        for (int t = 0; t < RM::nb; ++t)
 #pragma unroll
-        for (int e = 0; e < R; ++e)
-          if ((e & 7) == 0)  // rows e .. e + 3 against e + 4 .. e + 7
+          for (int e = 0; e < R; e += 8)  // rows e .. e + 3 against e + 4 .. e + 7
             swap32x4(acc[RM::mi(t, e)][ni][RM::v(t, e)], acc[RM::mi(t, e + 4)][ni][RM::v(t, e + 4)],
                      acc[RM::mi(t, e + 1)][ni][RM::v(t, e + 1)], acc[RM::mi(t, e + 5)][ni][RM::v(t, e + 5)],
                      acc[RM::mi(t, e + 2)][ni][RM::v(t, e + 2)], acc[RM::mi(t, e + 6)][ni][RM::v(t, e + 6)],
                      acc[RM::mi(t, e + 3)][ni][RM::v(t, e + 3)], acc[RM::mi(t, e + 7)][ni][RM::v(t, e + 7)]);
+    }
     // Every load requested before the epilogue (its operands, the next tile's row factors) has to be complete
     // here, stated in a form the compiler's wait-count bookkeeping sees: the uses below sit under branches, and a
     // load it believed pending at the end of the tile would make it wait for ALL loads inside the next main loop.
@@ -366,20 +414,20 @@ __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const v16f 
       o.tok_stride = (size_t)a.N;
       o.row_stride = (size_t)g.gridW * a.N;
     }
-    blocks_reg<RB, IS2D, 0, nb, YBF16, VEC, SYM, RAG, GRP>(a, acc, eo.P, eo.bias, eo.cs, o, s_rowfac + wm * 128 + kg * R, s_rowz + wm * 128 + kg * R,
-                                            m0 + wm * 128 + kg * R, n, m0);
+    const int r0 = wm * 128 + RM::block(0, kg) * R;
+    blocks_reg<RB, IS2D, 0, RM::nb, YBF16, VEC, SYM, RAG, GRP>(a, acc, eo.P, eo.bias, eo.cs, o, s_rowfac + r0, s_rowz + r0, m0 + r0, n, m0);
   }
 }
 
 // ODD: a fused-mode kernel for odd d_out.  (A branch between the two forms inside one fused kernel costs 50 to 110 spilled
 // registers: 2048 tokens, 4096 -> 11008, 3 levels, first token left out: 67.8 us against 64.4.)
 template <int EPI, int RB, bool IS2D, bool YBF16, int NIW = NI, int PAIR = 0, bool SYM = false, bool RAG = false, bool ODD = false>
-__device__ __forceinline__ void epilogue_reg(const GemmArgs& a, const v16f (&acc)[4][NIW], const uint8_t* row_info,
+__device__ __forceinline__ void epilogue_reg(const GemmArgs& a, const AccTiles (&acc)[4][NIW], const uint8_t* row_info,
                                              const RegEpiOperands<EPI, (IS2D ? 2 * RB : RB), RAG>& eo, int m0, int nw, int wm,
                                              int lane) {
   // pairs of columns are stored as one word when d_out is even (the pair then never straddles the end)
   if constexpr (EPI == 2) epilogue_reg_impl<EPI, RB, IS2D, YBF16, !ODD, NIW, PAIR, SYM, RAG>(a, acc, row_info, eo, m0, nw, wm, lane);
-  else if ((a.N & 1) == 0) epilogue_reg_impl<EPI, RB, IS2D, YBF16, true, NIW, PAIR, SYM, RAG>(a, acc, row_info, eo, m0, nw, wm, lane);
+  else if ((a.N & 1) == 0 && (EPI == 3 || (a.ld_out & 1) == 0)) epilogue_reg_impl<EPI, RB, IS2D, YBF16, true, NIW, PAIR, SYM, RAG>(a, acc, row_info, eo, m0, nw, wm, lane);
   else epilogue_reg_impl<EPI, RB, IS2D, YBF16, false, NIW, PAIR, SYM, RAG>(a, acc, row_info, eo, m0, nw, wm, lane);
 }
 

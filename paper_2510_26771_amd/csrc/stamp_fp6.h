@@ -17,6 +17,26 @@ constexpr int kBlock6 = 3 * kPart;            // a 32-row block of one K step: 3
 constexpr int kStageB6 = 4 * kBlock6;         // 128 columns: 12 KB
 constexpr int kStageA6 = 2 * kStageB6;        // 24 KB
 
+// Row r of activations: which of its lane's two operands (tiles of 16 rows) it is
+STAMP_HD bool row_half6(uint32_t r) { return (r >> 2) & 1; }
+// row of a 256-row tile -> byte of its lane in lane group 0, K step 0: bits 3 and 4 choose the block, 0, 1, 5 and 6 the lane
+STAMP_HD uint32_t row_off6(uint32_t r) {
+  return (((r >> 5) & 4) + ((r >> 3) & 3)) * (uint32_t)kBlock6 + (((r >> 3) & 12) + (r & 3)) * 16;
+}
+// row of a block of 8-bit rows, which stand by themselves: bits 0, 1, 3 and 4 choose the lane
+STAMP_HD uint32_t row_lane6(uint32_t r) { return (((r >> 1) & 12) + (r & 3)) * 16; }
+// byte offset of the 32 channels from c on; K steps are kt_bytes apart
+STAMP_HD uint32_t chan_off6(uint32_t c, uint32_t kt_bytes) { return (c >> 7) * kt_bytes + ((c >> 5) & 3) * 256; }
+
+// a fragment's 24 bytes -> their places; dst = its lane's place in part 0
+__device__ __forceinline__ void store_frag6(uint8_t* dst, bool half, const uint64_t (&part)[3]) {
+#pragma unroll
+  for (int w = 0; w < 3; ++w) {
+    const int off = (half ? 24 : 0) + w * 8;
+    *reinterpret_cast<uint64_t*>(dst + (off >> 4) * kPart + (off & 15)) = part[w];
+  }
+}
+
 // eight two's-complement nibbles -> eight sign-magnitude 6-bit fields
 __device__ __forceinline__ void nib8_to_48(uint32_t w, uint32_t& w0, uint32_t& w1) {
   const uint32_t s = w & 0x88888888u, sg = s >> 3;

@@ -9,14 +9,20 @@
 // holds acc / 64 EXACTLY, where acc is the integer sum the int8 pipeline computes: same result bit for
 // bit, at twice the matrix rate per clock.  The factor 64 is folded into the row scale.
 //
+// The products are v_mfma_f32_16x16x128_f8f6f4: as many operations per clock as the 32 x 32 x 64 form (34 cycles against 33 for
+// the same product), but its accumulators are read and written half as often, and the chip, which lowers its clock under this
+// load, draws less power: 18.0 against 20.2 ns per 2 * 65536 operations and SIMD with nothing else running (random codes).  GEMM of
+// 8 x 4096 x 4096 -> 4096: 268 us with 32 x 32 x 64, 246 with this; 4 x 8192 x 8192 -> 28672: 2973, 2815.
+//
 // Operand layout: the 32 codes that one lane feeds to one MFMA (channels 32 f .. 32 f + 31 of a K step of
-// 128 channels, f = 0..3) are a little-endian stream of 6-bit fields = 24 bytes.  MFMA half k (0, 1) of a
-// step consumes channels [64 k, 64 k + 64): lane group kg = lane / 32 takes f = 2 k + kg, so over a step a
-// lane needs fragments kg and 2 + kg of its row: 48 bytes, kept as three 16-byte parts.  Per block of 32
-// rows (columns) and K step: [3 parts][2 kg][32 rows][16 bytes] = 3 KB, so that the 64 lanes of a wave read
+// 128 channels, f = lane / 16) are a little-endian stream of 6-bit fields = 24 bytes.  A block of 32 rows (columns) is two
+// tiles of 16: lane 16 f + i has fragment f of row i of both, 48 bytes, kept as three 16-byte parts.  Per block
+// and K step: [3 parts][64 lanes][16 bytes] = 3 KB, so that the 64 lanes of a wave read
 // 1 KB of consecutive addresses with one 16-byte LDS read (no bank conflicts, no swizzle; 16-byte reads
 // move 1.75x the bytes per clock of 8-byte ones on this chip, and at 8 bytes the fragment reads of a step
-// take as long as its MFMAs).  Per tile and K step, activations: 8 blocks = 24 KB, weights: 4 blocks = 12 KB
+// take as long as its MFMAs).  Weights: tile = column / 16 of the block.  Activations (row_off6): the
+// rows are dealt to blocks, tiles and lanes so that a lane's results, rows 4 f + v of every tile, are 32 neighbouring rows
+// (stamp_epilogue_reg.h).  Per tile and K step, activations: 8 blocks = 24 KB, weights: 4 blocks = 12 KB
 // per 128 columns.  The global image equals the LDS image, so a K step is staged by plain asynchronous
 // 16-byte copies.
 #include <type_traits>
@@ -30,14 +36,14 @@ namespace {
 using namespace stamp_gemm;
 
 // q_lo (tiled [Mpad/256][KT][256 rows][64 bytes], channels in natural order) -> FP6 operand layout.
-// One workgroup per (row tile, K step); thread = (row, kg): fragments kg and 2 + kg, three 16-byte stores.
+// One workgroup per (row tile, K step); thread = a fragment of two rows, three 16-byte stores.
 // The first nhi blocks convert the 8-bit rows (stamp_hi6.h).
 __global__ __launch_bounds__(512) void k_repack6(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, int nhi, StampHi6Pack hp) {
   if ((int)blockIdx.x < nhi) {
     hi6_pack(hp, (int)blockIdx.x * 512 + (int)threadIdx.x);
     return;
   }
-  repack6_rows(q_lo, a6, blockIdx.x - nhi, threadIdx.x & 255, threadIdx.x >> 8);
+  repack6_rows(q_lo, a6, blockIdx.x - nhi, threadIdx.x);
 }
 
 // The same from rows in STaMP order to rows in the block order of StampRag (rows without a coefficient: zeros).
@@ -48,22 +54,18 @@ __global__ __launch_bounds__(512) void k_repack6_rag(const uint8_t* __restrict__
     return;
   }
   const int blk = blockIdx.x - nhi, mt = blk / KT, kt = blk - mt * KT;
-  const int row = threadIdx.x & 255, kg = threadIdx.x >> 8;
-  const int m = mt * 256 + row, R = 1 << rg.r;
-  int slot = -1, b = 0;
-  if (m < M) {
-    const int g = m / R;
-    b = g / rg.nb;
-    slot = stamp_rag_slot(rg, g - b * rg.nb, m - g * R);
+  const int u = threadIdx.x, m0 = mt * 256 + repack6_row(u), R = 1 << rg.r;
+  u4 w[2] = {};
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int m = m0 + 4 * i, g = m / R, b = g / rg.nb;
+    const int slot = m < M ? stamp_rag_slot(rg, g - b * rg.nb, m - g * R) : -1;
+    if (slot >= khi) {
+      const size_t ms = (size_t)b * s + slot;
+      w[i] = *reinterpret_cast<const u4*>(q_lo + (((ms >> 8) * KT + kt) * 256 + (ms & 255)) * 64 + repack6_frag(u) * 16);
+    }
   }
-  u4 w0 = {0u, 0u, 0u, 0u}, w1 = w0;
-  if (slot >= khi) {
-    const size_t ms = (size_t)b * s + slot;
-    const uint8_t* src = q_lo + (((ms >> 8) * KT + kt) * 256 + (ms & 255)) * 64 + kg * 16;
-    w0 = *reinterpret_cast<const u4*>(src);
-    w1 = *reinterpret_cast<const u4*>(src + 32);
-  }
-  repack6_store(a6 + (size_t)blk * kStageA6 + (row >> 5) * kBlock6 + kg * 512 + (row & 31) * 16, w0, w1);
+  repack6_store(a6 + (size_t)blk * kStageA6 + (u >> 6) * kBlock6 + (u & 63) * 16, w[0], w[1]);
 }
 
 // Plan-time weight codes in that layout: per output channel n, code = rne(W_cn * (7 / max)) as in
@@ -102,12 +104,11 @@ __global__ __launch_bounds__(256) void k_w_quant6(const float* __restrict__ W, c
   }
   const int KT = Kpad >> 7;
   const int kt = frag >> 2, f = frag & 3;
-  // fragment f is the (f >> 1)-th half of the 48-byte stream of lane group kg = f & 1
   // output column n = 64 w + 2 l + ni sits in the 32-column block 2 w + ni at row l: a lane of the GEMM then holds
   // two neighbouring output columns (stamp_epilogue_reg.h)
   const int blk = ((n & 127) >> 6) * 2 + (n & 1), rowb = (n & 63) >> 1;
-  uint8_t* dst = b6 + ((size_t)(n >> 7) * KT + kt) * kStageB6 + (size_t)blk * kBlock6 + (f & 1) * 512 + rowb * 16;
-  store_frag(dst, f, part);
+  uint8_t* dst = b6 + ((size_t)(n >> 7) * KT + kt) * kStageB6 + (size_t)blk * kBlock6 + f * 256 + (rowb & 15) * 16;
+  store_frag6(dst, rowb >> 4, part);
 }
 
 }  // namespace

@@ -27,8 +27,8 @@ using namespace stamp_gemm;
 //
 // Inside a step nothing waits for what it has just asked for: the LDS reads of an activation block fly under the
 // MFMAs of the block before it, the one workgroup barrier sits before the last block (whose MFMAs cover the reads
-// of the next step's first fragments), and the six loads of a stage request are issued one at a time among MFMAs (three in that last
-// block, three in the first two blocks of the next step).
+// of the next step's first fragments), and the loads of a stage request are issued one at a time among MFMAs, three in that last
+// block, the others in the next step.
 //
 // WAVES = 4: tile 128 x 256, one wave on every SIMD, 36 KB per K step; the same loop, nine loads per wave and step.  A tile
 // takes 0.64 of the time of a 256 x 256 one (8.5 us + 0.455 us per K step against 12.8 + 0.72, all CUs busy): for shapes that
@@ -70,23 +70,29 @@ __device__ __forceinline__ void hi_place_info(const GemmArgs& a, int tile, int p
   fac = a.scales[row] * (RAG ? 1.0f : haar_norm_dev(g.r + up, g.is2d));
   if (g.asym) rz = a.scales[zeros_off + row] - (slot < g.khi ? 128.0f : 8.0f);
 }
-// The 8-bit rows' block -> sums of the lane's blocks (eo.P); the token left out -> Y.  acch: register v is row 8 (v / 4) + 4 kg + v % 4,
-// i.e. h of a place in registers 0..7, l in 8..15.  Same operations in the same order as k_hi6.
+// The 8-bit rows' block -> sums of the lane's blocks (eo.P); the token left out -> Y.  acch: the row
+// tile of h (th = 0) and that of l, of 16 places each.  Same operations in the same order as k_hi6.
 template <int RL, bool YBF16, bool SYM, bool RAG, typename Eo>
-__device__ __forceinline__ void hi_block_sums(const GemmArgs& a, const v16f (&acch)[2], const float* info, Eo& eo, int tile, int nw, int lane) {
+__device__ __forceinline__ void hi_block_sums(const GemmArgs& a, const AccTiles (&acch)[2], const float* info, Eo& eo, int tile, int nw, int lane) {
   constexpr int lognb = 7 - RL, nb = 1 << lognb;
   const StampHiTiles& t = a.ht;
   const int l32 = lane & 31, kg = lane >> 5, n = nw + 2 * l32;
   float val[kHiPlaces][2];
 #pragma unroll
-  for (int ni = 0; ni < 2; ++ni)
+  for (int ni = 0; ni < 2; ++ni) {
+    float r[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) r[v] = acch[ni][v];
+    columns16(r);  // r[8 h + 4 th + v]: place 8 kg + 4 h + v of column l32
 #pragma unroll
     for (int v = 0; v < 8; ++v) {
-      float x = __builtin_fmaf(16.0f, acch[ni][v], acch[ni][v + 8]) * 64.0f, y = x;
-      swap32(x, y);  // x: lane group 0's row, y: lane group 1's, in both
-      val[8 * (v >> 2) + (v & 3)][ni] = x;
-      val[8 * (v >> 2) + 4 + (v & 3)][ni] = y;
+      const int i = 8 * (v >> 2) + (v & 3);
+      float x = __builtin_fmaf(16.0f, r[i], r[i + 4]) * 64.0f, y = x;
+      swap32(x, y);  // x: lane group 0's place, y: lane group 1's, in both
+      val[v][ni] = x;
+      val[8 + v][ni] = y;
     }
+  }
 #pragma unroll
   for (int p = 0; p < kHiPlaces; ++p) {
     const float fac = info[p], rz = SYM ? 0.0f : info[kHiPlaces + p];
@@ -142,7 +148,7 @@ __device__ __forceinline__ void hi_block_sums(const GemmArgs& a, const v16f (&ac
 #pragma unroll
   for (int q = 0; q < nb / 2; ++q)
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni) eo.P[q][ni] = kg ? val[2 * q + 1][ni] : val[2 * q][ni];
+    for (int ni = 0; ni < 2; ++ni) eo.P[q][ni] = kg ? val[RegMap<RL>::block(q, 1)][ni] : val[RegMap<RL>::block(q, 0)][ni];
 }
 
 // tile of position sid in the walk: 8 M-tiles, then the next N-tile, group of 8 M-tiles after group
@@ -171,7 +177,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
   constexpr int nA = kStageA / (NT * 16), nB = 2 * kStageB6 / (NT * 16);  // 16-byte chunks per thread and step
   constexpr int kLoadsPerStep = nA + nB + (HI ? 1 : 0);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
   // wave tile: rows [128 wm, +128), columns [32 NIW wn, +32 NIW)
   const int wm = wave >> 2, wn = wave & 3;
   const int KT = a.Kpad / BK;
@@ -187,11 +193,19 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
   // global image = LDS image: chunk q = i * NT + tid of an operand's stage goes to byte 16 q.  The
   // weight stage is two column tiles of 128 (KT * 12 KB apart in memory): chunks 0..767 and 768..1535;
   // the boundary falls between waves, so the source tile of a pass is wave-uniform.  Addresses are a
-  // wave-uniform base (tile, K step, pass) plus this thread's constant 32-bit offset.
-  const uint32_t off16 = (uint32_t)tid * 16u;
+  // wave-uniform base (tile, K step, pass, wave) plus the lane's 32-bit offset.
+  // (the lane number is read anew for every tile and every epilogue, so that nothing per lane is live across an epilogue, which has no
+  // register to spare: a value kept in scratch memory would be reloaded behind all stores)
+  auto lane_now = []() __attribute__((always_inline)) {
+    uint32_t l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+  };
+  uint32_t lane16 = lane_now() * 16u;
+  const uint32_t wave1k = (uint32_t)wave * 1024u;
   // cursor of the requests: request rq_kt of the tile at position rq_pos of this workgroup's walk (all scalar).  The
   // loads address memory through two buffer descriptors (the tile's activation panel; its two weight panels, KT * 12 KB
-  // apart) + a scalar byte offset + this thread's constant 32-bit offset: no vector address arithmetic per load.
+  // apart) + a scalar byte offset + the lane's 32-bit offset: no vector address arithmetic per load.
   // K step of a tile's first request.  The workgroups of an XCD that share an operand panel (same row or column of
   // the XCD's 8 x 4 window of tiles) ask for a line at the same moment when they walk K in step: one misses L2, the
   // others wait on the same miss.  Started a few K steps apart (every tile walks all KT steps once, from its own
@@ -220,9 +234,9 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
   // fixes its addresses and advances the cursor, rq_issue<i> issues its i-th load: the
   // main loop spreads them among its MFMAs (eight waves issuing all their loads at once keep the address unit busy
   // for several hundred cycles, during which none of them can issue anything else).
-  // Of a request's six loads three go out among the MFMAs of the step's last block, the others in the next step: two
-  // in its first block (rq_tail2: still to be issued), the last before its second block (rq_tail3)
-  bool rq_tail2 = false, rq_tail3 = false;
+  // Three of a request's loads go out among the MFMAs of the step's last block, the others in the next step (rq_tail: still to be
+  // issued), with two MFMAs or more between any two: one load keeps the address unit busy for 16 cycles, an MFMA the matrix pipe for 17.
+  bool rq_tail = false;
   uint8_t* rq_so = nullptr;
   [[maybe_unused]] uint32_t rq_oh = 0;
   uint32_t rq_oa = 0, rq_ob = 0;  // byte offsets of the request's K step in the activation / weight panels
@@ -241,8 +255,8 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
       }
     }
     rq_so = smem + rq_stg * kStage6 + wave * 1024;
-    rq_oa = (uint32_t)rq_kk * (uint32_t)kStageA6;
-    rq_ob = (uint32_t)rq_kk * (uint32_t)kStageB6;
+    rq_oa = (uint32_t)rq_kk * (uint32_t)kStageA6 + wave1k;
+    rq_ob = (uint32_t)rq_kk * (uint32_t)kStageB6 + wave1k;
     if constexpr (HI) rq_oh = (uint32_t)rq_kk * (uint32_t)kBlock6;
     rq_kk = (rq_kk == KT - 1) ? 0 : rq_kk + 1;
     rq_stg = (rq_stg == kNumStage6 - 1) ? 0 : rq_stg + 1;
@@ -251,44 +265,50 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
   auto rq_issue = [&](auto i_tag) __attribute__((always_inline)) {
     constexpr int li = decltype(i_tag)::value;
     if constexpr (li < nA) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rdA, (void __attribute__((address_space(3)))*)(rq_so + li * (NT * 16)), 16, off16,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rdA, (void __attribute__((address_space(3)))*)(rq_so + li * (NT * 16)), 16, lane16,
                                                rq_oa + (uint32_t)(li * (NT * 16)), 0, 0);
     } else if constexpr (li >= nA + nB) {
       // three waves' worth: the fourth asks for the first kilobyte again, so that every wave counts the same number of loads
       const int part = (wave % 3) * kPart;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rdH, (void __attribute__((address_space(3)))*)(rq_so - wave * 1024 + kStageAB + part), 16,
-                                               (uint32_t)lane * 16u, rq_oh + (uint32_t)part, 0, 0);
+                                               lane16, rq_oh + (uint32_t)part, 0, 0);
     } else {
       constexpr int i = li - nA;
       // chunk i * NT + tid of the 1536: column tile 1 (KT stages further on) from chunk 768 on (a whole number of waves)
       const bool half = (i * NT + wave * 64) >= 768;
       const uint32_t ob = rq_ob + (half ? (uint32_t)KT * (uint32_t)kStageB6 + (uint32_t)(i * NT * 16 - 768 * 16) : (uint32_t)(i * NT * 16));
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rdB, (void __attribute__((address_space(3)))*)(rq_so + kStageA + i * (NT * 16)), 16,
-                                               off16, ob, 0, 0);
+                                               lane16, ob, 0, 0);
     }
   };
-  static_assert(nA + nB == (WAVES == 8 ? 6 : 9), "the main loop spreads six (nine) loads per wave and step");
-  // load i, and with four waves load i + 3 as well
-  auto rq_issue2 = [&](auto i_tag) __attribute__((always_inline)) {
-    rq_issue(i_tag);
-    if constexpr (WAVES == 4) rq_issue(std::integral_constant<int, decltype(i_tag)::value + 3>{});
-    if constexpr (HI && decltype(i_tag)::value == 5) rq_issue(std::integral_constant<int, 9>{});
+  static_assert(kLoadsPerStep <= 10, "the main loop has places for ten loads per wave and step");
+  // loads FROM .. of the request
+  auto rq_rest = [&](auto from_tag) __attribute__((always_inline)) {
+    constexpr int from = decltype(from_tag)::value;
+    auto one = [&](auto i) __attribute__((always_inline)) {
+      if constexpr (i.value >= from && i.value < kLoadsPerStep) rq_issue(i);
+    };
+    one(std::integral_constant<int, 0>{});
+    one(std::integral_constant<int, 1>{});
+    one(std::integral_constant<int, 2>{});
+    one(std::integral_constant<int, 3>{});
+    one(std::integral_constant<int, 4>{});
+    one(std::integral_constant<int, 5>{});
+    one(std::integral_constant<int, 6>{});
+    one(std::integral_constant<int, 7>{});
+    one(std::integral_constant<int, 8>{});
+    one(std::integral_constant<int, 9>{});
   };
   auto request_next = [&]() {
     rq_begin();
-    rq_issue(std::integral_constant<int, 0>{});
-    rq_issue(std::integral_constant<int, 1>{});
-    rq_issue(std::integral_constant<int, 2>{});
-    rq_issue2(std::integral_constant<int, 3>{});
-    rq_issue2(std::integral_constant<int, 4>{});
-    rq_issue2(std::integral_constant<int, 5>{});
+    rq_rest(std::integral_constant<int, 0>{});
   };
 
-  // LDS byte addresses of part 0 of this lane's 48 bytes in stage 0: 32-row block, then lane * 16
+  // LDS byte addresses of part 0 of a wave's 48 bytes in stage 0: 32-row block (then lane * 16)
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)smem;
-  const uint32_t adrA0 = (uint32_t)((wm * 4) * kBlock6 + lane * 16);
-  const uint32_t adrH0 = (uint32_t)(kStageAB + lane * 16);
-  const uint32_t adrB0 = (uint32_t)(kStageA + (wn >> 1) * kStageB6 + ((wn & 1) * 2) * kBlock6 + lane * 16);
+  const uint32_t adrA0 = (uint32_t)((wm * 4) * kBlock6);
+  const uint32_t adrH0 = (uint32_t)kStageAB;
+  const uint32_t adrB0 = (uint32_t)(kStageA + (wn >> 1) * kStageB6 + ((wn & 1) * 2) * kBlock6);
 
   // ---- prologue: stages 0 and 1 requested, landed and published by a barrier; stage 2 requested ----
   request_next();
@@ -322,8 +342,8 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
   int stg = 0;     // stage of the step about to be multiplied
   int rbuf = 0;    // row-info buffer of the current tile
 
-  // Fragment registers.  A lane's 48 bytes of one 32-row block and K step are the two 24-byte MFMA operands of the
-  // step's halves, read as three 16-byte parts.  The parts of a fragment must land in 12 CONSECUTIVE registers (the
+  // Fragment registers.  A lane's 48 bytes of one 32-row block and K step are the 24-byte MFMA operands of the block's
+  // two tiles of 16 rows, read as three 16-byte parts.  The parts of a fragment must land in 12 CONSECUTIVE registers (the
   // first operand is registers 0..5, the second 6..11), which the register allocator does not arrange for separate
   // asm outputs (it copies parts into fresh tuples and runs out of registers); the fragments therefore live in fixed
   // registers v184..v255: two activation sets (block mi + 1 is read while block mi is multiplied) and the weights'
@@ -340,13 +360,13 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
 #define STAMP_RD_HS(base, off) STAMP_RD3(Hs, "v[172:177]", "v[178:183]", "v[172:175]", "v[176:179]", "v[180:183]", base, off)
 #define STAMP_WAIT_HS(cnt) STAMP_WAIT1(cnt, Hs, "v[172:177]", "v[178:183]")
 #define STAMP_RD_AS1(base, off) STAMP_RD3(As1, "v[196:201]", "v[202:207]", "v[196:199]", "v[200:203]", "v[204:207]", base, off)
-  // activation block 0 and the two weight blocks of a step in one statement, parts 0 and 1 of all three first (the
-  // first MFMA half's operands), then the parts 2
+  // activation block 0 and the two weight blocks of a step in one statement, what the first MFMA takes first, the second weight
+  // block last
 #define STAMP_RD9(fa, fb0, fb1, AH0, AH1, B0H0, B0H1, B1H0, B1H1, A0, A1, A2, B00_, B01_, B02_, B10_, B11_, B12_, basea, baseb)         \
   asm volatile("ds_read_b128 " A0 ", %6 offset:0\n\tds_read_b128 " A1 ", %6 offset:%8\n\t"                                          \
                "ds_read_b128 " B00_ ", %7 offset:0\n\tds_read_b128 " B01_ ", %7 offset:%8\n\t"                                      \
-               "ds_read_b128 " B10_ ", %7 offset:%10\n\tds_read_b128 " B11_ ", %7 offset:%11\n\t"                                   \
-               "ds_read_b128 " A2 ", %6 offset:%9\n\tds_read_b128 " B02_ ", %7 offset:%9\n\tds_read_b128 " B12_ ", %7 offset:%12"   \
+               "ds_read_b128 " A2 ", %6 offset:%9\n\tds_read_b128 " B02_ ", %7 offset:%9\n\t"                                       \
+               "ds_read_b128 " B10_ ", %7 offset:%10\n\tds_read_b128 " B11_ ", %7 offset:%11\n\tds_read_b128 " B12_ ", %7 offset:%12" \
                : "=&{" AH0 "}"(fa.h0), "=&{" AH1 "}"(fa.h1), "=&{" B0H0 "}"(fb0.h0), "=&{" B0H1 "}"(fb0.h1), "=&{" B1H0 "}"(fb1.h0),  \
                  "=&{" B1H1 "}"(fb1.h1)                                                                                              \
                : "v"(basea), "v"(baseb), "n"(kPart), "n"(2 * kPart), "n"(kBlock6), "n"(kBlock6 + kPart), "n"(kBlock6 + 2 * kPart))
@@ -369,32 +389,55 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
     const int m0 = tm * BMW, n0 = tn * BN6;
     const int nw = n0 + wn * (32 * NIW);
 
-    v16f acc[4][NIW];
+    AccTiles acc[4][NIW];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < NIW; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+        for (int q = 0; q < 4; ++q) acc[i][j].q[q] = (f4){0.0f, 0.0f, 0.0f, 0.0f};
 
-    [[maybe_unused]] v16f acch[NIW];  // HI: the 8-bit rows' block
+    [[maybe_unused]] AccTiles acch[NIW];  // HI: the 8-bit rows' block
     [[maybe_unused]] const bool has_hi = HI && hi_tile_has(a.ht, tm);
     if constexpr (HI) {
 #pragma unroll
       for (int j = 0; j < NIW; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acch[j][v] = 0.0f;
+        for (int q = 0; q < 4; ++q) acch[j].q[q] = (f4){0.0f, 0.0f, 0.0f, 0.0f};
     }
     [[maybe_unused]] Frag Hs;
     Frag As0, As1, B00, B01, B10, B11;  // per tile: no fragment is carried across the epilogue
-    // the four MFMAs of activation block mi: both halves against both weight blocks
-    auto mfma4 = [&](const Frag& A, const Frag& W0, const Frag& W1, auto mi_tag) __attribute__((always_inline)) {
-      constexpr int mi = decltype(mi_tag)::value;
-      acc[mi][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)A.h0), widen((v6i)W0.h0), acc[mi][0], 2, 2, 0, 0, 0, 0);
-      acc[mi][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)A.h0), widen((v6i)W1.h0), acc[mi][1], 2, 2, 0, 0, 0, 0);
-      acc[mi][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)A.h1), widen((v6i)W0.h1), acc[mi][0], 2, 2, 0, 0, 0, 0);
-      acc[mi][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)A.h1), widen((v6i)W1.h1), acc[mi][1], 2, 2, 0, 0, 0, 0);
+    // row tile th of an activation block against column tile tc of a weight block
+    auto mfma = [&](f4& c, const u6& A, const u6& W) __attribute__((always_inline)) {
+      c = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(widen((v6i)A), widen((v6i)W), c, 2, 2, 0, 0, 0, 0);
     };
+    // The eight MFMAs of an activation block; each shares an operand with the one before.  after(i): what goes between the i-th and the next
+    auto mfma8 = [&](AccTiles (&c)[NIW], const Frag& A, const Frag& W0, const Frag& W1, auto after) __attribute__((always_inline)) {
+      auto then = [&](auto i) __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        after(i);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      mfma(c[0].q[0], A.h0, W0.h0);
+      mfma(c[0].q[1], A.h1, W0.h0);
+      then(std::integral_constant<int, 2>{});
+      mfma(c[0].q[3], A.h1, W0.h1);
+      mfma(c[0].q[2], A.h0, W0.h1);
+      then(std::integral_constant<int, 4>{});
+      mfma(c[1].q[2], A.h0, W1.h1);
+      mfma(c[1].q[3], A.h1, W1.h1);
+      then(std::integral_constant<int, 6>{});
+      mfma(c[1].q[1], A.h1, W1.h0);
+      mfma(c[1].q[0], A.h0, W1.h0);
+    };
+    // load i of the request of the step before, if it has that many
+    auto tail = [&](auto i) __attribute__((always_inline)) {
+      constexpr int li = decltype(i)::value;
+      if constexpr (li < kLoadsPerStep) {
+        if (rq_tail) rq_issue(i);
+      }
+    };
+    constexpr int kFirst = 3;  // loads of a request in the step itself
 
     // Step kt (pb = 0: weights in B00, B01, the next step's go to B10, B11; pb = 1: the other way round).  On entry
     // the reads of the step's weights and of activation block 0 have been issued (by the head of the tile or by the
@@ -408,62 +451,69 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
       constexpr int pb = decltype(pb_tag)::value;
       const uint32_t sa = lds0 + (uint32_t)(stg * kStage6);
       __builtin_amdgcn_sched_barrier(0);
-      STAMP_RD_AS1(sa + adrA0, 1 * kBlock6);
-      // block 0: of the 12 reads in flight the first 4 feed the first MFMA, 6 the second, 8 the third, 9 the fourth
+      STAMP_RD_AS1(sa + adrA0 + lane16, 1 * kBlock6);
+      // block 0: of the 12 reads in flight the first 4 feed the first MFMA, 6 the next three, 9 the others
       if constexpr (pb == 0) {
         STAMP_WAIT2(8, As0.h0, "v[184:189]", B00.h0, "v[208:213]");
-        acc[0][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h0), widen((v6i)B00.h0), acc[0][0], 2, 2, 0, 0, 0, 0);
+        mfma(acc[0][0].q[0], As0.h0, B00.h0);
         __builtin_amdgcn_sched_barrier(0);
-        if (rq_tail2) rq_issue2(std::integral_constant<int, 3>{});
+        STAMP_WAIT2(6, As0.h1, "v[190:195]", B00.h1, "v[214:219]");
+        mfma(acc[0][0].q[1], As0.h1, B00.h0);
         __builtin_amdgcn_sched_barrier(0);
-        STAMP_WAITH(6, B01.h0, "v[220:225]");
-        acc[0][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h0), widen((v6i)B01.h0), acc[0][1], 2, 2, 0, 0, 0, 0);
+        tail(std::integral_constant<int, kFirst>{});
         __builtin_amdgcn_sched_barrier(0);
-        if (rq_tail2) rq_issue2(std::integral_constant<int, 4>{});
-        rq_tail3 = rq_tail2;
-        rq_tail2 = false;
+        mfma(acc[0][0].q[3], As0.h1, B00.h1);
+        mfma(acc[0][0].q[2], As0.h0, B00.h1);
         __builtin_amdgcn_sched_barrier(0);
-        STAMP_WAIT2(4, As0.h1, "v[190:195]", B00.h1, "v[214:219]");
-        acc[0][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h1), widen((v6i)B00.h1), acc[0][0], 2, 2, 0, 0, 0, 0);
+        STAMP_WAIT2(3, B01.h0, "v[220:225]", B01.h1, "v[226:231]");
+        mfma(acc[0][1].q[2], As0.h0, B01.h1);
+        mfma(acc[0][1].q[3], As0.h1, B01.h1);
         __builtin_amdgcn_sched_barrier(0);
-        STAMP_WAITH(3, B01.h1, "v[226:231]");
-        acc[0][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h1), widen((v6i)B01.h1), acc[0][1], 2, 2, 0, 0, 0, 0);
+        tail(std::integral_constant<int, kFirst + 1>{});
+        __builtin_amdgcn_sched_barrier(0);
+        mfma(acc[0][1].q[1], As0.h1, B01.h0);
+        mfma(acc[0][1].q[0], As0.h0, B01.h0);
       } else {
         STAMP_WAIT2(8, As0.h0, "v[184:189]", B10.h0, "v[232:237]");
-        acc[0][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h0), widen((v6i)B10.h0), acc[0][0], 2, 2, 0, 0, 0, 0);
+        mfma(acc[0][0].q[0], As0.h0, B10.h0);
         __builtin_amdgcn_sched_barrier(0);
-        if (rq_tail2) rq_issue2(std::integral_constant<int, 3>{});
+        STAMP_WAIT2(6, As0.h1, "v[190:195]", B10.h1, "v[238:243]");
+        mfma(acc[0][0].q[1], As0.h1, B10.h0);
         __builtin_amdgcn_sched_barrier(0);
-        STAMP_WAITH(6, B11.h0, "v[244:249]");
-        acc[0][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h0), widen((v6i)B11.h0), acc[0][1], 2, 2, 0, 0, 0, 0);
+        tail(std::integral_constant<int, kFirst>{});
         __builtin_amdgcn_sched_barrier(0);
-        if (rq_tail2) rq_issue2(std::integral_constant<int, 4>{});
-        rq_tail3 = rq_tail2;
-        rq_tail2 = false;
+        mfma(acc[0][0].q[3], As0.h1, B10.h1);
+        mfma(acc[0][0].q[2], As0.h0, B10.h1);
         __builtin_amdgcn_sched_barrier(0);
-        STAMP_WAIT2(4, As0.h1, "v[190:195]", B10.h1, "v[238:243]");
-        acc[0][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h1), widen((v6i)B10.h1), acc[0][0], 2, 2, 0, 0, 0, 0);
+        STAMP_WAIT2(3, B11.h0, "v[244:249]", B11.h1, "v[250:255]");
+        mfma(acc[0][1].q[2], As0.h0, B11.h1);
+        mfma(acc[0][1].q[3], As0.h1, B11.h1);
         __builtin_amdgcn_sched_barrier(0);
-        STAMP_WAITH(3, B11.h1, "v[250:255]");
-        acc[0][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As0.h1), widen((v6i)B11.h1), acc[0][1], 2, 2, 0, 0, 0, 0);
+        tail(std::integral_constant<int, kFirst + 1>{});
+        __builtin_amdgcn_sched_barrier(0);
+        mfma(acc[0][1].q[1], As0.h1, B11.h0);
+        mfma(acc[0][1].q[0], As0.h0, B11.h0);
       }
       __builtin_amdgcn_sched_barrier(0);
-      STAMP_RD_AS0(sa + adrA0, 2 * kBlock6);
-      if (rq_tail3) rq_issue2(std::integral_constant<int, 5>{});
+      STAMP_RD_AS0(sa + adrA0 + lane16, 2 * kBlock6);
       STAMP_WAIT_AS1(3);
-      if constexpr (pb == 0) mfma4(As1, B00, B01, std::integral_constant<int, 1>{});
-      else mfma4(As1, B10, B11, std::integral_constant<int, 1>{});
+      mfma8(acc[1], As1, pb == 0 ? B00 : B10, pb == 0 ? B01 : B11, [&](auto i) __attribute__((always_inline)) {
+        if constexpr (i.value == 2) tail(std::integral_constant<int, kFirst + 2>{});
+        if constexpr (i.value == 6) tail(std::integral_constant<int, kFirst + 3>{});
+      });
       __builtin_amdgcn_sched_barrier(0);
-      STAMP_RD_AS1(sa + adrA0, 3 * kBlock6);
-      rq_tail3 = false;
+      STAMP_RD_AS1(sa + adrA0 + lane16, 3 * kBlock6);
       if constexpr (HI) {
-        STAMP_RD_HS(sa + adrH0, 0);
+        STAMP_RD_HS(sa + adrH0 + lane16, 0);
         STAMP_WAIT_AS0(6);
       } else {
         STAMP_WAIT_AS0(3);
       }
-      if constexpr (pb == 0) mfma4(As0, B00, B01, std::integral_constant<int, 2>{});
-      else mfma4(As0, B10, B11, std::integral_constant<int, 2>{});
+      mfma8(acc[2], As0, pb == 0 ? B00 : B10, pb == 0 ? B01 : B11, [&](auto i) __attribute__((always_inline)) {
+        if constexpr (i.value == 2) tail(std::integral_constant<int, kFirst + 4>{});
+        if constexpr (i.value == 4) tail(std::integral_constant<int, kFirst + 5>{});
+        if constexpr (i.value == 6) tail(std::integral_constant<int, kFirst + 6>{});
+      });
       __builtin_amdgcn_sched_barrier(0);
       STAMP_WAIT_AS1(0);
       if constexpr (HI) STAMP_WAIT_HS(0);
@@ -483,56 +533,35 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
         // (after the tile's last step these reads fetch the next tile's first fragments, which the epilogue's
         // registers cannot keep: they are dropped and read again by the next head)
         const uint32_t sn = lds0 + (uint32_t)(stg * kStage6);
-        if constexpr (pb == 0) STAMP_RD9_PB1(sn + adrA0, sn + adrB0);
-        else STAMP_RD9_PB0(sn + adrA0, sn + adrB0);
+        if constexpr (pb == 0) STAMP_RD9_PB1(sn + adrA0 + lane16, sn + adrB0 + lane16);
+        else STAMP_RD9_PB0(sn + adrA0 + lane16, sn + adrB0 + lane16);
       }
       __builtin_amdgcn_sched_barrier(0);
       // block 3, the request's loads spread among its MFMAs
       const Frag& W0 = pb == 0 ? B00 : B10;
       const Frag& W1 = pb == 0 ? B01 : B11;
-      rq_issue(std::integral_constant<int, 0>{});
-      __builtin_amdgcn_sched_barrier(0);
-      acc[3][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As1.h0), widen((v6i)W0.h0), acc[3][0], 2, 2, 0, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      rq_issue(std::integral_constant<int, 1>{});
-      __builtin_amdgcn_sched_barrier(0);
-      acc[3][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As1.h0), widen((v6i)W1.h0), acc[3][1], 2, 2, 0, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      rq_issue(std::integral_constant<int, 2>{});
-      __builtin_amdgcn_sched_barrier(0);
-      acc[3][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As1.h1), widen((v6i)W0.h1), acc[3][0], 2, 2, 0, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_sched_barrier(0);
-      acc[3][1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)As1.h1), widen((v6i)W1.h1), acc[3][1], 2, 2, 0, 0, 0, 0);
+      mfma8(acc[3], As1, W0, W1, [&](auto i) __attribute__((always_inline)) { rq_issue(std::integral_constant<int, i.value / 2 - 1>{}); });
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (HI) {
-        if (has_hi) {
-          acch[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)Hs.h0), widen((v6i)W0.h0), acch[0], 2, 2, 0, 0, 0, 0);
-          acch[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)Hs.h0), widen((v6i)W1.h0), acch[1], 2, 2, 0, 0, 0, 0);
-          acch[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)Hs.h1), widen((v6i)W0.h1), acch[0], 2, 2, 0, 0, 0, 0);
-          acch[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(widen((v6i)Hs.h1), widen((v6i)W1.h1), acch[1], 2, 2, 0, 0, 0, 0);
-        }
+        if (has_hi) mfma8(acch, Hs, W0, W1, [](auto) {});
         __builtin_amdgcn_sched_barrier(0);
       }
-      rq_tail2 = true;  // loads 3, 4 and 5 follow among the MFMAs of the next step (or after the tile's last step)
+      rq_tail = true;  // the other loads follow among the MFMAs of the next step (or after the tile's last step)
     };
     // head of the tile: the barrier that published its first stage lies behind (prologue, or the last step of the
     // tile before)
     {
+      lane16 = lane_now() * 16u;
       const uint32_t sh = lds0 + (uint32_t)(stg * kStage6);
-      STAMP_RD9_PB0(sh + adrA0, sh + adrB0);
+      STAMP_RD9_PB0(sh + adrA0 + lane16, sh + adrB0 + lane16);
     }
     for (int kt = 0; kt + 1 < KT; kt += 2) {
       step(std::integral_constant<int, 0>{});
       step(std::integral_constant<int, 1>{});
     }
     if (KT & 1) step(std::integral_constant<int, 0>{});
-    if (rq_tail2) {
-      rq_issue2(std::integral_constant<int, 3>{});
-      rq_issue2(std::integral_constant<int, 4>{});
-      rq_issue2(std::integral_constant<int, 5>{});
-      rq_tail2 = false;
-    }
+    if (rq_tail) rq_rest(std::integral_constant<int, kFirst>{});
+    rq_tail = false;
     // the last step's look-ahead reads must have returned before their registers are used for anything else
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 
@@ -544,11 +573,11 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
     // Per-lane values of the epilogue are derived from an opaque copy of the lane number, so that they are
     // computed here, once per tile, instead of being carried in registers across the main loop (which has none
     // to spare: a spilled value would be reloaded with a wait for all outstanding loads inside that loop).
-    int lane_e = lane, tid_e = tid;
+    int lane_e = (int)lane_now(), tid_e = wave * 64 + lane_e;
     asm volatile("" : "+v"(lane_e), "+v"(tid_e));
     // the epilogue's operands from global memory: their latency passes under the lane swaps
     RegEpiOperands<EPI, (IS2D ? 2 * RB : RB), RAG> eo;
-    if constexpr (EPI >= 2) eo.template request<!HI>(a, m0, nw, wm, lane_e);
+    if constexpr (EPI >= 1) eo.template request<!HI>(a, m0, nw, wm, lane_e);
     // row factors of the next tile: loaded now, written to the other buffer after the epilogue (a barrier of
     // the next tile's first step publishes them long before its epilogue reads them)
     float nfac = 0.0f, nrz = 0.0f;
@@ -578,11 +607,23 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
       // (their loads have landed: eo.sw, eo.cs)
       if (has_hi) hi_block_sums<(IS2D ? 2 * RB : RB), YBF16, SYM, RAG>(a, acch, reinterpret_cast<const float*>(ri + kHiInfo), eo, tm, nw, lane_e);
     }
-    if constexpr (EPI >= 2) {
+    if constexpr (EPI >= 1) {
       epilogue_reg<EPI, RB, IS2D, YBF16, NI, 0, SYM, RAG, ODD>(a, acc, ri, eo, m0, nw, wm, lane_e);
     } else {
       EpiOperands<EPI, RB, IS2D> none;
-      epilogue<Acc, EPI, RB, IS2D, YBF16, true>(a, acc, smem, ri, none, m0, n0, lane_e, wave, wm, wn);
+      v16f accv[4][NIW];
+#pragma unroll
+      for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NIW; ++ni) {
+          float r[16];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) r[v] = acc[mi][ni][v];
+          columns16(r);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) accv[mi][ni][v] = r[v];
+        }
+      epilogue<Acc, EPI, RB, IS2D, YBF16, true>(a, accv, smem, ri, none, m0, n0, lane_e, wave, wm, wn);
     }
     rbuf ^= 1;
     if (has_next && tid_e < BMW) write_row_info(row_info + rbuf * kRowInfo, tid_e, nfac, ndst, nrz);

@@ -423,7 +423,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm6_grp(const GrpGemm ga) {
     GRP_WAIT_X(fa1, sa1, GRP_A1);
     block(fa1, sa1, std::integral_constant<int, 3>{});
   }
-  RegEpiOperands<2, 2 * RB> eo;
+  RegEpiOperands<2, 2 * RB, false, true> eo;
   eo.request(a, m0, nw, wm, lane);
   eo.sw = f2{1.0f, 1.0f};
   epilogue_reg_impl<2, RB, true, YBF16, true, NI, 0, true, false, true>(a, acc, nullptr, eo, m0, nw, wm, lane);

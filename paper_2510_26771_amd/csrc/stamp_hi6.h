@@ -11,13 +11,14 @@
 
 namespace stamp_gemm {
 
-// one fragment (48 bytes) of a lane, read from memory
+// a lane's 48 bytes of a block: the operands of its two tiles of 16 rows (per-block scales: of the two halves of the K step).  (The middle
+// part read as two 8-byte halves, which would save the moves: every line of it is touched twice, 17.4 us become 20.3.)
 struct Frag6 {
   u4 p0, p1, p2;
-  __device__ __forceinline__ void load(const uint8_t* q) {
-    p0 = *reinterpret_cast<const u4*>(q);
-    p1 = *reinterpret_cast<const u4*>(q + kPart);
-    p2 = *reinterpret_cast<const u4*>(q + 2 * kPart);
+  __device__ __forceinline__ void load(const uint8_t* q /* wave-uniform */, uint32_t lane16) {
+    p0 = *reinterpret_cast<const u4*>(q + lane16);
+    p1 = *reinterpret_cast<const u4*>(q + kPart + lane16);
+    p2 = *reinterpret_cast<const u4*>(q + 2 * kPart + lane16);
   }
   // the builtin's operand has 8 registers, of which the instruction reads 6
   __device__ __forceinline__ v8i h0() const { return (v8i)__builtin_shufflevector(p0, p1, 0, 1, 2, 3, 4, 5, -1, -1); }
@@ -40,6 +41,7 @@ __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
   const int nf = hp.KT * 4, m = i / nf, frag = i - m * nf, kt = frag >> 2, f = frag & 3;
   int row;
   uint8_t* dst;
+  bool hf = false;
   if (o.ht.on) {
     int b, slot, tile, place, n;
     if (hp.places == 0) {
@@ -53,11 +55,12 @@ __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
       if (slot < 0) return;  // (a place without a row may hold anything)
     }
     row = b * hp.seq_rows + slot;
-    dst = o.p + ((size_t)tile * hp.KT + kt) * kBlock6 + (f & 1) * 512 + place * 16;
+    dst = o.p + ((size_t)tile * hp.KT + kt) * kBlock6 + f * 256 + place * 16;
   } else {
     const int gr = 32 * o.np, grp = m / gr, r = m - grp * gr;
     row = m < hp.M ? m + (m / o.seq) * (hp.seq_rows - o.seq) : -1;
-    dst = o.p + ((size_t)grp * hp.KT + kt) * (2 * o.np * kBlock6) + (r >> 5) * (2 * kBlock6) + (f & 1) * 512 + (r & 31) * 16;
+    dst = o.p + ((size_t)grp * hp.KT + kt) * (2 * o.np * kBlock6) + (r >> 5) * (2 * kBlock6) + f * 256 + row_lane6((uint32_t)r & 31);
+    hf = row_half6((uint32_t)r);
   }
   u4 w[2] = {};
   if (row >= 0 && frag * 32 < hp.d) {  // d is a multiple of 32
@@ -78,11 +81,11 @@ __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
       part[q] |= field << sh;
       if (sh > 58) part[q + 1] |= field >> (64 - sh);
     }
-    store_frag(dst + (half ? (o.ht.on ? kHiPlaces * 16 : kBlock6) : 0), f, part);
+    store_frag6(dst + (half && !o.ht.on ? kBlock6 : 0), o.ht.on ? half == 1 : hf, part);
   }
 }
 
-// 64 packed codes of a row (fragments kg and 2 + kg) -> their 48 bytes of a block
+// 32 packed codes each of two rows four apart -> a lane's 48 bytes of a block
 __device__ __forceinline__ void repack6_store(uint8_t* dst, u4 w0, u4 w1) {
   uint64_t lo[3], hi[3];
   chunk_to_e2m3(w0, lo);
@@ -93,11 +96,14 @@ __device__ __forceinline__ void repack6_store(uint8_t* dst, u4 w0, u4 w1) {
   *reinterpret_cast<ul2*>(dst + 2 * kPart) = ul2{hi[1], hi[2]};
 }
 
-// packed 4-bit rows -> operand: block `blk` = (row tile, K step), one row of it and kg: fragments kg and 2 + kg
-__device__ __forceinline__ void repack6_rows(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, size_t blk, int row, int kg) {
-  const uint8_t* src = q_lo + blk * (256 * 64) + row * 64 + kg * 16;
-  repack6_store(a6 + blk * kStageA6 + (row >> 5) * kBlock6 + kg * 512 + (row & 31) * 16, *reinterpret_cast<const u4*>(src),
-                *reinterpret_cast<const u4*>(src + 32));
+// The two rows of unit u = 0 .. 511 of a (row tile, K step): the first of them (the other is four further on), and fragment
+__device__ __forceinline__ int repack6_row(int u) { return (u >> 8) * 128 + ((u & 12) << 3) + ((u >> 6) & 3) * 8 + (u & 3); }
+__device__ __forceinline__ int repack6_frag(int u) { return (u >> 4) & 3; }
+// packed 4-bit rows -> operand: block `blk` = (row tile, K step), unit u of it
+__device__ __forceinline__ void repack6_rows(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, size_t blk, int u) {
+  const uint8_t* src = q_lo + blk * (256 * 64) + repack6_row(u) * 64 + repack6_frag(u) * 16;
+  repack6_store(a6 + blk * kStageA6 + (u >> 6) * kBlock6 + (u & 63) * 16, *reinterpret_cast<const u4*>(src),
+                *reinterpret_cast<const u4*>(src + 4 * 64));
 }
 
 }  // namespace stamp_gemm

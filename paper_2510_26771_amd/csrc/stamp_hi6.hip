@@ -8,8 +8,8 @@
 // when there are more than 64 rows: each group takes 64), and only their sums meet in LDS.  The sums are whole numbers and
 // stay whole: fp32 holds each FP6 sum exactly, 16 h + l and the sum over the waves are int32.
 // Measured (rows x depth x d_out, microseconds; before: int8 GEMM + top levels of the inverse as a kernel of its own):
-// 64 x 4096 x 11008: 17.4 (16.1 + 10.1), 128 x 4096 x 4096: 11.9 (17.8 + 11.9), 64 x 11008 x 4096: 16.9 (19.1 + 4.8),
-// 128 x 1152 x 4608: 8.2 (15.7 + 5.2), 512 x 4096 x 4096: 37 (34 + 15).
+// 64 x 4096 x 11008: 15.3 (16.1 + 10.1), 128 x 4096 x 4096: 11.9 (17.8 + 11.9), 64 x 11008 x 4096: 16.9 (19.1 + 4.8),
+// 128 x 1152 x 4608: 8.2 (15.7 + 5.2), 512 x 4096 x 4096: 33 (34 + 15).
 #include "stamp_hi6.h"
 
 namespace {
@@ -33,15 +33,26 @@ struct Hi6Args {
   const float *sa, *sw;  // GRP: [row group][K step][rows][2], [column tile][K step][4 blocks][32][2]
 };
 
+// place of a sum in its wave's part (NC = 2: col = the column, else its place in the strip): the four lane groups of a wave write
+// rows 8 apart, to 16 banks each
+template <int NC>
+__device__ __forceinline__ int part_at(int row, int col) {
+  const int b3 = (row >> 3) & 1, b4 = (row >> 4) & 1;
+  return NC == 2 ? row * 64 + (col ^ b3 ^ (b4 << 5)) : (row ^ b4) * 32 + (col ^ (b3 << 4));
+}
+
 // GRP: one scale per 64 channels (a half of a K step) and row / column: the sums are rescaled half by half, s_part holds fp32
 // AHEAD: the next step's operands are in flight while a step is multiplied.  That takes twice the registers, so it is for
 // launches that leave no CU a second workgroup: 64 x 11008 x 4096 (128 workgroups) 16.9 us against 18.9, 128 x 4096 x 4096
 // (256) 11.9 against 12.8, but 64 x 4096 x 11008 (344) 21.4 against 17.4.
-template <int NP, bool GRP, bool AHEAD>
-__global__ __launch_bounds__(512, AHEAD ? 2 : 4) void k_hi6(const Hi6Args h) {
+// NC: strips of 32 columns per workgroup.  Two: the rows' operand, the larger share of what a CU's vector memory path moves (64 bytes a
+// clock: that path is what bounds the loop), is read half as often.  512 x 4096 x 4096 39 us with one strip, 33 with two; 64 x 4096 x 11008
+// 17.2, 15.3, of which the loop 10 and 8, the launch and the sums of the waves 5, the top levels 2.
+template <int NP, bool GRP, bool AHEAD, int NC = 1>
+__global__ __launch_bounds__(512, AHEAD || NC == 2 ? 2 : 4) void k_hi6(const Hi6Args h) {
   const GemmArgs& a = h.a;
   const StampGeom& g = a.g;
-  constexpr int C = 32, RW = 32 * NP;  // columns, rows of a wave
+  constexpr int C = 32 * NC, RW = 32 * NP, RS = 512 / C;  // columns, rows of a wave; rows apart that a thread finishes
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   int* const s_part = reinterpret_cast<int*>(smem);            // [8 waves][RW][C]
   __shared__ __attribute__((aligned(16))) uint8_t s_info[kRowInfoBytes];
@@ -51,56 +62,91 @@ __global__ __launch_bounds__(512, AHEAD ? 2 : 4) void k_hi6(const Hi6Args h) {
   const int KT = a.Kpad / BK, kw = 8 / h.ng, rg = wave / kw, kp = wave - rg * kw;
   const int RG = RW * h.ng, m0 = (int)blockIdx.y * RG;  // rows of the workgroup
   // strip of 32 columns: block `st` of the weight layout = columns 64 (st / 2) + 2 l + st % 2
-  const int st = blockIdx.x;
-  const uint8_t* pb = a.Bq + (size_t)(st >> 2) * KT * kStageB6 + (st & 3) * kBlock6 + lane * 16;
-  const uint8_t* pa = a.A + (size_t)((int)blockIdx.y * h.ng + rg) * KT * (2 * NP * kBlock6) + lane * 16;
+  const int st = NC * (int)blockIdx.x;
+  const uint8_t* pb = a.Bq + (size_t)(st >> 2) * KT * kStageB6 + (st & 3) * kBlock6;
+  const uint8_t* pa = a.A + (size_t)((int)blockIdx.y * h.ng + rg) * KT * (2 * NP * kBlock6);
+  const uint32_t lane16 = (uint32_t)lane * 16u;
   const int kt0 = KT * kp / kw, kt1 = KT * (kp + 1) / kw;
 
-  v16f acc[GRP ? NP : 2 * NP];
+  // GRP: MFMA blocks of 32 x 32; else four tiles of 16 x 16 per block, 2 tc + th as in the 4-bit rows' GEMM
+  v16f acc[GRP ? NP : 1];
+  f4 acct[NC][GRP ? 1 : 2 * NP][4];
+  if constexpr (GRP) {
 #pragma unroll
-  for (int i = 0; i < (GRP ? NP : 2 * NP); ++i)
+    for (int i = 0; i < NP; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+      for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+  } else {
+#pragma unroll
+    for (int s = 0; s < NC; ++s)
+#pragma unroll
+      for (int i = 0; i < 2 * NP; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acct[s][i][q] = (f4){0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  [[maybe_unused]] auto multiply1 = [&](f4 (&c)[4], const Frag6& b, const Frag6& f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      c[q] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4((q & 1) ? f.h1() : f.h0(), (q & 2) ? b.h1() : b.h0(), c[q], 2, 2, 0, 0, 0, 0);
+  };
+  [[maybe_unused]] auto multiply = [&](const Frag6& b, const Frag6 (&f)[2 * NP]) __attribute__((always_inline)) {
+    if constexpr (!GRP) {
+#pragma unroll
+      for (int i = 0; i < 2 * NP; ++i) multiply1(acct[0][i], b, f[i]);
+    }
+  };
   if (!GRP && tid < RG) {
     float fac = 0.0f, rz = 0.0f;
     int dst = -1;
     compute_row_info<AccHi6, 1>(a, m0, tid, fac, dst, rz);
     write_row_info(s_info, tid, fac, dst, rz);
   }
-  // Not AHEAD: at most 128 registers, four waves per SIMD (two workgroups per CU) hide each other's loads.
+  if constexpr (NC == 2) {
+    for (int kt = kt0; kt < kt1; ++kt) {
+      Frag6 fb[NC], fa[2 * NP];
+#pragma unroll
+      for (int s = 0; s < NC; ++s) fb[s].load(pb + (size_t)kt * kStageB6 + s * kBlock6, lane16);
+#pragma unroll
+      for (int i = 0; i < 2 * NP; ++i) fa[i].load(pa + (size_t)kt * (2 * NP * kBlock6) + i * kBlock6, lane16);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 2 * NP; ++i)
+#pragma unroll
+        for (int s = 0; s < NC; ++s) multiply1(acct[s][i], fb[s], fa[i]);
+    }
+  }
+  // Neither: at most 128 registers, four waves per SIMD (two workgroups per CU) hide each other's loads.
   if constexpr (AHEAD) {
     Frag6 fb[2], fa[2][2 * NP];
     auto fetch = [&](int kt, Frag6& b, Frag6 (&f)[2 * NP]) {
-      b.load(pb + (size_t)kt * kStageB6);
+      b.load(pb + (size_t)kt * kStageB6, lane16);
 #pragma unroll
-      for (int i = 0; i < 2 * NP; ++i) f[i].load(pa + (size_t)kt * (2 * NP * kBlock6) + i * kBlock6);
-    };
-    auto multiply = [&](const Frag6& b, const Frag6 (&f)[2 * NP]) {
-#pragma unroll
-      for (int i = 0; i < 2 * NP; ++i) {
-        acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[i].h0(), b.h0(), acc[i], 2, 2, 0, 0, 0, 0);
-        acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[i].h1(), b.h1(), acc[i], 2, 2, 0, 0, 0, 0);
-      }
+      for (int i = 0; i < 2 * NP; ++i) f[i].load(pa + (size_t)kt * (2 * NP * kBlock6) + i * kBlock6, lane16);
     };
     int kt = kt0;
     if (kt < kt1) {
       fetch(kt, fb[0], fa[0]);
       for (; kt + 2 < kt1; kt += 2) {
         fetch(kt + 1, fb[1], fa[1]);
+        __builtin_amdgcn_sched_barrier(0);  // (its loads would be put off one by one)
         multiply(fb[0], fa[0]);
+        __builtin_amdgcn_sched_barrier(0);
         fetch(kt + 2, fb[0], fa[0]);
+        __builtin_amdgcn_sched_barrier(0);
         multiply(fb[1], fa[1]);
+        __builtin_amdgcn_sched_barrier(0);
       }
       if (kt + 1 < kt1) fetch(kt + 1, fb[1], fa[1]);
+      __builtin_amdgcn_sched_barrier(0);
       multiply(fb[0], fa[0]);
       if (kt + 1 < kt1) multiply(fb[1], fa[1]);
     }
   }
-  for (int kt = AHEAD ? kt1 : kt0; kt < kt1; ++kt) {
+  for (int kt = AHEAD || NC == 2 ? kt1 : kt0; kt < kt1; ++kt) {
     Frag6 fb, fa[2 * NP];
-    fb.load(pb + (size_t)kt * kStageB6);
+    fb.load(pb + (size_t)kt * kStageB6, lane16);
 #pragma unroll
-    for (int i = 0; i < 2 * NP; ++i) fa[i].load(pa + (size_t)kt * (2 * NP * kBlock6) + i * kBlock6);
+    for (int i = 0; i < 2 * NP; ++i) fa[i].load(pa + (size_t)kt * (2 * NP * kBlock6) + i * kBlock6, lane16);
     if constexpr (GRP) {
       // S = row scale times column scale (k = 1 of the product is zero)
       const f2 sw = reinterpret_cast<const f2*>(h.sw)[((size_t)(st >> 2) * KT + kt) * 128 + (st & 3) * 32 + l32];
@@ -119,12 +165,8 @@ __global__ __launch_bounds__(512, AHEAD ? 2 : 4) void k_hi6(const Hi6Args h) {
           for (int v = 0; v < 16; ++v) acc[pr][v] = __builtin_fmaf(__builtin_fmaf(16.0f, th[v], tl[v]), S[v], acc[pr][v]);
         }
       }
-      continue;
-    }
-#pragma unroll
-    for (int i = 0; i < (GRP ? 0 : 2 * NP); ++i) {
-      acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[i].h0(), fb.h0(), acc[i], 2, 2, 0, 0, 0, 0);
-      acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[i].h1(), fb.h1(), acc[i], 2, 2, 0, 0, 0, 0);
+    } else {
+      multiply(fb, fa);
     }
   }
   // staging position of a row: its natural position among the block sums of its sequence (top levels), else the row itself
@@ -141,25 +183,32 @@ __global__ __launch_bounds__(512, AHEAD ? 2 : 4) void k_hi6(const Hi6Args h) {
   for (int pr = 0; pr < NP; ++pr)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int row = pr * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
-      if constexpr (GRP) s_part[(wave * RW + row) * C + l32] = __float_as_int(acc[pr][v]);
-      else s_part[(wave * RW + row) * C + l32] = 16 * (int)(acc[2 * pr][v] * 64.0f) + (int)(acc[2 * pr + 1][v] * 64.0f);
+      if constexpr (GRP) {
+        const int row = pr * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
+        s_part[(wave * RW + row) * C + l32] = __float_as_int(acc[pr][v]);
+      } else {
+        const int q = v >> 2, row = pr * 32 + 8 * (lane >> 4) + 4 * (q & 1) + (v & 3), col = 16 * (q >> 1) + (lane & 15);
+#pragma unroll
+        for (int s = 0; s < NC; ++s)
+          s_part[wave * RW * C + part_at<NC>(row, NC == 2 ? 2 * col + s : col)] =
+              16 * (int)(acct[s][2 * pr][q][v & 3] * 64.0f) + (int)(acct[s][2 * pr + 1][q][v & 3] * 64.0f);
+      }
     }
   __syncthreads();
 
   // sums over the waves, dequantized
   const float* s_fac = reinterpret_cast<const float*>(s_info);
   const float* s_rz = reinterpret_cast<const float*>(s_info + 2048);
-  const int c = tid & 31, r0 = tid >> 5;  // this thread: column c, rows r0, r0 + 16, ..
-  const int n = 64 * (st >> 1) + 2 * c + (st & 1);
+  const int c = tid & (C - 1), r0 = tid / C;  // this thread: column c, rows r0, r0 + RS, ..
+  const int n = NC == 2 ? 32 * st + c : 64 * (st >> 1) + 2 * c + (st & 1);
   const float swn = GRP ? 0.0f : a.sw[n], csn = !GRP && g.asym ? a.colsum[n] : 0.0f;
   float y[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const int r = r0 + 16 * i;
+    const int r = r0 + RS * i;
     y[i] = 0.0f;
     if (r < RG) {
-      const int base = ((r / RW) * kw * RW + (r & (RW - 1))) * C + c;
+      const int base = (r / RW) * kw * RW * C + (GRP ? (r & (RW - 1)) * C + c : part_at<NC>(r & (RW - 1), c));
       if constexpr (GRP) {
         float sum = 0.0f;
         for (int q = 0; q < kw; ++q) sum += __int_as_float(s_part[base + q * (RW * C)]);
@@ -178,13 +227,13 @@ __global__ __launch_bounds__(512, AHEAD ? 2 : 4) void k_hi6(const Hi6Args h) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      if (r0 + 16 * i < RG) s_buf[s_pos[r0 + 16 * i] * C + c] = y[i];
+      if (r0 + RS * i < RG) s_buf[s_pos[r0 + RS * i] * C + c] = y[i];
     __syncthreads();
     const int nseq = RG / g.k;
     if (!g.is2d) {
       for (int s2 = 1 << g.L; s2 >= 2; s2 >>= 1) {
         const int npair = RG / s2;
-        for (int i = r0; i < npair; i += 16) {
+        for (int i = r0; i < npair; i += RS) {
           float *px = &s_buf[(i * s2) * C + c], *pd = &s_buf[(i * s2 + (s2 >> 1)) * C + c];
           const float x = *px, d = *pd;
           *px = x + d;
@@ -195,7 +244,7 @@ __global__ __launch_bounds__(512, AHEAD ? 2 : 4) void k_hi6(const Hi6Args h) {
     } else {
       for (int s2 = 1 << g.L; s2 >= 2; s2 >>= 1) {
         const int nc = g.G / s2, hf = s2 >> 1, cells = nc * nc;
-        for (int i = r0; i < nseq * cells; i += 16) {
+        for (int i = r0; i < nseq * cells; i += RS) {
           const int seq = i / cells, q = i - seq * cells, cy = q / nc, cx = q - cy * nc;
           float* p00 = &s_buf[(seq * g.k + (cy * s2) * g.G + cx * s2) * C + c];
           float *p01 = p00 + hf * C, *p10 = p00 + hf * g.G * C, *p11 = p10 + hf * C;
@@ -211,14 +260,14 @@ __global__ __launch_bounds__(512, AHEAD ? 2 : 4) void k_hi6(const Hi6Args h) {
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      if (r0 + 16 * i < RG) y[i] = s_buf[(r0 + 16 * i) * C + c];
+      if (r0 + RS * i < RG) y[i] = s_buf[(r0 + RS * i) * C + c];
   }
   if (n >= a.N) return;
   float* const out = reinterpret_cast<float*>(a.out);
   const float bv = ((h.mode == 1 || h.mode == 3) && a.bias != nullptr) ? a.bias[n] : 0.0f;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const int r = r0 + 16 * i, m = m0 + r;
+    const int r = r0 + RS * i, m = m0 + r;
     if (r >= RG || m >= a.M) continue;
     if (h.mode == 0) {
       out[(size_t)m * a.ld_out + n] = y[i];
@@ -239,14 +288,14 @@ __global__ __launch_bounds__(512, AHEAD ? 2 : 4) void k_hi6(const Hi6Args h) {
   }
 }
 
-template <int NP, bool GRP, bool AHEAD>
+template <int NP, bool GRP, bool AHEAD, int NC = 1>
 hipError_t launch(const Hi6Args& h, hipStream_t st) {
-  constexpr size_t lds = (size_t)8 * 32 * NP * 32 * sizeof(int);
+  constexpr size_t lds = (size_t)8 * 32 * NP * 32 * NC * sizeof(int);
   static size_t lds_done[kStampMaxDevices] = {};
-  const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_hi6<NP, GRP, AHEAD>), lds, lds_done);
+  const hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_hi6<NP, GRP, AHEAD, NC>), lds, lds_done);
   if (e != hipSuccess) return e;
   const int rows = 32 * NP * h.ng;
-  hipLaunchKernelGGL((k_hi6<NP, GRP, AHEAD>), dim3((h.a.N + 63) / 64 * 2, (h.a.M + rows - 1) / rows), dim3(512), lds, st, h);
+  hipLaunchKernelGGL((k_hi6<NP, GRP, AHEAD, NC>), dim3((h.a.N + 63) / 64 * (2 / NC), (h.a.M + rows - 1) / rows), dim3(512), lds, st, h);
   return hipGetLastError();
 }
 
@@ -361,6 +410,7 @@ hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float*
   h.Y = Y;
   // workgroups up to one per CU: the rule of AHEAD
   if (h.np == 2 && (int64_t)((h.a.N + 63) / 64 * 2) * ((h.a.M + 64 * h.ng - 1) / (64 * h.ng)) <= stamp_device_cus()) return launch<2, false, true>(h, st);
+  if (h.np == 2 && h.ng == 1) return launch<2, false, false, 2>(h, st);
   return h.np == 1 ? launch<1, false, false>(h, st) : launch<2, false, false>(h, st);
 }
 

@@ -21,7 +21,7 @@ struct LaneArgs {
   int G, gridW;      // token grid: blocks per row, tokens per row
 };
 
-// 24 bytes of a fragment -> its places; dst = (lane group, row) of a block, half = fragment / 2
+// 24 bytes of a fragment -> their places; dst = its lane's place in part 0, half = row_half6 of the row
 __device__ __forceinline__ void store24(uint8_t* dst, u6v w, bool half) {
   const u4 a = {half ? w[2] : w[0], half ? w[3] : w[1], half ? w[4] : w[2], half ? w[5] : w[3]};
   const u2v b = {half ? w[0] : w[4], half ? w[1] : w[5]};
@@ -45,10 +45,10 @@ __device__ __forceinline__ void store_hi24(const Hi6Out& o, int m, int KT, f16v 
     od[i] = __builtin_fmaf(-16.0f, hv[1][i], od[i]);
   }
   const u6v l = to_e2m3(ev, od);
-  const uint32_t off = (uint32_t)(c >> 7) * hi_step_bytes(o) + ((c >> 5) & 1) * 512;
-  hi_rows(o, m, KT, [&](uint8_t* dst, int lo) {
-    store24(dst + off, h, (c >> 6) & 1);
-    store24(dst + off + lo, l, (c >> 6) & 1);
+  const uint32_t off = chan_off6((uint32_t)c, hi_step_bytes(o));
+  hi_rows(o, m, KT, [&](uint8_t* dst, bool hh, int lo, bool lh) {
+    store24(dst + off, h, hh);
+    store24(dst + off + lo, l, lh);
   });
 }
 

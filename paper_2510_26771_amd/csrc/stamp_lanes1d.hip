@@ -173,9 +173,8 @@ __global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs
   const float mb_ = fold ? __fmul_rn(inv_b, nb) : inv_b, nb_ = fold ? 1.0f : nb;
   const size_t brow = RAG ? ((size_t)b * a.rag.nb + j) * RK : seq0 + (size_t)j * R;
   uint8_t* const out = a.a6 + (brow >> 8) * (size_t)a.KT * kStageA6;
-  auto place = [&](int e, int c) {
-    const uint32_t mr = (uint32_t)(brow & 255) + (uint32_t)e;
-    return out + ((uint32_t)(c >> 7) * (uint32_t)kStageA6 + (mr >> 5) * kBlock6 + (mr & 31) * 16 + ((c >> 5) & 1) * 512);
+  auto place = [&](int e, int c) {  // (brow is a multiple of 8: e decides the half)
+    return out + (chan_off6((uint32_t)c, kStageA6) + row_off6((uint32_t)(brow & 255) + (uint32_t)e));
   };
   // codes of 16 values; shift: what the stored code is below the unsigned one
   auto code = [&](const float (&x)[32], int odd, float n, float mul, float z, bool two) __attribute__((always_inline)) {
@@ -190,7 +189,7 @@ __global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs
 #pragma unroll
   for (int g = NG - 1; g >= 0; --g) {
     const int c = c0[g];
-    const bool active = c < a.d, half = (c >> 6) & 1;
+    const bool active = c < a.d;
     if constexpr (NG == 2) {
       if (g == 0) {
 #pragma unroll
@@ -204,13 +203,13 @@ __global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs
       }
     }
     const u6v wa = to_e2m3(code(ra, 0, na, inv_a, za, !RAG), code(ra, 1, na, inv_a, za, !RAG));
-    if (active && (!RAG || sa >= 0)) store24(place(ea, c), wa, half);
+    if (active && (!RAG || sa >= 0)) store24(place(ea, c), wa, row_half6((uint32_t)ea));
     __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
     const int c = c0[g];
-    const bool active = c < a.d, half = (c >> 6) & 1;
+    const bool active = c < a.d;
     if (sum_out) {
       if (active && tl == 0) {
         float4* o = reinterpret_cast<float4*>(a.abot + ((size_t)b * (a.s >> RLOG) + blockIdx.x) * a.d + c);
@@ -231,7 +230,7 @@ __global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs
       }
     }
     const u6v wb = to_e2m3(code(rb[g], 0, nb_, mb_, zb, !RAG), code(rb[g], 1, nb_, mb_, zb, !RAG));
-    if (active && (!RAG || sb >= 0) && !(tl == 0 && (sum_out || row8))) store24(place(eb, c), wb, half);
+    if (active && (!RAG || sb >= 0) && !(tl == 0 && (sum_out || row8))) store24(place(eb, c), wb, row_half6((uint32_t)eb));
   }
 }
 
@@ -354,8 +353,7 @@ __global__ __launch_bounds__(256) void k_quant_parts(const float* __restrict__ T
     store_hi24(a.hi6, b * a.k + slot, a.KT, ev, od, c);
   } else {
     const uint32_t mr = (uint32_t)(srow & 255);
-    store24(a.a6 + (srow >> 8) * (size_t)a.KT * kStageA6 + (size_t)(c >> 7) * kStageA6 + (mr >> 5) * kBlock6 + (mr & 31) * 16 + ((c >> 5) & 1) * 512,
-            to_e2m3(ev, od), (c >> 6) & 1);
+    store24(a.a6 + (srow >> 8) * (size_t)a.KT * kStageA6 + (chan_off6((uint32_t)c, kStageA6) + row_off6(mr)), to_e2m3(ev, od), row_half6(mr));
   }
 }
 
@@ -415,8 +413,8 @@ __global__ __launch_bounds__(1024) void k_lanes_rows(const LaneArgs a, int rows)
   if (row8) {
     store_hi24(a.hi6, b * a.k + pr, a.KT, ev, od, c);
   } else {
-    store24(a.a6 + (size_t)(m >> 8) * a.KT * kStageA6 + (size_t)(c >> 7) * kStageA6 + ((m & 255) >> 5) * kBlock6 + (m & 31) * 16 + ((c >> 5) & 1) * 512,
-            to_e2m3(ev, od), (c >> 6) & 1);
+    store24(a.a6 + (size_t)(m >> 8) * a.KT * kStageA6 + (chan_off6((uint32_t)c, kStageA6) + row_off6((uint32_t)m & 255)), to_e2m3(ev, od),
+            row_half6((uint32_t)m));
   }
 }
 

@@ -95,8 +95,7 @@ __global__ __launch_bounds__(768) void k_lanes2d(const LaneArgs a) {
   const float nrm3 = cell_sum ? 1.0f / GB : 0.25f;
   const int e3 = cell_sum ? tl >> 2 : G2 * G2 * (tl & 3) + (RLOG == 3 ? (qy >> 1) * G2 + (qx >> 1) : 0);
   const size_t brow = seq0 + (size_t)j * RK;
-  uint8_t* const out = a.a6 + (brow >> 8) * (size_t)a.KT * kStageA6 + (size_t)(c >> 7) * kStageA6 + ((c >> 5) & 1) * 512;
-  const bool half = (c >> 6) & 1;
+  uint8_t* const out = a.a6 + (brow >> 8) * (size_t)a.KT * kStageA6 + chan_off6((uint32_t)c, kStageA6);
 #pragma unroll
   for (int o = 0; o < 4; ++o) {
     const int q = o == 2 ? 0 : (o == 3 ? 3 : o + 1);  // (8-bit rows need registers of their own: last)
@@ -150,7 +149,7 @@ __global__ __launch_bounds__(768) void k_lanes2d(const LaneArgs a) {
     }
     const u6v w = to_e2m3(ev, od);
     const uint32_t m = (uint32_t)(brow & 255) + (uint32_t)e;
-    if (active && !(top && (sum_out || row8))) store24(out + ((m >> 5) * kBlock6 + (m & 31) * 16), w, half);
+    if (active && !(top && (sum_out || row8))) store24(out + row_off6(m), w, row_half6(m));
     __builtin_amdgcn_sched_barrier(0);
   }
 }
