@@ -234,8 +234,9 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
   // fixes its addresses and advances the cursor, rq_issue<i> issues its i-th load: the
   // main loop spreads them among its MFMAs (eight waves issuing all their loads at once keep the address unit busy
   // for several hundred cycles, during which none of them can issue anything else).
-  // Three of a request's loads go out among the MFMAs of the step's last block, the others in the next step (rq_tail: still to be
+  // Three of its loads go out among the MFMAs of the step's last block (three more beside the 8-bit rows'), the others in the next step (rq_tail: still to be
   // issued), with two MFMAs or more between any two: one load keeps the address unit busy for 16 cycles, an MFMA the matrix pipe for 17.
+  // (Spread evenly over the whole step the last ones land too late: 2048 x 11008 -> 4096 60.3 us against 57.7.)
   bool rq_tail = false;
   uint8_t* rq_so = nullptr;
   [[maybe_unused]] uint32_t rq_oh = 0;
@@ -360,25 +361,16 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
 #define STAMP_RD_HS(base, off) STAMP_RD3(Hs, "v[172:177]", "v[178:183]", "v[172:175]", "v[176:179]", "v[180:183]", base, off)
 #define STAMP_WAIT_HS(cnt) STAMP_WAIT1(cnt, Hs, "v[172:177]", "v[178:183]")
 #define STAMP_RD_AS1(base, off) STAMP_RD3(As1, "v[196:201]", "v[202:207]", "v[196:199]", "v[200:203]", "v[204:207]", base, off)
-  // activation block 0 and the two weight blocks of a step in one statement, what the first MFMA takes first, the second weight
-  // block last
-#define STAMP_RD9(fa, fb0, fb1, AH0, AH1, B0H0, B0H1, B1H0, B1H1, A0, A1, A2, B00_, B01_, B02_, B10_, B11_, B12_, basea, baseb)         \
-  asm volatile("ds_read_b128 " A0 ", %6 offset:0\n\tds_read_b128 " A1 ", %6 offset:%8\n\t"                                          \
-               "ds_read_b128 " B00_ ", %7 offset:0\n\tds_read_b128 " B01_ ", %7 offset:%8\n\t"                                      \
-               "ds_read_b128 " A2 ", %6 offset:%9\n\tds_read_b128 " B02_ ", %7 offset:%9\n\t"                                       \
-               "ds_read_b128 " B10_ ", %7 offset:%10\n\tds_read_b128 " B11_ ", %7 offset:%11\n\tds_read_b128 " B12_ ", %7 offset:%12" \
-               : "=&{" AH0 "}"(fa.h0), "=&{" AH1 "}"(fa.h1), "=&{" B0H0 "}"(fb0.h0), "=&{" B0H1 "}"(fb0.h1), "=&{" B1H0 "}"(fb1.h0),  \
-                 "=&{" B1H1 "}"(fb1.h1)                                                                                              \
-               : "v"(basea), "v"(baseb), "n"(kPart), "n"(2 * kPart), "n"(kBlock6), "n"(kBlock6 + kPart), "n"(kBlock6 + 2 * kPart))
-#define STAMP_RD9_PB0(basea, baseb)                                                                                                  \
-  STAMP_RD9(As0, B00, B01, "v[184:189]", "v[190:195]", "v[208:213]", "v[214:219]", "v[220:225]", "v[226:231]", "v[184:187]", "v[188:191]", \
-            "v[192:195]", "v[208:211]", "v[212:215]", "v[216:219]", "v[220:223]", "v[224:227]", "v[228:231]", basea, baseb)
-#define STAMP_RD9_PB1(basea, baseb)                                                                                                  \
-  STAMP_RD9(As0, B10, B11, "v[184:189]", "v[190:195]", "v[232:237]", "v[238:243]", "v[244:249]", "v[250:255]", "v[184:187]", "v[188:191]", \
-            "v[192:195]", "v[232:235]", "v[236:239]", "v[240:243]", "v[244:247]", "v[248:251]", "v[252:255]", basea, baseb)
+#define STAMP_RD_B00(base) STAMP_RD3(B00, "v[208:213]", "v[214:219]", "v[208:211]", "v[212:215]", "v[216:219]", base, 0)
+#define STAMP_RD_B01(base) STAMP_RD3(B01, "v[220:225]", "v[226:231]", "v[220:223]", "v[224:227]", "v[228:231]", base, kBlock6)
+#define STAMP_RD_B10(base) STAMP_RD3(B10, "v[232:237]", "v[238:243]", "v[232:235]", "v[236:239]", "v[240:243]", base, 0)
+#define STAMP_RD_B11(base) STAMP_RD3(B11, "v[244:249]", "v[250:255]", "v[244:247]", "v[248:251]", "v[252:255]", base, kBlock6)
   // a wait names the fragments it covers (same registers in and out), which keeps their MFMAs behind it
 #define STAMP_WAIT2(cnt, x, XR, y, YR) asm volatile("s_waitcnt lgkmcnt(" #cnt ")" : "={" XR "}"(x), "={" YR "}"(y) : "0"(x), "1"(y))
-#define STAMP_WAITH(cnt, x, XR) asm volatile("s_waitcnt lgkmcnt(" #cnt ")" : "={" XR "}"(x) : "0"(x))
+#define STAMP_WAIT_AS0B(cnt, b, H0, H1)                                                                                     \
+  asm volatile("s_waitcnt lgkmcnt(" #cnt ")"                                                                                \
+               : "={v[184:189]}"(As0.h0), "={v[190:195]}"(As0.h1), "={" H0 "}"(b.h0), "={" H1 "}"(b.h1)                      \
+               : "0"(As0.h0), "1"(As0.h1), "2"(b.h0), "3"(b.h1))
 #define STAMP_WAIT1(cnt, f, H0, H1) asm volatile("s_waitcnt lgkmcnt(" #cnt ")" : "={" H0 "}"(f.h0), "={" H1 "}"(f.h1) : "0"(f.h0), "1"(f.h1))
 #define STAMP_WAIT_AS0(cnt) STAMP_WAIT1(cnt, As0, "v[184:189]", "v[190:195]")
 #define STAMP_WAIT_AS1(cnt) STAMP_WAIT1(cnt, As1, "v[196:201]", "v[202:207]")
@@ -437,7 +429,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
         if (rq_tail) rq_issue(i);
       }
     };
-    constexpr int kFirst = 3;  // loads of a request in the step itself
+    constexpr int kFirst = HI ? 6 : 3;  // loads of a request in the step itself
 
     // Step kt (pb = 0: weights in B00, B01, the next step's go to B10, B11; pb = 1: the other way round).  On entry
     // the reads of the step's weights and of activation block 0 have been issued (by the head of the tile or by the
@@ -452,12 +444,10 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
       const uint32_t sa = lds0 + (uint32_t)(stg * kStage6);
       __builtin_amdgcn_sched_barrier(0);
       STAMP_RD_AS1(sa + adrA0 + lane16, 1 * kBlock6);
-      // block 0: of the 12 reads in flight the first 4 feed the first MFMA, 6 the next three, 9 the others
+      // block 0: of the 12 reads in flight the first 6 feed the first four MFMAs, 9 the others
       if constexpr (pb == 0) {
-        STAMP_WAIT2(8, As0.h0, "v[184:189]", B00.h0, "v[208:213]");
+        STAMP_WAIT_AS0B(6, B00, "v[208:213]", "v[214:219]");
         mfma(acc[0][0].q[0], As0.h0, B00.h0);
-        __builtin_amdgcn_sched_barrier(0);
-        STAMP_WAIT2(6, As0.h1, "v[190:195]", B00.h1, "v[214:219]");
         mfma(acc[0][0].q[1], As0.h1, B00.h0);
         __builtin_amdgcn_sched_barrier(0);
         tail(std::integral_constant<int, kFirst>{});
@@ -474,10 +464,8 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
         mfma(acc[0][1].q[1], As0.h1, B01.h0);
         mfma(acc[0][1].q[0], As0.h0, B01.h0);
       } else {
-        STAMP_WAIT2(8, As0.h0, "v[184:189]", B10.h0, "v[232:237]");
+        STAMP_WAIT_AS0B(6, B10, "v[232:237]", "v[238:243]");
         mfma(acc[0][0].q[0], As0.h0, B10.h0);
-        __builtin_amdgcn_sched_barrier(0);
-        STAMP_WAIT2(6, As0.h1, "v[190:195]", B10.h1, "v[238:243]");
         mfma(acc[0][0].q[1], As0.h1, B10.h0);
         __builtin_amdgcn_sched_barrier(0);
         tail(std::integral_constant<int, kFirst>{});
@@ -499,7 +487,8 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
       STAMP_WAIT_AS1(3);
       mfma8(acc[1], As1, pb == 0 ? B00 : B10, pb == 0 ? B01 : B11, [&](auto i) __attribute__((always_inline)) {
         if constexpr (i.value == 2) tail(std::integral_constant<int, kFirst + 2>{});
-        if constexpr (i.value == 6) tail(std::integral_constant<int, kFirst + 3>{});
+        if constexpr (i.value == 4) tail(std::integral_constant<int, kFirst + 3>{});
+        if constexpr (i.value == 6) tail(std::integral_constant<int, kFirst + 4>{});
       });
       __builtin_amdgcn_sched_barrier(0);
       STAMP_RD_AS1(sa + adrA0 + lane16, 3 * kBlock6);
@@ -509,10 +498,13 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
       } else {
         STAMP_WAIT_AS0(3);
       }
+      const int stg1 = (stg == kNumStage6 - 1) ? 0 : stg + 1;
+      const uint32_t sn = lds0 + (uint32_t)(stg1 * kStage6);
       mfma8(acc[2], As0, pb == 0 ? B00 : B10, pb == 0 ? B01 : B11, [&](auto i) __attribute__((always_inline)) {
-        if constexpr (i.value == 2) tail(std::integral_constant<int, kFirst + 4>{});
-        if constexpr (i.value == 4) tail(std::integral_constant<int, kFirst + 5>{});
-        if constexpr (i.value == 6) tail(std::integral_constant<int, kFirst + 6>{});
+        if constexpr (i.value == 2) {
+          tail(std::integral_constant<int, kFirst + 5>{});
+          rq_begin();  // (addresses alone: the stage is asked for behind the barrier)
+        }
       });
       __builtin_amdgcn_sched_barrier(0);
       STAMP_WAIT_AS1(0);
@@ -526,24 +518,35 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
       }
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
-      rq_begin();
       __builtin_amdgcn_sched_barrier(0);
-      stg = (stg == kNumStage6 - 1) ? 0 : stg + 1;
-      {
-        // (after the tile's last step these reads fetch the next tile's first fragments, which the epilogue's
-        // registers cannot keep: they are dropped and read again by the next head)
-        const uint32_t sn = lds0 + (uint32_t)(stg * kStage6);
-        if constexpr (pb == 0) STAMP_RD9_PB1(sn + adrA0 + lane16, sn + adrB0 + lane16);
-        else STAMP_RD9_PB0(sn + adrA0 + lane16, sn + adrB0 + lane16);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      // block 3, the request's loads spread among its MFMAs
+      stg = stg1;
+      // block 3; among its MFMAs the reads of the next step's block 0 and weights, and the first loads of the request.  (After the
+      // tile's last step these reads fetch the next tile's first fragments, which the epilogue's registers cannot keep: they
+      // are dropped and read again by the next head.)
       const Frag& W0 = pb == 0 ? B00 : B10;
       const Frag& W1 = pb == 0 ? B01 : B11;
-      mfma8(acc[3], As1, W0, W1, [&](auto i) __attribute__((always_inline)) { rq_issue(std::integral_constant<int, i.value / 2 - 1>{}); });
+      STAMP_RD_AS0(sn + adrA0 + lane16, 0);
+      mfma8(acc[3], As1, W0, W1, [&](auto i) __attribute__((always_inline)) {
+        if constexpr (i.value == 2) {
+          if constexpr (pb == 0) STAMP_RD_B10(sn + adrB0 + lane16);
+          else STAMP_RD_B00(sn + adrB0 + lane16);
+        }
+        if constexpr (i.value == 4) {
+          if constexpr (pb == 0) STAMP_RD_B11(sn + adrB0 + lane16);
+          else STAMP_RD_B01(sn + adrB0 + lane16);
+        }
+        rq_issue(std::integral_constant<int, i.value / 2 - 1>{});
+      });
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (HI) {
-        if (has_hi) mfma8(acch, Hs, W0, W1, [](auto) {});
+        auto more = [&](auto i) __attribute__((always_inline)) { rq_issue(std::integral_constant<int, 2 + i.value / 2>{}); };
+        if (has_hi) {
+          mfma8(acch, Hs, W0, W1, more);
+        } else {
+          more(std::integral_constant<int, 2>{});
+          more(std::integral_constant<int, 4>{});
+          more(std::integral_constant<int, 6>{});
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
       rq_tail = true;  // the other loads follow among the MFMAs of the next step (or after the tile's last step)
@@ -553,7 +556,9 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
     {
       lane16 = lane_now() * 16u;
       const uint32_t sh = lds0 + (uint32_t)(stg * kStage6);
-      STAMP_RD9_PB0(sh + adrA0 + lane16, sh + adrB0 + lane16);
+      STAMP_RD_AS0(sh + adrA0 + lane16, 0);
+      STAMP_RD_B00(sh + adrB0 + lane16);
+      STAMP_RD_B01(sh + adrB0 + lane16);
     }
     for (int kt = 0; kt + 1 < KT; kt += 2) {
       step(std::integral_constant<int, 0>{});
