@@ -28,7 +28,34 @@ STAMP_HD uint32_t row_lane6(uint32_t r) { return (((r >> 1) & 12) + (r & 3)) * 1
 // byte offset of the 32 channels from c on; K steps are kt_bytes apart
 STAMP_HD uint32_t chan_off6(uint32_t c, uint32_t kt_bytes) { return (c >> 7) * kt_bytes + ((c >> 5) & 3) * 256; }
 
-// a fragment's 24 bytes -> their places; dst = its lane's place in part 0
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef uint32_t u6v __attribute__((ext_vector_type(6)));
+// 24 bytes of a fragment -> their places; dst = its lane's place in part 0, half = row_half6 of the row
+__device__ __forceinline__ void store24(uint8_t* dst, u6v w, bool half) {
+  const u4 a = {half ? w[2] : w[0], half ? w[3] : w[1], half ? w[4] : w[2], half ? w[5] : w[3]};
+  const u2 b = {half ? w[0] : w[4], half ? w[1] : w[5]};
+  *reinterpret_cast<u4*>(dst + (half ? 2 * kPart : 0)) = a;
+  *reinterpret_cast<u2*>(dst + kPart + (half ? 8 : 0)) = b;
+}
+// channels 2 i in ev[i], 2 i + 1 in od[i]: integers of magnitude up to 8 (or values that round to such)
+__device__ __forceinline__ u6v to_e2m3(f16v ev, f16v od) { return (u6v)__builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(ev, od, 8.0f); }
+// codes 16 h + l of magnitude up to 128 -> the fragments of h and l, l in [-8, 7]
+__device__ __forceinline__ void split_hi(f16v ev, f16v od, u6v& h, u6v& l) {
+  f16v hv[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) hv[p][i] = floorf(__builtin_fmaf(p ? od[i] : ev[i], 0.0625f, 0.5f));
+  h = to_e2m3(hv[0], hv[1]);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    ev[i] = __builtin_fmaf(-16.0f, hv[0][i], ev[i]);
+    od[i] = __builtin_fmaf(-16.0f, hv[1][i], od[i]);
+  }
+  l = to_e2m3(ev, od);
+}
+
+// the same by words, for fragments put together bit by bit
 __device__ __forceinline__ void store_frag6(uint8_t* dst, bool half, const uint64_t (&part)[3]) {
 #pragma unroll
   for (int w = 0; w < 3; ++w) {

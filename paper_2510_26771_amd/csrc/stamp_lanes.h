@@ -5,8 +5,11 @@
 
 namespace {
 
-typedef float f16v __attribute__((ext_vector_type(16)));
-typedef uint32_t u6v __attribute__((ext_vector_type(6)));
+using stamp_gemm::f16v;
+using stamp_gemm::split_hi;
+using stamp_gemm::store24;
+using stamp_gemm::to_e2m3;
+using stamp_gemm::u6v;
 
 struct LaneArgs {
   const void* X;
@@ -21,30 +24,10 @@ struct LaneArgs {
   int G, gridW;      // token grid: blocks per row, tokens per row
 };
 
-// 24 bytes of a fragment -> their places; dst = its lane's place in part 0, half = row_half6 of the row
-__device__ __forceinline__ void store24(uint8_t* dst, u6v w, bool half) {
-  const u4 a = {half ? w[2] : w[0], half ? w[3] : w[1], half ? w[4] : w[2], half ? w[5] : w[3]};
-  const u2v b = {half ? w[0] : w[4], half ? w[1] : w[5]};
-  *reinterpret_cast<u4*>(dst + (half ? 2 * kPart : 0)) = a;
-  *reinterpret_cast<u2v*>(dst + kPart + (half ? 8 : 0)) = b;
-}
-// channels 2 i in ev[i], 2 i + 1 in od[i]: integers of magnitude up to 8 (or values that round to such)
-__device__ __forceinline__ u6v to_e2m3(f16v ev, f16v od) { return (u6v)__builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(ev, od, 8.0f); }
-
 // codes of 8-bit rows, 16 h + l, as two fragments
 __device__ __forceinline__ void store_hi24(const Hi6Out& o, int m, int KT, f16v ev, f16v od, int c) {
-  f16v hv[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) hv[h][i] = floorf(__builtin_fmaf(h ? od[i] : ev[i], 0.0625f, 0.5f));
-  const u6v h = to_e2m3(hv[0], hv[1]);
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    ev[i] = __builtin_fmaf(-16.0f, hv[0][i], ev[i]);
-    od[i] = __builtin_fmaf(-16.0f, hv[1][i], od[i]);
-  }
-  const u6v l = to_e2m3(ev, od);
+  u6v h, l;
+  split_hi(ev, od, h, l);
   const uint32_t off = chan_off6((uint32_t)c, hi_step_bytes(o));
   hi_rows(o, m, KT, [&](uint8_t* dst, bool hh, int lo, bool lh) {
     store24(dst + off, h, hh);
