@@ -44,7 +44,8 @@ __device__ __forceinline__ int part_at(int row, int col) {
 // GRP: one scale per 64 channels (a half of a K step) and row / column: the sums are rescaled half by half, s_part holds fp32
 // AHEAD: the next step's operands are in flight while a step is multiplied.  That takes twice the registers, so it is for
 // launches that leave no CU a second workgroup: 64 x 11008 x 4096 (128 workgroups) 16.9 us against 18.9, 128 x 4096 x 4096
-// (256) 11.9 against 12.8, but 64 x 4096 x 11008 (344) 21.4 against 17.4.
+// (256) 11.9 against 12.8, but 64 x 4096 x 11008 (344) 21.4 against 17.4.  Up to 32 rows: WHT layer of 512 x 4096 -> 1024 43.0
+// without, 41.0 with, 2048 x 4096 -> 4096 81.3, 78.8.
 // NC: strips of 32 columns per workgroup.  Two: the rows' operand, the larger share of what a CU's vector memory path moves (64 bytes a
 // clock: that path is what bounds the loop), is read half as often.  512 x 4096 x 4096 39 us with one strip, 33 with two; 64 x 4096 x 11008
 // 17.2, 15.3, of which the loop 10 and 8, the launch and the sums of the waves 5, the top levels 2.
@@ -304,15 +305,25 @@ hipError_t launch(const Hi6Args& h, hipStream_t st) {
 // rows of this GEMM: all top rows of every sequence, or (own) the first khi of them
 namespace {
 int hi6_rows(const stamp_plan* p, int own) { return p->geom.B * (own ? p->geom.khi : p->geom.k); }
-int hi6_np(int M) { return M <= 32 ? 1 : 2; }
 // 64 rows per workgroup (more workgroups, each with its waves' depth split eight ways), 128 where a sequence has that many
 // top rows and its top levels are inverted here
 int hi6_ng(const stamp_plan* p, int own) { return !p->geom.ident && !own && p->geom.L > 0 && p->geom.k > 64 ? 2 : 1; }
+int hi6_strips(const stamp_plan* p) { return (p->geom.N + 63) / 64 * 2; }
+// 32-row pairs of a wave: one for up to 32 rows, and where two would leave half of the CUs without a workgroup (unless a sequence's top
+// levels need the rows together): more CUs then ask memory for the weights.  64 x 4096 x 4096 with weights that are not in the
+// caches 14.0 us in 128 workgroups, 10.3 in 256; layers, WHT of 1024 x 2048 -> 2048 42.1, 39.3, 2 x 256 x 4096 -> 2048 45.4, 40.6; 4 x
+// 300 tokens without transform, 1024 -> 768 21.9, 19.8.
+int hi6_np(const stamp_plan* p, int own) {
+  const int M = hi6_rows(p, own);
+  if (M <= 32) return 1;
+  const bool together = p->gen.group != 0 || (!p->geom.ident && !own && p->geom.L > 0 && p->geom.k > 32);
+  return !together && 2 * hi6_strips(p) * ((M + 63) / 64) <= stamp_device_cus() ? 1 : 2;
+}
 }  // namespace
 
 size_t stamp_hi6_bytes(const stamp_plan* p, int own) {
-  const int M = hi6_rows(p, own), gr = 32 * hi6_np(M);
-  return (size_t)((M + gr - 1) / gr) * (p->Kpad / 128) * (2 * hi6_np(M) * kBlock6);
+  const int M = hi6_rows(p, own), np = hi6_np(p, own), gr = 32 * np;
+  return (size_t)((M + gr - 1) / gr) * (p->Kpad / 128) * (2 * np * kBlock6);
 }
 
 // Plans that this kernel serves.  Every workgroup reads its rows' and columns' whole depth from L2, so its time goes with
@@ -366,7 +377,7 @@ size_t stamp_hi_tiles_bytes(const stamp_plan* p) {
 }
 
 StampHiOut stamp_hi6_out(const stamp_plan* p, uint8_t* a6, int own, const StampHiTiles& ht) {
-  return StampHiOut{a6, hi6_np(hi6_rows(p, own)), own ? p->geom.khi : p->geom.k, ht};
+  return StampHiOut{a6, hi6_np(p, own), own ? p->geom.khi : p->geom.k, ht};
 }
 
 StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own, const StampHiTiles& ht) {
@@ -380,7 +391,7 @@ StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6
   hp.KT = p->Kpad / 128;
   hp.nseq = g.B;
   const int gr = 32 * hp.out.np;  // (the rows' own kernel reads whole groups)
-  // A thread converts 32 channels with some 1500 instructions, and a wave with a few of them takes as long as a full one: narrow layers
+  // A thread converts 32 channels (with some 200 instructions; 1500 when this was measured), and a wave with a few of them takes as long as a full one: narrow layers
   // have threads for the rows (no top levels: each has one place), or for the places that can hold one, the first of a
   // tile.  Wide ones, where a place is whole waves, have them for all 16, which spreads those with work over more CUs.
   // linear_forward_q, us, all 16 places against these: blocks of 64, 4 x 1024 x 64 -> 1024 18.8, 12.4 (the rows' own kernel 15.3), 8 x
@@ -403,13 +414,15 @@ hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float*
   h.a.ld_out = ld_out;
   if (own) h.a.g.k = p->geom.khi;  // the kernel sees a plan of khi top rows per sequence
   h.a.rag = p->rag;
-  h.np = hi6_np(h.a.M);
+  h.np = hi6_np(p, own);
   h.ng = hi6_ng(p, own);
   h.mode = mode;
   h.norm = norm;
   h.Y = Y;
   // workgroups up to one per CU: the rule of AHEAD
-  if (h.np == 2 && (int64_t)((h.a.N + 63) / 64 * 2) * ((h.a.M + 64 * h.ng - 1) / (64 * h.ng)) <= stamp_device_cus()) return launch<2, false, true>(h, st);
+  const int rows = 32 * h.np * h.ng;
+  if ((int64_t)hi6_strips(p) * ((h.a.M + rows - 1) / rows) <= stamp_device_cus())
+    return h.np == 2 ? launch<2, false, true>(h, st) : launch<1, false, true>(h, st);
   if (h.np == 2 && h.ng == 1) return launch<2, false, false, 2>(h, st);
   return h.np == 1 ? launch<1, false, false>(h, st) : launch<2, false, false>(h, st);
 }
@@ -426,7 +439,7 @@ hipError_t stamp_launch_hi6_grp(const stamp_plan* p, const uint8_t* h6, const fl
   if (own) h.a.g.k = p->bgeom.khi;
   h.a.M = h.a.g.B * h.a.g.k;
   h.a.ld_out = p->Npad;
-  h.np = hi6_np(h.a.M);
+  h.np = h.a.M <= 32 ? 1 : 2;
   h.ng = 1;
   h.norm = 1.0f;
   h.sa = sh;
