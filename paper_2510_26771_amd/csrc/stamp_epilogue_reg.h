@@ -338,6 +338,10 @@ __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const Acc (
   const int n = nw + 2 * l32;
   const int nvalid = a.N - n;
   if constexpr (EPI == 1 || EPI == 3) {
+    // a row goes to the output row of its own number or nowhere (dst < 0): bytes from the tile's first one, which fit 32 bits (RegOut)
+    const uint32_t pitch = (uint32_t)(EPI == 1 ? a.ld_out : a.N) * (uint32_t)(EPI == 3 && YBF16 ? 2 : 4);
+    char* const base = reinterpret_cast<char*>(a.out) + (size_t)m0 * pitch;
+    const uint32_t off = (uint32_t)(wm * 128 + 64 * kg) * pitch + (uint32_t)n * (uint32_t)(EPI == 3 && YBF16 ? 2 : 4);
 #pragma unroll
     for (int mi = 0; mi < 4; ++mi) {
 #pragma unroll
@@ -348,6 +352,8 @@ __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const Acc (
         const f4 rf = *reinterpret_cast<const f4*>(s_rowfac + r0);
         const f4 rz = *reinterpret_cast<const f4*>(s_rowz + r0);
         const v4i rd = *reinterpret_cast<const v4i*>(s_rowdst + r0);
+        uint32_t oq = off + (uint32_t)row16(mi, 4 * q) * pitch;
+        if constexpr (EPI == 3) asm volatile("" : "+v"(oq));  // (computed here: the offsets of all rows at once would not fit the registers)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           float c0 = acc[mi][0][4 * q + j], c1 = acc[mi][1][4 * q + j];
@@ -356,18 +362,18 @@ __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const Acc (
             c1 = __builtin_fmaf(-rz[j], eo.cs[1], c1);
           }
           if (rd[j] >= 0 && nvalid > 0) {
+            const uint32_t o = oq + (uint32_t)j * pitch;
             if constexpr (EPI == 1) {  // (fp32 rows that the next kernel reads: kept in the caches)
-              float* const o = reinterpret_cast<float*>(a.out) + (size_t)rd[j] * a.ld_out + n;
               const float y0 = (c0 * rf[j]) * eo.sw[0], y1 = (c1 * rf[j]) * eo.sw[1];
               if constexpr (VEC) {
-                *reinterpret_cast<f2*>(o) = f2{y0, y1};
+                *reinterpret_cast<f2*>(base + o) = f2{y0, y1};
               } else {
-                o[0] = y0;
-                if (nvalid > 1) o[1] = y1;
+                *reinterpret_cast<float*>(base + o) = y0;
+                if (nvalid > 1) *reinterpret_cast<float*>(base + o + 4) = y1;
               }
             } else {
-              put_pair<YBF16, VEC>(a.out, (size_t)rd[j] * a.N + n, __builtin_fmaf(c0 * rf[j], eo.sw[0], eo.bias[0]),
-                                   __builtin_fmaf(c1 * rf[j], eo.sw[1], eo.bias[1]), nvalid);
+              put_pair_at<YBF16, VEC>(base, o, __builtin_fmaf(c0 * rf[j], eo.sw[0], eo.bias[0]), __builtin_fmaf(c1 * rf[j], eo.sw[1], eo.bias[1]),
+                                      nvalid);
             }
           }
         }
