@@ -318,7 +318,8 @@ typedef enum {
   STAMP_ROUTE_GROUP_QUANT = 512,      /* per-block scales on blocks of a token grid: transform and quantizer in one kernel */
   STAMP_ROUTE_HI_IN_TILES = 1024,     /* 8-bit rows in the tiles of the 4-bit rows' GEMM */
   STAMP_ROUTE_PARTS = 2048,           /* with STAMP_ROUTE_DIRECT: blocks quantized in parts of 8 tokens */
-  STAMP_ROUTE_Q_HI_IN_TILES = 4096    /* STAMP_ROUTE_HI_IN_TILES in stamp_linear_forward_q, whose operand has a place of its own */
+  STAMP_ROUTE_Q_HI_IN_TILES = 4096,   /* STAMP_ROUTE_HI_IN_TILES in stamp_linear_forward_q, whose operand has a place of its own */
+  STAMP_ROUTE_TILES_PAIR = 8192       /* 4-bit rows in 128 x 256 tiles, two workgroups per CU */
 } stamp_route_t;
 int32_t stamp_debug_routes(const stamp_plan_t* plan);
 

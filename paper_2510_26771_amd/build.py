@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libstamp_hip.so")
 
-SOURCES = ["stamp_bottom1d_6.hip", "stamp_bottom1d_5.hip", "stamp_bottom1d_7.hip", "stamp_gemm6.hip", "stamp_gemm6_half.hip", "stamp_gemm6_hi.hip",
+SOURCES = ["stamp_bottom1d_6.hip", "stamp_bottom1d_5.hip", "stamp_bottom1d_7.hip", "stamp_gemm6.hip", "stamp_gemm6_half.hip", "stamp_gemm6_pair.hip", "stamp_gemm6_hi.hip",
            "stamp_actquant.hip", "stamp_bottom1d_4.hip", "stamp_bottom1d_3.hip", "stamp_api.hip", "stamp_weight.hip", "stamp_gemm.hip", "stamp_hi6.hip", "stamp_grouped.hip", "stamp_inverse.hip", "stamp_probe.hip", "stamp_general.hip", "stamp_dct.hip", "stamp_lanes1d.hip", "stamp_lanes2d.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -1,4 +1,5 @@
-// The FP6 GEMM kernel over the 4-bit rows and its launchers for one tile size (STAMP_GEMM6_WAVES waves per workgroup: 8 or 4).
+// The FP6 GEMM kernel over the 4-bit rows and its launchers for one tile size (STAMP_GEMM6_WAVES waves per workgroup: 8 or 4; with
+// STAMP_GEMM6_PAIR two workgroups of 4 per CU).
 // Operand layout: stamp_gemm6.hip.
 #ifndef STAMP_GEMM6_KERNEL_H_
 #define STAMP_GEMM6_KERNEL_H_
@@ -34,7 +35,11 @@ using namespace stamp_gemm;
 // takes 0.64 of the time of a 256 x 256 one (8.5 us + 0.455 us per K step against 12.8 + 0.72, all CUs busy): for shapes that
 // leave CUs idle (the rule stands at stamp_gemm6_half_tiles).
 constexpr int BN6 = 256;
-constexpr int kNumStage6 = 3;
+//
+// PAIR (WAVES = 4): two workgroups per CU, two stages each (72 KB): one multiplies while the other is in its epilogue, and the last
+// tiles are half as large; but a CU moves half as much again per product.  For shallow layers of more than one round (the rule
+// stands at stamp_gemm6_pairs).
+constexpr int vm_wait6(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }  // s_waitcnt vmcnt(n)
 //
 // HI (WAVES = 4): the tile's 8-bit rows ride along as a fifth block of 32 operand rows (h of 16 places, then l; stamp_hi_places),
 // 3 KB more per K step and two MFMAs more per wave and half; their sums, the levels above and the block sums stay in
@@ -162,7 +167,7 @@ __device__ __forceinline__ void tile_of_sid(int sid, int mt, int nt, int& tm, in
 
 // SYM: a fused-mode kernel for plans with symmetric activation codes (no offset term in the epilogue)
 // RAG: fused mode over the blocks of a 1-D Haar transform of any length (StampRag); ODD: for odd d_out
-template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM = false, bool RAG = false, bool ODD = false, int WAVES = 8, bool HI = false>
+template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM = false, bool RAG = false, bool ODD = false, int WAVES = 8, bool HI = false, bool PAIR = false>
 __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm6(const GemmArgs a) {
   using Acc = AccF6Lo;
   constexpr int BMW = Tile6<WAVES, HI>::BMW, kStageA = Tile6<WAVES, HI>::kStageA, kStage6 = Tile6<WAVES, HI>::kStage;
@@ -170,6 +175,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
   constexpr int NIW = NI;  // 32-column MFMA blocks per wave along N
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   constexpr int NT = 64 * WAVES;  // threads
+  constexpr int kNumStage6 = PAIR ? 2 : 3;
   constexpr int kMainBytes = kNumStage6 * kStage6;
   uint8_t* const row_info = smem + kMainBytes;  // two buffers, alternating from tile to tile
   constexpr int kHiInfo = kRowInfoBytes + (RAG ? 256 : 0);  // RAG: + the token factors of a short block
@@ -311,9 +317,9 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
   const uint32_t adrH0 = (uint32_t)kStageAB;
   const uint32_t adrB0 = (uint32_t)(kStageA + (wn >> 1) * kStageB6 + ((wn & 1) * 2) * kBlock6);
 
-  // ---- prologue: stages 0 and 1 requested, landed and published by a barrier; stage 2 requested ----
-  request_next();
-  request_next();
+  // ---- prologue: all stages but one requested, landed and published by a barrier; the last one requested ----
+#pragma unroll
+  for (int i = 0; i < kNumStage6 - 1; ++i) request_next();
   {
     int tm0, tn0;
     tile_of_sid(first + local, mt, nt, tm0, tn0);
@@ -339,7 +345,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   request_next();
-  int landed = 1;  // steps from here on whose loads are known to have landed (their barrier needs no wait)
+  int landed = kNumStage6 - 2;  // steps from here on whose loads are known to have landed (their barrier needs no wait)
   int stg = 0;     // stage of the step about to be multiplied
   int rbuf = 0;    // row-info buffer of the current tile
 
@@ -514,7 +520,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
       if (landed > 0) {
         --landed;
       } else {
-        __builtin_amdgcn_s_waitcnt(0x0F70 | kLoadsPerStep);  // vmcnt(one step's loads): the request of the step before may be in flight
+        __builtin_amdgcn_s_waitcnt(vm_wait6(kLoadsPerStep * (kNumStage6 - 2)));  // three stages: the request of the step before may be in flight
       }
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
@@ -574,7 +580,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
     // its stores: the counter retires in order, so a later wait for a load would also wait for every store before
     // it.  The epilogue waits for that itself, after its lane swaps (the plain modes: before they start); after it
     // the next two steps therefore need no wait.
-    landed = 2;
+    landed = kNumStage6 - 1;
     // Per-lane values of the epilogue are derived from an opaque copy of the lane number, so that they are
     // computed here, once per tile, instead of being carried in registers across the main loop (which has none
     // to spare: a spilled value would be reloaded with a wait for all outstanding loads inside that loop).
@@ -642,6 +648,11 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
   }
 }
 
+#ifdef STAMP_GEMM6_PAIR
+constexpr bool kPair = true;
+#else
+constexpr bool kPair = false;
+#endif
 // whether this file's kernels take the 8-bit rows along
 #ifdef STAMP_GEMM6_HI
 constexpr bool kHiTiles = true;
@@ -649,17 +660,20 @@ constexpr bool kHiTiles = true;
 constexpr bool kHiTiles = false;
 #endif
 
-int gemm6_workgroups(int tiles) { return tiles < stamp_device_cus() ? tiles : stamp_device_cus(); }
+int gemm6_workgroups(int tiles) {
+  const int most = (kPair ? 2 : 1) * stamp_device_cus();
+  return tiles < most ? tiles : most;
+}
 
 template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM, bool RAG = false, bool ODD = false, bool HI = kHiTiles>
 hipError_t launch_k(const GemmArgs& a, hipStream_t st) {
   constexpr int WAVES = STAMP_GEMM6_WAVES;
-  constexpr size_t lds = (size_t)kNumStage6 * Tile6<WAVES, HI>::kStage + 2 * (kRowInfoBytes + (RAG ? 256 : 0) + (HI ? kHiInfoBytes : 0));
+  constexpr size_t lds = (size_t)(kPair ? 2 : 3) * Tile6<WAVES, HI>::kStage + 2 * (kRowInfoBytes + (RAG ? 256 : 0) + (HI ? kHiInfoBytes : 0));
   static size_t lds_done[kStampMaxDevices] = {};
-  hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD, WAVES, HI>), lds, lds_done);
+  hipError_t e = stamp_allow_lds(reinterpret_cast<const void*>(&k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD, WAVES, HI, kPair>), lds, lds_done);
   if (e != hipSuccess) return e;
   const int mt = (a.M + Tile6<WAVES>::BMW - 1) / Tile6<WAVES>::BMW, nt = a.Npad / BN6;
-  hipLaunchKernelGGL((k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD, WAVES, HI>), dim3(gemm6_workgroups(mt * nt)), dim3(64 * WAVES), lds, st, a);
+  hipLaunchKernelGGL((k_gemm6<EPI, RB, IS2D, YBF16, SYM, RAG, ODD, WAVES, HI, kPair>), dim3(gemm6_workgroups(mt * nt)), dim3(64 * WAVES), lds, st, a);
   return hipGetLastError();
 }
 

@@ -614,6 +614,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, typename Acc::V (&ac
 stamp_gemm::GemmArgs stamp_gemm_args(const stamp_plan* p, const float* scales, void* out);
 // the FP6 GEMM on 128 x 256 tiles
 hipError_t stamp_gemm6_half(const stamp_gemm::GemmArgs& a, int mode, hipStream_t st);
+hipError_t stamp_gemm6_pair(const stamp_gemm::GemmArgs& a, int mode, hipStream_t st);
 hipError_t stamp_gemm6_half_hi(const stamp_gemm::GemmArgs& a, hipStream_t st);  // a.ht.on: the 8-bit rows along
 
 #endif  // STAMP_GEMM_COMMON_H_

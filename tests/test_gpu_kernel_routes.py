@@ -639,6 +639,40 @@ def test_both_gemm_tile_sizes(w):
                  routes=("tiles_128" if w.name.startswith("t128") else "-tiles_128",))
 
 
+# ---- two workgroups of 128 x 256 tiles per CU: few tiles more than they hold at once (a row more than a tile, odd d_out), depths of 1, 9 and 10
+# K steps, every block length; and the sizes beside them that keep 256 x 256 tiles: a last round more than half full, one round
+PAIRS = [_tiles("pair_ident_odd", 8193, 2049, 128, xform="identity", levels=0), _tiles("pair_haar32_10_steps", 2048, 8448, 1248, levels=11, k_hi=64),
+         _tiles("pair_haar8_asym", 4096, 4354, 1152, levels=3, k_hi=512, act_quant="asym"), _tiles("pair_haar16_odd", 2048, 8449, 224, levels=4, k_hi=128, act_quant="asym"),
+         _tiles("pair_grid8", 4096, 4354, 96, xform="haar2d", grid_h=64, grid_w=64, levels=3, k_hi=64, corr_len=4.0),
+         _tiles("pair_rag64", 2100, 8193, 160, levels=6, skip_first=True, k_hi=32),
+         _tiles("t256_last_round_full", 4096, 6900, 1184, levels=3, k_hi=64), _tiles("t256_one_round", 4096, 4096, 96, levels=3, k_hi=64)]
+
+
+@pytest.mark.parametrize("w", PAIRS, ids=[w.name for w in PAIRS])
+def test_pairs_of_tiles(w):
+    tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16" if w.d_out % 4 else "f32", check_acc=False, engines=("fp6",),
+                 routes=("tiles_pair" if w.name.startswith("pair") else "-tiles_pair",))
+
+
+# ---- 8-bit rows' kernel: 32 rows a workgroup where 64 leave half of the CUs idle (either side of that line, a row more and less than whole
+# groups), two strips of columns a workgroup above one workgroup per CU, with and without top levels, odd d_out, all its outputs
+def _few(name, n, k, **kw):
+    base = dict(xform="identity", levels=0, seq_len=k + 40, d_in=416, d_out=n, k_hi=k)
+    base.update(kw)
+    return _tiles("few_" + name, base.pop("seq_len"), base.pop("d_out"), base.pop("d_in"), **base)
+
+
+FEW = [_few("ident_64_line", 4096, 64), _few("ident_64_above", 4097, 64), _few("ident_33", 1000, 33, act_quant="asym"), _few("ident_31", 8300, 31),
+       _few("ident_strips", 8301, 65, act_quant="asym"), _few("wht_33", 515, 33, xform="wht", seq_len=256), _few("wht_strips", 8258, 40, xform="wht", seq_len=64),
+       _few("tops_strips", 12290, 64, xform="haar1d", levels=9, seq_len=512), _few("tops_128", 8256, 128, xform="haar1d", levels=10, seq_len=1024),
+       _few("rag_strips", 8705, 64, xform="haar1d", levels=3, seq_len=700, skip_first=True)]
+
+
+@pytest.mark.parametrize("w", FEW, ids=[w.name for w in FEW])
+def test_rows_and_strips_of_the_8bit_rows(w):
+    tl.full_case(w, with_bias=True, check_unfused=False, y_dtype="bf16" if w.d_out % 4 else "f32", check_acc=False, engines=("fp6",), routes=("hi_fp6",))
+
+
 # ---- split channels without top levels: the bottom kernel's two passes carry the block sums' maxima too (a last split of one
 # channel group, both quantizer forms, every block sum at 8 bits or only some, one block length of the packed codes)
 SPLIT_TOP = [_wl("split_top_f32_asym", seq_len=64, d_in=4128, k_hi=3, act_quant="asym", mean_shift=0.5, seed=601),
