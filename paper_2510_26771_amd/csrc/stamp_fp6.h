@@ -38,7 +38,13 @@ __device__ __forceinline__ void store24(uint8_t* dst, u6v w, bool half) {
   *reinterpret_cast<u2*>(dst + kPart + (half ? 8 : 0)) = b;
 }
 // channels 2 i in ev[i], 2 i + 1 in od[i]: integers of magnitude up to 8 (or values that round to such)
-__device__ __forceinline__ u6v to_e2m3(f16v ev, f16v od) { return (u6v)__builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(ev, od, 8.0f); }
+// (An asm statement, so that the result has registers of its own: the instruction writes before it has read everything, and the builtin's
+// result was placed across its operands: results from v4 on, operands from v2 on, came out wrong.)
+__device__ __forceinline__ u6v to_e2m3(f16v ev, f16v od) {
+  u6v r;
+  asm("v_cvt_scalef32_2xpk16_fp6_f32 %0, %1, %2, %3" : "=&v"(r) : "v"(ev), "v"(od), "s"(8.0f));
+  return r;
+}
 // codes 16 h + l of magnitude up to 128 -> the fragments of h and l, l in [-8, 7]
 __device__ __forceinline__ void split_hi(f16v ev, f16v od, u6v& h, u6v& l) {
   f16v hv[2];
@@ -89,19 +95,6 @@ __device__ __forceinline__ void chunk_to_e2m3(u4 w, uint64_t (&part)[3]) {
   part[0] = lo[0] | ((uint64_t)(hi[0] | (lo[1] << 16)) << 32);
   part[1] = ((lo[1] >> 16) | (hi[1] << 16)) | ((uint64_t)lo[2] << 32);
   part[2] = (hi[2] | (lo[3] << 16)) | ((uint64_t)((lo[3] >> 16) | (hi[3] << 16)) << 32);
-}
-
-// 32 signed values of magnitude at most 8 -> 24 bytes of E2M3 numbers value / 8
-__device__ __forceinline__ void values_to_e2m3(const int (&v)[32], uint64_t (&part)[3]) {
-#pragma unroll
-  for (int w = 0; w < 3; ++w) part[w] = 0;
-#pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    const uint64_t f = (uint64_t)((uint32_t)abs(v[i]) | ((uint32_t)(v[i] >> 31) & 32u));
-    const int bit = 6 * i, w = bit >> 6, sh = bit & 63;
-    part[w] |= f << sh;
-    if (sh > 58) part[w + 1] |= f >> (64 - sh);
-  }
 }
 
 }  // namespace stamp_gemm

@@ -212,11 +212,9 @@ struct GrpPack {
   StampGeom g;
   int KT, M, own, hi_used, np, nhi;  // nhi: threads of the 8-bit rows
 };
-__device__ __forceinline__ void load_codes32(const int8_t* q, int (&v)[32]) {
-  const u4 a = reinterpret_cast<const u4*>(q)[0], b = reinterpret_cast<const u4*>(q)[1];
-  const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-  for (int c = 0; c < 32; ++c) v[c] = (int)(w[c >> 2] << (24 - 8 * (c & 3))) >> 24;
+__device__ __forceinline__ void load_codes32(const int8_t* q, u4 (&w)[2]) {
+  w[0] = reinterpret_cast<const u4*>(q)[0];
+  w[1] = reinterpret_cast<const u4*>(q)[1];
 }
 __device__ __forceinline__ f2 row_scales(const GrpPack& q, size_t row, int kt, float f) {
   const int ng = q.g.d >> 6;
@@ -227,8 +225,8 @@ __global__ __launch_bounds__(256) void k_grp_pack(const GrpPack q) {
   const StampGeom& g = q.g;
   int i = blockIdx.x * 256 + threadIdx.x;
   const int nhi = (q.nhi + 255) / 256 * 256;
-  int v[32];
-  uint64_t part[3];
+  u4 w[2] = {};
+  f16v ev, od;
   if (i < nhi) {
     if (i >= q.nhi) return;
     const int nf = q.KT * 4, m = i / nf, frag = i - m * nf, kt = frag >> 2, f = frag & 3;
@@ -236,20 +234,13 @@ __global__ __launch_bounds__(256) void k_grp_pack(const GrpPack q) {
     const int b = m / q.hi_used, slot = m - b * q.hi_used;
     const bool there = m < Mh;
     const size_t row = (size_t)b * g.s + slot;
-    int h[32];
-#pragma unroll
-    for (int c = 0; c < 32; ++c) v[c] = 0;
-    if (there && frag * 32 < g.d) load_codes32(q.codes + row * g.d + frag * 32, v);
-#pragma unroll
-    for (int c = 0; c < 32; ++c) {
-      h[c] = (v[c] + 8) >> 4;
-      v[c] -= 16 * h[c];
-    }
+    if (there && frag * 32 < g.d) load_codes32(q.codes + row * g.d + frag * 32, w);
+    codes32(w, ev, od);
+    u6v h, l;
+    split_hi(ev, od, h, l);
     uint8_t* dst = q.h6 + ((size_t)grp * q.KT + kt) * (2 * q.np * kBlock6) + (r >> 5) * (2 * kBlock6) + (f & 1) * 512 + (r & 31) * 16;
-    values_to_e2m3(h, part);
-    store_frag(dst, f, part);
-    values_to_e2m3(v, part);
-    store_frag(dst + kBlock6, f, part);
+    store24(dst, h, f >> 1);
+    store24(dst + kBlock6, l, f >> 1);
     if (f == 0) {
       f2 s = {0.0f, 0.0f};
       if (there) s = row_scales(q, row, kt, ldexpf(64.0f, -stamp_level_of_top_slot(slot, g.k, g.G, 1, g.r, g.L)));
@@ -262,19 +253,17 @@ __global__ __launch_bounds__(256) void k_grp_pack(const GrpPack q) {
   const int f = i & 3, row = (i >> 2) & 255, tk = i >> 10, mt = tk / q.KT, kt = tk - mt * q.KT;
   const int m = mt * 256 + row;
   f2 s = {0.0f, 0.0f};
-#pragma unroll
-  for (int c = 0; c < 32; ++c) v[c] = 0;
   if (m < q.M) {
     const int b = m / g.s, pr = m - b * g.s, j = pr / g.R, e = pr - j * g.R;
     if (e != 0 || (q.own && j >= g.khi)) {
       const int slot = e == 0 ? j : stamp_slot_of_block_e_2d(j / g.G, j % g.G, e, g.G);
       const size_t r = (size_t)b * g.s + slot;
-      if (kt * 128 + f * 32 < g.d) load_codes32(q.codes + r * g.d + kt * 128 + f * 32, v);
+      if (kt * 128 + f * 32 < g.d) load_codes32(q.codes + r * g.d + kt * 128 + f * 32, w);
       if (f == 0) s = row_scales(q, r, kt, ldexpf(64.0f, -(e == 0 ? g.r : stamp_level_of_e_2d(e, g.r))));
     }
   }
-  values_to_e2m3(v, part);
-  store_frag(q.a6 + (size_t)tk * kStageA6 + (row >> 5) * kBlock6 + (f & 1) * 512 + (row & 31) * 16, f, part);
+  codes32(w, ev, od);
+  store24(q.a6 + (size_t)tk * kStageA6 + (row >> 5) * kBlock6 + (f & 1) * 512 + (row & 31) * 16, to_e2m3(ev, od), f >> 1);
   if (f == 0) *reinterpret_cast<f2*>(q.sa + ((size_t)tk * 256 + row) * 2) = s;
 }
 
@@ -284,15 +273,13 @@ __global__ __launch_bounds__(256) void k_grp_wpack(const int8_t* __restrict__ qw
                                                    float* __restrict__ swp, int d, int Npad, int Npad256, int KT) {
   const int n = blockIdx.x * 256 + threadIdx.x, frag = blockIdx.y, kt = frag >> 2, f = frag & 3;
   if (n >= Npad256) return;
-  int v[32];
-#pragma unroll
-  for (int c = 0; c < 32; ++c) v[c] = 0;
-  if (n < Npad && frag * 32 < d) load_codes32(qw + (size_t)n * d + frag * 32, v);
-  uint64_t part[3];
-  values_to_e2m3(v, part);
+  u4 w[2] = {};
+  f16v ev, od;
+  if (n < Npad && frag * 32 < d) load_codes32(qw + (size_t)n * d + frag * 32, w);
+  codes32(w, ev, od);
   const int blk = ((n & 127) >> 6) * 2 + (n & 1), r = (n & 63) >> 1;
   const size_t tk = (size_t)(n >> 7) * KT + kt;
-  store_frag(b6 + tk * kStageB6 + (size_t)blk * kBlock6 + (f & 1) * 512 + r * 16, f, part);
+  store24(b6 + tk * kStageB6 + (size_t)blk * kBlock6 + (f & 1) * 512 + r * 16, to_e2m3(ev, od), f >> 1);
   if (f == 0) {
     const int ng = d >> 6, g0 = 2 * kt;
     f2 s = {0.0f, 0.0f};

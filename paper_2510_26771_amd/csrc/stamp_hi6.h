@@ -25,12 +25,13 @@ struct Frag6 {
   __device__ __forceinline__ v8i h1() const { return (v8i)__builtin_shufflevector(p1, p2, 2, 3, 4, 5, 6, 7, -1, -1); }
 };
 
-// a fragment's 24 bytes -> its places in a block; dst = (lane group, row) of the block
-__device__ __forceinline__ void store_frag(uint8_t* dst, int f, const uint64_t (&part)[3]) {
+// 32 codes (bytes) -> floats, channels 2 i in ev[i], 2 i + 1 in od[i]
+__device__ __forceinline__ void codes32(const u4 (&w)[2], f16v& ev, f16v& od) {
 #pragma unroll
-  for (int w = 0; w < 3; ++w) {
-    const int off = (f >> 1) * 24 + w * 8;
-    *reinterpret_cast<uint64_t*>(dst + (off >> 4) * kPart + (off & 15)) = part[w];
+  for (int i = 0; i < 16; ++i) {
+    const uint32_t x = w[i >> 3][(i >> 1) & 3] << (16 - 16 * (i & 1));
+    ev[i] = (float)((int)(x << 8) >> 24);
+    od[i] = (float)((int)x >> 24);
   }
 }
 
@@ -70,12 +71,7 @@ __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
   }
   // (field by field, some 1500 instructions in place of these 200: q_hi and q_lo of 2 x 1024 x 4096 in 6.4 us, now 6.0)
   f16v ev, od;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const uint32_t x = w[i >> 3][(i >> 1) & 3] << (16 - 16 * (i & 1));
-    ev[i] = (float)((int)(x << 8) >> 24);
-    od[i] = (float)((int)x >> 24);
-  }
+  codes32(w, ev, od);
   u6v hh, ll;
   split_hi(ev, od, hh, ll);
   store24(dst, hh, !o.ht.on && hf);
