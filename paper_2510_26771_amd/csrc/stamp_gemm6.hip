@@ -161,12 +161,13 @@ bool stamp_gemm6_half_tiles(int M, int Npad) {
 // 4 81.8, 78.5.  2048: 1 40.8, 41.8, 1.1 to 1.5 56.4, 53.3, 1.75 57.8, 58.4, 2 65.7, 62.8, 2.25 80.6, 76.4, 3 84.2, 85.4.  3072: 1.1 to 1.5 74.5,
 // 73.2, 1.75 75.9, 77.9, 2 83.7, 82.0, 3 109.9, 113.2.  4096: 1.25 86.0, 85.6, 1.5 86.8, 87.2, 1.75 88.3, 92.7, 2.25 126.1, 123.4, 4 158.7,
 // 165.7; 2048 x 4096 -> 11008 (1.34 rounds) 89.4, 88.7, with the first token left out 87.3, 85.7.  Depth 8192, 56 rounds: 2743, 3567 the
-// GEMM alone.  Hence: shallow layers from one round on, deeper ones where the last round is up to half full.
+// GEMM alone.  2 x 64 x 64 grid, 704 -> 3080 (1.6 rounds): 46.6, 49.2.  Hence: where the last round is up to half full, shallow layers also
+// where it is full.
 bool stamp_gemm6_pairs(int M, int Npad, int Kpad) {
   const int cus = stamp_device_cus(), kt = Kpad / BK;
   const int64_t tiles = (int64_t)((M + 127) / 128) * (Npad / BN6), rem = tiles % (2 * cus);
   if (tiles <= 2 * cus || kt > 32) return false;
-  if (kt <= 9) return true;
+  if (kt <= 9) return rem <= cus;
   if (rem == 0) return kt <= 24 && tiles == 4 * cus;
   return kt <= 24 ? rem <= cus : 4 * rem <= 3 * cus;
 }
