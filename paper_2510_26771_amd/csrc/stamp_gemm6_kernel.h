@@ -32,7 +32,7 @@ using namespace stamp_gemm;
 // block, the others in the next step.
 //
 // WAVES = 4: tile 128 x 256, one wave on every SIMD, 36 KB per K step; the same loop, nine loads per wave and step.  A tile
-// takes 0.64 of the time of a 256 x 256 one (8.5 us + 0.455 us per K step against 12.8 + 0.72, all CUs busy): for shapes that
+// takes 0.64 of the time of a 256 x 256 one (8.5 us + 0.455 us per K step against 12.8 + 0.72, all CUs busy, with 32 x 32 x 64 MFMAs): for shapes that
 // leave CUs idle (the rule stands at stamp_gemm6_half_tiles).
 constexpr int BN6 = 256;
 //
