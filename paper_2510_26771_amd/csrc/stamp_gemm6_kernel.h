@@ -85,17 +85,18 @@ __device__ __forceinline__ void hi_block_sums(const GemmArgs& a, const AccTiles 
   float val[kHiPlaces][2];
 #pragma unroll
   for (int ni = 0; ni < 2; ++ni) {
-    float r[16];
+    float x[8], y[8];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) r[v] = acch[ni][v];
-    columns16(r);  // r[8 h + 4 th + v]: place 8 kg + 4 h + v of column l32
+    for (int i = 0; i < 8; ++i) x[i] = __builtin_fmaf(16.0f, acch[ni][8 * (i >> 2) + (i & 3)], acch[ni][8 * (i >> 2) + 4 + (i & 3)]) * 64.0f;
+    swap16x4(x[0], x[4], x[1], x[5], x[2], x[6], x[3], x[7]);  // x[i]: place 8 kg + i of column l32
 #pragma unroll
-    for (int v = 0; v < 8; ++v) {
-      const int i = 8 * (v >> 2) + (v & 3);
-      float x = __builtin_fmaf(16.0f, r[i], r[i + 4]) * 64.0f, y = x;
-      swap32(x, y);  // x: lane group 0's place, y: lane group 1's, in both
-      val[v][ni] = x;
-      val[8 + v][ni] = y;
+    for (int i = 0; i < 8; ++i) y[i] = x[i];
+#pragma unroll
+    for (int i = 0; i < 8; i += 4) swap32x4(x[i], y[i], x[i + 1], y[i + 1], x[i + 2], y[i + 2], x[i + 3], y[i + 3]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {  // x: lane group 0's place, y: lane group 1's, in both
+      val[i][ni] = x[i];
+      val[8 + i][ni] = y[i];
     }
   }
 #pragma unroll
@@ -170,6 +171,7 @@ __device__ __forceinline__ void tile_of_sid(int sid, int mt, int nt, int& tm, in
 template <int EPI, int RB, bool IS2D, bool YBF16, bool SYM = false, bool RAG = false, bool ODD = false, int WAVES = 8, bool HI = false, bool PAIR = false>
 __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm6(const GemmArgs a) {
   using Acc = AccF6Lo;
+  request_args<GemmArgs>();
   constexpr int BMW = Tile6<WAVES, HI>::BMW, kStageA = Tile6<WAVES, HI>::kStageA, kStage6 = Tile6<WAVES, HI>::kStage;
   constexpr int kStageAB = Tile6<WAVES, HI>::kStageAB;
   constexpr int NIW = NI;  // 32-column MFMA blocks per wave along N

@@ -84,6 +84,17 @@ struct GemmArgs {
                          // STaMP order, P row b * g.khi + slot
 };
 
+// Asks for every 64-byte line of the kernel's arguments (and the one of the grid's size behind them) at once.  They are read where they
+// are first needed, each line from memory and one after the other otherwise, some 450 cycles a line: up to the first operand request of
+// a GEMM 3000 cycles, with this 950 (256 x 512 -> 512 in four tiles: 23300 and 20600 in all).
+template <typename Args>
+__device__ __forceinline__ void request_args() {
+  typedef const uint32_t __attribute__((address_space(4))) * Words;
+  const Words w = (Words)__builtin_amdgcn_kernarg_segment_ptr();
+  static_assert(sizeof(Args) > 192 && sizeof(Args) <= 320, "four or five lines are asked for");
+  asm volatile("" ::"s"(w[0]), "s"(w[16]), "s"(w[32]), "s"(w[48]), "s"(w[sizeof(Args) / 4 - 1]), "s"(gridDim.x));
+}
+
 // RAG kernels.  An inverse butterfly is (a +- d) / sqrt 2, but a node without partner is its parent unchanged.  The
 // epilogue runs plain a +- d as for whole blocks; a short block is made up for by factors: token i of it by sqrt(2) per
 // carry on its path (rag_leaf), a detail (and the approximation) by 1 / sqrt(2) per carry above it (rag_norm), so that

@@ -51,6 +51,7 @@ __device__ __forceinline__ int part_at(int row, int col) {
 // 17.2, 15.3, of which the loop 10 and 8, the launch and the sums of the waves 5, the top levels 2.
 template <int NP, bool GRP, bool AHEAD, int NC = 1>
 __global__ __launch_bounds__(512, AHEAD || NC == 2 ? 2 : 4) void k_hi6(const Hi6Args h) {
+  request_args<Hi6Args>();
   const GemmArgs& a = h.a;
   const StampGeom& g = a.g;
   constexpr int C = 32 * NC, RW = 32 * NP, RS = 512 / C;  // columns, rows of a wave; rows apart that a thread finishes
