@@ -53,11 +53,11 @@ constexpr int kTopCh = 32;
 // side by side).
 __global__ __launch_bounds__(256) void k_top(float* __restrict__ abot, uint32_t* __restrict__ rowmax_part, int k, int d,
                                              int is2d, int G, int r_bottom, int L, int asym, size_t npart, int ntop, int nslices,
-                                             const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6) {
+                                             const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, int gb) {
   extern __shared__ float s_buf[];  // [k][kTopCh + 1]
   if ((int)blockIdx.x >= ntop) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) stamp_gemm::repack6_rows(q_lo, a6, blockIdx.x - ntop, i * 256 + threadIdx.x);
+    for (int i = 0; i < 2; ++i) stamp_gemm::repack6_rows(q_lo, a6, blockIdx.x - ntop, i * 256 + threadIdx.x, gb);
     return;
   }
   const int b = (int)blockIdx.x / nslices, slice = (int)blockIdx.x - b * nslices, c_base = slice * kTopCh, tid = threadIdx.x;
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256) void k_quant_rows(const void* __restrict__ X, 
       if constexpr (OUT6) {
         uint32_t w0, w1;
         nib8_to_48(w, w0, w1);
-        store48(q_lo + a6_row(m, Kpad >> 7) + off48(c, kStageA6), row_half6(m), w0, w1, c, c < d);
+        store48(q_lo + a6_row(m, Kpad >> 7, 2) + off48(c, kStageA6), row_half6((uint32_t)m, 2), w0, w1, c, c < d);
       } else {
         *reinterpret_cast<uint32_t*>(q_lo + stamp_qlo_offset(m, c, Kpad)) = w;
       }
@@ -464,7 +464,7 @@ hipError_t stamp_launch_actquant(const stamp_plan* p, const void* X, int8_t* q_h
   const size_t npart = (size_t)g.B * g.k * nslices;
   const int ntop = nslices * g.B, nlo = dir != nullptr && dir->lo_packed ? (p->Mpad / 256) * (p->Kpad / 128) : 0;
   hipLaunchKernelGGL(k_top, dim3(ntop + nlo), dim3(256), lds, st, abot, rowmax, g.k, g.d, g.is2d, g.G, g.r, g.L, g.asym, npart,
-                     ntop, nslices, q_lo, dir != nullptr ? dir->a6 : nullptr);
+                     ntop, nslices, q_lo, dir != nullptr ? dir->a6 : nullptr, stamp_row_group_bit(p));
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_quant_hi, dim3(g.k, g.B), dim3(256), 0, st, abot, rowmax, nslices, q_hi, scales, g.k, g.d, g.s, g.R, g.asym,

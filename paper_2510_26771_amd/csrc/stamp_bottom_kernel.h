@@ -15,6 +15,7 @@ using stamp_gemm::kPart;
 using stamp_gemm::kStageA6;
 using stamp_gemm::nib8_to_48;
 using stamp_gemm::chan_off6;
+using stamp_gemm::hi_half6;
 using stamp_gemm::row_half6;
 using stamp_gemm::row_lane6;
 using stamp_gemm::row_off6;
@@ -105,7 +106,7 @@ __device__ __forceinline__ uint32_t off48(int c, uint32_t kt_bytes) {
   return chan_off6((uint32_t)c, kt_bytes) + (uint32_t)((t >> 1) * kPart + (t & 1) * 8);
 }
 
-// the quad's 4 x 48 bits -> 24 bytes (half: row_half6 of the row); every lane of the quad has to call this
+// the quad's 4 x 48 bits -> 24 bytes (half: row_half6 of the row, hi_half6 of an 8-bit one); every lane of the quad has to call this
 __device__ __forceinline__ void store48(uint8_t* dst, bool half, uint32_t w0, uint32_t w1, int c, bool active) {
   const uint32_t n0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w0, 0xF9, 0xF, 0xF, false);  // quad_perm [1,2,3,3]
   const uint32_t n1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w1, 0xF9, 0xF, 0xF, false);
@@ -117,9 +118,10 @@ __device__ __forceinline__ void store48(uint8_t* dst, bool half, uint32_t w0, ui
   if (active && t != 3) *reinterpret_cast<u2v*>(dst + (half ? (t == 1 ? 2 * kPart - 8 : kPart + 8) : 0)) = u2v{a, b};
 }
 
+constexpr int gb_of(int rows_log) { return rows_log < 2 ? 2 : rows_log > 6 ? 6 : rows_log; }
 // row m of the 4-bit operand: byte offset of its place in K step 0
-__device__ __forceinline__ size_t a6_row(size_t m, int KT) {
-  return (m >> 8) * (size_t)KT * kStageA6 + row_off6((uint32_t)m & 255);
+__device__ __forceinline__ size_t a6_row(size_t m, int KT, int gb) {
+  return (m >> 8) * (size_t)KT * kStageA6 + row_off6((uint32_t)m & 255, gb);
 }
 
 // an 8-bit row: codes 16 h + l to the operand of the kernel for few rows (stamp_hi6.h), row m of it
@@ -136,7 +138,7 @@ __device__ __forceinline__ void hi_rows(const Hi6Out& o, int m, int KT, Store st
     for (int i = 0; i < ntiles; ++i) store(o.p + (size_t)(tile + i) * KT * kBlock6 + place * 16, false, 0, true);
   } else {
     const int gr = 32 * o.np, grp = m / gr, r = m - grp * gr;
-    store(o.p + (size_t)grp * KT * (2 * o.np * kBlock6) + (r >> 5) * (2 * kBlock6) + row_lane6(r & 31), row_half6(r), kBlock6, row_half6(r));
+    store(o.p + (size_t)grp * KT * (2 * o.np * kBlock6) + (r >> 5) * (2 * kBlock6) + row_lane6(r & 31), hi_half6(r), kBlock6, hi_half6(r));
   }
 }
 __device__ __forceinline__ void store_hi48(const Hi6Out& o, int m, int KT, const int (&q)[8], int c, bool active) {
@@ -240,7 +242,8 @@ __device__ __forceinline__ void flush_rows(float (&rowv)[NR][8], MetaFn meta, in
                                            uint32_t* gpart_blk /* PASS 1: this split's partial maxima of the block's row e=0 */,
                                            size_t gpart_neg /* PASS 1: distance to the negative parts */,
                                            const uint32_t* s_amax /* PASS 2: [2][kMaxBlockRows] */, bool write_scales,
-                                           size_t row0 = 0, int Kpad = 0, int nwaves = 0 /* waves that share a row, 0: the workgroup's */) {
+                                           size_t row0 = 0, int Kpad = 0, int nwaves = 0 /* waves that share a row, 0: the workgroup's */,
+                                           int gb = 2 /* OUT6: row_off6 */) {
   // Values derived from the thread index are recomputed in every step from an opaque copy: cheap, and it
   // keeps them from being carried (and spilled: a scratch reload waits for ALL outstanding memory
   // operations, the asynchronous loads of the next batches included) across the whole unrolled kernel.
@@ -364,7 +367,7 @@ __device__ __forceinline__ void flush_rows(float (&rowv)[NR][8], MetaFn meta, in
       uint32_t w0, w1;
       nib8_to_48(w, w0, w1);
       const uint32_t m = (uint32_t)row0 + (uint32_t)rm.pos;
-      store48(q_lo_blk + row_off6(m) + q_off, row_half6(m), w0, w1, tid * 8, active && (!RAG || rm.e >= 0));
+      store48(q_lo_blk + row_off6(m, gb) + q_off, row_half6(m, gb), w0, w1, tid * 8, active && (!RAG || rm.e >= 0));
     } else if constexpr (RAG) {
       if (active && rm.e >= 0) *reinterpret_cast<uint32_t*>(q_lo_blk + stamp_qlo_offset(row0 + rm.e, 0, Kpad) + q_off) = w;
     } else {
@@ -386,7 +389,8 @@ template <bool IS2D, bool ASYM, bool RAG = false, bool OUT6 = false, int PASS = 
 __device__ __forceinline__ void finish_top_row(const float (&top)[8], int level, uint32_t* part /* >= 32 words, free */,
                                                int8_t* q_hi_row, uint8_t* q_lo_row, float* scale_out, size_t zeros_off,
                                                bool row8, bool active, int tid, Hi6Out hi6 = Hi6Out{}, int hi_row = 0, int KT = 0, int c0 = 0,
-                                               uint32_t* part_max = nullptr, size_t part_neg = 0, const uint32_t* s_amax = nullptr) {
+                                               uint32_t* part_max = nullptr, size_t part_neg = 0, const uint32_t* s_amax = nullptr,
+                                               bool half6 = false /* OUT6: row_half6 of the row */) {
   const int lane = tid & 63, wave = tid >> 6, nw = (int)(blockDim.x >> 6);
   const float nrm = IS2D ? ldexpf(1.0f, -level) : haar_norm(level);
   float t[8];
@@ -456,7 +460,7 @@ __device__ __forceinline__ void finish_top_row(const float (&top)[8], int level,
     } else {
       uint32_t w0, w1;
       nib8_to_48(w4, w0, w1);
-      store48(q_lo_row, false, w0, w1, c0, active);  // (a block's first row)
+      store48(q_lo_row, half6, w0, w1, c0, active);
     }
     return;
   }
@@ -610,11 +614,11 @@ __device__ __forceinline__ void step1d(const uint8_t* X_blk, uint32_t x_off, siz
       return RowMeta{0, stamp_rag_slot(rg.q, rg.j, e), e};
     };
     flush_rows<NR, false, ASYM, PASS, true, OUT6>(rowv, meta, IT, s_max, q_lo_blk, q_off, scales_blk, zeros_off, active, tid, gpart_blk,
-                                            gpart_neg, s_amax, write_scales, OUT6 ? (size_t)rg.tile_row : row0, rg.Kpad);
+                                            gpart_neg, s_amax, write_scales, OUT6 ? (size_t)rg.tile_row : row0, rg.Kpad, 0, gb_of(RLOG));
   } else {
     auto meta = [](int r) -> RowMeta { return meta1d<RLOG, IT>(r); };
     flush_rows<NR, false, ASYM, PASS, false, OUT6>(rowv, meta, IT, s_max, q_lo_blk, q_off, scales_blk, zeros_off, active, tid, gpart_blk,
-                                                   gpart_neg, s_amax, write_scales, row0);
+                                                   gpart_neg, s_amax, write_scales, row0, 0, 0, gb_of(RLOG));
   }
 }
 
@@ -685,9 +689,9 @@ __global__ __launch_bounds__(1024) void k_bottom1d(const void* __restrict__ X, u
   if (sp.q_hi != nullptr) {
     // s_max[R/4 & 1] was last used two steps ago: every thread has passed a barrier since
     finish_top_row<false, ASYM, false, OUT6, PASS>(top, RLOG, &s_max[(R / 4) & 1][0], sp.q_hi + ((size_t)b * k + j) * d + c0,
-                                                   (OUT6 ? q_lo + a6_row(row0, Kpad >> 7) : q_blk) + q_off, scales + row0, zeros_off,
+                                                   (OUT6 ? q_lo + a6_row(row0, Kpad >> 7, gb_of(RLOG)) : q_blk) + q_off, scales + row0, zeros_off,
                                                    j < sp.khi, active, tid, sp.hi6, b * sp.khi + j, Kpad >> 7, c0, gpart_blk,
-                                                   (size_t)sp.nsplit * sp.part_rows, s_amax);
+                                                   (size_t)sp.nsplit * sp.part_rows, s_amax, row_half6((uint32_t)row0, gb_of(RLOG)));
     return;
   }
   if (active && PASS != 1) {
@@ -734,8 +738,9 @@ __global__ __launch_bounds__(1024) void k_bottom1d_rag(const void* __restrict__ 
     slot = q.o + j;
   }
   finish_top_row<false, ASYM, true, OUT6>(top, 0, &s_max[(R / 4) & 1][0], q_hi + ((size_t)b * khi + slot) * d + c0,
-                                          q_lo + (OUT6 ? a6_row(brow, Kpad >> 7) : stamp_qlo_offset(seq0 + slot, 0, Kpad)) + q_off,
-                                          scales + seq0 + slot, zeros_off, slot < khi, active, tid, hi6, b * khi + slot, Kpad >> 7, c0);
+                                          q_lo + (OUT6 ? a6_row(brow, Kpad >> 7, gb_of(RLOG)) : stamp_qlo_offset(seq0 + slot, 0, Kpad)) + q_off,
+                                          scales + seq0 + slot, zeros_off, slot < khi, active, tid, hi6, b * khi + slot, Kpad >> 7, c0, nullptr, 0, nullptr,
+                                          row_half6((uint32_t)brow, gb_of(RLOG)));
 }
 
 // ------------------------------------------------------------------------------------------

@@ -4,10 +4,10 @@
 // the store of Y, all without leaving the registers.
 //
 // A wave owns 128 rows x 64 columns as 4 x 2 blocks of 32 x 32 operand rows and columns, each 2 x 2 MFMA tiles of 16 x 16
-// (row tile th, column tile tc).  Lane 16 f + i holds column i of a tile and its rows 4 f + v, and the operand's rows are laid
-// out (row_off6) so that these are the rows 32 f + 8 mi + 4 th + v of the wave tile (register 8 tc + 4 th + v of block (mi, ni)).
-// One v_permlane16_swap per register pair exchanges tc = 1 of even f with tc = 0 of odd f, after which lane (kg = lane / 32,
-// l32 = lane % 32) holds the column l32 and 64 neighbouring rows 64 kg .. 64 kg + 63: WHOLE blocks of R = 8 .. 64 rows (Haar
+// (row tile th, column tile tc).  Lane 16 f + i holds column i of a tile and its rows 4 f + v (register 8 tc + 4 th + v of block
+// (mi, ni)).  One v_permlane16_swap per register pair exchanges tc = 1 of even f with tc = 0 of odd f, after which lane (kg = lane / 32,
+// l32 = lane % 32) holds the column l32 and what two f had.  The operand's rows are dealt (row_off6) so that these are 64 rows in order,
+// place L in register 8 (L / 4 % 2) + 4 (L / 8 % 2) + L % 4 of block L / 16: lane group kg has the blocks 2 t + kg of R = 8 .. 64 rows, WHOLE (Haar
 // sub-trees).  The inverse butterflies are then plain register arithmetic.  The weights are stored so that column l32 of block ni is
 // output column 2 l32 + ni of the wave's 64: a lane's two results are neighbours, one 4-byte (bf16) or 8-byte (fp32) store per
 // token, and the 32 lanes of a group write one contiguous 128- or 256-byte run.  (Without the swaps a lane has 32 rows of two
@@ -23,6 +23,9 @@
 
 namespace stamp_gemm {
 
+// register of a block that holds row L of lane group kg (row_off6), less the block's 16, after columns16
+STAMP_HD constexpr int reg16(int L) { return 8 * ((L >> 2) & 1) + 4 * ((L >> 3) & 1) + (L & 3); }
+
 // Register (mi, v) that holds, after the swaps, coefficient e (in-block position) of the lane's t-th block.
 template <int RL, bool GRP = false>
 struct RegMap {
@@ -30,22 +33,22 @@ struct RegMap {
   static constexpr int nb = 64 / R;  // blocks per lane
   static_assert(RL >= 3 && RL <= 6, "blocks of 8 .. 64 rows");
   static constexpr int mi(int t, int e) {
-    if (!GRP) return ((t * R + e) >> 3) & 3;
+    if (!GRP) return (t * R + e) >> 4;
     return RL == 6 ? ((e >> 5) + 2 * ((e >> 2) & 1)) : RL == 5 ? (2 * t + ((e >> 2) & 1)) : RL == 4 ? t : (t >> 1);
   }
   static constexpr int v(int t, int e) {
-    if (!GRP) return 8 * ((t * R + e) >> 5) + (e & 7);
+    if (!GRP) return reg16(t * R + e);
     return RL >= 5   ? (4 * ((e >> 3) & 3) + (e & 3))
            : RL == 4 ? (4 * (((e >> 3) & 1) + 2 * ((e >> 2) & 1)) + (e & 3))
                      : (4 * (2 * (t & 1) + ((e >> 2) & 1)) + (e & 3));
   }
-  // lane group kg's t-th block of the wave tile
-  static constexpr int stride = GRP ? 2 : 1;
-  static STAMP_HD constexpr int block(int t, int kg) { return (GRP ? kg : kg * nb) + stride * t; }
+  static STAMP_HD constexpr int block(int t, int kg) { return 2 * t + kg; }  // lane group kg's t-th block of the wave tile
 };
 
-// Four independent swaps in one statement: the wait states are needed once before the first and once after the last
-// (nothing else can come between them).
+// lanes 32 .. 63 of x <-> lanes 0 .. 31 of y, four independent swaps in one asm statement.  (The builtin is treated as rematerialisable,
+// i.e. executed once per result with both inputs kept alive, which doubles the live registers of the epilogue.)  The wait states cover
+// the instruction's read-after-VALU-write and VALU-read-after-it hazards, which the assembler does not see inside an asm statement.
+// They are needed once before the first and once after the last (nothing else can come between them).
 __device__ __forceinline__ void swap32x4(float& x0, float& y0, float& x1, float& y1, float& x2, float& y2, float& x3, float& y3) {
   asm volatile(
       "s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\tv_permlane32_swap_b32 %2, %3\n\tv_permlane32_swap_b32 %4, %5\n\t"
@@ -63,16 +66,6 @@ __device__ __forceinline__ void swap16x4(float& x0, float& y0, float& x1, float&
 __device__ __forceinline__ void columns16(float (&r)[16]) {
 #pragma unroll
   for (int h = 0; h < 8; h += 4) swap16x4(r[h], r[8 + h], r[h + 1], r[9 + h], r[h + 2], r[10 + h], r[h + 3], r[11 + h]);
-}
-// row of the wave tile in register v of block (mi, .) after that, less 64 kg
-STAMP_HD constexpr int row16(int mi, int v) { return 32 * (v >> 3) + 8 * mi + (v & 7); }
-
-__device__ __forceinline__ void swap32(float& x, float& y) {
-  // lanes 32..63 of x <-> lanes 0..31 of y.  Written as an asm statement: the builtin form is treated as
-  // rematerialisable, i.e. executed once per result with both inputs kept alive, which doubles the live
-  // registers of the epilogue.  The wait states around it cover the instruction's read-after-VALU-write and
-  // VALU-read-after-it hazards, which the assembler does not see inside an asm statement.
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(x), "+v"(y));
 }
 
 // Two neighbouring output columns of one token.
@@ -244,7 +237,7 @@ __device__ __forceinline__ void blocks_reg(const GemmArgs& a, float (&acc)[4][NI
     constexpr int RL = IS2D ? 2 * RB : RB;
     constexpr int R = 1 << RL;
     using RM = RegMap<RL, GRP>;
-    constexpr int TR = RM::stride * T * R;
+    constexpr int TR = 2 * T * R;
     const StampGeom& g = a.g;
     const int mrow = mrow0 + TR;
     if (mrow < a.M && o.nvalid > 0) {
@@ -341,22 +334,24 @@ __device__ __forceinline__ void epilogue_reg_impl(const GemmArgs& a, const Acc (
     // a row goes to the output row of its own number or nowhere (dst < 0): bytes from the tile's first one, which fit 32 bits (RegOut)
     const uint32_t pitch = (uint32_t)(EPI == 1 ? a.ld_out : a.N) * (uint32_t)(EPI == 3 && YBF16 ? 2 : 4);
     char* const base = reinterpret_cast<char*>(a.out) + (size_t)m0 * pitch;
-    const uint32_t off = (uint32_t)(wm * 128 + 64 * kg) * pitch + (uint32_t)n * (uint32_t)(EPI == 3 && YBF16 ? 2 : 4);
+    const int gb = EPI == 3 ? 2 : a.gb, rk = wm * 128 + (kg << gb);
+    const uint32_t off = (uint32_t)rk * pitch + (uint32_t)n * (uint32_t)(EPI == 3 && YBF16 ? 2 : 4);
 #pragma unroll
     for (int mi = 0; mi < 4; ++mi) {
 #pragma unroll
       for (int ni = 0; ni < NI; ++ni) columns16(acc[mi][ni]);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int r0 = wm * 128 + 64 * kg + row16(mi, 4 * q);
+        const uint32_t rl = row_of_rest6((uint32_t)(16 * mi + 4 * q), gb);
+        const int r0 = rk + (int)rl, v0 = reg16(4 * q);
         const f4 rf = *reinterpret_cast<const f4*>(s_rowfac + r0);
         const f4 rz = *reinterpret_cast<const f4*>(s_rowz + r0);
         const v4i rd = *reinterpret_cast<const v4i*>(s_rowdst + r0);
-        uint32_t oq = off + (uint32_t)row16(mi, 4 * q) * pitch;
+        uint32_t oq = off + rl * pitch;
         if constexpr (EPI == 3) asm volatile("" : "+v"(oq));  // (computed here: the offsets of all rows at once would not fit the registers)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          float c0 = acc[mi][0][4 * q + j], c1 = acc[mi][1][4 * q + j];
+          float c0 = acc[mi][0][v0 + j], c1 = acc[mi][1][v0 + j];
           if (g.asym) {
             c0 = __builtin_fmaf(-rz[j], eo.cs[0], c0);
             c1 = __builtin_fmaf(-rz[j], eo.cs[1], c1);

@@ -17,20 +17,28 @@ constexpr int kBlock6 = 3 * kPart;            // a 32-row block of one K step: 3
 constexpr int kStageB6 = 4 * kBlock6;         // 128 columns: 12 KB
 constexpr int kStageA6 = 2 * kStageB6;        // 24 KB
 
-// Row r of activations: which of its lane's two operands (tiles of 16 rows) it is
-STAMP_HD bool row_half6(uint32_t r) { return (r >> 2) & 1; }
-// row of a 256-row tile -> byte of its lane in lane group 0, K step 0: bits 3 and 4 choose the block, 0, 1, 5 and 6 the lane
-STAMP_HD uint32_t row_off6(uint32_t r) {
-  return (((r >> 5) & 4) + ((r >> 3) & 3)) * (uint32_t)kBlock6 + (((r >> 3) & 12) + (r & 3)) * 16;
+// Activation rows.  Bit gb of a row (2 .. 6; bit 7: which half of a 256-row tile) is the group of 32 lanes that its results come out
+// in, the other six of bits 0 .. 6 are its place there, L: bits 0 and 1 the result register, 2 the lanes of the group, 3 which of a lane's
+// two operands (tiles of 16 rows), 4 and 5 the block.  gb = log2 of the rows that the epilogue keeps together in a lane, at least 2: the
+// two groups hold neighbouring blocks (plain rows: neighbouring four rows), and both have work in a tile with few rows.  With bit 6 for
+// all plans one of them had none where a tile has up to 64: 64 x 256 -> 128 18.7 us, 18.2 with this; 64 x 512 -> 4096 19.9, 19.6; 40 x 1024 ->
+// 4096 without transform 17.1, 16.5; 77 x 2048 -> 1024 21.2, 20.4.
+STAMP_HD uint32_t row_rest6(uint32_t r, int gb) { return ((r & 127) >> (gb + 1) << gb) | (r & ((1u << gb) - 1)); }
+STAMP_HD bool row_half6(uint32_t r, int gb) { return (row_rest6(r, gb) >> 3) & 1; }
+// row of a 256-row tile -> byte of its lane in channels 0 .. 31 of K step 0
+STAMP_HD uint32_t row_off6(uint32_t r, int gb) {
+  const uint32_t L = row_rest6(r, gb);
+  return (((r >> 5) & 4) + (L >> 4)) * (uint32_t)kBlock6 + (((r >> gb) & 1) * 8 + (L & 7)) * 16;
 }
-// row of a block of 8-bit rows, which stand by themselves: bits 0, 1, 3 and 4 choose the lane
+// row of a block of 8-bit rows, which stand by themselves: bits 0, 1, 3 and 4 choose the lane, bit 2 the operand
 STAMP_HD uint32_t row_lane6(uint32_t r) { return (((r >> 1) & 12) + (r & 3)) * 16; }
+STAMP_HD bool hi_half6(uint32_t r) { return (r >> 2) & 1; }
 // byte offset of the 32 channels from c on; K steps are kt_bytes apart
 STAMP_HD uint32_t chan_off6(uint32_t c, uint32_t kt_bytes) { return (c >> 7) * kt_bytes + ((c >> 5) & 3) * 256; }
 
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u6v __attribute__((ext_vector_type(6)));
-// 24 bytes of a fragment -> their places; dst = its lane's place in part 0, half = row_half6 of the row
+// 24 bytes of a fragment -> their places; dst = its lane's place in part 0, half = row_half6 of the row (8-bit rows: hi_half6)
 __device__ __forceinline__ void store24(uint8_t* dst, u6v w, bool half) {
   const u4 a = {half ? w[2] : w[0], half ? w[3] : w[1], half ? w[4] : w[2], half ? w[5] : w[3]};
   const u2 b = {half ? w[0] : w[4], half ? w[1] : w[5]};

@@ -520,6 +520,7 @@ stamp_gemm::GemmArgs stamp_gemm_args(const stamp_plan* p, const float* scales, v
   a.split_stride = 0;
   a.a_seq_rows = a.a_seq_used = 1;
   a.own_top = 0;
+  a.gb = stamp_row_group_bit(p);
   a.rag = StampRag{};
   a.H = nullptr;
   a.ht = StampHiTiles{};

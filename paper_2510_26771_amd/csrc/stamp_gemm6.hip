@@ -21,8 +21,8 @@
 // 1 KB of consecutive addresses with one 16-byte LDS read (no bank conflicts, no swizzle; 16-byte reads
 // move 1.75x the bytes per clock of 8-byte ones on this chip, and at 8 bytes the fragment reads of a step
 // take as long as its MFMAs).  Weights: tile = column / 16 of the block.  Activations (row_off6): the
-// rows are dealt to blocks, tiles and lanes so that a lane's results, rows 4 f + v of every tile, are 32 neighbouring rows
-// (stamp_epilogue_reg.h).  Per tile and K step, activations: 8 blocks = 24 KB, weights: 4 blocks = 12 KB
+// rows are dealt to blocks, tiles and lanes so that a lane's results, rows 4 f + v of every tile, are whole blocks of the inverse once
+// pairs of lanes have exchanged columns (stamp_epilogue_reg.h).  Per tile and K step, activations: 8 blocks = 24 KB, weights: 4 blocks = 12 KB
 // per 128 columns.  The global image equals the LDS image, so a K step is staged by plain asynchronous
 // 16-byte copies.
 #include <type_traits>
@@ -38,12 +38,12 @@ using namespace stamp_gemm;
 // q_lo (tiled [Mpad/256][KT][256 rows][64 bytes], channels in natural order) -> FP6 operand layout.
 // One workgroup per (row tile, K step); thread = a fragment of two rows, three 16-byte stores.
 // The first nhi blocks convert the 8-bit rows (stamp_hi6.h).
-__global__ __launch_bounds__(512) void k_repack6(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, int nhi, StampHi6Pack hp) {
+__global__ __launch_bounds__(512) void k_repack6(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, int nhi, StampHi6Pack hp, int gb) {
   if ((int)blockIdx.x < nhi) {
     hi6_pack(hp, (int)blockIdx.x * 512 + (int)threadIdx.x);
     return;
   }
-  repack6_rows(q_lo, a6, blockIdx.x - nhi, threadIdx.x);
+  repack6_rows(q_lo, a6, blockIdx.x - nhi, threadIdx.x, gb);
 }
 
 // The same from rows in STaMP order to rows in the block order of StampRag (rows without a coefficient: zeros).
@@ -54,11 +54,11 @@ __global__ __launch_bounds__(512) void k_repack6_rag(const uint8_t* __restrict__
     return;
   }
   const int blk = blockIdx.x - nhi, mt = blk / KT, kt = blk - mt * KT;
-  const int u = threadIdx.x, m0 = mt * 256 + repack6_row(u), R = 1 << rg.r;
+  const int u = threadIdx.x, m0 = mt * 256 + repack6_row(u, rg.r), R = 1 << rg.r;
   u4 w[2] = {};
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const int m = m0 + 4 * i, g = m / R, b = g / rg.nb;
+    const int m = m0 + repack6_dist(rg.r) * i, g = m / R, b = g / rg.nb;
     const int slot = m < M ? stamp_rag_slot(rg, g - b * rg.nb, m - g * R) : -1;
     if (slot >= khi) {
       const size_t ms = (size_t)b * s + slot;
@@ -129,7 +129,7 @@ hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_
   const int nlo = q_lo != nullptr ? (p->Mpad / 256) * (p->Kpad / 128) : 0;
   const StampHi6Pack hp = hi != nullptr ? *hi : StampHi6Pack{};
   const int nhi = (hp.threads + 511) / 512;
-  if (nlo + nhi > 0) hipLaunchKernelGGL(k_repack6, dim3(nlo + nhi), dim3(512), 0, st, q_lo, a6, nhi, hp);
+  if (nlo + nhi > 0) hipLaunchKernelGGL(k_repack6, dim3(nlo + nhi), dim3(512), 0, st, q_lo, a6, nhi, hp, stamp_row_group_bit(p));
   return hipGetLastError();
 }
 
@@ -187,6 +187,7 @@ hipError_t stamp_launch_gemm_lo6_rag(const stamp_plan* p, const uint8_t* a6, con
   a.Bq = p->qW6_dev;
   a.g = p->bgeom;
   a.rag = p->rag;
+  a.gb = p->rag.r;
   a.M = a.g.B * a.g.k * a.g.R;
   a.P = P;
   if (hi != nullptr) {

@@ -77,12 +77,16 @@ struct GemmArgs {
   int a_seq_used;        // GEMM multiplies: row m of the GEMM is row m + (m / a_seq_used) (a_seq_rows - a_seq_used) of A
   int own_top;           // 4-bit rows, fused mode: coefficient 0 of the blocks from g.khi on is a 4-bit row of A (see
                          // compute_row_info); P then holds g.khi rows per sequence
+  int gb;                // 4-bit rows of the FP6 engine: row_off6
   StampGeom g;
   const uint8_t* H;      // 8-bit rows in the tiles' places (ht.on), 3 KB per 128-row tile and K step
   StampHiTiles ht;
   StampRag rag;          // RAG kernels: rows in the block order of StampRag (g.k = blocks, g.khi = 8-bit slots), scales in
                          // STaMP order, P row b * g.khi + slot
 };
+
+// row of lane group 0 at place L (row_off6)
+STAMP_HD uint32_t row_of_rest6(uint32_t L, int gb) { return (L >> gb << (gb + 1)) | (L & ((1u << gb) - 1)); }
 
 // Asks for every 64-byte line of the kernel's arguments (and the one of the grid's size behind them) at once.  They are read where they
 // are first needed, each line from memory and one after the other otherwise, some 450 cycles a line: up to the first operand request of
@@ -431,7 +435,7 @@ __device__ __forceinline__ void store_row_info(const GemmArgs& a, int m0, int ti
 // rows only); RB = log2 of the block length for EPI 2 (1-D: tokens, 2-D: side); 3 = plans without a
 // sequence transform: dequantized rows + bias -> Y through the same staging (4-bit rows only).
 // PAIRCOLS: the weights are stored so that MFMA column l32 of block ni is column 2 l32 + ni of the wave's 64
-// (the FP6 engine's layout) instead of 32 ni + l32, and a lane holds 64 neighbouring rows (stamp_epilogue_reg.h).
+// (the FP6 engine's layout) instead of 32 ni + l32, and rows are dealt to lanes as in row_off6.
 template <typename Acc, int EPI, int RB, bool IS2D, bool YBF16, bool PAIRCOLS = false, bool RAG = false>
 __device__ __forceinline__ void epilogue(const GemmArgs& a, typename Acc::V (&acc)[4][NI], uint8_t* smem,
                                          const uint8_t* row_info, const EpiOperands<EPI, RB, IS2D, RAG>& eo, int m0,
@@ -452,7 +456,8 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, typename Acc::V (&ac
       for (int mi = 0; mi < 4; ++mi) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int rl = wm * 128 + (PAIRCOLS ? 64 * kg + 32 * (v >> 3) + 8 * mi + (v & 7) : mi * 32 + 8 * (v >> 2) + 4 * kg + (v & 3));
+          const int rl = wm * 128 + (PAIRCOLS ? (int)row_of_rest6(16 * mi + 8 * ((v >> 2) & 1) + 4 * (v >> 3) + (v & 3), a.gb) + (kg << a.gb)
+                                                  : mi * 32 + 8 * (v >> 2) + 4 * kg + (v & 3));
           const int dst = s_rowdst[rl];
           if (dst >= 0 && n < a.N) {
             if constexpr (EPI == 0) {

@@ -61,7 +61,7 @@ __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
     const int gr = 32 * o.np, grp = m / gr, r = m - grp * gr;
     row = m < hp.M ? m + (m / o.seq) * (hp.seq_rows - o.seq) : -1;
     dst = o.p + ((size_t)grp * hp.KT + kt) * (2 * o.np * kBlock6) + (r >> 5) * (2 * kBlock6) + f * 256 + row_lane6((uint32_t)r & 31);
-    hf = row_half6((uint32_t)r);
+    hf = hi_half6((uint32_t)r);
   }
   u4 w[2] = {};
   if (row >= 0 && frag * 32 < hp.d) {  // d is a multiple of 32
@@ -78,7 +78,7 @@ __device__ __forceinline__ void hi6_pack(const StampHi6Pack& hp, int i) {
   store24(dst + (o.ht.on ? 0 : kBlock6), ll, o.ht.on || hf);
 }
 
-// 32 packed codes each of two rows four apart -> a lane's 48 bytes of a block
+// 32 packed codes each of two rows (repack6_dist apart) -> a lane's 48 bytes of a block
 __device__ __forceinline__ void repack6_store(uint8_t* dst, u4 w0, u4 w1) {
   uint64_t lo[3], hi[3];
   chunk_to_e2m3(w0, lo);
@@ -89,14 +89,17 @@ __device__ __forceinline__ void repack6_store(uint8_t* dst, u4 w0, u4 w1) {
   *reinterpret_cast<ul2*>(dst + 2 * kPart) = ul2{hi[1], hi[2]};
 }
 
-// The two rows of unit u = 0 .. 511 of a (row tile, K step): the first of them (the other is four further on), and fragment
-__device__ __forceinline__ int repack6_row(int u) { return (u >> 8) * 128 + ((u & 12) << 3) + ((u >> 6) & 3) * 8 + (u & 3); }
+// The two rows of unit u = 0 .. 511 of a (row tile, K step): the first of them, how far on the other is, and fragment
+__device__ __forceinline__ int repack6_row(int u, int gb) {
+  return (u >> 8) * 128 + (int)row_of_rest6((uint32_t)(((u >> 6) & 3) * 16 + (u & 7)), gb) + (((u >> 3) & 1) << gb);
+}
+__device__ __forceinline__ int repack6_dist(int gb) { return gb <= 3 ? 16 : 8; }
 __device__ __forceinline__ int repack6_frag(int u) { return (u >> 4) & 3; }
 // packed 4-bit rows -> operand: block `blk` = (row tile, K step), unit u of it
-__device__ __forceinline__ void repack6_rows(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, size_t blk, int u) {
-  const uint8_t* src = q_lo + blk * (256 * 64) + repack6_row(u) * 64 + repack6_frag(u) * 16;
+__device__ __forceinline__ void repack6_rows(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, size_t blk, int u, int gb) {
+  const uint8_t* src = q_lo + blk * (256 * 64) + repack6_row(u, gb) * 64 + repack6_frag(u) * 16;
   repack6_store(a6 + blk * kStageA6 + (u >> 6) * kBlock6 + (u & 63) * 16, *reinterpret_cast<const u4*>(src),
-                *reinterpret_cast<const u4*>(src + 4 * 64));
+                *reinterpret_cast<const u4*>(src + repack6_dist(gb) * 64));
 }
 
 }  // namespace stamp_gemm

@@ -369,6 +369,12 @@ hipError_t stamp_launch_rag_top(const stamp_plan* p, const float* ythi, int npar
 // a 4-bit row of a6 like any other (the quantizer writes it there as well), and P holds khi rows per sequence
 hipError_t stamp_launch_gemm_lo6(const stamp_plan* p, const uint8_t* a6, const float* scales, int mode, void* out,
                                  const float* P, hipStream_t st, int own_top = 0, const StampHiOut* hi = nullptr);
+// 4-bit rows of the FP6 engine (row_off6): log2 of the rows that the fused epilogue keeps in a lane, 2 where rows are tokens
+inline int stamp_row_group_bit(const stamp_plan* p) {
+  const StampGeom& g = p->geom;
+  const int rl = g.ident ? 2 : g.is2d ? 2 * g.r : g.r;
+  return rl < 2 ? 2 : rl > 6 ? 6 : rl;
+}
 // whether the FP6 GEMM over M rows takes 128 x 256 tiles
 bool stamp_gemm6_half_tiles(int M, int Npad);
 bool stamp_gemm6_pairs(int M, int Npad, int Kpad);  // two workgroups of 128 x 256 tiles per CU

@@ -21,6 +21,7 @@ struct LaneArgs {
   size_t zeros_off;
   Hi6Out hi6;
   StampRag rag;
+  int gb;            // row_off6
   int G, gridW;      // token grid: blocks per row, tokens per row
 };
 

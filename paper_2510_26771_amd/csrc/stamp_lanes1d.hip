@@ -173,9 +173,18 @@ __global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs
   const float mb_ = fold ? __fmul_rn(inv_b, nb) : inv_b, nb_ = fold ? 1.0f : nb;
   const size_t brow = RAG ? ((size_t)b * a.rag.nb + j) * RK : seq0 + (size_t)j * R;
   uint8_t* const out = a.a6 + (brow >> 8) * (size_t)a.KT * kStageA6;
-  auto place = [&](int e, int c) {  // (brow is a multiple of 8: e decides the half)
-    return out + (chan_off6((uint32_t)c, kStageA6) + row_off6((uint32_t)(brow & 255) + (uint32_t)e));
+  const uint32_t row_a = (uint32_t)(brow & 255) + (uint32_t)ea, row_b = (uint32_t)(brow & 255) + (uint32_t)eb;
+  uint32_t off_a, off_b;
+  bool half_a, half_b;
+  auto places = [&](int gb) __attribute__((always_inline)) {
+    off_a = row_off6(row_a, gb);
+    off_b = row_off6(row_b, gb);
+    half_a = row_half6(row_a, gb);
+    half_b = row_half6(row_b, gb);
   };
+  if (RAG || parts == 1) places(RLOG);  // (most of it then depends on the block alone)
+  else places(a.gb);
+  auto place = [&](uint32_t off, int c) { return out + (chan_off6((uint32_t)c, kStageA6) + off); };
   // codes of 16 values; shift: what the stored code is below the unsigned one
   auto code = [&](const float (&x)[32], int odd, float n, float mul, float z, bool two) __attribute__((always_inline)) {
     f16v v;
@@ -203,7 +212,7 @@ __global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs
       }
     }
     const u6v wa = to_e2m3(code(ra, 0, na, inv_a, za, !RAG), code(ra, 1, na, inv_a, za, !RAG));
-    if (active && (!RAG || sa >= 0)) store24(place(ea, c), wa, row_half6((uint32_t)ea));
+    if (active && (!RAG || sa >= 0)) store24(place(off_a, c), wa, half_a);
     __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
@@ -230,7 +239,7 @@ __global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs
       }
     }
     const u6v wb = to_e2m3(code(rb[g], 0, nb_, mb_, zb, !RAG), code(rb[g], 1, nb_, mb_, zb, !RAG));
-    if (active && (!RAG || sb >= 0) && !(tl == 0 && (sum_out || row8))) store24(place(eb, c), wb, row_half6((uint32_t)eb));
+    if (active && (!RAG || sb >= 0) && !(tl == 0 && (sum_out || row8))) store24(place(off_b, c), wb, half_b);
   }
 }
 
@@ -353,7 +362,8 @@ __global__ __launch_bounds__(256) void k_quant_parts(const float* __restrict__ T
     store_hi24(a.hi6, b * a.k + slot, a.KT, ev, od, c);
   } else {
     const uint32_t mr = (uint32_t)(srow & 255);
-    store24(a.a6 + (srow >> 8) * (size_t)a.KT * kStageA6 + (chan_off6((uint32_t)c, kStageA6) + row_off6(mr)), to_e2m3(ev, od), row_half6(mr));
+    store24(a.a6 + (srow >> 8) * (size_t)a.KT * kStageA6 + (chan_off6((uint32_t)c, kStageA6) + row_off6(mr, a.gb)), to_e2m3(ev, od),
+            row_half6(mr, a.gb));
   }
 }
 
@@ -413,8 +423,8 @@ __global__ __launch_bounds__(1024) void k_lanes_rows(const LaneArgs a, int rows)
   if (row8) {
     store_hi24(a.hi6, b * a.k + pr, a.KT, ev, od, c);
   } else {
-    store24(a.a6 + (size_t)(m >> 8) * a.KT * kStageA6 + (chan_off6((uint32_t)c, kStageA6) + row_off6((uint32_t)m & 255)), to_e2m3(ev, od),
-            row_half6((uint32_t)m));
+    store24(a.a6 + (size_t)(m >> 8) * a.KT * kStageA6 + (chan_off6((uint32_t)c, kStageA6) + row_off6((uint32_t)m & 255, 2)), to_e2m3(ev, od),
+            row_half6((uint32_t)m, 2));
   }
 }
 
@@ -490,6 +500,7 @@ hipError_t stamp_launch_lanes1d(const stamp_plan* p, int rlog, const void* X, ui
   a.zeros_off = (size_t)g.B * g.s;
   a.hi6 = hi;
   a.rag = p->rag;
+  a.gb = stamp_row_group_bit(p);
   if (p->rag.on) {
     const int blocks = p->rag.nb + p->rag.o;
     return rlog == 3 ? launch<3, true>(a, g.x_bf16, g.asym, blocks, g.B, st) : launch<4, true>(a, g.x_bf16, g.asym, blocks, g.B, st);
@@ -514,6 +525,7 @@ hipError_t stamp_launch_top_parts(const stamp_plan* p, float* abot, uint8_t* a6,
   a.k = g.k;
   a.KT = p->Kpad >> 7;
   a.R = g.R;
+  a.gb = stamp_row_group_bit(p);
   a.zeros_off = (size_t)g.B * g.s;
   a.hi6 = hi;
   if (g.asym) hipLaunchKernelGGL(k_quant_parts<true>, dim3(n, g.B), dim3(threads), 0, st, abot, a);

@@ -149,7 +149,7 @@ __global__ __launch_bounds__(768) void k_lanes2d(const LaneArgs a) {
     }
     const u6v w = to_e2m3(ev, od);
     const uint32_t m = (uint32_t)(brow & 255) + (uint32_t)e;
-    if (active && !(top && (sum_out || row8))) store24(out + row_off6(m), w, row_half6(m));
+    if (active && !(top && (sum_out || row8))) store24(out + row_off6(m, 2 * RLOG), w, row_half6(m, 2 * RLOG));
     __builtin_amdgcn_sched_barrier(0);
   }
 }

@@ -627,6 +627,9 @@ TILES = [_tiles("t256_ident_odd_rows", 8193, 2050, 64, xform="identity", levels=
          _tiles("t256_wht", 2048, 7938, 32, xform="wht", levels=0),
          _tiles("t256_grid", 4096, 4098, 288, xform="haar2d", grid_h=64, grid_w=64, levels=3, k_hi=64, corr_len=4.0),
          _tiles("t128_ident_rows", 257, 300, 32, xform="identity", levels=0),
+         # tiles with few rows: a lane group without any, one row in the second
+         _tiles("t128_ident_4_rows", 260, 300, 32, xform="identity", levels=0), _tiles("t128_ident_5_rows", 261, 300, 32, xform="identity", levels=0, act_quant="asym"),
+         _tiles("t128_wht_64_rows", 64, 131, 160, xform="wht", levels=0), _tiles("t128_haar32_64_rows", 64, 131, 160, levels=6, k_hi=2),
          # 132 and 128 tiles of 256 x 256: either side of one round of half tiles
          _tiles("t256_haar_132_tiles", 1024, 8300, 416, levels=10, k_hi=32, act_quant="asym"),
          _tiles("t128_haar_128_tiles", 1024, 8180, 416, levels=10, k_hi=32, act_quant="asym"),
