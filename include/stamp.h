@@ -319,7 +319,9 @@ typedef enum {
   STAMP_ROUTE_HI_IN_TILES = 1024,     /* 8-bit rows in the tiles of the 4-bit rows' GEMM */
   STAMP_ROUTE_PARTS = 2048,           /* with STAMP_ROUTE_DIRECT: blocks quantized in parts of 8 tokens */
   STAMP_ROUTE_Q_HI_IN_TILES = 4096,   /* STAMP_ROUTE_HI_IN_TILES in stamp_linear_forward_q, whose operand has a place of its own */
-  STAMP_ROUTE_TILES_PAIR = 8192       /* 4-bit rows in 128 x 256 tiles, two workgroups per CU */
+  STAMP_ROUTE_TILES_PAIR = 8192,      /* 4-bit rows in 128 x 256 tiles, two workgroups per CU */
+  STAMP_ROUTE_HI_ROWS_32 = 16384,     /* 8-bit rows' own FP6 kernel: 32 rows a workgroup in place of 64 or 128 */
+  STAMP_ROUTE_HI_TWO_STRIPS = 32768   /* 8-bit rows' own FP6 kernel: two strips of 32 columns a workgroup */
 } stamp_route_t;
 int32_t stamp_debug_routes(const stamp_plan_t* plan);
 

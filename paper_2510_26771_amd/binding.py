@@ -31,7 +31,7 @@ CHOICES = {"hi_rows": 0, "operands": 1}
 ROUTES = {"general": 1, "any_length_blocks": 2, "group_blocks": 4, "direct": 8, "beside_top": 16, "hi_fp6": 32,
           "hi_top_fused": 64, "hi_split": 128, "tiles_128": 256, "tiles_pair": 8192,
           "group_quant": 512, "hi_in_tiles": 1024,
-          "parts": 2048, "q_hi_in_tiles": 4096}
+          "parts": 2048, "q_hi_in_tiles": 4096, "hi_rows_32": 16384, "hi_two_strips": 32768}
 
 
 class StampError(RuntimeError):

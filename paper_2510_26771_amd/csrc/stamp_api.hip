@@ -843,6 +843,8 @@ int32_t stamp_debug_routes(const stamp_plan_t* p) {
     else if ((own ? p->hi_ksplit_own : p->hi_ksplit) > 1) r |= STAMP_ROUTE_HI_SPLIT;
   }
   if (fr.hi.ht.on) r |= STAMP_ROUTE_HI_IN_TILES;
+  else if ((r & STAMP_ROUTE_HI_FP6) && stamp_hi6_rows_per_workgroup(p, own) == 32) r |= STAMP_ROUTE_HI_ROWS_32;
+  else if ((r & STAMP_ROUTE_HI_FP6) && stamp_hi6_two_strips(p, own)) r |= STAMP_ROUTE_HI_TWO_STRIPS;
   if (converted_place(p, 0).ht.on) r |= STAMP_ROUTE_Q_HI_IN_TILES;
   const int M = rag ? (g.B * p->rag.nb) << p->rag.r : g.B * g.s;
   if (p->engine == STAMP_GEMM_FP6 && stamp_gemm6_half_tiles(M, p->Npad)) r |= STAMP_ROUTE_TILES_128;

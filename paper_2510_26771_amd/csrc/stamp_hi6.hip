@@ -47,11 +47,10 @@ __device__ __forceinline__ int part_at(int row, int col) {
 // (256) 11.9 against 12.8, but 64 x 4096 x 11008 (344) 21.4 against 17.4.  Up to 32 rows: WHT layer of 512 x 4096 -> 1024 43.0
 // without, 41.0 with, 2048 x 4096 -> 4096 81.3, 78.8.
 // NC: strips of 32 columns per workgroup.  Two: the rows' operand, the larger share of what a CU's vector memory path moves (64 bytes a
-// clock: that path is what bounds the loop), is read half as often.  512 x 4096 x 4096 39 us with one strip, 33 with two; 64 x 4096 x 11008
-// 17.2, 15.3, of which the loop 10 and 8, the launch and the sums of the waves 5, the top levels 2.
+// clock: that path is what bounds the loop), is read half as often, but nothing covers a workgroup's start and end (the rule:
+// stamp_hi6_two_strips).  64 x 4096 x 11008 16.2 us with one, 15.3 with two, of which the loop 8, the launch and the sums of the waves 5, the top levels 2.
 template <int NP, bool GRP, bool AHEAD, int NC = 1>
 __global__ __launch_bounds__(512, AHEAD || NC == 2 ? 2 : 4) void k_hi6(const Hi6Args h) {
-  request_args<Hi6Args>();
   const GemmArgs& a = h.a;
   const StampGeom& g = a.g;
   constexpr int C = 32 * NC, RW = 32 * NP, RS = 512 / C;  // columns, rows of a wave; rows apart that a thread finishes
@@ -146,9 +145,11 @@ __global__ __launch_bounds__(512, AHEAD || NC == 2 ? 2 : 4) void k_hi6(const Hi6
   }
   for (int kt = AHEAD || NC == 2 ? kt1 : kt0; kt < kt1; ++kt) {
     Frag6 fb, fa[2 * NP];
+    const uint8_t* const ra = pa + (size_t)kt * (2 * NP * kBlock6);
     fb.load(pb + (size_t)kt * kStageB6, lane16);
+    constexpr int first = GRP ? 2 * NP : 2;
 #pragma unroll
-    for (int i = 0; i < 2 * NP; ++i) fa[i].load(pa + (size_t)kt * (2 * NP * kBlock6) + i * kBlock6, lane16);
+    for (int i = 0; i < first; ++i) fa[i].load(ra + i * kBlock6, lane16);
     if constexpr (GRP) {
       // S = row scale times column scale (k = 1 of the product is zero)
       const f2 sw = reinterpret_cast<const f2*>(h.sw)[((size_t)(st >> 2) * KT + kt) * 128 + (st & 3) * 32 + l32];
@@ -168,7 +169,18 @@ __global__ __launch_bounds__(512, AHEAD || NC == 2 ? 2 : 4) void k_hi6(const Hi6
         }
       }
     } else {
-      multiply(fb, fa);
+      // (the compiler would put the loads off to save registers and have four of them in flight: 3200 workgroups at depth 8192 189 us in place of 168,
+      // 528 at depth 4096 25.1, 21.6; all fifteen do not fit)
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 2 * NP; ++i) {
+        multiply1(acct[0][i], fb, fa[i]);
+        if (i + first < 2 * NP) {
+          __builtin_amdgcn_sched_barrier(0);
+          fa[i + first].load(ra + (i + first) * kBlock6, lane16);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
     }
   }
   // staging position of a row: its natural position among the block sums of its sequence (top levels), else the row itself
@@ -322,6 +334,27 @@ int hi6_np(const stamp_plan* p, int own) {
 }
 }  // namespace
 
+int stamp_hi6_rows_per_workgroup(const stamp_plan* p, int own) { return 32 * hi6_np(p, own) * hi6_ng(p, own); }
+namespace {
+int64_t hi6_groups(const stamp_plan* p, int own) {
+  const int rows = stamp_hi6_rows_per_workgroup(p, own);
+  return (hi6_rows(p, own) + rows - 1) / rows;
+}
+}  // namespace
+
+// Two strips of columns a workgroup (n of them, one per CU) in place of one: where the depth is worth the longer start and end and
+// their last round is not a nearly empty one.  64 rows a workgroup, us with one strip and with two, by K steps and n: 5: 129 7.4, 9.2, 264
+// 12.8, 17.2, 512 15.9, 17.6.  9: 129 8.9, 11.4, 240 10.2, 11.1, 264 14.6, 19.2, 512 17.8, 19.5.  16: 160 11.7, 12.6, 320 16.7, 20.2, 512 20.4,
+// 21.3.  32: 129 14.9, 14.1, 256 15.8, 14.5, 264 21.6, 27.6, 384 22.0, 25.5, 448 26.4, 26.3, 512 27.3, 26.5, 768 39.2, 41.3, 1056 56, 69.  64: 129
+// 23.7, 20.0, 256 24.7, 19.7, 264 34.8, 40.8, 384 35.5, 37.5, 448 44.9, 38.2, 528 55, 61, 640 57.1, 56.9, 768 72.6, 62.6, 1024 99, 91, 1056 106, 108,
+// 1600 168, 156.
+bool stamp_hi6_two_strips(const stamp_plan* p, int own) {
+  const int cus = stamp_device_cus(), kt = p->Kpad / BK;
+  const int64_t groups = hi6_groups(p, own), n = hi6_strips(p) / 2 * groups, rounds = (n + cus - 1) / cus, last = n - (rounds - 1) * cus;
+  if (hi6_np(p, own) != 2 || hi6_ng(p, own) != 1 || 2 * n <= cus || kt < 32) return false;  // (2 n up to cus: AHEAD)
+  return rounds == 1 || (kt < 64 ? rounds == 2 && 4 * last >= 3 * cus : 2 * last > cus);
+}
+
 size_t stamp_hi6_bytes(const stamp_plan* p, int own) {
   const int M = hi6_rows(p, own), np = hi6_np(p, own), gr = 32 * np;
   return (size_t)((M + gr - 1) / gr) * (p->Kpad / 128) * (2 * np * kBlock6);
@@ -421,10 +454,8 @@ hipError_t stamp_launch_hi6(const stamp_plan* p, const uint8_t* a6, const float*
   h.norm = norm;
   h.Y = Y;
   // workgroups up to one per CU: the rule of AHEAD
-  const int rows = 32 * h.np * h.ng;
-  if ((int64_t)hi6_strips(p) * ((h.a.M + rows - 1) / rows) <= stamp_device_cus())
-    return h.np == 2 ? launch<2, false, true>(h, st) : launch<1, false, true>(h, st);
-  if (h.np == 2 && h.ng == 1) return launch<2, false, false, 2>(h, st);
+  if (hi6_strips(p) * hi6_groups(p, own) <= stamp_device_cus()) return h.np == 2 ? launch<2, false, true>(h, st) : launch<1, false, true>(h, st);
+  if (stamp_hi6_two_strips(p, own)) return launch<2, false, false, 2>(h, st);
   return h.np == 1 ? launch<1, false, false>(h, st) : launch<2, false, false>(h, st);
 }
 

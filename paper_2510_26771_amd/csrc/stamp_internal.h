@@ -344,6 +344,8 @@ hipError_t stamp_launch_repack6(const stamp_plan* p, const uint8_t* q_lo, uint8_
 // [B*s][N] in STaMP order, 3: blocked form: block sums times norm -> out, the token left out + bias -> Y
 bool stamp_hi6_fits(const stamp_plan* p, int own);
 size_t stamp_hi6_bytes(const stamp_plan* p, int own);
+int stamp_hi6_rows_per_workgroup(const stamp_plan* p, int own);
+bool stamp_hi6_two_strips(const stamp_plan* p, int own);
 // the operand at `a6`; ht: in the tiles' places instead
 StampHiOut stamp_hi6_out(const stamp_plan* p, uint8_t* a6, int own, const StampHiTiles& ht);
 StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6, int own, const StampHiTiles& ht);
