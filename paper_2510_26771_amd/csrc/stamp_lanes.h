@@ -25,6 +25,18 @@ struct LaneArgs {
   int G, gridW;      // token grid: blocks per row, tokens per row
 };
 
+// Which of n units of ROWS rows a workgroup takes: 64 neighbouring rows go to one XCD.  The workgroups go to the eight XCDs in turn, and each
+// of these has an L2 of its own, but rows 8 or 16 apart share every 16 bytes of the middle third of the operand, and units of fewer than
+// eight rows share lines everywhere (row_off6): unit by unit they were put together from several L2s.  Rows without transform, us, before
+// and with this: 8192 x 4096 bf16 20.2, 17.6, 32768 x 4096 77.8, 65.0, 8192 x 11008 62.8, 49.5 (2 rows a unit), 8192 x 4096 fp32 32.2, 30.0; Haar blocks
+// of 8: 8192 x 4096 23.1, 20.5, 16384 x 4096 41.7, 36.3, of 16: 49.7, 48.0.  (Rows that share those 16 bytes in one workgroup, four rows of
+// eight each, instead: 22.3 and 91.8 for the first two.)
+template <int ROWS>
+__device__ __forceinline__ int unit_of_block(int blk, int n) {
+  constexpr int U = 64 / ROWS;
+  return blk < n / (8 * U) * (8 * U) ? (blk & ~(8 * U - 1)) + (blk & 7) * U + ((blk >> 3) & (U - 1)) : blk;
+}
+
 // codes of 8-bit rows, 16 h + l, as two fragments
 __device__ __forceinline__ void store_hi24(const Hi6Out& o, int m, int KT, f16v ev, f16v od, int c) {
   u6v h, l;

@@ -27,12 +27,14 @@ __global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs
   extern __shared__ __attribute__((aligned(16))) uint8_t s_row[];     // NG = 2: row A of the first group, [8][threads] 16 bytes
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = (int)(blockDim.x >> 6);
   const int tl = lane & (NL - 1), b = blockIdx.y;
-  const int parts = RAG ? 1 : a.R >> RLOG, j = (int)blockIdx.x / parts, part = (int)blockIdx.x - j * parts;  // block, part of it
+  // (NG = 2, one workgroup per CU: no difference)
+  const int unit = NG == 2 ? (int)blockIdx.x : unit_of_block<RK>(blockIdx.x, gridDim.x);
+  const int parts = RAG ? 1 : a.R >> RLOG, j = unit / parts, part = unit - j * parts;  // block, part of it
   const size_t seq0 = (size_t)b * a.s, row_bytes = (size_t)a.d * (BF16 ? 2 : 4);
   const bool left_out = RAG && j == a.rag.nb;  // the token left out: a row of its own, in the lanes of tl = 0
   const int m = left_out ? 1 : RAG && j == a.rag.nb - 1 ? a.rag.mlast : RK;
   const uint8_t* const X_blk =
-      reinterpret_cast<const uint8_t*>(a.X) + (seq0 + (left_out || !RAG ? 0 : a.rag.o) + (left_out ? 0 : (size_t)blockIdx.x * RK)) * row_bytes;
+      reinterpret_cast<const uint8_t*>(a.X) + (seq0 + (left_out || !RAG ? 0 : a.rag.o) + (left_out ? 0 : (size_t)unit * RK)) * row_bytes;
   int c0[NG];
   u4 raw[NG][2][CPR];
 #pragma unroll
@@ -221,7 +223,7 @@ __global__ __launch_bounds__(NG == 1 ? 1024 : 768) void k_lanes1d(const LaneArgs
     const bool active = c < a.d;
     if (sum_out) {
       if (active && tl == 0) {
-        float4* o = reinterpret_cast<float4*>(a.abot + ((size_t)b * (a.s >> RLOG) + blockIdx.x) * a.d + c);
+        float4* o = reinterpret_cast<float4*>(a.abot + ((size_t)b * (a.s >> RLOG) + unit) * a.d + c);
 #pragma unroll
         for (int i = 0; i < 8; ++i) o[i] = make_float4(rb[g][4 * i], rb[g][4 * i + 1], rb[g][4 * i + 2], rb[g][4 * i + 3]);
       }
@@ -377,7 +379,7 @@ __global__ __launch_bounds__(1024) void k_lanes_rows(const LaneArgs a, int rows)
   constexpr int CPR = BF16 ? 4 : 8;
   __shared__ __attribute__((aligned(16))) uint32_t s_max[2][ROWS][16];  // [sign][row][wave]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = (int)(blockDim.x >> 6);
-  const int tl = lane & (ROWS - 1), m = (int)blockIdx.x * ROWS + tl, mr = min(m, rows - 1);
+  const int tl = lane & (ROWS - 1), m = unit_of_block<ROWS>(blockIdx.x, gridDim.x) * ROWS + tl, mr = min(m, rows - 1);
   const int c = (wave * (64 / ROWS) + lane / ROWS) * 32, cl = min(c, a.d - 32);
   u4 raw[CPR];
   const uint8_t* const src = reinterpret_cast<const uint8_t*>(a.X) + ((size_t)mr * a.d + cl) * (BF16 ? 2 : 4);

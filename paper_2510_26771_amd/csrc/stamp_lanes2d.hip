@@ -26,7 +26,7 @@ __global__ __launch_bounds__(768) void k_lanes2d(const LaneArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t s_max[2][RK][16];  // [sign][row][wave]
   extern __shared__ __attribute__((aligned(16))) uint8_t s_row[];     // the x differences, [8][threads] 16 bytes
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = (int)(blockDim.x >> 6);
-  const int tl = lane & (NL - 1), b = blockIdx.y, j = blockIdx.x, by = j / a.G, bx = j - by * a.G;
+  const int tl = lane & (NL - 1), b = blockIdx.y, j = unit_of_block<RLOG == 3 ? 64 : 16>(blockIdx.x, gridDim.x), by = j / a.G, bx = j - by * a.G;
   // cell (qx, qy) of the block: bits 0, 2 and 1, 3 of the lane
   const int qx = (tl & 1) | ((tl >> 1) & 2), qy = ((tl >> 1) & 1) | ((tl >> 2) & 2);
   const size_t seq0 = (size_t)b * a.s;
