@@ -848,7 +848,8 @@ int32_t stamp_debug_routes(const stamp_plan_t* p) {
   if (converted_place(p, 0).ht.on) r |= STAMP_ROUTE_Q_HI_IN_TILES;
   const int M = rag ? (g.B * p->rag.nb) << p->rag.r : g.B * g.s;
   if (p->engine == STAMP_GEMM_FP6 && stamp_gemm6_half_tiles(M, p->Npad)) r |= STAMP_ROUTE_TILES_128;
-  else if (p->engine == STAMP_GEMM_FP6 && p->gen.group == 0 && stamp_gemm6_pairs(M, p->Npad, p->Kpad)) r |= STAMP_ROUTE_TILES_PAIR;
+  const int mode = rag ? 2 : p->gen.kind != kGenNone ? 1 : g.ident ? 3 : p->fused_ok && !p->unfused ? 2 : 1;
+  if (p->engine == STAMP_GEMM_FP6 && !(r & STAMP_ROUTE_TILES_128) && stamp_gemm6_pairs(M, p->Npad, p->Kpad, mode)) r |= STAMP_ROUTE_TILES_PAIR;
   return r;
 }
 

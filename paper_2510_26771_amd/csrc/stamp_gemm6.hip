@@ -156,27 +156,32 @@ bool stamp_gemm6_half_tiles(int M, int Npad) {
   return 100 * r8 > 68 * r4;
 }
 
-// Two workgroups of 128 x 256 tiles per CU against one of 256 x 256: layers of 8192 rows, 3 levels, us, by depth and rounds (256 x 256 tiles
-// over CUs).  Depth 1152: 1 round 34.3, 34.1, 1.1 to 1.5 rounds 45.7, 41.2, 1.75 46.7, 45.2, 2 53.5, 48.7, 2.25 64.3, 58.8, 3 67.0, 67.9,
-// 4 81.8, 78.5.  2048: 1 40.8, 41.8, 1.1 to 1.5 56.4, 53.3, 1.75 57.8, 58.4, 2 65.7, 62.8, 2.25 80.6, 76.4, 3 84.2, 85.4.  3072: 1.1 to 1.5 74.5,
-// 73.2, 1.75 75.9, 77.9, 2 83.7, 82.0, 3 109.9, 113.2.  4096: 1.25 86.0, 85.6, 1.5 86.8, 87.2, 1.75 88.3, 92.7, 2.25 126.1, 123.4, 4 158.7,
-// 165.7; 2048 x 4096 -> 11008 (1.34 rounds) 89.4, 88.7, with the first token left out 87.3, 85.7.  Depth 8192, 56 rounds: 2743, 3567 the
-// GEMM alone.  2 x 64 x 64 grid, 704 -> 3080 (1.6 rounds): 46.6, 49.2.  Hence: where the last round is up to half full, shallow layers also
-// where it is full.
-bool stamp_gemm6_pairs(int M, int Npad, int Kpad) {
+// Two workgroups of 128 x 256 tiles per CU against one of 256 x 256.  Layers of 8192 rows, us, by K steps and rounds (256 x 256 tiles over CUs);
+// last where the last round is up to half full, then fuller, then full.  Fused, 3 levels: 5 steps: 1.1 to 1.5 rounds 36.0, 32.5, 2.25 49.0,
+// 44.3, 2.5 49.2, 45.0; 1.75 37.2, 35.6; 2 42.3, 36.9, 3 52.2, 52.6, 4 70.7, 64.7.  9: 1.1 46.1, 41.8, 1.5 46.0, 41.9, 2.25 62.7, 56.7; 1.75 46.6, 45.1; 2
+// 53.4, 47.9, 3 67.2, 67.1, 4 89.5, 81.3.  16: 1.1 58.0, 54.3, 1.5 58.4, 56.3, 2.25 80.5, 76.0; 1.75 62.0, 61.6; 2 67.3, 63.6, 3 88.0, 88.5, 4 115.3, 112.0.
+// 32: 1.1 91.0, 90.0, 1.5 96.2, 92.3, 2.25 129.1, 126.8; 1.75 96.4, 99.2; 2 103.6, 103.8, 3 144.3, 146.9.  Blocks of any length and token grids the same but
+// for 1.6 rounds of a grid with rows that are no whole lines, 704 -> 3080: 46.6, 49.2.  Depth 8192, 56 rounds: 2743, 3567 the GEMM alone.
+// Without transform: 5: 1.1 33.8, 31.6, 2.25 46.9, 44.2; 2 37.8, 35.4, 3 48.8, 48.4, 4 68.3, 62.1.  9: 1.1 41.9, 39.1, 2.25 58.2, 54.4; 1.75 43.7, 43.6; 2
+// 46.9, 44.5, 3 61.4, 61.0.  16: 1.1 53.6, 51.8, 2.25 76.9, 74.3; 1.75 56.7, 58.0; 2 59.6, 59.9, 3 82.9, 85.6.  32: 1.1 87.4, 88.8, 2.25 123.8, 125.8.
+// fp32 rows (the whole WHT layer): 5: 1.1 103.1, 100.8, 1.5 125.3, 123.3, 2.25 179.1, 180.6; 2 161, 153.  9: 1.1 112.7, 111.4, 2.25 172.2, 174.3; 2 146.1,
+// 145.8, 3 212.7, 214.3.  16: 1.1 137.8, 135.9, 1.5 144.8, 144.1, 2.25 207.8, 211.1; 2 171.8, 174.1.  32: 1.1 200.8, 202.0, 2 240, 249.
+// Hence: last rounds up to half full, which pairs halve, and shallow layers' full ones, whose stores come all at once in 256 x 256 tiles.
+bool stamp_gemm6_pairs(int M, int Npad, int Kpad, int mode) {
   const int cus = stamp_device_cus(), kt = Kpad / BK;
-  const int64_t tiles = (int64_t)((M + 127) / 128) * (Npad / BN6), rem = tiles % (2 * cus);
-  if (tiles <= 2 * cus || kt > 32) return false;
-  if (kt <= 9) return rem <= cus;
-  if (rem == 0) return kt <= 24 && tiles == 4 * cus;
-  return kt <= 24 ? rem <= cus : 4 * rem <= 3 * cus;
+  const int64_t tiles = (int64_t)((M + 127) / 128) * (Npad / BN6), rem = tiles % (2 * cus), two = 4 * (int64_t)cus;  // two: of full rounds
+  if (mode == 0 || tiles <= 2 * cus || rem > cus) return false;
+  if (kt <= 9) return mode != 1 || tiles <= two;
+  if (mode == 1) return false;
+  if (rem == 0) return mode == 2 && kt <= 24 && tiles == two;
+  return kt <= (mode == 2 ? 32 : 24);
 }
 
 namespace {
 hipError_t gemm6(const GemmArgs& a, int mode, hipStream_t st) {
   if (a.ht.on) return mode == 2 ? stamp_gemm6_half_hi(a, st) : hipErrorInvalidValue;
   if (mode != 0 && stamp_gemm6_half_tiles(a.M, a.Npad)) return stamp_gemm6_half(a, mode, st);
-  return mode != 0 && stamp_gemm6_pairs(a.M, a.Npad, a.Kpad) ? stamp_gemm6_pair(a, mode, st) : gemm6_run(a, mode, st);
+  return stamp_gemm6_pairs(a.M, a.Npad, a.Kpad, mode) ? stamp_gemm6_pair(a, mode, st) : gemm6_run(a, mode, st);
 }
 }  // namespace
 

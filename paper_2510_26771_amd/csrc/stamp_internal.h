@@ -379,7 +379,7 @@ inline int stamp_row_group_bit(const stamp_plan* p) {
 }
 // whether the FP6 GEMM over M rows takes 128 x 256 tiles
 bool stamp_gemm6_half_tiles(int M, int Npad);
-bool stamp_gemm6_pairs(int M, int Npad, int Kpad);  // two workgroups of 128 x 256 tiles per CU
+bool stamp_gemm6_pairs(int M, int Npad, int Kpad, int mode);  // two workgroups of 128 x 256 tiles per CU
 // identity plans: 8-bit rows' dequantized partial rows [nparts][B*k][N] (+ bias) -> Y rows of tokens 0..k-1
 hipError_t stamp_launch_hi_rows_out(const stamp_plan* p, const float* Yt_hi, void* Y, hipStream_t st, int nparts);
 // P: block sums [B*k][ldP]; nparts partial sources (each B*k*ncols floats apart) are added while reading

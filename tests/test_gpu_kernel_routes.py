@@ -643,11 +643,15 @@ def test_both_gemm_tile_sizes(w):
 
 
 # ---- two workgroups of 128 x 256 tiles per CU: few tiles more than they hold at once (a row more than a tile, odd d_out), depths of 1, 9 and 10
-# K steps, every block length; and the sizes beside them that keep 256 x 256 tiles: a last round more than half full, one round
+# K steps, every block length, fp32 rows (WHT, a plan of blocks run level by level); and the sizes beside them that keep 256 x 256 tiles: a
+# last round more than half full, one round, fp32 rows at 10 steps and beyond two rounds
 PAIRS = [_tiles("pair_ident_odd", 8193, 2049, 128, xform="identity", levels=0), _tiles("pair_haar32_10_steps", 2048, 8448, 1248, levels=11, k_hi=64),
          _tiles("pair_haar8_asym", 4096, 4354, 1152, levels=3, k_hi=512, act_quant="asym"), _tiles("pair_haar16_odd", 2048, 8449, 224, levels=4, k_hi=128, act_quant="asym"),
          _tiles("pair_grid8", 4096, 4354, 96, xform="haar2d", grid_h=64, grid_w=64, levels=3, k_hi=64, corr_len=4.0),
          _tiles("pair_rag64", 2100, 8193, 160, levels=6, skip_first=True, k_hi=32),
+         _tiles("pair_wht", 8192, 2306, 1120, xform="wht", levels=0, k_hi=32), _tiles("pair_wht_odd_asym", 2048, 8193, 96, xform="wht", levels=0, act_quant="asym"),
+         _tiles("t256_wht_10_steps", 2048, 8193, 1184, xform="wht", levels=0), _tiles("t256_wht_more_than_two_rounds", 4096, 8200, 160, xform="wht", levels=0),
+         _tiles("pair_ident_10_steps", 2048, 8450, 1184, xform="identity", levels=0, act_quant="asym"),
          _tiles("t256_last_round_full", 4096, 6900, 1184, levels=3, k_hi=64), _tiles("t256_one_round", 4096, 4096, 96, levels=3, k_hi=64)]
 
 
