@@ -1,6 +1,6 @@
 // Measurement aid: the rate the matrix pipeline of this GPU sustains on the operand VALUES of this
-// layer with no memory traffic at all.  A register-only loop of independent MFMAs over pseudo-random
-// 4-bit codes in the operand format of the chosen engine, on every CU, timed with events.  The clock
+// layer with no memory traffic at all.  A register-only loop of independent MFMAs, the GEMM's own (FP6: 16 x 16 x 128), over
+// pseudo-random 4-bit codes in the operand format of the chosen engine, on every CU, timed with events.  The clock
 // of the chip under such a load depends on the data (random operands draw more power than constant
 // ones), so this rate, not the data-sheet peak, is what a GEMM on these values can approach.
 #include "stamp_internal.h"
@@ -10,7 +10,7 @@ namespace {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v16i __attribute__((ext_vector_type(16)));
-typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint32_t mix(uint32_t x) {
   x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; x ^= x >> 16;
@@ -51,12 +51,10 @@ __global__ __launch_bounds__(256) void k_rate_int8(int iters, float* sink) {
   if (s == 0x7fffffff) sink[0] = (float)s;
 }
 
-__global__ __launch_bounds__(256) void k_rate_fp6(int iters, float* sink) {
-  v16f acc[8];
+__global__ __launch_bounds__(256, 4) void k_rate_fp6(int iters, float* sink) {
+  v4f acc[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+  for (int i = 0; i < 8; ++i) acc[i] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
   v8i a, b;
 #pragma unroll
   for (int i = 0; i < 6; ++i) {
@@ -76,13 +74,15 @@ __global__ __launch_bounds__(256) void k_rate_fp6(int iters, float* sink) {
   a[6] = a[7] = b[6] = b[7] = 0;
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i], 2, 2, 0, 0, 0, 0);
+    for (int i = 0; i < 8; ++i) acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, acc[i], 2, 2, 0, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(acc[i]));  // (each stays where it is: else they are moved on from turn to turn)
   }
   float s = 0.0f;
 #pragma unroll
   for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) s += acc[i][v];
+    for (int v = 0; v < 4; ++v) s += acc[i][v];
   if (s == 1.2345e30f) sink[0] = s;
 }
 
@@ -98,8 +98,8 @@ extern "C" stamp_status_t stamp_debug_mfma_rate(int32_t engine, double* tera_ops
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipMalloc(reinterpret_cast<void**>(&sink), sizeof(float)) != hipSuccess) { (void)hipGetLastError(); return STAMP_ERR_ALLOC; }
   bool ok = hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess;
-  const int blocks = 2 * cus, iters = 20000;  // two workgroups of four waves per CU = two waves per SIMD
-  const double ops_per_mfma = engine == STAMP_GEMM_FP6 ? 2.0 * 32 * 32 * 64 : 2.0 * 32 * 32 * 32;
+  const int blocks = 2 * cus, iters = engine == STAMP_GEMM_FP6 ? 40000 : 20000;  // two workgroups of four waves per CU = two waves per SIMD
+  const double ops_per_mfma = engine == STAMP_GEMM_FP6 ? 2.0 * 16 * 16 * 128 : 2.0 * 32 * 32 * 32;
   double best = 0.0;
   for (int rep = 0; ok && rep < 4; ++rep) {  // the first repetition warms up
     ok = hipEventRecord(e0, nullptr) == hipSuccess;
