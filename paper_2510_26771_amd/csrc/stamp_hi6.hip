@@ -342,17 +342,19 @@ int64_t hi6_groups(const stamp_plan* p, int own) {
 }
 }  // namespace
 
-// Two strips of columns a workgroup (n of them, one per CU) in place of one: where the depth is worth the longer start and end and
-// their last round is not a nearly empty one.  64 rows a workgroup, us with one strip and with two, by K steps and n: 5: 129 7.4, 9.2, 264
-// 12.8, 17.2, 512 15.9, 17.6.  9: 129 8.9, 11.4, 240 10.2, 11.1, 264 14.6, 19.2, 512 17.8, 19.5.  16: 160 11.7, 12.6, 320 16.7, 20.2, 512 20.4,
-// 21.3.  32: 129 14.9, 14.1, 256 15.8, 14.5, 264 21.6, 27.6, 384 22.0, 25.5, 448 26.4, 26.3, 512 27.3, 26.5, 768 39.2, 41.3, 1056 56, 69.  64: 129
-// 23.7, 20.0, 256 24.7, 19.7, 264 34.8, 40.8, 384 35.5, 37.5, 448 44.9, 38.2, 528 55, 61, 640 57.1, 56.9, 768 72.6, 62.6, 1024 99, 91, 1056 106, 108,
-// 1600 168, 156.
+// Two strips of columns a workgroup (n of them, one per CU) in place of one: where the depth is worth the longer start and end, or they
+// fill the CUs once, and not where their last round is a nearly empty one.  64 rows a workgroup, inside layers of 2048 to 8192 tokens, us with one strip and with two, by K
+// steps and n: 5: 136 6.8, 7.9, 224 8.0, 7.5, 256 8.3, 7.9, 280 11.2, 13.7, 512 13.7, 14.2.  9: 136 8.3, 8.6, 172 9.3, 9.6, 256 9.6, 8.9, 280 13.3, 16.0, 512 15.7,
+// 15.9.  12: 136 9.0, 9.3, 172 9.6, 9.7, 256 10.4, 9.7, 280 14.1, 17.5, 512 17.0, 17.1.  16: 129 9.8, 9.5, 172 10.6, 10.0, 256 11.4, 10.0, 264 14.8, 17.8, 344
+// 15.5, 18.5, 512 18.8, 17.8.  32: 129 14.0, 12.4, 172 14.9, 13.2, 256 16.2, 13.2, 264 20.7, 24.4, 344 23.1, 26.1, 512 30.4, 26.4.  With the weights in the
+// caches, 32: 448 26.4, 26.3, 768 39.2, 41.3, 1056 56, 69; 64: 129 23.7, 20.0, 256 24.7, 19.7, 264 34.8, 40.8, 384 35.5, 37.5, 448 44.9, 38.2, 528 55, 61, 640
+// 57.1, 56.9, 768 72.6, 62.6, 1024 99, 91, 1056 106, 108, 1600 168, 156.
 bool stamp_hi6_two_strips(const stamp_plan* p, int own) {
   const int cus = stamp_device_cus(), kt = p->Kpad / BK;
   const int64_t groups = hi6_groups(p, own), n = hi6_strips(p) / 2 * groups, rounds = (n + cus - 1) / cus, last = n - (rounds - 1) * cus;
-  if (hi6_np(p, own) != 2 || hi6_ng(p, own) != 1 || 2 * n <= cus || kt < 32) return false;  // (2 n up to cus: AHEAD)
-  return rounds == 1 || (kt < 64 ? rounds == 2 && 4 * last >= 3 * cus : 2 * last > cus);
+  if (hi6_np(p, own) != 2 || hi6_ng(p, own) != 1 || 2 * n <= cus) return false;  // (2 n up to cus: AHEAD)
+  if (rounds == 1) return kt >= 16 || 8 * n >= 7 * cus;
+  return kt >= 64 ? 2 * last > cus : kt >= 16 && rounds == 2 && 4 * last >= 3 * cus;
 }
 
 size_t stamp_hi6_bytes(const stamp_plan* p, int own) {

@@ -662,8 +662,8 @@ def test_pairs_of_tiles(w):
 
 
 # ---- 8-bit rows' kernel: 32 rows a workgroup where 64 leave half of the CUs idle (either side of that line, a row more and less than whole
-# groups), two strips of columns a workgroup (deep layers, either side of one round and of three quarters of the second; their first
-# depth and one K step less), with and without top levels, odd d_out, all its outputs
+# groups), two strips of columns a workgroup (either side of one round, of three quarters of the second and of seven eighths of the first in
+# shallow layers; their first depth and one K step less), with and without top levels, odd d_out, all its outputs
 def _few(name, n, k, **kw):
     base = dict(xform="identity", levels=0, seq_len=k + 40, d_in=416, d_out=n, k_hi=k)
     base.update(kw)
@@ -674,12 +674,14 @@ R32, STRIPS, NEITHER = ("hi_rows_32", "-hi_two_strips"), ("hi_two_strips", "-hi_
 FEW = [(_few("ident_64_line", 4096, 64), R32), (_few("ident_64_above", 4097, 64), NEITHER), (_few("ident_33", 1000, 33, act_quant="asym"), R32),
        (_few("ident_31", 8300, 31), R32), (_few("ident_65_one_strip", 8301, 65, act_quant="asym"), NEITHER), (_few("wht_33", 515, 33, xform="wht", seq_len=256), R32),
        (_few("tops_128", 8256, 128, xform="haar1d", levels=10, seq_len=1024), NEITHER),
-       (_few("ident_strips_one_round", 8129, 65, act_quant="asym", d_in=4000), STRIPS), (_few("ident_strips_above", 8201, 65, d_in=4000), NEITHER), (_few("ident_strips_first", 8257, 64, act_quant="asym", d_in=4000), STRIPS),
-       (_few("ident_31_steps", 8257, 64, d_in=3968), NEITHER), (_few("ident_strips_second_round", 4129, 385, d_in=4000), STRIPS),
-       (_few("wht_strips", 8258, 40, xform="wht", seq_len=64, d_in=4000), STRIPS),
-       (_few("tops_strips", 12290, 64, xform="haar1d", levels=9, seq_len=512, d_in=4000), STRIPS),
+       (_few("ident_strips_one_round", 8129, 65, act_quant="asym"), STRIPS), (_few("ident_strips_above", 8201, 65, d_in=2048), NEITHER),
+       (_few("ident_strips_7_8", 7105, 65), STRIPS), (_few("ident_strips_less", 7040, 65), NEITHER),
+       (_few("ident_strips_first", 8257, 64, act_quant="asym", d_in=1952), STRIPS), (_few("ident_15_steps", 8257, 64, d_in=1920), NEITHER),
+       (_few("ident_strips_second_round", 4129, 385, d_in=1952), STRIPS), (_few("ident_strips_second_round_less", 3072, 450, d_in=1952), NEITHER),
+       (_few("wht_strips", 8258, 40, xform="wht", seq_len=64, d_in=1952), STRIPS),
+       (_few("tops_strips", 12290, 64, xform="haar1d", levels=9, seq_len=512, d_in=1952), STRIPS),
        # (below half of a round of 256 x 256 tiles these rows would ride in the 4-bit rows' tiles)
-       (_few("rag_strips", 10753, 64, xform="haar1d", levels=3, seq_len=800, skip_first=True, d_in=4000), STRIPS),
+       (_few("rag_strips", 10753, 64, xform="haar1d", levels=3, seq_len=800, skip_first=True, d_in=1952), STRIPS),
        (_few("rag_one_strip", 10753, 64, xform="haar1d", levels=3, seq_len=800, skip_first=True), NEITHER)]
 
 
