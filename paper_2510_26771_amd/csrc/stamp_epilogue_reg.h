@@ -33,11 +33,11 @@ struct RegMap {
   static constexpr int nb = 64 / R;  // blocks per lane
   static_assert(RL >= 3 && RL <= 6, "blocks of 8 .. 64 rows");
   static constexpr int mi(int t, int e) {
-    if (!GRP) return (t * R + e) >> 4;
+    if (!GRP) return (RL == 6 ? (int)place_of_64((uint32_t)e) : t * R + e) >> 4;
     return RL == 6 ? ((e >> 5) + 2 * ((e >> 2) & 1)) : RL == 5 ? (2 * t + ((e >> 2) & 1)) : RL == 4 ? t : (t >> 1);
   }
   static constexpr int v(int t, int e) {
-    if (!GRP) return reg16(t * R + e);
+    if (!GRP) return reg16(RL == 6 ? (int)place_of_64((uint32_t)e) : t * R + e);
     return RL >= 5   ? (4 * ((e >> 3) & 3) + (e & 3))
            : RL == 4 ? (4 * (((e >> 3) & 1) + 2 * ((e >> 2) & 1)) + (e & 3))
                      : (4 * (2 * (t & 1) + ((e >> 2) & 1)) + (e & 3));

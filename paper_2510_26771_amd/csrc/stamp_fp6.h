@@ -22,8 +22,11 @@ constexpr int kStageA6 = 2 * kStageB6;        // 24 KB
 // two operands (tiles of 16 rows), 4 and 5 the block.  gb = log2 of the rows that the epilogue keeps together in a lane, at least 2: the
 // two groups hold neighbouring blocks (plain rows: neighbouring four rows), and both have work in a tile with few rows.  With bit 6 for
 // all plans one of them had none where a tile has up to 64: 64 x 256 -> 128 18.7 us, 18.2 with this; 64 x 512 -> 4096 19.9, 19.6; 40 x 1024 ->
-// 4096 without transform 17.1, 16.5; 77 x 2048 -> 1024 21.2, 20.4.
-STAMP_HD uint32_t row_rest6(uint32_t r, int gb) { return ((r & 127) >> (gb + 1) << gb) | (r & ((1u << gb) - 1)); }
+// 4096 without transform 17.1, 16.5; 77 x 2048 -> 1024 21.2, 20.4.  Blocks of 64: place_of_64.
+STAMP_HD uint32_t row_rest6(uint32_t r, int gb) {
+  const uint32_t L = ((r & 127) >> (gb + 1) << gb) | (r & ((1u << gb) - 1));
+  return gb == 6 ? place_of_64(L) : L;
+}
 STAMP_HD bool row_half6(uint32_t r, int gb) { return (row_rest6(r, gb) >> 3) & 1; }
 // row of a 256-row tile -> byte of its lane in channels 0 .. 31 of K step 0
 STAMP_HD uint32_t row_off6(uint32_t r, int gb) {

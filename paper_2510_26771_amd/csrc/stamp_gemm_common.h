@@ -85,8 +85,13 @@ struct GemmArgs {
                          // STaMP order, P row b * g.khi + slot
 };
 
+// Places of blocks of 64 rows (gb = 6, row_off6): bits 2 .. 5 of the row turned by one, so that a tile of 16 rows has coarse and fine
+// differences: the matrix pipe draws less power on them.  8 x 4096 x 4096 -> 4096: GEMM 208.8 us, 210.6 with the rows in order.
+STAMP_HD constexpr uint32_t place_of_64(uint32_t r) { return (r & 3) | ((r >> 5) & 1) << 2 | ((r >> 2) & 7) << 3; }
 // row of lane group 0 at place L (row_off6)
-STAMP_HD uint32_t row_of_rest6(uint32_t L, int gb) { return (L >> gb << (gb + 1)) | (L & ((1u << gb) - 1)); }
+STAMP_HD uint32_t row_of_rest6(uint32_t L, int gb) {
+  return gb == 6 ? (L & 3) | ((L >> 3) & 7) << 2 | ((L >> 2) & 1) << 5 : (L >> gb << (gb + 1)) | (L & ((1u << gb) - 1));
+}
 
 // Asks for every 64-byte line of the kernel's arguments (and the one of the grid's size behind them) at once.  They are read where they
 // are first needed, each line from memory and one after the other otherwise, some 450 cycles a line: up to the first operand request of

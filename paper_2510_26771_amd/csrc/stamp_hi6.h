@@ -91,9 +91,10 @@ __device__ __forceinline__ void repack6_store(uint8_t* dst, u4 w0, u4 w1) {
 
 // The two rows of unit u = 0 .. 511 of a (row tile, K step): the first of them, how far on the other is, and fragment
 __device__ __forceinline__ int repack6_row(int u, int gb) {
-  return (u >> 8) * 128 + (int)row_of_rest6((uint32_t)(((u >> 6) & 3) * 16 + (u & 7)), gb) + (((u >> 3) & 1) << gb);
+  const int blk = __builtin_amdgcn_readfirstlane(u >> 6);  // (the same for a wave)
+  return (blk >> 2) * 128 + (int)row_of_rest6((uint32_t)(blk & 3) * 16, gb) + (int)row_of_rest6((uint32_t)u & 7, gb) + (((u >> 3) & 1) << gb);
 }
-__device__ __forceinline__ int repack6_dist(int gb) { return gb <= 3 ? 16 : 8; }
+__device__ __forceinline__ int repack6_dist(int gb) { return (int)row_of_rest6(8, gb); }
 __device__ __forceinline__ int repack6_frag(int u) { return (u >> 4) & 3; }
 // packed 4-bit rows -> operand: block `blk` = (row tile, K step), unit u of it
 __device__ __forceinline__ void repack6_rows(const uint8_t* __restrict__ q_lo, uint8_t* __restrict__ a6, size_t blk, int u, int gb) {
