@@ -149,7 +149,11 @@ hipError_t stamp_launch_repack6_rag(const stamp_plan* p, const uint8_t* q_lo, ui
 // 128 x 256 tiles where the rounds they need (tiles over CUs, rounded up), at two thirds of a round of 256 x 256 tiles each,
 // take less time.  Depth 4096, 1-D blocks of 32, 2048 rows, microseconds, 256 x 256 against 128 x 256: 128 tiles of 256 x 256
 // 28.3, 23.0; 344 (2 rounds against 3) 58.1, 57.4; depth 11008, 128 tiles: 64.4, 47; at full rounds (256 tiles) 35.8 against
-// twice 23.
+// twice 23.  (Measured while both multiplied with 32 x 32 x 64 MFMAs.)  With 16 x 16 x 128 ones and 8-bit rows in the tiles, whole
+// layers, us, 256 x 256 (or pairs of 128 x 256, if stamp_gemm6_pairs takes them) against 128 x 256: half a round 43 against 33 (2048 x 4096 ->
+// 4096, 3 levels), 57 against 48 (8192 x 4096 -> 1024); 0.56 to 0.6 rounds 27.2, 29.2 (4096 x 1152 -> 2304); two rounds against three, 2048
+// -> 8448 .. 11008, 3 levels: depth 1152 38.4, 36.5, 4096 78.3, 74.3, 8192 137.4, 138.5; without transform 1152 37.4, 41.7, 4096 76.6,
+// 77.3; full depth 4096 93.0, 92.2, 8192 156, 166.  The line stands where it was.
 bool stamp_gemm6_half_tiles(int M, int Npad) {
   const int cus = stamp_device_cus(), nt = Npad / BN6;
   const int r8 = ((M + 255) / 256 * nt + cus - 1) / cus, r4 = ((M + 127) / 128 * nt + cus - 1) / cus;

@@ -16,14 +16,14 @@ using namespace stamp_gemm;
 // Workgroup: 8 waves (2 x 4), tile 256 x 256, one workgroup per CU with two waves on every SIMD, all
 // eight sharing one operand stage: 48 KB per K step for 256 x 256 x 128 products, a third less L2 -> LDS
 // traffic per product than two independent 256 x 128 workgroups would need (the FP6 pipeline consumes a K
-// step in half the time of the int8 one, which makes that traffic the bound).  Three stages: while step kt is
-// multiplied, the stage of step kt+1 has landed or is landing and that of step kt+2 is in flight; the request for
-// step kt+3 goes out late in step kt, into the stage that step kt has just given up.
+// step in half the time of the int8 one, which makes that traffic the bound).  S stages (kNumStage6: three, PAIR
+// two): while step kt is multiplied, the stages of the S - 1 steps after it have landed or are in flight; the request
+// for step kt + S goes out late in step kt, into the stage that step kt has just given up.
 //
-// The kernel is persistent: one workgroup per CU walks its share of the tiles (the XCD-aware order of
+// The kernel is persistent: the workgroups (one per CU, PAIR: two) walk their shares of the tiles (the XCD-aware order of
 // tile_of_sid, every workgroup of an XCD taking every wx-th tile of that XCD's range), and the operand
-// pipeline runs on across tile boundaries: the first three K steps of the next tile are requested during the last
-// three steps of the current one, so they, and the stores of the epilogue, are in flight while the epilogue
+// pipeline runs on across tile boundaries: the first S K steps of the next tile are requested during the last
+// S steps of the current one, so they, and the stores of the epilogue, are in flight while the epilogue
 // computes.  The epilogue works in registers (stamp_epilogue_reg.h) and leaves the operand stages alone.
 //
 // Inside a step nothing waits for what it has just asked for: the LDS reads of an activation block fly under the
@@ -32,20 +32,21 @@ using namespace stamp_gemm;
 // block, the others in the next step.
 //
 // WAVES = 4: tile 128 x 256, one wave on every SIMD, 36 KB per K step; the same loop, nine loads per wave and step.  A tile
-// takes 0.64 of the time of a 256 x 256 one (8.5 us + 0.455 us per K step against 12.8 + 0.72, all CUs busy, with 32 x 32 x 64 MFMAs): for shapes that
-// leave CUs idle (the rule stands at stamp_gemm6_half_tiles).
-constexpr int BN6 = 256;
+// takes 0.64 of the time of a 256 x 256 one (8.5 us + 0.455 us per K step against 12.8 + 0.72, all CUs busy; measured while the products were 32 x 32 x 64
+// MFMAs): for shapes that leave CUs idle (the rule stands at stamp_gemm6_half_tiles).
 //
 // PAIR (WAVES = 4): two workgroups per CU, two stages each (72 KB): one multiplies while the other is in its epilogue, and the last
 // tiles are half as large; but a CU moves half as much again per product.  For shallow layers of more than one round (the rule
 // stands at stamp_gemm6_pairs).
-constexpr int vm_wait6(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }  // s_waitcnt vmcnt(n)
 //
 // HI (WAVES = 4): the tile's 8-bit rows ride along as a fifth block of 32 operand rows (h of 16 places, then l; stamp_hi_places),
-// 3 KB more per K step and two MFMAs more per wave and half; their sums, the levels above and the block sums stay in
+// 3 KB more per K step and eight MFMAs more per wave and step; their sums, the levels above and the block sums stay in
 // registers.  A launch and the stream of the weights a second time are saved (figures at stamp_hi_tiles).  Not for WAVES = 8: the
 // matrix pipe has no time to spare there (2048 x 4096 -> 11008 58 us and 17 for the rows' own kernel, 72 in one; 8 x 4096 x 4096 -> 4096
 // 261 and 38, 324).
+constexpr int BN6 = 256;
+constexpr int vm_wait6(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }  // s_waitcnt vmcnt(n)
+
 template <int WAVES, bool HI = false>
 struct Tile6 {
   static constexpr int BMW = 32 * WAVES;                    // rows
@@ -443,9 +444,9 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
     // the reads of the step's weights and of activation block 0 have been issued (by the head of the tile or by the
     // step before).  Block 1 is requested, block 0 multiplied, block 2 requested, block 1 multiplied, ...: the LDS
     // reads of a block fly under the MFMAs of the block before.  After block 2 every read of this stage has
-    // returned: the wave waits for its own loads of the NEXT step's stage (the step after that may still be in
-    // flight), meets the others at the workgroup barrier (next stage visible, this stage free), requests the step
-    // three ahead into this stage, issues the reads of the next step's block 0 and weights, and multiplies block 3
+    // returned: the wave waits for its own loads of the NEXT step's stage (with three stages the step after that may
+    // still be in flight), meets the others at the workgroup barrier (next stage visible, this stage free), requests the
+    // step kNumStage6 ahead into this stage, issues the reads of the next step's block 0 and weights, and multiplies block 3
     // under them.  One barrier per step, none between a read and its use.
     auto step = [&](auto pb_tag) __attribute__((always_inline)) {
       constexpr int pb = decltype(pb_tag)::value;
@@ -581,7 +582,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 || HI ? 1 : 2)) void k_gemm
     // Everything requested so far (the next tile's first steps included) must have landed before the epilogue issues
     // its stores: the counter retires in order, so a later wait for a load would also wait for every store before
     // it.  The epilogue waits for that itself, after its lane swaps (the plain modes: before they start); after it
-    // the next two steps therefore need no wait.
+    // the next kNumStage6 - 1 steps therefore need no wait.
     landed = kNumStage6 - 1;
     // Per-lane values of the epilogue are derived from an opaque copy of the lane number, so that they are
     // computed here, once per tile, instead of being carried in registers across the main loop (which has none

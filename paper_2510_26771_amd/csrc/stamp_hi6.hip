@@ -363,15 +363,17 @@ size_t stamp_hi6_bytes(const stamp_plan* p, int own) {
 }
 
 // Plans that this kernel serves.  Every workgroup reads its rows' and columns' whole depth from L2, so its time goes with
-// the product M N d (about 2.3e14 a second); the tiled int8 kernel shares operands through LDS and splits a tile's depth
+// the product M N d; the tiled int8 kernel shares operands through LDS and splits a tile's depth
 // while it has few tiles: its time hardly grows until its tiles fill the CUs, but it needs a second launch (parts, top levels) or
-// its longer start.  Layers with int8 against FP6, microseconds.  Without transform, all M rows at 8 bits: 512 x 4096 x 4096 40,
+// its longer start.  Layers with int8 against FP6, microseconds, with one strip of columns a workgroup throughout.  Without transform, all M rows at 8 bits: 512 x 4096 x 4096 40,
 // 34, 1024 x 4096 x 4096 48, 57; 8192 x 1536 x 1536 75, 113; 2048 x 2048 x 2048 40, 45; 1024 x 2048 x 2048 36, 27; 4096 x
 // 1024 x 1024 38, 35, 8192: 47, 62; 4096 x 4096 x 512 38, 55.  64 top rows a sequence, top levels: 2048 x 2048 x 4096 212 against 258 at
 // depth 4096, 104 against 126 at depth 1024; 512 x 4096 x 4096 89, 76.  The lines fitted to 1364 such pairs (M 192 .. 16384,
 // depth 192 .. 11008, d_out 16 .. 11008; five kinds of plan): M (d_out + 256) up to 6.5e6, and M (d_out + 768), the larger share of
 // the rows' own operand, up to 8e5 + 8e9 / depth.  That is 0.3 % above always taking the better one on average and 22 % at worst,
-// where a bound of 2e10 on the product is 6 % and 359 % (linear_forward_q of 7820 rows x 2656 x 12 27 us against 38).
+// where a bound of 2e10 on the product is 6 % and 359 % (linear_forward_q of 7820 rows x 2656 x 12 27 us against 38).  With two strips
+// (stamp_hi6_two_strips) 55 pairs around the line, 0.4 to 2.5 times it, are 2.2 % above the better one on average, 15 % at worst (3614 x
+// 9344 -> 150 without transform, 2.0 times the line: 70, 61); 512 x 4096 x 4096 33.  The line stands where it was.
 bool stamp_hi6_fits(const stamp_plan* p, int own) {
   const StampGeom& g = p->geom;
   const int M = hi6_rows(p, own);
@@ -427,7 +429,7 @@ StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6
   hp.KT = p->Kpad / 128;
   hp.nseq = g.B;
   const int gr = 32 * hp.out.np;  // (the rows' own kernel reads whole groups)
-  // A thread converts 32 channels (with some 200 instructions; 1500 when this was measured), and a wave with a few of them takes as long as a full one: narrow layers
+  // A thread converts 32 channels (some 200 instructions), and a wave with a few of them takes as long as a full one: narrow layers
   // have threads for the rows (no top levels: each has one place), or for the places that can hold one, the first of a
   // tile.  Wide ones, where a place is whole waves, have them for all 16, which spreads those with work over more CUs.
   // linear_forward_q, us, all 16 places against these: blocks of 64, 4 x 1024 x 64 -> 1024 18.8, 12.4 (the rows' own kernel 15.3), 8 x

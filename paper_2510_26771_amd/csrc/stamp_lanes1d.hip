@@ -370,9 +370,9 @@ __global__ __launch_bounds__(256) void k_quant_parts(const float* __restrict__ T
 }
 
 // Rows as they are (plans without transform, transformed tokens of the general path): a lane holds 32 channels of one row, a
-// workgroup ROWS neighbouring rows, whose 16-byte pieces of the operand lie side by side.  The first k rows of a sequence are
+// workgroup ROWS rows (unit_of_block: 64 neighbouring ones share an XCD, whose L2 gathers their lines of the operand).  The first k rows of a sequence are
 // 8-bit rows.  Each value is read once.  What bounds it: the launch and its first loads on few rows, memory on many.
-// 2048 rows x 4096 channels fp32 8.3 us (a workgroup per row that reads it twice and stores 8 bytes at a time: 14.2),
+// 2048 rows x 4096 channels fp32 8.6 us (a workgroup per row that reads it twice and stores 8 bytes at a time: 14.2),
 // 262144 x 256 bf16, the whole layer with 256 outputs, 75 (packed codes and a pass that converts them 188).
 template <int ROWS, bool BF16, bool ASYM>
 __global__ __launch_bounds__(1024) void k_lanes_rows(const LaneArgs a, int rows) {
