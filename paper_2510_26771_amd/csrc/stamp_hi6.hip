@@ -434,7 +434,8 @@ StampHi6Pack stamp_hi6_pack(const stamp_plan* p, const int8_t* q_hi, uint8_t* a6
   // tile.  Wide ones, where a place is whole waves, have them for all 16, which spreads those with work over more CUs.
   // linear_forward_q, us, all 16 places against these: blocks of 64, 4 x 1024 x 64 -> 1024 18.8, 12.4 (the rows' own kernel 15.3), 8 x
   // 1024 x 64 -> 256 16.8, 12.8; 16 x 200 x 128 -> 64, blocks of 16 16.5, 13.1.  Full depth, 16 against the 7 that can hold a row:
-  // 8 x 4096 x 1024 -> 256 33.7, 34.6, 4 x 4096 x 2048 -> 512 36.4, 37.3.
+  // 8 x 4096 x 1024 -> 256 33.7, 34.6, 4 x 4096 x 2048 -> 512 36.4, 37.3.  With the present conversion, three layers of one quantized activation, 16 against
+  // these: 4 x 1024 x 64 -> 1024 59.4, 55.3, 8 x 1024 x 64 -> 256 55.8, 56.3, 4 x 1024 x 480 -> 512, full depth 59.6, 60.9, 576 62.2, 63.9.
   const bool narrow = p->Kpad <= 512;
   hp.places = !narrow ? kHiPlaces : ht.L == 0 ? 0 : (1 << ht.lognb) + (ht.L > ht.lognb ? ht.L - ht.lognb : 0);
   const int rows = !ht.on ? (hp.M + gr - 1) / gr * gr : hp.places == 0 ? hp.M : ((g.B * ht.k + (1 << ht.lognb) - 1) >> ht.lognb) * hp.places;
